@@ -2,6 +2,9 @@
 
 Argument marshalling only.  Device buffers are torch CUDA tensors (allocation plumbing); the
 handle object keeps references to every tensor the C library borrows so they outlive it.
+The calls that a training step makes are marshalled by the native module ``_isp_torch``
+(csrc/torch_native.cpp: a small graph's SpMM costs less on the GPU than a ctypes call on the host);
+set-up and inspection go through ctypes.
 """
 from __future__ import annotations
 
@@ -11,6 +14,7 @@ import os
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libisp.so")
 _lib = None
+_nat = None  # the native module, loaded with the library (every CSR object has it)
 
 EXPORTED_SYMBOLS = [
     "isp_csr_build_workspace", "isp_csr_build", "isp_csr_transpose_workspace", "isp_csr_transpose_cached",
@@ -86,6 +90,18 @@ def load_library():
     return lib
 
 
+def _native():
+    """Load the native marshalling module beside the library; raises if it has not been built."""
+    global _nat
+    if _nat is None:
+        load_library()
+        import torch  # noqa: F401  (its libraries come first)
+        from . import _isp_torch
+        _isp_torch.init(_check, csr_transpose_cached)
+        _nat = _isp_torch
+    return _nat
+
+
 def _check(status: int):
     if status != 0:
         raise IspError(status, load_library().isp_last_error().decode())
@@ -95,6 +111,10 @@ def _stream(stream=None):
     import torch
     s = stream if stream is not None else torch.cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
+
+
+def _raw(stream):
+    return None if stream is None else stream.cuda_stream
 
 
 def _dptr(t):
@@ -111,6 +131,7 @@ class CSR:
 
     def __init__(self, handle, n_rows, n_cols, nnz, keep, owner=None):
         self._h = handle
+        self._cell = _native().cell(handle.value or 0, n_rows, n_cols, nnz)  # the handle as the native module sees it
         self.n_rows, self.n_cols, self.nnz = n_rows, n_cols, nnz
         self._keep = keep          # tensors the C side points into
         self._owner = owner        # the source CSR for a cached transpose
@@ -151,10 +172,14 @@ class CSR:
     def destroy(self):
         if self._h is not None and self._owner is None:
             load_library().isp_csr_destroy(self._h)
-        self._h = None
+        self._forget()
         if self._At is not None:
-            self._At._h = None
+            self._At._forget()
         self._keep = None
+
+    def _forget(self):
+        self._h = None
+        _nat.cell_clear(self._cell)
 
     def __del__(self):
         try:
@@ -225,13 +250,11 @@ def csr_build(indptr, indices, values=None, n_cols=None, *, trusted=False, strea
 def csr_transpose_cached(A: CSR, *, stream=None, workspace=None):
     """isp_csr_transpose_cached.  Returns (At, was_cached).
     workspace: optional uint8 CUDA tensor of at least csr_transpose_workspace(A) bytes, used on a cache miss."""
+    if A._At is not None and A._h is not None:  # a cache hit does no device work
+        return A._At, True
     lib = load_library()
     At_h = ctypes.c_void_p()
     was = ctypes.c_int(0)
-    if A._At is not None:
-        _check(lib.isp_csr_transpose_cached(A._h, None, 0, _stream(stream), ctypes.byref(At_h), ctypes.byref(was)))
-        assert At_h.value == A._At._h.value
-        return A._At, bool(was.value)
     need = ctypes.c_size_t()
     _check(lib.isp_csr_transpose_workspace(A._h, ctypes.byref(need)))
     ws = _own_workspace(workspace, need.value, A._keep[0].device)
@@ -270,54 +293,43 @@ def csr_values_changed(A: CSR, *, stream=None):
     _check(load_library().isp_csr_values_changed(A._h, _stream(stream)))
 
 
-def _ld(t):
-    assert t.dim() == 2 and t.stride(1) == 1 and t.is_cuda
-    import torch
-    assert t.dtype == torch.float32
-    return int(t.stride(0)) if t.shape[0] > 1 else max(int(t.stride(0)), int(t.shape[1]))
-
-
 def spmm(A: CSR, X, Y, *, stream=None):
     """isp_spmm: Y = A X (Y is overwritten)."""
-    d = X.shape[1]
-    assert X.shape[0] == A.n_cols and Y.shape == (A.n_rows, d)
-    _check(load_library().isp_spmm(A._h, _dptr(X), _ld(X), d, _dptr(Y), _ld(Y), _stream(stream)))
+    st = _nat.spmm(A._cell, X, Y, _raw(stream))
+    if st:
+        _check(st)
     return Y
 
 
 def spmm_static_scratch(A: CSR, X, Y, *, stream=None):
     """isp_spmm_static_scratch: isp_spmm with the hub-row partial sums in the library's static device array."""
-    d = X.shape[1]
-    assert X.shape[0] == A.n_cols and Y.shape == (A.n_rows, d)
-    _check(load_library().isp_spmm_static_scratch(A._h, _dptr(X), _ld(X), d, _dptr(Y), _ld(Y), _stream(stream)))
+    st = _nat.spmm_static_scratch(A._cell, X, Y, _raw(stream))
+    if st:
+        _check(st)
     return Y
 
 
 def sddmm(A: CSR, U, V, out, *, scale_by_a=False, stream=None):
     """isp_sddmm: out[p] = <U[row(p)], V[col(p)]>."""
-    d = U.shape[1]
-    assert U.shape[0] == A.n_rows and V.shape == (A.n_cols, d) and out.numel() == A.nnz
-    _check(load_library().isp_sddmm(A._h, _dptr(U), _ld(U), _dptr(V), _ld(V), d,
-                                    ISP_SCALE_BY_A if scale_by_a else 0, _dptr(out), _stream(stream)))
+    st = _nat.sddmm(A._cell, U, V, out, ISP_SCALE_BY_A if scale_by_a else 0, _raw(stream))
+    if st:
+        _check(st)
     return out
 
 
 def fusedmm(A: CSR, X, Y, *, op=ISP_OP_SIGMOID, stream=None):
     """isp_fusedmm forward; op is ISP_OP_* or one of 'sigmoid', 'dot', 'one'."""
-    op = EDGE_OPS.get(op, op)
-    d = X.shape[1]
-    assert X.shape[0] == A.n_rows and Y.shape == X.shape
-    _check(load_library().isp_fusedmm(A._h, _dptr(X), _ld(X), d, op, _dptr(Y), _ld(Y), _stream(stream)))
+    st = _nat.fusedmm(A._cell, X, Y, EDGE_OPS.get(op, op), _raw(stream))
+    if st:
+        _check(st)
     return Y
 
 
 def fusedmm_backward(A: CSR, X, dY, dX, *, op=ISP_OP_SIGMOID, stream=None):
     """isp_fusedmm_backward (needs csr_transpose_cached(A) first)."""
-    op = EDGE_OPS.get(op, op)
-    d = X.shape[1]
-    assert dY.shape == X.shape and dX.shape == X.shape
-    _check(load_library().isp_fusedmm_backward(A._h, _dptr(X), _ld(X), _dptr(dY), _ld(dY), d, op, _dptr(dX),
-                                               _ld(dX), _stream(stream)))
+    st = _nat.fusedmm_backward(A._cell, X, dY, dX, EDGE_OPS.get(op, op), _raw(stream))
+    if st:
+        _check(st)
     return dX
 
 
@@ -326,20 +338,15 @@ REDUCE = {"sum": 0, "mean": 1, "min": 2, "max": 3}
 
 def spmm_reduce(A: CSR, X, Y, reduce: str, arg=None, *, stream=None):
     """isp_spmm_reduce: reduce in 'sum' | 'mean' | 'min' | 'max'; arg (int32 [n_rows, d], contiguous) for min / max."""
-    import torch
-    d = X.shape[1]
-    assert X.shape[0] == A.n_cols and Y.shape == (A.n_rows, d)
-    if arg is not None:
-        assert arg.dtype == torch.int32 and arg.is_contiguous() and arg.shape == (A.n_rows, d)
-    _check(load_library().isp_spmm_reduce(A._h, _dptr(X), _ld(X), d, REDUCE[reduce], _dptr(Y), _ld(Y), _dptr(arg),
-                                          _stream(stream)))
+    st = _nat.spmm_reduce(A._cell, X, Y, REDUCE[reduce], arg, _raw(stream))
+    if st:
+        _check(st)
     return Y
 
 
 def spmm_reduce_backward(A: CSR, dY, dX, reduce: str, arg=None, *, stream=None):
     """isp_spmm_reduce_backward (needs csr_transpose_cached(A) first)."""
-    d = dY.shape[1]
-    assert dY.shape[0] == A.n_rows and dX.shape == (A.n_cols, d)
-    _check(load_library().isp_spmm_reduce_backward(A._h, _dptr(dY), _ld(dY), d, REDUCE[reduce], _dptr(arg),
-                                                   _dptr(dX), _ld(dX), _stream(stream)))
+    st = _nat.spmm_reduce_backward(A._cell, dY, dX, REDUCE[reduce], arg, _raw(stream))
+    if st:
+        _check(st)
     return dX

@@ -1,4 +1,4 @@
-"""Compile the HIP sources under csrc/ into libisp.so for gfx950 (hipcc, in-tree)."""
+"""Compile the HIP sources under csrc/ into libisp.so for gfx950 (hipcc, in-tree), and the binding's native module."""
 from __future__ import annotations
 
 import os
@@ -52,7 +52,26 @@ def build(verbose: bool = False) -> str:
     if res.returncode != 0:
         raise RuntimeError("hipcc failed on abi_example.cpp:\n" + res.stdout)
     os.replace(example + ".tmp", example)
+    build_native(verbose)
     return LIB
+
+
+def build_native(verbose: bool = False) -> str:
+    """The binding's native module (host code only: tensors to pointers, autograd nodes) against torch's headers."""
+    import sysconfig
+    import torch
+    t = os.path.dirname(torch.__file__)
+    out = os.path.join(HERE, "_isp_torch.so")
+    cxx11 = int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+          "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % cxx11,
+          "-I" + os.path.join(ROOT, "include"), "-isystem", os.path.join(t, "include"),
+          "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+          "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "torch_native.cpp"), "-o", out + ".tmp",
+          "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python",
+          "-L" + HERE, "-lisp", "-Wl,-rpath,$ORIGIN"], verbose)
+    os.replace(out + ".tmp", out)
+    return out
 
 
 if __name__ == "__main__":
