@@ -170,7 +170,7 @@ isp_status run_pass(const isp_csr* A, const typename P::args& pa, int d, float* 
   return ISP_OK;
 }
 
-// ---- grouped fast path (d % 4 == 0, 16-byte aligned operands) -----------------------------------
+// ---- grouped fast path (4 <= d <= 256, any alignment) -----------------------------------
 struct g_args1 { const float* src[1]; int64_t lds_[1]; const float* rowop[1]; int64_t ldr[1]; float* out_entry; int op; };
 struct g_args12 { const float* src[1]; int64_t lds_[1]; const float* rowop[2]; int64_t ldr[2]; float* out_entry; int op; };
 struct g_args21 { const float* src[2]; int64_t lds_[2]; const float* rowop[1]; int64_t ldr[1]; float* out_entry; int op; };
@@ -180,11 +180,11 @@ struct g_fwd {  // gathered x_j, row operand x_i
   static constexpr int NSRC = 1, NROW = 1, STEPS = 4;
   static constexpr bool PER_ENTRY = false, ACCUMULATE = false;
   using args = g_args1;
-  template <int LPG, int W>
+  template <int LPG, int W, bool TAIL>
   __device__ static inline void edge(const args&, float a, const float (&x)[1][W], const float (&r)[1][W],
-                                     float (&acc)[W], const lane_cols<W / 4>& lc, bool live) {
+                                     float (&acc)[W], const lane_cols<W / 4, TAIL>& lc, bool live) {
     float sg = 1.f, dsg = 0.f;
-    if (OP != ISP_OP_ONE) edge_fn(OP, group_allreduce<LPG>(dotw<W>(r[0], x[0], lc)), sg, dsg);
+    if (OP != ISP_OP_ONE) edge_fn(OP, group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc)), sg, dsg);
     const float w = a * sg;
     if (live) {
 #pragma unroll
@@ -198,12 +198,12 @@ struct g_bwd_row {  // gathered x_j, row operands x_i and g_i:  dX_i += dz x_j
   static constexpr int NSRC = 1, NROW = 2, STEPS = 3;  // (three operand rows per step: three steps per buffer keep four waves resident)
   static constexpr bool PER_ENTRY = false, ACCUMULATE = false;
   using args = g_args12;
-  template <int LPG, int W>
+  template <int LPG, int W, bool TAIL>
   __device__ static inline void edge(const args&, float a, const float (&x)[1][W], const float (&r)[2][W],
-                                     float (&acc)[W], const lane_cols<W / 4>& lc, bool live) {
+                                     float (&acc)[W], const lane_cols<W / 4, TAIL>& lc, bool live) {
     if (OP == ISP_OP_ONE) return;  // s does not depend on x_i: nothing flows through z
-    const float z = group_allreduce<LPG>(dotw<W>(r[0], x[0], lc));
-    const float gd = group_allreduce<LPG>(dotw<W>(r[1], x[0], lc));
+    const float z = group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc));
+    const float gd = group_allreduce<LPG>(dotw<W, TAIL>(r[1], x[0], lc));
     float sg, dsg;
     edge_fn(OP, z, sg, dsg);
     const float dz = a * gd * dsg;
@@ -219,13 +219,13 @@ struct g_bwd_col {  // over A^T: gathered x_i and g_i, row operand x_j:  dX_j +=
   static constexpr int NSRC = 2, NROW = 1, STEPS = 3;
   static constexpr bool PER_ENTRY = false, ACCUMULATE = true;
   using args = g_args21;
-  template <int LPG, int W>
+  template <int LPG, int W, bool TAIL>
   __device__ static inline void edge(const args&, float a, const float (&x)[2][W], const float (&r)[1][W],
-                                     float (&acc)[W], const lane_cols<W / 4>& lc, bool live) {
+                                     float (&acc)[W], const lane_cols<W / 4, TAIL>& lc, bool live) {
     float sg = 1.f, dsg = 0.f, gd = 0.f;
     if (OP != ISP_OP_ONE) {
-      edge_fn(OP, group_allreduce<LPG>(dotw<W>(r[0], x[0], lc)), sg, dsg);
-      gd = group_allreduce<LPG>(dotw<W>(r[0], x[1], lc));
+      edge_fn(OP, group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc)), sg, dsg);
+      gd = group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[1], lc));
     }
     const float w = a * sg;
     const float dz = a * gd * dsg;
@@ -249,14 +249,14 @@ struct g_bwd_mirror {  // gathered x_j and g_j, row operands x_i and g_i
   static constexpr int NSRC = 2, NROW = 2, STEPS = 2;
   static constexpr bool PER_ENTRY = false, ACCUMULATE = false, HAS_VAL2 = true;
   using args = g_args22;
-  template <int LPG, int W>
+  template <int LPG, int W, bool TAIL>
   __device__ static inline void edge(const args&, float a, float at, const float (&x)[2][W], const float (&r)[2][W],
-                                     float (&acc)[W], const lane_cols<W / 4>& lc, bool live) {
+                                     float (&acc)[W], const lane_cols<W / 4, TAIL>& lc, bool live) {
     float sg = 1.f, dsg = 0.f, gd_ij = 0.f, gd_ji = 0.f;
     if (OP != ISP_OP_ONE) {
-      edge_fn(OP, group_allreduce<LPG>(dotw<W>(r[0], x[0], lc)), sg, dsg);
-      gd_ij = group_allreduce<LPG>(dotw<W>(r[1], x[0], lc));  // <g_i, x_j>
-      gd_ji = group_allreduce<LPG>(dotw<W>(x[1], r[0], lc));  // <g_j, x_i>
+      edge_fn(OP, group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc)), sg, dsg);
+      gd_ij = group_allreduce<LPG>(dotw<W, TAIL>(r[1], x[0], lc));  // <g_i, x_j>
+      gd_ji = group_allreduce<LPG>(dotw<W, TAIL>(x[1], r[0], lc));  // <g_j, x_i>
     }
     const float w = at * sg;
     const float dz = (a * gd_ij + at * gd_ji) * dsg;
@@ -267,13 +267,13 @@ struct g_bwd_mirror {  // gathered x_j and g_j, row operands x_i and g_i
   }
 };
 
-template <class P, int LPG, int W, bool ADDR32>
+template <class P, int LPG, int W, bool ADDR32, bool TAIL>
 __global__ void __launch_bounds__(ISP_WG) k_fused_grouped(isp_view A, const int64_t* __restrict__ indptr,
                                                           const int32_t* __restrict__ indices,
                                                           const float* __restrict__ values, typename P::args pa, int d,
                                                           float* __restrict__ Y, int64_t ldy) {
   __shared__ gs_lds lds;
-  fused_grouped_item<P, LPG, W, ADDR32>(A, indptr, indices, values, pa, d, Y, ldy, lds);
+  fused_grouped_item<P, LPG, W, ADDR32, TAIL>(A, indptr, indices, values, pa, d, Y, ldy, lds);
 }
 
 // LPG lanes with W floats each span the feature width: W * LPG >= d.
@@ -285,8 +285,10 @@ isp_status run_grouped(const isp_csr* A, const typename P::args& pa, int d, floa
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
     bool a32 = true;
     for (int k = 0; k < P::NSRC; ++k) a32 = a32 && fused_offsets_fit_32(v.n_cols, pa.lds_[k], d);
-    if (a32) k_fused_grouped<P, LPG, W, true><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, pa, d, Y, ldy);
-    else k_fused_grouped<P, LPG, W, false><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, pa, d, Y, ldy);
+#define ISP_GO(A32, TL) k_fused_grouped<P, LPG, W, A32, TL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, pa, d, Y, ldy)
+    if (d % 4) { if (a32) ISP_GO(true, true); else ISP_GO(false, true); }
+    else { if (a32) ISP_GO(true, false); else ISP_GO(false, false); }
+#undef ISP_GO
     ISP_LAUNCH_CHECK();
   }
   if (v.n_hub > 0) {
@@ -359,7 +361,7 @@ isp_status isp_fusedmm_launch(const isp_csr* A, const float* X, int64_t ldx, int
                               int64_t ldy, hipStream_t s) {
   const bool ok4 = ldx % 4 == 0 && ldy % 4 == 0 && aligned(X, 16) && aligned(Y, 16);
   const bool ok2 = ldx % 2 == 0 && ldy % 2 == 0 && aligned(X, 8) && aligned(Y, 8);
-  if (ok4 && d % 4 == 0 && d <= ISP_PARTIAL_TILE && grouped_partition_ok(A)) {
+  if (d >= 4 && d <= ISP_PARTIAL_TILE && grouped_partition_ok(A)) {
     g_args1 pa{{X}, {ldx}, {X}, {ldx}, nullptr, op};
     if (op == ISP_OP_SIGMOID) return run_grouped_d<g_fwd<ISP_OP_SIGMOID>>(A, pa, d, Y, ldy, s);
     if (op == ISP_OP_DOT) return run_grouped_d<g_fwd<ISP_OP_DOT>>(A, pa, d, Y, ldy, s);
@@ -410,14 +412,14 @@ isp_status isp_fusedmm_bwd_launch(const isp_csr* A, const float* X, int64_t ldx,
                                   int32_t d, int op, float* dX, int64_t lddx, hipStream_t s) {
   const bool ok4 = ldx % 4 == 0 && ldg % 4 == 0 && lddx % 4 == 0 && aligned(X, 16) && aligned(G, 16) && aligned(dX, 16);
   const bool ok2 = ldx % 2 == 0 && ldg % 2 == 0 && lddx % 2 == 0 && aligned(X, 8) && aligned(G, 8) && aligned(dX, 8);
-  if (ok4 && d % 4 == 0 && d <= ISP_PARTIAL_TILE && grouped_partition_ok(A) && A->mirror_aligned && !A->tune.no_mirror) {
+  if (d >= 4 && d <= ISP_PARTIAL_TILE && grouped_partition_ok(A) && A->mirror_aligned && !A->tune.no_mirror) {
     // symmetric pattern: one pass over A serves both sums (the mirrored entries' values are A^T's)
     g_args22 pm{{X, G}, {ldx, ldg}, {X, G}, {ldx, ldg}, nullptr, op, A->At->v.values};
     if (op == ISP_OP_SIGMOID) return run_grouped_d<g_bwd_mirror<ISP_OP_SIGMOID>>(A, pm, d, dX, lddx, s);
     if (op == ISP_OP_DOT) return run_grouped_d<g_bwd_mirror<ISP_OP_DOT>>(A, pm, d, dX, lddx, s);
     return run_grouped_d<g_bwd_mirror<ISP_OP_ONE>>(A, pm, d, dX, lddx, s);
   }
-  if (ok4 && d % 4 == 0 && d <= ISP_PARTIAL_TILE && grouped_partition_ok(A) && grouped_partition_ok(A->At)) {
+  if (d >= 4 && d <= ISP_PARTIAL_TILE && grouped_partition_ok(A) && grouped_partition_ok(A->At)) {
     g_args12 p1{{X}, {ldx}, {X, G}, {ldx, ldg}, nullptr, op};
     g_args21 p2{{X, G}, {ldx, ldg}, {X}, {ldx}, nullptr, op};
     isp_status st1;

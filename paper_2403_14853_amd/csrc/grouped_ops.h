@@ -26,11 +26,14 @@ namespace isp_dev {
 // scalar base pointer instead of a 64-bit multiply (three quarter-rate instructions).
 // values may be null (every stored value is 1).
 // A lane's float4 vectors: whether each lies inside the feature width, and its first column (0 when it does not,
-// so that the lane still reads valid memory).
-template <int NV>
+// so that the lane still reads valid memory).  TAIL (a width that is no multiple of 4): the last vector of a row
+// moves back to end with the last column; dup = how many of its leading columns belong to the vector before it
+// and must not be counted twice in a dot product.
+template <int NV, bool TAIL>
 struct lane_cols {
   bool on[NV];
   int off[NV];
+  int dup[NV];
 };
 
 template <class P, class = void>
@@ -43,7 +46,7 @@ struct policy_sparse_rows : std::bool_constant<!P::PER_ENTRY> {};
 template <class P>
 struct policy_sparse_rows<P, std::void_t<decltype(P::SPARSE_ROWS)>> : std::bool_constant<P::SPARSE_ROWS> {};
 
-template <class P, int LPG, int W, bool ADDR32>
+template <class P, int LPG, int W, bool ADDR32, bool TAIL>
 __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __restrict__ indptr,
                                           const int32_t* __restrict__ indices, const float* __restrict__ values,
                                           const typename P::args& pa, int d, float* __restrict__ Y, int64_t ldy,
@@ -76,12 +79,13 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
                              : gs_prepare<G, false, sparse_rows, PAD>(it, indptr, indices, values, L, lane, &n_live);
 
   const int g = lane / LPG, q = lane % LPG;
-  lane_cols<NV> lc;  // this lane's columns: in range?  offset of the first (0 when out of range)
+  lane_cols<NV, TAIL> lc;  // this lane's columns: in range?  offset of the first (0 when out of range)
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const int col = k_lo + v * 4 * LPG + q * 4;
     lc.on[v] = col < d;
-    lc.off[v] = lc.on[v] ? col : 0;
+    lc.off[v] = lc.on[v] ? (TAIL && col + 4 > d ? d - 4 : col) : 0;
+    lc.dup[v] = TAIL && lc.on[v] ? col - lc.off[v] : 0;
   }
   unsigned src_pitch[NSRC];  // row pitches of the gathered operands in bytes (ADDR32)
 #pragma unroll
@@ -216,11 +220,11 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
         if constexpr (P::PER_ENTRY) {
           // one output per stored entry, parked in the entry's LDS slot (its value has been read by
           // the step's issue) and written out in one coalesced sweep when the item is done
-          const float val = P::template entry<LPG, W>(a[u], x[u], rr, lc);
+          const float val = P::template entry<LPG, W, TAIL>(a[u], x[u], rr, lc);
           if (live && q == 0) L.ent[gs_off(dsc[u]) + g].y = __float_as_int(val);
         } else {
-          if constexpr (policy_has_val2<P>::value) P::template edge<LPG, W>(pa, a[u], a2[u], x[u], rr, acc, lc, live);
-          else P::template edge<LPG, W>(pa, a[u], x[u], rr, acc, lc, live);
+          if constexpr (policy_has_val2<P>::value) P::template edge<LPG, W, TAIL>(pa, a[u], a2[u], x[u], rr, acc, lc, live);
+          else P::template edge<LPG, W, TAIL>(pa, a[u], x[u], rr, acc, lc, live);
           if (dsc[u] & GS_LAST) finish_row();
         }
       }
@@ -285,14 +289,23 @@ inline bool fused_offsets_fit_32(int64_t n_cols, int64_t ld, int d) {
          ((uint64_t)n_cols * (uint64_t)ld + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
 }
 
-// Partial dot product of a lane's columns; vectors whose columns lie past d contribute zero.
-template <int W>
-__device__ inline float dotw(const float (&a)[W], const float (&b)[W], const lane_cols<W / 4>& lc) {
+// Partial dot product of a lane's columns; vectors whose columns lie past d contribute zero, and so do the leading
+// columns that a moved-back vector shares with its neighbour (three selects a vector, in the TAIL kernels only).
+template <int W, bool TAIL>
+__device__ inline float dotw(const float (&a)[W], const float (&b)[W], const lane_cols<W / 4, TAIL>& lc) {
   float s = 0.f;
 #pragma unroll
   for (int v = 0; v < W / 4; ++v) {
-    const float p = fmaf(a[4 * v + 3], b[4 * v + 3], fmaf(a[4 * v + 2], b[4 * v + 2], fmaf(a[4 * v + 1], b[4 * v + 1], a[4 * v] * b[4 * v])));
-    s += lc.on[v] ? p : 0.f;
+    if constexpr (TAIL) {
+      float p = a[4 * v + 3] * b[4 * v + 3];
+      p = lc.dup[v] < 3 ? fmaf(a[4 * v + 2], b[4 * v + 2], p) : p;
+      p = lc.dup[v] < 2 ? fmaf(a[4 * v + 1], b[4 * v + 1], p) : p;
+      p = lc.dup[v] < 1 ? fmaf(a[4 * v], b[4 * v], p) : p;
+      s += lc.on[v] ? p : 0.f;
+    } else {
+      const float p = fmaf(a[4 * v + 3], b[4 * v + 3], fmaf(a[4 * v + 2], b[4 * v + 2], fmaf(a[4 * v + 1], b[4 * v + 1], a[4 * v] * b[4 * v])));
+      s += lc.on[v] ? p : 0.f;
+    }
   }
   return s;
 }

@@ -15,10 +15,20 @@
 
 namespace isp_dev {
 
+// Vectors of floats at any 4-byte aligned address: one global_load / global_store_dwordx2 / x4 all the same (the
+// hardware takes 4-byte aligned vector accesses in global memory; a row that does not start on a line costs the
+// extra line it touches, nothing else).
 template <int VEC> struct vec_of;
 template <> struct vec_of<1> { using type = float; };
-template <> struct vec_of<2> { using type = float2; };
-template <> struct vec_of<4> { using type = float4; };
+template <> struct vec_of<2> { typedef float type __attribute__((ext_vector_type(2), aligned(4))); };
+template <> struct vec_of<4> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+
+// First column (relative to the first of the `width` columns of a launch) of the lane that would start at rel:
+// where the width is no multiple of VEC the last lane moves back so that it ends with the last column.  The
+// columns it shares with its neighbour come out of the same operations in the same order in both lanes, so both
+// store the same bits.  Needs width >= VEC; negative rel does not occur.
+template <int VEC>
+__device__ inline int tail_col(int rel, int width) { return rel + VEC <= width ? rel : width - VEC; }
 
 template <int VEC>
 __device__ inline void load_vec(const float* __restrict__ p, float (&o)[VEC]) {
@@ -307,8 +317,9 @@ __device__ inline void hub_fixup(const isp_view& A, int d, int k0, float* __rest
   const int row = A.hub_rows[h];
 #pragma unroll
   for (int tt = 0; tt < T; ++tt) {
-    const int rel = (tt * ISP_WAVE + lane) * VEC;
+    int rel = (tt * ISP_WAVE + lane) * VEC;
     if (k0 + rel >= d) continue;
+    rel = tail_col<VEC>(rel, d - k0);
     float acc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
@@ -357,10 +368,11 @@ __device__ inline void hub_fixup_wg(const isp_view& A, int d, int k0, float* __r
   float acc[T][VEC];
 #pragma unroll
   for (int tt = 0; tt < T; ++tt) {
-    const int rel = (tt * ISP_WAVE + lane) * VEC;
+    int rel = (tt * ISP_WAVE + lane) * VEC;
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[tt][v] = 0.f;
     if (k0 + rel >= d) continue;
+    rel = tail_col<VEC>(rel, d - k0);
     int s = a;
     for (; s + 8 <= b; s += 8) {  // eight partial rows in flight, added in segment order
       float t[8][VEC];
@@ -399,8 +411,9 @@ __device__ inline void hub_fixup_wg(const isp_view& A, int d, int k0, float* __r
   const float inv = MEAN ? A.inv_len[row] : 1.f;  // (= 1.f / (float)length, as the row blocks compute it)
 #pragma unroll
   for (int tt = 0; tt < T; ++tt) {
-    const int rel = (tt * ISP_WAVE + lane) * VEC;
+    int rel = (tt * ISP_WAVE + lane) * VEC;
     if (k0 + rel >= d) continue;
+    rel = tail_col<VEC>(rel, d - k0);
     if (MEAN) {
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[tt][v] *= inv;

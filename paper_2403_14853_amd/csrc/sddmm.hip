@@ -89,7 +89,7 @@ __global__ void __launch_bounds__(ISP_WG) k_sddmm(isp_view A, const int64_t* __r
   }
 }
 
-// ---- grouped fast path (d % 4 == 0, 16-byte aligned operands) ------------------------------------
+// ---- grouped fast path (d >= 4, any alignment) ------------------------------------
 // ADD: this pass covers a window of the feature columns and adds its partial dot product to out.
 // The entry's staged value multiplies the dot product; it is 1 when the kernel is given no values
 // (unscaled SDDMM, or a matrix without stored values).
@@ -99,19 +99,19 @@ struct sddmm_policy {
   static constexpr int NSRC = 1, NROW = 1, STEPS = 4;
   static constexpr bool PER_ENTRY = true, ACCUMULATE = false, ADD = ADD_, SPARSE_ROWS = SPARSE_;
   struct args { const float* src[1]; int64_t lds_[1]; const float* rowop[1]; int64_t ldr[1]; float* out_entry; };
-  template <int LPG, int W>
-  __device__ static inline float entry(float a, const float (&x)[1][W], const float (&r)[1][W], const lane_cols<W / 4>& lc) {
-    return a * group_allreduce<LPG>(dotw<W>(r[0], x[0], lc));
+  template <int LPG, int W, bool TAIL>
+  __device__ static inline float entry(float a, const float (&x)[1][W], const float (&r)[1][W], const lane_cols<W / 4, TAIL>& lc) {
+    return a * group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc));
   }
 };
 
-template <int LPG, int W, bool ADDR32, bool ADD, bool SPARSE>
+template <int LPG, int W, bool ADDR32, bool ADD, bool SPARSE, bool TAIL>
 __global__ void __launch_bounds__(ISP_WG) k_sddmm_grouped(isp_view A, const int64_t* __restrict__ indptr,
                                                           const int32_t* __restrict__ indices,
                                                           const float* __restrict__ values,
                                                           typename sddmm_policy<ADD, SPARSE>::args pa, int d, int k_lo) {
   __shared__ gs_lds lds;
-  fused_grouped_item<sddmm_policy<ADD, SPARSE>, LPG, W, ADDR32>(A, indptr, indices, values, pa, d, nullptr, 0, lds, k_lo);
+  fused_grouped_item<sddmm_policy<ADD, SPARSE>, LPG, W, ADDR32, TAIL>(A, indptr, indices, values, pa, d, nullptr, 0, lds, k_lo);
 }
 
 // One pass over the feature columns [k_lo, d_hi) (d_hi - k_lo <= W * LPG); add: accumulate into out.
@@ -128,10 +128,12 @@ isp_status launch_grouped(const isp_csr* A, const float* U, int64_t ldu, const f
   // rows without entries: skipped through the list of non-empty rows when they are an eighth of all rows or more
   // (the list costs one LDS read per step, an empty row's step a whole step)
   const bool sparse = A->info.bin_rows[0] * 8 >= A->info.n_rows;
+  const bool tail = (d_hi - k_lo) % 4 != 0;
 #define ISP_GO(A32, AD, SP)                                                                                  \
   do {                                                                                                       \
     typename sddmm_policy<AD, SP>::args pb{{pa.src[0]}, {pa.lds_[0]}, {pa.rowop[0]}, {pa.ldr[0]}, pa.out_entry}; \
-    k_sddmm_grouped<LPG, W, A32, AD, SP><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, pb, d_hi, k_lo); \
+    if (tail) k_sddmm_grouped<LPG, W, A32, AD, SP, true><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, pb, d_hi, k_lo); \
+    else k_sddmm_grouped<LPG, W, A32, AD, SP, false><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, pb, d_hi, k_lo); \
   } while (0)
 #define ISP_GO2(A32, AD) do { if (sparse) ISP_GO(A32, AD, true); else ISP_GO(A32, AD, false); } while (0)
   if (a32) { if (add) ISP_GO2(true, true); else ISP_GO2(true, false); }
@@ -166,8 +168,7 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const float* V, int64_t ldv, int32_t d,
                             bool scale, float* out, hipStream_t s) {
   const isp_view& av = A->v;
-  const bool grouped_ok = d % 4 == 0 && ldu % 4 == 0 && ldv % 4 == 0 && aligned(U, 16) &&
-                          aligned(V, 16) && A->info.block_cost <= GS_MAX_ROWS &&
+  const bool grouped_ok = d >= 4 && A->info.block_cost <= GS_MAX_ROWS &&
                           A->info.block_cost + av.hub_t <= GS_MAX_ENT && av.seg_len <= GS_MAX_ENT &&
                           !A->tune.no_grouped;
   if (grouped_ok) {
@@ -184,9 +185,12 @@ isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const
     else if (big && d > 2 * ISP_WAVE) wp = 2 * ISP_WAVE;
     else if (d > ISP_PARTIAL_TILE) wp = ISP_PARTIAL_TILE;
     isp_status st = ISP_OK;
-    for (int k_lo = 0; k_lo < d && st == ISP_OK; k_lo += wp) {
-      const int k_hi = k_lo + wp < d ? k_lo + wp : d, w = k_hi - k_lo;
+    for (int k_lo = 0, k_next; k_lo < d && st == ISP_OK; k_lo = k_next) {
+      int k_hi = k_lo + wp < d ? k_lo + wp : d;
+      if (k_hi < d && d - k_hi < 4) k_hi = d - 4;  // (no window narrower than a float4 lane)
+      const int w = k_hi - k_lo;
       const bool add = k_lo > 0;
+      k_next = k_hi;
       // one float4 per lane up to 64 columns, two above (half the lanes per dot product: fewer instructions per
       // entry where a step's eight-plus entries are mostly live; measured on the benchmark graphs);
       // ISP_FUSED_W=4 / 8 forces either
