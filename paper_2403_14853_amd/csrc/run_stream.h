@@ -1,0 +1,211 @@
+// Run-streaming skeleton (gfx950, wave64): the fast path of SpMM and of the min / max reductions.
+//
+// A wavefront owns one work item (a block of whole short rows, a block of row pieces, or one hub-row segment) whose
+// nonzeros are contiguous in the CSR arrays.  The 64 lanes form G = 64 / LPG groups; a group gathers one dense row
+// slice of VEC * LPG floats with one load, so one instruction serves G nonzeros.  The item's (column, value) pairs
+// are staged in LDS, and every group then streams a CONTIGUOUS RUN of about n / G of them: it adds up one row after
+// the other and stores a row when it has met its last entry, so
+//  - every step serves G entries, wherever rows begin and end (sharing out each row's entries over the groups left
+//    half of the lanes idle on rows of a few entries);
+//  - a finished row costs its store, not a reduction over the groups; only the at most G rows that a run boundary
+//    cuts are put together at the end, the parts in order (deterministic, no atomics);
+//  - the item needs no table of steps: one ballot per 64 rows ranks the non-empty ones, one per group finds the row
+//    that its run starts in.
+// Empty rows own nothing in the runs; their outputs are written up front.
+#pragma once
+#include <limits.h>
+#include <utility>
+#include "group_stream.h"
+
+namespace isp_dev {
+
+constexpr int RN_PAD = 16;          // spare entries behind the item's last (steps of the last round may read there)
+constexpr int RN_CHUNK = 2;         // entries read from LDS at a time
+
+struct __attribute__((aligned(16))) rn_wave_lds {
+  int2 ent[GS_MAX_ENT + RN_PAD];   // (column, value bits); afterwards the runs' unfinished sums
+  int dst[GS_MAX_ROWS + 8];        // output row of each non-empty row, in order; from the top down: the empty rows
+  gs_u16 end[GS_MAX_ROWS + 8];     // where each non-empty row ends, relative to the item
+};
+struct rn_lds { rn_wave_lds w[ISP_WAVES_PER_WG]; };
+
+// This lane's group's run, and the item's shape.
+struct rn_run {
+  int start, cnt;   // entries [start, start + cnt) of the item
+  int k;            // index into dst of the row its first entry belongs to
+  bool mid;         // the run starts inside a row: that row's sum begins in an earlier run
+  int full, steps;  // steps in which every group has an entry; steps in which any has (wave-uniform)
+  int n_empty;      // empty rows, listed at dst[RN_EMPTY0 - i]
+};
+constexpr int RN_EMPTY0 = GS_MAX_ROWS + 7;
+
+// Stage the item and find the groups' runs.  slot_of: for blocks of pieces, the partial row of piece `row`
+// (else NULL).
+template <int G, bool HAS_VAL>
+__device__ inline rn_run rn_prepare(const item_range& it, const int64_t* __restrict__ indptr,
+                                    const int32_t* __restrict__ indices, const float* __restrict__ values,
+                                    const int32_t* __restrict__ slot_of, rn_wave_lds& L, int lane) {
+  const int n_ent = (int)(it.p_end - it.p);
+  const int n_rows = it.is_seg ? 0 : it.row_last - it.row;
+  // the first 64 rows' offsets are requested before the entries: both are on their way together
+  int a0 = 0, b0 = 0, d0 = it.row + lane;
+  if (lane < n_rows) {
+    a0 = (int)(indptr[it.row + lane] - it.p);
+    b0 = (int)(indptr[it.row + lane + 1] - it.p);
+    if (slot_of) d0 = slot_of[it.row + lane];
+  }
+  constexpr int SB = 8;  // loads in flight per lane
+  for (int base = 0; base < n_ent; base += SB * ISP_WAVE) {
+    int c[SB];
+    float v[SB];
+#pragma unroll
+    for (int u = 0; u < SB; ++u) {
+      const int i = base + u * ISP_WAVE + lane;
+      c[u] = 0;
+      v[u] = 1.f;
+      if (i < n_ent) {
+        c[u] = __builtin_nontemporal_load(indices + it.p + i);
+        if (HAS_VAL) v[u] = __builtin_nontemporal_load(values + it.p + i);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < SB; ++u) {
+      const int i = base + u * ISP_WAVE + lane;
+      if (i < n_ent) L.ent[i] = make_int2(c[u], __float_as_int(v[u]));
+    }
+  }
+  if (lane < RN_PAD) L.ent[n_ent + lane] = make_int2(0, 0);
+
+  const int g = lane / (ISP_WAVE / G);
+  const int q = n_ent / G, rest = n_ent - q * G;
+  rn_run R;
+  R.start = g * q + (g < rest ? g : rest);
+  R.cnt = q + (g < rest ? 1 : 0);
+  R.full = q;
+  R.steps = q + (rest > 0 ? 1 : 0);
+  R.k = 0;
+  R.mid = it.is_seg;
+  R.n_empty = 0;
+  int live = 0;
+  for (int base = 0; base < n_rows; base += ISP_WAVE) {
+    const int r = base + lane;
+    int a = a0, b = b0, dst = d0;
+    if (base > 0) {
+      a = b = 0;
+      dst = it.row + r;
+      if (r < n_rows) {
+        a = (int)(indptr[it.row + r] - it.p);
+        b = (int)(indptr[it.row + r + 1] - it.p);
+        if (slot_of) dst = slot_of[it.row + r];
+      }
+    }
+    const bool on = b > a;
+    const unsigned long long m = __ballot(on);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    if (on) {
+      const int rank = live + __popcll(m & below);
+      L.dst[rank] = dst;
+      L.end[rank] = (gs_u16)b;
+    }
+    const unsigned long long me = __ballot(r < n_rows && !on);
+    if (r < n_rows && !on) L.dst[RN_EMPTY0 - R.n_empty - __popcll(me & below)] = dst;
+    R.n_empty += __popcll(me);
+    const int bb = on ? b : INT_MAX;
+#pragma unroll
+    for (int j = 1; j < G; ++j) {  // rows that end before run j starts
+      const int before = __popcll(__ballot(bb <= j * q + (j < rest ? j : rest)));
+      R.k += g == j ? before : 0;
+    }
+    live += __popcll(m);
+  }
+  if (lane < 2) {  // (read ahead: a row that never ends)
+    L.dst[live + lane] = 0;
+    L.end[live + lane] = 0xffff;
+  }
+  wave_lds_sync();
+  // (the last row to end before the run's first entry ends right there, or the run starts inside a row)
+  if (!it.is_seg && R.cnt > 0) R.mid = R.k > 0 ? (int)L.end[R.k - 1] != R.start : R.start > 0;
+  return R;
+}
+
+// f(0) ... f(N - 1) with the index as a compile-time constant (ring slots live in registers).
+template <class F, int... U>
+__device__ __forceinline__ void rn_for_each(F&& f, std::integer_sequence<int, U...>) { (f(std::integral_constant<int, U>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void rn_for(F&& f) { rn_for_each(f, std::make_integer_sequence<int, N>{}); }
+
+// Stream the runs.  load(u, col): request the gather of ring slot u;  add(u, a, s): take slot u's row into the
+// running result, a the entry's value, s its number in the run;  end_row(k, row): the k-th non-empty row is complete in this lane's group,
+// its output row is `row` (called by the lanes it concerns only).  RING gathers are in flight per lane.
+// A round of RING steps is consumed while the next one is requested, slot by slot, into the same registers; the
+// entries are read from LDS RN_CHUNK steps before they are needed.  A row's end is the step number at which it
+// ends, kept per lane: one comparison a step.
+template <int RING, class Load, class Add, class End>
+__device__ __forceinline__ void rn_stream(const rn_wave_lds& L, const rn_run& R, Load&& load, Add&& add, End&& end_row) {
+  static_assert(RING % (2 * RN_CHUNK) == 0 && 2 * RN_CHUNK <= RN_PAD, "fetches alternate between two buffers");
+  const int2* __restrict__ ep = L.ent + R.start;
+  constexpr int C = RN_CHUNK;
+  float a[RING];
+  int2 e[2][C];  // entries to request next, and the ones after them
+  int k = R.k;
+  int row = L.dst[k], row_next = L.dst[k + 1];  // read one row ahead: a store does not wait for the list
+  const int start1 = R.start + 1;
+  int end = (int)L.end[k] - start1, end_next = L.end[k + 1];  // step that ends the row; where the next one ends
+  auto fetch = [&](int2 (&o)[C], int s0) {
+#pragma unroll
+    for (int u = 0; u < C; ++u) o[u] = ep[s0 + u];
+  };
+  auto request = [&](int u, const int2& n) {
+    load(u, n.x);
+    a[u] = __int_as_float(n.y);
+  };
+  auto take = [&](int u, int s0) {
+    add(u, a[u], s0 + u);
+    if (end == s0 + u) {
+      end_row(k, row);
+      ++k;
+      row = row_next;
+      end = end_next - start1;
+      row_next = L.dst[k + 1];
+      end_next = L.end[k + 1];
+    }
+  };
+  // Requests behind a condition make the compiler wait for everything in flight, so the steady state has none.  The
+  // steps left over after the last whole round do ask whether there is a step.
+  const int rounds = R.steps / RING, rest = R.steps - rounds * RING;  // wave-uniform
+  if (rounds + rest == 0) return;
+  fetch(e[0], 0);
+  int s0 = 0;  // steps consumed so far
+  if (rounds > 0) {
+    rn_for<RING>([&](auto u) {
+      if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], u + C);
+      request(u, e[(u / C) & 1][u % C]);
+    });
+    for (int r = 1; r < rounds; ++r, s0 += RING) {
+      rn_for<RING>([&](auto u) {
+        if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], s0 + RING + u + C);
+        take(u, s0);
+        request(u, e[(u / C) & 1][u % C]);
+      });
+    }
+    if (rest > 0) {
+      rn_for<RING>([&](auto u) {
+        if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], s0 + RING + u + C);
+        take(u, s0);
+        if (u < rest) request(u, e[(u / C) & 1][u % C]);
+      });
+      s0 += RING;
+    }
+  } else {
+    rn_for<RING>([&](auto u) {
+      if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], u + C);
+      if (u < rest) request(u, e[(u / C) & 1][u % C]);
+    });
+  }
+  const int left = R.cnt - s0;  // of this lane's run
+  rn_for<RING>([&](auto u) {
+    if (u < left) take(u, s0);
+  });
+}
+
+}  // namespace isp_dev
