@@ -11,7 +11,7 @@
 // Both backward forms are row passes over the cached transpose (whose perm gives p), so no
 // floating-point atomics are needed and results are deterministic.
 #include "row_stream.h"
-#include "group_stream.h"
+#include "run_stream.h"
 
 namespace {
 using namespace isp_dev;
@@ -80,75 +80,101 @@ __global__ void __launch_bounds__(ISP_WG) k_reduce_fwd(isp_view A, const int64_t
   stream_item<P>(A, indptr, indices, values, pa, d, k0, Y, ldy);
 }
 
-// ---- grouped forward of min / max ---------------------------------------------------------------------
-// The grouped SpMM's work items, LDS staging, step tables and two-buffer pipeline (group_stream.h) with the
-// accumulation replaced by a running (value, position) pair per column.  A group of LPG lanes covers a slice
-// of 4 * LPG columns and G = 64 / LPG entries share a gather; group g meets entries g, g + G, ... of a row in
-// ascending position, so "replace only if strictly better" keeps the first entry within a group, and the
-// groups' pairs are combined with ties going to the smaller position: the first entry of the row that
-// attains the extremum, as the definition asks.  Hub segments leave (value, position) halves in their
+// ---- run-streaming forward of min / max ------------------------------------------------------------------
+// The SpMM kernel's items and runs (run_stream.h) with the sum replaced by a running (value, position) pair per
+// column.  A run meets its entries in ascending position, so "replace only if strictly better" keeps the first
+// entry of a row that attains the extremum; the parts of a row that a run boundary cuts are put together with the
+// earlier part kept unless the later one is better.  Hub segments leave (value, position) halves in their
 // partial rows exactly as the generic kernel does, and the same fix-up combines them in segment order.
-// Needs float4 lanes and 32-bit gather offsets; a launch covers at most 128 columns (the partial rows).
+// Needs 4 columns or more and 32-bit gather offsets; a launch covers at most 128 columns (the partial rows).
+// Bound by the vector ALU on short rows (a comparison and two selects per column and entry, and the row ends): with
+// every row's entries shared out over the groups and a reduction of pairs at every row end 2.4 M entries took
+// 216 us at 16 columns and 159 at 64, now 34 and 67.
 template <int MODE>
 __device__ inline bool mm_better(float t, float best) { return MODE == R_MIN ? t < best : t > best; }
 
-template <int LPG, int MODE, bool HAS_VAL, bool SPARSE_ROWS>
+constexpr int MINMAX_RING = 4;
+
+template <int LPG, int MODE, bool HAS_VAL>
 __global__ void __launch_bounds__(ISP_WG) k_minmax_grouped(isp_view A, const int64_t* __restrict__ indptr,
                                                            const int32_t* __restrict__ indices,
                                                            const float* __restrict__ values,
                                                            const float* __restrict__ X, int64_t ldx, int d, int k_base,
-                                                           int n_slices, float* __restrict__ Y, int64_t ldy,
+                                                           float* __restrict__ Y, int64_t ldy,
                                                            int32_t* __restrict__ arg) {
   constexpr int G = ISP_WAVE / LPG;
-  constexpr int U = GS_U;
-  __shared__ gs_lds lds;
+  __shared__ rn_lds lds;
   const int lane = threadIdx.x & (ISP_WAVE - 1);
   const int w = threadIdx.x >> 6;
-  const int slice = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % n_slices));
-  const int item = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / n_slices) * ISP_WAVES_PER_WG + w);
+  const int item = __builtin_amdgcn_readfirstlane((int)blockIdx.x * ISP_WAVES_PER_WG + w);
   if (item >= A.n_blocks + A.n_seg) return;
   const item_range it = locate_item(A, indptr, item);
   if (it.skip) return;
-  gs_wave_lds& L = lds.w[w];
-  int n_live = 0;  // non-empty rows of a row block
-  const int n_steps = gs_prepare<G, HAS_VAL, SPARSE_ROWS>(it, indptr, indices, values, L, lane, &n_live);  // multiple of U
+  rn_wave_lds& L = lds.w[w];
+  const rn_run R = rn_prepare<G, HAS_VAL>(it, indptr, indices, values, nullptr, L, lane);
 
   const int g = lane / LPG, q = lane % LPG;
-  const int col = k_base + (slice * LPG + q) * 4;
-  const bool lane_on = col < d;
-  const unsigned lane_byte = lane_on ? (unsigned)col * 4u : 0u;
+  // (lanes past d work on the last columns again and store what the columns' own lane stores)
+  const int col = k_base + tail_col<4>(q * 4, d - k_base);
+  const unsigned lane_byte = (unsigned)col * 4u;
   const unsigned pitch_byte = (unsigned)ldx * 4u;
   const int p0 = (int)it.p;  // position of the item's first entry (nnz < 2^31)
 
-  float best[4];
-  int where[4];
+  float best[4], head[4], x[MINMAX_RING][4];
+  int where[4], head_where[4];  // entry's number in the run until a row ends, then its position
 #pragma unroll
-  for (int v = 0; v < 4; ++v) { best[v] = 0.f; where[v] = -1; }
-  const bool listed = SPARSE_ROWS && !it.is_seg;
-  auto store_row = [&](int row) {  // this lane's four columns of one finished row (or segment)
+  for (int v = 0; v < 4; ++v) { best[v] = head[v] = 0.f; where[v] = head_where[v] = -1; }
+  auto store_row = [&](int row, const float (&b)[4], const int (&wh)[4]) {
+    float wb[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) wb[v] = __int_as_float(wh[v]);
     if (it.is_seg) {
       float* pr = A.partials + (int64_t)row * ISP_PARTIAL_TILE + (col - k_base);
-      float wb[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) wb[v] = __int_as_float(where[v]);
-      store_vec<4>(pr, best);
+      store_vec<4>(pr, b);
       store_vec<4>(pr + ARG_OFF, wb);
     } else {
-      store_vec<4>(Y + (int64_t)row * ldy + col, best);
-      *reinterpret_cast<int4*>(arg + (int64_t)row * d + col) = make_int4(where[0], where[1], where[2], where[3]);
+      store_vec<4>(Y + (int64_t)row * ldy + col, b);
+      store_vec<4>(reinterpret_cast<float*>(arg) + (int64_t)row * d + col, wb);
     }
   };
-  if (listed && lane_on) {  // empty rows (listed behind the non-empty ones): value 0, position -1
-    const int n_empty = it.row_last - it.row - n_live;
-    for (int i = g; i < n_empty; i += G) store_row(it.row + (int)L.ss[n_live + 1 + i]);
-  }
-  int k_done = 0;
-  int r_next = listed ? (int)L.ss[0] : 0;
+  for (int i = g; i < R.n_empty; i += G) store_row(L.dst[RN_EMPTY0 - i], best, where);  // value 0, position -1
 
-  auto finish_row = [&]() {
-    const int row = it.row + __builtin_amdgcn_readfirstlane(r_next);
-    ++k_done;
-    r_next = listed ? (int)L.ss[k_done] : k_done;
+  bool carried = R.mid;  // the next row to end began in an earlier run
+  bool ended = false;    // a row has ended in this run
+  bool fresh = true;     // no entry of the current row has been met in this run
+  const int pos0 = p0 + R.start;
+  rn_stream<MINMAX_RING>(
+      L, R,
+      [&](int u, int c) {
+        const unsigned off = __umul24((unsigned)c, pitch_byte) + lane_byte;
+        load_vec<4>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) + off), x[u]);
+      },
+      [&](int u, float a, int s) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float t = __fmul_rn(a, x[u][v]);  // one rounded fp32 multiply, never fused
+          const bool take = fresh || mm_better<MODE>(t, best[v]);
+          best[v] = take ? t : best[v];
+          where[v] = take ? s : where[v];
+        }
+        fresh = false;
+      },
+      [&](int, int row) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          where[v] += pos0;
+          head[v] = carried ? best[v] : head[v];
+          head_where[v] = carried ? where[v] : head_where[v];
+        }
+        if (!carried) store_row(row, best, where);
+        carried = false;
+        ended = true;
+        fresh = true;
+      });
+#pragma unroll
+  for (int v = 0; v < 4; ++v) where[v] = fresh ? -1 : where[v] + pos0;
+
+  if (it.is_seg) {  // one row: the groups' pairs, ties going to the smaller position
 #pragma unroll
     for (int o = LPG; o < ISP_WAVE; o <<= 1) {
 #pragma unroll
@@ -160,65 +186,37 @@ __global__ void __launch_bounds__(ISP_WG) k_minmax_grouped(isp_view A, const int
         where[v] = take ? ow : where[v];
       }
     }
-    if (g == 0 && lane_on) store_row(row);
+    if (g == 0) store_row(it.row, best, where);
+    return;
+  }
+  if constexpr (G > 1) {  // rows cut by a run boundary (as in k_spmm_grouped)
+    const unsigned long long m_end = __ballot(ended), m_mid = __ballot(R.mid);
+    const unsigned long long m_head = m_end & m_mid;
+    if (m_head == 0) return;
+    wave_lds_sync();  // (every entry has been read)
+    float* __restrict__ tail = reinterpret_cast<float*>(L.ent);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) { best[v] = 0.f; where[v] = -1; }
-  };
-  auto issue = [&](int s0, unsigned (&dsc)[U], float (&x)[U][4], float (&a)[U]) {
-    const uint4 pk = *reinterpret_cast<const uint4*>(L.step + s0);
-    const unsigned raw[4] = {(unsigned)__builtin_amdgcn_readfirstlane(pk.x), (unsigned)__builtin_amdgcn_readfirstlane(pk.y),
-                             (unsigned)__builtin_amdgcn_readfirstlane(pk.z), (unsigned)__builtin_amdgcn_readfirstlane(pk.w)};
-    int2 e[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      dsc[u] = (raw[u >> 1] >> ((u & 1) * 16)) & 0xffffu;
-      e[u] = L.ent[gs_off(dsc[u]) + g];
+    for (int v = 0; v < 4; ++v) {
+      tail[lane * 8 + v] = best[v];
+      tail[lane * 8 + 4 + v] = __int_as_float(where[v]);
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool act = g < gs_cnt(dsc[u]) && lane_on;
-      a[u] = __int_as_float(e[u].y);
-      const int cj = act ? e[u].x : 0;  // dead lanes gather row 0; what they fetch is never used
-      const unsigned off = __umul24((unsigned)cj, pitch_byte) + lane_byte;
-      load_vec<4>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) + off), x[u]);
-    }
-  };
-  auto consume = [&](const unsigned (&dsc)[U], const float (&x)[U][4], const float (&a)[U]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (g < gs_cnt(dsc[u]) && lane_on) {
-        const int pos = p0 + gs_off(dsc[u]) + g;
+    wave_lds_sync();
+    if ((m_head >> lane) & 1ull) {
+      int j = lane - LPG;
+      for (;;) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const float t = __fmul_rn(a[u], x[u][v]);  // one rounded fp32 multiply, never fused
-          const bool take = where[v] < 0 || mm_better<MODE>(t, best[v]);
-          best[v] = take ? t : best[v];
-          where[v] = take ? pos : where[v];
+          const float tb = tail[j * 8 + v];
+          const int tw = __float_as_int(tail[j * 8 + 4 + v]);
+          const bool later = mm_better<MODE>(head[v], tb);
+          head[v] = later ? head[v] : tb;
+          head_where[v] = later ? head_where[v] : tw;
         }
+        if (((m_end >> j) & 1ull) || !((m_mid >> j) & 1ull)) break;  // the row began in that run
+        j -= LPG;
       }
-      if (dsc[u] & GS_LAST) finish_row();
+      store_row(L.dst[R.k], head, head_where);
     }
-  };
-
-  const int n_groups = n_steps / U;
-  if (n_groups == 0) return;
-  unsigned dA[U], dB[U];
-  float xA[U][4], xB[U][4], aA[U], aB[U];
-  issue(0, dA, xA, aA);
-  int gi = 0;
-  while (gi + 2 < n_groups) {
-    issue((gi + 1) * U, dB, xB, aB);
-    consume(dA, xA, aA);
-    issue((gi + 2) * U, dA, xA, aA);
-    consume(dB, xB, aB);
-    gi += 2;
-  }
-  if (gi + 1 < n_groups) {
-    issue((gi + 1) * U, dB, xB, aB);
-    consume(dA, xA, aA);
-    consume(dB, xB, aB);
-  } else {
-    consume(dA, xA, aA);
   }
 }
 
@@ -231,8 +229,8 @@ __global__ void __launch_bounds__(ISP_WG) k_reduce_fixup(isp_view A, int d, int 
   if (h >= A.n_hub) return;
   const int s0 = A.hub_seg_ptr[h], s1 = A.hub_seg_ptr[h + 1];
   const int row = A.hub_rows[h];
-  const int rel = lane * VEC;
-  if (k0 + rel >= d) return;
+  if (k0 + lane * VEC >= d) return;
+  const int rel = tail_col<VEC>(lane * VEC, d - k0);
   float best[VEC];
   int where[VEC];
 #pragma unroll
@@ -372,18 +370,15 @@ isp_status fwd_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int k0
 }
 
 template <int LPG, int MODE>
-isp_status minmax_grouped_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int k_base, int n_slices, float* Y,
+isp_status minmax_grouped_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int k_base, float* Y,
                                int64_t ldy, int32_t* arg, hipStream_t s) {
   const isp_view& v = A->v;
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
-    const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG) * (unsigned)n_slices;
-    const bool sparse_rows = A->info.bin_rows[0] * 16 > A->info.n_rows;  // (as the grouped SpMM chooses)
-#define ISP_GO(HV, SR)                                                                                             \
-  k_minmax_grouped<LPG, MODE, HV, SR><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, X, ldx, d, k_base, \
-                                                              n_slices, Y, ldy, arg)
-    if (v.values) { if (sparse_rows) ISP_GO(true, true); else ISP_GO(true, false); }
-    else { if (sparse_rows) ISP_GO(false, true); else ISP_GO(false, false); }
+    const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
+#define ISP_GO(HV) \
+  k_minmax_grouped<LPG, MODE, HV><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, X, ldx, d, k_base, Y, ldy, arg)
+    if (v.values) ISP_GO(true); else ISP_GO(false);
 #undef ISP_GO
     ISP_LAUNCH_CHECK();
   }
@@ -399,22 +394,22 @@ isp_status fwd_all(const isp_csr* A, const float* X, int64_t ldx, int d, float* 
                    hipStream_t s) {
   const isp_view& av = A->v;
   if constexpr (MODE != R_MEAN) {
-    // grouped kernel: float4 lanes, 32-bit gather offsets, the partition within the LDS tables' limits
+    // grouped kernel: 32-bit gather offsets, the partition within the LDS tables' limits
     const bool a32 = av.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
                      ((uint64_t)av.n_cols * (uint64_t)ldx + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
-    const bool ok = av.nnz > 0 && a32 && d % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0 && aligned(X, 16) &&
-                    aligned(Y, 16) && aligned(arg, 16) && A->info.block_cost <= GS_MAX_ROWS &&
+    const bool ok = av.nnz > 0 && a32 && d >= 4 && A->info.block_cost <= GS_MAX_ROWS &&
                     A->info.block_cost + av.hub_t <= GS_MAX_ENT && av.seg_len <= GS_MAX_ENT && !A->tune.no_grouped;
     if (ok) {
       // 128 columns per launch (a hub partial row holds 128 values and 128 positions), one slice: the two
       // 64-column slices that pay for the sum on large graphs cost more here than they save, the loop doing
       // four compare-and-select steps per entry instead of four multiply-adds (config 3: 7.09 vs 6.05 ms)
       isp_status st = ISP_OK;
-      for (int k_base = 0; k_base < d && st == ISP_OK; k_base += 2 * ISP_WAVE) {
+      for (int k0 = 0; k0 < d && st == ISP_OK; k0 += 2 * ISP_WAVE) {
+        const int k_base = d - k0 < 4 ? d - 4 : k0;  // (no launch narrower than a float4 lane)
         const int w = d - k_base < 2 * ISP_WAVE ? d - k_base : 2 * ISP_WAVE;
-        if (w <= 32) st = minmax_grouped_tile<8, MODE>(A, X, ldx, d, k_base, 1, Y, ldy, arg, s);
-        else if (w <= 64) st = minmax_grouped_tile<16, MODE>(A, X, ldx, d, k_base, 1, Y, ldy, arg, s);
-        else st = minmax_grouped_tile<32, MODE>(A, X, ldx, d, k_base, 1, Y, ldy, arg, s);
+        if (w <= 32) st = minmax_grouped_tile<8, MODE>(A, X, ldx, d, k_base, Y, ldy, arg, s);
+        else if (w <= 64) st = minmax_grouped_tile<16, MODE>(A, X, ldx, d, k_base, Y, ldy, arg, s);
+        else st = minmax_grouped_tile<32, MODE>(A, X, ldx, d, k_base, Y, ldy, arg, s);
       }
       return st;
     }
