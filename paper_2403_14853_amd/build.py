@@ -10,6 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libisp.so")
 SOURCES = ["isp_api.hip", "scan.hip", "csr_build.hip", "transpose.hip", "spmm.hip", "sddmm.hip", "fusedmm.hip",
+           "fused_fwd.hip", "fused_bwd_row.hip", "fused_bwd_col.hip", "fused_bwd_mirror.hip",
            "spmm_reduce.hip", "static_scratch.hip", "alias.hip"]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -5,21 +5,10 @@
 // The per-edge scores exist only in registers: each gathered row x_j is used for the dot product
 // and for the accumulation in the same pass, and the backward recomputes the scores instead of
 // reading them back.  The column sum of the backward runs over the rows of the cached transpose.
-#include "grouped_ops.h"
+#include "fused_grouped.h"
 
 namespace {
 using namespace isp_dev;
-
-// (hardware exponential and reciprocal, about 1 ulp each; exp overflow gives 1 / inf = 0)
-__device__ inline float sigmoidf_fast(float z) { return __builtin_amdgcn_rcpf(1.f + __expf(-z)); }
-
-// Edge function s = f(z) and its derivative; op is wave-uniform (ISP_OP_SIGMOID / _DOT / _ONE).
-// The grouped kernels pass it as a compile-time constant, the generic ones at run time.
-__device__ inline void edge_fn(int op, float z, float& s, float& ds) {
-  if (op == ISP_OP_SIGMOID) { s = sigmoidf_fast(z); ds = s * (1.f - s); }
-  else if (op == ISP_OP_DOT) { s = z; ds = 1.f; }
-  else { s = 1.f; ds = 0.f; }
-}
 
 template <int VEC, int T>
 __device__ inline float dot_lanes(const float (&a)[T][VEC], const float (&b)[T][VEC]) {
@@ -130,11 +119,6 @@ __global__ void __launch_bounds__(ISP_WG) k_fused(isp_view A, const int64_t* __r
   stream_item<P>(A, indptr, indices, values, pa, d, 0, Y, ldy, store_group, group_cnt);
 }
 
-template <int VEC, int T, bool ACC>
-__global__ void __launch_bounds__(ISP_WG) k_fused_fixup(isp_view A, int d, float* __restrict__ Y, int64_t ldy) {
-  hub_fixup<VEC, T, ACC>(A, d, 0, Y, ldy);
-}
-
 template <int VEC, bool ACC>
 __global__ void __launch_bounds__(ISP_WG) k_fused_fixup_group(isp_view A, int d, int k0, float* __restrict__ Y,
                                                               int64_t ldy, int stride, int slot) {
@@ -168,157 +152,6 @@ isp_status run_pass(const isp_csr* A, const typename P::args& pa, int d, float* 
     }
   }
   return ISP_OK;
-}
-
-// ---- grouped fast path (4 <= d <= 256, any alignment) -----------------------------------
-struct g_args1 { const float* src[1]; int64_t lds_[1]; const float* rowop[1]; int64_t ldr[1]; float* out_entry; int op; };
-struct g_args12 { const float* src[1]; int64_t lds_[1]; const float* rowop[2]; int64_t ldr[2]; float* out_entry; int op; };
-struct g_args21 { const float* src[2]; int64_t lds_[2]; const float* rowop[1]; int64_t ldr[1]; float* out_entry; int op; };
-
-template <int OP>
-struct g_fwd {  // gathered x_j, row operand x_i
-  static constexpr int NSRC = 1, NROW = 1, STEPS = 4;
-  static constexpr bool PER_ENTRY = false, ACCUMULATE = false;
-  using args = g_args1;
-  template <int LPG, int W, bool TAIL>
-  __device__ static inline void edge(const args&, float a, const float (&x)[1][W], const float (&r)[1][W],
-                                     float (&acc)[W], const lane_cols<W / 4, TAIL>& lc, bool live) {
-    float sg = 1.f, dsg = 0.f;
-    if (OP != ISP_OP_ONE) edge_fn(OP, group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc)), sg, dsg);
-    const float w = a * sg;
-    if (live) {
-#pragma unroll
-      for (int v = 0; v < W; ++v) acc[v] = fmaf(w, x[0][v], acc[v]);
-    }
-  }
-};
-
-template <int OP>
-struct g_bwd_row {  // gathered x_j, row operands x_i and g_i:  dX_i += dz x_j
-  static constexpr int NSRC = 1, NROW = 2, STEPS = 3;  // (three operand rows per step: three steps per buffer keep four waves resident)
-  static constexpr bool PER_ENTRY = false, ACCUMULATE = false;
-  using args = g_args12;
-  template <int LPG, int W, bool TAIL>
-  __device__ static inline void edge(const args&, float a, const float (&x)[1][W], const float (&r)[2][W],
-                                     float (&acc)[W], const lane_cols<W / 4, TAIL>& lc, bool live) {
-    if (OP == ISP_OP_ONE) return;  // s does not depend on x_i: nothing flows through z
-    const float z = group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc));
-    const float gd = group_allreduce<LPG>(dotw<W, TAIL>(r[1], x[0], lc));
-    float sg, dsg;
-    edge_fn(OP, z, sg, dsg);
-    const float dz = a * gd * dsg;
-    if (live) {
-#pragma unroll
-      for (int v = 0; v < W; ++v) acc[v] = fmaf(dz, x[0][v], acc[v]);
-    }
-  }
-};
-
-template <int OP>
-struct g_bwd_col {  // over A^T: gathered x_i and g_i, row operand x_j:  dX_j += a s g_i + dz x_i
-  static constexpr int NSRC = 2, NROW = 1, STEPS = 3;
-  static constexpr bool PER_ENTRY = false, ACCUMULATE = true;
-  using args = g_args21;
-  template <int LPG, int W, bool TAIL>
-  __device__ static inline void edge(const args&, float a, const float (&x)[2][W], const float (&r)[1][W],
-                                     float (&acc)[W], const lane_cols<W / 4, TAIL>& lc, bool live) {
-    float sg = 1.f, dsg = 0.f, gd = 0.f;
-    if (OP != ISP_OP_ONE) {
-      edge_fn(OP, group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc)), sg, dsg);
-      gd = group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[1], lc));
-    }
-    const float w = a * sg;
-    const float dz = a * gd * dsg;
-    if (live) {
-#pragma unroll
-      for (int v = 0; v < W; ++v) acc[v] = fmaf(w, x[1][v], fmaf(dz, x[0][v], acc[v]));
-    }
-  }
-};
-
-// Backward in ONE pass over A when A^T's structure equals A's (symmetric pattern, ascending rows): entry p of
-// row i names neighbour j, and position p of A^T holds the mirrored entry (j, i) with value a_ji.  Both sums of
-// the backward then run over the same neighbours, and x_j and g_j are gathered once for both:
-//   dX_i = sum_j (dz_ij + dz_ji) x_j + a_ji s g_j,   dz_ij = a_ij <g_i, x_j> f'(z),  dz_ji = a_ji <g_j, x_i> f'(z),
-// z = <x_i, x_j> being the same for (i, j) and (j, i).  Two gathered rows per entry instead of three, one sweep
-// over the index arrays instead of two.
-struct g_args22 { const float* src[2]; int64_t lds_[2]; const float* rowop[2]; int64_t ldr[2]; float* out_entry; int op; const float* val2; };
-
-template <int OP>
-struct g_bwd_mirror {  // gathered x_j and g_j, row operands x_i and g_i
-  static constexpr int NSRC = 2, NROW = 2, STEPS = 2;
-  static constexpr bool PER_ENTRY = false, ACCUMULATE = false, HAS_VAL2 = true;
-  using args = g_args22;
-  template <int LPG, int W, bool TAIL>
-  __device__ static inline void edge(const args&, float a, float at, const float (&x)[2][W], const float (&r)[2][W],
-                                     float (&acc)[W], const lane_cols<W / 4, TAIL>& lc, bool live) {
-    float sg = 1.f, dsg = 0.f, gd_ij = 0.f, gd_ji = 0.f;
-    if (OP != ISP_OP_ONE) {
-      edge_fn(OP, group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc)), sg, dsg);
-      gd_ij = group_allreduce<LPG>(dotw<W, TAIL>(r[1], x[0], lc));  // <g_i, x_j>
-      gd_ji = group_allreduce<LPG>(dotw<W, TAIL>(x[1], r[0], lc));  // <g_j, x_i>
-    }
-    const float w = at * sg;
-    const float dz = (a * gd_ij + at * gd_ji) * dsg;
-    if (live) {
-#pragma unroll
-      for (int v = 0; v < W; ++v) acc[v] = fmaf(w, x[1][v], fmaf(dz, x[0][v], acc[v]));
-    }
-  }
-};
-
-template <class P, int LPG, int W, bool ADDR32, bool TAIL>
-__global__ void __launch_bounds__(ISP_WG) k_fused_grouped(isp_view A, const int64_t* __restrict__ indptr,
-                                                          const int32_t* __restrict__ indices,
-                                                          const float* __restrict__ values, typename P::args pa, int d,
-                                                          float* __restrict__ Y, int64_t ldy) {
-  __shared__ gs_lds lds;
-  fused_grouped_item<P, LPG, W, ADDR32, TAIL>(A, indptr, indices, values, pa, d, Y, ldy, lds);
-}
-
-// LPG lanes with W floats each span the feature width: W * LPG >= d.
-template <class P, int LPG, int W>
-isp_status run_grouped(const isp_csr* A, const typename P::args& pa, int d, float* Y, int64_t ldy, hipStream_t s) {
-  const isp_view& v = A->v;
-  const int n_items = v.n_blocks + v.n_seg;
-  if (n_items > 0) {
-    const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
-    bool a32 = true;
-    for (int k = 0; k < P::NSRC; ++k) a32 = a32 && fused_offsets_fit_32(v.n_cols, pa.lds_[k], d);
-#define ISP_GO(A32, TL) k_fused_grouped<P, LPG, W, A32, TL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, pa, d, Y, ldy)
-    if (d % 4) { if (a32) ISP_GO(true, true); else ISP_GO(false, true); }
-    else { if (a32) ISP_GO(true, false); else ISP_GO(false, false); }
-#undef ISP_GO
-    ISP_LAUNCH_CHECK();
-  }
-  if (v.n_hub > 0) {
-    const unsigned grid = (unsigned)((v.n_hub + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
-    k_fused_fixup<4, 1, P::ACCUMULATE><<<grid, ISP_WG, 0, s>>>(v, d, Y, ldy);
-    ISP_LAUNCH_CHECK();
-  }
-  return ISP_OK;
-}
-
-// One or two float4 per lane.  Two halve the lanes per dot product, so a step covers twice the entries with one
-// lane-reduction stage and one evaluation of the edge function less per entry, and a step costs more
-// instructions: it pays where steps are full.  Measured on the benchmark graphs at widths 48 .. 256: two above
-// 64 columns; up to 64 columns one, except in the forward pass (one gathered row, the fewest instructions per
-// step) on graphs whose non-empty rows average 24 entries or more.  ISP_FUSED_W=4 / 8 forces either (d > 32).
-template <class P>
-isp_status run_grouped_d(const isp_csr* A, const typename P::args& pa, int d, float* Y, int64_t ldy, hipStream_t s) {
-  if (d <= 32) return run_grouped<P, 8, 4>(A, pa, d, Y, ldy, s);
-  const int64_t live_rows = A->info.n_rows - A->info.bin_rows[0];
-  const bool long_rows = live_rows > 0 && A->info.nnz >= 24 * live_rows;
-  const bool fwd = P::NSRC + P::NROW == 2;
-  const bool two = A->tune.fused_w ? A->tune.fused_w == 8 : (d > 64 || (fwd && long_rows));
-  if (!two) {
-    if (d <= 64) return run_grouped<P, 16, 4>(A, pa, d, Y, ldy, s);
-    if (d <= 128) return run_grouped<P, 32, 4>(A, pa, d, Y, ldy, s);
-    return run_grouped<P, 64, 4>(A, pa, d, Y, ldy, s);
-  }
-  if (d <= 64) return run_grouped<P, 8, 8>(A, pa, d, Y, ldy, s);
-  if (d <= 128) return run_grouped<P, 16, 8>(A, pa, d, Y, ldy, s);
-  return run_grouped<P, 32, 8>(A, pa, d, Y, ldy, s);
 }
 
 // Column groups (of 256) a hub segment may store per launch of a wide pass: as many as the partial-row scratch
@@ -362,10 +195,7 @@ isp_status isp_fusedmm_launch(const isp_csr* A, const float* X, int64_t ldx, int
   const bool ok4 = ldx % 4 == 0 && ldy % 4 == 0 && aligned(X, 16) && aligned(Y, 16);
   const bool ok2 = ldx % 2 == 0 && ldy % 2 == 0 && aligned(X, 8) && aligned(Y, 8);
   if (d >= 4 && d <= ISP_PARTIAL_TILE && grouped_partition_ok(A)) {
-    g_args1 pa{{X}, {ldx}, {X}, {ldx}, nullptr, op};
-    if (op == ISP_OP_SIGMOID) return run_grouped_d<g_fwd<ISP_OP_SIGMOID>>(A, pa, d, Y, ldy, s);
-    if (op == ISP_OP_DOT) return run_grouped_d<g_fwd<ISP_OP_DOT>>(A, pa, d, Y, ldy, s);
-    return run_grouped_d<g_fwd<ISP_OP_ONE>>(A, pa, d, Y, ldy, s);
+    return isp_fused_grouped_fwd(A, X, ldx, d, op, Y, ldy, s);
   }
   const bool hv = A->v.values != nullptr;
   isp_status st = ISP_OK;
@@ -414,25 +244,11 @@ isp_status isp_fusedmm_bwd_launch(const isp_csr* A, const float* X, int64_t ldx,
   const bool ok2 = ldx % 2 == 0 && ldg % 2 == 0 && lddx % 2 == 0 && aligned(X, 8) && aligned(G, 8) && aligned(dX, 8);
   if (d >= 4 && d <= ISP_PARTIAL_TILE && grouped_partition_ok(A) && A->mirror_aligned && !A->tune.no_mirror) {
     // symmetric pattern: one pass over A serves both sums (the mirrored entries' values are A^T's)
-    g_args22 pm{{X, G}, {ldx, ldg}, {X, G}, {ldx, ldg}, nullptr, op, A->At->v.values};
-    if (op == ISP_OP_SIGMOID) return run_grouped_d<g_bwd_mirror<ISP_OP_SIGMOID>>(A, pm, d, dX, lddx, s);
-    if (op == ISP_OP_DOT) return run_grouped_d<g_bwd_mirror<ISP_OP_DOT>>(A, pm, d, dX, lddx, s);
-    return run_grouped_d<g_bwd_mirror<ISP_OP_ONE>>(A, pm, d, dX, lddx, s);
+    return isp_fused_grouped_bwd_mirror(A, X, ldx, G, ldg, d, op, dX, lddx, s);
   }
   if (d >= 4 && d <= ISP_PARTIAL_TILE && grouped_partition_ok(A) && grouped_partition_ok(A->At)) {
-    g_args12 p1{{X}, {ldx}, {X, G}, {ldx, ldg}, nullptr, op};
-    g_args21 p2{{X, G}, {ldx, ldg}, {X}, {ldx}, nullptr, op};
-    isp_status st1;
-    if (op == ISP_OP_SIGMOID) {
-      st1 = run_grouped_d<g_bwd_row<ISP_OP_SIGMOID>>(A, p1, d, dX, lddx, s);
-      return st1 != ISP_OK ? st1 : run_grouped_d<g_bwd_col<ISP_OP_SIGMOID>>(A->At, p2, d, dX, lddx, s);
-    }
-    if (op == ISP_OP_DOT) {
-      st1 = run_grouped_d<g_bwd_row<ISP_OP_DOT>>(A, p1, d, dX, lddx, s);
-      return st1 != ISP_OK ? st1 : run_grouped_d<g_bwd_col<ISP_OP_DOT>>(A->At, p2, d, dX, lddx, s);
-    }
-    st1 = run_grouped_d<g_bwd_row<ISP_OP_ONE>>(A, p1, d, dX, lddx, s);
-    return st1 != ISP_OK ? st1 : run_grouped_d<g_bwd_col<ISP_OP_ONE>>(A->At, p2, d, dX, lddx, s);
+    const isp_status st1 = isp_fused_grouped_bwd_row(A, X, ldx, G, ldg, d, op, dX, lddx, s);
+    return st1 != ISP_OK ? st1 : isp_fused_grouped_bwd_col(A->At, X, ldx, G, ldg, d, op, dX, lddx, s);
   }
   const bool hv = A->v.values != nullptr;
   isp_status st = ISP_OK;

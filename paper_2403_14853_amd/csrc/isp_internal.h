@@ -51,7 +51,7 @@ struct isp_tuning {
   int spmm_lpg;         // ISP_SPMM_LPG: lanes per group of the grouped SpMM (0 = chosen by shape)
   int spmm_tile;        // ISP_SPMM_TILE: feature columns per launch of the grouped SpMM (0 = chosen by shape)
   bool no_mirror;       // ISP_NO_MIRROR: the FusedMM backward never takes the one-pass form of symmetric patterns
-  int fused_w;          // ISP_FUSED_W: 4 / 8 = the grouped SDDMM / FusedMM kernels give a lane one / two float4 at every width above 32 (0 = chosen by width and graph)
+  int fused_w;          // ISP_FUSED_W: 4 / 8 = the grouped FusedMM kernels give a lane one / two float4 at every width above 32 (0 = chosen by width and graph)
   int wide_groups;      // ISP_WIDE_GROUPS: most column groups a hub segment stores per launch of a wide FusedMM pass (0 = as many as fit)
 };
 isp_tuning isp_read_tuning();
@@ -157,6 +157,15 @@ isp_status isp_fusedmm_launch(const isp_csr* A, const float* X, int64_t ldx, int
                               int64_t ldy, hipStream_t s);
 isp_status isp_fusedmm_bwd_launch(const isp_csr* A, const float* X, int64_t ldx, const float* G, int64_t ldg,
                                   int32_t d, int op, float* dX, int64_t lddx, hipStream_t s);
+// Grouped passes of FusedMM, 4 <= d <= 256 (fused_fwd.hip, fused_bwd_*.hip); the column pass takes the transpose's handle.
+isp_status isp_fused_grouped_fwd(const isp_csr* A, const float* X, int64_t ldx, int d, int op, float* Y, int64_t ldy,
+                                 hipStream_t s);
+isp_status isp_fused_grouped_bwd_row(const isp_csr* A, const float* X, int64_t ldx, const float* G, int64_t ldg, int d,
+                                     int op, float* Y, int64_t ldy, hipStream_t s);
+isp_status isp_fused_grouped_bwd_col(const isp_csr* A, const float* X, int64_t ldx, const float* G, int64_t ldg, int d,
+                                     int op, float* Y, int64_t ldy, hipStream_t s);
+isp_status isp_fused_grouped_bwd_mirror(const isp_csr* A, const float* X, int64_t ldx, const float* G, int64_t ldg,
+                                        int d, int op, float* Y, int64_t ldy, hipStream_t s);
 isp_status isp_spmm_reduce_launch(const isp_csr* A, const float* X, int64_t ldx, int32_t d, int reduce, float* Y,
                                   int64_t ldy, int32_t* arg, hipStream_t s);
 isp_status isp_spmm_reduce_bwd_launch(isp_csr* A, const float* dY, int64_t lddy, int32_t d, int reduce,

@@ -39,9 +39,9 @@ struct rn_run {
 };
 constexpr int RN_EMPTY0 = GS_MAX_ROWS + 7;
 
-// Stage the item and find the groups' runs.  slot_of: for blocks of pieces, the partial row of piece `row`
+// Stage the item and find the groups' runs.  values may be NULL (every entry is 1).  slot_of: for blocks of pieces, the partial row of piece `row`
 // (else NULL).
-template <int G, bool HAS_VAL>
+template <int G>
 __device__ inline rn_run rn_prepare(const item_range& it, const int64_t* __restrict__ indptr,
                                     const int32_t* __restrict__ indices, const float* __restrict__ values,
                                     const int32_t* __restrict__ slot_of, rn_wave_lds& L, int lane) {
@@ -65,7 +65,7 @@ __device__ inline rn_run rn_prepare(const item_range& it, const int64_t* __restr
       v[u] = 1.f;
       if (i < n_ent) {
         c[u] = __builtin_nontemporal_load(indices + it.p + i);
-        if (HAS_VAL) v[u] = __builtin_nontemporal_load(values + it.p + i);
+        if (values) v[u] = __builtin_nontemporal_load(values + it.p + i);
       }
     }
 #pragma unroll
@@ -134,41 +134,56 @@ __device__ __forceinline__ void rn_for_each(F&& f, std::integer_sequence<int, U.
 template <int N, class F>
 __device__ __forceinline__ void rn_for(F&& f) { rn_for_each(f, std::make_integer_sequence<int, N>{}); }
 
-// Stream the runs.  load(u, col): request the gather of ring slot u;  add(u, a, s): take slot u's row into the
-// running result, a the entry's value, s its number in the run;  end_row(k, row): the k-th non-empty row is complete in this lane's group,
-// its output row is `row` (called by the lanes it concerns only).  RING gathers are in flight per lane.
+// A cursor over a run's rows: the row of the current step, the step that ends it, and the row after it (read one row
+// ahead, so that nothing waits for the list).
+struct rn_cursor {
+  int k, row, row_next, end, end_next;
+  __device__ __forceinline__ rn_cursor(const rn_wave_lds& L, const rn_run& R)
+      : k(R.k), row(L.dst[R.k]), row_next(L.dst[R.k + 1]), end((int)L.end[R.k] - R.start - 1), end_next(L.end[R.k + 1]) {}
+  __device__ __forceinline__ void advance(const rn_wave_lds& L, const rn_run& R) {
+    ++k;
+    row = row_next;
+    end = end_next - R.start - 1;
+    row_next = L.dst[k + 1];
+    end_next = L.end[k + 1];
+  }
+};
+
+// Stream the runs.  load(u, col, s, row, first): request what ring slot u needs of entry s of the run, which lies in row `row`
+// (ROWS only: else 0);  add(u, a, s): take slot u into the running result, a the entry's value;  end_row(k, row): the
+// k-th non-empty row is complete in this lane's group, its output row is `row` (ENDS only; called by the lanes it
+// concerns only).  RING steps are in flight per lane.
 // A round of RING steps is consumed while the next one is requested, slot by slot, into the same registers; the
-// entries are read from LDS RN_CHUNK steps before they are needed.  A row's end is the step number at which it
+// entries are read from LDS CHUNK steps before they are needed.  A row's end is the step number at which it
 // ends, kept per lane: one comparison a step.
-template <int RING, class Load, class Add, class End>
+template <int RING, bool ENDS, bool ROWS, int CHUNK = RN_CHUNK, class Load, class Add, class End>
 __device__ __forceinline__ void rn_stream(const rn_wave_lds& L, const rn_run& R, Load&& load, Add&& add, End&& end_row) {
-  static_assert(RING % (2 * RN_CHUNK) == 0 && 2 * RN_CHUNK <= RN_PAD, "fetches alternate between two buffers");
+  static_assert(RING % (2 * CHUNK) == 0 && 2 * CHUNK <= RN_PAD, "fetches alternate between two buffers");
   const int2* __restrict__ ep = L.ent + R.start;
-  constexpr int C = RN_CHUNK;
+  constexpr int C = CHUNK;
   float a[RING];
   int2 e[2][C];  // entries to request next, and the ones after them
-  int k = R.k;
-  int row = L.dst[k], row_next = L.dst[k + 1];  // read one row ahead: a store does not wait for the list
-  const int start1 = R.start + 1;
-  int end = (int)L.end[k] - start1, end_next = L.end[k + 1];  // step that ends the row; where the next one ends
+  rn_cursor out(L, R), in(L, R);
+  bool in_first = true;  // (ROWS) the step to request next is its row's first in this run
   auto fetch = [&](int2 (&o)[C], int s0) {
 #pragma unroll
     for (int u = 0; u < C; ++u) o[u] = ep[s0 + u];
   };
-  auto request = [&](int u, const int2& n) {
-    load(u, n.x);
+  auto request = [&](int u, const int2& n, int s) {
+    load(u, n.x, s, ROWS ? in.row : 0, in_first);
     a[u] = __int_as_float(n.y);
+    if constexpr (ROWS) {
+      in_first = in.end == s;
+      if (in_first) in.advance(L, R);
+    }
   };
   auto take = [&](int u, int s0) {
     add(u, a[u], s0 + u);
-    if (end == s0 + u) {
-      end_row(k, row);
-      ++k;
-      row = row_next;
-      end = end_next - start1;
-      row_next = L.dst[k + 1];
-      end_next = L.end[k + 1];
-    }
+    if constexpr (ENDS)
+      if (out.end == s0 + u) {
+        end_row(out.k, out.row);
+        out.advance(L, R);
+      }
   };
   // Requests behind a condition make the compiler wait for everything in flight, so the steady state has none.  The
   // steps left over after the last whole round do ask whether there is a step.
@@ -179,27 +194,27 @@ __device__ __forceinline__ void rn_stream(const rn_wave_lds& L, const rn_run& R,
   if (rounds > 0) {
     rn_for<RING>([&](auto u) {
       if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], u + C);
-      request(u, e[(u / C) & 1][u % C]);
+      request(u, e[(u / C) & 1][u % C], u);
     });
     for (int r = 1; r < rounds; ++r, s0 += RING) {
       rn_for<RING>([&](auto u) {
         if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], s0 + RING + u + C);
         take(u, s0);
-        request(u, e[(u / C) & 1][u % C]);
+        request(u, e[(u / C) & 1][u % C], s0 + RING + u);
       });
     }
     if (rest > 0) {
       rn_for<RING>([&](auto u) {
         if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], s0 + RING + u + C);
         take(u, s0);
-        if (u < rest) request(u, e[(u / C) & 1][u % C]);
+        if (u < rest) request(u, e[(u / C) & 1][u % C], s0 + RING + u);
       });
       s0 += RING;
     }
   } else {
     rn_for<RING>([&](auto u) {
       if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], u + C);
-      if (u < rest) request(u, e[(u / C) & 1][u % C]);
+      if (u < rest) request(u, e[(u / C) & 1][u % C], u);
     });
   }
   const int left = R.cnt - s0;  // of this lane's run

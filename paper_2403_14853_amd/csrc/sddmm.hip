@@ -93,11 +93,10 @@ __global__ void __launch_bounds__(ISP_WG) k_sddmm(isp_view A, const int64_t* __r
 // ADD: this pass covers a window of the feature columns and adds its partial dot product to out.
 // The entry's staged value multiplies the dot product; it is 1 when the kernel is given no values
 // (unscaled SDDMM, or a matrix without stored values).
-// SPARSE: empty rows own no step (worth it where many rows are empty).
-template <bool ADD_ = false, bool SPARSE_ = false>
+template <bool ADD_ = false>
 struct sddmm_policy {
-  static constexpr int NSRC = 1, NROW = 1, STEPS = 4;
-  static constexpr bool PER_ENTRY = true, ACCUMULATE = false, ADD = ADD_, SPARSE_ROWS = SPARSE_;
+  static constexpr int NSRC = 1, NROW = 1, RING4 = 4, RING8 = 4;
+  static constexpr bool PER_ENTRY = true, ACCUMULATE = false, ADD = ADD_;
   struct args { const float* src[1]; int64_t lds_[1]; const float* rowop[1]; int64_t ldr[1]; float* out_entry; };
   template <int LPG, int W, bool TAIL>
   __device__ static inline float entry(float a, const float (&x)[1][W], const float (&r)[1][W], const lane_cols<W / 4, TAIL>& lc) {
@@ -105,17 +104,17 @@ struct sddmm_policy {
   }
 };
 
-template <int LPG, int W, bool ADDR32, bool ADD, bool SPARSE, bool TAIL>
+template <int LPG, bool ADDR32, bool ADD, bool TAIL>
 __global__ void __launch_bounds__(ISP_WG) k_sddmm_grouped(isp_view A, const int64_t* __restrict__ indptr,
                                                           const int32_t* __restrict__ indices,
                                                           const float* __restrict__ values,
-                                                          typename sddmm_policy<ADD, SPARSE>::args pa, int d, int k_lo) {
-  __shared__ gs_lds lds;
-  fused_grouped_item<sddmm_policy<ADD, SPARSE>, LPG, W, ADDR32, TAIL>(A, indptr, indices, values, pa, d, nullptr, 0, lds, k_lo);
+                                                          typename sddmm_policy<ADD>::args pa, int d, int k_lo) {
+  __shared__ rn_lds lds;
+  fused_grouped_item<sddmm_policy<ADD>, LPG, 4, ADDR32, TAIL>(A, indptr, indices, values, pa, d, nullptr, 0, lds, k_lo);
 }
 
-// One pass over the feature columns [k_lo, d_hi) (d_hi - k_lo <= W * LPG); add: accumulate into out.
-template <int LPG, int W>
+// One pass over the feature columns [k_lo, d_hi) (d_hi - k_lo <= 4 * LPG); add: accumulate into out.
+template <int LPG>
 isp_status launch_grouped(const isp_csr* A, const float* U, int64_t ldu, const float* V, int64_t ldv, int k_lo,
                           int d_hi, bool add, bool scale, float* out, hipStream_t s) {
   const isp_view& v = A->v;
@@ -123,19 +122,14 @@ isp_status launch_grouped(const isp_csr* A, const float* U, int64_t ldu, const f
   if (n_items == 0 || v.nnz == 0) return ISP_OK;
   const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
   const float* vals = scale ? v.values : nullptr;
-  const bool a32 = fused_offsets_fit_32(v.n_cols, ldv, d_hi);
-  typename sddmm_policy<false>::args pa{{V}, {ldv}, {U}, {ldu}, out};  // (the same members in every variant)
-  // rows without entries: skipped through the list of non-empty rows when they are an eighth of all rows or more
-  // (the list costs one LDS read per step, an empty row's step a whole step)
-  const bool sparse = A->info.bin_rows[0] * 8 >= A->info.n_rows;
+  const bool a32 = fused_offsets_fit_32(v.n_cols, ldv, d_hi) && fused_offsets_fit_32(v.n_rows, ldu, d_hi);
   const bool tail = (d_hi - k_lo) % 4 != 0;
-#define ISP_GO(A32, AD, SP)                                                                                  \
-  do {                                                                                                       \
-    typename sddmm_policy<AD, SP>::args pb{{pa.src[0]}, {pa.lds_[0]}, {pa.rowop[0]}, {pa.ldr[0]}, pa.out_entry}; \
-    if (tail) k_sddmm_grouped<LPG, W, A32, AD, SP, true><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, pb, d_hi, k_lo); \
-    else k_sddmm_grouped<LPG, W, A32, AD, SP, false><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, pb, d_hi, k_lo); \
+#define ISP_GO(A32, AD, TL)                                                                                         \
+  do {                                                                                                              \
+    typename sddmm_policy<AD>::args pa{{V}, {ldv}, {U}, {ldu}, out};                                                 \
+    k_sddmm_grouped<LPG, A32, AD, TL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, pa, d_hi, k_lo);       \
   } while (0)
-#define ISP_GO2(A32, AD) do { if (sparse) ISP_GO(A32, AD, true); else ISP_GO(A32, AD, false); } while (0)
+#define ISP_GO2(A32, AD) do { if (tail) ISP_GO(A32, AD, true); else ISP_GO(A32, AD, false); } while (0)
   if (a32) { if (add) ISP_GO2(true, true); else ISP_GO2(true, false); }
   else { if (add) ISP_GO2(false, true); else ISP_GO2(false, false); }
 #undef ISP_GO2
@@ -191,19 +185,13 @@ isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const
       const int w = k_hi - k_lo;
       const bool add = k_lo > 0;
       k_next = k_hi;
-      // one float4 per lane up to 64 columns, two above (half the lanes per dot product: fewer instructions per
-      // entry where a step's eight-plus entries are mostly live; measured on the benchmark graphs);
-      // ISP_FUSED_W=4 / 8 forces either
-      const bool two = A->tune.fused_w ? A->tune.fused_w == 8 : w > 64;
-      if (w <= 32) st = launch_grouped<8, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
-      else if (!two) {
-        if (w <= 64) st = launch_grouped<16, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
-        else if (w <= 128) st = launch_grouped<32, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
-        else st = launch_grouped<64, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
-      }
-      else if (w <= 64) st = launch_grouped<8, 8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
-      else if (w <= 128) st = launch_grouped<16, 8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
-      else st = launch_grouped<32, 8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      // One float4 per lane (two, which serve twice the entries per step, load the row operand with every step and
+      // hold twice the registers: 128 columns in one pass, us, one / two: 115 M entries 2648 / 2704, 16.9 M 717 /
+      // 737, 2.4 M 108 / 110).
+      if (w <= 32) st = launch_grouped<8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      else if (w <= 64) st = launch_grouped<16>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      else if (w <= 128) st = launch_grouped<32>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      else st = launch_grouped<64>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
     }
     return st;
   }

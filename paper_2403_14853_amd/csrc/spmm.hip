@@ -77,7 +77,7 @@ isp_status launch_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int
 // MEAN: finished rows are divided by their length (partial rows are not: their fix-up divides).
 constexpr int SPMM_RING = 4;
 
-template <int LPG, bool HAS_VAL, bool ADDR32, int VEC, bool MEAN>
+template <int LPG, bool ADDR32, int VEC, bool MEAN>
 __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
     isp_view A, const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
     const float* __restrict__ values, const float* __restrict__ X, int64_t ldx, int d, int k_base, int n_slices,
@@ -96,8 +96,8 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
   // each adds into a partial row, named by piece_slot.  A block never mixes real rows and pieces.
   const bool pieces = !it.is_seg && (int64_t)it.row >= A.n_real_rows;
   const bool to_partial = it.is_seg || pieces;
-  const rn_run R = rn_prepare<G, HAS_VAL>(it, indptr, indices, values,
-                                          pieces ? A.piece_slot - A.n_real_rows : nullptr, L, lane);
+  const rn_run R = rn_prepare<G>(it, indptr, indices, values,
+                                 pieces ? A.piece_slot - A.n_real_rows : nullptr, L, lane);
 
   const int g = lane / LPG, q = lane % LPG;
   int col = k_base + (slice * LPG + q) * VEC;
@@ -121,9 +121,9 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
   bool carried = R.mid;  // the next row to end began in an earlier run
   bool ended = false;    // a row has ended in this run
   auto inv_len = [&](int k) { return 1.f / (float)((int)L.end[k] - (k > 0 ? (int)L.end[k - 1] : 0)); };
-  rn_stream<SPMM_RING>(
+  rn_stream<SPMM_RING, true, false>(
       L, R,
-      [&](int u, int c) {
+      [&](int u, int c, int, int, bool) {
         if constexpr (ADDR32) {
           const unsigned off = __umul24((unsigned)c, pitch_byte) + lane_byte;
           load_vec<VEC>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) + off), x[u]);
@@ -208,16 +208,15 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG) * (unsigned)n_slices;
     const bool a32 = v.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
                      ((uint64_t)v.n_cols * (uint64_t)ldx + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
-#define ISP_GO(HV, A32, MN)                                                                                        \
-  k_spmm_grouped<LPG, HV, A32, VEC, MN><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
-                                                                n_slices, Y, ldy)
+#define ISP_GO(A32, MN)                                                                                        \
+  k_spmm_grouped<LPG, A32, VEC, MN><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
+                                                            n_slices, Y, ldy)
     if constexpr (VEC < 4) {  // scalar lanes are only dispatched with 32-bit addressing and for the plain sum
-      if (vals) ISP_GO(true, true, false); else ISP_GO(false, true, false);
+      ISP_GO(true, false);
+    } else if (mean_mode == 1) {
+      if (a32) ISP_GO(true, true); else ISP_GO(false, true);
     } else {
-#define ISP_GO2(HV, A32) do { if (mean_mode == 1) ISP_GO(HV, A32, true); else ISP_GO(HV, A32, false); } while (0)
-      if (vals) { if (a32) ISP_GO2(true, true); else ISP_GO2(true, false); }
-      else { if (a32) ISP_GO2(false, true); else ISP_GO2(false, false); }
-#undef ISP_GO2
+      if (a32) ISP_GO(true, false); else ISP_GO(false, false);
     }
 #undef ISP_GO
     ISP_LAUNCH_CHECK();

@@ -95,7 +95,7 @@ __device__ inline bool mm_better(float t, float best) { return MODE == R_MIN ? t
 
 constexpr int MINMAX_RING = 4;
 
-template <int LPG, int MODE, bool HAS_VAL>
+template <int LPG, int MODE>
 __global__ void __launch_bounds__(ISP_WG) k_minmax_grouped(isp_view A, const int64_t* __restrict__ indptr,
                                                            const int32_t* __restrict__ indices,
                                                            const float* __restrict__ values,
@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(ISP_WG) k_minmax_grouped(isp_view A, const int
   const item_range it = locate_item(A, indptr, item);
   if (it.skip) return;
   rn_wave_lds& L = lds.w[w];
-  const rn_run R = rn_prepare<G, HAS_VAL>(it, indptr, indices, values, nullptr, L, lane);
+  const rn_run R = rn_prepare<G>(it, indptr, indices, values, nullptr, L, lane);
 
   const int g = lane / LPG, q = lane % LPG;
   // (lanes past d work on the last columns again and store what the columns' own lane stores)
@@ -143,9 +143,9 @@ __global__ void __launch_bounds__(ISP_WG) k_minmax_grouped(isp_view A, const int
   bool ended = false;    // a row has ended in this run
   bool fresh = true;     // no entry of the current row has been met in this run
   const int pos0 = p0 + R.start;
-  rn_stream<MINMAX_RING>(
+  rn_stream<MINMAX_RING, true, false>(
       L, R,
-      [&](int u, int c) {
+      [&](int u, int c, int, int, bool) {
         const unsigned off = __umul24((unsigned)c, pitch_byte) + lane_byte;
         load_vec<4>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) + off), x[u]);
       },
@@ -376,10 +376,7 @@ isp_status minmax_grouped_tile(const isp_csr* A, const float* X, int64_t ldx, in
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
-#define ISP_GO(HV) \
-  k_minmax_grouped<LPG, MODE, HV><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, X, ldx, d, k_base, Y, ldy, arg)
-    if (v.values) ISP_GO(true); else ISP_GO(false);
-#undef ISP_GO
+    k_minmax_grouped<LPG, MODE><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, X, ldx, d, k_base, Y, ldy, arg);
     ISP_LAUNCH_CHECK();
   }
   if (v.n_hub > 0) {
