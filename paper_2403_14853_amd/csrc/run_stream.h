@@ -34,54 +34,38 @@ struct rn_run {
   int start, cnt;   // entries [start, start + cnt) of the item
   int k;            // index into dst of the row its first entry belongs to
   bool mid;         // the run starts inside a row: that row's sum begins in an earlier run
-  int full, steps;  // steps in which every group has an entry; steps in which any has (wave-uniform)
+  int steps;        // steps in which any group has an entry (wave-uniform)
   int n_empty;      // empty rows, listed at dst[RN_EMPTY0 - i]
 };
 constexpr int RN_EMPTY0 = GS_MAX_ROWS + 7;
 
-// Stage the item and find the groups' runs.  values may be NULL (every entry is 1).  slot_of: for blocks of pieces, the partial row of piece `row`
-// (else NULL).
-template <int G>
-__device__ inline rn_run rn_prepare(const item_range& it, const int64_t* __restrict__ indptr,
-                                    const int32_t* __restrict__ indices, const float* __restrict__ values,
-                                    const int32_t* __restrict__ slot_of, rn_wave_lds& L, int lane) {
-  const int n_ent = (int)(it.p_end - it.p);
-  const int n_rows = it.is_seg ? 0 : it.row_last - it.row;
-  // the first 64 rows' offsets are requested before the entries: both are on their way together
-  int a0 = 0, b0 = 0, d0 = it.row + lane;
-  if (lane < n_rows) {
-    a0 = (int)(indptr[it.row + lane] - it.p);
-    b0 = (int)(indptr[it.row + lane + 1] - it.p);
-    if (slot_of) d0 = slot_of[it.row + lane];
+// The first 64 rows' offsets of a row block, requested before its entries so that both are on their way together.
+struct rn_first_rows {
+  int a, b, dst;  // of row it.row + lane: its entries [a, b) relative to the item, its output row
+};
+__device__ __forceinline__ rn_first_rows rn_request_rows(const item_range& it, const int64_t* __restrict__ indptr,
+                                                         const int32_t* __restrict__ slot_of, int lane) {
+  rn_first_rows f{0, 0, it.row + lane};
+  if (!it.is_seg && lane < it.row_last - it.row) {
+    f.a = (int)(indptr[it.row + lane] - it.p);
+    f.b = (int)(indptr[it.row + lane + 1] - it.p);
+    if (slot_of) f.dst = slot_of[it.row + lane];
   }
-  constexpr int SB = 8;  // loads in flight per lane
-  for (int base = 0; base < n_ent; base += SB * ISP_WAVE) {
-    int c[SB];
-    float v[SB];
-#pragma unroll
-    for (int u = 0; u < SB; ++u) {
-      const int i = base + u * ISP_WAVE + lane;
-      c[u] = 0;
-      v[u] = 1.f;
-      if (i < n_ent) {
-        c[u] = __builtin_nontemporal_load(indices + it.p + i);
-        if (values) v[u] = __builtin_nontemporal_load(values + it.p + i);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < SB; ++u) {
-      const int i = base + u * ISP_WAVE + lane;
-      if (i < n_ent) L.ent[i] = make_int2(c[u], __float_as_int(v[u]));
-    }
-  }
-  if (lane < RN_PAD) L.ent[n_ent + lane] = make_int2(0, 0);
+  return f;
+}
 
+// The groups' runs over n_ent staged entries.  slot_of: for blocks of pieces, the partial row of piece `row` (else
+// NULL).  staged(o): how many of the item's first o entries are staged (all, where nothing is left out).
+template <int G, class Staged>
+__device__ __forceinline__ rn_run rn_find_runs(const item_range& it, const int64_t* __restrict__ indptr,
+                                               const int32_t* __restrict__ slot_of, int n_ent, const rn_first_rows& f,
+                                               Staged&& staged, rn_wave_lds& L, int lane) {
+  const int n_rows = it.is_seg ? 0 : it.row_last - it.row;
   const int g = lane / (ISP_WAVE / G);
   const int q = n_ent / G, rest = n_ent - q * G;
   rn_run R;
   R.start = g * q + (g < rest ? g : rest);
   R.cnt = q + (g < rest ? 1 : 0);
-  R.full = q;
   R.steps = q + (rest > 0 ? 1 : 0);
   R.k = 0;
   R.mid = it.is_seg;
@@ -89,7 +73,7 @@ __device__ inline rn_run rn_prepare(const item_range& it, const int64_t* __restr
   int live = 0;
   for (int base = 0; base < n_rows; base += ISP_WAVE) {
     const int r = base + lane;
-    int a = a0, b = b0, dst = d0;
+    int a = f.a, b = f.b, dst = f.dst;
     if (base > 0) {
       a = b = 0;
       dst = it.row + r;
@@ -99,6 +83,8 @@ __device__ inline rn_run rn_prepare(const item_range& it, const int64_t* __restr
         if (slot_of) dst = slot_of[it.row + r];
       }
     }
+    a = staged(a);
+    b = staged(b);
     const bool on = b > a;
     const unsigned long long m = __ballot(on);
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -126,6 +112,37 @@ __device__ inline rn_run rn_prepare(const item_range& it, const int64_t* __restr
   // (the last row to end before the run's first entry ends right there, or the run starts inside a row)
   if (!it.is_seg && R.cnt > 0) R.mid = R.k > 0 ? (int)L.end[R.k - 1] != R.start : R.start > 0;
   return R;
+}
+
+// Stage the item and find the groups' runs.  values may be NULL (every entry is 1).
+template <int G>
+__device__ inline rn_run rn_prepare(const item_range& it, const int64_t* __restrict__ indptr,
+                                    const int32_t* __restrict__ indices, const float* __restrict__ values,
+                                    const int32_t* __restrict__ slot_of, rn_wave_lds& L, int lane) {
+  const int n_ent = (int)(it.p_end - it.p);
+  const rn_first_rows f = rn_request_rows(it, indptr, slot_of, lane);
+  constexpr int SB = 8;  // loads in flight per lane
+  for (int base = 0; base < n_ent; base += SB * ISP_WAVE) {
+    int c[SB];
+    float v[SB];
+#pragma unroll
+    for (int u = 0; u < SB; ++u) {
+      const int i = base + u * ISP_WAVE + lane;
+      c[u] = 0;
+      v[u] = 1.f;
+      if (i < n_ent) {
+        c[u] = __builtin_nontemporal_load(indices + it.p + i);
+        if (values) v[u] = __builtin_nontemporal_load(values + it.p + i);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < SB; ++u) {
+      const int i = base + u * ISP_WAVE + lane;
+      if (i < n_ent) L.ent[i] = make_int2(c[u], __float_as_int(v[u]));
+    }
+  }
+  if (lane < RN_PAD) L.ent[n_ent + lane] = make_int2(0, 0);
+  return rn_find_runs<G>(it, indptr, slot_of, n_ent, f, [](int o) { return o; }, L, lane);
 }
 
 // f(0) ... f(N - 1) with the index as a compile-time constant (ring slots live in registers).

@@ -326,6 +326,137 @@ __global__ void __launch_bounds__(ISP_WG) k_reduce_bwd(isp_view At, const int64_
   stream_item<P>(At, indptr, indices, values, pa, d, k0, dX, lddx);
 }
 
+// The same pass on contiguous runs (run_stream.h), for widths from 4 columns and 32-bit offsets.  Only the live
+// entries of an item are staged (packed with ballots; a row's end is the number of live entries before it), so the
+// loop sees a short matrix without dead entries, G of them per step, and a row without live entries is an empty one.
+// Bound by the two gathered rows per live entry (dY and arg) on large graphs.  The whole backward, us, against one entry
+// per wavefront and iteration: 40 M entries, 100 columns 2335 -> 1946; 2.4 M entries, 16 / 301 columns 142 -> 56 /
+// 1024 -> 568.
+struct sel_wave_lds {
+  rn_wave_lds rn;                     // ent: (column, source position)
+  float val[GS_MAX_ENT + RN_PAD];     // value of each staged entry
+  unsigned long long mask[GS_MAX_ENT / ISP_WAVE + 1];  // live entries of each 64 of the item ...
+  int before[GS_MAX_ENT / ISP_WAVE + 1];               // ... and how many live ones precede them
+};
+
+constexpr int SELECT_RING = 4;
+
+template <int LPG>
+__global__ void __launch_bounds__(ISP_WG) k_select_grouped(isp_view At, const int64_t* __restrict__ indptr,
+                                                           const int32_t* __restrict__ indices,
+                                                           const float* __restrict__ values,
+                                                           const int32_t* __restrict__ perm,
+                                                           const uint8_t* __restrict__ live,
+                                                           const float* __restrict__ dY, int64_t lddy,
+                                                           const int32_t* __restrict__ arg, int d, int k_base,
+                                                           float* __restrict__ dX, int64_t lddx) {
+  constexpr int G = ISP_WAVE / LPG;
+  __shared__ sel_wave_lds lds[ISP_WAVES_PER_WG];
+  const int lane = threadIdx.x & (ISP_WAVE - 1);
+  const int w = threadIdx.x >> 6;
+  const int item = __builtin_amdgcn_readfirstlane((int)blockIdx.x * ISP_WAVES_PER_WG + w);
+  if (item >= At.n_blocks + At.n_seg) return;
+  const item_range it = locate_item(At, indptr, item);
+  if (it.skip) return;
+  sel_wave_lds& S = lds[w];
+  rn_wave_lds& L = S.rn;
+  const int n_all = (int)(it.p_end - it.p);
+  const rn_first_rows f = rn_request_rows(it, indptr, nullptr, lane);
+  // stage the live entries: all the marks first, then what the live ones need
+  constexpr int SB = GS_MAX_ENT / ISP_WAVE;
+  unsigned char on[SB];
+#pragma unroll
+  for (int u = 0; u < SB; ++u) {
+    const int i = u * ISP_WAVE + lane;
+    on[u] = 0;
+    if (u * ISP_WAVE < n_all && i < n_all) on[u] = live[it.p + i];
+  }
+  int n_ent = 0;
+#pragma unroll
+  for (int u = 0; u < SB; ++u) {
+    const unsigned long long m = __ballot(on[u] != 0);
+    if (lane == 0) { S.mask[u] = m; S.before[u] = n_ent; }
+    if (on[u] != 0) {
+      const int64_t p = it.p + u * ISP_WAVE + lane;
+      const int o = n_ent + __popcll(m & ((1ull << lane) - 1ull));
+      L.ent[o] = make_int2(indices[p], perm[p]);
+      S.val[o] = values ? values[p] : 1.f;
+    }
+    n_ent += __popcll(m);
+  }
+  if (lane == 0) { S.mask[SB] = 0; S.before[SB] = n_ent; }
+  if (lane < RN_PAD) { L.ent[n_ent + lane] = make_int2(0, 0); S.val[n_ent + lane] = 0.f; }
+  wave_lds_sync();
+  const rn_run R = rn_find_runs<G>(it, indptr, nullptr, n_ent, f, [&](int o) {
+    return S.before[o >> 6] + __popcll(S.mask[o >> 6] & ((1ull << (o & 63)) - 1ull));
+  }, L, lane);
+
+  const int g = lane / LPG, q = lane % LPG;
+  const int col = k_base + tail_col<4>(q * 4, d - k_base);
+  float* __restrict__ out = it.is_seg ? At.partials + (col - k_base) : dX + col;
+  const int64_t ldo = it.is_seg ? (int64_t)ISP_PARTIAL_TILE : lddx;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f}, head[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int i = g; i < R.n_empty; i += G) store_vec<4>(out + (int64_t)L.dst[RN_EMPTY0 - i] * ldo, acc);
+
+  float x[SELECT_RING][4], wh[SELECT_RING][4], val[SELECT_RING];
+  bool carried = R.mid, ended = false;  // (as in k_spmm_grouped)
+  rn_stream<SELECT_RING, true, false>(
+      L, R,
+      [&](int u, int c, int s, int, bool) {
+        const unsigned cb = (unsigned)col * 4u;
+        load_vec<4>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(dY) + (__umul24((unsigned)c, (unsigned)lddy * 4u) + cb)), x[u]);
+        load_vec<4>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(arg) + (__umul24((unsigned)c, (unsigned)d * 4u) + cb)), wh[u]);
+        val[u] = S.val[R.start + s];
+      },
+      [&](int u, float a, int) {  // (a: the entry's source position, as bits)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const bool mine = __float_as_int(wh[u][v]) == __float_as_int(a);
+          acc[v] = mine ? fmaf(val[u], x[u][v], acc[v]) : acc[v];
+        }
+      },
+      [&](int, int row) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) head[v] = carried ? acc[v] : head[v];
+        if (!carried) store_vec<4>(out + (int64_t)row * ldo, acc);
+        carried = false;
+        ended = true;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = 0.f;
+      });
+  if (it.is_seg) {
+    constexpr int N = 4 / G > 0 ? 4 / G : 1;
+    const int idx0 = group_reduce_scatter<LPG, 4>(acc, lane);
+    if (group_owner<LPG, 4>(lane)) {
+      float t[N];
+#pragma unroll
+      for (int c = 0; c < N; ++c) t[c] = acc[c];
+      store_vec<N>(out + (int64_t)it.row * ldo + idx0, t);
+    }
+    return;
+  }
+  if constexpr (G > 1) {
+    const unsigned long long m_end = __ballot(ended), m_mid = __ballot(R.mid);
+    const unsigned long long m_head = m_end & m_mid;
+    if (m_head == 0) return;
+    wave_lds_sync();
+    float* __restrict__ tail = reinterpret_cast<float*>(L.ent);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) tail[lane * 4 + v] = acc[v];
+    wave_lds_sync();
+    if ((m_head >> lane) & 1ull) {
+      int j = lane - LPG;
+      for (;;) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) head[v] += tail[j * 4 + v];
+        if (((m_end >> j) & 1ull) || !((m_mid >> j) & 1ull)) break;
+        j -= LPG;
+      }
+      store_vec<4>(out + (int64_t)L.dst[R.k] * ldo, head);
+    }
+  }
+}
+
 // live[q] = 1 for every entry q of the transpose whose source position p = perm[q] arg names (positions
 // outside [0, nnz) - the -1 of empty rows, or anything a caller's array may hold - are ignored); live was
 // zeroed before.  A row's columns name positions inside that row, so the lookups in inv_perm stay local.
@@ -419,6 +550,22 @@ isp_status fwd_all(const isp_csr* A, const float* X, int64_t ldx, int d, float* 
   return st;
 }
 
+template <int LPG>
+isp_status select_grouped_tile(const isp_csr* At, const float* dY, int64_t lddy, const int32_t* arg, int d, int k_base,
+                               float* dX, int64_t lddx, hipStream_t s) {
+  const isp_view& v = At->v;
+  if (v.n_blocks + v.n_seg > 0) {
+    k_select_grouped<LPG><<<item_grid(v), ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, At->perm, At->sel_flags, dY,
+                                                          lddy, arg, d, k_base, dX, lddx);
+    ISP_LAUNCH_CHECK();
+  }
+  if (v.n_hub > 0) {
+    k_sum_fixup<4><<<hub_grid(v), ISP_WG, 0, s>>>(v, d < k_base + 4 * LPG ? d : k_base + 4 * LPG, k_base, dX, lddx);
+    ISP_LAUNCH_CHECK();
+  }
+  return ISP_OK;
+}
+
 template <class P, int VEC>
 isp_status bwd_tile(const isp_csr* At, const typename P::args& pa, int d, int k0, float* dX, int64_t lddx,
                     hipStream_t s) {
@@ -491,6 +638,22 @@ isp_status isp_spmm_reduce_bwd_launch(isp_csr* A, const float* dY, int64_t lddy,
       k_mark_selected<<<(unsigned)((n_arg + 255) / 256), 256, 0, s>>>(arg, n_arg, nnz, inv_perm, At->sel_flags);
       ISP_LAUNCH_CHECK();
     }
+  }
+  const isp_view& tv = At->v;
+  auto fits = [&](int64_t ld) {  // 32-bit gather offsets into a matrix of A's rows
+    return tv.n_cols < (1 << 24) && ld * 4 < (1 << 24) && ((uint64_t)tv.n_cols * (uint64_t)ld + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
+  };
+  if (reduce != R_MEAN && tv.nnz > 0 && d >= 4 && fits(lddy) && fits(d) && At->info.block_cost <= GS_MAX_ROWS &&
+      At->info.block_cost + tv.hub_t <= GS_MAX_ENT && tv.seg_len <= GS_MAX_ENT && !At->tune.no_grouped) {
+    for (int k0 = 0; k0 < d && st == ISP_OK; k0 += ISP_PARTIAL_TILE) {
+      const int k_base = d - k0 < 4 ? d - 4 : k0;  // (no launch narrower than a float4 lane)
+      const int w = d - k_base < ISP_PARTIAL_TILE ? d - k_base : ISP_PARTIAL_TILE;
+      if (w <= 32) st = select_grouped_tile<8>(At, dY, lddy, arg, d, k_base, dX, lddx, s);
+      else if (w <= 64) st = select_grouped_tile<16>(At, dY, lddy, arg, d, k_base, dX, lddx, s);
+      else if (w <= 128) st = select_grouped_tile<32>(At, dY, lddy, arg, d, k_base, dX, lddx, s);
+      else st = select_grouped_tile<64>(At, dY, lddy, arg, d, k_base, dX, lddx, s);
+    }
+    return st;
   }
   for (int k0 = 0; k0 < d && st == ISP_OK; k0 += (v2 ? 2 : 1) * ISP_WAVE) {
     if (reduce == R_MEAN) {
