@@ -11,11 +11,14 @@
 // of all of them.
 // Everything here is integer work and runs once per graph (balanced scheduling: paper Section 1(b); CSR
 // operand: Section 3.5).
+#include <limits.h>
 #include <stdlib.h>
 #include <new>
-#include "isp_internal.h"
+#include "block_scan.h"
+#include "host_slot.h"
 
 namespace {
+using namespace isp_dev;
 
 struct build_counters {
   unsigned long long bin_rows[5];
@@ -33,6 +36,10 @@ struct partition_params {
 };
 
 constexpr int MAX_BANDS = 64;  // one piece per lane
+constexpr int CUT_COUNT = 16;  // wavefronts' worth of entries that cutting a hub row looks at first
+
+// Matrices up to this size have everything about their partition enqueued in one go (see build_partition).
+constexpr int64_t SMALL_NNZ = 4 << 20;
 
 int env_int(const char* name, int dflt, int lo, int hi) {
   const char* s = getenv(name);
@@ -121,16 +128,19 @@ int isp_wave_slots() {
 
 namespace {
 
-__global__ void k_zero_counters(build_counters* c) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *c = build_counters{};
+// (and passes a flag that earlier launches left on the device on to the host, if there is one)
+__global__ void k_zero_counters(build_counters* c, const int* flag, int* host_flag) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) {
+    *c = build_counters{};
+    if (host_flag) *host_flag = *flag;
+  }
 }
 
 // Pieces of a hub row: its entries [a, b) cut where the columns cross band boundaries.  A row of degree
 // deg is cut into br = the largest power of two <= min(bands, deg / min_piece) coarse bands, each made of
 // bands / br fine bands of width ceil(n_cols / bands).  The whole wavefront calls this with the same row
 // (a, b wave-uniform): lane j < br gets piece j as [*first, *last), the other lanes an empty piece.  Every
-// lane finds one cut position by binary search, which assumes ascending columns; on a row that is not
-// sorted the positions are made monotone, so they are still valid cuts (inside the row, in order) and only
+// lane finds one cut position by counting and searching, which assumes ascending columns; on a row that is not sorted the positions are made monotone, so they are still valid cuts (inside the row, in order) and only
 // the scheduling benefit is lost, never correctness.
 __device__ inline void wave_hub_pieces(const int32_t* __restrict__ indices, int64_t a, int64_t b, int64_t n_cols,
                                        const partition_params& pp, int lane, int64_t* first, int64_t* last) {
@@ -139,15 +149,37 @@ __device__ inline void wave_hub_pieces(const int32_t* __restrict__ indices, int6
   while (br * 2 <= pp.bands && (int64_t)(br * 2) * pp.min_piece <= deg) br *= 2;
   const int64_t bw = (n_cols + pp.bands - 1) / pp.bands;
   const int step = pp.bands / br;
-  // cut j = first position whose column is >= j * step * bw; cut 0 = a, cuts >= br = b
+  // cut j = number of the row's columns below j * step * bw; cut 0 = a, cuts >= br = b
+  const int64_t target = (int64_t)lane * step * bw;
   int64_t lo = a, hi = b;
   if (lane == 0) hi = a;
   if (lane >= br) lo = b;
-  const int64_t target = (int64_t)lane * step * bw;
-  while (__any(lo < hi)) {
-    if (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if ((int64_t)indices[mid] < target) lo = mid + 1; else hi = mid;
+  {
+    // CUT_COUNT * 64 evenly spaced entries (a short row whole) in one trip to memory, counted with ballots, leave each
+    // cut a range of `gap` entries; a binary search from the start would be a chain of a dozen trips.
+    const int64_t gap = (deg + CUT_COUNT * ISP_WAVE - 1) / (CUT_COUNT * ISP_WAVE);
+    int c[CUT_COUNT];
+#pragma unroll
+    for (int k = 0; k < CUT_COUNT; ++k) {
+      const int64_t o = (int64_t)(k * ISP_WAVE + lane) * gap;
+      c[k] = o < deg ? indices[a + o] : INT_MAX;
+    }
+    for (int j = 1; j < br; ++j) {
+      const int64_t t64 = (int64_t)j * step * bw;
+      const int tj = t64 < INT_MAX ? (int)t64 : INT_MAX;
+      int64_t n = 0;  // samples below the cut
+#pragma unroll
+      for (int k = 0; k < CUT_COUNT; ++k) n += __popcll(__ballot(c[k] < tj));
+      if (lane == j) {
+        lo = a + (n > 0 ? (n - 1) * gap + 1 : 0);
+        hi = a + n * gap < b ? a + n * gap : b;
+      }
+    }
+    while (__any(lo < hi)) {
+      if (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if ((int64_t)indices[mid] < target) lo = mid + 1; else hi = mid;
+      }
     }
   }
   int64_t cut = lo;
@@ -170,43 +202,86 @@ __device__ inline int degree_bin(long long deg, int hub_t) {
   return 3;
 }
 
-// Per row: degree, class, cost, segment count; indptr checks.  Grid-stride; the class histogram,
-// maximum degree and segment total are reduced per workgroup before a handful of integer atomics.
-__global__ void __launch_bounds__(256) k_row_pass(const int64_t* __restrict__ indptr,
+// The partition's bookkeeping runs in three passes over the rows, each a tile of consecutive rows per workgroup: the
+// first leaves every tile's sums, the later ones start by adding up the sums of the tiles before theirs (a few
+// thousand numbers at most) instead of waiting for a scan in launches of its own.  A launch of this size takes about
+// 5 us whatever it does, and a graph that is seen once (1 M entries) spent 632 us in 93 of them.
+constexpr int64_t MAX_TILES = 4096;
+
+// What pass 1 finds out about a tile besides the sums, STATS numbers per tile: rows per class, entries per class, longest
+// row.  (Added up in pass 2: hundreds of workgroups with a dozen atomics each on one line took 25 us.)
+constexpr int STATS = 11;
+
+struct row_tiles {
+  int64_t rows;    // per tile
+  int n;           // tiles
+  int64_t* cost;   // sums per tile
+  int32_t *hub, *seg, *mark;
+  unsigned long long* stats;  // [STATS][MAX_TILES]
+};
+
+// Rows per wavefront: the workgroup's wavefronts turn to its hub rows one after the other, a few trips to memory each, so
+// small matrices spread their rows thin.
+constexpr int RPW_SMALL = 16, RPW_LARGE = ISP_WAVE;
+
+// Pass 1.  Per row: degree, class, cost, segment count; indptr checks; column indices in [0, n_cols) (check).  Workgroups beyond the
+// tiles only check indices.
+template <int RPW>
+__global__ void __launch_bounds__(BS_THREADS) k_row_pass(const int64_t* __restrict__ indptr,
                                                   const int32_t* __restrict__ indices, int64_t n_rows, int64_t n_cols,
-                                                  int64_t nnz, partition_params pp, int32_t* __restrict__ cost,
-                                                  int32_t* __restrict__ hubflag, int32_t* __restrict__ nseg,
-                                                  float* __restrict__ inv_len, build_counters* __restrict__ ctr) {
-  __shared__ unsigned long long s_rows[5], s_nnz[5], s_max;
-  __shared__ int s_err, s_seg;
-  if (threadIdx.x < 5) { s_rows[threadIdx.x] = 0; s_nnz[threadIdx.x] = 0; }
-  if (threadIdx.x == 0) { s_max = 0; s_err = 0; s_seg = 0; }
-  __syncthreads();
-  unsigned long long my_rows[5] = {0, 0, 0, 0, 0}, my_nnz[5] = {0, 0, 0, 0, 0}, my_max = 0;
-  int my_err = 0, my_seg = 0;
+                                                  int64_t nnz, partition_params pp, bool check, row_tiles T,
+                                                  int32_t* __restrict__ cost, int32_t* __restrict__ hubflag,
+                                                  int32_t* __restrict__ nseg, float* __restrict__ inv_len,
+                                                  build_counters* __restrict__ ctr) {
+  __shared__ unsigned long long s_stat[BS_THREADS / ISP_WAVE][STATS];
+  __shared__ unsigned long long s_cost[BS_THREADS / ISP_WAVE];
+  __shared__ int s_seg[BS_THREADS / ISP_WAVE], s_hub[BS_THREADS / ISP_WAVE], s_hubs[BS_THREADS / ISP_WAVE];
+  __shared__ int64_t s_ha[BS_THREADS], s_hb[BS_THREADS];  // the step's hub rows, [a, b), and their segments
+  __shared__ int s_ns[BS_THREADS];
   const int lane = threadIdx.x & (ISP_WAVE - 1);
-  // every wavefront walks whole chunks of 64 rows (one per lane), so that it can turn to a hub row together
-  for (int64_t base = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); base < n_rows;
-       base += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = base + lane;
-    const bool valid = i < n_rows;
+  if (check) {
+    bool bad = false;
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += (int64_t)gridDim.x * blockDim.x) {
+      const int32_t c = indices[p];
+      bad |= (c < 0 || c >= n_cols);
+    }
+    if (__any(bad) && lane == 0) atomicOr(&ctr->err, 2);
+  }
+  if ((int)blockIdx.x >= T.n) return;
+  unsigned long long my_rows[5] = {0, 0, 0, 0, 0}, my_nnz[5] = {0, 0, 0, 0, 0}, my_max = 0, my_cost = 0;
+  int my_err = 0, my_seg = 0, my_hub = 0;
+  const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
+  const int w = threadIdx.x / ISP_WAVE;
+  for (int64_t base = r0; base < r1; base += (BS_THREADS / ISP_WAVE) * RPW) {  // (the workgroup stays together)
+    const int64_t i = base + w * RPW + lane;
+    const bool valid = lane < RPW && i < r1;
     const int64_t a = valid ? indptr[i] : 0, b = valid ? indptr[i + 1] : 0;
     long long deg = b - a;
     if (valid && (deg < 0 || a < 0 || b > nnz || (i == 0 && a != 0) || (i == n_rows - 1 && b != nnz))) { my_err = 1; deg = 0; }
     const bool hub = deg > pp.hub_t;
-    int ns = 0;
-    for (unsigned long long hm = __ballot(hub); hm; hm &= hm - 1) {  // the chunk's hub rows, one at a time
-      const int src = __ffsll((long long)hm) - 1;
-      const int64_t ha = __shfl(a, src), hb = __shfl(b, src);
+    // the step's hub rows, shared out over the wavefronts
+    const unsigned long long hm = __ballot(hub);
+    if (lane == 0) s_hubs[w] = __popcll(hm);
+    __syncthreads();
+    int h0 = 0, n_hubs = 0;
+#pragma unroll
+    for (int ww = 0; ww < BS_THREADS / ISP_WAVE; ++ww) { h0 += ww < w ? s_hubs[ww] : 0; n_hubs += s_hubs[ww]; }
+    const int hx = h0 + __popcll(hm & ((1ull << lane) - 1ull));
+    if (hub) { s_ha[hx] = a; s_hb[hx] = b; }
+    __syncthreads();
+    for (int h = w; h < n_hubs; h += BS_THREADS / ISP_WAVE) {
       int64_t first, last;
-      wave_hub_pieces(indices, ha, hb, n_cols, pp, lane, &first, &last);
+      wave_hub_pieces(indices, s_ha[h], s_hb[h], n_cols, pp, lane, &first, &last);
       int cnt = (int)((last - first + pp.seg_len - 1) / pp.seg_len);
 #pragma unroll
       for (int o = 1; o < ISP_WAVE; o <<= 1) cnt += __shfl_xor(cnt, o);
-      if (lane == src) ns = cnt;
+      if (lane == 0) s_ns[h] = cnt;
     }
+    __syncthreads();
+    const int ns = hub ? s_ns[hx] : 0;
     if (!valid) continue;
-    cost[i] = hub ? 0 : (int32_t)deg + pp.row_cost;
+    const int32_t c = hub ? 0 : (int32_t)deg + pp.row_cost;
+    cost[i] = c;
     hubflag[i] = hub ? 1 : 0;
     nseg[i] = ns;
     inv_len[i] = deg > 0 ? 1.f / (float)deg : 0.f;
@@ -218,67 +293,109 @@ __global__ void __launch_bounds__(256) k_row_pass(const int64_t* __restrict__ in
     }
     my_max = (unsigned long long)deg > my_max ? (unsigned long long)deg : my_max;
     my_seg += ns;
+    my_hub += hub;
+    my_cost += c;
   }
+  if (__any(my_err) && lane == 0) atomicOr(&ctr->err, 1);
+  auto wave_sum = [](unsigned long long v) {
+#pragma unroll
+    for (int o = 1; o < ISP_WAVE; o <<= 1) v += __shfl_xor(v, o);
+    return v;
+  };
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
-    if (my_rows[k]) atomicAdd(&s_rows[k], my_rows[k]);
-    if (my_nnz[k]) atomicAdd(&s_nnz[k], my_nnz[k]);
+    const unsigned long long a = wave_sum(my_rows[k]), b = wave_sum(my_nnz[k]);
+    if (lane == 0) { s_stat[w][k] = a; s_stat[w][5 + k] = b; }
   }
-  if (my_max) atomicMax(&s_max, my_max);
-  if (my_err) atomicOr(&s_err, 1);
-  if (my_seg) atomicAdd(&s_seg, my_seg);
+#pragma unroll
+  for (int o = 1; o < ISP_WAVE; o <<= 1) {
+    const unsigned long long u = __shfl_xor(my_max, o);
+    my_max = u > my_max ? u : my_max;
+  }
+  const unsigned long long cost_sum = wave_sum(my_cost);
+  const int seg_sum = (int)wave_sum((unsigned)my_seg), hub_sum = (int)wave_sum((unsigned)my_hub);
+  if (lane == 0) { s_stat[w][10] = my_max; s_cost[w] = cost_sum; s_seg[w] = seg_sum; s_hub[w] = hub_sum; }
   __syncthreads();
-  if (threadIdx.x < 5) {
-    if (s_rows[threadIdx.x]) atomicAdd(&ctr->bin_rows[threadIdx.x], s_rows[threadIdx.x]);
-    if (s_nnz[threadIdx.x]) atomicAdd(&ctr->bin_nnz[threadIdx.x], s_nnz[threadIdx.x]);
-  }
-  if (threadIdx.x == 0) {
-    if (s_max) atomicMax(&ctr->max_degree, s_max);
-    if (s_err) atomicOr(&ctr->err, 1);
-    if (s_seg) atomicAdd(&ctr->n_seg, s_seg);
+  if (threadIdx.x < STATS) {
+    const int k = threadIdx.x;
+    unsigned long long v = s_stat[0][k];
+#pragma unroll
+    for (int ww = 1; ww < BS_THREADS / ISP_WAVE; ++ww) {
+      const unsigned long long u = s_stat[ww][k];
+      v = k < 10 ? v + u : (u > v ? u : v);
+    }
+    T.stats[k * MAX_TILES + blockIdx.x] = v;
+  } else if (threadIdx.x == ISP_WAVE) {
+    T.cost[blockIdx.x] = (int64_t)(s_cost[0] + s_cost[1] + s_cost[2] + s_cost[3]);
+    T.hub[blockIdx.x] = s_hub[0] + s_hub[1] + s_hub[2] + s_hub[3];
+    T.seg[blockIdx.x] = s_seg[0] + s_seg[1] + s_seg[2] + s_seg[3];
   }
 }
 
-// Column indices must lie in [0, n_cols).
-__global__ void __launch_bounds__(256) k_check_indices(const int32_t* __restrict__ indices, int64_t nnz, int64_t n_cols,
-                                                       build_counters* __restrict__ ctr) {
-  bool bad = false;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t c = indices[p];
-    bad |= (c < 0 || c >= n_cols);
+// Pass 2.  Where blocks begin: block b at the first row whose cumulative short-row cost reaches b * block_cost, and at
+// every hub row, at the row after one and at force_row (if inside the matrix; the derived matrix of the packed SpMM
+// layout keeps blocks of whole rows and blocks of row pieces apart that way).
+__global__ void __launch_bounds__(BS_THREADS) k_mark_rows(const int32_t* __restrict__ cost,
+                                                          const int32_t* __restrict__ hubflag, int64_t n_rows,
+                                                          int block_cost, int64_t force_row, row_tiles T,
+                                                          int32_t* __restrict__ mark, build_counters* __restrict__ ctr) {
+  if ((int)blockIdx.x == T.n) {  // one workgroup more than tiles: what the counters tell the caller
+    __shared__ unsigned long long part[BS_THREADS / ISP_WAVE][STATS];
+    const int lane = threadIdx.x & (ISP_WAVE - 1);
+    unsigned long long v[STATS] = {};
+#pragma unroll 2
+    for (int t = threadIdx.x; t < T.n; t += BS_THREADS) {
+#pragma unroll
+      for (int k = 0; k < STATS; ++k) {
+        const unsigned long long u = T.stats[k * MAX_TILES + t];
+        v[k] = k < 10 ? v[k] + u : (u > v[k] ? u : v[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < STATS; ++k) {
+#pragma unroll
+      for (int o = 1; o < ISP_WAVE; o <<= 1) {
+        const unsigned long long u = __shfl_xor(v[k], o);
+        v[k] = k < 10 ? v[k] + u : (u > v[k] ? u : v[k]);
+      }
+      if (lane == 0) part[threadIdx.x / ISP_WAVE][k] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < STATS) {
+      const int k = threadIdx.x;
+      unsigned long long z = part[0][k];
+      for (int w = 1; w < BS_THREADS / ISP_WAVE; ++w) z = k < 10 ? z + part[w][k] : (part[w][k] > z ? part[w][k] : z);
+      if (k < 5) ctr->bin_rows[k] = z; else if (k < 10) ctr->bin_nnz[k - 5] = z; else ctr->max_degree = z;
+    }
+    return;
   }
-  if (__any(bad) && (threadIdx.x & (ISP_WAVE - 1)) == 0) atomicOr(&ctr->err, 2);
-}
-
-// Block boundaries forced by hub rows: a hub row starts a block and so does the row after it.
-// force_row (if inside the matrix) also starts a block: the derived matrix of the packed SpMM layout keeps
-// blocks of whole rows and blocks of row pieces apart that way.
-__global__ void __launch_bounds__(256) k_mark_rows(const int32_t* __restrict__ hubflag, int64_t n_rows,
-                                                   int64_t force_row, int32_t* __restrict__ mark) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_rows) return;
-  mark[i] = (i == 0 || i == force_row || hubflag[i] || hubflag[i - 1]) ? 1 : 0;
-}
-
-// Balanced boundaries: block b starts at the first row whose cumulative short-row cost reaches b * block_cost.
-__global__ void __launch_bounds__(256) k_mark_balanced(const int64_t* __restrict__ cum_cost, int64_t n_rows,
-                                                       int64_t n_bal, int block_cost, int32_t* __restrict__ mark) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= n_bal) return;
-  const int64_t target = b * (int64_t)block_cost;
-  int64_t lo = 0, hi = n_rows;  // first i in [0, n_rows] with cum_cost[i] >= target
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (cum_cost[mid] >= target) hi = mid; else lo = mid + 1;
+  int64_t cum0 = block_sum_of<int64_t>(T.cost, blockIdx.x);
+  const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
+  int marks = 0;
+  for (int64_t base = r0; base < r1; base += BS_THREADS) {
+    const int64_t i = base + threadIdx.x;
+    const bool valid = i < r1;
+    int tot;
+    const int64_t cum = cum0 + block_exclusive_scan<int>(valid ? cost[i] : 0, &tot);
+    if (valid) {
+      // a multiple of block_cost lies in (cum - cost[i - 1], cum]: the remainder of cum is below the row before's cost
+      const int m = i == 0 || i == force_row || hubflag[i] || hubflag[i - 1] || cum % block_cost < cost[i - 1];
+      mark[i] = m;
+      marks += m;
+    }
+    cum0 += tot;
   }
-  if (lo < n_rows) mark[lo] = 1;
+  int tot;
+  block_exclusive_scan<int>(marks, &tot);
+  if (threadIdx.x == 0) T.mark[blockIdx.x] = tot;
 }
 
-__global__ void __launch_bounds__(256) k_compact(const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
-                                                 int64_t n_cols, partition_params pp,
-                                                 const int32_t* __restrict__ mark, const int32_t* __restrict__ mpos,
-                                                 const int32_t* __restrict__ hubflag, const int32_t* __restrict__ hpos,
-                                                 const int32_t* __restrict__ segbase,
+// Pass 3.  The tables: block starts, hub rows, their segments.
+template <int RPW>
+__global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
+                                                 int64_t n_cols, partition_params pp, row_tiles T,
+                                                 const int32_t* __restrict__ mark, const int32_t* __restrict__ hubflag,
+                                                 const int32_t* __restrict__ nseg,
                                                  int64_t n_rows, int32_t* __restrict__ blk_row,
                                                  int32_t* __restrict__ hub_rows, int32_t* __restrict__ hub_seg_ptr,
                                                  int32_t* __restrict__ seg_hub, int32_t* __restrict__ seg_begin,
@@ -286,45 +403,122 @@ __global__ void __launch_bounds__(256) k_compact(const int64_t* __restrict__ ind
                                                  int64_t max_blocks, int64_t max_hub, int64_t max_seg) {
   // The bounds only bite for a malformed indptr (the host then reports ISP_EBADCSR); they keep
   // every write inside the workspace in that case too.
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & (ISP_WAVE - 1);
-  if (i == 0) {
-    const int nb = mpos[n_rows], nh = hpos[n_rows];
-    if (nb <= max_blocks) blk_row[nb] = (int32_t)n_rows;
-    if (nh <= max_hub) hub_seg_ptr[nh] = segbase[n_rows];
-    ctr->n_blocks = nb;
-    ctr->n_hub = nh;
+  __shared__ int64_t s_ha[BS_THREADS], s_hb[BS_THREADS];
+  __shared__ int s_hs[BS_THREADS];
+  int mpos0, hpos0, seg0;
+  {
+    unsigned long long mh = 0;  // marks and hub rows of the earlier tiles, 32 bits each
+    int sg = 0;
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += BS_THREADS) {
+      mh += (unsigned long long)(unsigned)T.mark[t] << 32 | (unsigned)T.hub[t];
+      sg += T.seg[t];
+    }
+    unsigned long long tot;
+    block_exclusive_scan<unsigned long long>(mh, &tot);
+    mpos0 = (int)(tot >> 32);
+    hpos0 = (int)(unsigned)tot;
+    block_exclusive_scan<int>(sg, &seg0);
   }
-  const bool valid = i < n_rows;  // (no early exit: the wavefront handles its hub rows together)
-  if (valid && mark[i] && mpos[i] < max_blocks) blk_row[mpos[i]] = (int32_t)i;
-  const bool hub = valid && hubflag[i];
-  const int h = hub ? hpos[i] : 0, s0 = hub ? segbase[i] : 0;
-  const int64_t a = hub ? indptr[i] : 0, b = hub ? indptr[i + 1] : 0;
-  if (hub && h < max_hub) {
-    hub_rows[h] = (int32_t)i;
-    hub_seg_ptr[h] = s0;
-  }
-  for (unsigned long long hm = __ballot(hub); hm; hm &= hm - 1) {
-    const int src = __ffsll((long long)hm) - 1;
-    const int64_t ha = __shfl(a, src), hb = __shfl(b, src);
-    const int hh = __shfl(h, src), hs0 = __shfl(s0, src);
-    int64_t first, last;
-    wave_hub_pieces(indices, ha, hb, n_cols, pp, lane, &first, &last);
-    // the row's segments, in order of position: piece by piece (lane by lane), each piece in runs of seg_len
-    const int cnt = (int)((last - first + pp.seg_len - 1) / pp.seg_len);
-    int inc = cnt;
+  const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
+  for (int64_t base = r0; base < r1; base += (BS_THREADS / ISP_WAVE) * RPW) {
+    const int64_t i = base + (threadIdx.x / ISP_WAVE) * RPW + lane;
+    const bool valid = lane < RPW && i < r1;  // (no early exit: the wavefront handles its hub rows together)
+    const int m = valid ? mark[i] : 0;
+    const bool hub = valid && hubflag[i];
+    // one scan for the three positions (at most 256 marks and hub rows here)
+    unsigned long long tot;
+    const unsigned long long pos = block_exclusive_scan<unsigned long long>(
+        (unsigned long long)m << 48 | (unsigned long long)(hub ? 1 : 0) << 32 | (unsigned)(hub ? nseg[i] : 0), &tot);
+    const int mpos = mpos0 + (int)(pos >> 48), h = hpos0 + (int)(pos >> 32 & 0xffff), s0 = seg0 + (int)(unsigned)pos;
+    mpos0 += (int)(tot >> 48);
+    hpos0 += (int)(tot >> 32 & 0xffff);
+    seg0 += (int)(unsigned)tot;
+    if (m && mpos < max_blocks) blk_row[mpos] = (int32_t)i;
+    const int64_t a = hub ? indptr[i] : 0, b = hub ? indptr[i + 1] : 0;
+    if (hub && h < max_hub) {
+      hub_rows[h] = (int32_t)i;
+      hub_seg_ptr[h] = s0;
+    }
+    const int hx = (int)(pos >> 32 & 0xffff);  // the step's hub rows, shared out over the wavefronts
+    if (hub) { s_ha[hx] = a; s_hb[hx] = b; s_hs[hx] = s0; }
+    __syncthreads();
+    const int n_hubs = (int)(tot >> 32 & 0xffff), hh0 = hpos0 - n_hubs;
+    for (int hq = threadIdx.x / ISP_WAVE; hq < n_hubs; hq += BS_THREADS / ISP_WAVE) {
+      const int hh = hh0 + hq, hs0 = s_hs[hq];
+      int64_t first, last;
+      wave_hub_pieces(indices, s_ha[hq], s_hb[hq], n_cols, pp, lane, &first, &last);
+      // the row's segments, in order of position: piece by piece (lane by lane), each piece in runs of seg_len
+      const int cnt = (int)((last - first + pp.seg_len - 1) / pp.seg_len);
+      int inc = cnt;
 #pragma unroll
-    for (int o = 1; o < ISP_WAVE; o <<= 1) {
-      const int t = __shfl_up(inc, o);
-      if (lane >= o) inc += t;
+      for (int o = 1; o < ISP_WAVE; o <<= 1) {
+        const int t = __shfl_up(inc, o);
+        if (lane >= o) inc += t;
+      }
+      int64_t s = (int64_t)hs0 + inc - cnt;
+      for (int64_t q = first; q < last; q += pp.seg_len, ++s) {
+        if (s >= max_seg) continue;
+        seg_hub[s] = hh;
+        seg_begin[s] = (int32_t)q;
+        seg_key[s] = indices[q];
+      }
     }
-    int64_t s = (int64_t)hs0 + inc - cnt;
-    for (int64_t q = first; q < last; q += pp.seg_len, ++s) {
-      if (s >= max_seg) continue;
-      seg_hub[s] = hh;
-      seg_begin[s] = (int32_t)q;
-      seg_key[s] = indices[q];
-    }
+  }
+  if ((int)blockIdx.x == T.n - 1 && threadIdx.x == 0) {  // the last tile's ends are the totals
+    if (mpos0 <= max_blocks) blk_row[mpos0] = (int32_t)n_rows;
+    if (hpos0 <= max_hub) hub_seg_ptr[hpos0] = seg0;
+    ctr->n_blocks = mpos0;
+    ctr->n_hub = hpos0;
+    ctr->n_seg = seg0;
+  }
+}
+
+// Up to SO_SMALL segments: schedule order in one launch, every segment counting those before it (by first column, then
+// number).  SO_SMALL^2 comparisons are 1.5 us of the chip's vector ALUs; the radix sort below is five launches per
+// digit (a matrix of 1 M entries has about 5,000 segments: 100 us), a bitonic sort in one workgroup took 88 us.
+constexpr int SO_SMALL = 8192;
+constexpr int SO_WAVES = 16;  // wavefronts that share a segment's comparisons
+__global__ void __launch_bounds__(SO_WAVES * ISP_WAVE) k_seg_rank(const int32_t* __restrict__ key,
+                                                                  const build_counters* __restrict__ ctr,
+                                                                  int32_t* __restrict__ order) {
+  __shared__ __align__(16) int keys[SO_SMALL];
+  __shared__ int part[SO_WAVES][ISP_WAVE];
+  const int n = ctr->n_seg;
+  if (ctr->err || n > SO_SMALL) return;  // (a malformed matrix has no bounds to rely on)
+  if ((int)blockIdx.x * ISP_WAVE >= n) return;
+  const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x / ISP_WAVE;
+  const int n4 = (n + 3) & ~3;
+  for (int j = threadIdx.x; j < n4; j += SO_WAVES * ISP_WAVE) keys[j] = j < n ? key[j] : INT_MAX;
+  __syncthreads();
+  const int s = blockIdx.x * ISP_WAVE + lane;
+  const int k = s < n ? keys[s] : 0;
+  const int q = (n4 / 4 + SO_WAVES - 1) / SO_WAVES, j1 = (w + 1) * q < n4 / 4 ? (w + 1) * q : n4 / 4;
+  int rank = 0;
+  // keys of lower-numbered segments count when equal, higher-numbered ones only when smaller (columns are below
+  // 2^31 - 1): two loops around the 64 segments of this workgroup itself
+  const int4* __restrict__ k4 = reinterpret_cast<const int4*>(keys);
+  const int d0 = blockIdx.x * (ISP_WAVE / 4), d1 = d0 + ISP_WAVE / 4;
+  const int e1 = j1 < d0 ? j1 : d0, b2 = w * q > d1 ? w * q : d1;
+#pragma unroll 4
+  for (int j = w * q; j < e1; ++j) {
+    const int4 kj = k4[j];
+    rank += (kj.x <= k) + (kj.y <= k) + (kj.z <= k) + (kj.w <= k);
+  }
+#pragma unroll 4
+  for (int j = b2; j < j1; ++j) {
+    const int4 kj = k4[j];
+    rank += (kj.x < k) + (kj.y < k) + (kj.z < k) + (kj.w < k);
+  }
+  if (w == 0) {
+    for (int j = 4 * d0; j < 4 * d1 && j < n; ++j) rank += keys[j] < k + (j < s ? 1 : 0);
+  }
+  part[w][lane] = rank;
+  __syncthreads();
+  if (w == 0 && s < n) {
+#pragma unroll
+    for (int ww = 1; ww < SO_WAVES; ++ww) rank += part[ww][lane];
+    order[rank] = s;
   }
 }
 
@@ -369,7 +563,15 @@ __global__ void __launch_bounds__(256) k_item_desc(const int64_t* __restrict__ i
                                                    const int32_t* __restrict__ seg_hub,
                                                    const int32_t* __restrict__ seg_begin,
                                                    const int32_t* __restrict__ seg_order, int n_seg, int hub_t,
-                                                   int4* __restrict__ desc) {
+                                                   const build_counters* __restrict__ ctr, int64_t max_items,
+                                                   build_counters* host_ctr, int4* __restrict__ desc) {
+  // ctr: the counts are read there (they are not known on the host yet) and the counters are left in host_ctr
+  if (ctr) {
+    if (host_ctr && blockIdx.x == 0 && threadIdx.x == 0) *host_ctr = *ctr;
+    n_blocks = ctr->n_blocks;
+    n_seg = ctr->n_seg;
+    if (ctr->err || n_seg > SO_SMALL || (int64_t)n_blocks + n_seg > max_items) return;  // (the host sees to it)
+  }
   const int item = blockIdx.x * blockDim.x + threadIdx.x;
   if (item >= n_blocks + n_seg) return;
   int4 q;
@@ -488,9 +690,11 @@ __global__ void __launch_bounds__(256) k_regather_values(const int32_t* __restri
   if (q < nnz) values2[q] = values[src_pos[q]];
 }
 
+static_assert(sizeof(build_counters) <= host_slot::SIZE, "the counters fit a slot");
+
 // ---- workspace layout ------------------------------------------------------------------------------------
 struct ws_layout {
-  size_t counters, cost, hubflag, nseg, cum_cost, mark, mpos, hpos, segbase, scan_tmp;
+  size_t counters, cost, hubflag, nseg, mark, tile_cost, tile_hub, tile_seg, tile_mark, tile_stat;
   size_t blk_row, hub_rows, hub_seg_ptr, seg_hub, seg_begin, seg_key[2], seg_order[2], so_table, so_scanned, so_tmp;
   size_t inv_len, item_desc, partials, total;
   int64_t max_blocks, max_hub, max_seg;
@@ -515,12 +719,12 @@ ws_layout make_layout(int64_t n_rows, int64_t nnz, const partition_params& pp, s
   L.cost = take((size_t)(n_rows + 1) * 4);
   L.hubflag = take((size_t)(n_rows + 1) * 4);
   L.nseg = take((size_t)(n_rows + 1) * 4);
-  L.cum_cost = take((size_t)(n_rows + 1) * 8);
   L.mark = take((size_t)(n_rows + 1) * 4);
-  L.mpos = take((size_t)(n_rows + 1) * 4);
-  L.hpos = take((size_t)(n_rows + 1) * 4);
-  L.segbase = take((size_t)(n_rows + 1) * 4);
-  L.scan_tmp = take(isp_scan_tmp_bytes(n_rows + 1));
+  L.tile_cost = take((size_t)MAX_TILES * 8);
+  L.tile_hub = take((size_t)MAX_TILES * 4);
+  L.tile_seg = take((size_t)MAX_TILES * 4);
+  L.tile_mark = take((size_t)MAX_TILES * 4);
+  L.tile_stat = take((size_t)MAX_TILES * STATS * 8);
   L.blk_row = take((size_t)(max_blocks + 1) * 4);
   L.hub_rows = take((size_t)(max_hub + 1) * 4);
   L.hub_seg_ptr = take((size_t)(max_hub + 2) * 4);
@@ -644,17 +848,13 @@ struct partition_out {
 
 isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const int64_t* indptr, const int32_t* indices,
                            const partition_params& pp, char* base, const ws_layout& L, bool validate,
-                           int64_t force_row, hipStream_t s, partition_out* out) {
+                           int64_t force_row, hipStream_t s, partition_out* out, const int* flag = nullptr,
+                           int* host_flag = nullptr) {
   build_counters* ctr = (build_counters*)(base + L.counters);
   int32_t* cost = (int32_t*)(base + L.cost);
   int32_t* hubflag = (int32_t*)(base + L.hubflag);
   int32_t* nseg = (int32_t*)(base + L.nseg);
-  int64_t* cum_cost = (int64_t*)(base + L.cum_cost);
   int32_t* mark = (int32_t*)(base + L.mark);
-  int32_t* mpos = (int32_t*)(base + L.mpos);
-  int32_t* hpos = (int32_t*)(base + L.hpos);
-  int32_t* segbase = (int32_t*)(base + L.segbase);
-  void* scan_tmp = base + L.scan_tmp;
   int32_t* blk_row = (int32_t*)(base + L.blk_row);
   int32_t* hub_rows = (int32_t*)(base + L.hub_rows);
   int32_t* hub_seg_ptr = (int32_t*)(base + L.hub_seg_ptr);
@@ -663,70 +863,94 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   int32_t* seg_key[2] = {(int32_t*)(base + L.seg_key[0]), (int32_t*)(base + L.seg_key[1])};
   int32_t* seg_ord[2] = {(int32_t*)(base + L.seg_order[0]), (int32_t*)(base + L.seg_order[1])};
   const int32_t* seg_order = seg_ord[0];
+  int4* item_desc = (int4*)(base + L.item_desc);
 
-  k_zero_counters<<<1, 64, 0, s>>>(ctr);
+  // Few rows: one step of thin wavefronts per workgroup; else the rows the chip has tiles for.
+  const bool spread = n_rows <= MAX_TILES * (BS_THREADS / ISP_WAVE) * RPW_SMALL;
+  row_tiles T;
+  T.rows = spread ? (BS_THREADS / ISP_WAVE) * RPW_SMALL
+                  : ((n_rows + MAX_TILES - 1) / MAX_TILES + BS_THREADS - 1) / BS_THREADS * BS_THREADS;
+  T.n = n_rows > 0 ? (int)((n_rows + T.rows - 1) / T.rows) : 1;
+  T.cost = (int64_t*)(base + L.tile_cost);
+  T.hub = (int32_t*)(base + L.tile_hub);
+  T.seg = (int32_t*)(base + L.tile_seg);
+  T.mark = (int32_t*)(base + L.tile_mark);
+  T.stats = (unsigned long long*)(base + L.tile_stat);
+  k_zero_counters<<<1, 64, 0, s>>>(ctr, flag, host_flag);
   ISP_LAUNCH_CHECK();
-  const unsigned row_grid = (unsigned)((n_rows + 255) / 256);
-  if (n_rows > 0) {
-    k_row_pass<<<row_grid < 2048 ? row_grid : 2048, 256, 0, s>>>(indptr, indices, n_rows, n_cols, nnz, pp, cost,
-                                                                 hubflag, nseg, (float*)(base + L.inv_len), ctr);
-    ISP_LAUNCH_CHECK();
-  }
+  int grid1 = T.n;
   if (validate && nnz > 0) {
-    k_check_indices<<<2048, 256, 0, s>>>(indices, nnz, n_cols, ctr);
-    ISP_LAUNCH_CHECK();
+    const int64_t want = (nnz + 4095) / 4096;
+    if (want > grid1) grid1 = want < 2048 ? (int)want : (grid1 > 2048 ? grid1 : 2048);
   }
-  isp_status st;
-  if ((st = isp_scan_i32_to_i64(cost, cum_cost, n_rows, scan_tmp, s)) != ISP_OK) return st;
-  if (n_rows > 0) {
-    k_mark_rows<<<row_grid, 256, 0, s>>>(hubflag, n_rows, force_row, mark);
-    ISP_LAUNCH_CHECK();
-    // total short-row cost <= nnz + n_rows, so this many targets cover it
-    const int64_t n_bal = (nnz + (int64_t)pp.row_cost * n_rows) / pp.block_cost + 1;
-    k_mark_balanced<<<(unsigned)((n_bal + 255) / 256), 256, 0, s>>>(cum_cost, n_rows, n_bal, pp.block_cost, mark);
-    ISP_LAUNCH_CHECK();
-  }
-  if ((st = isp_scan_i32_to_i32(mark, mpos, n_rows, scan_tmp, s)) != ISP_OK) return st;
-  if ((st = isp_scan_i32_to_i32(hubflag, hpos, n_rows, scan_tmp, s)) != ISP_OK) return st;
-  if ((st = isp_scan_i32_to_i32(nseg, segbase, n_rows, scan_tmp, s)) != ISP_OK) return st;
-  k_compact<<<row_grid > 0 ? row_grid : 1, 256, 0, s>>>(indptr, indices, n_cols, pp, mark, mpos, hubflag, hpos, segbase,
-                                                       n_rows, blk_row, hub_rows, hub_seg_ptr, seg_hub, seg_begin,
-                                                       seg_key[0], ctr, L.max_blocks, L.max_hub, L.max_seg);
+#define ISP_GO(R)                                                                                                      \
+  k_row_pass<R><<<grid1, BS_THREADS, 0, s>>>(indptr, indices, n_rows, n_cols, nnz, pp, validate, T, cost, hubflag, nseg, \
+                                             (float*)(base + L.inv_len), ctr)
+  if (spread) ISP_GO(RPW_SMALL); else ISP_GO(RPW_LARGE);
+#undef ISP_GO
   ISP_LAUNCH_CHECK();
+  k_mark_rows<<<T.n + 1, BS_THREADS, 0, s>>>(cost, hubflag, n_rows, pp.block_cost, force_row, T, mark, ctr);
+  ISP_LAUNCH_CHECK();
+#define ISP_GO(R)                                                                                                     \
+  k_compact<R><<<T.n, BS_THREADS, 0, s>>>(indptr, indices, n_cols, pp, T, mark, hubflag, nseg, n_rows, blk_row, hub_rows, \
+                                          hub_seg_ptr, seg_hub, seg_begin, seg_key[0], ctr, L.max_blocks, L.max_hub,  \
+                                          L.max_seg)
+  if (spread) ISP_GO(RPW_SMALL); else ISP_GO(RPW_LARGE);
+#undef ISP_GO
+  ISP_LAUNCH_CHECK();
+
+  // Matrices of up to SMALL_NNZ entries: the rest is enqueued right behind, before the counts are known on the host (a
+  // round trip through the host costs as much as three launches); more segments than the ranking takes, or a
+  // partition beyond its bounds, leave it to the steps below.
   build_counters& h = out->h;
-  ISP_HIP(hipMemcpyAsync(&h, ctr, sizeof(h), hipMemcpyDeviceToHost, s));
+  const bool small = nnz <= SMALL_NNZ;
+  const int64_t max_items = L.max_blocks + L.max_seg;
+  host_slot slot;  // pinned: the device writes the counters there itself
+  build_counters* host_ctr = small ? (build_counters*)slot.get() : nullptr;
+  if (small) {
+    k_seg_rank<<<SO_SMALL / ISP_WAVE, SO_WAVES * ISP_WAVE, 0, s>>>(seg_key[0], ctr, seg_ord[0]);
+    ISP_LAUNCH_CHECK();
+    k_item_desc<<<(unsigned)((max_items + 255) / 256), 256, 0, s>>>(indptr, blk_row, 0, hub_rows, hub_seg_ptr, seg_hub,
+                                                                  seg_begin, seg_ord[0], 0, pp.hub_t, ctr, max_items,
+                                                                  host_ctr, item_desc);
+    ISP_LAUNCH_CHECK();
+  }
+  if (!host_ctr) ISP_HIP(hipMemcpyAsync(&h, ctr, sizeof(h), hipMemcpyDeviceToHost, s));
   ISP_HIP(hipStreamSynchronize(s));
+  if (host_ctr) h = *host_ctr;
   if (h.err & 1) return isp_fail(ISP_EBADCSR, "indptr is not a monotone offset array from 0 to nnz");
   if (h.err & 2) return isp_fail(ISP_EBADCSR, "a column index lies outside [0, n_cols)");
   if (h.n_blocks > L.max_blocks || h.n_hub > L.max_hub || h.n_seg > L.max_seg)
     return isp_fail(ISP_EINVAL, "internal: partition exceeds its bounds (%d/%lld blocks, %d/%lld hubs, %d/%lld segs)",
                     h.n_blocks, (long long)L.max_blocks, h.n_hub, (long long)L.max_hub, h.n_seg, (long long)L.max_seg);
-  if (h.n_seg > 0) {  // schedule order: by first column, equal ones in order of position (stable)
-    const int n_tiles = (h.n_seg + SO_TILE - 1) / SO_TILE;
-    int32_t* table = (int32_t*)(base + L.so_table);
-    int32_t* scanned = (int32_t*)(base + L.so_scanned);
-    int bits = 1;  // the keys are columns (< n_cols)
-    while (bits < 31 && ((int64_t)1 << bits) < n_cols) ++bits;
-    const int n_pass = (bits + 7) / 8;
-    for (int pass = 0; pass < n_pass; ++pass) {
-      const int32_t* kin = seg_key[pass & 1];
-      const int32_t* vin = pass == 0 ? nullptr : seg_ord[pass & 1];
-      k_seg_hist<<<n_tiles, SO_TILE, 0, s>>>(kin, h.n_seg, 8 * pass, n_tiles, table);
-      ISP_LAUNCH_CHECK();
-      if ((st = isp_scan_i32_to_i32(table, scanned, (int64_t)SO_RADIX * n_tiles, base + L.so_tmp, s)) != ISP_OK) return st;
-      k_seg_scatter<<<n_tiles, SO_TILE, 0, s>>>(kin, vin, h.n_seg, 8 * pass, n_tiles, scanned, seg_key[(pass + 1) & 1],
-                                                seg_ord[(pass + 1) & 1]);
+  if (!small || h.n_seg > SO_SMALL) {
+    if (h.n_seg > 0) {  // schedule order: by first column, equal ones in order of position (stable)
+      const int n_tiles = (h.n_seg + SO_TILE - 1) / SO_TILE;
+      int32_t* table = (int32_t*)(base + L.so_table);
+      int32_t* scanned = (int32_t*)(base + L.so_scanned);
+      int bits = 1;  // the keys are columns (< n_cols)
+      while (bits < 31 && ((int64_t)1 << bits) < n_cols) ++bits;
+      const int n_pass = (bits + 7) / 8;
+      for (int pass = 0; pass < n_pass; ++pass) {
+        const int32_t* kin = seg_key[pass & 1];
+        const int32_t* vin = pass == 0 ? nullptr : seg_ord[pass & 1];
+        k_seg_hist<<<n_tiles, SO_TILE, 0, s>>>(kin, h.n_seg, 8 * pass, n_tiles, table);
+        ISP_LAUNCH_CHECK();
+        isp_status st;
+        if ((st = isp_scan_i32_to_i32(table, scanned, (int64_t)SO_RADIX * n_tiles, base + L.so_tmp, s)) != ISP_OK) return st;
+        k_seg_scatter<<<n_tiles, SO_TILE, 0, s>>>(kin, vin, h.n_seg, 8 * pass, n_tiles, scanned, seg_key[(pass + 1) & 1],
+                                                  seg_ord[(pass + 1) & 1]);
+        ISP_LAUNCH_CHECK();
+      }
+      seg_order = seg_ord[n_pass & 1];
+    }
+    if (h.n_blocks + h.n_seg > 0) {
+      k_item_desc<<<(unsigned)((h.n_blocks + h.n_seg + 255) / 256), 256, 0, s>>>(indptr, blk_row, h.n_blocks, hub_rows,
+                                                                               hub_seg_ptr, seg_hub, seg_begin, seg_order,
+                                                                               h.n_seg, pp.hub_t, nullptr, 0, nullptr,
+                                                                               item_desc);
       ISP_LAUNCH_CHECK();
     }
-    seg_order = seg_ord[n_pass & 1];
-  }
-
-  int4* item_desc = (int4*)(base + L.item_desc);
-  if (h.n_blocks + h.n_seg > 0) {
-    k_item_desc<<<(unsigned)((h.n_blocks + h.n_seg + 255) / 256), 256, 0, s>>>(indptr, blk_row, h.n_blocks, hub_rows,
-                                                                             hub_seg_ptr, seg_hub, seg_begin, seg_order,
-                                                                             h.n_seg, pp.hub_t, item_desc);
-    ISP_LAUNCH_CHECK();
   }
   out->blk_row = blk_row; out->hub_rows = hub_rows; out->hub_seg_ptr = hub_seg_ptr; out->seg_hub = seg_hub;
   out->seg_begin = seg_begin; out->hubflag = hubflag; out->seg_order = seg_order; out->item_desc = item_desc;
@@ -833,7 +1057,7 @@ isp_status isp_refresh_packed_values(isp_csr* A, hipStream_t s) {
 
 isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const int64_t* indptr,
                             const int32_t* indices, const float* values, void* ws, size_t ws_bytes, bool validate,
-                            hipStream_t s, isp_csr** out) {
+                            hipStream_t s, isp_csr** out, const int* flag, int* host_flag) {
   const partition_params pp = get_params(n_rows, n_cols, nnz);
   const ws_layout L = make_layout(n_rows, nnz, pp);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, pp);
@@ -847,7 +1071,7 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   if (((uintptr_t)ws & 255) != 0) return isp_fail(ISP_EINVAL, "workspace must be 256-byte aligned");
   char* base = (char*)ws;
   partition_out po;
-  isp_status st = build_partition(n_rows, n_cols, nnz, indptr, indices, pp, base, L, validate, -1, s, &po);
+  isp_status st = build_partition(n_rows, n_cols, nnz, indptr, indices, pp, base, L, validate, -1, s, &po, flag, host_flag);
   if (st != ISP_OK) return st;
 
   int device = 0;

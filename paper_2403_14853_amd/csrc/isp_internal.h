@@ -122,9 +122,11 @@ isp_status isp_scan_i32_to_i32(const int32_t* in, int32_t* out, int64_t n, void*
 
 // ---- partition (csr_build.hip) ---------------------------------------------------------------
 size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz);
+// flag / host_flag (pinned), optional: *flag as earlier launches on s leave it has arrived in *host_flag on return.
 isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const int64_t* indptr,
                             const int32_t* indices, const float* values, void* ws, size_t ws_bytes,
-                            bool validate, hipStream_t s, isp_csr** out);
+                            bool validate, hipStream_t s, isp_csr** out, const int* flag = nullptr,
+                            int* host_flag = nullptr);
 // Copy A's (rewritten) values into the packed SpMM layout's own value array again.
 isp_status isp_refresh_packed_values(isp_csr* A, hipStream_t s);
 

@@ -1,43 +1,14 @@
 // Device-wide exclusive prefix sums used by the CSR partition and the transpose
 // (integer bookkeeping only).  Three launches: per-tile sums, a single-workgroup scan of the
 // tile sums, per-tile scan with the tile offset added.
-#include "isp_internal.h"
+#include "block_scan.h"
 
 namespace {
+using namespace isp_dev;
 
-constexpr int SCAN_THREADS = 256;
+constexpr int SCAN_THREADS = BS_THREADS;
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
-
-template <typename T>
-__device__ inline T wave_inclusive_scan(T v, int lane) {
-#pragma unroll
-  for (int o = 1; o < ISP_WAVE; o <<= 1) {
-    T t = __shfl_up(v, o);
-    if (lane >= o) v += t;
-  }
-  return v;
-}
-
-// Exclusive scan of one value per thread across the workgroup; returns the exclusive prefix and
-// writes the workgroup total to *total (same value in every thread).
-template <typename T>
-__device__ inline T block_exclusive_scan(T v, T* total) {
-  __shared__ T wave_tot[SCAN_THREADS / ISP_WAVE];
-  const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x / ISP_WAVE;
-  T inc = wave_inclusive_scan(v, lane);
-  __syncthreads();  // protect wave_tot against a previous call's readers
-  if (lane == ISP_WAVE - 1) wave_tot[w] = inc;
-  __syncthreads();
-  T base = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < SCAN_THREADS / ISP_WAVE; ++i) {
-    if (i < w) base += wave_tot[i];
-    tot += wave_tot[i];
-  }
-  *total = tot;
-  return base + inc - v;
-}
 
 template <typename TI, typename TO>
 __global__ void __launch_bounds__(SCAN_THREADS) scan_tile_sums(const TI* __restrict__ in, TO* __restrict__ tile_sum,

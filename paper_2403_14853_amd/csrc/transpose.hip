@@ -3,54 +3,91 @@
 //
 // "Stable" = entries of one column keep their order of appearance in A, which makes the result
 // unique and lets it be compared bit for bit.  It is computed as a least-significant-digit radix
-// sort of the column indices (digits of up to 8 bits) that carries source position, source row and value as
+// sort of the column indices (digits of up to 9 bits) that carries source position, source row and value as
 // payload; every pass is a stable counting sort: per-tile digit histograms -> exclusive scan over
 // (digit, tile) -> scatter with ranks taken in source order.  Integer work only, no atomics on
 // anything order-dependent.
-#include "isp_internal.h"
+#include "block_scan.h"
+#include "host_slot.h"
 
 namespace {
+using namespace isp_dev;
 
 constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / ISP_WAVE;
-constexpr int RS_ROUNDS = 16;                       // keys per lane
-constexpr int RS_WAVE_KEYS = RS_ROUNDS * ISP_WAVE;  // contiguous keys owned by one wave
-constexpr int RS_TILE = RS_WAVE_KEYS * RS_WAVES;    // keys per workgroup
-constexpr int RS_RADIX = 256;
+// Keys per lane: a workgroup walks them in order, so small matrices get shorter tiles (1 M entries: 4 keys instead of 16
+// spread a pass over 977 workgroups).
+constexpr int RS_ROUNDS_SMALL = 4, RS_ROUNDS_LARGE = 16;
+constexpr int rs_tile(int rounds) { return rounds * RS_THREADS; }  // keys per workgroup
+constexpr int64_t RS_SMALL_NNZ = 4 << 20;
+constexpr int RS_MAX_BITS = 9;                      // bits per digit (512 counters per wave)
 
-// Row that owns the first entry of every sort tile: the smallest r with indptr[r + 1] > tile * RS_TILE.
-__global__ void __launch_bounds__(256) k_tile_rows(const int64_t* __restrict__ indptr, int64_t n_rows, int n_tiles,
-                                                   int32_t* __restrict__ tile_row) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_tiles) return;
-  const int64_t q = (int64_t)t * RS_TILE;
-  int64_t lo = 0, hi = n_rows - 1;  // q < nnz = indptr[n_rows], so the answer exists
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (indptr[mid + 1] > q) hi = mid; else lo = mid + 1;
-  }
-  tile_row[t] = (int32_t)lo;
-}
-
-// Per-tile digit histogram; table is digit-major: table[digit * n_tiles + tile].
+// Per-tile digit histogram; table is digit-major: table[digit * n_tiles + tile].  FIRST: also finds the row that owns
+// the tile's first entry (the smallest r with indptr[r + 1] > tile * RS_TILE) and clears *flag.
+template <bool FIRST, int ROUNDS>
 __global__ void __launch_bounds__(RS_THREADS) k_radix_hist(const int32_t* __restrict__ keys, int64_t n, int shift,
-                                                           int mask, int n_tiles, int32_t* __restrict__ table) {
-  __shared__ int hist[RS_RADIX];
-  hist[threadIdx.x] = 0;
+                                                           int bits, int n_tiles, int32_t* __restrict__ table,
+                                                           const int64_t* __restrict__ indptr, int64_t n_rows,
+                                                           int32_t* __restrict__ tile_row, int* __restrict__ flag) {
+  __shared__ int hist[1 << RS_MAX_BITS];
+  constexpr int RS_TILE = rs_tile(ROUNDS);
+  const int radix = 1 << bits;
+  for (int i = threadIdx.x; i < radix; i += RS_THREADS) hist[i] = 0;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * RS_TILE;
+  if (FIRST) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
+    int64_t lo = 0, hi = n_rows - 1;  // base < nnz = indptr[n_rows], so the answer exists
+    while (lo < hi) {                 // 256 probes at a time: every step is a trip to memory
+      const int64_t step = (hi - lo + RS_THREADS) / RS_THREADS;
+      const int64_t last = lo + (threadIdx.x + 1) * step - 1, r = last < hi ? last : hi;  // the end of this thread's part
+      const int c = __syncthreads_count(indptr[r + 1] <= base);  // parts that lie before the answer
+      lo += c * step;
+      hi = lo + step - 1 < hi ? lo + step - 1 : hi;
+    }
+    if (threadIdx.x == 0) tile_row[blockIdx.x] = (int32_t)lo;
+  }
   for (int i = threadIdx.x; i < RS_TILE; i += RS_THREADS) {
     const int64_t q = base + i;
-    if (q < n) atomicAdd(&hist[(keys[q] >> shift) & mask], 1);
+    if (q < n) atomicAdd(&hist[(keys[q] >> shift) & (radix - 1)], 1);
   }
   __syncthreads();
-  table[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = hist[threadIdx.x];
+  for (int i = threadIdx.x; i < radix; i += RS_THREADS) table[(int64_t)i * n_tiles + blockIdx.x] = hist[i];
+}
+
+// One workgroup per digit: exclusive prefix of its counts over the tiles, in place, and the digit's total.  (The prefix
+// over the digits is a few hundred numbers, which every scatter workgroup adds up for itself: one launch instead of
+// the three of a device-wide scan.)
+__global__ void __launch_bounds__(RS_THREADS) k_digit_scan(int32_t* __restrict__ table, int n_tiles,
+                                                           int32_t* __restrict__ digit_total) {
+  int32_t* __restrict__ t = table + (int64_t)blockIdx.x * n_tiles;
+  int carry = 0;
+  constexpr int PER = 8;
+  for (int base = 0; base < n_tiles; base += RS_THREADS * PER) {
+    int v[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int i = base + (int)threadIdx.x * PER + k;
+      v[k] = i < n_tiles ? t[i] : 0;
+      sum += v[k];
+    }
+    int tot;
+    int run = carry + block_exclusive_scan<int>(sum, &tot);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int i = base + (int)threadIdx.x * PER + k;
+      if (i < n_tiles) t[i] = run;
+      run += v[k];
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) digit_total[blockIdx.x] = carry;
 }
 
 // Stable scatter of one pass; the records travel as four parallel arrays (column key, source position,
 // source row, value), so the last pass leaves perm, the source rows and the values of A^T where they
 // belong and nothing has to be gathered afterwards.
-// Wave w of a workgroup owns the contiguous keys [tile + w * RS_WAVE_KEYS, +RS_WAVE_KEYS) and walks them
+// Wave w of a workgroup owns the contiguous keys [tile + w * ROUNDS * 64, + ROUNDS * 64) and walks them
 // 64 at a time in source order, so a key's rank among equal digits = (equal digits in earlier tiles:
 // scanned table) + (in earlier waves of the tile) + (earlier rounds of this wave) + (lower lanes of this
 // round).  The tile is first put in digit order in LDS and written out from there, which turns the
@@ -58,20 +95,24 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_hist(const int32_t* __rest
 // FIRST: the input is the CSR itself: keys = indices, source position = index, value = values (val_in), and
 // the source rows are rebuilt per tile from the row offsets: every row that starts inside the tile marks its
 // first position in LDS, a running maximum spreads the marks (tile_row = the row owning the tile's first entry).
-template <bool FIRST, bool HAS_VAL>
+// BITS: most bits a digit of this launch may have (sizes the counters in LDS).
+template <bool FIRST, bool HAS_VAL, int BITS, int ROUNDS>
 __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
     const int32_t* __restrict__ keys_in, const int32_t* __restrict__ src_in, const int32_t* __restrict__ row_in,
     const int32_t* __restrict__ val_in, const int64_t* __restrict__ indptr, int64_t n_rows,
     const int32_t* __restrict__ tile_row, int64_t n, int shift, int mask, int n_tiles,
-    const int32_t* __restrict__ table_scanned, int32_t* __restrict__ keys_out, int32_t* __restrict__ src_out,
+    const int32_t* __restrict__ table_scanned, const int32_t* __restrict__ digit_total, int32_t* __restrict__ keys_out, int32_t* __restrict__ src_out,
     int32_t* __restrict__ row_out, int32_t* __restrict__ val_out) {
-  __shared__ volatile int wave_cnt[RS_WAVES][RS_RADIX];
-  __shared__ int wave_base[RS_WAVES][RS_RADIX];  // tile-local sorted position of each wave's first key of a digit
-  __shared__ int delta[RS_RADIX];                // output position minus tile-local position, per digit
+  constexpr int RADIX = 1 << BITS;
+  constexpr int RS_ROUNDS = ROUNDS, RS_WAVE_KEYS = ROUNDS * ISP_WAVE;  // contiguous keys owned by one wave
+  constexpr int RS_TILE = rs_tile(ROUNDS);
+  __shared__ volatile int wave_cnt[RS_WAVES][RADIX];
+  __shared__ int wave_base[RS_WAVES][RADIX];  // tile-local sorted position of each wave's first key of a digit
+  __shared__ int delta[RADIX];                // output position minus tile-local position, per digit
   __shared__ int wave_tot[RS_WAVES];
   __shared__ int buf[RS_TILE];
   const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x / ISP_WAVE;
-  for (int i = threadIdx.x; i < RS_WAVES * RS_RADIX; i += RS_THREADS) (&wave_cnt[0][0])[i] = 0;
+  for (int i = threadIdx.x; i < RS_WAVES * RADIX; i += RS_THREADS) (&wave_cnt[0][0])[i] = 0;
   const int64_t tile_base = (int64_t)blockIdx.x * RS_TILE;
   const int tile_count = (int)((n - tile_base < RS_TILE) ? n - tile_base : RS_TILE);
   if (FIRST) {
@@ -87,7 +128,7 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
       atomicMax(&buf[o], (int)r);
     }
     __syncthreads();
-    // running maximum over the tile: thread t owns positions [16 t, 16 t + 16)
+    // running maximum over the tile: thread t owns ROUNDS consecutive positions
     int loc[RS_ROUNDS], run = 0;
 #pragma unroll
     for (int k = 0; k < RS_ROUNDS; ++k) {
@@ -134,7 +175,7 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
     const int dg = (key[r] >> shift) & mask;
     unsigned long long m = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < BITS; ++b) {
       const unsigned long long bal = __ballot((dg >> b) & 1);
       m &= ((dg >> b) & 1) ? bal : ~bal;
     }
@@ -144,25 +185,37 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
     if (valid && (m & lt_mask) == 0) wave_cnt[w][dg] = before + __popcll(m);  // lowest lane of the group
   }
   __syncthreads();
-  {  // thread t owns digit t: exclusive scan of the tile's digit counts -> where each digit starts in the tile
-    const int dg = threadIdx.x;
-    int cnt[RS_WAVES], tot = 0;
+  {  // thread t owns digits t * PER ...: exclusive scan of the tile's digit counts -> where each digit starts in the tile
+    constexpr int PER = RADIX / RS_THREADS > 0 ? RADIX / RS_THREADS : 1;
+    int cnt[PER][RS_WAVES], tot[PER], all[PER], sum = 0, sum_all = 0;
 #pragma unroll
-    for (int ww = 0; ww < RS_WAVES; ++ww) { cnt[ww] = wave_cnt[ww][dg]; tot += cnt[ww]; }
-    int inc = tot;
+    for (int k = 0; k < PER; ++k) {
+      const int dg = threadIdx.x * PER + k;
+      tot[k] = all[k] = 0;
+      if (dg < RADIX) {
 #pragma unroll
-    for (int o = 1; o < ISP_WAVE; o <<= 1) {
-      const int t = __shfl_up(inc, o);
-      if (lane >= o) inc += t;
+        for (int ww = 0; ww < RS_WAVES; ++ww) { cnt[k][ww] = wave_cnt[ww][dg]; tot[k] += cnt[k][ww]; }
+        if (dg <= mask) all[k] = digit_total[dg];
+      }
+      sum += tot[k];
+      sum_all += all[k];
     }
-    if (lane == ISP_WAVE - 1) wave_tot[w] = inc;
-    __syncthreads();
-    int start = inc - tot;
-    for (int ww = 0; ww < w; ++ww) start += wave_tot[ww];
-    delta[dg] = table_scanned[(int64_t)dg * n_tiles + blockIdx.x] - start;
-    int run = start;
+    int t0;
+    int start = block_exclusive_scan<int>(sum, &t0);
+    int before = block_exclusive_scan<int>(sum_all, &t0);  // entries with a smaller digit, in all tiles
 #pragma unroll
-    for (int ww = 0; ww < RS_WAVES; ++ww) { wave_base[ww][dg] = run; run += cnt[ww]; }
+    for (int k = 0; k < PER; ++k) {
+      const int dg = threadIdx.x * PER + k;
+      if (dg < RADIX) {
+        const int prior = dg <= mask ? table_scanned[(int64_t)dg * n_tiles + blockIdx.x] : 0;
+        delta[dg] = before + prior - start;
+        int run = start;
+#pragma unroll
+        for (int ww = 0; ww < RS_WAVES; ++ww) { wave_base[ww][dg] = run; run += cnt[k][ww]; }
+      }
+      start += tot[k];
+      before += all[k];
+    }
   }
   __syncthreads();
   // keys: into digit order in LDS, then out; remember both positions for the other arrays
@@ -253,25 +306,24 @@ __global__ void __launch_bounds__(256) k_compare_pattern(const int64_t* __restri
   if (__any(bad) && (threadIdx.x & (ISP_WAVE - 1)) == 0) *differs = 1;  // (plain store of the same value from any wave)
 }
 
-__global__ void k_zero_int(int* p) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0;
-}
-
 __global__ void __launch_bounds__(256) k_fill_i64(int64_t* __restrict__ a, int64_t n, int64_t v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) a[i] = v;
 }
 
 struct t_layout {
-  size_t t_indptr, t_indices, perm, t_values, set[2][4], tile_row, table, table_scanned, scan_tmp, part, total;
+  size_t t_indptr, t_indices, perm, t_values, set[2][4], tile_row, table, digit_total, flag, part, total;
   int64_t n_tiles;
+  bool small;  // RS_ROUNDS_SMALL keys per lane
 };
 
 t_layout make_layout(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_values) {
   t_layout L;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += isp_align(bytes); return o; };
-  L.n_tiles = (nnz + RS_TILE - 1) / RS_TILE;
+  L.small = nnz <= RS_SMALL_NNZ;
+  const int tile = rs_tile(L.small ? RS_ROUNDS_SMALL : RS_ROUNDS_LARGE);
+  L.n_tiles = (nnz + tile - 1) / tile;
   const size_t e = (size_t)(nnz + 1) * 4;
   L.t_indptr = take((size_t)(n_cols + 1) * 8);
   L.t_indices = take(e);
@@ -281,10 +333,9 @@ t_layout make_layout(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_value
   for (int k = 0; k < 2; ++k)
     for (int a = 0; a < 4; ++a) L.set[k][a] = take(a == 3 && !has_values ? 0 : e);
   L.tile_row = take((size_t)(L.n_tiles + 1) * 4);
-  const int64_t tbl = (int64_t)RS_RADIX * L.n_tiles;
-  L.table = take((size_t)(tbl + 1) * 4);
-  L.table_scanned = take((size_t)(tbl + 1) * 4);
-  L.scan_tmp = take(isp_scan_tmp_bytes(tbl + 1));
+  L.table = take((size_t)(((int64_t)L.n_tiles << RS_MAX_BITS) + 1) * 4);
+  L.digit_total = take((size_t)(1 << RS_MAX_BITS) * 4);
+  L.flag = take(4);
   L.part = take(isp_partition_workspace(n_cols, n_rows, nnz));  // (A^T: n_cols rows, n_rows columns)
   L.total = off;
   return L;
@@ -311,8 +362,8 @@ isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_
   float* t_values = has_values ? (float*)(base + L.t_values) : nullptr;
   int32_t* tile_row = (int32_t*)(base + L.tile_row);
   int32_t* table = (int32_t*)(base + L.table);
-  int32_t* table_scanned = (int32_t*)(base + L.table_scanned);
-  void* scan_tmp = base + L.scan_tmp;
+  int32_t* digit_total = (int32_t*)(base + L.digit_total);
+  int* differs = (int*)(base + L.flag);
 
   if (nnz == 0) {
     k_fill_i64<<<(unsigned)((n_cols + 1 + 255) / 256), 256, 0, s>>>(t_indptr, n_cols + 1, 0);
@@ -320,19 +371,25 @@ isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_
   } else {
     int bits = 1;
     while (bits < 31 && ((int64_t)1 << bits) < n_cols) ++bits;
-    const int n_pass = (bits + 7) / 8;  // digits of at most 8 bits (5-, 6- and 7-bit digits measured slower)
+    // Digits of at most 8 bits, on small matrices 9 where that saves a pass (17 and 18 bits; large ones write shorter
+    // runs per digit then: 115 M entries, 18 bits, 6.9 ms in three passes, 7.6 in two; 5-, 6- and 7-bit digits
+    // measured slower too).
+    const int n_pass = L.small && (bits + 8) / 9 < (bits + 7) / 8 ? (bits + 8) / 9 : (bits + 7) / 8;
     const int n_tiles = (int)L.n_tiles;
-    k_tile_rows<<<(n_tiles + 255) / 256, 256, 0, s>>>(v.indptr, n_rows, n_tiles, tile_row);
-    ISP_LAUNCH_CHECK();
     const int32_t* in[4] = {v.indices, nullptr, nullptr, (const int32_t*)v.values};
     for (int pass = 0; pass < n_pass; ++pass) {
       // digits of about equal width: pass p takes bits [p * bits / n_pass, (p + 1) * bits / n_pass)
       const int shift = pass * bits / n_pass;
-      const int mask = (1 << ((pass + 1) * bits / n_pass - shift)) - 1;
-      k_radix_hist<<<n_tiles, RS_THREADS, 0, s>>>(in[0], nnz, shift, mask, n_tiles, table);
+      const int width = (pass + 1) * bits / n_pass - shift;
+      const int mask = (1 << width) - 1;
+#define ISP_GO(F, R)                                                                                                 \
+  k_radix_hist<F, R><<<n_tiles, RS_THREADS, 0, s>>>(in[0], nnz, shift, width, n_tiles, table, v.indptr, n_rows, tile_row, differs)
+      if (L.small) { if (pass == 0) ISP_GO(true, RS_ROUNDS_SMALL); else ISP_GO(false, RS_ROUNDS_SMALL); }
+      else { if (pass == 0) ISP_GO(true, RS_ROUNDS_LARGE); else ISP_GO(false, RS_ROUNDS_LARGE); }
+#undef ISP_GO
       ISP_LAUNCH_CHECK();
-      isp_status st = isp_scan_i32_to_i32(table, table_scanned, (int64_t)RS_RADIX * n_tiles, scan_tmp, s);
-      if (st != ISP_OK) return st;
+      k_digit_scan<<<1 << width, RS_THREADS, 0, s>>>(table, n_tiles, digit_total);
+      ISP_LAUNCH_CHECK();
       int32_t* out[4];
       for (int a = 0; a < 4; ++a) out[a] = (int32_t*)(base + L.set[pass & 1][a]);
       if (pass == n_pass - 1) {  // the last pass writes A^T's arrays; its keys still go to the set (for the offsets)
@@ -340,11 +397,17 @@ isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_
         out[2] = t_indices;
         out[3] = (int32_t*)t_values;
       }
-#define ISP_GO(F, HV)                                                                                             \
-  k_radix_scatter<F, HV><<<n_tiles, RS_THREADS, 0, s>>>(in[0], in[1], in[2], in[3], v.indptr, n_rows, tile_row, nnz, shift, mask, \
-                                                        n_tiles, table_scanned, out[0], out[1], out[2], out[3])
-      if (pass == 0) { if (has_values) ISP_GO(true, true); else ISP_GO(true, false); }
-      else { if (has_values) ISP_GO(false, true); else ISP_GO(false, false); }
+#define ISP_GO(F, HV, B, R)                                                                                          \
+  k_radix_scatter<F, HV, B, R><<<n_tiles, RS_THREADS, 0, s>>>(in[0], in[1], in[2], in[3], v.indptr, n_rows, tile_row, nnz, shift, \
+                                                           mask, n_tiles, table, digit_total, out[0], out[1], out[2], out[3])
+#define ISP_GO2(F, HV)                                                                                               \
+  do {                                                                                                               \
+    if (L.small) { if (width > 8) ISP_GO(F, HV, 9, RS_ROUNDS_SMALL); else ISP_GO(F, HV, 8, RS_ROUNDS_SMALL); }          \
+    else ISP_GO(F, HV, 8, RS_ROUNDS_LARGE);                                                                          \
+  } while (0)
+      if (pass == 0) { if (has_values) ISP_GO2(true, true); else ISP_GO2(true, false); }
+      else { if (has_values) ISP_GO2(false, true); else ISP_GO2(false, false); }
+#undef ISP_GO2
 #undef ISP_GO
       ISP_LAUNCH_CHECK();
       for (int a = 0; a < 4; ++a) in[a] = out[a];
@@ -352,22 +415,24 @@ isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_
     k_col_offsets<<<(unsigned)((nnz + 255) / 256), 256, 0, s>>>(in[0], nnz, n_cols, t_indptr);
     ISP_LAUNCH_CHECK();
   }
-  // Is the pattern symmetric (A^T's structure identical to A's)?  The flag lives in the sort's histogram table,
-  // which is free by now, and is read back with the counters of the partition build below.
-  int* differs = (int*)table;
+  // Is the pattern symmetric (A^T's structure identical to A's)?  (The first histogram has cleared the flag.)
   const bool square = n_rows == n_cols && nnz > 0;
   if (square) {
-    k_zero_int<<<1, 64, 0, s>>>(differs);
-    ISP_LAUNCH_CHECK();
     k_compare_pattern<<<2048, 256, 0, s>>>(v.indptr, t_indptr, n_rows, v.indices, t_indices, nnz, differs);
     ISP_LAUNCH_CHECK();
   }
   isp_csr* At = nullptr;
-  isp_status st = isp_build_handle(n_cols, n_rows, nnz, t_indptr, t_indices, t_values, base + L.part,
-                                   ws_bytes - L.part, false, s, &At);
-  if (st != ISP_OK) return st;
+  isp_status st;
   int h_differs = 1;
-  if (square) {
+  host_slot slot;
+  int* host_flag = square ? (int*)slot.get() : nullptr;
+  // (the symmetric-pattern flag comes to the host with the partition's counters)
+  st = isp_build_handle(n_cols, n_rows, nnz, t_indptr, t_indices, t_values, base + L.part, ws_bytes - L.part, false, s, &At,
+                        differs, host_flag);
+  if (st != ISP_OK) return st;
+  if (host_flag) {
+    h_differs = *host_flag;
+  } else if (square) {
     ISP_HIP(hipMemcpyAsync(&h_differs, differs, sizeof(int), hipMemcpyDeviceToHost, s));
     ISP_HIP(hipStreamSynchronize(s));
   }

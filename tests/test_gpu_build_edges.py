@@ -1,0 +1,77 @@
+"""Handle building and transposition at the sizes where their kernels change shape: row counts around a tile of rows and
+around the count from which tiles grow, entry counts around a tile of keys, column counts around a digit boundary, and more
+hub segments than the one-launch ordering takes."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2403_14853_amd as isp
+from gpu_util import assert_close, build, dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _random(n_rows, n_cols, nnz, seed, hub=0):
+    """nnz entries in random rows, columns in no order; `hub` of them in the second row."""
+    rng = np.random.default_rng(seed)
+    rows = np.sort(np.concatenate([rng.integers(0, n_rows, nnz - hub), np.full(hub, min(1, n_rows - 1))]))
+    indptr = np.zeros(n_rows + 1, np.int64)
+    np.cumsum(np.bincount(rows, minlength=n_rows), out=indptr[1:])
+    indices = rng.integers(0, n_cols, nnz).astype(np.int32)
+    if hub:  # the cuts look for sorted columns
+        a, b = indptr[min(1, n_rows - 1)], indptr[min(1, n_rows - 1) + 1]
+        indices[a:b] = np.sort(indices[a:b])
+    return indptr, indices, rng.standard_normal(nnz).astype(np.float32)
+
+
+def _check(indptr, indices, values, n_cols, d=5):
+    n_rows = len(indptr) - 1
+    rng = np.random.default_rng(0)
+    X = rng.standard_normal((n_cols, d)).astype(np.float32)
+    G = rng.standard_normal((n_rows, d)).astype(np.float32)
+    dv = dev(values)
+    A = isp.csr_build(dev(indptr), dev(indices), dv, n_cols=n_cols)
+    info, deg = A.info(), np.diff(indptr)
+    assert info["max_degree"] == deg.max() and info["n_hub_rows"] == int((deg > info["hub_threshold"]).sum())
+    assert sum(info["bin_rows"]) == n_rows and sum(info["bin_nnz"]) == len(indices)
+    Y = torch.full((n_rows, d), float("nan"), device="cuda")
+    isp.spmm(A, dev(X), Y)
+    assert_close(Y, *oracle.spmm(indptr, indices, values, X), "spmm")
+    At, _ = isp.csr_transpose_cached(A)
+    ti, tj, tp, tv = oracle.transpose(n_rows, n_cols, indptr, indices, values)
+    for got, ref in zip(At.export(), (ti, tj, tv, tp)):
+        assert np.array_equal(got.cpu().numpy(), ref)
+    dX = torch.full((n_cols, d), float("nan"), device="cuda")
+    isp.spmm(At, dev(G), dX)
+    assert_close(dX, *oracle.spmm(ti, tj, tv, G), "spmm of the transpose")
+    return A, At, (ti, tj, tp), dv, G
+
+
+@pytest.mark.parametrize("n_rows,n_cols,nnz,hub", [
+    (1, 1, 1, 0), (1, 300, 1023, 0), (63, 255, 1024, 0), (64, 256, 1025, 0), (65, 257, 4097, 2500),
+    (255, 511, 5000, 0), (256, 512, 5000, 4000), (257, 513, 5000, 0), (700, 65537, 30000, 20000),
+    (100, 131072, 9000, 0), (100, 131073, 9000, 0), (3, 262145, 9000, 5000),
+    (262143, 50, 60000, 9000), (262144, 50, 60000, 9000), (262145, 50, 60000, 9000), (1048577, 50, 60000, 9000),
+    (3000, 1000, (4 << 20), 70000), (3000, 1000, (4 << 20) + 1, 70000)])
+def test_tile_edges(n_rows, n_cols, nnz, hub):
+    print("rows %d cols %d nnz %d" % (n_rows, n_cols, nnz), flush=True)
+    _check(*_random(n_rows, n_cols, nnz, n_rows + nnz, hub), n_cols)
+
+
+@pytest.mark.parametrize("n_hub", [8191, 8192, 8193, 20000])
+def test_many_segments(n_hub):
+    print("hub rows %d" % n_hub, flush=True)
+    os.environ["ISP_HUB_THRESHOLD"] = "16"
+    try:
+        rng = np.random.default_rng(n_hub)
+        deg = np.concatenate([np.full(n_hub, 17), rng.integers(0, 9, 1000)])
+        rng.shuffle(deg)
+        indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+        indices = rng.integers(0, 4000, indptr[-1]).astype(np.int32)
+        A, *_ = _check(indptr, indices, rng.standard_normal(indptr[-1]).astype(np.float32), 4000)
+        assert A.info()["n_segments"] >= n_hub
+    finally:
+        os.environ.pop("ISP_HUB_THRESHOLD")
