@@ -1,6 +1,6 @@
 """Handle building and transposition at the sizes where their kernels change shape: row counts around a tile of rows and
-around the count from which tiles grow, entry counts around a tile of keys, column counts around a digit boundary, and more
-hub segments than the one-launch ordering takes."""
+around the count from which tiles grow, entry counts around a tile of keys, column counts around a digit boundary, more
+hub segments than the one-launch ordering takes, and large symmetric patterns, whose transpose shares A's partitions."""
 import os
 
 import numpy as np
@@ -75,3 +75,51 @@ def test_many_segments(n_hub):
         assert A.info()["n_segments"] >= n_hub
     finally:
         os.environ.pop("ISP_HUB_THRESHOLD")
+
+
+@pytest.mark.parametrize("mid,with_values", [(0, True), (64, True), (64, False)])
+def test_large_symmetric(mid, with_values):
+    print("threshold %d" % mid, flush=True)
+    os.environ["ISP_MID_THRESHOLD"] = str(mid)
+    try:
+        rng = np.random.default_rng(7)
+        n = 70000
+        i, j = rng.integers(0, n, 2300000), rng.integers(0, n, 2300000)
+        i[:40000] = 5  # a hub
+        code = np.unique(np.concatenate([i * n + j, j * n + i]))
+        indptr = np.concatenate([[0], np.cumsum(np.bincount(code // n, minlength=n))]).astype(np.int64)
+        indices = (code % n).astype(np.int32)
+        assert len(indices) > 4 << 20
+        values = rng.standard_normal(len(indices)).astype(np.float32) if with_values else None
+        if with_values:
+            A, At, (ti, tj, tp), dv, G = _check(indptr, indices, values, n)
+            # rewritten values reach the transpose and both packed layouts
+            new = torch.randn(len(indices), device="cuda")
+            dv.copy_(new)
+            isp.csr_values_changed(A)
+            dX = torch.empty(n, 5, device="cuda")
+            isp.spmm(At, dev(G), dX)
+            assert_close(dX, *oracle.spmm(ti, tj, new.cpu().numpy()[tp], G), "after new values")
+        else:
+            A = build(indptr, indices, None)
+            At, _ = isp.csr_transpose_cached(A)
+            G = rng.standard_normal((n, 5)).astype(np.float32)
+            dX = torch.empty(n, 5, device="cuda")
+            isp.spmm(At, dev(G), dX)
+            assert_close(dX, *oracle.spmm(indptr, indices, None, G), "without values")
+        assert A.info()["symmetric_pattern"] == 1 and (A.info()["spmm_pieces"] > 0) == (mid > 0)
+        assert At.info()["spmm_pieces"] == A.info()["spmm_pieces"] and At.info()["is_transpose"] == 1
+        # both handles at once, each on a stream of its own, as when they kept separate tables
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        Xd = torch.randn(n, 64, device="cuda")
+        Y1, Y2, ref1, ref2 = (torch.empty(n, 64, device="cuda") for _ in range(4))
+        isp.spmm(A, Xd, ref1)
+        isp.spmm(At, Xd, ref2)
+        torch.cuda.synchronize()
+        for _ in range(3):
+            isp.spmm(A, Xd, Y1, stream=s1)
+            isp.spmm(At, Xd, Y2, stream=s2)
+        torch.cuda.synchronize()
+        assert torch.equal(Y1, ref1) and torch.equal(Y2, ref2)
+    finally:
+        os.environ.pop("ISP_MID_THRESHOLD")
