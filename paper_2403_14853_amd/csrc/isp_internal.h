@@ -82,6 +82,9 @@ struct isp_csr {
                            // marks there which entries its arg array names
   int32_t* inv_perm;       // transposes only, same spare workspace: inv_perm[perm[q]] = q, filled on first use
   bool inv_perm_valid;
+  int32_t* gather_bound;   // transposes only, same spare workspace: the columns' parts per block of rows, for gathering
+                           // rewritten values, filled on first use (NULL: gathered in one sweep)
+  bool gather_bound_valid;
   isp_csr_info_t info;
   int device;
   isp_csr* At;             // cached transpose (owned), or NULL
@@ -127,6 +130,8 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
                             const int32_t* indices, const float* values, void* ws, size_t ws_bytes,
                             bool validate, hipStream_t s, isp_csr** out, const int* flag = nullptr,
                             int* host_flag = nullptr);
+// out[q] = values[pos[q]] for nnz > 0 entries.
+isp_status isp_gather_values(const int32_t* pos, const float* values, int64_t nnz, float* out, hipStream_t s);
 // Copy A's (rewritten) values into the packed SpMM layout's own value array again.
 isp_status isp_refresh_packed_values(isp_csr* A, hipStream_t s);
 

@@ -123,3 +123,22 @@ def test_large_symmetric(mid, with_values):
         assert torch.equal(Y1, ref1) and torch.equal(Y2, ref2)
     finally:
         os.environ.pop("ISP_MID_THRESHOLD")
+
+
+@pytest.mark.parametrize("n_rows,n_cols", [(20000, 70001), (300000, 1000), (16385, 63), (3, 9)])
+def test_rewritten_values_of_long_columns(n_rows, n_cols):
+    """The transpose's values gathered block of rows by block of rows: long, short and empty parts, columns past the last."""
+    print("rows %d cols %d" % (n_rows, n_cols), flush=True)
+    nnz = (16 << 20) + 5
+    g = torch.Generator(device="cuda").manual_seed(n_cols)
+    rows = torch.randint(n_rows, (nnz,), device="cuda", generator=g)
+    cols = (torch.rand(nnz, device="cuda", generator=g) ** 3 * n_cols).to(torch.int32)  # the first columns are long
+    indptr = torch.zeros(n_rows + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(torch.bincount(rows, minlength=n_rows), 0, out=indptr[1:])
+    values = torch.ones(nnz, device="cuda")
+    A = isp.csr_build(indptr, cols, values, n_cols=n_cols)
+    At, _ = isp.csr_transpose_cached(A)
+    values.copy_(torch.randn(nnz, device="cuda", generator=g))
+    isp.csr_values_changed(A)
+    _, _, t_values, perm = At.export()
+    assert torch.equal(t_values, values[perm.long()])
