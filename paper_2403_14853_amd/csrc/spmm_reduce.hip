@@ -329,36 +329,110 @@ __global__ void __launch_bounds__(ISP_WG) k_reduce_bwd(isp_view At, const int64_
 // The same pass on contiguous runs (run_stream.h), for widths from 4 columns and 32-bit offsets.  Only the live
 // entries of an item are staged (packed with ballots; a row's end is the number of live entries before it), so the
 // loop sees a short matrix without dead entries, G of them per step, and a row without live entries is an empty one.
-// Bound by the two gathered rows per live entry (dY and arg) on large graphs.  The whole backward, us, against one entry
-// per wavefront and iteration: 40 M entries, 100 columns 2335 -> 1946; 2.4 M entries, 16 / 301 columns 142 -> 56 /
-// 1024 -> 568.
+// Of dY and arg a live entry gathers only the eighths of the slice that the marks name: a row of 50 entries and 100
+// columns selects two or three columns per entry.  Bound by these gathers on large graphs.  The whole backward, us,
+// against one entry per wavefront and iteration -> whole rows of live entries -> their marked eighths: 40 M entries, 100
+// columns 2335 -> 1951 -> 1371; 115 M, 64 columns 1665 -> 1679 -> 1250; 2.4 M, 16 / 100 columns 142 -> 56 -> 51 /
+// 255 -> 179 -> 141.
+template <bool HAS_VAL>
 struct sel_wave_lds {
-  rn_wave_lds rn;                     // ent: (column, source position)
-  float val[GS_MAX_ENT + RN_PAD];     // value of each staged entry
+  rn_wave_lds rn;                     // ent: (column | marks of the lanes that selected the entry << 24, source position)
+  float val[HAS_VAL ? GS_MAX_ENT + RN_PAD : 1];  // value of each staged entry
   unsigned long long mask[GS_MAX_ENT / ISP_WAVE + 1];  // live entries of each 64 of the item ...
   int before[GS_MAX_ENT / ISP_WAVE + 1];               // ... and how many live ones precede them
 };
 
 constexpr int SELECT_RING = 4;
+constexpr int SELECT_WAVES = 2;  // per workgroup: the LDS then holds 16 wavefronts per CU (14 with values), not 12
+
+// The mark of a lane's columns in an entry's byte: eight parts of a row's slice, 64 bytes each with 32 lanes (memory
+// fetches no less).
+template <int LPG>
+__device__ __forceinline__ int lane_part(int q) { return q * 8 / LPG; }
+
+// marks[inv_perm[p]] = the eighths of the row slice whose columns of arg name p, for the columns from k_base; marks was zeroed
+// before.  A wavefront takes a row block of A, whose rows name only the block's own entries, and gathers their marks in
+// LDS, a byte per eighth (bits set by LDS atomics queue up: in a row of 14 entries 100 columns meet on 14 words, 71 us
+// against 23 on 2.4 M entries); or one hub row, which has at most as many selected entries as columns and marks them whole.  (What a
+// caller's array may hold besides - the -1 of empty rows, positions elsewhere - is ignored; a mark too many costs a look
+// at arg.)  Bound by the scattered bytes: 40 M entries, 100 columns 227 us (363 with
+// a lookup per row and column).
+constexpr int MARK_ROWS = 4;  // rows per lane group in flight (8: 1 % slower, blocks of few rows load in vain)
 
 template <int LPG>
-__global__ void __launch_bounds__(ISP_WG) k_select_grouped(isp_view At, const int64_t* __restrict__ indptr,
+__global__ void __launch_bounds__(ISP_WG) k_mark_lanes(isp_view A, const int64_t* __restrict__ indptr,
+                                                       const int32_t* __restrict__ arg, int d, int k_base,
+                                                       const int32_t* __restrict__ inv_perm, uint8_t* __restrict__ marks) {
+  constexpr int G = ISP_WAVE / LPG, U = MARK_ROWS;
+  __shared__ uint2 lds[ISP_WAVES_PER_WG][GS_MAX_ENT];  // a byte per entry and part
+  const int lane = threadIdx.x & (ISP_WAVE - 1);
+  const int w = threadIdx.x >> 6;
+  const int item = __builtin_amdgcn_readfirstlane((int)blockIdx.x * ISP_WAVES_PER_WG + w);
+  if (item >= A.n_blocks) {
+    if (item >= A.n_blocks + A.n_hub) return;
+    const int row = A.hub_rows[item - A.n_blocks];
+    const int64_t p0 = indptr[row], p1 = indptr[row + 1];
+    const int k_end = d < k_base + 4 * LPG ? d : k_base + 4 * LPG;
+    for (int k = k_base + lane; k < k_end; k += ISP_WAVE) {
+      const int p = arg[(int64_t)row * d + k];
+      if (p >= p0 && p < p1) marks[inv_perm[p]] = 0xff;
+    }
+    return;
+  }
+  const item_range it = locate_item(A, indptr, item);
+  if (it.skip) return;
+  uint2* __restrict__ m = lds[w];
+  const unsigned n = (unsigned)(it.p_end - it.p), p0 = (unsigned)it.p;
+  for (unsigned i = lane; i < n; i += ISP_WAVE) m[i] = make_uint2(0u, 0u);
+  wave_lds_sync();
+  const int g = lane / LPG, q = lane % LPG;
+  const int col = k_base + tail_col<4>(q * 4, d - k_base);
+  uint8_t* __restrict__ mine = reinterpret_cast<uint8_t*>(m) + lane_part<LPG>(q);
+  for (int r = it.row + g; r < it.row_last; r += G * U) {
+    int where[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int row = r + u * G < it.row_last ? r + u * G : it.row_last - 1;
+      float t[4];
+      load_vec<4>(reinterpret_cast<const float*>(arg) + (int64_t)row * d + col, t);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) where[u][v] = __float_as_int(t[v]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const unsigned i = (unsigned)where[u][v] - p0;
+        if (i < n && r + u * G < it.row_last) mine[i * 8u] = 1;
+      }
+  }
+  wave_lds_sync();
+  for (unsigned i = lane; i < n; i += ISP_WAVE) {
+    const uint2 b = m[i];
+    // (the low bits of four bytes: the product's bits 24 to 27)
+    const unsigned parts = (b.x * 0x01020408u >> 24 & 15u) | (b.y * 0x01020408u >> 20 & 240u);
+    if (parts) marks[inv_perm[it.p + i]] = (uint8_t)parts;
+  }
+}
+
+template <int LPG, bool HAS_VAL>
+__global__ void __launch_bounds__(SELECT_WAVES * ISP_WAVE) k_select_grouped(isp_view At, const int64_t* __restrict__ indptr,
                                                            const int32_t* __restrict__ indices,
                                                            const float* __restrict__ values,
                                                            const int32_t* __restrict__ perm,
-                                                           const uint8_t* __restrict__ live,
+                                                           const uint8_t* __restrict__ marks,
                                                            const float* __restrict__ dY, int64_t lddy,
                                                            const int32_t* __restrict__ arg, int d, int k_base,
                                                            float* __restrict__ dX, int64_t lddx) {
   constexpr int G = ISP_WAVE / LPG;
-  __shared__ sel_wave_lds lds[ISP_WAVES_PER_WG];
+  __shared__ sel_wave_lds<HAS_VAL> lds[SELECT_WAVES];
   const int lane = threadIdx.x & (ISP_WAVE - 1);
   const int w = threadIdx.x >> 6;
-  const int item = __builtin_amdgcn_readfirstlane((int)blockIdx.x * ISP_WAVES_PER_WG + w);
+  const int item = __builtin_amdgcn_readfirstlane((int)blockIdx.x * SELECT_WAVES + w);
   if (item >= At.n_blocks + At.n_seg) return;
   const item_range it = locate_item(At, indptr, item);
   if (it.skip) return;
-  sel_wave_lds& S = lds[w];
+  sel_wave_lds<HAS_VAL>& S = lds[w];
   rn_wave_lds& L = S.rn;
   const int n_all = (int)(it.p_end - it.p);
   const rn_first_rows f = rn_request_rows(it, indptr, nullptr, lane);
@@ -369,7 +443,7 @@ __global__ void __launch_bounds__(ISP_WG) k_select_grouped(isp_view At, const in
   for (int u = 0; u < SB; ++u) {
     const int i = u * ISP_WAVE + lane;
     on[u] = 0;
-    if (u * ISP_WAVE < n_all && i < n_all) on[u] = live[it.p + i];
+    if (u * ISP_WAVE < n_all && i < n_all) on[u] = marks[it.p + i];
   }
   int n_ent = 0;
 #pragma unroll
@@ -379,13 +453,13 @@ __global__ void __launch_bounds__(ISP_WG) k_select_grouped(isp_view At, const in
     if (on[u] != 0) {
       const int64_t p = it.p + u * ISP_WAVE + lane;
       const int o = n_ent + __popcll(m & ((1ull << lane) - 1ull));
-      L.ent[o] = make_int2(indices[p], perm[p]);
-      S.val[o] = values ? values[p] : 1.f;
+      L.ent[o] = make_int2((int)((unsigned)indices[p] | (unsigned)on[u] << 24), perm[p]);
+      if (HAS_VAL) S.val[o] = values[p];
     }
     n_ent += __popcll(m);
   }
   if (lane == 0) { S.mask[SB] = 0; S.before[SB] = n_ent; }
-  if (lane < RN_PAD) { L.ent[n_ent + lane] = make_int2(0, 0); S.val[n_ent + lane] = 0.f; }
+  if (lane < RN_PAD) L.ent[n_ent + lane] = make_int2(0, 0);
   wave_lds_sync();
   const rn_run R = rn_find_runs<G>(it, indptr, nullptr, n_ent, f, [&](int o) {
     return S.before[o >> 6] + __popcll(S.mask[o >> 6] & ((1ull << (o & 63)) - 1ull));
@@ -393,26 +467,35 @@ __global__ void __launch_bounds__(ISP_WG) k_select_grouped(isp_view At, const in
 
   const int g = lane / LPG, q = lane % LPG;
   const int col = k_base + tail_col<4>(q * 4, d - k_base);
+  const unsigned mine = 1u << (24 + lane_part<LPG>(q));
   float* __restrict__ out = it.is_seg ? At.partials + (col - k_base) : dX + col;
   const int64_t ldo = it.is_seg ? (int64_t)ISP_PARTIAL_TILE : lddx;
   float acc[4] = {0.f, 0.f, 0.f, 0.f}, head[4] = {0.f, 0.f, 0.f, 0.f};
   for (int i = g; i < R.n_empty; i += G) store_vec<4>(out + (int64_t)L.dst[RN_EMPTY0 - i] * ldo, acc);
 
   float x[SELECT_RING][4], wh[SELECT_RING][4], val[SELECT_RING];
+  unsigned key[SELECT_RING];
   bool carried = R.mid, ended = false;  // (as in k_spmm_grouped)
   rn_stream<SELECT_RING, true, false>(
       L, R,
       [&](int u, int c, int s, int, bool) {
+        // (a lane without a mark reads the first row's first columns, which stay in the L1: no branch around the loads)
+        key[u] = (unsigned)c;
+        const bool on = (key[u] & mine) != 0;
         const unsigned cb = (unsigned)col * 4u;
-        load_vec<4>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(dY) + (__umul24((unsigned)c, (unsigned)lddy * 4u) + cb)), x[u]);
-        load_vec<4>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(arg) + (__umul24((unsigned)c, (unsigned)d * 4u) + cb)), wh[u]);
-        val[u] = S.val[R.start + s];
+        const unsigned oy = on ? __umul24(key[u], (unsigned)lddy * 4u) + cb : 0u;  // (the product takes the low 24 bits)
+        const unsigned oa = on ? __umul24(key[u], (unsigned)d * 4u) + cb : 0u;
+        load_vec<4>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(dY) + oy), x[u]);
+        load_vec<4>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(arg) + oa), wh[u]);
+        if (HAS_VAL) val[u] = S.val[R.start + s];
       },
       [&](int u, float a, int) {  // (a: the entry's source position, as bits)
+        const bool on = (key[u] & mine) != 0;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const bool mine = __float_as_int(wh[u][v]) == __float_as_int(a);
-          acc[v] = mine ? fmaf(val[u], x[u][v], acc[v]) : acc[v];
+          const bool take = on && __float_as_int(wh[u][v]) == __float_as_int(a);
+          const float sum = HAS_VAL ? fmaf(val[u], x[u][v], acc[v]) : acc[v] + x[u][v];
+          acc[v] = take ? sum : acc[v];
         }
       },
       [&](int, int row) {
@@ -551,12 +634,23 @@ isp_status fwd_all(const isp_csr* A, const float* X, int64_t ldx, int d, float* 
 }
 
 template <int LPG>
-isp_status select_grouped_tile(const isp_csr* At, const float* dY, int64_t lddy, const int32_t* arg, int d, int k_base,
-                               float* dX, int64_t lddx, hipStream_t s) {
-  const isp_view& v = At->v;
+isp_status select_grouped_tile(const isp_csr* A, const int32_t* inv_perm, const float* dY, int64_t lddy, const int32_t* arg,
+                               int d, int k_base, float* dX, int64_t lddx, hipStream_t s) {
+  const isp_csr* At = A->At;
+  const isp_view &v = At->v, &va = A->v;
+  const int64_t words = (v.nnz + 3) / 4;
+  k_zero_u32<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(At->sel_flags), words);
+  ISP_LAUNCH_CHECK();
+  if (va.n_blocks + va.n_hub > 0) {
+    const unsigned grid = (unsigned)((va.n_blocks + va.n_hub + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
+    k_mark_lanes<LPG><<<grid, ISP_WG, 0, s>>>(va, va.indptr, arg, d, k_base, inv_perm, At->sel_flags);
+    ISP_LAUNCH_CHECK();
+  }
   if (v.n_blocks + v.n_seg > 0) {
-    k_select_grouped<LPG><<<item_grid(v), ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, At->perm, At->sel_flags, dY,
-                                                          lddy, arg, d, k_base, dX, lddx);
+    const unsigned grid = (unsigned)((v.n_blocks + v.n_seg + SELECT_WAVES - 1) / SELECT_WAVES);
+    constexpr int WG = SELECT_WAVES * ISP_WAVE;
+    if (v.values) k_select_grouped<LPG, true><<<grid, WG, 0, s>>>(v, v.indptr, v.indices, v.values, At->perm, At->sel_flags, dY, lddy, arg, d, k_base, dX, lddx);
+    else k_select_grouped<LPG, false><<<grid, WG, 0, s>>>(v, v.indptr, v.indices, v.values, At->perm, At->sel_flags, dY, lddy, arg, d, k_base, dX, lddx);
     ISP_LAUNCH_CHECK();
   }
   if (v.n_hub > 0) {
@@ -627,33 +721,34 @@ isp_status isp_spmm_reduce_bwd_launch(isp_csr* A, const float* dY, int64_t lddy,
   const bool v2 = d % 2 == 0 && lddy % 2 == 0 && lddx % 2 == 0 && aligned(dY, 8) && aligned(dX, 8) &&
                   aligned(arg, 8) && d > ISP_WAVE;
   isp_status st = ISP_OK;
-  if (reduce != R_MEAN && At->v.nnz > 0) {  // which entries of A does arg name at all (any column)?
-    const int64_t nnz = At->v.nnz, words = (nnz + 3) / 4, n_arg = A->v.n_rows * (int64_t)d;
-    const int32_t* inv_perm = nullptr;
-    st = isp_transpose_inverse_perm(A, s, &inv_perm);
-    if (st != ISP_OK) return st;
-    k_zero_u32<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(At->sel_flags), words);
-    ISP_LAUNCH_CHECK();
-    if (n_arg > 0) {
-      k_mark_selected<<<(unsigned)((n_arg + 255) / 256), 256, 0, s>>>(arg, n_arg, nnz, inv_perm, At->sel_flags);
-      ISP_LAUNCH_CHECK();
-    }
-  }
   const isp_view& tv = At->v;
+  const int32_t* inv_perm = nullptr;
+  if (reduce != R_MEAN && tv.nnz > 0 && (st = isp_transpose_inverse_perm(A, s, &inv_perm)) != ISP_OK) return st;
   auto fits = [&](int64_t ld) {  // 32-bit gather offsets into a matrix of A's rows
     return tv.n_cols < (1 << 24) && ld * 4 < (1 << 24) && ((uint64_t)tv.n_cols * (uint64_t)ld + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
   };
-  if (reduce != R_MEAN && tv.nnz > 0 && d >= 4 && fits(lddy) && fits(d) && At->info.block_cost <= GS_MAX_ROWS &&
-      At->info.block_cost + tv.hub_t <= GS_MAX_ENT && tv.seg_len <= GS_MAX_ENT && !At->tune.no_grouped) {
+  auto items_fit = [](const isp_csr* M) {
+    return M->info.block_cost <= GS_MAX_ROWS && M->info.block_cost + M->v.hub_t <= GS_MAX_ENT && M->v.seg_len <= GS_MAX_ENT;
+  };
+  if (reduce != R_MEAN && tv.nnz > 0 && d >= 4 && fits(lddy) && fits(d) && items_fit(A) && items_fit(At) && !At->tune.no_grouped) {
     for (int k0 = 0; k0 < d && st == ISP_OK; k0 += ISP_PARTIAL_TILE) {
       const int k_base = d - k0 < 4 ? d - 4 : k0;  // (no launch narrower than a float4 lane)
       const int w = d - k_base < ISP_PARTIAL_TILE ? d - k_base : ISP_PARTIAL_TILE;
-      if (w <= 32) st = select_grouped_tile<8>(At, dY, lddy, arg, d, k_base, dX, lddx, s);
-      else if (w <= 64) st = select_grouped_tile<16>(At, dY, lddy, arg, d, k_base, dX, lddx, s);
-      else if (w <= 128) st = select_grouped_tile<32>(At, dY, lddy, arg, d, k_base, dX, lddx, s);
-      else st = select_grouped_tile<64>(At, dY, lddy, arg, d, k_base, dX, lddx, s);
+      if (w <= 32) st = select_grouped_tile<8>(A, inv_perm, dY, lddy, arg, d, k_base, dX, lddx, s);
+      else if (w <= 64) st = select_grouped_tile<16>(A, inv_perm, dY, lddy, arg, d, k_base, dX, lddx, s);
+      else if (w <= 128) st = select_grouped_tile<32>(A, inv_perm, dY, lddy, arg, d, k_base, dX, lddx, s);
+      else st = select_grouped_tile<64>(A, inv_perm, dY, lddy, arg, d, k_base, dX, lddx, s);
     }
     return st;
+  }
+  if (reduce != R_MEAN && tv.nnz > 0) {  // which entries of A does arg name at all (any column)?
+    const int64_t words = (tv.nnz + 3) / 4, n_arg = A->v.n_rows * (int64_t)d;
+    k_zero_u32<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(At->sel_flags), words);
+    ISP_LAUNCH_CHECK();
+    if (n_arg > 0) {
+      k_mark_selected<<<(unsigned)((n_arg + 255) / 256), 256, 0, s>>>(arg, n_arg, tv.nnz, inv_perm, At->sel_flags);
+      ISP_LAUNCH_CHECK();
+    }
   }
   for (int k0 = 0; k0 < d && st == ISP_OK; k0 += (v2 ? 2 : 1) * ISP_WAVE) {
     if (reduce == R_MEAN) {

@@ -119,3 +119,24 @@ def test_reduce_argument_errors():
         isp.spmm_reduce_backward(A, X, Y, "mean")
     assert e.value.status_name == "ISP_EINVAL"
     A.destroy()
+
+
+@pytest.mark.parametrize("d", [4, 8, 31, 32, 33, 64, 65, 128, 129, 256, 257, 260])
+def test_max_backward_marks_at_width(d):
+    """Slices of 32, 64, 128 and 256 columns are marked in eighths; the last columns' lanes move back, the last slice may
+    be one column wide, and hub rows (cut into segments), short rows and blocks of several rows each mark their own way."""
+    rng = np.random.default_rng(d)
+    n = 700
+    deg = np.concatenate([[600, 0, 550, 1], rng.integers(0, 40, n - 4)])
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    indices = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in deg]).astype(np.int32)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    G = rng.standard_normal((n, d)).astype(np.float32)
+    for values in (None, rng.standard_normal(len(indices)).astype(np.float32)):
+        A = build(indptr, indices, values)
+        assert A.info()["n_hub_rows"] == 2
+        isp.csr_transpose_cached(A)
+        _, arg, _ = oracle.spmm_reduce(indptr, indices, values, X, "max")
+        dX = torch.full((n, d), float("nan"), device="cuda")
+        isp.spmm_reduce_backward(A, dev(G), dX, "max", dev(arg.astype(np.int32)))
+        assert_close(dX, *oracle.spmm_reduce_backward(n, indptr, indices, values, G, "max", arg), "max backward d=%d" % d)
