@@ -104,17 +104,17 @@ struct sddmm_policy {
   }
 };
 
-template <int LPG, bool ADDR32, bool ADD, bool TAIL>
+template <int LPG, int W, bool ADDR32, bool ADD, bool TAIL>
 __global__ void __launch_bounds__(ISP_WG) k_sddmm_grouped(isp_view A, const int64_t* __restrict__ indptr,
                                                           const int32_t* __restrict__ indices,
                                                           const float* __restrict__ values,
                                                           typename sddmm_policy<ADD>::args pa, int d, int k_lo) {
   __shared__ rn_lds lds;
-  fused_grouped_item<sddmm_policy<ADD>, LPG, 4, ADDR32, TAIL>(A, indptr, indices, values, pa, d, nullptr, 0, lds, k_lo);
+  fused_grouped_item<sddmm_policy<ADD>, LPG, W, ADDR32, TAIL>(A, indptr, indices, values, pa, d, nullptr, 0, lds, k_lo);
 }
 
-// One pass over the feature columns [k_lo, d_hi) (d_hi - k_lo <= 4 * LPG); add: accumulate into out.
-template <int LPG>
+// One pass over the feature columns [k_lo, d_hi) (d_hi - k_lo <= W * LPG); add: accumulate into out.
+template <int LPG, int W>
 isp_status launch_grouped(const isp_csr* A, const float* U, int64_t ldu, const float* V, int64_t ldv, int k_lo,
                           int d_hi, bool add, bool scale, float* out, hipStream_t s) {
   const isp_view& v = A->v;
@@ -127,7 +127,7 @@ isp_status launch_grouped(const isp_csr* A, const float* U, int64_t ldu, const f
 #define ISP_GO(A32, AD, TL)                                                                                         \
   do {                                                                                                              \
     typename sddmm_policy<AD>::args pa{{V}, {ldv}, {U}, {ldu}, out};                                                 \
-    k_sddmm_grouped<LPG, A32, AD, TL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, pa, d_hi, k_lo);       \
+    k_sddmm_grouped<LPG, W, A32, AD, TL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, pa, d_hi, k_lo);       \
   } while (0)
 #define ISP_GO2(A32, AD) do { if (tail) ISP_GO(A32, AD, true); else ISP_GO(A32, AD, false); } while (0)
   if (a32) { if (add) ISP_GO2(true, true); else ISP_GO2(true, false); }
@@ -155,6 +155,8 @@ isp_status launch(const isp_csr* A, const float* U, int64_t ldu, const float* V,
   return ISP_OK;
 }
 
+constexpr int64_t SLICE_FLOATS = 16 << 20;  // V of 64 MB, twice the L2s
+
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
 }  // namespace
@@ -170,13 +172,15 @@ isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const
     //  - big graphs with many columns, rows of whole 64-float halves: 64-column passes, so that every L2 holds
     //    half-rows of twice as many hot columns (the same effect, under the same conditions, as the column
     //    slices of SpMM);
-    //  - otherwise rows wider than 128 floats go 128 columns at a time on the big graphs, 256 on the others.
+    //  - otherwise rows wider than 128 floats go 128 columns at a time on the big graphs, and on others whose V is
+    //    beyond the L2s, where that cuts no cache line (256 columns, 2.4 M / 3 M entries: 259 -> 229 us / 366 -> 326;
+    //    at 200 columns it would be 222 -> 242), 256 on the rest.
     const bool big = av.nnz >= ((int64_t)8 << 20);
     int wp = d;
     if (big && av.n_cols >= (1 << 19) && d > ISP_WAVE && d % ISP_WAVE == 0 && ldu % 32 == 0 && ldv % 32 == 0 &&
         !A->tune.sddmm_one_pass)
       wp = ISP_WAVE;
-    else if (big && d > 2 * ISP_WAVE) wp = 2 * ISP_WAVE;
+    else if (d > 2 * ISP_WAVE && (big || (ldu % 32 == 0 && ldv % 32 == 0 && av.n_cols * ldv >= SLICE_FLOATS))) wp = 2 * ISP_WAVE;
     else if (d > ISP_PARTIAL_TILE) wp = ISP_PARTIAL_TILE;
     isp_status st = ISP_OK;
     for (int k_lo = 0, k_next; k_lo < d && st == ISP_OK; k_lo = k_next) {
@@ -185,13 +189,17 @@ isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const
       const int w = k_hi - k_lo;
       const bool add = k_lo > 0;
       k_next = k_hi;
-      // One float4 per lane (two, which serve twice the entries per step, load the row operand with every step and
-      // hold twice the registers: 128 columns in one pass, us, one / two: 115 M entries 2648 / 2704, 16.9 M 717 /
-      // 737, 2.4 M 108 / 110).
-      if (w <= 32) st = launch_grouped<8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
-      else if (w <= 64) st = launch_grouped<16>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
-      else if (w <= 128) st = launch_grouped<32>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
-      else st = launch_grouped<64>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      // One float4 per lane up to 128 columns (two, which serve twice the entries per step, load the row operand with
+      // every step and hold twice the registers: 128 columns in one pass, us, one / two: 115 M entries 2648 / 2704, 16.9 M
+      // 717 / 737, 2.4 M 108 / 110), two above: with one, a wavefront has a single
+      // run and a reduction over all its lanes per entry.  That is only the better way for nearly full rows on graphs
+      // with work for several times as many wavefronts as the chip holds (248 columns, us, one / two: 108 k entries
+      // 41 / 25, 589 k 61 / 45, 1.2 M 112 / 121, 3 M 380 / 391; 160 columns: 3 M 243 / 228).
+      if (w <= 32) st = launch_grouped<8, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      else if (w <= 64) st = launch_grouped<16, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      else if (w <= 128) st = launch_grouped<32, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      else if (w <= 192 || av.nnz < (1 << 20)) st = launch_grouped<32, 8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      else st = launch_grouped<64, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
     }
     return st;
   }
