@@ -17,10 +17,10 @@ struct alias_layout {
 };
 
 // Partial rows one launch on h may touch: one per hub-row segment and column group (FusedMM wider than 256
-// columns stores `groups` groups of 256 columns per segment and launch), one per piece of the packed layout.
+// columns stores `groups` groups of 256 columns per segment and launch), and what a SpMM on either partition writes.
 int64_t rows_needed(const isp_csr* h, int64_t groups) {
   int64_t r = (int64_t)h->v.n_seg * groups;
-  if (h->has_packed && h->info.spmm_pieces > r) r = h->info.spmm_pieces;
+  if (h->spmm_rows > r) r = h->spmm_rows;
   return r > 0 ? r : 1;
 }
 

@@ -12,13 +12,14 @@
 // Everything here is integer work and runs once per graph (balanced scheduling: paper Section 1(b); CSR
 // operand: Section 3.5).
 #include <limits.h>
-#include <stdlib.h>
 #include <new>
 #include "block_scan.h"
 #include "host_slot.h"
+#include "partition_sizes.h"
 
 namespace {
 using namespace isp_dev;
+using namespace isp_part;
 
 struct build_counters {
   unsigned long long bin_rows[5];
@@ -28,69 +29,10 @@ struct build_counters {
   int n_blocks, n_hub, n_seg;
 };
 
-struct partition_params {
-  int block_cost, hub_t, seg_len;
-  int row_cost;   // cost units of a row besides its entries (1; 2 in the derived matrix, which allows larger blocks)
-  int bands;      // column bands of the finest cut (a power of two); 1 = no band cuts
-  int min_piece;  // a hub row is cut into at most degree / min_piece bands
-};
-
-constexpr int MAX_BANDS = 64;  // one piece per lane
 constexpr int CUT_COUNT = 16;  // wavefronts' worth of entries that cutting a hub row looks at first
 
 // Matrices up to this size have everything about their partition enqueued in one go (see build_partition).
 constexpr int64_t SMALL_NNZ = 4 << 20;
-
-int env_int(const char* name, int dflt, int lo, int hi) {
-  const char* s = getenv(name);
-  if (!s || !*s) return dflt;
-  long v = strtol(s, nullptr, 10);
-  if (v < lo) v = lo;
-  if (v > hi) v = hi;
-  return (int)v;
-}
-
-partition_params get_params(int64_t n_rows, int64_t n_cols, int64_t nnz) {
-  partition_params p;
-  p.row_cost = 1;
-  const int64_t slots = isp_wave_slots();  // 4,096 on an MI355X (256 compute units)
-  // Upper limits = what the grouped kernels' per-wave LDS tables hold (block_cost + hub_t <= 768
-  // entries, block_cost <= 256 rows, seg_len <= 768 entries).  The environment overrides exist for
-  // tuning and for tests that want many small work items.
-  // Small matrices get smaller row blocks, about as many as the chip has wavefront slots (compute units x 16):
-  // a wavefront's work is a chain of dependent memory round trips, and a short chain on every slot
-  // finishes sooner than a long one on a few (4,096 rows x 9 entries: 16 -> 7 us per SpMM).
-  int64_t auto_cost = (nnz + n_rows + slots - 1) / slots;
-  auto_cost = auto_cost < 16 ? 16 : (auto_cost > 256 ? 256 : auto_cost);
-  p.block_cost = env_int("ISP_BLOCK_COST", (int)auto_cost, 16, 256);
-  // ... and shorter hub segments, for the same reason and because the segments are the heavy items that the
-  // launch hands out last: a quarter of the per-slot share, between 80 and 512 entries, rows of more than two
-  // segments' worth being hubs (2.4 M entries: segments of 157 instead of 512, 0.512 -> 0.468 ms for four
-  // SpMMs; 0.6 M entries: 0.167 -> 0.155 ms; from 8 M entries up the sizes are 512 / 512 as before).
-  // With many columns a column band of the dense operand is far larger than an L2, and finer pieces of the
-  // hub rows (segments of at most 384, pieces from 192 entries) keep more of each segment's gathers inside its
-  // band (2.4 M columns: 5.30 -> 5.19 ms per SpMM, the other kernels 1-3 %); with few columns a band's popular
-  // rows fit an L2 anyway and the longer segments win (233 k columns: SDDMM 3.21 vs 3.32 ms).
-  // Measured again with the present kernels (segments 256 .. 512, smallest pieces 64 .. 256, on the three large
-  // benchmark graphs): segments of at most 320 and pieces from 128 entries are best or within 1 % of it for every
-  // kernel on every one of them (233 k columns: SpMM 2.68 -> 2.59 ms, SDDMM 2.71 -> 2.60 ms; 2.4 M columns:
-  // FusedMM 5.59 -> 5.41 ms; 1 M columns: FusedMM backward 1.36 -> 1.32 ms).
-  const int seg_cap = 320;
-  int64_t auto_seg = (nnz + n_rows + slots - 1) / slots / 4;
-  auto_seg = auto_seg < 80 ? 80 : (auto_seg > seg_cap ? seg_cap : auto_seg);
-  const int auto_hub = 2 * auto_seg > 512 ? 512 : (int)(2 * auto_seg);
-  p.hub_t = env_int("ISP_HUB_THRESHOLD", auto_hub, 8, 512);
-  p.seg_len = env_int("ISP_SEGMENT_LEN", (int)auto_seg, 8, 768);
-  int b = env_int("ISP_BANDS", 32, 1, MAX_BANDS);
-  while (b & (b - 1)) b &= b - 1;  // round down to a power of two
-  p.bands = b;
-  // (the lower limit bounds the number of segments, hence the partial-sum rows the workspace must hold)
-  const int mp_lo = p.seg_len / 8 > 4 ? p.seg_len / 8 : 4;
-  int mp = p.seg_len / 2 < 128 ? p.seg_len / 2 : 128;
-  if (mp < mp_lo) mp = mp_lo;
-  p.min_piece = env_int("ISP_MIN_PIECE", mp, mp_lo, 1 << 20);
-  return p;
-}
 
 }  // namespace
 
@@ -145,8 +87,7 @@ __global__ void k_zero_counters(build_counters* c, const int* flag, int* host_fl
 __device__ inline void wave_hub_pieces(const int32_t* __restrict__ indices, int64_t a, int64_t b, int64_t n_cols,
                                        const partition_params& pp, int lane, int64_t* first, int64_t* last) {
   const int64_t deg = b - a;
-  int br = 1;
-  while (br * 2 <= pp.bands && (int64_t)(br * 2) * pp.min_piece <= deg) br *= 2;
+  const int br = hub_bands(deg, pp);
   const int64_t bw = (n_cols + pp.bands - 1) / pp.bands;
   const int step = pp.bands / br;
   // cut j = number of the row's columns below j * step * bw; cut 0 = a, cuts >= br = b
@@ -719,13 +660,10 @@ ws_layout make_layout(int64_t n_rows, int64_t nnz, const partition_params& pp, s
   size_t off = start;
   auto take = [&](size_t bytes) { size_t o = off; off += isp_align(bytes); return o; };
   const int64_t n_bal = (nnz + (int64_t)pp.row_cost * n_rows) / pp.block_cost + 2;
-  int64_t max_hub = nnz / ((int64_t)pp.hub_t + 1);
-  if (max_hub > n_rows) max_hub = n_rows;
+  const int64_t max_hub = max_hub_rows(n_rows, nnz, pp);
   int64_t max_blocks = n_bal + 2 * max_hub + 3;
   if (max_blocks > n_rows + 1) max_blocks = n_rows + 1;
-  // a row of degree deg has at most deg / min_piece pieces, and a piece of len entries at most
-  // len / seg_len + 1 segments
-  const int64_t max_seg = nnz / pp.seg_len + (pp.bands > 1 ? nnz / pp.min_piece : 0) + max_hub + 1;
+  const int64_t max_seg = max_segments(n_rows, nnz, pp);
   L.max_blocks = max_blocks; L.max_hub = max_hub; L.max_seg = max_seg;
   L.counters = take(sizeof(build_counters));
   L.cost = take((size_t)(n_rows + 1) * 4);
@@ -765,44 +703,6 @@ struct packed_layout {
   size_t part2_start; // the derived matrix's partition starts here (laid out once its row count is known)
   size_t total;
 };
-
-// Block cost of the derived matrix.  Its rows cost two units besides their entries, so a block of B units holds
-// at most B / 2 rows and B may reach twice the ordinary 256 within the kernels' 256-row tables; its entries
-// (fewer than B plus the longest row) must fit their 768-entry tables.
-// One and a half times the ordinary block where the longest row leaves room for it (config 3: 384 units next to
-// rows of up to 384 entries; measured 4.75 ms per SpMM against 4.81 at 256 and 4.76 at 512, where the segments
-// have to shrink to 256 entries): every work item starts with a chain of dependent loads before its first
-// gather, and fewer, larger items pay it less often.
-int derived_block_cost(const partition_params& p1, int mid_t) {
-  const int longest = mid_t > p1.seg_len ? mid_t : p1.seg_len;
-  int dflt = p1.block_cost * 3 / 2;
-  if (dflt > 768 - longest) dflt = 768 - longest;
-  if (dflt < 16) dflt = 16;
-  return env_int("ISP_PACKED_BLOCK", dflt, 16, 512);
-}
-
-partition_params cut_params(const partition_params& p1, int mid_t) {
-  partition_params c = p1;
-  c.hub_t = mid_t;
-  const int room = 768 - derived_block_cost(p1, mid_t);  // longest row the derived matrix may have
-  // (the ordinary partition's segment length also bounds the pieces here: 320 against 384 measured 4.65 / 4.64 ms
-  // per SpMM on 2.4 M columns, 0.345 / 0.357 ms on 1 M columns at d = 64)
-  if (c.seg_len > room) c.seg_len = room;
-  // pieces of 64 entries or more, on up to 32 bands (measured on 2.4 M columns: smaller pieces fetch less but
-  // pay it back in partial rows)
-  c.min_piece = env_int("ISP_MIN_PIECE", 64, c.seg_len / 8 > 4 ? c.seg_len / 8 : 4, 1 << 20);
-  return c;
-}
-
-partition_params derived_params(const partition_params& p1, const partition_params& cut) {
-  partition_params d = p1;
-  d.hub_t = cut.hub_t > cut.seg_len ? cut.hub_t : cut.seg_len;  // no row of the derived matrix is longer
-  d.seg_len = d.hub_t;
-  d.bands = 1;
-  d.row_cost = 2;
-  d.block_cost = derived_block_cost(p1, cut.hub_t);
-  return d;
-}
 
 packed_layout make_packed_layout(int64_t n_rows, int64_t nnz, bool has_values, const partition_params& p1, int mid_t,
                                  size_t start) {
@@ -1038,6 +938,7 @@ isp_status build_packed(isp_csr* A, const partition_params& p1, int mid_t, char*
   vp.n_real_rows = n;
   vp.piece_slot = cut.seg_order;
   A->has_packed = true;
+  if (n_pc > A->spmm_rows) A->spmm_rows = n_pc;
   A->packed_block_cost = pd.block_cost;
   A->packed_row_cost = pd.row_cost;
   A->packed_values_rw = values2;
@@ -1052,7 +953,7 @@ isp_status build_packed(isp_csr* A, const partition_params& p1, int mid_t, char*
 }  // namespace
 
 size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz) {
-  const partition_params p1 = get_params(n_rows, n_cols, nnz);
+  const partition_params p1 = get_params(n_rows, nnz, isp_wave_slots());
   const ws_layout L = make_layout(n_rows, nnz, p1);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, p1);
   if (mid_t == 0) return L.total;
@@ -1076,7 +977,7 @@ isp_status isp_refresh_packed_values(isp_csr* A, hipStream_t s) {
 isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const int64_t* indptr,
                             const int32_t* indices, const float* values, void* ws, size_t ws_bytes, bool validate,
                             hipStream_t s, isp_csr** out, const int* flag, int* host_flag) {
-  const partition_params pp = get_params(n_rows, n_cols, nnz);
+  const partition_params pp = get_params(n_rows, nnz, isp_wave_slots());
   const ws_layout L = make_layout(n_rows, nnz, pp);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, pp);
   packed_layout P{};
@@ -1101,6 +1002,7 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   fill_view(A->v, n_rows, n_cols, nnz, indptr, indices, values, po, pp);
   A->vp = A->v;
   A->partial_rows = L.max_seg + 1;
+  A->spmm_rows = po.h.n_seg;
   A->has_packed = false; A->packed_values_rw = nullptr; A->packed_src_pos = nullptr;
   A->perm = nullptr; A->t_values_rw = nullptr; A->At = nullptr; A->is_transpose = false; A->mirror_aligned = false;
   A->mean_values = nullptr; A->mean_values_packed = nullptr; A->mean_values_valid = false; A->mean_values_used = false;

@@ -66,6 +66,9 @@ struct isp_csr {
   // Only the tuned SpMM reads it.  Without it vp == v.
   isp_view vp;
   int64_t partial_rows;           // partial rows (ISP_PARTIAL_TILE floats each) v.partials has room for
+  int64_t spmm_rows;              // partial rows a SpMM launch on v or vp writes: n_seg, or the pieces where they are
+                                  // more.  A built handle keeps scratch of its own for the pieces; whoever points v
+                                  // and vp at one scratch gives it this many rows.
   bool has_packed;
   int packed_block_cost, packed_row_cost;  // of vp's partition (bounds of its blocks: see csr_build.hip)
   float* packed_values_rw;        // vp.values, writable, NULL without values
@@ -122,6 +125,13 @@ isp_status isp_check_dense(const void* p, int64_t ld, int32_t d, int64_t rows, c
 size_t isp_scan_tmp_bytes(int64_t n);
 isp_status isp_scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, void* tmp, hipStream_t s);
 isp_status isp_scan_i32_to_i32(const int32_t* in, int32_t* out, int64_t n, void* tmp, hipStream_t s);
+
+// Rows of a scratch that serves v and vp of a second handle with A's partitions (the shared transpose: transpose.hip).
+// The pieces can outnumber what the ordinary partition is laid out for: they start at half its smallest piece, from
+// half its row length (70,000 rows of 290 entries: 273,000 pieces, 262,000 rows).
+static inline int64_t isp_shared_rows(const isp_csr* A) {
+  return A->partial_rows > A->spmm_rows ? A->partial_rows : A->spmm_rows;
+}
 
 // ---- partition (csr_build.hip) ---------------------------------------------------------------
 size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz);

@@ -1,0 +1,124 @@
+// Sizes of the work partitions (csr_build.hip) as functions of the matrix's shape: host arithmetic only, so that the
+// bounds the workspaces are laid out by can be checked without a device.
+#pragma once
+#include <stdlib.h>
+#include "isp_internal.h"
+
+namespace isp_part {
+
+struct partition_params {
+  int block_cost, hub_t, seg_len;
+  int row_cost;   // cost units of a row besides its entries (1; 2 in the derived matrix, which allows larger blocks)
+  int bands;      // column bands of the finest cut (a power of two); 1 = no band cuts
+  int min_piece;  // a hub row is cut into at most degree / min_piece bands
+};
+
+constexpr int MAX_BANDS = 64;  // one piece per lane
+// Column bands a hub row of deg entries is cut into: the largest power of two <= min(bands, deg / min_piece).
+__host__ __device__ inline int hub_bands(int64_t deg, const partition_params& pp) {
+  int br = 1;
+  while (br * 2 <= pp.bands && (int64_t)(br * 2) * pp.min_piece <= deg) br *= 2;
+  return br;
+}
+
+inline int64_t max_hub_rows(int64_t n_rows, int64_t nnz, const partition_params& pp) {
+  const int64_t h = nnz / ((int64_t)pp.hub_t + 1);
+  return h < n_rows ? h : n_rows;
+}
+
+// Most segments: a row of degree deg has at most deg / min_piece pieces, and a piece of len entries at most
+// len / seg_len + 1 segments.
+inline int64_t max_segments(int64_t n_rows, int64_t nnz, const partition_params& pp) {
+  return nnz / pp.seg_len + (pp.bands > 1 ? nnz / pp.min_piece : 0) + max_hub_rows(n_rows, nnz, pp) + 1;
+}
+
+inline int env_int(const char* name, int dflt, int lo, int hi) {
+  const char* s = getenv(name);
+  if (!s || !*s) return dflt;
+  long v = strtol(s, nullptr, 10);
+  if (v < lo) v = lo;
+  if (v > hi) v = hi;
+  return (int)v;
+}
+
+// slots: wavefront slots of the device (4,096 on an MI355X: 256 compute units)
+inline partition_params get_params(int64_t n_rows, int64_t nnz, int64_t slots) {
+  partition_params p;
+  p.row_cost = 1;
+  // Upper limits = what the grouped kernels' per-wave LDS tables hold (block_cost + hub_t <= 768
+  // entries, block_cost <= 256 rows, seg_len <= 768 entries).  The environment overrides exist for
+  // tuning and for tests that want many small work items.
+  // Small matrices get smaller row blocks, about as many as the chip has wavefront slots (compute units x 16):
+  // a wavefront's work is a chain of dependent memory round trips, and a short chain on every slot
+  // finishes sooner than a long one on a few (4,096 rows x 9 entries: 16 -> 7 us per SpMM).
+  int64_t auto_cost = (nnz + n_rows + slots - 1) / slots;
+  auto_cost = auto_cost < 16 ? 16 : (auto_cost > 256 ? 256 : auto_cost);
+  p.block_cost = env_int("ISP_BLOCK_COST", (int)auto_cost, 16, 256);
+  // ... and shorter hub segments, for the same reason and because the segments are the heavy items that the
+  // launch hands out last: a quarter of the per-slot share, between 80 and 512 entries, rows of more than two
+  // segments' worth being hubs (2.4 M entries: segments of 157 instead of 512, 0.512 -> 0.468 ms for four
+  // SpMMs; 0.6 M entries: 0.167 -> 0.155 ms; from 8 M entries up the sizes are 512 / 512 as before).
+  // With many columns a column band of the dense operand is far larger than an L2, and finer pieces of the
+  // hub rows (segments of at most 384, pieces from 192 entries) keep more of each segment's gathers inside its
+  // band (2.4 M columns: 5.30 -> 5.19 ms per SpMM, the other kernels 1-3 %); with few columns a band's popular
+  // rows fit an L2 anyway and the longer segments win (233 k columns: SDDMM 3.21 vs 3.32 ms).
+  // Measured again with the present kernels (segments 256 .. 512, smallest pieces 64 .. 256, on the three large
+  // benchmark graphs): segments of at most 320 and pieces from 128 entries are best or within 1 % of it for every
+  // kernel on every one of them (233 k columns: SpMM 2.68 -> 2.59 ms, SDDMM 2.71 -> 2.60 ms; 2.4 M columns:
+  // FusedMM 5.59 -> 5.41 ms; 1 M columns: FusedMM backward 1.36 -> 1.32 ms).
+  const int seg_cap = 320;
+  int64_t auto_seg = (nnz + n_rows + slots - 1) / slots / 4;
+  auto_seg = auto_seg < 80 ? 80 : (auto_seg > seg_cap ? seg_cap : auto_seg);
+  const int auto_hub = 2 * auto_seg > 512 ? 512 : (int)(2 * auto_seg);
+  p.hub_t = env_int("ISP_HUB_THRESHOLD", auto_hub, 8, 512);
+  p.seg_len = env_int("ISP_SEGMENT_LEN", (int)auto_seg, 8, 768);
+  int b = env_int("ISP_BANDS", 32, 1, MAX_BANDS);
+  while (b & (b - 1)) b &= b - 1;  // round down to a power of two
+  p.bands = b;
+  // (the lower limit bounds the number of segments, hence the partial-sum rows the workspace must hold)
+  const int mp_lo = p.seg_len / 8 > 4 ? p.seg_len / 8 : 4;
+  int mp = p.seg_len / 2 < 128 ? p.seg_len / 2 : 128;
+  if (mp < mp_lo) mp = mp_lo;
+  p.min_piece = env_int("ISP_MIN_PIECE", mp, mp_lo, 1 << 20);
+  return p;
+}
+
+// Block cost of the derived matrix.  Its rows cost two units besides their entries, so a block of B units holds
+// at most B / 2 rows and B may reach twice the ordinary 256 within the kernels' 256-row tables; its entries
+// (fewer than B plus the longest row) must fit their 768-entry tables.
+// One and a half times the ordinary block where the longest row leaves room for it (config 3: 384 units next to
+// rows of up to 384 entries; measured 4.75 ms per SpMM against 4.81 at 256 and 4.76 at 512, where the segments
+// have to shrink to 256 entries): every work item starts with a chain of dependent loads before its first
+// gather, and fewer, larger items pay it less often.
+inline int derived_block_cost(const partition_params& p1, int mid_t) {
+  const int longest = mid_t > p1.seg_len ? mid_t : p1.seg_len;
+  int dflt = p1.block_cost * 3 / 2;
+  if (dflt > 768 - longest) dflt = 768 - longest;
+  if (dflt < 16) dflt = 16;
+  return env_int("ISP_PACKED_BLOCK", dflt, 16, 512);
+}
+
+inline partition_params cut_params(const partition_params& p1, int mid_t) {
+  partition_params c = p1;
+  c.hub_t = mid_t;
+  const int room = 768 - derived_block_cost(p1, mid_t);  // longest row the derived matrix may have
+  // (the ordinary partition's segment length also bounds the pieces here: 320 against 384 measured 4.65 / 4.64 ms
+  // per SpMM on 2.4 M columns, 0.345 / 0.357 ms on 1 M columns at d = 64)
+  if (c.seg_len > room) c.seg_len = room;
+  // pieces of 64 entries or more, on up to 32 bands (measured on 2.4 M columns: smaller pieces fetch less but
+  // pay it back in partial rows)
+  c.min_piece = env_int("ISP_MIN_PIECE", 64, c.seg_len / 8 > 4 ? c.seg_len / 8 : 4, 1 << 20);
+  return c;
+}
+
+inline partition_params derived_params(const partition_params& p1, const partition_params& cut) {
+  partition_params d = p1;
+  d.hub_t = cut.hub_t > cut.seg_len ? cut.hub_t : cut.seg_len;  // no row of the derived matrix is longer
+  d.seg_len = d.hub_t;
+  d.bands = 1;
+  d.row_cost = 2;
+  d.block_cost = derived_block_cost(p1, cut.hub_t);
+  return d;
+}
+
+}  // namespace isp_part

@@ -47,10 +47,10 @@ extern "C" isp_status isp_spmm_static_scratch(const isp_csr_t* A, const float* X
   if ((st = isp_check_dense(Y, ldy, d, A->v.n_rows, "Y")) != ISP_OK) return st;
   // partial rows a launch may touch: one per hub-row segment, or one per piece where the handle has the
   // packed SpMM layout (large matrices with many columns)
-  const int n_partial = A->has_packed && A->info.spmm_pieces > A->v.n_seg ? A->info.spmm_pieces : A->v.n_seg;
+  const int64_t n_partial = A->spmm_rows;
   if (n_partial > ISP_STATIC_SCRATCH_ROWS)
-    return isp_fail(ISP_EUNSUPPORTED, "the handle needs %d partial rows (hub-row segments / row pieces); the static "
-                    "scratch holds %d (use isp_spmm, whose scratch is the build workspace)", n_partial,
+    return isp_fail(ISP_EUNSUPPORTED, "the handle needs %lld partial rows (hub-row segments / row pieces); the static "
+                    "scratch holds %d (use isp_spmm, whose scratch is the build workspace)", (long long)n_partial,
                     ISP_STATIC_SCRATCH_ROWS);
   float* ptr = nullptr;
   if ((st = scratch_address(A->device, &ptr)) != ISP_OK) return st;

@@ -125,6 +125,46 @@ def test_large_symmetric(mid, with_values):
         os.environ.pop("ISP_MID_THRESHOLD")
 
 
+def test_large_symmetric_with_more_pieces_than_segment_rows():
+    """Rows of about 290 entries: the packed layout cuts each into four pieces, more partial rows than the ordinary partition
+    is laid out for.  The shared transpose's scratch holds them in front of its packed values, which stay as they are."""
+    n, half = 70000, 145 * 70000
+    g = torch.Generator(device="cuda").manual_seed(3)
+    i, j = (torch.randint(n, (half,), device="cuda", generator=g) for _ in range(2))
+    code = torch.unique(torch.cat([i * n + j, j * n + i]))
+    indptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(torch.bincount(code // n, minlength=n), 0, out=indptr[1:])
+    indices = (code % n).to(torch.int32)
+    values = torch.randn(len(code), device="cuda", generator=g)
+    A = isp.csr_build(indptr, indices, values)
+    info = A.info()
+    seg, hub = info["segment_len"], info["hub_threshold"]
+    laid_out = info["nnz"] // seg + info["nnz"] // 128 + info["nnz"] // (hub + 1) + 2
+    assert info["spmm_pieces"] > laid_out, info  # (what this test is about)
+    At, _ = isp.csr_transpose_cached(A)
+    assert At.info()["symmetric_pattern"] == 1 and At.info()["spmm_pieces"] == info["spmm_pieces"]
+    B = isp.csr_alias(A, 128)
+    h_indptr, h_indices = indptr.cpu().numpy(), indices.cpu().numpy()
+    X = np.random.default_rng(0).standard_normal((n, 5)).astype(np.float32)
+
+    def check(handle, what):
+        ti, tj, _, tv = oracle.transpose(n, n, h_indptr, h_indices, values.cpu().numpy())
+        ref, mag = oracle.spmm(ti, tj, tv, X)
+        for k in range(2):  # the second call reads the packed values that the first one's partial rows lie in front of
+            Y = torch.full((n, 5), float("nan"), device="cuda")
+            isp.spmm(handle, dev(X), Y)
+            assert_close(Y, ref, mag, "%s, call %d" % (what, k))
+
+    check(At, "transpose")
+    check(B._At, "alias of the transpose")
+    values.copy_(torch.randn(len(code), device="cuda", generator=g))
+    isp.csr_values_changed(A)
+    check(At, "transpose, new values")
+    Y = torch.empty(n, 5, device="cuda")
+    isp.spmm(A, dev(X), Y)
+    assert_close(Y, *oracle.spmm(h_indptr, h_indices, values.cpu().numpy(), X), "the matrix itself")
+
+
 @pytest.mark.parametrize("n_rows,n_cols", [(20000, 70001), (300000, 1000), (16385, 63), (3, 9)])
 def test_rewritten_values_of_long_columns(n_rows, n_cols):
     """The transpose's values gathered block of rows by block of rows: long, short and empty parts, columns past the last."""
