@@ -86,8 +86,14 @@ const char* dense_of(const Tensor& t, Dense& o) {
   o.ld = o.rows > 1 ? t.stride(0) : std::max<int64_t>(t.stride(0), o.d);
   return nullptr;
 }
+// (THPVariable_Unpack trusts its argument: whatever comes from a caller is looked at first)
+bool is_tensor(PyObject* o) {
+  if (THPVariable_Check(o)) return true;
+  PyErr_SetString(PyExc_TypeError, "a torch tensor is expected");
+  return false;
+}
 bool dense_of(PyObject* o, Dense& out) {
-  if (!THPVariable_Check(o)) { PyErr_SetString(PyExc_TypeError, "a torch tensor is expected"); return false; }
+  if (!is_tensor(o)) return false;
   const char* bad = dense_of(THPVariable_Unpack(o), out);
   if (bad) fail(bad);
   return !bad;
@@ -364,7 +370,7 @@ PyObject* py_graph(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   HANDLE_TH_ERRORS
   ISP_ARGS(3)
   auto* c = static_cast<CellPtr*>(PyCapsule_GetPointer(a[0], CELL));
-  if (!c) return nullptr;
+  if (!c || (a[2] != Py_None && !is_tensor(a[2]))) return nullptr;
   auto g = std::make_shared<Graph>();
   g->A = *c;
   Py_INCREF(a[1]);
@@ -390,6 +396,7 @@ PyObject* py_ag_spmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   HANDLE_TH_ERRORS
   ISP_ARGS(3)
   GraphPtr g = graph_of(a[0]);
+  if ((a[1] != Py_None && !is_tensor(a[1])) || !is_tensor(a[2])) return nullptr;
   const Tensor values = a[1] == Py_None ? Tensor() : THPVariable_Unpack(a[1]);
   const Tensor x = THPVariable_Unpack(a[2]);
   Tensor Y;
@@ -424,6 +431,7 @@ PyObject* py_ag_reduce(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   HANDLE_TH_ERRORS
   ISP_ARGS(3)
   GraphPtr g = graph_of(a[0]);
+  if (!is_tensor(a[1])) return nullptr;
   const Tensor x = THPVariable_Unpack(a[1]);
   const int reduce = (int)PyLong_AsLong(a[2]);
   if (PyErr_Occurred()) return nullptr;
@@ -460,6 +468,7 @@ PyObject* py_ag_fused(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   HANDLE_TH_ERRORS
   ISP_ARGS(2)
   GraphPtr g = graph_of(a[0]);
+  if (!is_tensor(a[1])) return nullptr;
   const Tensor x = THPVariable_Unpack(a[1]);
   Tensor Y;
   {
