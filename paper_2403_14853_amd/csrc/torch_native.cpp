@@ -506,7 +506,18 @@ PyObject* py_init(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   Py_RETURN_NONE;
 }
 
-#define ISP_DEF(name, fn) {name, (PyCFunction)(void (*)(void))(PyObject * (*)(PyObject*, PyObject* const*, Py_ssize_t)) fn, METH_FASTCALL, nullptr}
+// No C++ exception leaves an entry point: asking some tensors (vmap's, sparse ones) for strides or storage throws.
+template <PyObject* (*FN)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t nargs) {
+  try {
+    return FN(self, a, nargs);
+  } catch (...) {
+    torch::translate_exception_to_python(std::current_exception());
+    return nullptr;
+  }
+}
+
+#define ISP_DEF(name, fn) {name, (PyCFunction)(void (*)(void))(PyObject * (*)(PyObject*, PyObject* const*, Py_ssize_t)) guarded<fn>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
     ISP_DEF("init", py_init),
     ISP_DEF("cell", py_cell),

@@ -33,3 +33,19 @@ def test_dense_operands_must_be_tensors(nat, cell, x):
             nat.ag_spmm(graph, x, t)
         with pytest.raises(TypeError):
             nat.graph(cell, object(), x)
+
+
+def test_tensors_without_storage_raise(nat, cell):
+    """vmap's tensors have no storage to point into: an exception, in every entry point."""
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    graph = nat.graph(cell, object(), None)
+    calls = [lambda x: nat.spmm(cell, x, x, 0), lambda x: nat.spmm_static_scratch(cell, x, x, 0),
+             lambda x: nat.sddmm(cell, x, x, x, 0, 0), lambda x: nat.fusedmm(cell, x, x, 0, 0),
+             lambda x: nat.fusedmm_backward(cell, x, x, x, 0, 0), lambda x: nat.spmm_reduce(cell, x, x, 3, x, 0),
+             lambda x: nat.spmm_reduce_backward(cell, x, x, 3, x, 0), lambda x: nat.ag_spmm(graph, None, x),
+             lambda x: nat.ag_reduce(graph, x, 3), lambda x: nat.ag_fused(graph, x)]
+    with FakeTensorMode():
+        X = torch.empty(3, 4, 8, device="cuda")
+        for call in calls:
+            with pytest.raises(RuntimeError):
+                torch.func.vmap(call)(X)
