@@ -359,6 +359,13 @@ struct FusedBackward : torch::autograd::Node {
   }
 };
 
+// The nodes have no forward-mode rule: a tangent would be lost without a word.
+bool no_tangent(const Tensor& t) {
+  if (!t.defined() || !t._fw_grad(/*level=*/0).defined()) return true;
+  PyErr_SetString(PyExc_NotImplementedError, "the sparse operations have no forward-mode derivative");
+  return false;
+}
+
 GraphPtr graph_of(PyObject* c) {
   auto* p = static_cast<GraphPtr*>(PyCapsule_GetPointer(c, GRAPH));
   if (!p) throw python_error();
@@ -399,6 +406,7 @@ PyObject* py_ag_spmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   if ((a[1] != Py_None && !is_tensor(a[1])) || !is_tensor(a[2])) return nullptr;
   const Tensor values = a[1] == Py_None ? Tensor() : THPVariable_Unpack(a[1]);
   const Tensor x = THPVariable_Unpack(a[2]);
+  if (!no_tangent(values) || !no_tangent(x)) return nullptr;
   Tensor Y;
   {
     pybind11::gil_scoped_release release;
@@ -433,6 +441,7 @@ PyObject* py_ag_reduce(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   GraphPtr g = graph_of(a[0]);
   if (!is_tensor(a[1])) return nullptr;
   const Tensor x = THPVariable_Unpack(a[1]);
+  if (!no_tangent(x)) return nullptr;
   const int reduce = (int)PyLong_AsLong(a[2]);
   if (PyErr_Occurred()) return nullptr;
   Tensor Y, arg;
@@ -470,6 +479,7 @@ PyObject* py_ag_fused(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   GraphPtr g = graph_of(a[0]);
   if (!is_tensor(a[1])) return nullptr;
   const Tensor x = THPVariable_Unpack(a[1]);
+  if (!no_tangent(x)) return nullptr;
   Tensor Y;
   {
     pybind11::gil_scoped_release release;

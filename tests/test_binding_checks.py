@@ -49,3 +49,18 @@ def test_tensors_without_storage_raise(nat, cell):
         for call in calls:
             with pytest.raises(RuntimeError):
                 torch.func.vmap(call)(X)
+
+
+def test_forward_mode_is_refused(nat, cell):
+    import torch.autograd.forward_ad as fw
+    graph = nat.graph(cell, object(), None)
+    t = torch.zeros(4, 8)
+    with fw.dual_level():
+        x = fw.make_dual(t, torch.ones(4, 8))
+        v = fw.make_dual(torch.ones(6), torch.ones(6))
+        for call in (lambda: nat.ag_spmm(graph, None, x), lambda: nat.ag_spmm(graph, v, t),
+                     lambda: nat.ag_reduce(graph, x, 3), lambda: nat.ag_fused(graph, x)):
+            with pytest.raises(NotImplementedError):
+                call()
+        with fw._set_fwd_grad_enabled(False), pytest.raises(AssertionError):  # (not a tangent then; refused as a CPU tensor)
+            nat.ag_spmm(graph, None, x)
