@@ -9,7 +9,11 @@ handle for all later epochs (Section 3.3).
 """
 from __future__ import annotations
 
+import torch
+
 from . import binding as _b
+
+_recorder = torch._C._get_tracing_state  # None unless torch.jit.trace is recording
 
 
 class SparseGraph:
@@ -33,8 +37,38 @@ class SparseGraph:
         return _b.csr_transpose_cached(self.handle)[0]
 
 
+class _Recorded(torch.autograd.Function):
+    """One of the operations below while torch.jit.trace records a program: the native nodes are not among the operations
+    that a recording knows (all that it would keep is the empty output they write into), an autograd function is."""
+
+    @staticmethod
+    def forward(ctx, run, values, X):
+        Y = X.new_empty(0)  # (an output has to be made while the recorder looks on)
+        recorder = _recorder()
+        torch._C._set_tracing_state(None)
+        try:
+            with torch.enable_grad():
+                ctx.leaves = [t if t is None else t.detach().requires_grad_(need)
+                              for t, need in zip((values, X), ctx.needs_input_grad[1:])]
+                ctx.output = run(*ctx.leaves)
+            Y.set_(ctx.output.detach())
+        finally:
+            torch._C._set_tracing_state(recorder)
+        ctx.save_for_backward(X)  # (X overwritten, or a second backward without retain_graph: refused)
+        return Y
+
+    @staticmethod
+    def backward(ctx, dY):
+        ctx.saved_tensors
+        wanted = [t for t, need in zip(ctx.leaves, ctx.needs_input_grad[1:]) if need]
+        got = iter(torch.autograd.grad(ctx.output, wanted, dY, retain_graph=True))
+        return (None, *(next(got) if need else None for need in ctx.needs_input_grad[1:]))
+
+
 def spmm(graph: SparseGraph, X):
     """Differentiable Y = A X (with respect to X and, if ``graph.values`` requires grad, to the values)."""
+    if _recorder() is not None:
+        return _Recorded.apply(lambda values, X: _b._nat.ag_spmm(graph._native, values, X), graph.values, X)
     return _b._nat.ag_spmm(graph._native, graph.values, X)
 
 
@@ -48,6 +82,8 @@ def matmul(graph: SparseGraph, X, reduce: str = "sum"):
         raise ValueError("reduce must be 'sum', 'mean', 'min' or 'max'")
     if graph.values is not None and graph.values.requires_grad:
         raise NotImplementedError("gradients with respect to the edge values exist for reduce='sum' only")
+    if _recorder() is not None:
+        return _Recorded.apply(lambda _, X: _b._nat.ag_reduce(graph._native, X, _b.REDUCE[reduce]), None, X)
     return _b._nat.ag_reduce(graph._native, X, _b.REDUCE[reduce])
 
 
@@ -55,4 +91,6 @@ def fusedmm(graph: SparseGraph, X):
     """Differentiable sigmoid FusedMM: y_i = sum_j a_ij sigmoid(<x_i, x_j>) x_j (with respect to X only)."""
     if graph.values is not None and graph.values.requires_grad:
         raise NotImplementedError("FusedMM has no gradient with respect to the edge values")
+    if _recorder() is not None:
+        return _Recorded.apply(lambda _, X: _b._nat.ag_fused(graph._native, X), None, X)
     return _b._nat.ag_fused(graph._native, X)

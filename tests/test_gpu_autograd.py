@@ -121,3 +121,53 @@ def test_matmul_with_the_other_reductions(reduce):
     trainable = ag.SparseGraph(dev(w.indptr), dev(w.indices), dev(w.values).requires_grad_(True))
     with pytest.raises(NotImplementedError):
         ag.matmul(trainable, X, reduce)
+
+
+@pytest.mark.parametrize("op", ["spmm", "mean", "max", "fused"])
+def test_recorded_by_jit_trace(op):
+    """A traced program runs the operation on new inputs, and its backward, as the program itself does."""
+    from paper_2403_14853_amd import autograd as ag
+    w = graphgen.make_config(1, shrink=64)
+    g = ag.SparseGraph(dev(w.indptr), dev(w.indices), dev(w.values))
+    if op == "spmm":
+        f = lambda x: torch.relu(ag.spmm(g, 2 * x)) + 1
+    elif op == "fused":
+        f = lambda x: torch.relu(ag.fusedmm(g, 0.1 * x)) + 1
+    else:
+        f = lambda x: torch.relu(ag.matmul(g, 2 * x, op)) + 1
+    traced = torch.jit.trace(f, dev(w.X), check_trace=False)
+    new = dev(w.dY)
+    assert torch.equal(traced(new), f(new))
+    grads = []
+    for run in (f, traced):
+        x = new.clone().requires_grad_(True)
+        (run(x) * dev(w.X)).sum().backward()
+        grads.append(x.grad)
+    assert torch.equal(*grads) and float(grads[0].abs().max()) > 0
+
+
+def test_trace_with_trained_values():
+    """The edge values as an input of the traced program that takes part in the gradients."""
+    from paper_2403_14853_amd import autograd as ag
+    w = graphgen.make_config(1, shrink=64)
+    values = dev(w.values).requires_grad_(True)
+    g = ag.SparseGraph(dev(w.indptr), dev(w.indices), values)
+
+    class Layer(torch.nn.Module):
+        def __init__(self):
+            super().__init__()
+            self.values = torch.nn.Parameter(values.detach())
+            g.values = self.values
+
+        def forward(self, x):
+            return ag.spmm(g, x)
+
+    layer = Layer()
+    traced = torch.jit.trace(layer, dev(w.X), check_trace=False)
+    grads = []
+    for run in (layer, traced):
+        layer.zero_grad()
+        x = dev(w.dY).requires_grad_(True)
+        (run(x) * dev(w.X)).sum().backward()
+        grads.append((x.grad, layer.values.grad))
+    assert torch.equal(grads[0][0], grads[1][0]) and torch.equal(grads[0][1], grads[1][1])
