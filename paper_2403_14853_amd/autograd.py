@@ -66,7 +66,10 @@ class _Recorded(torch.autograd.Function):
 
 
 def spmm(graph: SparseGraph, X):
-    """Differentiable Y = A X (with respect to X and, if ``graph.values`` requires grad, to the values)."""
+    """Differentiable Y = A X (with respect to X and, if ``graph.values`` requires grad, to the values).
+    X is kept for the backward only where the values have a gradient.  Without one the backward needs nothing of the
+    forward, as with torch's own linear operations: X may be overwritten before it, and it may run again without
+    ``retain_graph``."""
     if _recorder() is not None:
         return _Recorded.apply(lambda values, X: _b._nat.ag_spmm(graph._native, values, X), graph.values, X)
     return _b._nat.ag_spmm(graph._native, graph.values, X)

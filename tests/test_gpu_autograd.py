@@ -171,3 +171,34 @@ def test_trace_with_trained_values():
         (run(x) * dev(w.X)).sum().backward()
         grads.append((x.grad, layer.values.grad))
     assert torch.equal(grads[0][0], grads[1][0]) and torch.equal(grads[0][1], grads[1][1])
+
+
+def test_second_backward_and_overwritten_input():
+    """What a backward still needs decides: nothing for constant values, X for trained ones and for FusedMM."""
+    from paper_2403_14853_amd import autograd as ag
+    w = graphgen.make_config(1, shrink=128)
+    fixed = ag.SparseGraph(dev(w.indptr), dev(w.indices), dev(w.values))
+    trained = ag.SparseGraph(dev(w.indptr), dev(w.indices), dev(w.values).requires_grad_(True))
+    ti, tj, _, tv = oracle.transpose(w.n, w.n, w.indptr, w.indices, w.values)
+    for g, op, kept in ((fixed, ag.spmm, False), (trained, ag.spmm, True), (fixed, ag.fusedmm, True)):
+        leaf = dev(w.X).requires_grad_(True)
+        Y = op(g, leaf)
+        Y.backward(dev(w.dY))
+        if kept:
+            with pytest.raises(RuntimeError):
+                Y.backward(dev(w.dY))
+        else:
+            leaf.grad = None
+            Y.backward(dev(w.dY))
+            assert_close(leaf.grad, *oracle.spmm(ti, tj, tv, w.dY), "second backward")
+        X = leaf.clone()
+        Y = op(g, X)
+        with torch.no_grad():
+            X.zero_()
+        leaf.grad = None
+        if kept:
+            with pytest.raises(RuntimeError):
+                Y.backward(dev(w.dY))
+        else:
+            Y.backward(dev(w.dY))
+            assert_close(leaf.grad, *oracle.spmm(ti, tj, tv, w.dY), "after X was overwritten")
