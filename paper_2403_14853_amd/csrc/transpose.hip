@@ -291,21 +291,23 @@ int gather_blocks(int64_t n_rows, int64_t n_cols, int64_t nnz) {
   return n_cols * b * 4 <= nnz ? (int)b : 0;
 }
 
-// bound[b * n_cols + c]: first entry of column c in block b or later, for b = 1 .. n_blocks - 1.
+// bound[b * n_cols + c]: first entry of column c in block b or later, for b = 0 .. n_blocks - 1.  n_chunks workgroups per
+// block, all in the grid's first dimension (a matrix of 2^31 rows has 131,072 blocks, the second holds 65,535).
 __global__ void __launch_bounds__(256) k_block_bounds(const int64_t* __restrict__ t_indptr,
                                                       const int32_t* __restrict__ t_indices, int64_t n_cols,
-                                                      int rows_per_block, int32_t* __restrict__ bound) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                                      int rows_per_block, unsigned n_chunks, int32_t* __restrict__ bound) {
+  const unsigned b = blockIdx.x / n_chunks;
+  const int64_t c = (int64_t)(blockIdx.x % n_chunks) * blockDim.x + threadIdx.x;
   if (c >= n_cols) return;
-  const int64_t row = (int64_t)blockIdx.y * rows_per_block;
+  const int64_t row = (int64_t)b * rows_per_block;
   int64_t lo = t_indptr[c], hi = t_indptr[c + 1];
-  if (blockIdx.y > 0) {
+  if (b > 0) {
     while (lo < hi) {
       const int64_t mid = (lo + hi) >> 1;
       if (t_indices[mid] < row) lo = mid + 1; else hi = mid;
     }
   }
-  bound[blockIdx.y * n_cols + c] = (int32_t)lo;
+  bound[b * n_cols + c] = (int32_t)lo;
 }
 
 __global__ void __launch_bounds__(256) k_gather_blocked(const int32_t* __restrict__ perm, const float* __restrict__ values,
@@ -642,8 +644,10 @@ isp_status isp_transpose_refresh_values(isp_csr* A, hipStream_t s) {
     const int n_blocks = gather_blocks(A->v.n_rows, A->v.n_cols, A->v.nnz);
     const int n_chunks = (int)((A->v.n_cols + GB_COLS - 1) / GB_COLS);
     if (!At->gather_bound_valid) {  // (115 M entries, 233 k columns: 216 us once)
-      k_block_bounds<<<dim3((unsigned)((A->v.n_cols + 255) / 256), (unsigned)n_blocks), 256, 0, s>>>(
-          At->v.indptr, At->v.indices, A->v.n_cols, (int)((A->v.n_rows + n_blocks - 1) / n_blocks), At->gather_bound);
+      const unsigned chunks = (unsigned)((A->v.n_cols + 255) / 256);  // (n_cols * n_blocks <= nnz / 4: gather_blocks)
+      k_block_bounds<<<chunks * (unsigned)n_blocks, 256, 0, s>>>(At->v.indptr, At->v.indices, A->v.n_cols,
+                                                                 (int)((A->v.n_rows + n_blocks - 1) / n_blocks), chunks,
+                                                                 At->gather_bound);
       ISP_LAUNCH_CHECK();
       At->gather_bound_valid = !stream_is_capturing(s);
     }

@@ -182,3 +182,24 @@ def test_rewritten_values_of_long_columns(n_rows, n_cols):
     isp.csr_values_changed(A)
     _, _, t_values, perm = At.export()
     assert torch.equal(t_values, values[perm.long()])
+
+
+def test_rewritten_values_of_more_blocks_than_a_grid_dimension_holds():
+    """1.07 G rows, most of them empty: 65,552 blocks of rows."""
+    n_rows, n_cols, nnz = 1_074_000_000, 60, (16 << 20) + 5
+    g = torch.Generator(device="cuda").manual_seed(1)
+    rows = torch.randint(n_rows, (nnz,), device="cuda", generator=g)
+    rows[:8] = n_rows - 1
+    cols = torch.randint(n_cols, (nnz,), device="cuda", generator=g, dtype=torch.int32)
+    indptr = torch.zeros(n_rows + 1, dtype=torch.int64, device="cuda")
+    indptr[1:].scatter_add_(0, rows, torch.ones_like(rows))
+    torch.cumsum(indptr, 0, out=indptr)
+    values = torch.ones(nnz, device="cuda")
+    A = isp.csr_build(indptr, cols, values, n_cols=n_cols)
+    At, _ = isp.csr_transpose_cached(A)
+    for _ in range(2):  # the bounds are found by the first call and kept
+        values.copy_(torch.randn(nnz, device="cuda", generator=g))
+        isp.csr_values_changed(A)
+        _, _, t_values, perm = At.export()
+        assert torch.equal(t_values, values[perm.long()])
+    A.destroy()
