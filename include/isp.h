@@ -21,8 +21,10 @@
  *     alignment is accepted; rows that start on 128-byte lines (ld a multiple of 32, base pointer aligned)
  *     gather fastest.
  *   - stream is a hipStream_t passed as void* (NULL = the default stream).  Compute calls are
- *     asynchronous on it.  isp_csr_build and a cache-missing isp_csr_transpose_cached
- *     synchronise the stream once, to read a few counters back.
+ *     asynchronous on it.  isp_csr_build and a cache-missing isp_csr_transpose_cached synchronise the
+ *     stream, once to three times, to read a few counters back (once per work partition they build: one, or
+ *     three with the packed SpMM layout; the transpose of a large square matrix once more, for the
+ *     comparison with A).
  *   - Outputs are overwritten (Y = A X, not +=).  n_rows = 0 and nnz = 0 are valid.
  *   - Every function returns a status; nothing throws or aborts across this boundary.  After a
  *     failure isp_last_error() returns a thread-local message.
@@ -33,8 +35,9 @@
  *   - Results are run-to-run bitwise deterministic: no floating-point atomics are used.
  *   - Environment variables (tuning and tests only; none is needed).  All are read when isp_csr_build runs and
  *     are kept in the handle; no compute call reads the environment.  (The partition sizes of a cached transpose
- *     are read when it is built, by the first isp_csr_transpose_cached call and its workspace query; the other
- *     settings it inherits from its source.)
+ *     are read when it is built, by the first isp_csr_transpose_cached call and its workspace query - except that
+ *     a symmetric pattern of more than 4 Mi entries shares the partitions of its source as they are, whatever the
+ *     environment says by then.  The other settings it inherits from its source.)
  *       ISP_BLOCK_COST, ISP_HUB_THRESHOLD, ISP_SEGMENT_LEN, ISP_BANDS, ISP_MIN_PIECE, ISP_MID_THRESHOLD,
  *       ISP_PACKED_BLOCK:
  *                              sizes of the work partition (clamped to what the kernels' tables hold)
@@ -118,7 +121,7 @@ isp_status isp_csr_build_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, 
  *   workspace: device memory, 256-byte aligned, >= isp_csr_build_workspace() bytes; borrowed
  *              until isp_csr_destroy.
  *   flags: 0 or ISP_TRUSTED.  Without ISP_TRUSTED a malformed CSR yields ISP_EBADCSR and no handle.
- * Synchronises `stream` once.  n_rows, n_cols < 2^31 - 1 and nnz < 2^31 - 1, else ISP_EUNSUPPORTED.
+ * Synchronises `stream` (see above).  n_rows, n_cols < 2^31 - 1 and nnz < 2^31 - 1, else ISP_EUNSUPPORTED.
  */
 isp_status isp_csr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int64_t* indptr,
                          const int32_t* indices, const float* values, void* workspace,
@@ -135,7 +138,7 @@ isp_status isp_csr_transpose_workspace(const isp_csr_t* A, size_t* bytes);
  *   A of each transposed entry), t_values[q] = values[perm[q]] (absent when A has no values).
  * These arrays live in `workspace` (256-byte aligned, borrowed until isp_csr_destroy(A)).
  *   *At: handle owned by A (never destroy it yourself).  *was_cached: 1 on a cache hit (may be NULL).
- * A cache miss synchronises `stream` once.
+ * A cache miss synchronises `stream` (see above).
  */
 isp_status isp_csr_transpose_cached(isp_csr_t* A, void* workspace, size_t workspace_bytes,
                                     void* stream, const isp_csr_t** At, int* was_cached);
@@ -143,15 +146,16 @@ isp_status isp_csr_transpose_cached(isp_csr_t* A, void* workspace, size_t worksp
 /*
  * Tell the handle that the caller has overwritten A's values array in place (same pointer, same structure),
  * as happens every epoch when the edge values are trained from the SDDMM gradients.  What Section 3.3 caches
- * stays cached - A^T's structure, its permutation and both work partitions - and only the transposed values
- * are gathered again: t_values[q] = values[perm[q]], one asynchronous pass on `stream`; if a mean-reduction
+ * stays cached - A^T's structure, its permutation and both work partitions - and only the copies of the values
+ * are gathered again, asynchronously on `stream`: t_values[q] = values[perm[q]] and, where the packed SpMM layout
+ * exists, that layout's copies; if a mean-reduction
  * backward has run on the handle, the per-entry values it keeps (value / row length) are recomputed right
  * behind it on the same stream.  Everything happens in stream order, so the call may be captured into a HIP
  * graph (every replay refreshes), and graphs captured earlier read the refreshed arrays.  What a graph cannot
  * see is a change of the cache's bookkeeping on the host: a graph captured BEFORE the first mean backward of a
  * handle contains that first call's fill pass and keeps running it on every replay - correct, only redundant.
- * A no-op for a handle without values or without a cached transpose.  A must be the source handle, not its
- * transpose.
+ * A no-op for a handle without values, or with neither a cached transpose nor the packed layout.  A must be the
+ * source handle, not its transpose.
  */
 isp_status isp_csr_values_changed(isp_csr_t* A, void* stream);
 
@@ -260,9 +264,9 @@ isp_status isp_fusedmm_backward(isp_csr_t* A, const float* X, int64_t ldx, const
  *         and comparison in fp32; arg[i,k] = position p (index into indices / values) of the first entry that
  *         attains it; empty row -> Y = 0, arg = -1.  arg is int32, n_rows x d, row-major, dense (leading
  *         dimension d), required for min / max, ignored otherwise.
- * sum has the tuned kernels; mean reuses them, and min / max have a kernel of the same design, when width and
- * alignment allow (d and the leading dimensions multiples of 4, 16-byte aligned pointers); other shapes run
- * on the generic path.
+ * sum has the tuned kernels; mean reuses them, and min / max have kernels of the same design, from 4 columns up
+ * at any leading dimension and alignment; narrower operands, and min / max on operands of 4 GB or 2^24 rows
+ * and more, run on the generic path.
  */
 isp_status isp_spmm_reduce(const isp_csr_t* A, const float* X, int64_t ldx, int32_t d, int reduce, float* Y,
                            int64_t ldy, int32_t* arg, void* stream);

@@ -4,10 +4,10 @@
 // or two float4), so G = 64 / LPG dot products are reduced side by side with the same DPP
 // instructions.  Two float4 per lane halve the lanes per dot product: a step covers twice the entries,
 // with one lane-reduction stage and one evaluation of the edge function less per entry - these kernels
-// keep the vector ALU busy, so instructions per entry count.  In row blocks the row operand (U's row
-// for SDDMM, x_i / g_i for FusedMM) is loaded with every step instead of being kept across steps: it
-// is an L1 hit after a row's first step and keeps the main loop free of row-change stalls; a hub
-// segment, which is one row throughout, loads it once.
+// keep the vector ALU busy, so instructions per entry count.  The row operand (U's row for SDDMM, x_i / g_i
+// for FusedMM) is loaded once per hub segment, which is one row throughout.  In row blocks one float4 per
+// lane loads it with a row's first step in a run and keeps it; two float4 load it with every step (an L1 hit
+// after the first).
 #pragma once
 #include <type_traits>
 #include "run_stream.h"
@@ -148,7 +148,8 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
   bool carried = R.mid;  // the next row to end began in an earlier run
   bool ended = false;    // a row has ended in this run
   // SEG (a hub segment: one matrix row for the whole item): the row operand is loaded once and stays in
-  // registers.  Row blocks load it with every step, which keeps their loop free of row-change stalls.
+  // registers.  Row blocks issue a load with every step (load_first), FIRST_ONLY or not, which keeps their loop free
+  // of row-change stalls.
   auto run = [&](auto seg_tag) {
     constexpr bool SEG = decltype(seg_tag)::value;
     constexpr int NR = SEG ? 0 : NROW;  // per-step row-operand registers

@@ -264,9 +264,12 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
   //  - in a launch of up to 128 columns the smallest group that covers them wins (groups of 4 lanes, which share an
   //    instruction between 16 entries, only from 1 M entries up: they take longer to set an item up);
   //  - 128 whole-line columns run as two 64-column slices, dealt to alternating XCDs, where the dense operand is far
-  //    larger than an L2 (each L2 then keeps half-rows of twice as many hot columns): from 80 k columns up (169 k:
-  //    108 -> 95; 60 k: 47 -> 50), but with the packed layout, whose bands already fit, only from 512 k (233 k
-  //    columns: 2509 -> 2665; 2.4 M: 5144 -> 4731);
+  //    larger than an L2 (each L2 then keeps half-rows of twice as many hot columns): from 80 k columns up (60 k: 47 ->
+  //    50), but with the packed layout, whose bands already fit, only from 512 k (233 k columns: 2509 -> 2665; 2.4 M:
+  //    5144 -> 4731).  What it gives in between depends on where X is: 169 k columns (X and Y 87 MB each), one X and Y
+  //    again and again, which the Infinity Cache holds, 108 -> 95; two pairs in turn 109 -> 108; four or more pairs in
+  //    turn, X from HBM every time, 112 -> 113: the misses' rate decides there, whatever the L2s keep.  A layer's X
+  //    has usually just been written;
   //  - between 129 and 256 columns in one launch, one 64-lane group up to 224 columns (but 128 columns and the rest
   //    from 512 k columns up: 200 columns, 4586 against 5021 on 233 k, 1608 against 1531 on 1 M), else two
   //    128-column slices.

@@ -1,8 +1,8 @@
 // Sparse-dense product with the other reductions the paper's matmul offers (Section 3.4, 3.5):
 // mean, min, max - and their backward through the cached transpose.  The sum reduction has the tuned
-// kernels; mean reuses them when the operands qualify (rows divided by their length), min / max have a
-// grouped forward kernel of the same design for float4-aligned operands, and everything else runs on the
-// generic row-streaming skeleton (one nonzero per wave iteration, any width and alignment).
+// kernels and mean reuses them (rows divided by their length); min / max have run-streaming kernels of the same
+// design, forward and backward, from 4 columns up at any alignment where gather offsets fit 32 bits.  The rest
+// runs on the generic row-streaming skeleton (one nonzero per wave iteration, any width and alignment).
 //   mean : Y[i] = (sum_p a_p x_j) / len_i
 //   min / max : Y[i,k] = min / max_p a_p x_jk (product and comparison in fp32), arg[i,k] = position p of
 //               the first entry attaining it; empty row -> 0 and -1

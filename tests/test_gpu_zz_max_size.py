@@ -1,6 +1,6 @@
 """Close to the largest matrix the index types allow (nnz = 2.12e9, 99 % of 2^31 - 2): int64
 offsets, grid sizes and the radix sort's tables at full scale.  About half a minute and ~50 GB of
-host memory on the GPU machine; collected last, and skipped when ISP_SKIP_HUGE=1.  Outputs are checked
+host memory on the host; collected last, and skipped when ISP_SKIP_HUGE=1.  Outputs are checked
 on sampled rows / columns against the oracle."""
 import os
 import time
