@@ -12,8 +12,10 @@ The default workload is configuration 3, the largest power-law graph (R-MAT, n =
 ~123.6 M stored entries, d = 128), which is the one the bandwidth target is quoted on.
 """
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -233,7 +235,9 @@ def main():
         "achieved_frac_of_copy_ceiling": round(achieved / copy_gbps, 4),
     }
     rec = None if (args.no_relabel or args.shrink != 1 or args.ops) else counter_record(w.name, dom_kernel)
-    if rec:  # counter bytes of the stored profile record over this run's launch time
+    if rec and not rec["current"]:
+        roofline["traffic_note"] = "the counters kept in profiles/counter_records.txt are of other source (%s)" % rec["commit"]
+    elif rec:  # counter bytes of the stored profile record over this run's launch time
         roofline["traffic"] = rec["bytes"]
         roofline["traffic_commit"] = rec["commit"]
         roofline["traffic_source"] = "profiles/counter_records.txt (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, calibrated)"
@@ -268,11 +272,30 @@ def main():
     print(json.dumps(out))
 
 
+def source_digest(kernel, csrc=os.path.join(ROOT, "paper_2403_14853_amd", "csrc")):
+    """Digest of the code that decides what a dominant kernel fetches: its translation unit, the work partition's, and the
+    headers that they include, without comments and white space."""
+    units = {"k_spmm_grouped": "spmm.hip", "k_fused_grouped<g_fwd>": "fused_fwd.hip"}
+    if kernel not in units:
+        return None
+    todo, code = [units[kernel], "csr_build.hip"], {}
+    while todo:
+        name = todo.pop()
+        path = os.path.join(csrc, name)
+        if name in code or not os.path.exists(path):
+            continue
+        text = open(path).read()
+        todo += re.findall(r'#include "([^"]+)"', text)
+        code[name] = re.sub(r"\s+", "", re.sub(r"//[^\n]*|/\*.*?\*/", "", text, flags=re.S))
+    return hashlib.sha256("".join(k + code[k] for k in sorted(code)).encode()).hexdigest()[:12]
+
+
 def counter_record(workload, kernel):
     """The rocprofv3 counter readings kept for this workload's dominant kernel in profiles/counter_records.txt
     (per launch: FETCH_SIZE and WRITE_SIZE in KiB, TCC_HIT_sum, TCC_MISS_sum, the average duration of the run
-    that was counted, and the commit whose kernels were measured), or None.  The calibration factors that
-    turn counter KiB into bytes are lines of the same file."""
+    that was counted, the commit whose kernels were measured and the digest of their source; current = that is
+    the present source), or None.  The calibration factors that turn counter KiB into bytes are lines of the
+    same file."""
     path = os.path.join(ROOT, "profiles", "counter_records.txt")
     if not os.path.exists(path):
         return None
@@ -282,9 +305,9 @@ def counter_record(workload, kernel):
         f = line.split("#")[0].split()
         if len(f) == 2 and f[0] in factor:
             factor[f[0]] = float(f[1])
-        elif len(f) == 8 and f[0] == workload and f[1] == kernel:
+        elif len(f) == 9 and f[0] == workload and f[1] == kernel:
             rec = dict(fetch_kib=float(f[2]), write_kib=float(f[3]), tcc_hit=float(f[4]), tcc_miss=float(f[5]),
-                       avg_us=float(f[6]), commit=f[7])
+                       avg_us=float(f[6]), commit=f[7], current=f[8] == source_digest(kernel))
     if rec is None:
         return None
     rec["bytes"] = (factor["fetch_factor"] * rec["fetch_kib"] + factor["write_factor"] * rec["write_kib"]) * 1024.0

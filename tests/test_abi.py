@@ -93,3 +93,25 @@ def test_counter_records_parse_with_their_calibration():
         assert rec["bytes"] == (2.0 * rec["fetch_kib"] + rec["write_kib"]) * 1024.0
         assert rec["bytes"] > 2 * 4.0 * n * d, (workload, rec["bytes"])  # X read and Y written at least once
         assert rec["write_kib"] * 1024.0 >= 4.0 * n * d * 0.95, workload   # Y is written whole
+
+
+def test_counter_records_know_their_source(repo_root, tmp_path):
+    """bench.py prints a record's traffic only for the source that was measured: comments do not count, code does, in the
+    kernel's own unit, in the partition's and in the headers they include."""
+    import shutil
+    import bench
+    src = os.path.join(repo_root, "paper_2403_14853_amd", "csrc")
+    for kernel in ("k_spmm_grouped", "k_fused_grouped<g_fwd>"):
+        ref = bench.source_digest(kernel)
+        for name, counts in (("run_stream.h", True), ("csr_build.hip", True), ("partition_sizes.h", True), ("alias.hip", False)):
+            copy = str(tmp_path / ("%s_%s" % (kernel[:8], name)))
+            shutil.copytree(src, copy)
+            path = os.path.join(copy, name)
+            text = open(path).read()
+            open(path, "w").write("// a remark\n" + text + "\n/* another\n   one */\n")
+            assert bench.source_digest(kernel, copy) == ref
+            open(path, "w").write(text + "\nstatic int planted;\n")
+            assert (bench.source_digest(kernel, copy) != ref) == counts
+    assert bench.source_digest("sddmm") is None
+    rec = bench.counter_record("c3-rmat2.4m-d128", "k_spmm_grouped")
+    assert rec["current"] in (True, False)
