@@ -43,11 +43,13 @@
  *                              sizes of the work partition (clamped to what the kernels' tables hold)
  *       ISP_NO_GROUPED         run every operation on the general kernels
  *       ISP_SPMM_LPG, ISP_SPMM_TILE   lanes per group / feature columns per launch of the tuned SpMM
+ *       ISP_STAGE_MIN          entries per column from which SpMM copies the columns of a ragged dense operand to whole
+ *                              lines, whatever its width (0 = never)
  *       ISP_SDDMM_ONE_PASS     SDDMM keeps 128-column rows in one pass
  *       ISP_NO_MIRROR          the FusedMM backward always runs its two passes, also on symmetric patterns
  *       ISP_FUSED_W            4 / 8: the tuned FusedMM kernels give a lane one / two float4 at every width above 32
  *       ISP_WIDE_GROUPS        most 256-column groups a split row stores per launch of a FusedMM pass wider than 256
- *     isp_csr_build_workspace reads the partition sizes too, so set them before both calls or not at all.
+ *     isp_csr_build_workspace reads the partition sizes and ISP_STAGE_MIN too, so set them before both calls or not at all.
  */
 #ifndef ISP_H
 #define ISP_H
@@ -181,7 +183,7 @@ isp_status isp_csr_info(const isp_csr_t* A, isp_csr_info_t* info);
  *   workspace: device memory, 256-byte aligned, isp_csr_alias_workspace bytes, borrowed until the alias is
  *     destroyed; it needs no clearing.  Size: 1 KiB per hub-row segment or row piece (isp_csr_info: n_segments,
  *     spmm_pieces) of A and as much again for its cached transpose, plus one byte per stored entry when the
- *     transpose exists - about 2 GiB for 124 M entries in 2.4 M rows.
+ *     transpose exists, plus 512 bytes per column of A and of the transpose where columns have 32 entries or more - about 2 GiB for 124 M entries in 2.4 M rows.
  *   The alias takes over A's cached transpose as it is at this call: build it on A first if the alias is to
  *     run backward calls (isp_csr_transpose_cached on the alias returns it, or ISP_EINVAL if A had none).
  *   Destroy the alias (isp_csr_destroy) before A.  After isp_csr_values_changed(A) every alias made before is

@@ -13,6 +13,7 @@ namespace {
 struct alias_layout {
   int64_t rows_a, rows_t;   // partial rows for the handle and for its transpose
   size_t off_t, off_flags;  // byte offsets of the transpose's partial rows and of its entry marks
+  size_t off_stage, off_stage_t;  // ... of the copies of ragged operands
   size_t total;
 };
 
@@ -34,6 +35,11 @@ alias_layout make_alias_layout(const isp_csr* A, int32_t max_d) {
   off += isp_align((size_t)L.rows_t * ISP_PARTIAL_TILE * sizeof(float));
   L.off_flags = off;
   if (A->At) off += isp_align((size_t)A->v.nnz + 4);  // (cleared in 32-bit words)
+  auto stage = [&](const isp_csr* h) { return h && h->stage ? isp_align((size_t)h->v.n_cols * ISP_STAGE_COLS * sizeof(float)) : 0; };
+  L.off_stage = off;
+  off += stage(A);
+  L.off_stage_t = off;
+  off += stage(A->At);
   L.total = off;
   return L;
 }
@@ -79,6 +85,7 @@ extern "C" isp_status isp_csr_alias(const isp_csr_t* A, int32_t max_d, void* wor
   B->v.partials = reinterpret_cast<float*>(base);
   B->vp.partials = B->v.partials;  // (a call runs on one of the two partitions, never on both)
   B->partial_rows = L.rows_a;
+  if (A->stage) B->stage = reinterpret_cast<float*>(base + L.off_stage);
   if (A->At) {
     isp_csr* Bt = new (std::nothrow) isp_csr(*A->At);
     if (!Bt) { delete B; return isp_fail(ISP_ENOMEM, "host allocation of the handle failed"); }
@@ -88,6 +95,7 @@ extern "C" isp_status isp_csr_alias(const isp_csr_t* A, int32_t max_d, void* wor
     Bt->v.partials = reinterpret_cast<float*>(base + L.off_t);
     Bt->vp.partials = Bt->v.partials;
     Bt->partial_rows = L.rows_t;
+    if (Bt->stage) Bt->stage = reinterpret_cast<float*>(base + L.off_stage_t);
     // The marks of the min / max backward are written by every call: the alias's own.  What the transpose
     // caches on first use besides (value / row length, the inverse permutation) is a pure function of the
     // shared arrays and stays shared: whichever handle fills it first writes the same numbers any other would.

@@ -44,6 +44,7 @@ isp_tuning isp_read_tuning() {
   t.spmm_lpg = (lpg == 4 || lpg == 8 || lpg == 16 || lpg == 32 || lpg == 64) ? lpg : 0;
   const int tile = env_int("ISP_SPMM_TILE", 0, 0, 256);
   t.spmm_tile = (tile == 64 || tile == 128 || tile == 256) ? tile : 0;
+  t.stage_always = env_int("ISP_STAGE_MIN", -1, -1, 1 << 20) > 0;
   t.wide_groups = env_int("ISP_WIDE_GROUPS", 0, 0, 4);
   t.no_mirror = getenv("ISP_NO_MIRROR") != nullptr;
   const int fw = env_int("ISP_FUSED_W", 0, 0, 8);
@@ -952,12 +953,21 @@ isp_status build_packed(isp_csr* A, const partition_params& p1, int mid_t, char*
 
 }  // namespace
 
+// Room for the copies of ragged operands (spmm.hip: rule and figures).  ISP_STAGE_MIN (entries per column; 0 = no copies)
+// overrides the rule and its limit on the size.
+size_t isp_stage_bytes(int64_t n_cols, int64_t nnz) {
+  const int forced = env_int("ISP_STAGE_MIN", -1, -1, 1 << 20);
+  if (n_cols <= 0 || forced == 0) return 0;
+  if (forced > 0 ? nnz / n_cols < forced : nnz / n_cols < 32 || nnz < 3000000) return 0;
+  return isp_align((size_t)n_cols * ISP_STAGE_COLS * sizeof(float));
+}
+
 size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz) {
   const partition_params p1 = get_params(n_rows, nnz, isp_wave_slots());
-  const ws_layout L = make_layout(n_rows, nnz, p1);
+  const size_t own = make_layout(n_rows, nnz, p1).total + isp_stage_bytes(n_cols, nnz);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, p1);
-  if (mid_t == 0) return L.total;
-  return make_packed_layout(n_rows, nnz, true, p1, mid_t, L.total).total;
+  if (mid_t == 0) return own;
+  return make_packed_layout(n_rows, nnz, true, p1, mid_t, own).total;
 }
 
 isp_status isp_gather_values(const int32_t* pos, const float* values, int64_t nnz, float* out, hipStream_t s) {
@@ -981,9 +991,10 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   const ws_layout L = make_layout(n_rows, nnz, pp);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, pp);
   packed_layout P{};
-  size_t need = L.total;
+  const size_t stage_bytes = isp_stage_bytes(n_cols, nnz);  // (behind the ordinary partition)
+  size_t need = L.total + stage_bytes;
   if (mid_t > 0) {
-    P = make_packed_layout(n_rows, nnz, values != nullptr, pp, mid_t, L.total);
+    P = make_packed_layout(n_rows, nnz, values != nullptr, pp, mid_t, need);
     need = P.total;
   }
   if (ws_bytes < need) return isp_fail(ISP_EINVAL, "workspace too small: %zu < %zu bytes", ws_bytes, need);
@@ -1003,6 +1014,8 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   A->vp = A->v;
   A->partial_rows = L.max_seg + 1;
   A->spmm_rows = po.h.n_seg;
+  A->stages = stage_bytes > 0;
+  A->stage = A->stages ? (float*)(base + L.total) : nullptr;
   A->has_packed = false; A->packed_values_rw = nullptr; A->packed_src_pos = nullptr;
   A->perm = nullptr; A->t_values_rw = nullptr; A->At = nullptr; A->is_transpose = false; A->mirror_aligned = false;
   A->mean_values = nullptr; A->mean_values_packed = nullptr; A->mean_values_valid = false; A->mean_values_used = false;

@@ -52,6 +52,7 @@ struct isp_tuning {
   int spmm_tile;        // ISP_SPMM_TILE: feature columns per launch of the grouped SpMM (0 = chosen by shape)
   bool no_mirror;       // ISP_NO_MIRROR: the FusedMM backward never takes the one-pass form of symmetric patterns
   int fused_w;          // ISP_FUSED_W: 4 / 8 = the grouped FusedMM kernels give a lane one / two float4 at every width above 32 (0 = chosen by width and graph)
+  bool stage_always;    // ISP_STAGE_MIN given: ragged operands are copied whatever the width and the size
   int wide_groups;      // ISP_WIDE_GROUPS: most column groups a hub segment stores per launch of a wide FusedMM pass (0 = as many as fit)
 };
 isp_tuning isp_read_tuning();
@@ -73,6 +74,8 @@ struct isp_csr {
   int packed_block_cost, packed_row_cost;  // of vp's partition (bounds of its blocks: see csr_build.hip)
   float* packed_values_rw;        // vp.values, writable, NULL without values
   const int32_t* packed_src_pos;  // position in v's arrays of every entry of the derived matrix
+  bool stages;                    // SpMM copies the columns of a ragged dense operand to whole lines (isp_stage_bytes > 0)
+  float* stage;                   // scratch for that copy; NULL: the same launches gather from the operand itself
   isp_tuning tune;
   const int32_t* perm;     // transposes only
   float* t_values_rw;      // transposes only: the values array (in the workspace), writable
@@ -132,6 +135,13 @@ isp_status isp_scan_i32_to_i32(const int32_t* in, int32_t* out, int64_t n, void*
 static inline int64_t isp_shared_rows(const isp_csr* A) {
   return A->partial_rows > A->spmm_rows ? A->partial_rows : A->spmm_rows;
 }
+
+// ---- ragged dense operands (spmm.hip) ---------------------------------------------------------
+// Rows of a dense operand that do not start on 128-byte lines make every gathered slice touch one line more than it
+// holds.  Where a column has many entries a SpMM copies the columns of each launch to whole lines first.
+#define ISP_STAGE_COLS 128
+// Bytes of the copy for a matrix of this shape; 0 where it does not pay.
+size_t isp_stage_bytes(int64_t n_cols, int64_t nnz);
 
 // ---- partition (csr_build.hip) ---------------------------------------------------------------
 size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz);

@@ -233,6 +233,46 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
+// The launches that cover d columns: first column (a last tile of fewer than 4 columns starts earlier and computes some
+// columns again: float4 lanes) and width of the one that continues at k0.
+int tile_start(int k0, int d) { return d >= 4 && d - k0 < 4 ? d - 4 : k0; }
+int tile_width(int k_base, int d, int tile, int64_t n_cols) {
+  const int w = d - k_base < tile ? d - k_base : tile;
+  return w > 128 && w <= 224 && n_cols >= 512 << 10 ? 128 : w;
+}
+
+// 32 times the 128-byte lines that those launches touch of a row of X, on average over the offsets its rows start at.
+int64_t tile_lines(const float* X, int64_t ldx, int d, int tile, int64_t n_cols) {
+  const int base = (int)((uintptr_t)X & 127) / 4;  // (in floats; a line holds 32)
+  int step = 32;
+  while (ldx % step != 0) step /= 2;  // rows start at base + multiples of step
+  int64_t sum = 0;
+  for (int k0 = 0, w; k0 < d; k0 += w) {
+    const int k_base = tile_start(k0, d);
+    w = tile_width(k_base, d, tile, n_cols);
+    for (int o = 0; o < 32; o += step) sum += step * (((base + k_base + o) % 32 + w + 31) / 32);
+  }
+  return sum;
+}
+
+// Copy of columns [k0, k0 + w) of X, row by row, to rows of `pitch` floats (w rounded up to whole lines; what lies
+// behind column w is never read).  pitch / 4 lanes per row; the last lane of a row that is no multiple of 4 moves back.
+__global__ void __launch_bounds__(256) k_stage_cols(const float* __restrict__ X, int64_t ldx, int64_t n, int k0, int w,
+                                                    int pitch, float* __restrict__ out) {
+  const int q = threadIdx.x & 31;
+  if (q * 4 >= w) return;
+  const int c = tail_col<4>(q * 4, w);
+  constexpr int R = 4;  // rows in flight per lane
+  const int64_t r0 = (int64_t)blockIdx.x * (8 * R) + (threadIdx.x >> 5);
+  float t[R][4];
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+    if (r0 + 8 * u < n) load_vec<4>(X + (r0 + 8 * u) * ldx + k0 + c, t[u]);
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+    if (r0 + 8 * u < n) store_vec<4>(out + (r0 + 8 * u) * pitch + c, t[u]);
+}
+
 }  // namespace
 
 // The grouped fast path; *done = false (and nothing launched) when the operands do not qualify.
@@ -258,9 +298,9 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
   // follows was measured on graphs of 37 k ... 124 M entries at widths 16 ... 301 (us, best of the shapes tried):
   //  - wide rows of whole lines are covered 128 columns at a time, each launch with the group that fits it, from 2 M
   //    entries up (2.4 M entries, 256 columns: 2 x 95 against 210 in one launch; 115 M entries, 160 columns:
-  //    2509 + 771 against 4310), 256 at a time below (1.2 M entries, 192 columns: 72 against 77) and wherever rows
-  //    start anywhere: there every launch pays for the lines that its edges cut (602 columns: 667 -> 620 on 2.4 M
-  //    entries, 4931 -> 4584 on 16.9 M);
+  //    2509 + 771 against 4310), 256 at a time below (1.2 M entries, 192 columns: 72 against 77) and where rows
+  //    start anywhere and are not copied (below): there every launch pays for the lines that its edges cut (602 columns:
+  //    667 -> 620 on 2.4 M entries, 4931 -> 4584 on 16.9 M);
   //  - in a launch of up to 128 columns the smallest group that covers them wins (groups of 4 lanes, which share an
   //    instruction between 16 entries, only from 1 M entries up: they take longer to set an item up);
   //  - 128 whole-line columns run as two 64-column slices, dealt to alternating XCDs, where the dense operand is far
@@ -275,15 +315,26 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
   //    128-column slices.
   // ISP_SPMM_LPG / ISP_SPMM_TILE (read when the handle was built) override the choices for tuning.
   const bool packed = A->has_packed && (!values_override || values_override_packed);
-  const bool slices = ldx % 32 == 0 && av.n_cols >= (packed ? 512 << 10 : 80 << 10);
   int tile = av.nnz >= 2000000 && ldx % 32 == 0 ? 128 : ISP_PARTIAL_TILE;
+  // The copy of a ragged operand costs one pass over X and a launch per 128 columns, and saves the lines that row ends
+  // cut.  It is taken where a column has 32 entries or more (isp_stage_bytes), the work outweighs the launches (8 Mi
+  // entries, or 2e9 multiply-adds) and the lines a row touches on average fall by 5 % or more.  us per SpMM without / with
+  // it (mean over several X in turn): 233 k columns, 115 M entries: 602 columns 13853 / 11816, 301 7200 / 6140, 50 1404 /
+  // 1241, 20 852 / 726; 2.4 M, 124 M: 301 15246 / 12698, 50 2745 / 2507; 1 M, 40 M: 602 9066 / 8221; 200 k, 6.4 M: 602 1425 /
+  // 1206.  Outside the rule: 1 M, 16 M: 602 4720 / 4870; 50 k, 1.5 M: 602 290 / 330; 10 k, 1 M: 602 154 / 196; 50 k, 6 M: 20
+  // 58 / 61; 100 columns, whose 400 bytes touch four lines anyway: 2349 / 2426 (233 k), 4832 / 5364 (2.4 M).
+  const bool stage = A->stages && d >= 4 &&
+                     (A->tune.stage_always ? ldx % 32 != 0 || !aligned(X, 128)
+                                           : (av.nnz >= ((int64_t)8 << 20) || av.nnz * d >= 2000000000) &&
+                                                 20 * tile_lines(X, ldx, d, tile, av.n_cols) >=
+                                                     21 * tile_lines(nullptr, 32, d, ISP_STAGE_COLS, av.n_cols));
+  if (stage) tile = ISP_STAGE_COLS;
   if (A->tune.spmm_tile) tile = A->tune.spmm_tile;
+  const bool slices = (ldx % 32 == 0 || stage) && av.n_cols >= (packed ? 512 << 10 : 80 << 10);
   isp_status st = ISP_OK;
   for (int k0 = 0, w; k0 < d && st == ISP_OK; k0 += w) {
-    // (a last tile of fewer than 4 columns starts earlier and computes some columns again: float4 lanes)
-    const int k_base = d - k0 < 4 ? d - 4 : k0;
-    w = (d - k_base < tile) ? d - k_base : tile;
-    if (w > 128 && w <= 224 && av.n_cols >= 512 << 10) w = 128;
+    const int k_base = tile_start(k0, d);
+    w = tile_width(k_base, d, tile, av.n_cols);
     int lpg = 32;
     if (w <= 16 && av.nnz >= 1000000) lpg = 4;
     else if (w <= 32) lpg = 8;
@@ -291,12 +342,21 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
     else if (w > 128 && w <= 224) lpg = 64;
     if (A->tune.spmm_lpg) lpg = A->tune.spmm_lpg;
     const int ns = (w + 4 * lpg - 1) / (4 * lpg);
+    const float* Xt = X;  // what this launch gathers from
+    int64_t ldt = ldx;
+    // (a launch whose groups reach beyond w, which only the overrides make, gathers from X)
+    if (stage && A->stage && w <= ISP_STAGE_COLS && (k_base + w == d || ns * 4 * lpg == w)) {
+      ldt = (w + 31) & ~31;
+      k_stage_cols<<<(unsigned)((av.n_cols + 31) / 32), 256, 0, s>>>(X, ldx, av.n_cols, k_base, w, (int)ldt, A->stage);
+      ISP_LAUNCH_CHECK();
+      Xt = A->stage - k_base;
+    }
     switch (lpg) {
-      case 4: st = launch_grouped<4>(A, X, ldx, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
-      case 8: st = launch_grouped<8>(A, X, ldx, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
-      case 16: st = launch_grouped<16>(A, X, ldx, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
-      case 32: st = launch_grouped<32>(A, X, ldx, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
-      default: st = launch_grouped<64>(A, X, ldx, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
+      case 4: st = launch_grouped<4>(A, Xt, ldt, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
+      case 8: st = launch_grouped<8>(A, Xt, ldt, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
+      case 16: st = launch_grouped<16>(A, Xt, ldt, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
+      case 32: st = launch_grouped<32>(A, Xt, ldt, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
+      default: st = launch_grouped<64>(A, Xt, ldt, d, k_base, ns, Y, ldy, mean_mode, values_override, s, values_override_packed); break;
     }
   }
   return st;

@@ -60,5 +60,6 @@ extern "C" isp_status isp_spmm_static_scratch(const isp_csr_t* A, const float* X
   isp_csr view = *A;
   view.v.partials = ptr;
   view.vp.partials = ptr;
+  view.stage = nullptr;  // (ragged operands are gathered from where they are, by the same launches: same results)
   return isp_spmm_launch(&view, X, ldx, d, Y, ldy, (hipStream_t)stream);
 }

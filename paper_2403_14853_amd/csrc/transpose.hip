@@ -422,12 +422,13 @@ t_layout make_layout(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_value
 // Bytes share_handle takes of the transpose's workspace.
 size_t share_bytes(const isp_csr* A) {
   return isp_align((size_t)isp_shared_rows(A) * ISP_PARTIAL_TILE * sizeof(float)) +
+         (A->stages ? isp_align((size_t)A->v.n_cols * ISP_STAGE_COLS * sizeof(float)) : 0) +
          (A->has_packed ? isp_align((size_t)A->v.nnz * sizeof(float)) : 0);
 }
 
 // The transpose's handle when its offsets and indices equal A's: A's partition tables and packed layout, which are
-// only read, serve both; values and partial rows are its own (scratch: share_bytes of workspace, the partial rows of
-// either partition in front and the packed values behind them).
+// only read, serve both; values and scratch are its own (scratch: share_bytes of workspace, the partial rows of
+// either partition in front, the copy of a ragged operand and the packed values behind them).
 isp_status share_handle(const isp_csr* A, const int64_t* t_indptr, const int32_t* t_indices, float* t_values,
                         char* scratch, hipStream_t s, isp_csr** out) {
   isp_csr* At = new (std::nothrow) isp_csr(*A);
@@ -438,8 +439,12 @@ isp_status share_handle(const isp_csr* A, const int64_t* t_indptr, const int32_t
   At->v.values = t_values;
   At->v.partials = (float*)scratch;
   At->partial_rows = isp_shared_rows(A);
+  scratch += isp_align((size_t)At->partial_rows * ISP_PARTIAL_TILE * sizeof(float));
+  if (A->stages) {
+    At->stage = (float*)scratch;
+    scratch += isp_align((size_t)A->v.n_cols * ISP_STAGE_COLS * sizeof(float));
+  }
   if (A->has_packed) {
-    scratch += isp_align((size_t)At->partial_rows * ISP_PARTIAL_TILE * sizeof(float));
     At->packed_values_rw = t_values ? (float*)scratch : nullptr;
     At->vp.values = At->packed_values_rw;
     At->vp.partials = At->v.partials;

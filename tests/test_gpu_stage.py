@@ -1,0 +1,102 @@
+"""Ragged dense operands of SpMM copied to whole lines (rows that start between 128-byte lines, many entries per column):
+forced onto small graphs, at widths around the copies' tiles, at pitches and base addresses of every alignment, against the
+oracle; bit-identical through an alias and the static-scratch entry point, also where those gather from the operand itself."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import graphgen
+import oracle
+import paper_2403_14853_amd as isp
+from gpu_util import assert_close, build
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def graph():
+    os.environ["ISP_STAGE_MIN"] = "1"
+    try:
+        w = graphgen.make_config(1, shrink=64)
+        A = build(w.indptr, w.indices, w.values)
+        At, _ = isp.csr_transpose_cached(A)
+    finally:
+        os.environ.pop("ISP_STAGE_MIN")
+    yield w, A, At, oracle.transpose(w.n, w.n, w.indptr, w.indices, w.values)
+    A.destroy()
+
+
+def _operand(rng, n, d, ld, shift):
+    """(n, d) view with rows ld apart that starts `shift` floats behind a line; NaN everywhere else."""
+    buf = torch.full((n * ld + shift + 32,), float("nan"), device="cuda")
+    V = buf[shift:shift + n * ld].view(n, ld)[:, :d]
+    Xh = rng.standard_normal((n, d)).astype(np.float32)
+    V.copy_(torch.from_numpy(Xh))
+    return V, Xh
+
+
+# widths: below / at / above one copied tile, a last tile narrower than a float4 lane, several tiles; pitches: the width
+# itself, padded, whole lines (with a shifted base)
+@pytest.mark.parametrize("d,ld,shift", [(4, 4, 0), (5, 5, 1), (31, 31, 0), (33, 40, 0), (64, 64, 3), (127, 127, 0), (128, 128, 1),
+                                        (129, 129, 0), (131, 132, 2), (200, 200, 0), (259, 301, 5), (602, 602, 0)])
+def test_against_the_oracle(graph, d, ld, shift):
+    w, A, At, (ti, tj, _, tv) = graph
+    print("[case] staged", d, ld, shift, flush=True)
+    rng = np.random.default_rng(d)
+    X, Xh = _operand(rng, w.n, d, ld, shift)
+    Y = torch.full((w.n, d), float("nan"), device="cuda")
+    isp.spmm(A, X, Y)
+    assert_close(Y, *oracle.spmm(w.indptr, w.indices, w.values, Xh), "staged spmm")
+    again = torch.empty_like(Y)
+    isp.spmm_static_scratch(A, X, again)  # (the same launches without the copies)
+    assert torch.equal(Y, again)
+    B = isp.csr_alias(A, max_d=d)
+    isp.spmm(B, X, again)
+    assert torch.equal(Y, again)
+    isp.spmm(At, X, Y)
+    assert_close(Y, *oracle.spmm(ti, tj, tv, Xh), "staged spmm on the transpose")
+    isp.spmm(isp.csr_transpose_cached(B)[0], X, again)
+    assert torch.equal(Y, again)
+    B.destroy()
+
+
+def test_non_finite_rows_stay_where_they_are(graph):
+    w, A, _, _ = graph
+    print("[case] staged, one infinite row", flush=True)
+    X = torch.ones(w.n, 50, device="cuda")
+    j = int(w.indices[0])
+    X[j] = float("inf")
+    Y = torch.empty_like(X)
+    isp.spmm(A, X, Y)
+    rows = np.repeat(np.arange(w.n), np.diff(w.indptr))
+    hit = np.zeros(w.n, dtype=bool)
+    hit[rows[w.indices == j]] = True
+    assert np.array_equal(~np.isfinite(Y.cpu().numpy()).all(1), hit)
+
+
+def test_large_enough_by_itself():
+    """The rule's own choice: 8 Mi entries, 32 and more per column, at a width whose rows cut a line more than they fill;
+    forward and backward (a symmetric pattern of this size shares its partitions with the transpose)."""
+    print("[case] staged by rule", flush=True)
+    n, d, deg = 70_001, 20, 126
+    rng = np.random.default_rng(0)
+    half = rng.integers(1, n, (deg // 2,))
+    off = np.unique(np.concatenate([half, n - half]))  # a circulant pattern: symmetric, distinct columns
+    cols = np.sort((np.arange(n)[:, None] + off[None, :]) % n, axis=1).astype(np.int32)
+    indptr = (np.arange(n + 1, dtype=np.int64) * off.size)
+    vals = rng.standard_normal(n * off.size).astype(np.float32)
+    assert indptr[-1] >= 8 << 20
+    A = build(indptr, cols.reshape(-1), vals)
+    At, _ = isp.csr_transpose_cached(A)
+    assert A.info()["symmetric_pattern"] == 1
+    Xh = rng.standard_normal((n, d)).astype(np.float32)
+    X = torch.from_numpy(Xh).cuda()
+    Y = torch.empty_like(X)
+    isp.spmm(A, X, Y)
+    assert_close(Y, *oracle.spmm(indptr, cols.reshape(-1), vals, Xh), "staged by rule")
+    ti, tj, _, tv = oracle.transpose(n, n, indptr, cols.reshape(-1), vals)
+    isp.spmm(At, X, Y)
+    assert_close(Y, *oracle.spmm(ti, tj, tv, Xh), "staged by rule, transpose")
+    A.destroy()
