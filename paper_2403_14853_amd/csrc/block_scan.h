@@ -6,6 +6,13 @@ namespace isp_dev {
 
 constexpr int BS_THREADS = 256;
 
+// Orders this wave's earlier LDS writes before its later LDS reads (other lanes' data).  The LDS
+// unit executes one wave's operations in order, so only the compiler has to be held back.
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 template <typename T>
 __device__ inline T wave_inclusive_scan(T v, int lane) {
 #pragma unroll

@@ -30,6 +30,7 @@ struct build_counters {
 };
 
 constexpr int CUT_COUNT = 16;  // wavefronts' worth of entries that cutting a hub row looks at first
+constexpr int CUT_LAST = 8;    // candidates of a cut that are looked at together
 
 // Matrices up to this size have everything about their partition enqueued in one go (see build_partition).
 constexpr int64_t SMALL_NNZ = 4 << 20;
@@ -71,69 +72,72 @@ int isp_wave_slots() {
 
 namespace {
 
-// (and passes a flag that earlier launches left on the device on to the host, if there is one)
-__global__ void k_zero_counters(build_counters* c, const int* flag, int* host_flag) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    *c = build_counters{};
-    if (host_flag) *host_flag = *flag;
-  }
-}
-
 // Pieces of a hub row: its entries [a, b) cut where the columns cross band boundaries.  A row of degree
 // deg is cut into br = the largest power of two <= min(bands, deg / min_piece) coarse bands, each made of
 // bands / br fine bands of width ceil(n_cols / bands).  The whole wavefront calls this with the same row
 // (a, b wave-uniform): lane j < br gets piece j as [*first, *last), the other lanes an empty piece.  Every
-// lane finds one cut position by counting and searching, which assumes ascending columns; on a row that is not sorted the positions are made monotone, so they are still valid cuts (inside the row, in order) and only
+// lane finds one cut position by searching, which assumes ascending columns; on a row that is not sorted the positions are made monotone, so they are still valid cuts (inside the row, in order) and only
 // the scheduling benefit is lost, never correctness.
 __device__ inline void wave_hub_pieces(const int32_t* __restrict__ indices, int64_t a, int64_t b, int64_t n_cols,
-                                       const partition_params& pp, int lane, int64_t* first, int64_t* last) {
-  const int64_t deg = b - a;
+                                       const partition_params& pp, int lane, int* samples, int64_t* first, int64_t* last) {
+  // (positions and columns fit 32 bits; relative to the row from here on)
+  const int deg = (int)(b - a);
+  const int32_t* __restrict__ row = indices + a;
   const int br = hub_bands(deg, pp);
-  const int64_t bw = (n_cols + pp.bands - 1) / pp.bands;
+  const unsigned bw = ((unsigned)n_cols + pp.bands - 1u) / (unsigned)pp.bands;
   const int step = pp.bands / br;
-  // cut j = number of the row's columns below j * step * bw; cut 0 = a, cuts >= br = b
-  const int64_t target = (int64_t)lane * step * bw;
-  int64_t lo = a, hi = b;
-  if (lane == 0) hi = a;
-  if (lane >= br) lo = b;
-  {
-    // CUT_COUNT * 64 evenly spaced entries (a short row whole) in one trip to memory, counted with ballots, leave each
-    // cut a range of `gap` entries; a binary search from the start would be a chain of a dozen trips.
-    const int64_t gap = (deg + CUT_COUNT * ISP_WAVE - 1) / (CUT_COUNT * ISP_WAVE);
+  // cut j = number of the row's columns below j * step * bw; cut 0 = 0, cuts >= br = deg
+  const unsigned target = (unsigned)lane * step * bw;  // (below 2^31 + bands for the lanes that search)
+  int lo = lane >= br ? deg : 0;
+  if (br > 1) {
+    // CUT_COUNT * 64 evenly spaced entries (a short row whole) in one trip to memory, searched in LDS, leave each cut a
+    // range of `gap` entries; a binary search from the start would be a chain of a dozen trips, counting the samples
+    // below each cut with ballots some 2,000 instructions per row (with that, 64-bit positions and 64-bit sums, the two
+    // passes that cut rows took 23.6 and 15.7 us on 1 M entries, now 15 and 10).
+    const int gap = (int)(((unsigned)deg + CUT_COUNT * ISP_WAVE - 1u) / (CUT_COUNT * ISP_WAVE));
+    const int ns = (int)((unsigned)(deg + gap - 1) / (unsigned)gap);
     int c[CUT_COUNT];
 #pragma unroll
     for (int k = 0; k < CUT_COUNT; ++k) {
-      const int64_t o = (int64_t)(k * ISP_WAVE + lane) * gap;
-      c[k] = o < deg ? indices[a + o] : INT_MAX;
+      const int i = k * ISP_WAVE + lane;
+      c[k] = i < ns ? row[i * gap] : 0;
     }
-    for (int j = 1; j < br; ++j) {
-      const int64_t t64 = (int64_t)j * step * bw;
-      const int tj = t64 < INT_MAX ? (int)t64 : INT_MAX;
-      int64_t n = 0;  // samples below the cut
+    wave_lds_sync();  // (the row before this one has been searched)
 #pragma unroll
-      for (int k = 0; k < CUT_COUNT; ++k) n += __popcll(__ballot(c[k] < tj));
-      if (lane == j) {
-        lo = a + (n > 0 ? (n - 1) * gap + 1 : 0);
-        hi = a + n * gap < b ? a + n * gap : b;
+    for (int k = 0; k < CUT_COUNT; ++k) samples[k * ISP_WAVE + lane] = c[k];
+    wave_lds_sync();
+    const bool mine = lane > 0 && lane < br;
+    int n = 0;  // samples below the cut
+    for (int st = 1 << (31 - __clz(ns)); st > 0; st >>= 1)
+      if (mine && n + st <= ns && (unsigned)samples[n + st - 1] < target) n += st;
+    int hi = lo;
+    if (mine) {
+      lo = n > 0 ? (n - 1) * gap + 1 : 0;
+      hi = n < ns ? n * gap : deg;
+    }
+    while (__any(hi - lo > CUT_LAST)) {
+      if (hi - lo > CUT_LAST) {
+        const int mid = (int)(((unsigned)lo + (unsigned)hi) >> 1);
+        if ((unsigned)row[mid] < target) lo = mid + 1; else hi = mid;
       }
     }
-    while (__any(lo < hi)) {
-      if (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)indices[mid] < target) lo = mid + 1; else hi = mid;
-      }
+    if (__any(lo < hi)) {  // the last few candidates in one trip
+      int below = 0;
+#pragma unroll
+      for (int k = 0; k < CUT_LAST; ++k) below += lo + k < hi && (unsigned)row[lo + k] < target;
+      lo += below;
     }
   }
-  int64_t cut = lo;
+  int cut = lo;
 #pragma unroll
   for (int o = 1; o < ISP_WAVE; o <<= 1) {  // running maximum over the lanes: monotone cuts
-    const int64_t t = __shfl_up(cut, o);
+    const int t = __shfl_up(cut, o);
     if (lane >= o && t > cut) cut = t;
   }
-  int64_t next = __shfl_down(cut, 1);
-  if (lane == ISP_WAVE - 1) next = b;  // (the last lane has no neighbour; it holds a piece only with 64 bands)
-  *first = lane < br ? cut : b;
-  *last = lane < br ? next : b;
+  int next = __shfl_down(cut, 1);
+  if (lane == ISP_WAVE - 1) next = deg;  // (the last lane has no neighbour; it holds a piece only with 64 bands)
+  *first = lane < br ? a + cut : b;
+  *last = lane < br ? a + next : b;
 }
 
 __device__ inline int degree_bin(long long deg, int hub_t) {
@@ -160,6 +164,7 @@ struct row_tiles {
   int64_t* cost;   // sums per tile
   int32_t *hub, *seg, *mark;
   unsigned long long* stats;  // [STATS][MAX_TILES]
+  int32_t* err;    // build_counters::err of every workgroup of pass 1, MAX_TILES at most
 };
 
 // Rows per wavefront: the workgroup's wavefronts turn to its hub rows one after the other, a few trips to memory each, so
@@ -173,33 +178,40 @@ __global__ void __launch_bounds__(BS_THREADS) k_row_pass(const int64_t* __restri
                                                   const int32_t* __restrict__ indices, int64_t n_rows, int64_t n_cols,
                                                   int64_t nnz, partition_params pp, bool check, row_tiles T,
                                                   int32_t* __restrict__ cost, int32_t* __restrict__ hubflag,
-                                                  int32_t* __restrict__ nseg, float* __restrict__ inv_len,
-                                                  build_counters* __restrict__ ctr) {
+                                                  int32_t* __restrict__ nseg, float* __restrict__ inv_len) {
   __shared__ unsigned long long s_stat[BS_THREADS / ISP_WAVE][STATS];
   __shared__ unsigned long long s_cost[BS_THREADS / ISP_WAVE];
   __shared__ int s_seg[BS_THREADS / ISP_WAVE], s_hub[BS_THREADS / ISP_WAVE], s_hubs[BS_THREADS / ISP_WAVE];
   __shared__ int64_t s_ha[BS_THREADS], s_hb[BS_THREADS];  // the step's hub rows, [a, b), and their segments
   __shared__ int s_ns[BS_THREADS];
-  const int lane = threadIdx.x & (ISP_WAVE - 1);
+  __shared__ int s_samples[BS_THREADS / ISP_WAVE][CUT_COUNT * ISP_WAVE];
+  __shared__ int s_err[BS_THREADS / ISP_WAVE];
+  const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x / ISP_WAVE;
+  int my_err = 0;
   if (check) {
     bool bad = false;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += (int64_t)gridDim.x * blockDim.x) {
       const int32_t c = indices[p];
       bad |= (c < 0 || c >= n_cols);
     }
-    if (__any(bad) && lane == 0) atomicOr(&ctr->err, 2);
+    my_err = bad ? 2 : 0;
   }
-  if ((int)blockIdx.x >= T.n) return;
-  unsigned long long my_rows[5] = {0, 0, 0, 0, 0}, my_nnz[5] = {0, 0, 0, 0, 0}, my_max = 0, my_cost = 0;
-  int my_err = 0, my_seg = 0, my_hub = 0;
+  auto report = [&]() {  // what this workgroup found wrong
+    const int e = (__any(my_err & 1) ? 1 : 0) | (__any(my_err & 2) ? 2 : 0);
+    if (lane == 0) s_err[w] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) T.err[blockIdx.x] = s_err[0] | s_err[1] | s_err[2] | s_err[3];
+  };
+  if ((int)blockIdx.x >= T.n) { report(); return; }
+  unsigned my_rows[5] = {0, 0, 0, 0, 0}, my_nnz[5] = {0, 0, 0, 0, 0}, my_max = 0, my_cost = 0;  // (a tile's cost: nnz + two units per row, below 2^32)
+  int my_seg = 0, my_hub = 0;
   const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
-  const int w = threadIdx.x / ISP_WAVE;
   for (int64_t base = r0; base < r1; base += (BS_THREADS / ISP_WAVE) * RPW) {  // (the workgroup stays together)
     const int64_t i = base + w * RPW + lane;
     const bool valid = lane < RPW && i < r1;
     const int64_t a = valid ? indptr[i] : 0, b = valid ? indptr[i + 1] : 0;
     long long deg = b - a;
-    if (valid && (deg < 0 || a < 0 || b > nnz || (i == 0 && a != 0) || (i == n_rows - 1 && b != nnz))) { my_err = 1; deg = 0; }
+    if (valid && (deg < 0 || a < 0 || b > nnz || (i == 0 && a != 0) || (i == n_rows - 1 && b != nnz))) { my_err |= 1; deg = 0; }
     const bool hub = deg > pp.hub_t;
     // the step's hub rows, shared out over the wavefronts
     const unsigned long long hm = __ballot(hub);
@@ -213,8 +225,8 @@ __global__ void __launch_bounds__(BS_THREADS) k_row_pass(const int64_t* __restri
     __syncthreads();
     for (int h = w; h < n_hubs; h += BS_THREADS / ISP_WAVE) {
       int64_t first, last;
-      wave_hub_pieces(indices, s_ha[h], s_hb[h], n_cols, pp, lane, &first, &last);
-      int cnt = (int)((last - first + pp.seg_len - 1) / pp.seg_len);
+      wave_hub_pieces(indices, s_ha[h], s_hb[h], n_cols, pp, lane, s_samples[w], &first, &last);
+      int cnt = (int)((unsigned)(last - first + pp.seg_len - 1) / (unsigned)pp.seg_len);
 #pragma unroll
       for (int o = 1; o < ISP_WAVE; o <<= 1) cnt += __shfl_xor(cnt, o);
       if (lane == 0) s_ns[h] = cnt;
@@ -231,33 +243,32 @@ __global__ void __launch_bounds__(BS_THREADS) k_row_pass(const int64_t* __restri
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
       my_rows[k] += (bin == k);
-      my_nnz[k] += (bin == k) ? (unsigned long long)deg : 0ull;
+      my_nnz[k] += (bin == k) ? (unsigned)deg : 0u;
     }
-    my_max = (unsigned long long)deg > my_max ? (unsigned long long)deg : my_max;
+    my_max = (unsigned)deg > my_max ? (unsigned)deg : my_max;
     my_seg += ns;
     my_hub += hub;
     my_cost += c;
   }
-  if (__any(my_err) && lane == 0) atomicOr(&ctr->err, 1);
-  auto wave_sum = [](unsigned long long v) {
+  auto wave_sum = [](unsigned v) {
 #pragma unroll
     for (int o = 1; o < ISP_WAVE; o <<= 1) v += __shfl_xor(v, o);
     return v;
   };
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
-    const unsigned long long a = wave_sum(my_rows[k]), b = wave_sum(my_nnz[k]);
+    const unsigned a = wave_sum(my_rows[k]), b = wave_sum(my_nnz[k]);
     if (lane == 0) { s_stat[w][k] = a; s_stat[w][5 + k] = b; }
   }
 #pragma unroll
   for (int o = 1; o < ISP_WAVE; o <<= 1) {
-    const unsigned long long u = __shfl_xor(my_max, o);
+    const unsigned u = __shfl_xor(my_max, o);
     my_max = u > my_max ? u : my_max;
   }
-  const unsigned long long cost_sum = wave_sum(my_cost);
+  const unsigned cost_sum = wave_sum(my_cost);
   const int seg_sum = (int)wave_sum((unsigned)my_seg), hub_sum = (int)wave_sum((unsigned)my_hub);
   if (lane == 0) { s_stat[w][10] = my_max; s_cost[w] = cost_sum; s_seg[w] = seg_sum; s_hub[w] = hub_sum; }
-  __syncthreads();
+  report();  // (a barrier)
   if (threadIdx.x < STATS) {
     const int k = threadIdx.x;
     unsigned long long v = s_stat[0][k];
@@ -279,11 +290,21 @@ __global__ void __launch_bounds__(BS_THREADS) k_row_pass(const int64_t* __restri
 // layout keeps blocks of whole rows and blocks of row pieces apart that way).
 __global__ void __launch_bounds__(BS_THREADS) k_mark_rows(const int32_t* __restrict__ cost,
                                                           const int32_t* __restrict__ hubflag, int64_t n_rows,
-                                                          int block_cost, int64_t force_row, row_tiles T,
-                                                          int32_t* __restrict__ mark, build_counters* __restrict__ ctr) {
-  if ((int)blockIdx.x == T.n) {  // one workgroup more than tiles: what the counters tell the caller
+                                                          int block_cost, int64_t force_row, row_tiles T, int n_err,
+                                                          int32_t* __restrict__ mark, build_counters* __restrict__ ctr,
+                                                          const int* __restrict__ flag, int* __restrict__ host_flag) {
+  // One workgroup more than tiles: what the counters tell the caller (pass 3 adds the counts), and a flag that earlier
+  // launches left on the device, if there is one, for the host.
+  if ((int)blockIdx.x == T.n) {
     __shared__ unsigned long long part[BS_THREADS / ISP_WAVE][STATS];
     const int lane = threadIdx.x & (ISP_WAVE - 1);
+    int err = 0;
+    for (int i = threadIdx.x; i < n_err; i += BS_THREADS) err |= T.err[i];
+    const int err1 = __syncthreads_or(err & 1), err2 = __syncthreads_or(err & 2);
+    if (threadIdx.x == 0) {
+      ctr->err = (err1 ? 1 : 0) | (err2 ? 2 : 0);
+      if (host_flag) *host_flag = *flag;
+    }
     unsigned long long v[STATS] = {};
 #pragma unroll 2
     for (int t = threadIdx.x; t < T.n; t += BS_THREADS) {
@@ -348,6 +369,7 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
   const int lane = threadIdx.x & (ISP_WAVE - 1);
   __shared__ int64_t s_ha[BS_THREADS], s_hb[BS_THREADS];
   __shared__ int s_hs[BS_THREADS];
+  __shared__ int s_samples[BS_THREADS / ISP_WAVE][CUT_COUNT * ISP_WAVE];
   int mpos0, hpos0, seg0;
   {
     unsigned long long mh = 0;  // marks and hub rows of the earlier tiles, 32 bits each
@@ -389,9 +411,9 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
     for (int hq = threadIdx.x / ISP_WAVE; hq < n_hubs; hq += BS_THREADS / ISP_WAVE) {
       const int hh = hh0 + hq, hs0 = s_hs[hq];
       int64_t first, last;
-      wave_hub_pieces(indices, s_ha[hq], s_hb[hq], n_cols, pp, lane, &first, &last);
+      wave_hub_pieces(indices, s_ha[hq], s_hb[hq], n_cols, pp, lane, s_samples[threadIdx.x / ISP_WAVE], &first, &last);
       // the row's segments, in order of position: piece by piece (lane by lane), each piece in runs of seg_len
-      const int cnt = (int)((last - first + pp.seg_len - 1) / pp.seg_len);
+      const int cnt = (int)((unsigned)(last - first + pp.seg_len - 1) / (unsigned)pp.seg_len);
       int inc = cnt;
 #pragma unroll
       for (int o = 1; o < ISP_WAVE; o <<= 1) {
@@ -417,49 +439,53 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
 }
 
 // Up to SO_SMALL segments: schedule order in one launch, every segment counting those before it (by first column, then
-// number).  SO_SMALL^2 comparisons are 1.5 us of the chip's vector ALUs; the radix sort below is five launches per
-// digit (a matrix of 1 M entries has about 5,000 segments: 100 us), a bitonic sort in one workgroup took 88 us.
+// number).  SO_SMALL^2 comparisons are 1.5 us of the chip's vector ALUs if all of it works on them, hence few segments per
+// workgroup (5,000 segments: 11.4 us at 64, which left most of the chip idle, 7.4 at 16); the radix sort below is five
+// launches per digit (a matrix of 1 M entries has about 5,000 segments: 100 us), a bitonic sort in one workgroup took 88 us.
 constexpr int SO_SMALL = 8192;
-constexpr int SO_WAVES = 16;  // wavefronts that share a segment's comparisons
-__global__ void __launch_bounds__(SO_WAVES * ISP_WAVE) k_seg_rank(const int32_t* __restrict__ key,
-                                                                  const build_counters* __restrict__ ctr,
-                                                                  int32_t* __restrict__ order) {
+constexpr int SO_SEGS = 16;     // segments per workgroup, one per lane of 16
+constexpr int SO_THREADS = 1024;
+__global__ void __launch_bounds__(SO_THREADS) k_seg_rank(const int32_t* __restrict__ key,
+                                                         const build_counters* __restrict__ ctr, int32_t* __restrict__ order) {
+  constexpr int PER = SO_SMALL / SO_THREADS, WAVES = SO_THREADS / ISP_WAVE, SHARES = SO_THREADS / SO_SEGS;
   __shared__ __align__(16) int keys[SO_SMALL];
-  __shared__ int part[SO_WAVES][ISP_WAVE];
+  __shared__ int part[WAVES][SO_SEGS];
   const int n = ctr->n_seg;
   if (ctr->err || n > SO_SMALL) return;  // (a malformed matrix has no bounds to rely on)
-  if ((int)blockIdx.x * ISP_WAVE >= n) return;
-  const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x / ISP_WAVE;
-  const int n4 = (n + 3) & ~3;
-  for (int j = threadIdx.x; j < n4; j += SO_WAVES * ISP_WAVE) keys[j] = j < n ? key[j] : INT_MAX;
-  __syncthreads();
-  const int s = blockIdx.x * ISP_WAVE + lane;
-  const int k = s < n ? keys[s] : 0;
-  const int q = (n4 / 4 + SO_WAVES - 1) / SO_WAVES, j1 = (w + 1) * q < n4 / 4 ? (w + 1) * q : n4 / 4;
-  int rank = 0;
-  // keys of lower-numbered segments count when equal, higher-numbered ones only when smaller (columns are below
-  // 2^31 - 1): two loops around the 64 segments of this workgroup itself
-  const int4* __restrict__ k4 = reinterpret_cast<const int4*>(keys);
-  const int d0 = blockIdx.x * (ISP_WAVE / 4), d1 = d0 + ISP_WAVE / 4;
-  const int e1 = j1 < d0 ? j1 : d0, b2 = w * q > d1 ? w * q : d1;
-#pragma unroll 4
-  for (int j = w * q; j < e1; ++j) {
-    const int4 kj = k4[j];
-    rank += (kj.x <= k) + (kj.y <= k) + (kj.z <= k) + (kj.w <= k);
-  }
-#pragma unroll 4
-  for (int j = b2; j < j1; ++j) {
-    const int4 kj = k4[j];
-    rank += (kj.x < k) + (kj.y < k) + (kj.z < k) + (kj.w < k);
-  }
-  if (w == 0) {
-    for (int j = 4 * d0; j < 4 * d1 && j < n; ++j) rank += keys[j] < k + (j < s ? 1 : 0);
-  }
-  part[w][lane] = rank;
-  __syncthreads();
-  if (w == 0 && s < n) {
+  if ((int)blockIdx.x * SO_SEGS >= n) return;
+  int kk[PER];  // (all of them on their way together)
 #pragma unroll
-    for (int ww = 1; ww < SO_WAVES; ++ww) rank += part[ww][lane];
+  for (int u = 0; u < PER; ++u) {
+    const int j = u * SO_THREADS + threadIdx.x;
+    kk[u] = j < n ? key[j] : INT_MAX;
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) keys[u * SO_THREADS + threadIdx.x] = kk[u];
+  __syncthreads();
+  const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x / ISP_WAVE;
+  const int s = blockIdx.x * SO_SEGS + (threadIdx.x & (SO_SEGS - 1));
+  const int k = s < n ? keys[s] : 0;
+  // Share h of a segment's comparisons: every SHARES-th four keys.  Keys of lower-numbered segments count when equal,
+  // others only when smaller (columns are below 2^31 - 1); the four around the segment itself are put right at the end.
+  const int4* __restrict__ k4 = reinterpret_cast<const int4*>(keys);
+  const int n4 = (n + 3) / 4, own = s / 4;
+  int rank = 0;
+#pragma unroll 4
+  for (int j = threadIdx.x / SO_SEGS; j < n4; j += SHARES) {
+    const int4 kj = k4[j];
+    const int t = k + (j < own ? 1 : 0);
+    rank += (kj.x < t) + (kj.y < t) + (kj.z < t) + (kj.w < t);
+  }
+  if (threadIdx.x < SO_SEGS)
+    for (int j = own * 4; j < s; ++j) rank += keys[j] == k;
+#pragma unroll
+  for (int o = SO_SEGS; o < ISP_WAVE; o <<= 1) rank += __shfl_xor(rank, o);
+  if (lane < SO_SEGS) part[w][lane] = rank;
+  __syncthreads();
+  if (threadIdx.x < SO_SEGS && s < n) {
+    rank = 0;
+#pragma unroll
+    for (int ww = 0; ww < WAVES; ++ww) rank += part[ww][threadIdx.x];
     order[rank] = s;
   }
 }
@@ -648,7 +674,7 @@ static_assert(sizeof(build_counters) <= host_slot::SIZE, "the counters fit a slo
 
 // ---- workspace layout ------------------------------------------------------------------------------------
 struct ws_layout {
-  size_t counters, cost, hubflag, nseg, mark, tile_cost, tile_hub, tile_seg, tile_mark, tile_stat;
+  size_t counters, cost, hubflag, nseg, mark, tile_cost, tile_hub, tile_seg, tile_mark, tile_stat, tile_err;
   size_t blk_row, hub_rows, hub_seg_ptr, seg_hub, seg_begin, seg_key[2], seg_order[2], so_table, so_scanned, so_tmp;
   size_t inv_len, item_desc, partials, total;
   int64_t max_blocks, max_hub, max_seg;
@@ -676,6 +702,7 @@ ws_layout make_layout(int64_t n_rows, int64_t nnz, const partition_params& pp, s
   L.tile_seg = take((size_t)MAX_TILES * 4);
   L.tile_mark = take((size_t)MAX_TILES * 4);
   L.tile_stat = take((size_t)MAX_TILES * STATS * 8);
+  L.tile_err = take((size_t)MAX_TILES * 4);
   L.blk_row = take((size_t)(max_blocks + 1) * 4);
   L.hub_rows = take((size_t)(max_hub + 1) * 4);
   L.hub_seg_ptr = take((size_t)(max_hub + 2) * 4);
@@ -789,8 +816,7 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   T.seg = (int32_t*)(base + L.tile_seg);
   T.mark = (int32_t*)(base + L.tile_mark);
   T.stats = (unsigned long long*)(base + L.tile_stat);
-  k_zero_counters<<<1, 64, 0, s>>>(ctr, flag, host_flag);
-  ISP_LAUNCH_CHECK();
+  T.err = (int32_t*)(base + L.tile_err);
   int grid1 = T.n;
   if (validate && nnz > 0) {
     const int64_t want = (nnz + 4095) / 4096;
@@ -798,11 +824,11 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   }
 #define ISP_GO(R)                                                                                                      \
   k_row_pass<R><<<grid1, BS_THREADS, 0, s>>>(indptr, indices, n_rows, n_cols, nnz, pp, validate, T, cost, hubflag, nseg, \
-                                             (float*)(base + L.inv_len), ctr)
+                                             (float*)(base + L.inv_len))
   if (spread) ISP_GO(RPW_SMALL); else ISP_GO(RPW_LARGE);
 #undef ISP_GO
   ISP_LAUNCH_CHECK();
-  k_mark_rows<<<T.n + 1, BS_THREADS, 0, s>>>(cost, hubflag, n_rows, pp.block_cost, force_row, T, mark, ctr);
+  k_mark_rows<<<T.n + 1, BS_THREADS, 0, s>>>(cost, hubflag, n_rows, pp.block_cost, force_row, T, grid1, mark, ctr, flag, host_flag);
   ISP_LAUNCH_CHECK();
 #define ISP_GO(R)                                                                                                     \
   k_compact<R><<<T.n, BS_THREADS, 0, s>>>(indptr, indices, n_cols, pp, T, mark, hubflag, nseg, n_rows, blk_row, hub_rows, \
@@ -821,7 +847,7 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   host_slot slot;  // pinned: the device writes the counters there itself
   build_counters* host_ctr = small ? (build_counters*)slot.get() : nullptr;
   if (small) {
-    k_seg_rank<<<SO_SMALL / ISP_WAVE, SO_WAVES * ISP_WAVE, 0, s>>>(seg_key[0], ctr, seg_ord[0]);
+    k_seg_rank<<<SO_SMALL / SO_SEGS, SO_THREADS, 0, s>>>(seg_key[0], ctr, seg_ord[0]);
     ISP_LAUNCH_CHECK();
     k_item_desc<<<(unsigned)((max_items + 255) / 256), 256, 0, s>>>(indptr, blk_row, 0, hub_rows, hub_seg_ptr, seg_hub,
                                                                   seg_begin, seg_ord[0], 0, pp.hub_t, ctr, max_items,

@@ -1,6 +1,7 @@
 // Lane groups (gfx950, wave64): what the run-streaming kernels (run_stream.h) share.  A group of LPG consecutive lanes
 // spans one dense row slice; G = 64 / LPG groups of a wavefront work on G stored entries at a time.
 #pragma once
+#include "block_scan.h"
 #include "row_stream.h"
 
 namespace isp_dev {
@@ -10,13 +11,6 @@ constexpr int GS_MAX_ENT = 768;    // nonzeros per item:  block_cost - 1 + hub_t
 constexpr int GS_MAX_ROWS = 256;   // rows per item: block_cost
 
 typedef unsigned short gs_u16;
-
-// Orders this wave's earlier LDS writes before its later LDS reads (other lanes' data).  The LDS
-// unit executes one wave's operations in order, so only the compiler has to be held back.
-__device__ inline void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 // Sum over the LPG consecutive lanes of a group, result in every lane of the group.  Lane
 // exchanges inside 16 lanes are DPP modifiers (no LDS traffic); xor 16 is a ds_swizzle, xor 32 a

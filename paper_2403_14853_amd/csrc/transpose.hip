@@ -32,10 +32,17 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_hist(const int32_t* __rest
                                                            int32_t* __restrict__ tile_row, int* __restrict__ flag) {
   __shared__ int hist[1 << RS_MAX_BITS];
   constexpr int RS_TILE = rs_tile(ROUNDS);
+  constexpr int STRIDE = !FIRST && ROUNDS == RS_ROUNDS_SMALL ? 4 : 1;  // (keys in records)
   const int radix = 1 << bits;
   for (int i = threadIdx.x; i < radix; i += RS_THREADS) hist[i] = 0;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * RS_TILE;
+  int key[ROUNDS];  // (on their way while the row is searched for)
+#pragma unroll
+  for (int k = 0; k < ROUNDS; ++k) {
+    const int64_t q = base + k * RS_THREADS + threadIdx.x;
+    key[k] = q < n ? keys[q * STRIDE] : -1;
+  }
   if (FIRST) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
     int64_t lo = 0, hi = n_rows - 1;  // base < nnz = indptr[n_rows], so the answer exists
@@ -48,10 +55,9 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_hist(const int32_t* __rest
     }
     if (threadIdx.x == 0) tile_row[blockIdx.x] = (int32_t)lo;
   }
-  for (int i = threadIdx.x; i < RS_TILE; i += RS_THREADS) {
-    const int64_t q = base + i;
-    if (q < n) atomicAdd(&hist[(keys[q] >> shift) & (radix - 1)], 1);
-  }
+#pragma unroll
+  for (int k = 0; k < ROUNDS; ++k)
+    if (base + k * RS_THREADS + threadIdx.x < n) atomicAdd(&hist[(key[k] >> shift) & (radix - 1)], 1);
   __syncthreads();
   for (int i = threadIdx.x; i < radix; i += RS_THREADS) table[(int64_t)i * n_tiles + blockIdx.x] = hist[i];
 }
@@ -97,7 +103,11 @@ __global__ void __launch_bounds__(RS_THREADS) k_digit_scan(int32_t* __restrict__
 // the source rows are rebuilt per tile from the row offsets: every row that starts inside the tile marks its
 // first position in LDS, a running maximum spreads the marks (tile_row = the row owning the tile's first entry).
 // BITS: most bits a digit of this launch may have (sizes the counters in LDS).
-template <bool FIRST, bool HAS_VAL, int BITS, int ROUNDS>
+// Short tiles (small matrices) keep a record's four numbers together, in LDS and between the passes (in the set's four
+// arrays taken as one; keys_in / keys_out): a run of four equal digits is then one 64-byte piece instead of four of 16, and
+// the tile is reordered once instead of four times with two barriers each (1 M entries, two passes: 24.4 + 17.3 us,
+// 15.1 + 17.9 this way: the last pass writes its four arrays as before).  Long tiles fill their runs either way, and 64 KB of LDS would leave two workgroups per compute unit.
+template <bool FIRST, bool LAST, bool HAS_VAL, int BITS, int ROUNDS>
 __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
     const int32_t* __restrict__ keys_in, const int32_t* __restrict__ src_in, const int32_t* __restrict__ row_in,
     const int32_t* __restrict__ val_in, const int64_t* __restrict__ indptr, int64_t n_rows,
@@ -111,11 +121,41 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
   __shared__ int wave_base[RS_WAVES][RADIX];  // tile-local sorted position of each wave's first key of a digit
   __shared__ int delta[RADIX];                // output position minus tile-local position, per digit
   __shared__ int wave_tot[RS_WAVES];
-  __shared__ int buf[RS_TILE];
+  constexpr bool RECORDS = ROUNDS == RS_ROUNDS_SMALL;
+  __shared__ __align__(16) int buf[RS_TILE * (RECORDS ? 4 : 1)];
   const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x / ISP_WAVE;
   for (int i = threadIdx.x; i < RS_WAVES * RADIX; i += RS_THREADS) (&wave_cnt[0][0])[i] = 0;
   const int64_t tile_base = (int64_t)blockIdx.x * RS_TILE;
   const int tile_count = (int)((n - tile_base < RS_TILE) ? n - tile_base : RS_TILE);
+  const int64_t wbase = tile_base + (int64_t)w * RS_WAVE_KEYS;
+  int key[RS_ROUNDS], src[RS_ROUNDS], row[RS_ROUNDS], val[RS_ROUNDS], pos[RS_ROUNDS];
+#pragma unroll
+  for (int r = 0; r < RS_ROUNDS; ++r) {
+    const int64_t q = wbase + r * ISP_WAVE + lane;
+    const bool valid = q < n;
+    if constexpr (RECORDS && !FIRST) {
+      const int4 rec = valid ? reinterpret_cast<const int4*>(keys_in)[q] : make_int4(0, 0, 0, 0);
+      key[r] = rec.x;
+      src[r] = rec.y;
+      row[r] = rec.z;
+      val[r] = rec.w;
+    } else {
+      key[r] = valid ? keys_in[q] : 0;
+      src[r] = FIRST ? (int32_t)q : valid ? src_in[q] : 0;
+      row[r] = !FIRST && valid ? row_in[q] : 0;
+      val[r] = HAS_VAL && valid ? val_in[q] : 0;
+    }
+  }
+  // thread t owns digits t * PER ...
+  constexpr int PER = RADIX / RS_THREADS > 0 ? RADIX / RS_THREADS : 1;
+  int all[PER], prior[PER];  // a digit's entries in all tiles, in the tiles before this one
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int dg = threadIdx.x * PER + k;
+    const bool on = dg < RADIX && dg <= mask;
+    all[k] = on ? digit_total[dg] : 0;
+    prior[k] = on ? table_scanned[(int64_t)dg * n_tiles + blockIdx.x] : 0;
+  }
   if (FIRST) {
     for (int i = threadIdx.x; i < RS_TILE; i += RS_THREADS) buf[i] = 0;
     __syncthreads();
@@ -152,23 +192,10 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
     for (int k = 0; k < RS_ROUNDS; ++k) buf[threadIdx.x * RS_ROUNDS + k] = loc[k] > before ? loc[k] : before;
   }
   __syncthreads();
-  const int64_t wbase = tile_base + (int64_t)w * RS_WAVE_KEYS;
   const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  int key[RS_ROUNDS], src[RS_ROUNDS], row[RS_ROUNDS], val[RS_ROUNDS], pos[RS_ROUNDS];
+  if (FIRST) {
 #pragma unroll
-  for (int r = 0; r < RS_ROUNDS; ++r) {
-    const int64_t q = wbase + r * ISP_WAVE + lane;
-    const bool valid = q < n;
-    key[r] = valid ? keys_in[q] : 0;
-    if (FIRST) {
-      src[r] = (int32_t)q;
-      row[r] = valid ? buf[w * RS_WAVE_KEYS + r * ISP_WAVE + lane] : 0;
-      val[r] = (HAS_VAL && valid) ? val_in[q] : 0;
-    } else {
-      src[r] = valid ? src_in[q] : 0;
-      row[r] = valid ? row_in[q] : 0;
-      val[r] = (HAS_VAL && valid) ? val_in[q] : 0;
-    }
+    for (int r = 0; r < RS_ROUNDS; ++r) row[r] = buf[w * RS_WAVE_KEYS + r * ISP_WAVE + lane];
   }
 #pragma unroll
   for (int r = 0; r < RS_ROUNDS; ++r) {
@@ -186,17 +213,15 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
     if (valid && (m & lt_mask) == 0) wave_cnt[w][dg] = before + __popcll(m);  // lowest lane of the group
   }
   __syncthreads();
-  {  // thread t owns digits t * PER ...: exclusive scan of the tile's digit counts -> where each digit starts in the tile
-    constexpr int PER = RADIX / RS_THREADS > 0 ? RADIX / RS_THREADS : 1;
-    int cnt[PER][RS_WAVES], tot[PER], all[PER], sum = 0, sum_all = 0;
+  {  // exclusive scan of the tile's digit counts -> where each digit starts in the tile
+    int cnt[PER][RS_WAVES], tot[PER], sum = 0, sum_all = 0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int dg = threadIdx.x * PER + k;
-      tot[k] = all[k] = 0;
+      tot[k] = 0;
       if (dg < RADIX) {
 #pragma unroll
         for (int ww = 0; ww < RS_WAVES; ++ww) { cnt[k][ww] = wave_cnt[ww][dg]; tot[k] += cnt[k][ww]; }
-        if (dg <= mask) all[k] = digit_total[dg];
       }
       sum += tot[k];
       sum_all += all[k];
@@ -208,8 +233,7 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
     for (int k = 0; k < PER; ++k) {
       const int dg = threadIdx.x * PER + k;
       if (dg < RADIX) {
-        const int prior = dg <= mask ? table_scanned[(int64_t)dg * n_tiles + blockIdx.x] : 0;
-        delta[dg] = before + prior - start;
+        delta[dg] = before + prior[k] - start;
         int run = start;
 #pragma unroll
         for (int ww = 0; ww < RS_WAVES; ++ww) { wave_base[ww][dg] = run; run += cnt[k][ww]; }
@@ -219,6 +243,31 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
     }
   }
   __syncthreads();
+  if constexpr (RECORDS) {
+    int4* __restrict__ rec = reinterpret_cast<int4*>(buf);  // (the rows in buf have been read: barriers above)
+#pragma unroll
+    for (int r = 0; r < RS_ROUNDS; ++r)
+      if (wbase + r * ISP_WAVE + lane < n)
+        rec[wave_base[w][(key[r] >> shift) & mask] + pos[r]] = make_int4(key[r], src[r], row[r], val[r]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < RS_ROUNDS; ++k) {
+      const int i = k * RS_THREADS + threadIdx.x;
+      if (i < tile_count) {
+        const int4 e = rec[i];
+        const int dst = delta[(e.x >> shift) & mask] + i;
+        if (LAST) {
+          keys_out[dst] = e.x;
+          src_out[dst] = e.y;
+          row_out[dst] = e.z;
+          if (HAS_VAL) val_out[dst] = e.w;
+        } else {
+          reinterpret_cast<int4*>(keys_out)[dst] = e;
+        }
+      }
+    }
+    return;
+  }
   // keys: into digit order in LDS, then out; remember both positions for the other arrays
 #pragma unroll
   for (int r = 0; r < RS_ROUNDS; ++r) {
@@ -254,19 +303,32 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
   if (HAS_VAL) move(val, val_out);
 }
 
-// Row offsets of A^T from the sorted column keys: an offset changes where the sorted column changes;
-// empty columns get the next offset.
+// Row offsets of A^T from the sorted column keys: an offset changes where the sorted column changes; empty columns get the
+// next offset.  COMPARE (square matrices): *differs becomes 1 when A^T's offsets and indices are not, element for element,
+// A's own; otherwise the pattern is symmetric with every row's columns ascending, and entry p of A^T is the mirror (j, i)
+// of entry p = (i, j) of A.  (*differs is zeroed before.)
+template <bool COMPARE>
 __global__ void __launch_bounds__(256) k_col_offsets(const int32_t* __restrict__ skey, int64_t nnz, int64_t n_cols,
-                                                     int64_t* __restrict__ t_indptr) {
+                                                     int64_t* __restrict__ t_indptr, const int32_t* __restrict__ t_indices,
+                                                     const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
+                                                     int* __restrict__ differs) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nnz) return;
-  const int32_t c = skey[q];
-  const int32_t prev = q > 0 ? skey[q - 1] : -1;
-  // (the clamp only matters for an unvalidated CSR with a column >= n_cols)
-  const int64_t c_hi = c < n_cols ? (int64_t)c : n_cols - 1;
-  for (int64_t cc = (int64_t)prev + 1; cc <= c_hi; ++cc) t_indptr[cc] = q;
-  if (q == nnz - 1)
-    for (int64_t cc = (int64_t)c + 1; cc <= n_cols; ++cc) t_indptr[cc] = nnz;
+  bool bad = false;
+  if (q < nnz) {
+    const int32_t c = skey[q];
+    const int32_t prev = q > 0 ? skey[q - 1] : -1;
+    if (COMPARE) bad = indices[q] != t_indices[q];
+    auto offset = [&](int64_t cc, int64_t o) {
+      t_indptr[cc] = o;
+      if (COMPARE) bad |= indptr[cc] != o;
+    };
+    // (the clamp only matters for an unvalidated CSR with a column >= n_cols)
+    const int64_t c_hi = c < n_cols ? (int64_t)c : n_cols - 1;
+    for (int64_t cc = (int64_t)prev + 1; cc <= c_hi; ++cc) offset(cc, q);
+    if (q == nnz - 1)
+      for (int64_t cc = (int64_t)c + 1; cc <= n_cols; ++cc) offset(cc, nnz);
+  }
+  if (COMPARE && __any(bad) && (threadIdx.x & (ISP_WAVE - 1)) == 0) *differs = 1;  // (plain store of the same value from any wave)
 }
 
 // t_values[q] = values[perm[q]] for matrices whose columns are long, in blocks of rows.  In the order of q, neighbouring loads lie a row apart
@@ -369,21 +431,6 @@ __global__ void __launch_bounds__(256) k_inverse_perm(const int32_t* __restrict_
   if (q < nnz) inv_perm[perm[q]] = (int32_t)q;
 }
 
-// *differs becomes 1 when A^T's offsets and indices are not, element for element, A's own: otherwise the pattern
-// is symmetric with every row's columns ascending, and entry p of A^T is the mirror (j, i) of entry p = (i, j)
-// of A.  (*differs is zeroed before.)
-__global__ void __launch_bounds__(256) k_compare_pattern(const int64_t* __restrict__ indptr, const int64_t* __restrict__ t_indptr,
-                                                         int64_t n, const int32_t* __restrict__ indices,
-                                                         const int32_t* __restrict__ t_indices, int64_t nnz,
-                                                         int* __restrict__ differs) {
-  bool bad = false;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nnz + n + 1; i += (int64_t)gridDim.x * blockDim.x) {
-    if (i < nnz) bad |= indices[i] != t_indices[i];
-    else bad |= indptr[i - nnz] != t_indptr[i - nnz];
-  }
-  if (__any(bad) && (threadIdx.x & (ISP_WAVE - 1)) == 0) *differs = 1;  // (plain store of the same value from any wave)
-}
-
 __global__ void __launch_bounds__(256) k_fill_i64(int64_t* __restrict__ a, int64_t n, int64_t v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) a[i] = v;
@@ -407,9 +454,10 @@ t_layout make_layout(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_value
   L.t_indices = take(e);
   L.perm = take(e);
   L.t_values = take(has_values ? e : 0);
-  // two sets of record arrays (key, source position, source row, value) that the passes alternate between
+  // two sets of record arrays (key, source position, source row, value) that the passes alternate between (small
+  // matrices: of records of the four)
   for (int k = 0; k < 2; ++k)
-    for (int a = 0; a < 4; ++a) L.set[k][a] = take(a == 3 && !has_values ? 0 : e);
+    for (int a = 0; a < 4; ++a) L.set[k][a] = take(a == 3 && !has_values && !L.small ? 0 : e);
   L.tile_row = take((size_t)(L.n_tiles + 1) * 4);
   L.table = take((size_t)(((int64_t)L.n_tiles << RS_MAX_BITS) + 1) * 4);
   L.digit_total = take((size_t)(1 << RS_MAX_BITS) * 4);
@@ -513,30 +561,37 @@ isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_
         out[2] = t_indices;
         out[3] = (int32_t*)t_values;
       }
-#define ISP_GO(F, HV, B, R)                                                                                          \
-  k_radix_scatter<F, HV, B, R><<<n_tiles, RS_THREADS, 0, s>>>(in[0], in[1], in[2], in[3], v.indptr, n_rows, tile_row, nnz, shift, \
-                                                           mask, n_tiles, table, digit_total, out[0], out[1], out[2], out[3])
-#define ISP_GO2(F, HV)                                                                                               \
+#define ISP_GO(F, LA, HV, B, R)                                                                                      \
+  k_radix_scatter<F, LA, HV, B, R><<<n_tiles, RS_THREADS, 0, s>>>(in[0], in[1], in[2], in[3], v.indptr, n_rows, tile_row, nnz, \
+                                                               shift, mask, n_tiles, table, digit_total, out[0], out[1], out[2], out[3])
+#define ISP_GO2(F, LA, HV)                                                                                           \
   do {                                                                                                               \
-    if (L.small) { if (width > 8) ISP_GO(F, HV, 9, RS_ROUNDS_SMALL); else ISP_GO(F, HV, 8, RS_ROUNDS_SMALL); }          \
-    else ISP_GO(F, HV, 8, RS_ROUNDS_LARGE);                                                                          \
+    if (width > 8) ISP_GO(F, LA, HV, 9, RS_ROUNDS_SMALL); else ISP_GO(F, LA, HV, 8, RS_ROUNDS_SMALL);                     \
   } while (0)
-      if (pass == 0) { if (has_values) ISP_GO2(true, true); else ISP_GO2(true, false); }
-      else { if (has_values) ISP_GO2(false, true); else ISP_GO2(false, false); }
+#define ISP_GO3(F, LA) do { if (has_values) ISP_GO2(F, LA, true); else ISP_GO2(F, LA, false); } while (0)
+#define ISP_GO4(F) do { if (has_values) ISP_GO(F, true, true, 8, RS_ROUNDS_LARGE); else ISP_GO(F, true, false, 8, RS_ROUNDS_LARGE); } while (0)
+      const bool first = pass == 0, last = pass == n_pass - 1;
+      if (!L.small) { if (first) ISP_GO4(true); else ISP_GO4(false); }  // (four arrays in and out in every pass)
+      else if (first && last) ISP_GO3(true, true);
+      else if (first) ISP_GO3(true, false);
+      else if (last) ISP_GO3(false, true);
+      else ISP_GO3(false, false);
+#undef ISP_GO4
+#undef ISP_GO3
 #undef ISP_GO2
 #undef ISP_GO
       ISP_LAUNCH_CHECK();
       for (int a = 0; a < 4; ++a) in[a] = out[a];
     }
-    k_col_offsets<<<(unsigned)((nnz + 255) / 256), 256, 0, s>>>(in[0], nnz, n_cols, t_indptr);
+    // (and is the pattern symmetric?  The first histogram has cleared the flag.)
+#define ISP_GO(C)                                                                                                    \
+  k_col_offsets<C><<<(unsigned)((nnz + 255) / 256), 256, 0, s>>>(in[0], nnz, n_cols, t_indptr, t_indices, v.indptr, v.indices, \
+                                                                 differs)
+    if (n_rows == n_cols) ISP_GO(true); else ISP_GO(false);
+#undef ISP_GO
     ISP_LAUNCH_CHECK();
   }
-  // Is the pattern symmetric (A^T's structure identical to A's)?  (The first histogram has cleared the flag.)
   const bool square = n_rows == n_cols && nnz > 0;
-  if (square) {
-    k_compare_pattern<<<2048, 256, 0, s>>>(v.indptr, t_indptr, n_rows, v.indices, t_indices, nnz, differs);
-    ISP_LAUNCH_CHECK();
-  }
   isp_csr* At = nullptr;
   isp_status st;
   int h_differs = 1;

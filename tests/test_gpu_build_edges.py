@@ -61,6 +61,31 @@ def test_tile_edges(n_rows, n_cols, nnz, hub):
     _check(*_random(n_rows, n_cols, nnz, n_rows + nnz, hub), n_cols)
 
 
+@pytest.mark.parametrize("n_rows,n_cols,nnz", [(64, 256, 1025), (65, 257, 4097), (100, 131073, 9000), (3000, 1 << 20, 50000),
+                                               (5, 1 << 26, 3000)])
+def test_pattern_only_transposes(n_rows, n_cols, nnz):
+    """One to four passes of the sort without values (records of a small matrix still hold four numbers)."""
+    print("rows %d cols %d nnz %d, no values" % (n_rows, n_cols, nnz), flush=True)
+    indptr, indices, _ = _random(n_rows, n_cols, nnz, nnz)
+    At, _ = isp.csr_transpose_cached(build(indptr, indices, None, n_cols=n_cols))
+    ti, tj, tp, _ = oracle.transpose(n_rows, n_cols, indptr, indices, None)
+    got = At.export()
+    assert got[2] is None
+    for g, ref in ((got[0], ti), (got[1], tj), (got[3], tp)):
+        assert np.array_equal(g.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("at", [0, 4_999_999])
+def test_column_out_of_range_is_reported(at):
+    """Few rows, many entries: the workgroup that meets the bad column need not own any rows."""
+    print("bad column at %d" % at, flush=True)
+    indices = np.zeros(5_000_000, np.int32)
+    indices[at] = 7
+    with pytest.raises(isp.IspError) as e:
+        build(np.array([0, 1_000_000, 2_000_000, 5_000_000], np.int64), indices, None, n_cols=7)
+    assert e.value.status_name == "ISP_EBADCSR"
+
+
 @pytest.mark.parametrize("n_hub", [8191, 8192, 8193, 20000])
 def test_many_segments(n_hub):
     print("hub rows %d" % n_hub, flush=True)
