@@ -77,6 +77,13 @@ isp_status launch_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int
 // MEAN: finished rows are divided by their length (partial rows are not: their fix-up divides).
 constexpr int SPMM_RING = 4;
 
+// On the packed layout, launches wider than 64 columns ask for LDS they do not use, so that a compute unit holds four
+// workgroups instead of five: the rows of X that the whole chip has in flight and in use at a time then fit the L2s better.
+// us per SpMM with five / four / three: 233 k columns, 115 M entries: 128 columns 2518 / 2440 / 2599, 256 5069 / 4905 / 5219; 2.4 M,
+// 124 M: 128 4755 / 4672 / 4804; 200 k, 20 M: 128 565 / 549 / 566; 800 k, 40 M: 100 1481 / 1453 / 1472.  At 64 columns it
+// makes no difference (2326 / 2325), at 32 latency counts (1213 / 1248).
+constexpr unsigned SPMM_FOUR_PER_CU = 160 * 1024 / 4 - sizeof(rn_lds);
+
 template <int LPG, bool ADDR32, int VEC, bool MEAN>
 __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
     isp_view A, const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
@@ -206,10 +213,11 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG) * (unsigned)n_slices;
+    const unsigned spare = packed && n_slices * LPG * VEC > 64 ? SPMM_FOUR_PER_CU : 0u;
     const bool a32 = v.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
                      ((uint64_t)v.n_cols * (uint64_t)ldx + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
 #define ISP_GO(A32, MN)                                                                                        \
-  k_spmm_grouped<LPG, A32, VEC, MN><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
+  k_spmm_grouped<LPG, A32, VEC, MN><<<grid, ISP_WG, spare, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
                                                             n_slices, Y, ldy)
     if constexpr (VEC < 4) {  // scalar lanes are only dispatched with 32-bit addressing and for the plain sum
       ISP_GO(true, false);
