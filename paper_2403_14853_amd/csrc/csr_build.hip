@@ -1035,6 +1035,7 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   isp_csr* A = new (std::nothrow) isp_csr();
   if (!A) return isp_fail(ISP_ENOMEM, "host allocation of the handle failed");
   A->device = device;
+  A->wave_slots = isp_wave_slots();
   A->tune = isp_read_tuning();
   fill_view(A->v, n_rows, n_cols, nnz, indptr, indices, values, po, pp);
   A->vp = A->v;

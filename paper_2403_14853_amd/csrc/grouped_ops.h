@@ -41,11 +41,11 @@ struct policy_has_val2 : std::false_type {};
 template <class P>
 struct policy_has_val2<P, std::void_t<decltype(P::HAS_VAL2)>> : std::bool_constant<P::HAS_VAL2> {};
 
-template <class P, int LPG, int W, bool ADDR32, bool TAIL>
+template <class P, int LPG, int W, bool ADDR32, bool TAIL, class Lds>
 __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __restrict__ indptr,
                                           const int32_t* __restrict__ indices, const float* __restrict__ values,
                                           const typename P::args& pa, int d, float* __restrict__ Y, int64_t ldy,
-                                          rn_lds& lds, int k_lo = 0) {
+                                          Lds& lds, int k_lo = 0) {
   // k_lo: first feature column of this pass (only the per-entry policies run in column windows;
   // their partial dot products are then added up across passes)
   static_assert(W == 4 || W == 8, "one or two float4 per lane");
@@ -60,7 +60,7 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
   if (item >= A.n_blocks + A.n_seg) return;
   const item_range it = locate_item(A, indptr, item);
   if (it.skip) return;
-  rn_wave_lds& L = lds.w[w];
+  auto& L = lds.w[w];
   const rn_run R = rn_prepare<G>(it, indptr, indices, values, nullptr, L, lane);
 
   const int g = lane / LPG, q = lane % LPG;

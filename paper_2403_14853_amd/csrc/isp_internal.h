@@ -93,6 +93,7 @@ struct isp_csr {
   bool gather_bound_valid;
   isp_csr_info_t info;
   int device;
+  int wave_slots;          // isp_wave_slots() of that device
   isp_csr* At;             // cached transpose (owned), or NULL
   bool is_transpose;
   // Alias handles (alias.hip): a copy of another handle ("the source") with scratch of its own.  source is

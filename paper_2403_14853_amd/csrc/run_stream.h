@@ -22,12 +22,31 @@ namespace isp_dev {
 constexpr int RN_PAD = 16;          // spare entries behind the item's last (steps of the last round may read there)
 constexpr int RN_CHUNK = 2;         // entries read from LDS at a time
 
-struct __attribute__((aligned(16))) rn_wave_lds {
-  int2 ent[GS_MAX_ENT + RN_PAD];   // (column, value bits); afterwards the runs' unfinished sums
+template <int CAP>
+struct __attribute__((aligned(16))) rn_wave_lds_of {
+  int2 ent[CAP + RN_PAD];          // (column, value bits); afterwards the runs' unfinished sums
   int dst[GS_MAX_ROWS + 8];        // output row of each non-empty row, in order; from the top down: the empty rows
   gs_u16 end[GS_MAX_ROWS + 8];     // where each non-empty row ends, relative to the item
 };
-struct rn_lds { rn_wave_lds w[ISP_WAVES_PER_WG]; };
+template <int CAP>
+struct rn_lds_of { rn_wave_lds_of<CAP> w[ISP_WAVES_PER_WG]; };
+using rn_wave_lds = rn_wave_lds_of<GS_MAX_ENT>;
+using rn_lds = rn_lds_of<GS_MAX_ENT>;
+
+// Tables of 768 entries let a compute unit (160 KB) hold five workgroups, tables of RN_SMALL seven.  Where the items are
+// that small and the dense operand fits the L2s (eight of 4 MB, shared with everything else), the additional wavefronts hide
+// more of the loads' latency; where it does not fit they only spread the chip's gathers over more rows than the L2s
+// keep, and a launch that does not fill five per compute unit gains nothing.  us with tables of 768 / RN_SMALL entries (the launches' rules
+// stand with them):
+//   SpMM: 20 k columns, 400 k entries, 64 columns 14.5 / 13.7; 10 k, 1 M: 16 16.3 / 14.7, 128 33.4 / 32.2; 50 k, 1.5 M: 32 27.1 /
+//   24.2, 64 35.3 / 32.6; beyond the L2s, 100 k, 1 M: 64 (26 MB) 29.4 / 30.0, 100 55.0 / 58.2;
+//   SDDMM: 10 k, 1 M: 16 13.0 / 11.7; 50 k, 1.5 M: 64 31.0 / 27.7; beyond, 100 k, 1 M: 64 27.3 / 28.2; 169 k, 2.4 M: 100 106 / 112.
+constexpr int RN_SMALL = 448;
+constexpr int64_t RN_FIT_BYTES = 24 << 20;
+inline bool rn_small_tables(const isp_csr* A, const isp_view& v, int width, int64_t wgs) {
+  return A->info.block_cost + v.hub_t <= RN_SMALL && v.seg_len <= RN_SMALL && v.n_cols * width * 4 <= RN_FIT_BYTES &&
+         wgs * 16 > 5 * (int64_t)A->wave_slots;  // (16 slots per compute unit)
+}
 
 // This lane's group's run, and the item's shape.
 struct rn_run {
@@ -56,10 +75,10 @@ __device__ __forceinline__ rn_first_rows rn_request_rows(const item_range& it, c
 
 // The groups' runs over n_ent staged entries.  slot_of: for blocks of pieces, the partial row of piece `row` (else
 // NULL).  staged(o): how many of the item's first o entries are staged (all, where nothing is left out).
-template <int G, class Staged>
+template <int G, class Lds, class Staged>
 __device__ __forceinline__ rn_run rn_find_runs(const item_range& it, const int64_t* __restrict__ indptr,
                                                const int32_t* __restrict__ slot_of, int n_ent, const rn_first_rows& f,
-                                               Staged&& staged, rn_wave_lds& L, int lane) {
+                                               Staged&& staged, Lds& L, int lane) {
   const int n_rows = it.is_seg ? 0 : it.row_last - it.row;
   const int g = lane / (ISP_WAVE / G);
   const int q = n_ent / G, rest = n_ent - q * G;
@@ -115,10 +134,10 @@ __device__ __forceinline__ rn_run rn_find_runs(const item_range& it, const int64
 }
 
 // Stage the item and find the groups' runs.  values may be NULL (every entry is 1).
-template <int G>
+template <int G, class Lds>
 __device__ inline rn_run rn_prepare(const item_range& it, const int64_t* __restrict__ indptr,
                                     const int32_t* __restrict__ indices, const float* __restrict__ values,
-                                    const int32_t* __restrict__ slot_of, rn_wave_lds& L, int lane) {
+                                    const int32_t* __restrict__ slot_of, Lds& L, int lane) {
   const int n_ent = (int)(it.p_end - it.p);
   const rn_first_rows f = rn_request_rows(it, indptr, slot_of, lane);
   constexpr int SB = 8;  // loads in flight per lane
@@ -155,9 +174,11 @@ __device__ __forceinline__ void rn_for(F&& f) { rn_for_each(f, std::make_integer
 // ahead, so that nothing waits for the list).
 struct rn_cursor {
   int k, row, row_next, end, end_next;
-  __device__ __forceinline__ rn_cursor(const rn_wave_lds& L, const rn_run& R)
+  template <class Lds>
+  __device__ __forceinline__ rn_cursor(const Lds& L, const rn_run& R)
       : k(R.k), row(L.dst[R.k]), row_next(L.dst[R.k + 1]), end((int)L.end[R.k] - R.start - 1), end_next(L.end[R.k + 1]) {}
-  __device__ __forceinline__ void advance(const rn_wave_lds& L, const rn_run& R) {
+  template <class Lds>
+  __device__ __forceinline__ void advance(const Lds& L, const rn_run& R) {
     ++k;
     row = row_next;
     end = end_next - R.start - 1;
@@ -173,8 +194,8 @@ struct rn_cursor {
 // A round of RING steps is consumed while the next one is requested, slot by slot, into the same registers; the
 // entries are read from LDS CHUNK steps before they are needed.  A row's end is the step number at which it
 // ends, kept per lane: one comparison a step.
-template <int RING, bool ENDS, bool ROWS, int CHUNK = RN_CHUNK, class Load, class Add, class End>
-__device__ __forceinline__ void rn_stream(const rn_wave_lds& L, const rn_run& R, Load&& load, Add&& add, End&& end_row) {
+template <int RING, bool ENDS, bool ROWS, int CHUNK = RN_CHUNK, class Lds, class Load, class Add, class End>
+__device__ __forceinline__ void rn_stream(const Lds& L, const rn_run& R, Load&& load, Add&& add, End&& end_row) {
   static_assert(RING % (2 * CHUNK) == 0 && 2 * CHUNK <= RN_PAD, "fetches alternate between two buffers");
   const int2* __restrict__ ep = L.ent + R.start;
   constexpr int C = CHUNK;

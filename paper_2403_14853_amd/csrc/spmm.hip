@@ -84,13 +84,13 @@ constexpr int SPMM_RING = 4;
 // makes no difference (2326 / 2325), at 32 latency counts (1213 / 1248).
 constexpr unsigned SPMM_FOUR_PER_CU = 160 * 1024 / 4 - sizeof(rn_lds);
 
-template <int LPG, bool ADDR32, int VEC, bool MEAN>
+template <int LPG, bool ADDR32, int VEC, bool MEAN, int CAP = GS_MAX_ENT>
 __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
     isp_view A, const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
     const float* __restrict__ values, const float* __restrict__ X, int64_t ldx, int d, int k_base, int n_slices,
     float* __restrict__ Y, int64_t ldy) {
   constexpr int G = ISP_WAVE / LPG;
-  __shared__ rn_lds lds;
+  __shared__ rn_lds_of<CAP> lds;
   const int lane = threadIdx.x & (ISP_WAVE - 1);
   const int w = threadIdx.x >> 6;
   const int slice = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % n_slices));
@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
   if (item >= A.n_blocks + A.n_seg) return;
   const item_range it = locate_item(A, indptr, item);
   if (it.skip) return;
-  rn_wave_lds& L = lds.w[w];
+  auto& L = lds.w[w];
   // Rows of a derived matrix (packed layout) beyond the real ones are pieces of long rows: like a hub segment
   // each adds into a partial row, named by piece_slot.  A block never mixes real rows and pieces.
   const bool pieces = !it.is_seg && (int64_t)it.row >= A.n_real_rows;
@@ -144,7 +144,8 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
       },
       [&](int k, int row) {
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) head[v] = carried ? acc[v] : head[v];
+        for (int v = 0; v < VEC; ++v)
+          if (carried) head[v] = acc[v];  // (as a choice between the two the scalar-lane kernel kept them in memory)
         if (!carried) {
           if (MEAN && !to_partial) {
             const float inv = inv_len(k);
@@ -219,7 +220,14 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
 #define ISP_GO(A32, MN)                                                                                        \
   k_spmm_grouped<LPG, A32, VEC, MN><<<grid, ISP_WG, spare, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
                                                             n_slices, Y, ldy)
-    if constexpr (VEC < 4) {  // scalar lanes are only dispatched with 32-bit addressing and for the plain sum
+    const int width = n_slices * LPG * VEC < d - k_base ? n_slices * LPG * VEC : d - k_base;
+    if (VEC == 4 && a32 && !packed && rn_small_tables(A, v, width, grid)) {
+#define ISP_SMALL(MN)                                                                                              \
+  k_spmm_grouped<LPG, true, 4, MN, RN_SMALL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
+                                                                     n_slices, Y, ldy)
+      if (mean_mode == 1) ISP_SMALL(true); else ISP_SMALL(false);
+#undef ISP_SMALL
+    } else if constexpr (VEC < 4) {  // scalar lanes are only dispatched with 32-bit addressing and for the plain sum
       ISP_GO(true, false);
     } else if (mean_mode == 1) {
       if (a32) ISP_GO(true, true); else ISP_GO(false, true);
