@@ -299,6 +299,7 @@ __global__ void __launch_bounds__(BS_THREADS) k_mark_rows(const int32_t* __restr
     __shared__ unsigned long long part[BS_THREADS / ISP_WAVE][STATS];
     const int lane = threadIdx.x & (ISP_WAVE - 1);
     int err = 0;
+#pragma unroll 8
     for (int i = threadIdx.x; i < n_err; i += BS_THREADS) err |= T.err[i];
     const int err1 = __syncthreads_or(err & 1), err2 = __syncthreads_or(err & 2);
     if (threadIdx.x == 0) {
@@ -438,6 +439,25 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
   }
 }
 
+// What a work item covers, written once per handle (see isp_view::item_desc).
+struct item_tables {
+  const int64_t* indptr;
+  const int32_t *blk_row, *hub_rows, *hub_seg_ptr, *seg_hub, *seg_begin;
+  int hub_t;
+};
+__device__ __forceinline__ int4 block_item(const item_tables& I, int b) {
+  const int row = I.blk_row[b], row_last = I.blk_row[b + 1];
+  const int64_t p = I.indptr[row], p_end = I.indptr[row_last];
+  const bool skip = (row_last == row + 1) && (p_end - p > I.hub_t);
+  return make_int4((int)p, (int)p_end, row, skip ? -1 : row_last);
+}
+__device__ __forceinline__ int4 segment_item(const item_tables& I, int s) {
+  const int h = I.seg_hub[s];
+  const int hr = I.hub_rows[h];
+  const int64_t p_end = (s + 1 < I.hub_seg_ptr[h + 1]) ? (int64_t)I.seg_begin[s + 1] : I.indptr[hr + 1];
+  return make_int4(I.seg_begin[s], (int)p_end, s, hr);
+}
+
 // Up to SO_SMALL segments: schedule order in one launch, every segment counting those before it (by first column, then
 // number).  SO_SMALL^2 comparisons are 1.5 us of the chip's vector ALUs if all of it works on them, hence few segments per
 // workgroup (5,000 segments: 11.4 us at 64, which left most of the chip idle, 7.4 at 16); the radix sort below is five
@@ -445,13 +465,24 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
 constexpr int SO_SMALL = 8192;
 constexpr int SO_SEGS = 16;     // segments per workgroup, one per lane of 16
 constexpr int SO_THREADS = 1024;
+// The same launch writes the work items: a segment's place is known with its rank, and workgroups beyond those of the segments
+// write the row blocks' (max_items bounds what the tables hold).  The counters are left in host_ctr.
 __global__ void __launch_bounds__(SO_THREADS) k_seg_rank(const int32_t* __restrict__ key,
-                                                         const build_counters* __restrict__ ctr, int32_t* __restrict__ order) {
+                                                         const build_counters* __restrict__ ctr, int32_t* __restrict__ order,
+                                                         item_tables I, int64_t max_items, build_counters* __restrict__ host_ctr,
+                                                         int4* __restrict__ desc) {
   constexpr int PER = SO_SMALL / SO_THREADS, WAVES = SO_THREADS / ISP_WAVE, SHARES = SO_THREADS / SO_SEGS;
   __shared__ __align__(16) int keys[SO_SMALL];
   __shared__ int part[WAVES][SO_SEGS];
-  const int n = ctr->n_seg;
-  if (ctr->err || n > SO_SMALL) return;  // (a malformed matrix has no bounds to rely on)
+  if (host_ctr && blockIdx.x == 0 && threadIdx.x == 0) *host_ctr = *ctr;
+  const int n = ctr->n_seg, n_blocks = ctr->n_blocks;
+  // (a malformed matrix has no bounds to rely on; the rest the host sees to)
+  if (ctr->err || n > SO_SMALL || (int64_t)n_blocks + n > max_items) return;
+  if ((int)blockIdx.x >= SO_SMALL / SO_SEGS) {
+    const int b = ((int)blockIdx.x - SO_SMALL / SO_SEGS) * SO_THREADS + (int)threadIdx.x;
+    if (b < n_blocks) desc[b] = block_item(I, b);
+    return;
+  }
   if ((int)blockIdx.x * SO_SEGS >= n) return;
   int kk[PER];  // (all of them on their way together)
 #pragma unroll
@@ -487,6 +518,7 @@ __global__ void __launch_bounds__(SO_THREADS) k_seg_rank(const int32_t* __restri
 #pragma unroll
     for (int ww = 0; ww < WAVES; ++ww) rank += part[ww][threadIdx.x];
     order[rank] = s;
+    desc[n_blocks + rank] = segment_item(I, s);
   }
 }
 
@@ -524,38 +556,12 @@ __global__ void __launch_bounds__(SO_TILE) k_seg_scatter(const int32_t* __restri
   val_out[dst] = val_in ? val_in[s] : s;
 }
 
-// What work item `item` covers, written once per handle (see isp_view::item_desc).
-__global__ void __launch_bounds__(256) k_item_desc(const int64_t* __restrict__ indptr, const int32_t* __restrict__ blk_row,
-                                                   int n_blocks, const int32_t* __restrict__ hub_rows,
-                                                   const int32_t* __restrict__ hub_seg_ptr,
-                                                   const int32_t* __restrict__ seg_hub,
-                                                   const int32_t* __restrict__ seg_begin,
-                                                   const int32_t* __restrict__ seg_order, int n_seg, int hub_t,
-                                                   const build_counters* __restrict__ ctr, int64_t max_items,
-                                                   build_counters* host_ctr, int4* __restrict__ desc) {
-  // ctr: the counts are read there (they are not known on the host yet) and the counters are left in host_ctr
-  if (ctr) {
-    if (host_ctr && blockIdx.x == 0 && threadIdx.x == 0) *host_ctr = *ctr;
-    n_blocks = ctr->n_blocks;
-    n_seg = ctr->n_seg;
-    if (ctr->err || n_seg > SO_SMALL || (int64_t)n_blocks + n_seg > max_items) return;  // (the host sees to it)
-  }
+// All work items at once, for partitions whose counts the host knows.
+__global__ void __launch_bounds__(256) k_item_desc(item_tables I, int n_blocks, const int32_t* __restrict__ seg_order, int n_seg,
+                                                   int4* __restrict__ desc) {
   const int item = blockIdx.x * blockDim.x + threadIdx.x;
-  if (item >= n_blocks + n_seg) return;
-  int4 q;
-  if (item < n_blocks) {
-    const int row = blk_row[item], row_last = blk_row[item + 1];
-    const int64_t p = indptr[row], p_end = indptr[row_last];
-    const bool skip = (row_last == row + 1) && (p_end - p > hub_t);
-    q = make_int4((int)p, (int)p_end, row, skip ? -1 : row_last);
-  } else {
-    const int s = seg_order[item - n_blocks];
-    const int h = seg_hub[s];
-    const int hr = hub_rows[h];
-    const int64_t p_end = (s + 1 < hub_seg_ptr[h + 1]) ? (int64_t)seg_begin[s + 1] : indptr[hr + 1];
-    q = make_int4(seg_begin[s], (int)p_end, s, hr);
-  }
-  desc[item] = q;
+  if (item < n_blocks) desc[item] = block_item(I, item);
+  else if (item < n_blocks + n_seg) desc[item] = segment_item(I, seg_order[item - n_blocks]);
 }
 
 // ---- the derived matrix of the packed SpMM layout ------------------------------------------------------
@@ -844,14 +850,12 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   build_counters& h = out->h;
   const bool small = nnz <= SMALL_NNZ;
   const int64_t max_items = L.max_blocks + L.max_seg;
+  const item_tables items{indptr, blk_row, hub_rows, hub_seg_ptr, seg_hub, seg_begin, pp.hub_t};
   host_slot slot;  // pinned: the device writes the counters there itself
   build_counters* host_ctr = small ? (build_counters*)slot.get() : nullptr;
   if (small) {
-    k_seg_rank<<<SO_SMALL / SO_SEGS, SO_THREADS, 0, s>>>(seg_key[0], ctr, seg_ord[0]);
-    ISP_LAUNCH_CHECK();
-    k_item_desc<<<(unsigned)((max_items + 255) / 256), 256, 0, s>>>(indptr, blk_row, 0, hub_rows, hub_seg_ptr, seg_hub,
-                                                                  seg_begin, seg_ord[0], 0, pp.hub_t, ctr, max_items,
-                                                                  host_ctr, item_desc);
+    const unsigned wgs = SO_SMALL / SO_SEGS + (unsigned)((L.max_blocks + SO_THREADS - 1) / SO_THREADS);
+    k_seg_rank<<<wgs, SO_THREADS, 0, s>>>(seg_key[0], ctr, seg_ord[0], items, max_items, host_ctr, item_desc);
     ISP_LAUNCH_CHECK();
   }
   if (!host_ctr) ISP_HIP(hipMemcpyAsync(&h, ctr, sizeof(h), hipMemcpyDeviceToHost, s));
@@ -884,9 +888,7 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
       seg_order = seg_ord[n_pass & 1];
     }
     if (h.n_blocks + h.n_seg > 0) {
-      k_item_desc<<<(unsigned)((h.n_blocks + h.n_seg + 255) / 256), 256, 0, s>>>(indptr, blk_row, h.n_blocks, hub_rows,
-                                                                               hub_seg_ptr, seg_hub, seg_begin, seg_order,
-                                                                               h.n_seg, pp.hub_t, nullptr, 0, nullptr,
+      k_item_desc<<<(unsigned)((h.n_blocks + h.n_seg + 255) / 256), 256, 0, s>>>(items, h.n_blocks, seg_order, h.n_seg,
                                                                                item_desc);
       ISP_LAUNCH_CHECK();
     }
