@@ -676,6 +676,24 @@ __global__ void __launch_bounds__(256) k_gather_values(const int32_t* __restrict
     if (q0 + u * 256 < nnz) out[q0 + u * 256] = v[u];
 }
 
+// The same for two arrays of values with one set of positions (a symmetric pattern's packed layout serves the matrix and its
+// transpose: 115 M entries, 2 x 282 us one after the other, 433 together, which reads the positions once).
+constexpr int GV2_PER_THREAD = 4;
+__global__ void __launch_bounds__(256) k_gather_values_pair(const int32_t* __restrict__ pos, const float* __restrict__ a,
+                                                            const float* __restrict__ b, int64_t nnz,
+                                                            float* __restrict__ out_a, float* __restrict__ out_b) {
+  int32_t p[GV2_PER_THREAD];
+  float va[GV2_PER_THREAD], vb[GV2_PER_THREAD];
+  const int64_t q0 = (int64_t)blockIdx.x * (256 * GV2_PER_THREAD) + threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < GV2_PER_THREAD; ++u) p[u] = q0 + u * 256 < nnz ? pos[q0 + u * 256] : 0;
+#pragma unroll
+  for (int u = 0; u < GV2_PER_THREAD; ++u) { va[u] = a[p[u]]; vb[u] = b[p[u]]; }
+#pragma unroll
+  for (int u = 0; u < GV2_PER_THREAD; ++u)
+    if (q0 + u * 256 < nnz) { out_a[q0 + u * 256] = va[u]; out_b[q0 + u * 256] = vb[u]; }
+}
+
 static_assert(sizeof(build_counters) <= host_slot::SIZE, "the counters fit a slot");
 
 // ---- workspace layout ------------------------------------------------------------------------------------
@@ -1010,6 +1028,21 @@ isp_status isp_gather_values(const int32_t* pos, const float* values, int64_t nn
 isp_status isp_refresh_packed_values(isp_csr* A, hipStream_t s) {
   if (!A->has_packed || !A->packed_values_rw || !A->v.values || A->v.nnz == 0) return ISP_OK;
   return isp_gather_values(A->packed_src_pos, A->v.values, A->v.nnz, A->packed_values_rw, s);
+}
+
+isp_status isp_refresh_packed_pair(isp_csr* A, hipStream_t s) {
+  isp_csr* At = A->At;
+  const bool shared = At && A->has_packed && At->has_packed && A->packed_values_rw && At->packed_values_rw &&
+                      A->packed_src_pos == At->packed_src_pos && A->v.nnz > 0;
+  if (!shared) {
+    const isp_status st = isp_refresh_packed_values(A, s);
+    return st != ISP_OK || !At ? st : isp_refresh_packed_values(At, s);
+  }
+  const int64_t nnz = A->v.nnz;
+  k_gather_values_pair<<<(unsigned)((nnz + 256 * GV2_PER_THREAD - 1) / (256 * GV2_PER_THREAD)), 256, 0, s>>>(
+      A->packed_src_pos, A->v.values, At->v.values, nnz, A->packed_values_rw, At->packed_values_rw);
+  ISP_LAUNCH_CHECK();
+  return ISP_OK;
 }
 
 isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const int64_t* indptr,

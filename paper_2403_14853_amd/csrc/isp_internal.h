@@ -155,6 +155,8 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
 isp_status isp_gather_values(const int32_t* pos, const float* values, int64_t nnz, float* out, hipStream_t s);
 // Copy A's (rewritten) values into the packed SpMM layout's own value array again.
 isp_status isp_refresh_packed_values(isp_csr* A, hipStream_t s);
+// The same for A and its cached transpose, if there is one (whose own values must be up to date).
+isp_status isp_refresh_packed_pair(isp_csr* A, hipStream_t s);
 
 // ---- transpose (transpose.hip) ---------------------------------------------------------------
 size_t isp_transpose_workspace_bytes(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_values);
