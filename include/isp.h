@@ -183,7 +183,7 @@ isp_status isp_csr_info(const isp_csr_t* A, isp_csr_info_t* info);
  *   workspace: device memory, 256-byte aligned, isp_csr_alias_workspace bytes, borrowed until the alias is
  *     destroyed; it needs no clearing.  Size: 1 KiB per hub-row segment or row piece (isp_csr_info: n_segments,
  *     spmm_pieces) of A and as much again for its cached transpose, plus one byte per stored entry when the
- *     transpose exists, plus 512 bytes per column of A and of the transpose where columns have 32 entries or more - about 2 GiB for 124 M entries in 2.4 M rows.
+ *     transpose exists, plus 512 bytes per column of A and of the transpose where columns have 32 entries or more - about 4.4 GiB for 124 M entries in 2.4 M rows.
  *   The alias takes over A's cached transpose as it is at this call: build it on A first if the alias is to
  *     run backward calls (isp_csr_transpose_cached on the alias returns it, or ISP_EINVAL if A had none).
  *   Destroy the alias (isp_csr_destroy) before A.  After isp_csr_values_changed(A) every alias made before is
