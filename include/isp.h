@@ -31,7 +31,8 @@
  *   - A handle belongs to the HIP device that was current when it was built; using it with another device
  *     current yields ISP_EINVAL.
  *   - Calls that use the same handle (or a handle and its cached transpose) on different streams
- *     at the same time race on the handle's scratch (hub-row partial sums); serialise them.
+ *     at the same time race on the handle's scratch (hub-row partial sums, SpMM's copy of a ragged dense operand);
+ *     serialise them.
  *   - Results are run-to-run bitwise deterministic: no floating-point atomics are used.
  *   - Environment variables (tuning and tests only; none is needed).  All are read when isp_csr_build runs and
  *     are kept in the handle; no compute call reads the environment.  (The partition sizes of a cached transpose
@@ -171,8 +172,8 @@ isp_status isp_csr_info(const isp_csr_t* A, isp_csr_info_t* info);
 
 /*
  * Overlapping calls on one matrix (Section 1(b): the work partition, and Section 3.3: the cached transpose,
- * are built once and shared).  The compute calls keep the partial sums of hub-row segments, and the min / max
- * backward its per-entry marks, in the handle's workspace, so two calls on ONE handle must not run at the same
+ * are built once and shared).  The compute calls keep the partial sums of hub-row segments, SpMM the copy of a ragged
+ * operand, and the min / max backward its per-entry marks, in the handle's workspace, so two calls on ONE handle must not run at the same
  * time.  An alias is a second handle on the same matrix that keeps exactly that scratch in a workspace of its
  * own and shares everything else - the caller's arrays, both work partitions, the packed SpMM layout, the
  * cached transpose and its permutation: calls on A, on the alias and on other aliases may overlap freely
@@ -183,7 +184,8 @@ isp_status isp_csr_info(const isp_csr_t* A, isp_csr_info_t* info);
  *   workspace: device memory, 256-byte aligned, isp_csr_alias_workspace bytes, borrowed until the alias is
  *     destroyed; it needs no clearing.  Size: 1 KiB per hub-row segment or row piece (isp_csr_info: n_segments,
  *     spmm_pieces) of A and as much again for its cached transpose, plus one byte per stored entry when the
- *     transpose exists, plus 512 bytes per column of A and of the transpose where columns have 32 entries or more - about 4.4 GiB for 124 M entries in 2.4 M rows.
+ *     transpose exists, plus 512 bytes per column of A and of the transpose where SpMM copies ragged operands (32 entries or
+ *     more per column) - about 4.4 GiB for 124 M entries in 2.4 M rows.
  *   The alias takes over A's cached transpose as it is at this call: build it on A first if the alias is to
  *     run backward calls (isp_csr_transpose_cached on the alias returns it, or ISP_EINVAL if A had none).
  *   Destroy the alias (isp_csr_destroy) before A.  After isp_csr_values_changed(A) every alias made before is
