@@ -173,8 +173,8 @@ isp_status isp_csr_info(const isp_csr_t* A, isp_csr_info_t* info);
 /*
  * Overlapping calls on one matrix (Section 1(b): the work partition, and Section 3.3: the cached transpose,
  * are built once and shared).  The compute calls keep the partial sums of hub-row segments, SpMM the copy of a ragged
- * operand, and the min / max backward its per-entry marks, in the handle's workspace, so two calls on ONE handle must not run at the same
- * time.  An alias is a second handle on the same matrix that keeps exactly that scratch in a workspace of its
+ * operand, and the min / max backward its per-entry marks, in the handle's workspace, so two calls on ONE handle
+ * must not run at the same time.  An alias is a second handle on the same matrix that keeps exactly that scratch in a workspace of its
  * own and shares everything else - the caller's arrays, both work partitions, the packed SpMM layout, the
  * cached transpose and its permutation: calls on A, on the alias and on other aliases may overlap freely
  * (different streams or threads); calls on one alias must still follow each other.  Results are bit-identical

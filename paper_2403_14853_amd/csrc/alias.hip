@@ -2,9 +2,9 @@
 //
 // The kernels of a handle keep the partial sums of hub-row segments (and, in the min / max backward, one mark
 // per entry) in that handle's workspace, so two calls on one handle that run at the same time on two streams
-// would overwrite each other's partial rows (and SpMM's copies of ragged operands).  An alias shares everything that is only read - the caller's
-// CSR arrays, the work partitions, the packed SpMM layout, the cached transpose's arrays - and keeps what a
-// call writes in a workspace of its own.
+// would overwrite each other's partial rows (and SpMM's copies of ragged operands).  An alias shares everything that is
+// only read - the caller's CSR arrays, the work partitions, the packed SpMM layout, the cached transpose's arrays - and
+// keeps what a call writes in a workspace of its own.
 #include <new>
 #include "isp_internal.h"
 
