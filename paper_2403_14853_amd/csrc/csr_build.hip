@@ -365,8 +365,8 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
                                                  int32_t* __restrict__ seg_hub, int32_t* __restrict__ seg_begin,
                                                  int32_t* __restrict__ seg_key, build_counters* __restrict__ ctr,
                                                  int64_t max_blocks, int64_t max_hub, int64_t max_seg) {
-  // The bounds only bite for a malformed indptr (the host then reports ISP_EBADCSR); they keep
-  // every write inside the workspace in that case too.
+  // (asked for here, looked at behind the sums below; written by pass 2)
+  const int err = ctr->err;
   const int lane = threadIdx.x & (ISP_WAVE - 1);
   __shared__ int64_t s_ha[BS_THREADS], s_hb[BS_THREADS];
   __shared__ int s_hs[BS_THREADS];
@@ -385,6 +385,8 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
     hpos0 = (int)(unsigned)tot;
     block_exclusive_scan<int>(sg, &seg0);
   }
+  // Rows of a malformed indptr may overlap: their segments together can wrap the 32-bit sums, whatever the tables' bounds.
+  if (err & 1) return;  // (the host reports ISP_EBADCSR)
   const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
   for (int64_t base = r0; base < r1; base += (BS_THREADS / ISP_WAVE) * RPW) {
     const int64_t i = base + (threadIdx.x / ISP_WAVE) * RPW + lane;

@@ -86,6 +86,20 @@ def test_column_out_of_range_is_reported(at):
     assert e.value.status_name == "ISP_EBADCSR"
 
 
+def test_overlapping_rows_are_reported():
+    """Every second row claims all entries: more segments together than 32 bits count."""
+    n_rows, nnz = 600_000, 1_000_000
+    print("overlapping rows", flush=True)
+    indptr = np.zeros(n_rows + 1, np.int64)
+    indptr[1::2] = nnz
+    indptr[-1] = nnz
+    assert n_rows // 2 * (nnz // ((n_rows + nnz) // 16384)) > 1 << 31  # (segments of a quarter of a wavefront slot's share)
+    for trusted in (False, True):
+        with pytest.raises(isp.IspError) as e:
+            isp.csr_build(dev(indptr), torch.zeros(nnz, dtype=torch.int32, device="cuda"), None, n_cols=50, trusted=trusted)
+        assert e.value.status_name == "ISP_EBADCSR"
+
+
 @pytest.mark.parametrize("n_hub", [8191, 8192, 8193, 20000])
 def test_many_segments(n_hub):
     print("hub rows %d" % n_hub, flush=True)
