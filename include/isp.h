@@ -119,6 +119,9 @@ isp_status isp_csr_build_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, 
  * layout of its own: rows longer than 256 entries are cut into column-band pieces of 64 entries or more, and
  * the pieces, scheduled in column order, share work items with each other; that layout keeps a reordered copy
  * of the index and value arrays in the workspace (isp_csr_values_changed refreshes the values).
+ * SpMM's copy of a ragged dense operand (3 M entries or more, 32 or more per column: 512 bytes per column) takes the place of
+ * partial rows that are idle meanwhile; the workspace grows for it by at most 5 bytes per entry where the packed layout
+ * exists and by at most 128 MiB elsewhere, and a handle without room for the copy takes none.
  * Integer work and copies only.  Rows with ascending columns schedule best; any order is accepted.
  *   indptr/indices/values: borrowed device arrays (values may be NULL).
  *   workspace: device memory, 256-byte aligned, >= isp_csr_build_workspace() bytes; borrowed
@@ -180,12 +183,14 @@ isp_status isp_csr_info(const isp_csr_t* A, isp_csr_info_t* info);
  * (different streams or threads); calls on one alias must still follow each other.  Results are bit-identical
  * to A's.
  *   max_d: the widest feature width the alias will be used with (sizes the partial rows of FusedMM beyond 256
- *     columns; wider calls still work, one 256-column group per launch).
+ *     columns and the copy of a ragged operand; wider calls still work, FusedMM one 256-column group per launch, SpMM
+ *     without the copy, and give the same results).
  *   workspace: device memory, 256-byte aligned, isp_csr_alias_workspace bytes, borrowed until the alias is
  *     destroyed; it needs no clearing.  Size: 1 KiB per hub-row segment or row piece (isp_csr_info: n_segments,
  *     spmm_pieces) of A and as much again for its cached transpose, plus one byte per stored entry when the
- *     transpose exists, plus 512 bytes per column of A and of the transpose where SpMM copies ragged operands (32 entries or
- *     more per column) - about 4.4 GiB for 124 M entries in 2.4 M rows.
+ *     transpose exists, plus, where SpMM copies ragged operands (3 M entries or more, 32 or more per column), room for min(max_d,
+ *     128) floats per column of A and of the transpose, in whole lines from 17 floats up; none below max_d = 12 - for 124 M
+ *     entries in 2.4 M rows about 2 GiB without and 4.4 GiB with the widest copies.
  *   The alias takes over A's cached transpose as it is at this call: build it on A first if the alias is to
  *     run backward calls (isp_csr_transpose_cached on the alias returns it, or ISP_EINVAL if A had none).
  *   Destroy the alias (isp_csr_destroy) before A.  After isp_csr_values_changed(A) every alias made before is

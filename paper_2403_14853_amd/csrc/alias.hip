@@ -6,14 +6,15 @@
 // only read - the caller's CSR arrays, the work partitions, the packed SpMM layout, the cached transpose's arrays - and
 // keeps what a call writes in a workspace of its own.
 #include <new>
-#include "isp_internal.h"
+#include "stage_rule.h"
 
 namespace {
 
 struct alias_layout {
   int64_t rows_a, rows_t;   // partial rows for the handle and for its transpose
   size_t off_t, off_flags;  // byte offsets of the transpose's partial rows and of its entry marks
-  size_t off_stage, off_stage_t;  // ... of the copies of ragged operands
+  size_t off_stage, off_stage_t;  // ... of the copies of ragged operands,
+  int stage_cols;                 // which are as wide as calls of max_d columns need them
   size_t total;
 };
 
@@ -35,7 +36,8 @@ alias_layout make_alias_layout(const isp_csr* A, int32_t max_d) {
   off += isp_align((size_t)L.rows_t * ISP_PARTIAL_TILE * sizeof(float));
   L.off_flags = off;
   if (A->At) off += isp_align((size_t)A->v.nnz + 4);  // (cleared in 32-bit words)
-  auto stage = [&](const isp_csr* h) { return h && h->stage ? isp_align((size_t)h->v.n_cols * ISP_STAGE_COLS * sizeof(float)) : 0; };
+  L.stage_cols = isp_stage::pitch_up_to(max_d, A->tune.stage_always);
+  auto stage = [&](const isp_csr* h) { return h && h->stage ? isp_stage::bytes(h->v.n_cols, L.stage_cols) : 0; };
   L.off_stage = off;
   off += stage(A);
   L.off_stage_t = off;
@@ -85,7 +87,12 @@ extern "C" isp_status isp_csr_alias(const isp_csr_t* A, int32_t max_d, void* wor
   B->v.partials = reinterpret_cast<float*>(base);
   B->vp.partials = B->v.partials;  // (a call runs on one of the two partitions, never on both)
   B->partial_rows = L.rows_a;
-  if (A->stage) B->stage = reinterpret_cast<float*>(base + L.off_stage);
+  auto own_stage = [&](isp_csr* h, size_t off) {
+    if (!h->stage) return;
+    h->stage = L.stage_cols > 0 ? reinterpret_cast<float*>(base + off) : nullptr;
+    h->stage_cols = L.stage_cols;
+  };
+  own_stage(B, L.off_stage);
   if (A->At) {
     isp_csr* Bt = new (std::nothrow) isp_csr(*A->At);
     if (!Bt) { delete B; return isp_fail(ISP_ENOMEM, "host allocation of the handle failed"); }
@@ -95,7 +102,7 @@ extern "C" isp_status isp_csr_alias(const isp_csr_t* A, int32_t max_d, void* wor
     Bt->v.partials = reinterpret_cast<float*>(base + L.off_t);
     Bt->vp.partials = Bt->v.partials;
     Bt->partial_rows = L.rows_t;
-    if (Bt->stage) Bt->stage = reinterpret_cast<float*>(base + L.off_stage_t);
+    own_stage(Bt, L.off_stage_t);
     // The marks of the min / max backward are written by every call: the alias's own.  What the transpose
     // caches on first use besides (value / row length, the inverse permutation) is a pure function of the
     // shared arrays and stays shared: whichever handle fills it first writes the same numbers any other would.

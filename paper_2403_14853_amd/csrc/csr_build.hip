@@ -15,7 +15,7 @@
 #include <new>
 #include "block_scan.h"
 #include "host_slot.h"
-#include "partition_sizes.h"
+#include "stage_rule.h"
 
 namespace {
 using namespace isp_dev;
@@ -29,6 +29,7 @@ struct build_counters {
   int n_blocks, n_hub, n_seg;
 };
 
+constexpr size_t PARTIAL_ROW = ISP_PARTIAL_TILE * sizeof(float);
 constexpr int CUT_COUNT = 16;  // wavefronts' worth of entries that cutting a hub row looks at first
 constexpr int CUT_LAST = 8;    // candidates of a cut that are looked at together
 
@@ -1001,21 +1002,21 @@ isp_status build_packed(isp_csr* A, const partition_params& p1, int mid_t, char*
 
 }  // namespace
 
-// Room for the copies of ragged operands (spmm.hip: rule and figures).  ISP_STAGE_MIN (entries per column; 0 = no copies)
-// overrides the rule and its limit on the size.
-size_t isp_stage_bytes(int64_t n_cols, int64_t nnz) {
-  const int forced = env_int("ISP_STAGE_MIN", -1, -1, 1 << 20);
-  if (n_cols <= 0 || forced == 0) return 0;
-  if (forced > 0 ? nnz / n_cols < forced : nnz / n_cols < 32 || nnz < 3000000) return 0;
-  return isp_align((size_t)n_cols * ISP_STAGE_COLS * sizeof(float));
-}
-
 size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz) {
   const partition_params p1 = get_params(n_rows, nnz, isp_wave_slots());
-  const size_t own = make_layout(n_rows, nnz, p1).total + isp_stage_bytes(n_cols, nnz);
+  const ws_layout L = make_layout(n_rows, nnz, p1);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, p1);
+  const size_t own = L.total + isp_stage::own_bytes(n_cols, nnz, L.total - L.partials, mid_t > 0);
   if (mid_t == 0) return own;
   return make_packed_layout(n_rows, nnz, true, p1, mid_t, own).total;
+}
+
+void isp_place_stage(isp_csr* A, isp_stage::room* rooms, int n) {
+  const size_t b = isp_stage::wanted(A->v.n_cols, A->v.nnz);
+  A->stage = nullptr;
+  for (int k = 0; k < n && b > 0 && !A->stage; ++k) A->stage = isp_stage::take(rooms[k], b);
+  A->stages = A->stage != nullptr;
+  A->stage_cols = A->stages ? isp_stage::COLS : 0;
 }
 
 isp_status isp_gather_values(const int32_t* pos, const float* values, int64_t nnz, float* out, hipStream_t s) {
@@ -1054,8 +1055,8 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   const ws_layout L = make_layout(n_rows, nnz, pp);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, pp);
   packed_layout P{};
-  const size_t stage_bytes = isp_stage_bytes(n_cols, nnz);  // (behind the ordinary partition)
-  size_t need = L.total + stage_bytes;
+  const size_t rows_end = L.total + isp_stage::own_bytes(n_cols, nnz, L.total - L.partials, mid_t > 0);
+  size_t need = rows_end;
   if (mid_t > 0) {
     P = make_packed_layout(n_rows, nnz, values != nullptr, pp, mid_t, need);
     need = P.total;
@@ -1078,8 +1079,6 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   A->vp = A->v;
   A->partial_rows = L.max_seg + 1;
   A->spmm_rows = po.h.n_seg;
-  A->stages = stage_bytes > 0;
-  A->stage = A->stages ? (float*)(base + L.total) : nullptr;
   A->has_packed = false; A->packed_values_rw = nullptr; A->packed_src_pos = nullptr;
   A->perm = nullptr; A->t_values_rw = nullptr; A->At = nullptr; A->is_transpose = false; A->mirror_aligned = false;
   A->mean_values = nullptr; A->mean_values_packed = nullptr; A->mean_values_valid = false; A->mean_values_used = false;
@@ -1097,6 +1096,14 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
     st = build_packed(A, pp, mid_t, base, P, ws_bytes, s);
     if (st != ISP_OK) { delete A; return st; }
   }
+  // The copies of ragged operands: among the partial rows that no operation writes, the packed layout's first; else among
+  // those that a SpMM does not write (the calls on a handle follow each other).
+  char* rows = base + L.partials;
+  isp_stage::room rooms[3] = {
+      {base + P.cut.partials + (A->has_packed ? A->info.spmm_pieces : 0) * PARTIAL_ROW, base + P.cut.total},
+      {rows + isp_busy_rows(A) * PARTIAL_ROW, base + rows_end},
+      {rows + (A->has_packed ? 0 : A->v.n_seg) * PARTIAL_ROW, base + rows_end}};
+  isp_place_stage(A, rooms + (mid_t > 0 ? 0 : 1), mid_t > 0 ? 3 : 2);
   *out = A;
   return ISP_OK;
 }

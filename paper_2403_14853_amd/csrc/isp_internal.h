@@ -74,8 +74,9 @@ struct isp_csr {
   int packed_block_cost, packed_row_cost;  // of vp's partition (bounds of its blocks: see csr_build.hip)
   float* packed_values_rw;        // vp.values, writable, NULL without values
   const int32_t* packed_src_pos;  // position in v's arrays of every entry of the derived matrix
-  bool stages;                    // SpMM copies the columns of a ragged dense operand to whole lines (isp_stage_bytes > 0)
-  float* stage;                   // scratch for that copy; NULL: the same launches gather from the operand itself
+  bool stages;                    // SpMM copies the columns of a ragged dense operand to whole lines (stage_rule.h)
+  float* stage;                   // scratch for that copy, stage_cols floats per column of the matrix; NULL, or a launch
+  int stage_cols;                 // that needs more: the same launch gathers from the operand itself
   isp_tuning tune;
   const int32_t* perm;     // transposes only
   float* t_values_rw;      // transposes only: the values array (in the workspace), writable
@@ -130,19 +131,18 @@ size_t isp_scan_tmp_bytes(int64_t n);
 isp_status isp_scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, void* tmp, hipStream_t s);
 isp_status isp_scan_i32_to_i32(const int32_t* in, int32_t* out, int64_t n, void* tmp, hipStream_t s);
 
+// Partial rows of v's scratch that any operation writes: FusedMM wider than 256 columns has up to four to a segment.
+static inline int64_t isp_busy_rows(const isp_csr* A) {
+  const int64_t r = 4 * (int64_t)A->v.n_seg;
+  return r < A->partial_rows ? r : A->partial_rows;
+}
+
 // Rows of a scratch that serves v and vp of a second handle with A's partitions (the shared transpose: transpose.hip).
 // The pieces can outnumber what the ordinary partition is laid out for: they start at half its smallest piece, from
 // half its row length (70,000 rows of 290 entries: 273,000 pieces, 262,000 rows).
 static inline int64_t isp_shared_rows(const isp_csr* A) {
   return A->partial_rows > A->spmm_rows ? A->partial_rows : A->spmm_rows;
 }
-
-// ---- ragged dense operands (spmm.hip) ---------------------------------------------------------
-// Rows of a dense operand that do not start on 128-byte lines make every gathered slice touch one line more than it
-// holds.  Where a column has many entries a SpMM copies the columns of each launch to whole lines first.
-#define ISP_STAGE_COLS 128
-// Bytes of the copy for a matrix of this shape; 0 where it does not pay.
-size_t isp_stage_bytes(int64_t n_cols, int64_t nnz);
 
 // ---- partition (csr_build.hip) ---------------------------------------------------------------
 size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz);
@@ -151,6 +151,9 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
                             const int32_t* indices, const float* values, void* ws, size_t ws_bytes,
                             bool validate, hipStream_t s, isp_csr** out, const int* flag = nullptr,
                             int* host_flag = nullptr);
+// The first of n rooms that holds the copies of A's ragged operands becomes their place; A takes none if there is none.
+namespace isp_stage { struct room; }
+void isp_place_stage(isp_csr* A, isp_stage::room* rooms, int n);
 // out[q] = values[pos[q]] for nnz > 0 entries.
 isp_status isp_gather_values(const int32_t* pos, const float* values, int64_t nnz, float* out, hipStream_t s);
 // Copy A's (rewritten) values into the packed SpMM layout's own value array again.

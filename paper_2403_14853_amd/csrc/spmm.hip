@@ -3,6 +3,7 @@
 // (Section 3.3).  Gather-bound: per nonzero one 4*d-byte row of X is fetched and d FMAs are done,
 // so the kernels are built around coalesced row gathers, not around matrix cores.
 #include "run_stream.h"
+#include "stage_rule.h"
 
 namespace {
 using namespace isp_dev;
@@ -271,10 +272,6 @@ int64_t tile_lines(const float* X, int64_t ldx, int d, int tile, int64_t n_cols)
   return sum;
 }
 
-// Floats per row of the copy of w columns: whole lines, or the part of one (16 floats, 8) that the row fits, so that rows share
-// lines but none is cut.
-int stage_pitch(int w) { return w <= 8 ? 8 : w <= 16 ? 16 : (w + 31) & ~31; }
-
 // Copy of columns [k0, k0 + w) of X, row by row, to rows of `pitch` floats (what lies behind column w is never
 // read).  pitch / 4 lanes per row; the last lane of a row that is no multiple of 4 moves back.
 __global__ void __launch_bounds__(256) k_stage_cols(const float* __restrict__ X, int64_t ldx, int64_t n, int k0, int w,
@@ -336,22 +333,15 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
   // ISP_SPMM_LPG / ISP_SPMM_TILE (read when the handle was built) override the choices for tuning.
   const bool packed = A->has_packed && (!values_override || values_override_packed);
   int tile = av.nnz >= 2000000 && ldx % 32 == 0 ? 128 : ISP_PARTIAL_TILE;
-  // The copy of a ragged operand costs one pass over X and a launch per 128 columns, and saves the lines that row ends
-  // cut.  It is taken from 12 columns up where a column has 32 entries or more (isp_stage_bytes), the work outweighs the
-  // launches (8 Mi entries, or 2e9 multiply-adds) and the lines a row touches on average fall by a fifth, or by 5 % beyond 128
-  // columns, which the copies also let run 128 at a time.  us per SpMM without / with it (mean over several X in turn): 233 k
-  // columns, 115 M entries: 602 columns 13853 / 11816, 301 7200 / 6140, 50 1404 / 1241; 2.4 M, 124 M: 301 15246 / 12698, 50
-  // 2745 / 2507; 1 M, 40 M: 602 9066 / 8221, 140 2337 / 2078, 50 852 / 793, 28 557 / 409, 12 366 / 361; 200 k, 20 M: 140 795 / 719, 20
-  // 178 / 153, 12 145 / 141; 200 k, 6.4 M: 602 1425 / 1206.  Outside the rule: 1 M, 40 M: 6 302 / 328, 9 352 / 357, 42 752 / 770, 76
-  // 1197 / 1264; 1 M, 16 M: 602 4720 / 4870; 50 k, 1.5 M: 602 290 / 330; 10 k, 1 M: 602 154 / 196; 50 k, 6 M: 20 58 / 61; 100
-  // columns, whose 400 bytes touch four lines anyway: 2349 / 2426 (233 k), 4832 / 5364 (2.4 M).
+  // Are the columns of each launch copied to whole lines first?  (Rule and figures: stage_rule.h.)
   const bool stage = A->stages && d >= 4 &&
                      (A->tune.stage_always ? ldx % 32 != 0 || !aligned(X, 128)
-                                           : d >= 12 && (av.nnz >= ((int64_t)8 << 20) || av.nnz * d >= 2000000000) &&
-                                                 100 * tile_lines(X, ldx, d, tile, av.n_cols) >=
-                                                     (d > 128 ? 105 : 120) * tile_lines(nullptr, 32, d, ISP_STAGE_COLS, av.n_cols));
-  if (stage) tile = ISP_STAGE_COLS;
+                                           : isp_stage::call_pays(av.nnz, d, tile_lines(X, ldx, d, tile, av.n_cols),
+                                                                  tile_lines(nullptr, 32, d, isp_stage::COLS, av.n_cols)));
+  if (stage) tile = isp_stage::COLS;
   if (A->tune.spmm_tile) tile = A->tune.spmm_tile;
+  // (a handle with the packed layout may keep its copies among the rows that launches on the other partition write)
+  const bool place_free = packed || !A->has_packed;
   const bool slices = (ldx % 32 == 0 || stage) && av.n_cols >= (packed ? 512 << 10 : 80 << 10);
   isp_status st = ISP_OK;
   for (int k0 = 0, w; k0 < d && st == ISP_OK; k0 += w) {
@@ -367,8 +357,8 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
     const float* Xt = X;  // what this launch gathers from
     int64_t ldt = ldx;
     // (a launch whose groups reach beyond w, which only the overrides make, gathers from X)
-    if (stage && A->stage && w <= ISP_STAGE_COLS && (k_base + w == d || ns * 4 * lpg == w)) {
-      ldt = stage_pitch(w);
+    if (stage && A->stage && place_free && isp_stage::pitch(w) <= A->stage_cols && (k_base + w == d || ns * 4 * lpg == w)) {
+      ldt = isp_stage::pitch(w);
       k_stage_cols<<<(unsigned)((av.n_cols + 31) / 32), 256, 0, s>>>(X, ldx, av.n_cols, k_base, w, (int)ldt, A->stage);
       ISP_LAUNCH_CHECK();
       Xt = A->stage - k_base;

@@ -1,0 +1,77 @@
+// Copies of ragged dense operands (spmm.hip): which handles keep room for one, which calls take one, and how much
+// workspace that costs.  Host arithmetic only, so that it can be checked without a device.
+//
+// Rows of a dense operand that do not start on 128-byte lines make every gathered slice touch one line more than it holds.
+// The copy (k_stage_cols: the columns of one launch, row by row, to whole lines) costs one pass over X and a launch per 128
+// columns.  us per SpMM without / with it, mean over several X in turn:
+//   233 k columns, 115 M entries: 602 columns 13853 / 11816, 301 7200 / 6140, 50 1404 / 1241;
+//   2.4 M, 124 M: 301 15246 / 12698, 50 2745 / 2507;
+//   1 M, 40 M: 602 9066 / 8221, 140 2337 / 2078, 50 852 / 793, 28 557 / 409, 12 366 / 361;
+//   200 k, 20 M: 140 795 / 719, 20 178 / 153, 12 145 / 141;  200 k, 6.4 M: 602 1425 / 1206.
+// Outside the rule:
+//   1 M, 40 M: 6 302 / 328, 9 352 / 357, 42 752 / 770, 76 1197 / 1264;  1 M, 16 M: 602 4720 / 4870;
+//   50 k, 1.5 M: 602 290 / 330;  10 k, 1 M: 602 154 / 196;  50 k, 6 M: 20 58 / 61;
+//   100 columns, whose 400 bytes touch four lines anyway: 2349 / 2426 (233 k), 4832 / 5364 (2.4 M).
+#pragma once
+#include "partition_sizes.h"
+
+namespace isp_stage {
+
+constexpr int COLS = 128;  // columns of a launch that gathers from a copy
+constexpr int ALIGN = 32;  // floats of a line
+
+// A handle keeps room for 128 columns where a column has so many entries that its row is gathered far more often than
+// copied, and the matrix is of a size at which any call takes a copy.
+constexpr int64_t MIN_PER_COL = 32, MIN_NNZ = 3000000;
+// A call takes the copy from 12 columns up, where the work outweighs the launches, and where the lines that a row touches
+// fall by a fifth, or by 5 % beyond 128 columns, which the copies also let run 128 at a time.
+constexpr int MIN_D = 12;
+constexpr int64_t MANY_NNZ = (int64_t)8 << 20, MANY_MULS = 2000000000;
+constexpr int LINES_NARROW = 120, LINES_WIDE = 105;  // per cent
+
+inline bool call_pays(int64_t nnz, int d, int64_t lines, int64_t lines_copied) {
+  return d >= MIN_D && (nnz >= MANY_NNZ || nnz * d >= MANY_MULS) &&
+         100 * lines >= (d > COLS ? LINES_WIDE : LINES_NARROW) * lines_copied;
+}
+
+// Floats per row of the copy of w columns: whole lines, or the part of one (16 floats, 8) that the row fits, so that rows
+// share lines but none is cut.
+inline int pitch(int w) { return w <= 8 ? 8 : w <= 16 ? 16 : (w + ALIGN - 1) / ALIGN * ALIGN; }
+
+// The widest pitch that calls of up to max_d columns ask for; `always`: ISP_STAGE_MIN is set.
+inline int pitch_up_to(int max_d, bool always) {
+  return max_d < (always ? 4 : MIN_D) ? 0 : pitch(max_d < COLS ? max_d : COLS);
+}
+
+inline size_t bytes(int64_t n_cols, int n_floats) { return isp_align((size_t)n_cols * n_floats * sizeof(float)); }
+
+// Bytes that a matrix of this shape needs for its copies; 0 where none is taken.  ISP_STAGE_MIN (entries per column; 0 = no
+// copies) overrides the rule and its limit on the size.
+inline size_t wanted(int64_t n_cols, int64_t nnz) {
+  const int forced = isp_part::env_int("ISP_STAGE_MIN", -1, -1, 1 << 20);
+  if (n_cols <= 0 || forced == 0) return 0;
+  if (forced > 0 ? nnz / n_cols < forced : nnz / n_cols < MIN_PER_COL || nnz < MIN_NNZ) return 0;
+  return bytes(n_cols, COLS);
+}
+
+// Workspace laid out for the copies besides the partial rows.  These are sized for the worst case, some 12 bytes per entry
+// where the copies ask for at most 16, and a SpMM leaves most of them idle; with the packed layout it leaves all rows of the
+// ordinary partition, so that only what those lack is added and the copies always have a place.  Without it (less than 8 Mi
+// entries, less than 64 Ki columns, or more than 256 Mi entries) the copies have workspace of their own up to OWN_MAX
+// and beyond that whatever is idle, or there are none.
+constexpr size_t OWN_MAX = (size_t)128 << 20;
+inline size_t own_bytes(int64_t n_cols, int64_t nnz, size_t partial_bytes, bool packed) {
+  const size_t b = wanted(n_cols, nnz);
+  if (packed) return b > partial_bytes ? isp_align(b - partial_bytes) : 0;
+  return b <= OWN_MAX ? b : 0;
+}
+
+// A stretch of workspace that nothing else uses while a copy is.
+struct room { char *begin, *end; };
+inline float* take(room& r, size_t n) {
+  if (r.end < r.begin || (size_t)(r.end - r.begin) < n) return nullptr;
+  r.end -= n;
+  return reinterpret_cast<float*>(r.end);
+}
+
+}  // namespace isp_stage

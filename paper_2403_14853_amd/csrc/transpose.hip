@@ -10,6 +10,7 @@
 #include <new>
 #include "block_scan.h"
 #include "host_slot.h"
+#include "stage_rule.h"
 
 namespace {
 using namespace isp_dev;
@@ -467,18 +468,18 @@ t_layout make_layout(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_value
   return L;
 }
 
-// Bytes share_handle takes of the transpose's workspace.
+// Bytes share_handle takes of the transpose's workspace (besides the copy of a ragged operand).
 size_t share_bytes(const isp_csr* A) {
   return isp_align((size_t)isp_shared_rows(A) * ISP_PARTIAL_TILE * sizeof(float)) +
-         (A->stages ? isp_align((size_t)A->v.n_cols * ISP_STAGE_COLS * sizeof(float)) : 0) +
          (A->has_packed ? isp_align((size_t)A->v.nnz * sizeof(float)) : 0);
 }
 
 // The transpose's handle when its offsets and indices equal A's: A's partition tables and packed layout, which are
-// only read, serve both; values and scratch are its own (scratch: share_bytes of workspace, the partial rows of
-// either partition in front, the copy of a ragged operand and the packed values behind them).
+// only read, serve both; values and scratch are its own (scratch: the partial rows of either partition in front, then the
+// packed values, share_bytes in all; the copy of a ragged operand behind them, or among the partial rows that are not
+// written).
 isp_status share_handle(const isp_csr* A, const int64_t* t_indptr, const int32_t* t_indices, float* t_values,
-                        char* scratch, hipStream_t s, isp_csr** out) {
+                        char* scratch, char* scratch_end, hipStream_t s, isp_csr** out) {
   isp_csr* At = new (std::nothrow) isp_csr(*A);
   if (!At) return isp_fail(ISP_ENOMEM, "host allocation of the handle failed");
   At->At = nullptr;
@@ -487,18 +488,23 @@ isp_status share_handle(const isp_csr* A, const int64_t* t_indptr, const int32_t
   At->v.values = t_values;
   At->v.partials = (float*)scratch;
   At->partial_rows = isp_shared_rows(A);
-  scratch += isp_align((size_t)At->partial_rows * ISP_PARTIAL_TILE * sizeof(float));
-  if (A->stages) {
-    At->stage = (float*)scratch;
-    scratch += isp_align((size_t)A->v.n_cols * ISP_STAGE_COLS * sizeof(float));
-  }
+  const size_t row = ISP_PARTIAL_TILE * sizeof(float);
+  char* rows_end = scratch + isp_align((size_t)At->partial_rows * row);
+  char* behind = rows_end;
   if (A->has_packed) {
-    At->packed_values_rw = t_values ? (float*)scratch : nullptr;
+    At->packed_values_rw = t_values ? (float*)behind : nullptr;
     At->vp.values = At->packed_values_rw;
     At->vp.partials = At->v.partials;
+    behind += isp_align((size_t)A->v.nnz * sizeof(float));
   } else {
     At->vp = At->v;
   }
+  const int64_t busy = isp_busy_rows(At);
+  scratch_end -= (uintptr_t)scratch_end & 255;
+  isp_stage::room rooms[3] = {{behind, scratch_end},
+                              {scratch + (size_t)(busy > At->spmm_rows ? busy : At->spmm_rows) * row, rows_end},
+                              {scratch + (size_t)At->spmm_rows * row, rows_end}};
+  isp_place_stage(At, rooms, 3);
   const isp_status st = isp_refresh_packed_values(At, s);
   if (st != ISP_OK) { delete At; return st; }
   *out = At;
@@ -606,7 +612,7 @@ isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_
     if (host_flag) h_differs = *host_flag;
   }
   if (ask_first && h_differs == 0 && share_bytes(A) <= ws_bytes - L.part) {
-    if ((st = share_handle(A, t_indptr, t_indices, t_values, base + L.part, s, &At)) != ISP_OK) return st;
+    if ((st = share_handle(A, t_indptr, t_indices, t_values, base + L.part, base + ws_bytes, s, &At)) != ISP_OK) return st;
   } else {
     // (on a small one the flag comes to the host with the partition's counters)
     int* with_counters = ask_first ? nullptr : host_flag;

@@ -115,3 +115,20 @@ def test_counter_records_know_their_source(repo_root, tmp_path):
     assert bench.source_digest("sddmm") is None
     rec = bench.counter_record("c3-rmat2.4m-d128", "k_spmm_grouped")
     assert rec["current"] in (True, False)
+
+
+@pytest.mark.parametrize("n,nnz", [(2_449_029, 123_629_211), (232_965, 114_629_852), (1_000_000, 33_000_000), (70_000, 8_400_000),
+                                   (100_000, 4_500_000), (60_000, 60_000_000), (4_000_000, 300_000_000), (60_000_000, 2_000_000_000)])
+def test_room_for_copies_of_ragged_operands(n, nnz, monkeypatch):
+    """What the copies add to the build workspace: nothing or little where the packed layout leaves partial rows idle, never
+    more than 5 bytes per entry there and 128 MiB elsewhere."""
+    for key in list(os.environ):
+        if key.startswith("ISP_"):
+            monkeypatch.delenv(key)
+    with_copies = isp.csr_build_workspace(n, n, nnz)
+    monkeypatch.setenv("ISP_STAGE_MIN", "0")
+    extra = with_copies - isp.csr_build_workspace(n, n, nnz)
+    packed = (8 << 20) <= nnz <= (256 << 20) and n >= 1 << 16
+    assert 0 <= extra <= (5 * nnz if packed else (128 << 20))
+    if packed and nnz >= 48 * n:
+        assert extra == 0

@@ -62,6 +62,55 @@ def test_against_the_oracle(graph, d, ld, shift):
     B.destroy()
 
 
+# The copies' place in the workspace: among the packed layout's idle partial rows (many entries per column), in place of
+# the ordinary partition's (few: the copies then need all of them), behind it (no packed layout).
+@pytest.mark.parametrize("per_row,mid", [(60, 16), (5, 100), (60, 0)])
+@pytest.mark.parametrize("d", [20, 130, 301])
+def test_places_of_the_copies(per_row, mid, d):
+    print("[case] place", per_row, mid, d, flush=True)
+    n, hub = 3000, 700
+    rng = np.random.default_rng(per_row)
+    rows = np.concatenate([rng.integers(0, n, n * per_row), np.repeat([7, 8, n - 1], hub)])
+    code = np.unique(rows * n + rng.integers(0, n, rows.size))
+    indptr = np.concatenate([[0], np.cumsum(np.bincount(code // n, minlength=n))]).astype(np.int64)
+    indices, values = (code % n).astype(np.int32), rng.standard_normal(code.size).astype(np.float32)
+    env = {"ISP_STAGE_MIN": "1", "ISP_MID_THRESHOLD": str(mid)}
+    os.environ.update(env)
+    try:
+        A = build(indptr, indices, values)
+        At, _ = isp.csr_transpose_cached(A)
+    finally:
+        for k in env:
+            os.environ.pop(k)
+    assert (A.info()["spmm_pieces"] > 0) == (mid > 0) and A.info()["n_segments"] > 0
+    X, Xh = _operand(rng, n, d, d, 1)
+    Y, Z, dX = (torch.full((n, d), float("nan"), device="cuda") for _ in range(3))
+    arg = torch.empty(n, d, dtype=torch.int32, device="cuda")
+    ref = oracle.spmm(indptr, indices, values, Xh)
+    ti, tj, _, tv = oracle.transpose(n, n, indptr, indices, values)
+    for _ in range(2):  # (and among the partial rows of other operations: the calls on a handle follow each other)
+        isp.spmm(A, X, Y)
+        assert_close(Y, *ref, "spmm")
+        isp.spmm_reduce(A, X, Z, "max", arg)
+        top, at, _ = oracle.spmm_reduce(indptr, indices, values, Xh, "max")
+        assert np.array_equal(Z.cpu().numpy(), top) and np.array_equal(arg.cpu().numpy(), at)
+        isp.spmm(At, X, dX)
+        assert_close(dX, *oracle.spmm(ti, tj, tv, Xh), "spmm on the transpose")
+        isp.fusedmm(A, X[:, :20], Z[:, :20])
+        assert_close(Z[:, :20], *oracle.fusedmm(indptr, indices, values, np.ascontiguousarray(Xh[:, :20])), "fusedmm")
+    # an alias for narrow calls has little room or none; wider ones still give the same bits
+    for max_d in (3, 16, d):
+        B = isp.csr_alias(A, max_d=max_d)
+        isp.spmm(B, X, Z)
+        assert torch.equal(Y, Z)
+        isp.spmm(isp.csr_transpose_cached(B)[0], X, Z)
+        assert torch.equal(dX, Z)
+        B.destroy()
+    assert isp.csr_alias_workspace(A, max_d=128) - isp.csr_alias_workspace(A, max_d=16) == 2 * 4 * n * (128 - 16)
+    assert isp.csr_alias_workspace(A, max_d=16) - isp.csr_alias_workspace(A, max_d=3) == 2 * 4 * n * 16
+    A.destroy()
+
+
 def test_non_finite_rows_stay_where_they_are(graph):
     w, A, _, _ = graph
     print("[case] staged, one infinite row", flush=True)
