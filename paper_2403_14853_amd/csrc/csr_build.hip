@@ -1011,14 +1011,6 @@ size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz) {
   return make_packed_layout(n_rows, nnz, true, p1, mid_t, own).total;
 }
 
-void isp_place_stage(isp_csr* A, isp_stage::room* rooms, int n) {
-  const size_t b = isp_stage::wanted(A->v.n_cols, A->v.nnz);
-  A->stage = nullptr;
-  for (int k = 0; k < n && b > 0 && !A->stage; ++k) A->stage = isp_stage::take(rooms[k], b);
-  A->stages = A->stage != nullptr;
-  A->stage_cols = A->stages ? isp_stage::COLS : 0;
-}
-
 isp_status isp_gather_values(const int32_t* pos, const float* values, int64_t nnz, float* out, hipStream_t s) {
   if (nnz >= GV_MANY_NNZ)
     k_gather_values<8><<<(unsigned)((nnz + 256 * 8 - 1) / (256 * 8)), 256, 0, s>>>(pos, values, nnz, out);
@@ -1103,7 +1095,7 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
       {base + P.cut.partials + (A->has_packed ? A->info.spmm_pieces : 0) * PARTIAL_ROW, base + P.cut.total},
       {rows + isp_busy_rows(A) * PARTIAL_ROW, base + rows_end},
       {rows + (A->has_packed ? 0 : A->v.n_seg) * PARTIAL_ROW, base + rows_end}};
-  isp_place_stage(A, rooms + (mid_t > 0 ? 0 : 1), mid_t > 0 ? 3 : 2);
+  isp_stage::place(A, rooms + (mid_t > 0 ? 0 : 1), mid_t > 0 ? 3 : 2);
   *out = A;
   return ISP_OK;
 }

@@ -9,6 +9,9 @@
 #define ISP_WG 256                 // threads per workgroup in the row-streaming kernels
 #define ISP_WAVES_PER_WG (ISP_WG / ISP_WAVE)
 #define ISP_PARTIAL_TILE 256       // floats per hub-segment partial row (one column tile)
+// Partial rows one call of isp_spmm_static_scratch may use: 32 MiB per device, held from the first use of the library on
+// that device until the process ends.
+#define ISP_STATIC_SCRATCH_ROWS 32768
 
 // Device-side view of a CSR with its work partition.  Passed to kernels by value.
 struct isp_view {
@@ -77,6 +80,8 @@ struct isp_csr {
   bool stages;                    // SpMM copies the columns of a ragged dense operand to whole lines (stage_rule.h)
   float* stage;                   // scratch for that copy, stage_cols floats per column of the matrix; NULL, or a launch
   int stage_cols;                 // that needs more: the same launch gathers from the operand itself
+  float* static_stage;            // the same (128 floats) for isp_spmm_static_scratch, whose calls follow each other on a GPU
+                                  // whatever handles they use: aliases share it.  No other call writes there.
   isp_tuning tune;
   const int32_t* perm;     // transposes only
   float* t_values_rw;      // transposes only: the values array (in the workspace), writable
@@ -151,9 +156,6 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
                             const int32_t* indices, const float* values, void* ws, size_t ws_bytes,
                             bool validate, hipStream_t s, isp_csr** out, const int* flag = nullptr,
                             int* host_flag = nullptr);
-// The first of n rooms that holds the copies of A's ragged operands becomes their place; A takes none if there is none.
-namespace isp_stage { struct room; }
-void isp_place_stage(isp_csr* A, isp_stage::room* rooms, int n);
 // out[q] = values[pos[q]] for nnz > 0 entries.
 isp_status isp_gather_values(const int32_t* pos, const float* values, int64_t nnz, float* out, hipStream_t s);
 // Copy A's (rewritten) values into the packed SpMM layout's own value array again.

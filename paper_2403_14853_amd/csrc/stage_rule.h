@@ -66,12 +66,26 @@ inline size_t own_bytes(int64_t n_cols, int64_t nnz, size_t partial_bytes, bool 
   return b <= OWN_MAX ? b : 0;
 }
 
-// A stretch of workspace that nothing else uses while a copy is.
+// A stretch of workspace, 256-byte aligned.
 struct room { char *begin, *end; };
 inline float* take(room& r, size_t n) {
   if (r.end < r.begin || (size_t)(r.end - r.begin) < n) return nullptr;
   r.end -= n;
   return reinterpret_cast<float*>(r.end);
+}
+
+// The first of n rooms that holds the copies of A's ragged operands becomes their place; without one A takes none.  No other
+// call writes in the rooms but in the last, which takes in the one before it to its end: the calls on a handle follow each
+// other, the last room serves all the same.  isp_spmm_static_scratch, where it serves the handle, gets a place in what is
+// left of the others (nothing that would hold it, if the first copy had to take the last).
+inline void place(isp_csr* A, room* rooms, int n) {
+  const size_t b = wanted(A->v.n_cols, A->v.nnz);
+  A->stage = A->static_stage = nullptr;
+  for (int k = 0; k < n && b > 0 && !A->stage; ++k) A->stage = take(rooms[k], b);
+  A->stages = A->stage != nullptr;
+  A->stage_cols = A->stages ? COLS : 0;
+  if (!A->stages || A->spmm_rows > ISP_STATIC_SCRATCH_ROWS) return;
+  for (int k = 0; k < n - 1 && !A->static_stage; ++k) A->static_stage = take(rooms[k], b);
 }
 
 }  // namespace isp_stage

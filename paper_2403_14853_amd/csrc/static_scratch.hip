@@ -4,13 +4,11 @@
 // isp_csr_build.  This variant runs the same kernels with those partial rows in a fixed array in the
 // library's own device image instead: no buffer besides X and Y is taken from the caller or from an
 // allocator, and the call itself makes no HIP allocation (nor does isp_spmm; the difference is where the
-// scratch lives).  The array exists once per GPU, for every handle and every call.
+// scratch lives).  The array exists once per GPU, for every handle and every call.  (The copy of a ragged operand is as large as
+// the operand's columns are many: it lies in the handle's workspace, among rows that nothing else writes.)
 #include <mutex>
-#include "isp_internal.h"
+#include "stage_rule.h"
 
-// Partial-sum rows (ISP_PARTIAL_TILE floats each) one call may use: 32,768 rows = 32 MiB per device, held
-// from the first use of the library on that device until the process ends.
-#define ISP_STATIC_SCRATCH_ROWS 32768
 // (No attribute such as `used` here: the compiler gives this internal-linkage array a global symbol in the
 // device image because host code takes its address below, and that symbol is what the runtime looks up; with
 // `used` the symbol stays local and the lookup aborts the process.)
@@ -60,6 +58,13 @@ extern "C" isp_status isp_spmm_static_scratch(const isp_csr_t* A, const float* X
   isp_csr view = *A;
   view.v.partials = ptr;
   view.vp.partials = ptr;
-  view.stage = nullptr;  // (ragged operands are gathered from where they are, by the same launches: same results)
+  // A ragged operand is copied to a place in the handle's workspace that no other call writes.  Without one (little idle
+  // room) it is gathered from where it is, by the same launches, so that the results stay isp_spmm's: 128 columns at a time,
+  // the slower way to gather rows that start anywhere.  us without / with the copies / 256 at a time without (no hub segments):
+  // 250 k columns, 10 M entries: 140 columns 1220 / 900 / 920, 301 2485 / 1860 / 2230, 602 4845 / 3525 / 4165; 600 k, 24 M: 200
+  // 3600 / 3250 / 3345, 602 11575 / 9040 / 10020; 60 k, 12 M: 140 1030 / 813 / 887, 602 4525 / 3400 / 4500.  100 k, 4.4 M, 2,483
+  // segments, has no room: 602 columns 1760, 256 at a time 1650.
+  view.stage = A->static_stage;
+  view.stage_cols = A->static_stage ? isp_stage::COLS : 0;
   return isp_spmm_launch(&view, X, ldx, d, Y, ldy, (hipStream_t)stream);
 }

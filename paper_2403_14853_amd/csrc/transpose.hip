@@ -504,7 +504,7 @@ isp_status share_handle(const isp_csr* A, const int64_t* t_indptr, const int32_t
   isp_stage::room rooms[3] = {{behind, scratch_end},
                               {scratch + (size_t)(busy > At->spmm_rows ? busy : At->spmm_rows) * row, rows_end},
                               {scratch + (size_t)At->spmm_rows * row, rows_end}};
-  isp_place_stage(At, rooms, 3);
+  isp_stage::place(At, rooms, 3);
   const isp_status st = isp_refresh_packed_values(At, s);
   if (st != ISP_OK) { delete At; return st; }
   *out = At;

@@ -1,0 +1,75 @@
+"""Places of SpMM's copies of ragged operands in the workspace, on the CPU (csrc/stage_rule.h): over rooms of every relative
+size a copy lies in a room, the one for the static-scratch entry point only where no other call writes, and the two apart;
+and the workspace that the sizes ask for always holds the copies where the packed layout exists."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <stdio.h>
+#include "stage_rule.h"
+using namespace isp_part;
+using isp_stage::room;
+
+static char* at(int64_t kib) { return (char*)((1 << 20) + kib * 1024); }
+static bool in(const float* p, size_t b, char* lo, char* hi) { return (char*)p >= lo && (char*)p + b <= hi; }
+static bool apart(const float* p, const float* q, size_t b) { return (char*)p + b <= (char*)q || (char*)q + b <= (char*)p; }
+#define FAIL(...) do { printf(__VA_ARGS__); return 1; } while (0)
+
+int main() {
+  long copies = 0, both = 0, shared = 0;
+  // rows [0, busy) of a partition are written by other calls, of which a SpMM writes the first `used`; `cut` idle rows elsewhere
+  for (int64_t n_cols : {100000, 200000})
+    for (int64_t cut = 0; cut <= 320000; cut += 40000)
+      for (int64_t end = 0; end <= 320000; end += 20000)
+        for (int64_t busy = 0; busy <= end; busy += 20000)
+          for (int64_t used : {(int64_t)0, busy / 4, busy})
+            for (int64_t rows : {100, 40000}) {
+              isp_csr A{};
+              A.v.n_cols = n_cols; A.v.nnz = 40 * n_cols; A.spmm_rows = rows;
+              const size_t b = isp_stage::wanted(n_cols, A.v.nnz);
+              room r[3] = {{at(1000000), at(1000000 + cut)}, {at(busy), at(end)}, {at(used), at(end)}};
+              isp_stage::place(&A, r + (cut ? 0 : 1), cut ? 3 : 2);
+              const bool fits = (size_t)cut * 1024 >= b || (size_t)(end - used) * 1024 >= b;
+              if (A.stages != fits || (A.stage != nullptr) != fits || (fits && A.stage_cols != 128)) FAIL("place missed\n");
+              if (!fits) { if (A.static_stage) FAIL("static copy alone\n"); continue; }
+              ++copies;
+              if (!in(A.stage, b, at(1000000), at(1000000 + cut)) && !in(A.stage, b, at(used), at(end))) FAIL("copy outside\n");
+              shared += !in(A.stage, b, at(1000000), at(1000000 + cut)) && !in(A.stage, b, at(busy), at(end));
+              if (!A.static_stage) continue;
+              ++both;
+              if (rows > ISP_STATIC_SCRATCH_ROWS) FAIL("static copy of a handle that the entry point refuses\n");
+              if (!in(A.static_stage, b, at(1000000), at(1000000 + cut)) && !in(A.static_stage, b, at(busy), at(end)))
+                FAIL("static copy where other calls write\n");
+              if (!apart(A.stage, A.static_stage, b)) FAIL("copies overlap\n");
+            }
+  if (!copies || !both || !shared) FAIL("%ld %ld %ld\n", copies, both, shared);
+  // with the packed layout the rows of the ordinary partition and what is added always hold the copies
+  for (int64_t n : {65536, 100003, 262144, 1000000, 2449029, 8000000})
+    for (int64_t per = 4; per <= 4000; per += per / 4 + 1) {
+      const int64_t nnz = n * per;
+      if (nnz < (8 << 20) || nnz > (256 << 20)) continue;
+      const partition_params p1 = get_params(n, nnz, 4096);
+      const size_t rows = (size_t)(max_segments(n, nnz, p1) + 1) * 1024, own = isp_stage::own_bytes(n, nnz, rows, true);
+      if (rows + own < isp_stage::wanted(n, nnz)) FAIL("no place: %lld x %lld\n", (long long)n, (long long)per);
+    }
+  for (int w = 1, last = 0; w <= 128; ++w) {  // an alias for max_d columns has room for every narrower call
+    const int p = isp_stage::pitch(w);
+    if (p < w || p < last || p > isp_stage::pitch_up_to(w, true) + (w < 4 ? 8 : 0)) FAIL("pitch of %d\n", w);
+    last = p;
+  }
+  return 0;
+}
+"""
+
+
+def test_places(tmp_path):
+    src, exe = tmp_path / "places.cpp", tmp_path / "places"
+    src.write_text(PROGRAM)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__=1", "-I" + os.path.join(ROOT, "include"),
+                           "-I" + os.path.join(ROOT, "paper_2403_14853_amd", "csrc"), "-isystem", "/opt/rocm/include",
+                           str(src), "-o", str(exe)])
+    env = {k: v for k, v in os.environ.items() if not k.startswith("ISP_")}
+    res = subprocess.run([str(exe)], env=env, stdout=subprocess.PIPE, text=True)
+    assert res.returncode == 0, res.stdout
