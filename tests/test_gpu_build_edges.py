@@ -139,6 +139,8 @@ def test_large_symmetric(mid, with_values):
             dX = torch.empty(n, 5, device="cuda")
             isp.spmm(At, dev(G), dX)
             assert_close(dX, *oracle.spmm(ti, tj, new.cpu().numpy()[tp], G), "after new values")
+            isp.spmm(A, dev(G), dX)
+            assert_close(dX, *oracle.spmm(indptr, indices, new.cpu().numpy(), G), "the matrix itself, after new values")
         else:
             A = build(indptr, indices, None)
             At, _ = isp.csr_transpose_cached(A)

@@ -1,6 +1,7 @@
 """Ragged dense operands of SpMM copied to whole lines (rows that start between 128-byte lines, many entries per column):
 forced onto small graphs, at widths around the copies' tiles, at pitches and base addresses of every alignment, against the
-oracle; bit-identical through an alias and the static-scratch entry point, also where those gather from the operand itself."""
+oracle; bit-identical through an alias and the static-scratch entry point, also where those gather from the operand itself;
+on the packed layout, in the mean and its backward, after rewritten values and in a captured graph."""
 import os
 
 import numpy as np
@@ -50,7 +51,7 @@ def test_against_the_oracle(graph, d, ld, shift):
     isp.spmm(A, X, Y)
     assert_close(Y, *oracle.spmm(w.indptr, w.indices, w.values, Xh), "staged spmm")
     again = torch.empty_like(Y)
-    isp.spmm_static_scratch(A, X, again)  # (the same launches without the copies)
+    isp.spmm_static_scratch(A, X, again)  # (the same launches, copies of its own or none)
     assert torch.equal(Y, again)
     B = isp.csr_alias(A, max_d=d)
     isp.spmm(B, X, again)
@@ -62,18 +63,22 @@ def test_against_the_oracle(graph, d, ld, shift):
     B.destroy()
 
 
+def _graph_with_hubs(n, per_row, seed=0):
+    rng = np.random.default_rng(seed)
+    rows = np.concatenate([rng.integers(0, n, n * per_row), np.repeat([7, 8, n - 1], 700)])
+    code = np.unique(rows * n + rng.integers(0, n, rows.size))
+    indptr = np.concatenate([[0], np.cumsum(np.bincount(code // n, minlength=n))]).astype(np.int64)
+    return indptr, (code % n).astype(np.int32), rng.standard_normal(code.size).astype(np.float32)
+
+
 # The copies' place in the workspace: among the packed layout's idle partial rows (many entries per column), in place of
 # the ordinary partition's (few: the copies then need all of them), behind it (no packed layout).
 @pytest.mark.parametrize("per_row,mid", [(60, 16), (5, 100), (60, 0)])
 @pytest.mark.parametrize("d", [20, 130, 301])
 def test_places_of_the_copies(per_row, mid, d):
     print("[case] place", per_row, mid, d, flush=True)
-    n, hub = 3000, 700
-    rng = np.random.default_rng(per_row)
-    rows = np.concatenate([rng.integers(0, n, n * per_row), np.repeat([7, 8, n - 1], hub)])
-    code = np.unique(rows * n + rng.integers(0, n, rows.size))
-    indptr = np.concatenate([[0], np.cumsum(np.bincount(code // n, minlength=n))]).astype(np.int64)
-    indices, values = (code % n).astype(np.int32), rng.standard_normal(code.size).astype(np.float32)
+    n, rng = 3000, np.random.default_rng(per_row)
+    indptr, indices, values = _graph_with_hubs(n, per_row)
     env = {"ISP_STAGE_MIN": "1", "ISP_MID_THRESHOLD": str(mid)}
     os.environ.update(env)
     try:
@@ -108,6 +113,65 @@ def test_places_of_the_copies(per_row, mid, d):
         B.destroy()
     assert isp.csr_alias_workspace(A, max_d=128) - isp.csr_alias_workspace(A, max_d=16) == 2 * 4 * n * (128 - 16)
     assert isp.csr_alias_workspace(A, max_d=16) - isp.csr_alias_workspace(A, max_d=3) == 2 * 4 * n * 16
+    A.destroy()
+
+
+# 602: four tiles of 128 and one of 90; 131: a tile of 128, then one of four columns that starts before it ends, whose copy
+# has rows of 8 floats, and with it a second pitch in the same scratch
+@pytest.mark.parametrize("d", [20, 131, 602])
+@pytest.mark.parametrize("mid", [16, 0])
+def test_reductions_new_values_and_replays(mid, d):
+    print("[case] staged mean, new values, graph", mid, d, flush=True)
+    n, rng = 2000, np.random.default_rng(d)
+    indptr, indices, values = _graph_with_hubs(n, 40)
+    env = {"ISP_STAGE_MIN": "1", "ISP_MID_THRESHOLD": str(mid)}
+    os.environ.update(env)
+    try:
+        vals = torch.from_numpy(values.copy()).cuda()
+        A = isp.csr_build(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), vals)
+        At, _ = isp.csr_transpose_cached(A)
+    finally:
+        for k in env:
+            os.environ.pop(k)
+    assert (A.info()["spmm_pieces"] > 0) == (mid > 0)
+    X, Xh = _operand(rng, n, d, d, 1)
+    G, Gh = _operand(rng, n, d, d + 2, 0)
+    Y, M, dX, dM = outs = [torch.full((n, d), float("nan"), device="cuda") for _ in range(4)]
+
+    def step():
+        isp.spmm(A, X, Y)
+        isp.spmm_reduce(A, X, M, "mean")
+        isp.spmm(At, G, dX)
+        isp.spmm_reduce_backward(A, G, dM, "mean")
+
+    def check(values, what):
+        ti, tj, _, tv = oracle.transpose(n, n, indptr, indices, values)
+        assert_close(Y, *oracle.spmm(indptr, indices, values, Xh), what + ", spmm")
+        assert_close(dX, *oracle.spmm(ti, tj, tv, Gh), what + ", spmm of the transpose")
+        ref, _, mag = oracle.spmm_reduce(indptr, indices, values, Xh, "mean")
+        assert_close(M, ref, mag, what + ", mean")
+        assert_close(dM, *oracle.spmm_reduce_backward(n, indptr, indices, values, Gh, "mean"), what + ", mean backward")
+
+    step()
+    check(values, "eager")
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        step()
+    torch.cuda.synchronize()
+    for rep in range(3):  # every replay on new values and new operands, with eager work of the handle before it
+        new = rng.standard_normal(values.size).astype(np.float32)
+        vals.copy_(torch.from_numpy(new))
+        isp.csr_values_changed(A)
+        isp.spmm(A, torch.randn(n, 37, device="cuda"), torch.empty(n, 37, device="cuda"))
+        Xh[:] = rng.standard_normal((n, d))
+        X.copy_(torch.from_numpy(Xh))
+        for o in outs:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        check(new, "replay %d" % rep)
     A.destroy()
 
 
@@ -148,4 +212,38 @@ def test_large_enough_by_itself():
     ti, tj, _, tv = oracle.transpose(n, n, indptr, cols.reshape(-1), vals)
     isp.spmm(At, X, Y)
     assert_close(Y, *oracle.spmm(ti, tj, tv, Xh), "staged by rule, transpose")
+    A.destroy()
+
+
+def test_rule_on_a_packed_layout_that_the_transpose_shares():
+    """The rule's own choice on a symmetric pattern with cut rows, 140 columns: 128 from one copy, 12 from the next."""
+    print("[case] staged by rule, packed, shared", flush=True)
+    n, d = 70_001, 140
+    rng = np.random.default_rng(1)
+    i, j = rng.integers(0, n, 4_700_000), rng.integers(0, n, 4_700_000)
+    i[:9000] = np.repeat([3, 4, n - 1], 3000)
+    code = np.unique(np.concatenate([i * n + j, j * n + i]))
+    indptr = np.concatenate([[0], np.cumsum(np.bincount(code // n, minlength=n))]).astype(np.int64)
+    indices, values = (code % n).astype(np.int32), rng.standard_normal(code.size).astype(np.float32)
+    assert code.size >= 8 << 20
+    vals = torch.from_numpy(values).cuda()
+    A = isp.csr_build(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), vals)
+    At, _ = isp.csr_transpose_cached(A)
+    assert A.info()["symmetric_pattern"] == 1 and A.info()["spmm_pieces"] == At.info()["spmm_pieces"] > 0
+    Xh = rng.standard_normal((n, d)).astype(np.float32)
+    X = torch.from_numpy(Xh).cuda()
+    Y, Z = torch.empty_like(X), torch.empty_like(X)
+    for turn in range(2):
+        isp.spmm(A, X, Y)
+        isp.spmm_static_scratch(A, X, Z)
+        assert torch.equal(Y, Z)
+        assert_close(Y, *oracle.spmm(indptr, indices, values, Xh), "staged by rule, packed")
+        ti, tj, _, tv = oracle.transpose(n, n, indptr, indices, values)
+        isp.spmm(At, X, Y)
+        isp.spmm_static_scratch(At, X, Z)
+        assert torch.equal(Y, Z)
+        assert_close(Y, *oracle.spmm(ti, tj, tv, Xh), "staged by rule, packed, transpose")
+        values = rng.standard_normal(code.size).astype(np.float32)
+        vals.copy_(torch.from_numpy(values))
+        isp.csr_values_changed(A)
     A.destroy()
