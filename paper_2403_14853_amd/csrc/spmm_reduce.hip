@@ -611,9 +611,11 @@ isp_status fwd_all(const isp_csr* A, const float* X, int64_t ldx, int d, float* 
     const bool ok = av.nnz > 0 && a32 && d >= 4 && A->info.block_cost <= GS_MAX_ROWS &&
                     A->info.block_cost + av.hub_t <= GS_MAX_ENT && av.seg_len <= GS_MAX_ENT && !A->tune.no_grouped;
     if (ok) {
-      // 128 columns per launch (a hub partial row holds 128 values and 128 positions), one slice: the two
-      // 64-column slices that pay for the sum on large graphs cost more here than they save, the loop doing
-      // four compare-and-select steps per entry instead of four multiply-adds (config 3: 7.09 vs 6.05 ms)
+      // 128 columns per launch (a hub partial row holds 128 values and 128 positions), in one slice at every size.  Two
+      // 64-column slices, measured with this kernel (us, one / two): 128 columns 2.4 M rows, 124 M entries 5715 / 5267, 800 k, 40 M
+      // 1579 / 1579, 233 k, 115 M 2770 / 3105; 100 columns 5660 / 6700, 1546 / 1889, 2737 / 3417: they would pay for whole-line
+      // rows of an operand far larger than the L2s alone, as for the sum.  Fewer workgroups per compute unit (15,000 bytes
+      // more LDS each), which pay for the sum on its packed layout, lose in either form (one slice: 5923, 1837, 3944).
       isp_status st = ISP_OK;
       for (int k0 = 0; k0 < d && st == ISP_OK; k0 += 2 * ISP_WAVE) {
         const int k_base = d - k0 < 4 ? d - 4 : k0;  // (no launch narrower than a float4 lane)
