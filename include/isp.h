@@ -223,9 +223,9 @@ isp_status isp_spmm(const isp_csr_t* A, const float* X, int64_t ldx, int32_t d, 
  *     on one GPU (different streams or threads) race, whichever handles they use; calls on one stream are safe;
  *   - nothing in the array needs clearing between calls (each launch writes every partial row it later reads).
  *   - where isp_spmm copies a ragged dense operand (isp_csr_build) this call has room for a copy of its own among the idle partial
- *     rows of the handle's workspace, which no other call writes.  A handle that has too few of them (less than some 48
- *     entries per column, without the packed layout) is served without the copy, by the same launches: more than 128 ragged
- *     columns then take up to a third longer.
+ *     rows of the handle's workspace, which no other call writes.  A handle that has too few of them (some with 32 to 60
+ *     entries per column) is served without the copy, by the same launches: more than 128 ragged columns then take up to a
+ *     third longer than gathered 256 at a time.
  */
 isp_status isp_spmm_static_scratch(const isp_csr_t* A, const float* X, int64_t ldx, int32_t d, float* Y,
                                    int64_t ldy, void* stream);
