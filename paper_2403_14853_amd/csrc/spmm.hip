@@ -78,11 +78,16 @@ isp_status launch_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int
 // MEAN: finished rows are divided by their length (partial rows are not: their fix-up divides).
 constexpr int SPMM_RING = 4;
 
-// On the packed layout, launches wider than 64 columns ask for LDS they do not use, so that a compute unit holds four
-// workgroups instead of five: the rows of X that the whole chip has in flight and in use at a time then fit the L2s better.
-// us per SpMM with five / four / three: 233 k columns, 115 M entries: 128 columns 2518 / 2440 / 2599, 256 5069 / 4905 / 5219; 2.4 M,
-// 124 M: 128 4755 / 4672 / 4804; 200 k, 20 M: 128 565 / 549 / 566; 800 k, 40 M: 100 1481 / 1453 / 1472.  At 64 columns it
-// makes no difference (2326 / 2325), at 32 latency counts (1213 / 1248).
+// On the packed layout, launches that gather more than three and a half lines of a row ask for LDS they do not use, so that a
+// compute unit holds four workgroups instead of five: the rows of X that the whole chip has in flight and in use at a time then
+// fit the L2s better.  With fewer lines the latency counts.  us per SpMM with five / four (/ three):
+//   4 lines and more: 233 k columns, 115 M entries: 128 columns 2518 / 2440 / 2599, 256 5069 / 4905 / 5219, 97 2347 / 2335; 2.4 M, 124 M: 128 4755 /
+//   4672 / 4804, 100 4832 / 4774; 200 k, 20 M: 128 565 / 549 / 566; 800 k, 40 M: 100 1437 / 1418; 400 k, 12 M: 200 1019 / 985;
+//   3.75 and 3.9 (92 and 94 columns, ragged): 400 k, 12 M: 442 / 431, 463 / 449; 1 M, 20 M: 847 / 829, 875 / 861;
+//   3.5 (84, 88 columns, ragged): 233 k, 115 M: 2105 / 2145, 2110 / 2149; 2.4 M, 124 M: 88 4117 / 4109; 500 k, 10 M: 88 384 / 376;
+//   3 to 3.1 (65 to 96): 233 k, 115 M: 69 1956 / 2035, 96 1949 / 2043; 139 k, 43 M: 69 734 / 771; 800 k, 40 M: 72 1028 / 1049, 96 1058 / 1078; 2.4 M,
+//   124 M: 96 3514 / 3572; 80 k, 12 M: 96 222 / 232; copies of 90 columns (96 floats): 233 k 1984 / 2075;
+//   2 (64 columns): 2326 / 2325;  1 (32): 1213 / 1248.
 constexpr unsigned SPMM_FOUR_PER_CU = 160 * 1024 / 4 - sizeof(rn_lds);
 
 template <int LPG, bool ADDR32, int VEC, bool MEAN, int CAP = GS_MAX_ENT>
@@ -215,13 +220,14 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG) * (unsigned)n_slices;
-    const unsigned spare = packed && n_slices * LPG * VEC > 64 ? SPMM_FOUR_PER_CU : 0u;
+    const int width = n_slices * LPG * VEC < d - k_base ? n_slices * LPG * VEC : d - k_base;
+    const unsigned spare = packed && 2 * isp_stage::line_sum((uintptr_t)(X + k_base), ldx, width) > 7 * isp_stage::ALIGN
+                               ? SPMM_FOUR_PER_CU : 0u;
     const bool a32 = v.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
                      ((uint64_t)v.n_cols * (uint64_t)ldx + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
 #define ISP_GO(A32, MN)                                                                                        \
   k_spmm_grouped<LPG, A32, VEC, MN><<<grid, ISP_WG, spare, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
                                                             n_slices, Y, ldy)
-    const int width = n_slices * LPG * VEC < d - k_base ? n_slices * LPG * VEC : d - k_base;
     if (VEC == 4 && a32 && !packed && rn_small_tables(A, v, width, grid)) {
 #define ISP_SMALL(MN)                                                                                              \
   k_spmm_grouped<LPG, true, 4, MN, RN_SMALL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
@@ -260,14 +266,11 @@ int tile_width(int k_base, int d, int tile, int64_t n_cols) {
 
 // 32 times the 128-byte lines that those launches touch of a row of X, on average over the offsets its rows start at.
 int64_t tile_lines(const float* X, int64_t ldx, int d, int tile, int64_t n_cols) {
-  const int base = (int)((uintptr_t)X & 127) / 4;  // (in floats; a line holds 32)
-  int step = 32;
-  while (ldx % step != 0) step /= 2;  // rows start at base + multiples of step
   int64_t sum = 0;
   for (int k0 = 0, w; k0 < d; k0 += w) {
     const int k_base = tile_start(k0, d);
     w = tile_width(k_base, d, tile, n_cols);
-    for (int o = 0; o < 32; o += step) sum += step * (((base + k_base + o) % 32 + w + 31) / 32);
+    sum += isp_stage::line_sum((uintptr_t)X + 4 * (uintptr_t)k_base, ldx, w);
   }
   return sum;
 }

@@ -20,6 +20,17 @@ namespace isp_stage {
 constexpr int COLS = 128;  // columns of a launch that gathers from a copy
 constexpr int ALIGN = 32;  // floats of a line
 
+// 32 times the 128-byte lines that w floats of a row touch, on average over the rows: `ld` floats apart, the first begins at
+// address `at`.
+inline int64_t line_sum(uintptr_t at, int64_t ld, int w) {
+  const int base = (int)(at & (4 * ALIGN - 1)) / 4;  // (in floats)
+  int step = ALIGN;
+  while (ld % step != 0) step /= 2;  // rows begin at base + multiples of step
+  int64_t sum = 0;
+  for (int o = 0; o < ALIGN; o += step) sum += step * (((base + o) % ALIGN + w + ALIGN - 1) / ALIGN);
+  return sum;
+}
+
 // A handle keeps room for 128 columns where a column has so many entries that its row is gathered far more often than
 // copied, and the matrix is of a size at which any call takes a copy.
 constexpr int64_t MIN_PER_COL = 32, MIN_NNZ = 3000000;

@@ -54,6 +54,16 @@ int main() {
       const size_t rows = (size_t)(max_segments(n, nnz, p1) + 1) * 1024, own = isp_stage::own_bytes(n, nnz, rows, true);
       if (rows + own < isp_stage::wanted(n, nnz)) FAIL("no place: %lld x %lld\n", (long long)n, (long long)per);
     }
+  for (int ld = 1; ld <= 140; ++ld)  // lines touched, row by row
+    for (int w = 1; w <= ld; w += 3)
+      for (uintptr_t at : {(uintptr_t)0, (uintptr_t)4, (uintptr_t)64, (uintptr_t)(4096 + 124)}) {
+        int64_t sum = 0;
+        for (int r = 0; r < 32; ++r) {
+          const uintptr_t first = at + (uintptr_t)r * ld * 4, last = first + (uintptr_t)w * 4 - 1;
+          sum += (int64_t)(last / 128 - first / 128 + 1);
+        }
+        if (isp_stage::line_sum(at, ld, w) != sum) FAIL("lines of %d floats, pitch %d\\n", w, ld);
+      }
   for (int w = 1, last = 0; w <= 128; ++w) {  // an alias for max_d columns has room for every narrower call
     const int p = isp_stage::pitch(w);
     if (p < w || p < last || p > isp_stage::pitch_up_to(w, true) + (w < 4 ? 8 : 0)) FAIL("pitch of %d\n", w);
