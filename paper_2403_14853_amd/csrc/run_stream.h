@@ -36,16 +36,16 @@ using rn_lds = rn_lds_of<GS_MAX_ENT>;
 // Tables of 768 entries let a compute unit (160 KB) hold five workgroups, tables of RN_SMALL seven.  Where the items are
 // that small and the dense operand fits the L2s (eight of 4 MB, shared with everything else), the additional wavefronts hide
 // more of the loads' latency; where it does not fit they only spread the chip's gathers over more rows than the L2s
-// keep, and a launch that does not fill five per compute unit gains nothing.  us with tables of 768 / RN_SMALL entries (the launches' rules
-// stand with them):
+// keep, and a launch that does not fill five per compute unit gains nothing (per_cu: workgroups per compute unit that the launch
+// must have more of; the launches' rules stand with them).  us with tables of 768 / RN_SMALL entries:
 //   SpMM: 20 k columns, 400 k entries, 64 columns 14.5 / 13.7; 10 k, 1 M: 16 16.3 / 14.7, 128 33.4 / 32.2; 50 k, 1.5 M: 32 27.1 /
 //   24.2, 64 35.3 / 32.6; beyond the L2s, 100 k, 1 M: 64 (26 MB) 29.4 / 30.0, 100 55.0 / 58.2;
 //   SDDMM: 10 k, 1 M: 16 13.0 / 11.7; 50 k, 1.5 M: 64 31.0 / 27.7; beyond, 100 k, 1 M: 64 27.3 / 28.2; 169 k, 2.4 M: 100 106 / 112.
 constexpr int RN_SMALL = 448;
 constexpr int64_t RN_FIT_BYTES = 24 << 20;
-inline bool rn_small_tables(const isp_csr* A, const isp_view& v, int width, int64_t wgs) {
+inline bool rn_small_tables(const isp_csr* A, const isp_view& v, int width, int64_t wgs, int per_cu) {
   return A->info.block_cost + v.hub_t <= RN_SMALL && v.seg_len <= RN_SMALL && v.n_cols * width * 4 <= RN_FIT_BYTES &&
-         wgs * 16 > 5 * (int64_t)A->wave_slots;  // (16 slots per compute unit)
+         wgs * 16 > per_cu * (int64_t)A->wave_slots;  // (16 slots per compute unit)
 }
 
 // This lane's group's run, and the item's shape.

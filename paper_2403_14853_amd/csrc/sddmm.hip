@@ -131,9 +131,11 @@ isp_status launch_grouped(const isp_csr* A, const float* U, int64_t ldu, const f
   } while (0)
 #define ISP_GO2(A32, AD, CAP) do { if (tail) ISP_GO(A32, AD, true, CAP); else ISP_GO(A32, AD, false, CAP); } while (0)
   if constexpr (LPG <= 16 && W == 4) {
-    // (small tables only with a few hundred entries per wavefront, and up to 64 columns: 50 k columns, 400 k entries, 64
-    // columns 16.0 us with five workgroups, 16.3 with seven; 10 k, 1 M, 128 columns 34.4 and 35.4)
-    if (a32 && v.nnz >= 800000 && rn_small_tables(A, v, d_hi - k_lo, grid)) {
+    // Small tables only where the launch is long enough for the last workgroups to matter less: more than 12 per compute
+    // unit, beyond 32 columns 15.  us with five / seven at a time: 13 k columns, 674 k entries (12.1 per unit): 24 columns 10.2 / 9.4; 39 k,
+    // 993 k (12.3): 32 14.2 / 13.5, but 56 23.5 / 24.6; 111 k, 1.4 M (13.7): 40 31.0 / 33.1; 43 k, 1.2 M (21): 32 19.1 / 16.8; 42 k, 1.5 M (22): 48 29.8 /
+    // 26.5; 35 k, 870 k (10.5): 54 21.3 / 22.4; 51 k, 1 M (11.1): 8 12.9 / 13.4.  Never beyond 64 columns: 10 k, 1 M: 128 34.4 / 35.4.
+    if (a32 && rn_small_tables(A, v, d_hi - k_lo, grid, d_hi - k_lo <= 32 ? 12 : 15)) {
       if (add) ISP_GO2(true, true, RN_SMALL); else ISP_GO2(true, false, RN_SMALL);
       ISP_LAUNCH_CHECK();
       return ISP_OK;

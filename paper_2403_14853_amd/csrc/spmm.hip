@@ -228,7 +228,10 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
 #define ISP_GO(A32, MN)                                                                                        \
   k_spmm_grouped<LPG, A32, VEC, MN><<<grid, ISP_WG, spare, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
                                                             n_slices, Y, ldy)
-    if (VEC == 4 && a32 && !packed && rn_small_tables(A, v, width, grid)) {
+    // (one group to a wavefront, 129 to 224 columns, has work for 14 per compute unit before seven at a time pay: 25 k columns,
+    // 408 k entries, 208 columns (6.6 per unit) 31.4 us with five, 33.8 with seven; 17 k, 601 k: 176 (8.5) 34.7 / 36.7; 23 k, 1 M: 135 (17.2)
+    // 51.2 / 46.8; 22 k, 862 k: 207 (14.8) 51.0 / 49.8)
+    if (VEC == 4 && a32 && !packed && rn_small_tables(A, v, width, grid, LPG == ISP_WAVE ? 14 : 5)) {
 #define ISP_SMALL(MN)                                                                                              \
   k_spmm_grouped<LPG, true, 4, MN, RN_SMALL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
                                                                      n_slices, Y, ldy)

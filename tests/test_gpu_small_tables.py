@@ -12,13 +12,20 @@ from gpu_util import assert_close, build, dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(scope="module", params=[900_000, 1_500_000])
+@pytest.fixture(scope="module", params=[(900_000, False), (1_500_000, False), (1_500_000, True)])
 def graph(request):
-    """Rows of 0 ... hub threshold entries in no order, so that row blocks end with rows of the longest kind, and a few hubs."""
-    rng = np.random.default_rng(request.param)
-    n, nnz = 9_001, request.param
+    """Rows of 0 ... hub threshold entries in no order, so that row blocks end with rows of the longest kind, and a few hubs; or
+    (`many`) most entries in rows that are cut into several segments: enough work items for the rules of every width."""
+    nnz, many = request.param
+    rng = np.random.default_rng(nnz)
+    n = 9_001
     deg = rng.choice([0, 1, 3, 30, 60, 120, 159, 160, 161, 187, 188], n, p=[.1, .1, .1, .1, .1, .1, .1, .1, .1, .05, .05])
     deg[rng.integers(0, n, 5)] = 8_000
+    if many:
+        deg[rng.permutation(n)[:3_900]] = 330
+        deg[deg == 188] = rng.choice([0, 188], int((deg == 188).sum()))
+        deg[deg < 160] //= 30
+        nnz = int(deg.sum())
     deg = (deg * (nnz / deg.sum())).astype(np.int64) if deg.sum() > nnz else deg.astype(np.int64)
     deg[7] += nnz - deg.sum()
     indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
@@ -28,7 +35,8 @@ def graph(request):
     values = rng.standard_normal(nnz).astype(np.float32)
     A = build(indptr, cols, values)
     info = A.info()
-    assert info["block_cost"] + info["hub_threshold"] <= 448 and info["n_row_blocks"] + info["n_segments"] > 5 * 256 * 4
+    assert info["block_cost"] + info["hub_threshold"] <= 448
+    assert info["n_row_blocks"] + info["n_segments"] > (15 if many else 5) * 256 * 4
     yield n, indptr, cols, values, A, build(indptr, cols, None)
     A.destroy()
 
