@@ -339,16 +339,19 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
   // ISP_SPMM_LPG / ISP_SPMM_TILE (read when the handle was built) override the choices for tuning.
   const bool packed = A->has_packed && (!values_override || values_override_packed);
   int tile = av.nnz >= 2000000 && ldx % 32 == 0 ? 128 : ISP_PARTIAL_TILE;
+  const int64_t slice_cols = packed ? 512 << 10 : 80 << 10;
   // Are the columns of each launch copied to whole lines first?  (Rule and figures: stage_rule.h.)
   const bool stage = A->stages && d >= 4 &&
                      (A->tune.stage_always ? ldx % 32 != 0 || !aligned(X, 128)
-                                           : isp_stage::call_pays(av.nnz, d, tile_lines(X, ldx, d, tile, av.n_cols),
-                                                                  tile_lines(nullptr, 32, d, isp_stage::COLS, av.n_cols)));
+                                           : isp_stage::call_pays({av.nnz, av.n_cols, ldx, d, tile_lines(X, ldx, d, tile, av.n_cols),
+                                                                   tile_lines(nullptr, 32, d, isp_stage::COLS, av.n_cols), packed,
+                                                                   av.n_cols >= slice_cols,
+                                                                   2 * (int64_t)A->info.spmm_cut_rows > av.n_rows}));
   if (stage) tile = isp_stage::COLS;
   if (A->tune.spmm_tile) tile = A->tune.spmm_tile;
   // (a handle with the packed layout may keep its copies among the rows that launches on the other partition write)
   const bool place_free = packed || !A->has_packed;
-  const bool slices = (ldx % 32 == 0 || stage) && av.n_cols >= (packed ? 512 << 10 : 80 << 10);
+  const bool slices = (ldx % 32 == 0 || stage) && av.n_cols >= slice_cols;
   isp_status st = ISP_OK;
   for (int k0 = 0, w; k0 < d && st == ISP_OK; k0 += w) {
     const int k_base = tile_start(k0, d);

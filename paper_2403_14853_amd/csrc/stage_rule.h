@@ -11,7 +11,11 @@
 // Outside the rule:
 //   1 M, 40 M: 6 302 / 328, 9 352 / 357, 42 752 / 770, 76 1197 / 1264;  1 M, 16 M: 602 4720 / 4870;
 //   50 k, 1.5 M: 602 290 / 330;  10 k, 1 M: 602 154 / 196;  50 k, 6 M: 20 58 / 61;
-//   100 columns, whose 400 bytes touch four lines anyway: 2349 / 2426 (233 k), 4832 / 5364 (2.4 M).
+//   100 columns, whose 400 bytes touch four lines anyway: 2349 / 2426 (233 k), 4832 / 5364 (2.4 M);
+//   cut, without slices: 500 k, 16.5 M: 500 2750 / 2869, 602 3387 / 3418, 19 M: 500 3057 / 3142 (inside: 22 M: 301 2226 / 2120, 602
+//   4267 / 4049);
+//   uniform, all rows cut: 350 k, 105 M: 17 1273 / 1445, 20 1407 / 1444; 150 k, 45 M: 50 985 / 1042 (inside: 350 k: 13 1082 / 964, 22 1626 /
+//   1445, 28 2088 / 1452; 150 k: 28 528 / 396).
 #pragma once
 #include "partition_sizes.h"
 
@@ -39,15 +43,31 @@ constexpr int64_t MIN_PER_COL = 32, MIN_NNZ = 3000000;
 constexpr int MIN_D = 12;
 constexpr int64_t MANY_NNZ = (int64_t)8 << 20, MANY_MULS = 2000000000;
 constexpr int LINES_NARROW = 120, LINES_WIDE = 105;  // per cent
+// On the packed layout, where most gathers hit the L2s, the lines saved have to outweigh the lines copied, unless the copies
+// also give two slices: a copied line costs as much as gathering five.
+constexpr int COPIED_LINE = 5;
 
-inline bool call_pays(int64_t nnz, int d, int64_t lines, int64_t lines_copied) {
-  return d >= MIN_D && (nnz >= MANY_NNZ || nnz * d >= MANY_MULS) &&
-         100 * lines >= (d > COLS ? LINES_WIDE : LINES_NARROW) * lines_copied;
-}
+// What a call brings along: lines and lines_copied in the units of line_sum; cut: it runs on the packed layout, two_slices:
+// its 128-column launches run as two slices if they gather from copies, long_rows: more than half of the rows are cut.
+struct call {
+  int64_t nnz, n_cols, ldx;
+  int d;
+  int64_t lines, lines_copied;
+  bool cut, two_slices, long_rows;
+};
 
 // Floats per row of the copy of w columns: whole lines, or the part of one (16 floats, 8) that the row fits, so that rows
 // share lines but none is cut.
 inline int pitch(int w) { return w <= 8 ? 8 : w <= 16 ? 16 : (w + ALIGN - 1) / ALIGN * ALIGN; }
+
+inline bool call_pays(const call& c) {
+  if (c.d < MIN_D || (c.nnz < MANY_NNZ && c.nnz * c.d < MANY_MULS)) return false;
+  if (100 * c.lines < (c.d > COLS ? LINES_WIDE : LINES_NARROW) * c.lines_copied) return false;
+  if (c.cut && !c.two_slices && c.nnz / c.n_cols * (c.lines - c.lines_copied) < COPIED_LINE * c.lines_copied) return false;
+  // Where most rows are cut, all are long: no columns are popular, the L2s keep the band in work alone, and a copy that takes more
+  // room than X by a larger factor than it saves lines makes more of them miss.
+  return !(c.cut && c.long_rows && c.d <= COLS && c.lines * c.ldx < c.lines_copied * pitch(c.d));
+}
 
 // The widest pitch that calls of up to max_d columns ask for; `always`: ISP_STAGE_MIN is set.
 inline int pitch_up_to(int max_d, bool always) {

@@ -64,6 +64,18 @@ int main() {
         }
         if (isp_stage::line_sum(at, ld, w) != sum) FAIL("lines of %d floats, pitch %d\\n", w, ld);
       }
+  // the rule on calls whose both sides are measured: packed X of d columns, `lines` of it per row and in its copy
+  struct { int64_t n, nnz; int d, long_rows; bool pays; } calls[] = {
+      {500000, 16500000, 500, 0, false}, {500000, 16500000, 602, 0, false}, {500000, 22000000, 602, 0, true}, {1000000, 33000000, 500, 0, true},
+      {232965, 114600001, 602, 0, true}, {233000, 115000000, 100, 0, false}, {1000000, 40000000, 12, 0, true}, {1000000, 40000000, 9, 0, false},
+      {350000, 105000000, 17, 1, false}, {350000, 105000000, 17, 0, true}, {350000, 105000000, 22, 1, true}, {350000, 105000000, 13, 1, true}};
+  for (auto& q : calls) {
+    int64_t lines = 0, copied = 0;
+    for (int k = 0; k < q.d; k += 256) lines += isp_stage::line_sum(4 * k, q.d, q.d - k < 256 ? q.d - k : 256);
+    for (int k = 0; k < q.d; k += 128) copied += isp_stage::line_sum(0, 32, q.d - k < 128 ? q.d - k : 128);
+    if (isp_stage::call_pays({q.nnz, q.n, q.d, q.d, lines, copied, true, q.n >= 512 << 10, q.long_rows != 0}) != q.pays)
+      FAIL("%d columns of %lld\\n", q.d, (long long)q.n);
+  }
   for (int w = 1, last = 0; w <= 128; ++w) {  // an alias for max_d columns has room for every narrower call
     const int p = isp_stage::pitch(w);
     if (p < w || p < last || p > isp_stage::pitch_up_to(w, true) + (w < 4 ? 8 : 0)) FAIL("pitch of %d\n", w);
