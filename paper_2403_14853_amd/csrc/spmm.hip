@@ -259,25 +259,6 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
-// The launches that cover d columns: first column (a last tile of fewer than 4 columns starts earlier and computes some
-// columns again: float4 lanes) and width of the one that continues at k0.
-int tile_start(int k0, int d) { return d >= 4 && d - k0 < 4 ? d - 4 : k0; }
-int tile_width(int k_base, int d, int tile, int64_t n_cols) {
-  const int w = d - k_base < tile ? d - k_base : tile;
-  return w > 128 && w <= 224 && n_cols >= 512 << 10 ? 128 : w;
-}
-
-// 32 times the 128-byte lines that those launches touch of a row of X, on average over the offsets its rows start at.
-int64_t tile_lines(const float* X, int64_t ldx, int d, int tile, int64_t n_cols) {
-  int64_t sum = 0;
-  for (int k0 = 0, w; k0 < d; k0 += w) {
-    const int k_base = tile_start(k0, d);
-    w = tile_width(k_base, d, tile, n_cols);
-    sum += isp_stage::line_sum((uintptr_t)X + 4 * (uintptr_t)k_base, ldx, w);
-  }
-  return sum;
-}
-
 // Copy of columns [k0, k0 + w) of X, row by row, to rows of `pitch` floats (what lies behind column w is never
 // read).  pitch / 4 lanes per row; the last lane of a row that is no multiple of 4 moves back.
 __global__ void __launch_bounds__(256) k_stage_cols(const float* __restrict__ X, int64_t ldx, int64_t n, int k0, int w,
@@ -343,19 +324,20 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
   // Are the columns of each launch copied to whole lines first?  (Rule and figures: stage_rule.h.)
   const bool stage = A->stages && d >= 4 &&
                      (A->tune.stage_always ? ldx % 32 != 0 || !aligned(X, 128)
-                                           : isp_stage::call_pays({av.nnz, av.n_cols, ldx, d, tile_lines(X, ldx, d, tile, av.n_cols),
-                                                                   tile_lines(nullptr, 32, d, isp_stage::COLS, av.n_cols), packed,
+                                           : isp_stage::call_pays({av.nnz, av.n_cols, ldx, d,
+                                                                   isp_stage::operand_lines((uintptr_t)X, ldx, d, tile, av.n_cols),
+                                                                   isp_stage::copied_lines(d, av.n_cols), packed,
                                                                    av.n_cols >= slice_cols,
                                                                    2 * (int64_t)A->info.spmm_cut_rows > av.n_rows}));
-  if (stage) tile = isp_stage::COLS;
+  if (stage || (A->stages && A->tune.stage_always)) tile = isp_stage::COLS;  // (the latter for aligned X too: same launches)
   if (A->tune.spmm_tile) tile = A->tune.spmm_tile;
   // (a handle with the packed layout may keep its copies among the rows that launches on the other partition write)
   const bool place_free = packed || !A->has_packed;
   const bool slices = (ldx % 32 == 0 || stage) && av.n_cols >= slice_cols;
   isp_status st = ISP_OK;
   for (int k0 = 0, w; k0 < d && st == ISP_OK; k0 += w) {
-    const int k_base = tile_start(k0, d);
-    w = tile_width(k_base, d, tile, av.n_cols);
+    const int k_base = isp_stage::tile_start(k0, d);
+    w = isp_stage::tile_width(k_base, d, tile, av.n_cols);
     int lpg = 32;
     if (w <= 16 && av.nnz >= 1000000) lpg = 4;
     else if (w <= 32) lpg = 8;

@@ -35,6 +35,33 @@ inline int64_t line_sum(uintptr_t at, int64_t ld, int w) {
   return sum;
 }
 
+// The launches that cover d columns: first column (a last tile of fewer than 4 columns starts earlier and computes some
+// columns again: float4 lanes) and width of the one that continues at k0.
+inline int tile_start(int k0, int d) { return d >= 4 && d - k0 < 4 ? d - 4 : k0; }
+inline int tile_width(int k_base, int d, int tile, int64_t n_cols) {
+  const int w = d - k_base < tile ? d - k_base : tile;
+  return w > 128 && w <= 224 && n_cols >= 512 << 10 ? 128 : w;
+}
+
+// line_sum of all of them.
+inline int64_t tile_lines(uintptr_t at, int64_t ldx, int d, int tile, int64_t n_cols) {
+  int64_t sum = 0;
+  for (int k0 = 0, w; k0 < d; k0 += w) {
+    const int k_base = tile_start(k0, d);
+    w = tile_width(k_base, d, tile, n_cols);
+    sum += line_sum(at + 4 * (uintptr_t)k_base, ldx, w);
+  }
+  return sum;
+}
+
+// The lines that a call on X touches, and with copies, for its rule.  The same values give the same bits wherever X lies,
+// so its address counts only where a copy leaves the launches as they are: rows of whole lines (128 columns at a time anyway)
+// and less than 128 columns (one launch).  Other rows count as if the first began a line.
+inline int64_t operand_lines(uintptr_t at, int64_t ldx, int d, int tile, int64_t n_cols) {
+  return tile_lines(ldx % ALIGN == 0 || d < COLS ? at : 0, ldx, d, tile, n_cols);
+}
+inline int64_t copied_lines(int d, int64_t n_cols) { return tile_lines(0, ALIGN, d, COLS, n_cols); }
+
 // A handle keeps room for 128 columns where a column has so many entries that its row is gathered far more often than
 // copied, and the matrix is of a size at which any call takes a copy.
 constexpr int64_t MIN_PER_COL = 32, MIN_NNZ = 3000000;

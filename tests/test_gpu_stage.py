@@ -215,6 +215,27 @@ def test_large_enough_by_itself():
     A.destroy()
 
 
+def test_same_bits_wherever_the_operand_lies():
+    """Widths and pitches whose rows touch as many lines as their copies or more, by where the first row begins in one."""
+    n, deg = 70_001, 126
+    rng = np.random.default_rng(4)
+    off = np.sort(rng.permutation(n)[:deg])
+    cols = np.sort((np.arange(n)[:, None] + off[None, :]) % n, axis=1).astype(np.int32).reshape(-1)
+    indptr = np.arange(n + 1, dtype=np.int64) * deg
+    A = build(indptr, cols, rng.standard_normal(cols.size).astype(np.float32))
+    for d, ld in ((40, 48), (132, 136), (140, 144), (192, 192), (270, 272)):
+        print("[case] bases", d, ld, flush=True)
+        X = torch.randn(n, d, device="cuda")
+        first = None
+        for shift in (0, 1, 5, 8, 14, 31):
+            V = torch.empty(n * ld + shift + 32, device="cuda")[shift:shift + n * ld].view(n, ld)[:, :d]
+            V.copy_(X)
+            Y = isp.spmm(A, V, torch.empty(n, d, device="cuda"))
+            first = Y if first is None else first
+            assert torch.equal(first, Y), "base %d" % shift
+    A.destroy()
+
+
 def test_rule_on_a_packed_layout_that_the_transpose_shares():
     """The rule's own choice on a symmetric pattern with cut rows, 140 columns: 128 from one copy, 12 from the next."""
     print("[case] staged by rule, packed, shared", flush=True)

@@ -64,6 +64,17 @@ int main() {
         }
         if (isp_stage::line_sum(at, ld, w) != sum) FAIL("lines of %d floats, pitch %d\\n", w, ld);
       }
+  // from 128 columns up a copy changes the launches, hence the order of the sums: X's address has no say in it, but where
+  // rows are whole lines and run 128 columns at a time with and without
+  long by_base = 0;
+  for (int d = 12; d <= 640; ++d)
+    for (int64_t ld = d; ld <= d + 24; ++ld)
+      for (uintptr_t at = 4; at < 128; at += 4)
+        if (isp_stage::operand_lines(4096 + at, ld, d, 256, 100000) != isp_stage::operand_lines(4096, ld, d, 256, 100000)) {
+          if (d >= 128 && ld % 32 != 0) FAIL("%d columns, pitch %d, base %d\n", d, (int)ld, (int)at);
+          ++by_base;
+        }
+  if (!by_base) FAIL("no call looks at the address\n");
   // the rule on calls whose both sides are measured: packed X of d columns, `lines` of it per row and in its copy
   struct { int64_t n, nnz; int d, long_rows; bool pays; } calls[] = {
       {500000, 16500000, 500, 0, false}, {500000, 16500000, 602, 0, false}, {500000, 22000000, 602, 0, true}, {1000000, 33000000, 500, 0, true},
