@@ -260,7 +260,7 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
 // Copy of columns [k0, k0 + w) of X, row by row, to rows of `pitch` floats (what lies behind column w is never
-// read).  pitch / 4 lanes per row; the last lane of a row that is no multiple of 4 moves back.
+// read).  32 lanes per row, of which the first ceil(w / 4) have work; the last one of a row that is no multiple of 4 moves back.
 __global__ void __launch_bounds__(256) k_stage_cols(const float* __restrict__ X, int64_t ldx, int64_t n, int k0, int w,
                                                     int pitch, float* __restrict__ out) {
   const int q = threadIdx.x & 31;
@@ -326,7 +326,7 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
                      (A->tune.stage_always ? ldx % 32 != 0 || !aligned(X, 128)
                                            : isp_stage::call_pays({av.nnz, av.n_cols, ldx, d,
                                                                    isp_stage::operand_lines((uintptr_t)X, ldx, d, tile, av.n_cols),
-                                                                   isp_stage::copied_lines(d, av.n_cols), packed,
+                                                                   isp_stage::copied_lines(d), packed,
                                                                    av.n_cols >= slice_cols,
                                                                    2 * (int64_t)A->info.spmm_cut_rows > av.n_rows}));
   if (stage || (A->stages && A->tune.stage_always)) tile = isp_stage::COLS;  // (the latter for aligned X too: same launches)

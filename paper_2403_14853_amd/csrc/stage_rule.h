@@ -7,7 +7,9 @@
 //   233 k columns, 115 M entries: 602 columns 13853 / 11816, 301 7200 / 6140, 50 1404 / 1241;
 //   2.4 M, 124 M: 301 15246 / 12698, 50 2745 / 2507;
 //   1 M, 40 M: 602 9066 / 8221, 140 2337 / 2078, 50 852 / 793, 28 557 / 409, 12 366 / 361;
-//   200 k, 20 M: 140 795 / 719, 20 178 / 153, 12 145 / 141;  200 k, 6.4 M: 602 1425 / 1206.
+//   200 k, 20 M: 140 795 / 719, 20 178 / 153, 12 145 / 141;  200 k, 6.4 M: 602 1425 / 1206;
+//   257 columns, whose last launch starts 3 columns earlier: 233 k, 115 M 6616 / 5744; 2.4 M, 60 M 8092 / 7392; 200 k, 20 M 1510 / 1355;
+//   200 k, 6.4 M 694 / 596.
 // Outside the rule:
 //   1 M, 40 M: 6 302 / 328, 9 352 / 357, 42 752 / 770, 76 1197 / 1264;  1 M, 16 M: 602 4720 / 4870;
 //   50 k, 1.5 M: 602 290 / 330;  10 k, 1 M: 602 154 / 196;  50 k, 6 M: 20 58 / 61;
@@ -60,7 +62,16 @@ inline int64_t tile_lines(uintptr_t at, int64_t ldx, int d, int tile, int64_t n_
 inline int64_t operand_lines(uintptr_t at, int64_t ldx, int d, int tile, int64_t n_cols) {
   return tile_lines(ldx % ALIGN == 0 || d < COLS ? at : 0, ldx, d, tile, n_cols);
 }
-inline int64_t copied_lines(int d, int64_t n_cols) { return tile_lines(0, ALIGN, d, COLS, n_cols); }
+// (every copied tile begins its rows at lines, or within the part of one that they fit: also the last tile that starts earlier)
+inline int64_t copied_lines(int d) {
+  int64_t sum = 0;
+  for (int k0 = 0, w; k0 < d; k0 += w) {
+    const int k_base = tile_start(k0, d);
+    w = d - k_base < COLS ? d - k_base : COLS;
+    sum += line_sum(0, ALIGN, w);
+  }
+  return sum;
+}
 
 // A handle keeps room for 128 columns where a column has so many entries that its row is gathered far more often than
 // copied, and the matrix is of a size at which any call takes a copy.

@@ -75,6 +75,14 @@ int main() {
           ++by_base;
         }
   if (!by_base) FAIL("no call looks at the address\n");
+  // a copy's rows begin at lines in every tile
+  for (int d = 4; d <= 640; ++d) {
+    int64_t sum = d < 128 ? (d + 31) / 32 : d / 128 * 4 + (d % 128 == 0 ? 0 : d % 128 < 4 ? 1 : (d % 128 + 31) / 32);
+    if (isp_stage::copied_lines(d) != 32 * sum) FAIL("copied lines of %d columns\n", d);
+  }
+  for (int d : {257, 258, 259, 385, 387})  // (measured: 4 to 14 % faster with copies)
+    if (!isp_stage::call_pays({20000000, 200000, d, d, isp_stage::operand_lines(0, d, d, 256, 200000), isp_stage::copied_lines(d), true, false, false}))
+      FAIL("%d columns are not copied\n", d);
   // the rule on calls whose both sides are measured: packed X of d columns, `lines` of it per row and in its copy
   struct { int64_t n, nnz; int d, long_rows; bool pays; } calls[] = {
       {500000, 16500000, 500, 0, false}, {500000, 16500000, 602, 0, false}, {500000, 22000000, 602, 0, true}, {1000000, 33000000, 500, 0, true},
