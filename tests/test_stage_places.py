@@ -95,6 +95,12 @@ int main() {
     if (isp_stage::call_pays({q.nnz, q.n, q.d, q.d, lines, copied, true, q.n >= 512 << 10, q.long_rows != 0}) != q.pays)
       FAIL("%d columns of %lld\\n", q.d, (long long)q.n);
   }
+  struct { int64_t n, nnz; int d; bool pays; } sliced[] = {
+      {524300, 17000000, 200, false}, {524300, 17000000, 500, false}, {524300, 17000000, 140, true}, {560000, 20000000, 200, false}, {560000, 20000000, 602, true},
+      {640000, 21000000, 200, false}, {640000, 21000000, 301, true}, {800000, 26000000, 200, true}, {1400000, 46000000, 500, true}};
+  for (auto& q : sliced)
+    if (isp_stage::call_pays({q.nnz, q.n, q.d, q.d, isp_stage::operand_lines(0, q.d, q.d, 256, q.n), isp_stage::copied_lines(q.d), true, true, false}) != q.pays)
+      FAIL("two slices: %d columns of %lld\n", q.d, (long long)q.n);
   for (int w = 1, last = 0; w <= 128; ++w) {  // an alias for max_d columns has room for every narrower call
     const int p = isp_stage::pitch(w);
     if (p < w || p < last || p > isp_stage::pitch_up_to(w, true) + (w < 4 ? 8 : 0)) FAIL("pitch of %d\n", w);
