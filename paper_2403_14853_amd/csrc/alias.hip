@@ -36,7 +36,7 @@ alias_layout make_alias_layout(const isp_csr* A, int32_t max_d) {
   off += isp_align((size_t)L.rows_t * ISP_PARTIAL_TILE * sizeof(float));
   L.off_flags = off;
   if (A->At) off += isp_align((size_t)A->v.nnz + 4);  // (cleared in 32-bit words)
-  L.stage_cols = isp_stage::pitch_up_to(max_d, A->tune.stage_always);
+  L.stage_cols = isp_stage::pitch_up_to(max_d, A->tune.stage_min > 0);
   auto stage = [&](const isp_csr* h) { return h && h->stage ? isp_stage::bytes(h->v.n_cols, L.stage_cols) : 0; };
   L.off_stage = off;
   off += stage(A);

@@ -46,7 +46,7 @@ isp_tuning isp_read_tuning() {
   t.spmm_lpg = (lpg == 4 || lpg == 8 || lpg == 16 || lpg == 32 || lpg == 64) ? lpg : 0;
   const int tile = env_int("ISP_SPMM_TILE", 0, 0, 256);
   t.spmm_tile = (tile == 64 || tile == 128 || tile == 256) ? tile : 0;
-  t.stage_always = env_int("ISP_STAGE_MIN", -1, -1, 1 << 20) > 0;
+  t.stage_min = isp_stage::read_min();
   t.wide_groups = env_int("ISP_WIDE_GROUPS", 0, 0, 4);
   t.no_mirror = getenv("ISP_NO_MIRROR") != nullptr;
   const int fw = env_int("ISP_FUSED_W", 0, 0, 8);
@@ -1002,11 +1002,11 @@ isp_status build_packed(isp_csr* A, const partition_params& p1, int mid_t, char*
 
 }  // namespace
 
-size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz) {
+size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int stage_min) {
   const partition_params p1 = get_params(n_rows, nnz, isp_wave_slots());
   const ws_layout L = make_layout(n_rows, nnz, p1);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, p1);
-  const size_t own = L.total + isp_stage::own_bytes(n_cols, nnz, L.total - L.partials, mid_t > 0);
+  const size_t own = L.total + isp_stage::own_bytes(n_cols, nnz, L.total - L.partials, mid_t > 0, stage_min);
   if (mid_t == 0) return own;
   return make_packed_layout(n_rows, nnz, true, p1, mid_t, own).total;
 }
@@ -1042,12 +1042,12 @@ isp_status isp_refresh_packed_pair(isp_csr* A, hipStream_t s) {
 
 isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const int64_t* indptr,
                             const int32_t* indices, const float* values, void* ws, size_t ws_bytes, bool validate,
-                            hipStream_t s, isp_csr** out, const int* flag, int* host_flag) {
+                            const isp_tuning& tune, hipStream_t s, isp_csr** out, const int* flag, int* host_flag) {
   const partition_params pp = get_params(n_rows, nnz, isp_wave_slots());
   const ws_layout L = make_layout(n_rows, nnz, pp);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, pp);
   packed_layout P{};
-  const size_t rows_end = L.total + isp_stage::own_bytes(n_cols, nnz, L.total - L.partials, mid_t > 0);
+  const size_t rows_end = L.total + isp_stage::own_bytes(n_cols, nnz, L.total - L.partials, mid_t > 0, tune.stage_min);
   size_t need = rows_end;
   if (mid_t > 0) {
     P = make_packed_layout(n_rows, nnz, values != nullptr, pp, mid_t, need);
@@ -1066,7 +1066,7 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   if (!A) return isp_fail(ISP_ENOMEM, "host allocation of the handle failed");
   A->device = device;
   A->wave_slots = isp_wave_slots();
-  A->tune = isp_read_tuning();
+  A->tune = tune;
   fill_view(A->v, n_rows, n_cols, nnz, indptr, indices, values, po, pp);
   A->vp = A->v;
   A->partial_rows = L.max_seg + 1;

@@ -1,7 +1,7 @@
 // The C ABI (include/isp.h): argument checks, error reporting, dispatch.  No device code here.
 #include <stdarg.h>
 #include <stdio.h>
-#include "isp_internal.h"
+#include "stage_rule.h"
 
 namespace {
 thread_local char g_err[512] = "";
@@ -32,7 +32,7 @@ isp_status isp_csr_build_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, 
   if (!bytes) return isp_fail(ISP_EINVAL, "bytes is NULL");
   isp_status st = check_shape(n_rows, n_cols, nnz);
   if (st != ISP_OK) return st;
-  *bytes = isp_partition_workspace(n_rows, n_cols, nnz);
+  *bytes = isp_partition_workspace(n_rows, n_cols, nnz, isp_stage::read_min());
   return ISP_OK;
 }
 
@@ -49,7 +49,7 @@ isp_status isp_csr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int6
   if (flags & ~ISP_TRUSTED) return isp_fail(ISP_EUNSUPPORTED, "unknown flag bits 0x%x", flags & ~ISP_TRUSTED);
   if (n_rows == 0 && nnz != 0) return isp_fail(ISP_EBADCSR, "nnz must be 0 when n_rows is 0");
   return isp_build_handle(n_rows, n_cols, nnz, indptr, indices, values, workspace, workspace_bytes,
-                          !(flags & ISP_TRUSTED), (hipStream_t)stream, out);
+                          !(flags & ISP_TRUSTED), isp_read_tuning(), (hipStream_t)stream, out);
 }
 
 }  // extern "C"
@@ -77,7 +77,7 @@ extern "C" {
 
 isp_status isp_csr_transpose_workspace(const isp_csr_t* A, size_t* bytes) {
   if (!A || !bytes) return isp_fail(ISP_EINVAL, "NULL argument");
-  *bytes = isp_transpose_workspace_bytes(A->v.n_rows, A->v.n_cols, A->v.nnz, A->v.values != nullptr);
+  *bytes = isp_transpose_workspace_bytes(A);
   return ISP_OK;
 }
 

@@ -55,7 +55,7 @@ struct isp_tuning {
   int spmm_tile;        // ISP_SPMM_TILE: feature columns per launch of the grouped SpMM (0 = chosen by shape)
   bool no_mirror;       // ISP_NO_MIRROR: the FusedMM backward never takes the one-pass form of symmetric patterns
   int fused_w;          // ISP_FUSED_W: 4 / 8 = the grouped FusedMM kernels give a lane one / two float4 at every width above 32 (0 = chosen by width and graph)
-  bool stage_always;    // ISP_STAGE_MIN given: ragged operands are copied whatever the width and the size
+  int stage_min;        // ISP_STAGE_MIN (stage_rule.h): above 0, ragged operands are copied whatever the width and the size
   int wide_groups;      // ISP_WIDE_GROUPS: most column groups a hub segment stores per launch of a wide FusedMM pass (0 = as many as fit)
 };
 isp_tuning isp_read_tuning();
@@ -150,12 +150,14 @@ static inline int64_t isp_shared_rows(const isp_csr* A) {
 }
 
 // ---- partition (csr_build.hip) ---------------------------------------------------------------
-size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz);
-// flag / host_flag (pinned), optional: *flag as earlier launches on s leave it has arrived in *host_flag on return.
+// stage_min: isp_tuning's, of the handle to be built.
+size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int stage_min);
+// tune: the handle's settings.  flag / host_flag (pinned), optional: *flag as earlier launches on s leave it has arrived in
+// *host_flag on return.
 isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const int64_t* indptr,
                             const int32_t* indices, const float* values, void* ws, size_t ws_bytes,
-                            bool validate, hipStream_t s, isp_csr** out, const int* flag = nullptr,
-                            int* host_flag = nullptr);
+                            bool validate, const isp_tuning& tune, hipStream_t s, isp_csr** out,
+                            const int* flag = nullptr, int* host_flag = nullptr);
 // out[q] = values[pos[q]] for nnz > 0 entries.
 isp_status isp_gather_values(const int32_t* pos, const float* values, int64_t nnz, float* out, hipStream_t s);
 // Copy A's (rewritten) values into the packed SpMM layout's own value array again.
@@ -164,7 +166,7 @@ isp_status isp_refresh_packed_values(isp_csr* A, hipStream_t s);
 isp_status isp_refresh_packed_pair(isp_csr* A, hipStream_t s);
 
 // ---- transpose (transpose.hip) ---------------------------------------------------------------
-size_t isp_transpose_workspace_bytes(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_values);
+size_t isp_transpose_workspace_bytes(const isp_csr* A);
 isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_t s);
 // Gather the cached transpose's values again from A's (rewritten) values.
 isp_status isp_transpose_refresh_values(isp_csr* A, hipStream_t s);

@@ -323,13 +323,13 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
   const int64_t slice_cols = packed ? 512 << 10 : 80 << 10;
   // Are the columns of each launch copied to whole lines first?  (Rule and figures: stage_rule.h.)
   const bool stage = A->stages && d >= 4 &&
-                     (A->tune.stage_always ? ldx % 32 != 0 || !aligned(X, 128)
+                     (A->tune.stage_min > 0 ? ldx % 32 != 0 || !aligned(X, 128)
                                            : isp_stage::call_pays({av.nnz, av.n_cols, ldx, d,
                                                                    isp_stage::operand_lines((uintptr_t)X, ldx, d, tile, av.n_cols),
                                                                    isp_stage::copied_lines(d), packed,
                                                                    av.n_cols >= slice_cols,
                                                                    2 * (int64_t)A->info.spmm_cut_rows > av.n_rows}));
-  if (stage || (A->stages && A->tune.stage_always)) tile = isp_stage::COLS;  // (the latter for aligned X too: same launches)
+  if (stage || (A->stages && A->tune.stage_min > 0)) tile = isp_stage::COLS;  // (the latter for aligned X too: same launches)
   if (A->tune.spmm_tile) tile = A->tune.spmm_tile;
   // (a handle with the packed layout may keep its copies among the rows that launches on the other partition write)
   const bool place_free = packed || !A->has_packed;

@@ -16,6 +16,8 @@
 //   100 columns, whose 400 bytes touch four lines anyway: 2349 / 2426 (233 k), 4832 / 5364 (2.4 M);
 //   cut, without slices: 500 k, 16.5 M: 500 2750 / 2869, 602 3387 / 3418, 19 M: 500 3057 / 3142 (inside: 22 M: 301 2226 / 2120, 602
 //   4267 / 4049);
+//   cut, two slices: 524 k, 17 M: 200 1238 / 1325, 500 2956 / 3123; 560 k, 20 M: 200 1493 / 1531 (inside: 257 2046 / 2022); 640 k, 21 M:
+//   200 1632 / 1671 (inside: 301 2532 / 2445; 800 k, 26 M: 200 2089 / 2102, 500 4939 / 4927; 1.4 M, 46 M: 200 3990 / 3858, 500 9639 / 8954);
 //   uniform, all rows cut: 350 k, 105 M: 17 1273 / 1445, 20 1407 / 1444; 150 k, 45 M: 50 985 / 1042 (inside: 350 k: 13 1082 / 964, 22 1626 /
 //   1445, 28 2088 / 1452; 150 k: 28 528 / 396).
 #pragma once
@@ -81,9 +83,10 @@ constexpr int64_t MIN_PER_COL = 32, MIN_NNZ = 3000000;
 constexpr int MIN_D = 12;
 constexpr int64_t MANY_NNZ = (int64_t)8 << 20, MANY_MULS = 2000000000;
 constexpr int LINES_NARROW = 120, LINES_WIDE = 105;  // per cent
-// On the packed layout, where most gathers hit the L2s, the lines saved have to outweigh the lines copied, unless the copies
-// also give two slices: a copied line costs as much as gathering five.
-constexpr int COPIED_LINE = 5;
+// On the packed layout, where most gathers hit the L2s, the lines saved have to outweigh the lines copied: a copied line costs
+// as much as gathering five, or four where the copies also give two slices.  From SLICES_FAR columns on these save enough by themselves.
+constexpr int COPIED_LINE = 5, COPIED_LINE_SLICES = 4;
+constexpr int64_t SLICES_FAR = 640 << 10;
 
 // What a call brings along: lines and lines_copied in the units of line_sum; cut: it runs on the packed layout, two_slices:
 // its 128-column launches run as two slices if they gather from copies, long_rows: more than half of the rows are cut.
@@ -101,7 +104,9 @@ inline int pitch(int w) { return w <= 8 ? 8 : w <= 16 ? 16 : (w + ALIGN - 1) / A
 inline bool call_pays(const call& c) {
   if (c.d < MIN_D || (c.nnz < MANY_NNZ && c.nnz * c.d < MANY_MULS)) return false;
   if (100 * c.lines < (c.d > COLS ? LINES_WIDE : LINES_NARROW) * c.lines_copied) return false;
-  if (c.cut && !c.two_slices && c.nnz / c.n_cols * (c.lines - c.lines_copied) < COPIED_LINE * c.lines_copied) return false;
+  const int copied_line = c.two_slices ? COPIED_LINE_SLICES : COPIED_LINE;
+  if (c.cut && !(c.two_slices && c.n_cols >= SLICES_FAR) &&
+      c.nnz / c.n_cols * (c.lines - c.lines_copied) < copied_line * c.lines_copied) return false;
   // Where most rows are cut, all are long: no columns are popular, the L2s keep the band in work alone, and a copy that takes more
   // room than X by a larger factor than it saves lines makes more of them miss.
   return !(c.cut && c.long_rows && c.d <= COLS && c.lines * c.ldx < c.lines_copied * pitch(c.d));
@@ -114,11 +119,16 @@ inline int pitch_up_to(int max_d, bool always) {
 
 inline size_t bytes(int64_t n_cols, int n_floats) { return isp_align((size_t)n_cols * n_floats * sizeof(float)); }
 
-// Bytes that a matrix of this shape needs for its copies; 0 where none is taken.  ISP_STAGE_MIN (entries per column; 0 = no
-// copies) overrides the rule and its limit on the size.
-inline size_t wanted(int64_t n_cols, int64_t nnz) {
-  const int forced = isp_part::env_int("ISP_STAGE_MIN", -1, -1, 1 << 20);
-  if (n_cols <= 0 || forced == 0) return 0;
+// ISP_STAGE_MIN (entries per column; 0 = no copies) overrides the rule and its limit on the size: isp_tuning::stage_min, 0 where
+// it is not set and -1 for no copies.
+inline int read_min() {
+  const int m = isp_part::env_int("ISP_STAGE_MIN", -1, -1, 1 << 20);
+  return m < 0 ? 0 : m == 0 ? -1 : m;
+}
+
+// Bytes that a matrix of this shape needs for its copies; 0 where none is taken.
+inline size_t wanted(int64_t n_cols, int64_t nnz, int forced = 0) {
+  if (n_cols <= 0 || forced < 0) return 0;
   if (forced > 0 ? nnz / n_cols < forced : nnz / n_cols < MIN_PER_COL || nnz < MIN_NNZ) return 0;
   return bytes(n_cols, COLS);
 }
@@ -129,8 +139,8 @@ inline size_t wanted(int64_t n_cols, int64_t nnz) {
 // entries, less than 64 Ki columns, or more than 256 Mi entries) the copies have workspace of their own up to OWN_MAX
 // and beyond that whatever is idle, or there are none.
 constexpr size_t OWN_MAX = (size_t)128 << 20;
-inline size_t own_bytes(int64_t n_cols, int64_t nnz, size_t partial_bytes, bool packed) {
-  const size_t b = wanted(n_cols, nnz);
+inline size_t own_bytes(int64_t n_cols, int64_t nnz, size_t partial_bytes, bool packed, int forced = 0) {
+  const size_t b = wanted(n_cols, nnz, forced);
   if (packed) return b > partial_bytes ? isp_align(b - partial_bytes) : 0;
   return b <= OWN_MAX ? b : 0;
 }
@@ -148,7 +158,7 @@ inline float* take(room& r, size_t n) {
 // other, the last room serves all the same.  isp_spmm_static_scratch, where it serves the handle, gets a place in what is
 // left of the others (nothing that would hold it, if the first copy had to take the last).
 inline void place(isp_csr* A, room* rooms, int n) {
-  const size_t b = wanted(A->v.n_cols, A->v.nnz);
+  const size_t b = wanted(A->v.n_cols, A->v.nnz, A->tune.stage_min);
   A->stage = A->static_stage = nullptr;
   for (int k = 0; k < n && b > 0 && !A->stage; ++k) A->stage = take(rooms[k], b);
   A->stages = A->stage != nullptr;

@@ -443,7 +443,9 @@ struct t_layout {
   bool small;  // RS_ROUNDS_SMALL keys per lane
 };
 
-t_layout make_layout(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_values) {
+t_layout make_layout(const isp_csr* A) {
+  const int64_t n_rows = A->v.n_rows, n_cols = A->v.n_cols, nnz = A->v.nnz;
+  const bool has_values = A->v.values != nullptr;
   t_layout L;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += isp_align(bytes); return o; };
@@ -463,7 +465,7 @@ t_layout make_layout(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_value
   L.table = take((size_t)(((int64_t)L.n_tiles << RS_MAX_BITS) + 1) * 4);
   L.digit_total = take((size_t)(1 << RS_MAX_BITS) * 4);
   L.flag = take(4);
-  L.part = take(isp_partition_workspace(n_cols, n_rows, nnz));  // (A^T: n_cols rows, n_rows columns)
+  L.part = take(isp_partition_workspace(n_cols, n_rows, nnz, A->tune.stage_min));  // (A^T: n_cols rows, n_rows columns)
   L.total = off;
   return L;
 }
@@ -513,15 +515,15 @@ isp_status share_handle(const isp_csr* A, const int64_t* t_indptr, const int32_t
 
 }  // namespace
 
-size_t isp_transpose_workspace_bytes(int64_t n_rows, int64_t n_cols, int64_t nnz, bool has_values) {
-  return make_layout(n_rows, n_cols, nnz, has_values).total;
+size_t isp_transpose_workspace_bytes(const isp_csr* A) {
+  return make_layout(A).total;
 }
 
 isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_t s) {
   const isp_view& v = A->v;
   const int64_t nnz = v.nnz, n_cols = v.n_cols, n_rows = v.n_rows;
   const bool has_values = v.values != nullptr;
-  const t_layout L = make_layout(n_rows, n_cols, nnz, has_values);
+  const t_layout L = make_layout(A);
   if (!ws) return isp_fail(ISP_EINVAL, "transpose workspace is NULL");
   if (ws_bytes < L.total) return isp_fail(ISP_EINVAL, "transpose workspace too small: %zu < %zu bytes", ws_bytes, L.total);
   if (((uintptr_t)ws & 255) != 0) return isp_fail(ISP_EINVAL, "workspace must be 256-byte aligned");
@@ -616,7 +618,7 @@ isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_
   } else {
     // (on a small one the flag comes to the host with the partition's counters)
     int* with_counters = ask_first ? nullptr : host_flag;
-    st = isp_build_handle(n_cols, n_rows, nnz, t_indptr, t_indices, t_values, base + L.part, ws_bytes - L.part, false, s,
+    st = isp_build_handle(n_cols, n_rows, nnz, t_indptr, t_indices, t_values, base + L.part, ws_bytes - L.part, false, A->tune, s,
                           &At, differs, with_counters);
     if (st != ISP_OK) return st;
     if (with_counters) {
@@ -628,7 +630,6 @@ isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_
   }
   A->mirror_aligned = At->mirror_aligned = (h_differs == 0);
   A->info.symmetric_pattern = At->info.symmetric_pattern = A->mirror_aligned ? 1 : 0;
-  At->tune = A->tune;  // (resolved when A was built)
   At->perm = perm;
   At->t_values_rw = t_values;
   // the record arrays of the sort are free from here on; one of them later holds the mean reduction's values

@@ -175,6 +175,29 @@ def test_reductions_new_values_and_replays(mid, d):
     A.destroy()
 
 
+def test_setting_is_the_sources():
+    """ISP_STAGE_MIN is read when the matrix is built; its transpose and the room for its aliases follow, whatever is set by then."""
+    n = 3000
+    g = _graph_with_hubs(n, 20)
+    for at_build, later in (("1", None), (None, "1"), ("1", "0")):
+        print("[case] ISP_STAGE_MIN", at_build, later, flush=True)
+        try:
+            if at_build:
+                os.environ["ISP_STAGE_MIN"] = at_build
+            A = build(*g)
+            os.environ.pop("ISP_STAGE_MIN", None)
+            if later:
+                os.environ["ISP_STAGE_MIN"] = later
+            need = isp.csr_transpose_workspace(A)
+            isp.csr_transpose_cached(A)
+        finally:
+            os.environ.pop("ISP_STAGE_MIN", None)
+        assert isp.csr_transpose_workspace(A) == need
+        rooms = isp.csr_alias_workspace(A, max_d=128) - isp.csr_alias_workspace(A, max_d=3)
+        assert rooms == (2 * 4 * n * 128 if at_build else 0)  # (A's and the transpose's)
+        A.destroy()
+
+
 def test_non_finite_rows_stay_where_they_are(graph):
     w, A, _, _ = graph
     print("[case] staged, one infinite row", flush=True)
