@@ -175,6 +175,82 @@ def test_reductions_new_values_and_replays(mid, d):
     A.destroy()
 
 
+def _holds_copy(ws, X, c0, pitch):
+    """Do the rows of the columns [c0, ...) of X, up to the last one, lie `pitch` floats apart somewhere in the workspace ws?"""
+    part = X[:, c0:]
+    n, w = part.shape
+    mem = ws[: ws.numel() // 4 * 4].view(torch.float32)
+    for at in torch.nonzero(mem == part[0, 0]).flatten().tolist():
+        if at + n * pitch <= mem.numel() and torch.equal(mem[at:at + n * pitch].view(n, pitch)[:, :w], part):
+            return True
+    return False
+
+
+def _build_in(ws_of, indptr, indices, values, **env):
+    """(A, its transpose, their workspaces) with the environment `env` set meanwhile."""
+    os.environ.update(env)
+    try:
+        n = len(indptr) - 1
+        ws = ws_of(isp.csr_build_workspace(n, n, len(indices)))
+        A = isp.csr_build(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(values).cuda(), workspace=ws)
+        wst = ws_of(isp.csr_transpose_workspace(A))
+        At, _ = isp.csr_transpose_cached(A, workspace=wst)
+    finally:
+        for k in env:
+            os.environ.pop(k)
+    return A, At, ws, wst
+
+
+def _clean(nbytes):
+    return torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+
+
+# (131 columns: the last tile's copy has rows of 8 floats)
+@pytest.mark.parametrize("d,c0,pitch", [(7, 0, 8), (20, 0, 32), (100, 0, 128), (131, 127, 8), (300, 256, 64)])
+@pytest.mark.parametrize("mid", [16, 0])
+def test_copies_are_made(mid, d, c0, pitch):
+    """The handle's workspace holds the last tile's columns after a call, and a call without copies leaves none there."""
+    print("[case] copies made", mid, d, flush=True)
+    g = _graph_with_hubs(2500, 30)
+    A, At, ws, wst = _build_in(_clean, *g, ISP_STAGE_MIN="1", ISP_MID_THRESHOLD=str(mid))
+    for h, mem in ((A, ws), (At, wst)):
+        X = torch.randn(2500, d, device="cuda")
+        isp.spmm(h, X, torch.empty_like(X))
+        assert _holds_copy(mem, X, c0, pitch)
+        X = torch.randn(2500, 128, device="cuda")  # (whole lines)
+        isp.spmm(h, X, torch.empty_like(X))
+        assert not _holds_copy(mem, X, 0, 128)
+    B = isp.csr_alias(A, max_d=d, workspace=(wsb := _clean(isp.csr_alias_workspace(A, max_d=d))))
+    X = torch.randn(2500, d, device="cuda")
+    isp.spmm(B, X, torch.empty_like(X))
+    assert _holds_copy(wsb, X, c0, pitch) and not _holds_copy(ws, X, c0, pitch)
+    X = torch.randn(2500, d, device="cuda")
+    isp.spmm_static_scratch(A, X, torch.empty_like(X))
+    assert _holds_copy(ws, X, c0, pitch)
+    B.destroy()
+    A.destroy()
+
+
+# from 80 Ki columns (512 Ki on the packed layout) a tile of 128 copied columns is gathered as two slices of 64
+@pytest.mark.parametrize("n,per_row,mid", [(90_001, 12, 0), (524_301, 5, 16)])
+@pytest.mark.parametrize("d,c0,pitch", [(131, 127, 8), (150, 128, 32)])
+def test_copies_in_two_slices(n, per_row, mid, d, c0, pitch):
+    print("[case] copies, two slices", n, mid, d, flush=True)
+    indptr, indices, values = _graph_with_hubs(n, per_row, seed=2)
+    A, At, ws, wst = _build_in(_clean, indptr, indices, values, ISP_STAGE_MIN="1", ISP_MID_THRESHOLD=str(mid))
+    assert (A.info()["spmm_pieces"] > 0) == (mid > 0)
+    X, Xh = _operand(np.random.default_rng(d), n, d, d, 1)
+    Y = torch.full((n, d), float("nan"), device="cuda")
+    isp.spmm(A, X, Y)
+    assert _holds_copy(ws, X, c0, pitch)
+    assert_close(Y, *oracle.spmm(indptr, indices, values, Xh), "two slices of copies")
+    ti, tj, _, tv = oracle.transpose(n, n, indptr, indices, values)
+    isp.spmm(At, X, Y)
+    assert _holds_copy(wst, X, c0, pitch)
+    assert_close(Y, *oracle.spmm(ti, tj, tv, Xh), "two slices of copies, transpose")
+    A.destroy()
+
+
 def test_setting_is_the_sources():
     """ISP_STAGE_MIN is read when the matrix is built; its transpose and the room for its aliases follow, whatever is set by then."""
     n = 3000
@@ -271,7 +347,8 @@ def test_rule_on_a_packed_layout_that_the_transpose_shares():
     indices, values = (code % n).astype(np.int32), rng.standard_normal(code.size).astype(np.float32)
     assert code.size >= 8 << 20
     vals = torch.from_numpy(values).cuda()
-    A = isp.csr_build(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), vals)
+    ws = _clean(isp.csr_build_workspace(n, n, code.size))
+    A = isp.csr_build(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), vals, workspace=ws)
     At, _ = isp.csr_transpose_cached(A)
     assert A.info()["symmetric_pattern"] == 1 and A.info()["spmm_pieces"] == At.info()["spmm_pieces"] > 0
     Xh = rng.standard_normal((n, d)).astype(np.float32)
@@ -279,6 +356,7 @@ def test_rule_on_a_packed_layout_that_the_transpose_shares():
     Y, Z = torch.empty_like(X), torch.empty_like(X)
     for turn in range(2):
         isp.spmm(A, X, Y)
+        assert _holds_copy(ws, X, 128, 16)
         isp.spmm_static_scratch(A, X, Z)
         assert torch.equal(Y, Z)
         assert_close(Y, *oracle.spmm(indptr, indices, values, Xh), "staged by rule, packed")
