@@ -479,7 +479,7 @@ size_t share_bytes(const isp_csr* A) {
 // The transpose's handle when its offsets and indices equal A's: A's partition tables and packed layout, which are
 // only read, serve both; values and scratch are its own (scratch: the partial rows of either partition in front, then the
 // packed values, share_bytes in all; the copy of a ragged operand behind them, or among the partial rows that are not
-// written).
+// written; scratch_end: of what the matrix asks for, so that more workspace changes nothing).
 isp_status share_handle(const isp_csr* A, const int64_t* t_indptr, const int32_t* t_indices, float* t_values,
                         char* scratch, char* scratch_end, hipStream_t s, isp_csr** out) {
   isp_csr* At = new (std::nothrow) isp_csr(*A);
@@ -502,7 +502,6 @@ isp_status share_handle(const isp_csr* A, const int64_t* t_indptr, const int32_t
     At->vp = At->v;
   }
   const int64_t busy = isp_busy_rows(At);
-  scratch_end -= (uintptr_t)scratch_end & 255;
   isp_stage::room rooms[3] = {{behind, scratch_end},
                               {scratch + (size_t)(busy > At->spmm_rows ? busy : At->spmm_rows) * row, rows_end},
                               {scratch + (size_t)At->spmm_rows * row, rows_end}};
@@ -613,8 +612,8 @@ isp_status isp_transpose_build(isp_csr* A, void* ws, size_t ws_bytes, hipStream_
     ISP_HIP(hipStreamSynchronize(s));
     if (host_flag) h_differs = *host_flag;
   }
-  if (ask_first && h_differs == 0 && share_bytes(A) <= ws_bytes - L.part) {
-    if ((st = share_handle(A, t_indptr, t_indices, t_values, base + L.part, base + ws_bytes, s, &At)) != ISP_OK) return st;
+  if (ask_first && h_differs == 0 && share_bytes(A) <= L.total - L.part) {
+    if ((st = share_handle(A, t_indptr, t_indices, t_values, base + L.part, base + L.total, s, &At)) != ISP_OK) return st;
   } else {
     // (on a small one the flag comes to the host with the partition's counters)
     int* with_counters = ask_first ? nullptr : host_flag;

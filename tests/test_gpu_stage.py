@@ -274,6 +274,23 @@ def test_setting_is_the_sources():
         A.destroy()
 
 
+def test_more_workspace_than_asked_for_changes_nothing():
+    """A transpose that shares its matrix's partitions takes copies by what the matrix asks for, not by what is left."""
+    print("[case] larger workspace", flush=True)
+    n, rng = 300_001, np.random.default_rng(0)
+    i, j = rng.integers(0, n, 2_200_000), rng.integers(0, n, 2_200_000)
+    code = np.unique(np.concatenate([i * n + j, j * n + i]))
+    indptr = np.concatenate([[0], np.cumsum(np.bincount(code // n, minlength=n))]).astype(np.int64)
+    g = indptr, (code % n).astype(np.int32), rng.standard_normal(code.size).astype(np.float32)
+    rooms = []
+    for more in (0, 512 * n + 4096):  # (the widest copies)
+        A, At, _, _ = _build_in(lambda need: _clean(need + more), *g, ISP_STAGE_MIN="1", ISP_MID_THRESHOLD="0")
+        assert A.info()["symmetric_pattern"] == 1
+        rooms.append(isp.csr_alias_workspace(A, max_d=128) - isp.csr_alias_workspace(A, max_d=3))
+        A.destroy()
+    assert rooms[0] == rooms[1] == 0
+
+
 def test_non_finite_rows_stay_where_they_are(graph):
     w, A, _, _ = graph
     print("[case] staged, one infinite row", flush=True)
