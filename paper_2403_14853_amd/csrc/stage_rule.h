@@ -60,7 +60,8 @@ inline int64_t tile_lines(uintptr_t at, int64_t ldx, int d, int tile, int64_t n_
 
 // The lines that a call on X touches, and with copies, for its rule.  The same values give the same bits wherever X lies,
 // so its address counts only where a copy leaves the launches as they are: rows of whole lines (128 columns at a time anyway)
-// and less than 128 columns (one launch).  Other rows count as if the first began a line.
+// and less than 128 columns (one launch).  Other rows count as if the first began a line: a view that begins elsewhere can miss
+// a copy for it (132 of 136 columns from the sixth on, 233 k columns, 115 M entries: 3830 us, 3240 with copies).
 inline int64_t operand_lines(uintptr_t at, int64_t ldx, int d, int tile, int64_t n_cols) {
   return tile_lines(ldx % ALIGN == 0 || d < COLS ? at : 0, ldx, d, tile, n_cols);
 }
