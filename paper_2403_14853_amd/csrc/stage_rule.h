@@ -18,6 +18,7 @@
 //   4267 / 4049);
 //   cut, two slices: 524 k, 17 M: 200 1238 / 1325, 500 2956 / 3123; 560 k, 20 M: 200 1493 / 1531 (inside: 257 2046 / 2022); 640 k, 21 M:
 //   200 1632 / 1671 (inside: 301 2532 / 2445; 800 k, 26 M: 200 2089 / 2102, 500 4939 / 4927; 1.4 M, 46 M: 200 3990 / 3858, 500 9639 / 8954);
+//   rows that begin at half lines, 1.1 M, 37 M: 303 of 304 columns 5 % slower; 882 k, 30 M: 592 5894 / 6208; 1.06 M, 36 M: 196 of 208 2660 / 2798;
 //   uniform, all rows cut: 350 k, 105 M: 17 1273 / 1445, 20 1407 / 1444; 150 k, 45 M: 50 985 / 1042 (inside: 350 k: 13 1082 / 964, 22 1626 /
 //   1445, 28 2088 / 1452; 150 k: 28 528 / 396).
 #pragma once
@@ -85,8 +86,9 @@ constexpr int MIN_D = 12;
 constexpr int64_t MANY_NNZ = (int64_t)8 << 20, MANY_MULS = 2000000000;
 constexpr int LINES_NARROW = 120, LINES_WIDE = 105;  // per cent
 // On the packed layout, where most gathers hit the L2s, the lines saved have to outweigh the lines copied: a copied line costs
-// as much as gathering five, or four where the copies also give two slices.  From SLICES_FAR columns on these save enough by themselves.
-constexpr int COPIED_LINE = 5, COPIED_LINE_SLICES = 4;
+// as much as gathering five; four where the copies also give two slices, two and a half there from SLICES_FAR columns on.  (In
+// tenths.)
+constexpr int COPIED_LINE = 50, COPIED_LINE_SLICES = 40, COPIED_LINE_FAR = 25;
 constexpr int64_t SLICES_FAR = 640 << 10;
 
 // What a call brings along: lines and lines_copied in the units of line_sum; cut: it runs on the packed layout, two_slices:
@@ -105,9 +107,8 @@ inline int pitch(int w) { return w <= 8 ? 8 : w <= 16 ? 16 : (w + ALIGN - 1) / A
 inline bool call_pays(const call& c) {
   if (c.d < MIN_D || (c.nnz < MANY_NNZ && c.nnz * c.d < MANY_MULS)) return false;
   if (100 * c.lines < (c.d > COLS ? LINES_WIDE : LINES_NARROW) * c.lines_copied) return false;
-  const int copied_line = c.two_slices ? COPIED_LINE_SLICES : COPIED_LINE;
-  if (c.cut && !(c.two_slices && c.n_cols >= SLICES_FAR) &&
-      c.nnz / c.n_cols * (c.lines - c.lines_copied) < copied_line * c.lines_copied) return false;
+  const int copied_line = !c.two_slices ? COPIED_LINE : c.n_cols < SLICES_FAR ? COPIED_LINE_SLICES : COPIED_LINE_FAR;
+  if (c.cut && 10 * (c.nnz / c.n_cols) * (c.lines - c.lines_copied) < copied_line * c.lines_copied) return false;
   // Where most rows are cut, all are long: no columns are popular, the L2s keep the band in work alone, and a copy that takes more
   // room than X by a larger factor than it saves lines makes more of them miss.
   return !(c.cut && c.long_rows && c.d <= COLS && c.lines * c.ldx < c.lines_copied * pitch(c.d));

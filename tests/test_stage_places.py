@@ -97,7 +97,8 @@ int main() {
   }
   struct { int64_t n, nnz; int d; bool pays; } sliced[] = {
       {524300, 17000000, 200, false}, {524300, 17000000, 500, false}, {524300, 17000000, 140, true}, {560000, 20000000, 200, false}, {560000, 20000000, 602, true},
-      {640000, 21000000, 200, false}, {640000, 21000000, 301, true}, {800000, 26000000, 200, true}, {1400000, 46000000, 500, true}};
+      {640000, 21000000, 200, false}, {640000, 21000000, 301, true}, {800000, 26000000, 200, true}, {1400000, 46000000, 500, true},
+      {881974, 29733124, 592, false}, {1106926, 36734308, 304, false}, {1060161, 36415778, 208, false}, {1400000, 70000000, 592, true}, {1000000, 40000000, 301, true}};
   for (auto& q : sliced)
     if (isp_stage::call_pays({q.nnz, q.n, q.d, q.d, isp_stage::operand_lines(0, q.d, q.d, 256, q.n), isp_stage::copied_lines(q.d), true, true, false}) != q.pays)
       FAIL("two slices: %d columns of %lld\n", q.d, (long long)q.n);
