@@ -328,7 +328,7 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
                                                                    isp_stage::operand_lines((uintptr_t)X, ldx, d, tile, av.n_cols),
                                                                    isp_stage::copied_lines(d), packed,
                                                                    av.n_cols >= slice_cols,
-                                                                   2 * (int64_t)A->info.spmm_cut_rows > av.n_rows}));
+                                                                   packed ? 2 * (int64_t)A->info.spmm_cut_rows > av.n_rows : av.n_hub == 0}));
   if (stage || (A->stages && A->tune.stage_min > 0)) tile = isp_stage::COLS;  // (the latter for aligned X too: same launches)
   if (A->tune.spmm_tile) tile = A->tune.spmm_tile;
   // (a handle with the packed layout may keep its copies among the rows that launches on the other partition write)

@@ -20,7 +20,9 @@
 //   200 1632 / 1671 (inside: 301 2532 / 2445; 800 k, 26 M: 200 2089 / 2102, 500 4939 / 4927; 1.4 M, 46 M: 200 3990 / 3858, 500 9639 / 8954);
 //   rows that begin at half lines, 1.1 M, 37 M: 303 of 304 columns 5 % slower; 882 k, 30 M: 592 5894 / 6208; 1.06 M, 36 M: 196 of 208 2660 / 2798;
 //   uniform, all rows cut: 350 k, 105 M: 17 1273 / 1445, 20 1407 / 1444; 150 k, 45 M: 50 985 / 1042 (inside: 350 k: 13 1082 / 964, 22 1626 /
-//   1445, 28 2088 / 1452; 150 k: 28 528 / 396).
+//   1445, 28 2088 / 1452; 150 k: 28 528 / 396);
+//   uniform, not cut, per cent slower with: 91 k, 8.9 M: 18 16; 76 k, 12 M: 18 16; 115 k, 9.3 M: 17 9; 167 k, 14 M: 12 9 (inside, faster: 85 k, 12 M:
+//   13 6, 24 9; 183 k, 11 M: 18 14; 222 k, 25 M: 12 2).
 #pragma once
 #include "partition_sizes.h"
 
@@ -90,14 +92,16 @@ constexpr int LINES_NARROW = 120, LINES_WIDE = 105;  // per cent
 // tenths.)
 constexpr int COPIED_LINE = 50, COPIED_LINE_SLICES = 40, COPIED_LINE_FAR = 25;
 constexpr int64_t SLICES_FAR = 640 << 10;
+constexpr int64_t KEPT_BYTES = 8 << 20;  // (an L2: 4 MB)
 
 // What a call brings along: lines and lines_copied in the units of line_sum; cut: it runs on the packed layout, two_slices:
-// its 128-column launches run as two slices if they gather from copies, long_rows: more than half of the rows are cut.
+// its 128-column launches run as two slices if they gather from copies, even: its rows are about equally long, more than half
+// of them cut or, on the ordinary partition, none a hub row.
 struct call {
   int64_t nnz, n_cols, ldx;
   int d;
   int64_t lines, lines_copied;
-  bool cut, two_slices, long_rows;
+  bool cut, two_slices, even;
 };
 
 // Floats per row of the copy of w columns: whole lines, or the part of one (16 floats, 8) that the row fits, so that rows
@@ -109,9 +113,11 @@ inline bool call_pays(const call& c) {
   if (100 * c.lines < (c.d > COLS ? LINES_WIDE : LINES_NARROW) * c.lines_copied) return false;
   const int copied_line = !c.two_slices ? COPIED_LINE : c.n_cols < SLICES_FAR ? COPIED_LINE_SLICES : COPIED_LINE_FAR;
   if (c.cut && 10 * (c.nnz / c.n_cols) * (c.lines - c.lines_copied) < copied_line * c.lines_copied) return false;
-  // Where most rows are cut, all are long: no columns are popular, the L2s keep the band in work alone, and a copy that takes more
-  // room than X by a larger factor than it saves lines makes more of them miss.
-  return !(c.cut && c.long_rows && c.d <= COLS && c.lines * c.ldx < c.lines_copied * pitch(c.d));
+  // Where rows are equally long no columns are popular: the L2s keep a part of X, the band in work on the packed layout, and a copy
+  // that takes more room than X by a larger factor than it saves lines makes more of them miss; without bands where X is little
+  // larger than an L2.
+  const bool kept = c.cut || c.n_cols * c.ldx * 4 < KEPT_BYTES;
+  return !(kept && c.even && c.d <= COLS && c.lines * c.ldx < c.lines_copied * pitch(c.d));
 }
 
 // The widest pitch that calls of up to max_d columns ask for; `always`: ISP_STAGE_MIN is set.

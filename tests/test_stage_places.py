@@ -102,6 +102,12 @@ int main() {
   for (auto& q : sliced)
     if (isp_stage::call_pays({q.nnz, q.n, q.d, q.d, isp_stage::operand_lines(0, q.d, q.d, 256, q.n), isp_stage::copied_lines(q.d), true, true, false}) != q.pays)
       FAIL("two slices: %d columns of %lld\n", q.d, (long long)q.n);
+  struct { int64_t n, nnz; int d; bool pays; } uniform[] = {
+      {91342, 8901716, 18, false}, {75751, 12442518, 18, false}, {114609, 9299487, 17, false}, {166803, 14124212, 12, false}, {84990, 12035986, 13, true},
+      {91342, 8901716, 24, true}, {183756, 11407391, 18, true}, {221850, 24848037, 12, true}};
+  for (auto& q : uniform)
+    if (isp_stage::call_pays({q.nnz, q.n, q.d, q.d, isp_stage::operand_lines(0, q.d, q.d, 256, q.n), isp_stage::copied_lines(q.d), false, false, true}) != q.pays)
+      FAIL("equally long rows: %d columns of %lld\n", q.d, (long long)q.n);
   for (int w = 1, last = 0; w <= 128; ++w) {  // an alias for max_d columns has room for every narrower call
     const int p = isp_stage::pitch(w);
     if (p < w || p < last || p > isp_stage::pitch_up_to(w, true) + (w < 4 ? 8 : 0)) FAIL("pitch of %d\n", w);
