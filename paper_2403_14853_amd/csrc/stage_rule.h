@@ -22,7 +22,9 @@
 //   uniform, all rows cut: 350 k, 105 M: 17 1273 / 1445, 20 1407 / 1444; 150 k, 45 M: 50 985 / 1042 (inside: 350 k: 13 1082 / 964, 22 1626 /
 //   1445, 28 2088 / 1452; 150 k: 28 528 / 396);
 //   uniform, not cut, per cent slower with: 91 k, 8.9 M: 18 16; 76 k, 12 M: 18 16; 115 k, 9.3 M: 17 9; 167 k, 14 M: 12 9 (inside, faster: 85 k, 12 M:
-//   13 6, 24 9; 183 k, 11 M: 18 14; 222 k, 25 M: 12 2).
+//   13 6, 24 9; 183 k, 11 M: 18 14; 222 k, 25 M: 12 2);
+//   not cut, hub rows, per cent slower with, mean over graphs of 30 k to 240 k columns: 272, 304, 528, 560, 592 columns 1.6 to 2.0, at worst 7.8 (98 k,
+//   6.3 M: 528) (inside, faster: those around 390 2.4, 460 1.8, 490 5.5; widths that save 6 to 7 % of the lines 3.4).
 #pragma once
 #include "partition_sizes.h"
 
@@ -83,10 +85,11 @@ inline int64_t copied_lines(int d) {
 // copied, and the matrix is of a size at which any call takes a copy.
 constexpr int64_t MIN_PER_COL = 32, MIN_NNZ = 3000000;
 // A call takes the copy from 12 columns up, where the work outweighs the launches, and where the lines that a row touches
-// fall by a fifth, or by 5 % beyond 128 columns, which the copies also let run 128 at a time.
+// fall by a fifth, or by 5 % beyond 128 columns, which the copies also let run 128 at a time; by 6 % where hub rows on the
+// ordinary partition hide some of it, unless a launch of 129 to 255 columns, which take longest for their width, is replaced.
 constexpr int MIN_D = 12;
 constexpr int64_t MANY_NNZ = (int64_t)8 << 20, MANY_MULS = 2000000000;
-constexpr int LINES_NARROW = 120, LINES_WIDE = 105;  // per cent
+constexpr int LINES_NARROW = 120, LINES_WIDE = 105, LINES_WIDE_UNEVEN = 106;  // per cent
 // On the packed layout, where most gathers hit the L2s, the lines saved have to outweigh the lines copied: a copied line costs
 // as much as gathering five; four where the copies also give two slices, two and a half there from SLICES_FAR columns on.  (In
 // tenths.)
@@ -110,7 +113,9 @@ inline int pitch(int w) { return w <= 8 ? 8 : w <= 16 ? 16 : (w + ALIGN - 1) / A
 
 inline bool call_pays(const call& c) {
   if (c.d < MIN_D || (c.nnz < MANY_NNZ && c.nnz * c.d < MANY_MULS)) return false;
-  if (100 * c.lines < (c.d > COLS ? LINES_WIDE : LINES_NARROW) * c.lines_copied) return false;
+  const bool wide_tail = c.d % ISP_PARTIAL_TILE > COLS;  // (the copies replace a launch of 129 to 255 columns)
+  const int lines = c.d <= COLS ? LINES_NARROW : c.cut || c.even || wide_tail ? LINES_WIDE : LINES_WIDE_UNEVEN;
+  if (100 * c.lines < lines * c.lines_copied) return false;
   const int copied_line = !c.two_slices ? COPIED_LINE : c.n_cols < SLICES_FAR ? COPIED_LINE_SLICES : COPIED_LINE_FAR;
   if (c.cut && 10 * (c.nnz / c.n_cols) * (c.lines - c.lines_copied) < copied_line * c.lines_copied) return false;
   // Where rows are equally long no columns are popular: the L2s keep a part of X, the band in work on the packed layout, and a copy

@@ -108,6 +108,11 @@ int main() {
   for (auto& q : uniform)
     if (isp_stage::call_pays({q.nnz, q.n, q.d, q.d, isp_stage::operand_lines(0, q.d, q.d, 256, q.n), isp_stage::copied_lines(q.d), false, false, true}) != q.pays)
       FAIL("equally long rows: %d columns of %lld\n", q.d, (long long)q.n);
+  for (int d : {272, 304, 528, 560, 592, 140, 301, 602})  // (five of half lines, three of any)
+    for (int even : {0, 1}) {
+      const bool pays = isp_stage::call_pays({8500000, 98496, d, d, isp_stage::operand_lines(0, d, d, 256, 98496), isp_stage::copied_lines(d), false, true, even != 0});
+      if (pays != (even || d == 140 || d == 301 || d == 602)) FAIL("hub rows %d: %d columns\n", !even, d);
+    }
   for (int w = 1, last = 0; w <= 128; ++w) {  // an alias for max_d columns has room for every narrower call
     const int p = isp_stage::pitch(w);
     if (p < w || p < last || p > isp_stage::pitch_up_to(w, true) + (w < 4 ? 8 : 0)) FAIL("pitch of %d\n", w);
