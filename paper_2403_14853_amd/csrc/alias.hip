@@ -86,6 +86,7 @@ extern "C" isp_status isp_csr_alias(const isp_csr_t* A, int32_t max_d, void* wor
   // Every partial row a launch reads was written by that launch before, so the workspace needs no clearing.
   B->v.partials = reinterpret_cast<float*>(base);
   B->vp.partials = B->v.partials;  // (a call runs on one of the two partitions, never on both)
+  B->v.hub_done = B->vp.hub_done = nullptr;  // (counters of its own would have to be cleared on some stream)
   B->partial_rows = L.rows_a;
   auto own_stage = [&](isp_csr* h, size_t off) {
     if (!h->stage) return;
@@ -101,6 +102,7 @@ extern "C" isp_status isp_csr_alias(const isp_csr_t* A, int32_t max_d, void* wor
     Bt->At = nullptr;
     Bt->v.partials = reinterpret_cast<float*>(base + L.off_t);
     Bt->vp.partials = Bt->v.partials;
+    Bt->v.hub_done = Bt->vp.hub_done = nullptr;
     Bt->partial_rows = L.rows_t;
     own_stage(Bt, L.off_stage_t);
     // The marks of the min / max backward are written by every call: the alias's own.  What the transpose

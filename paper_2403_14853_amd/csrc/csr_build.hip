@@ -15,6 +15,7 @@
 #include <new>
 #include "block_scan.h"
 #include "host_slot.h"
+#include "hub_finish.h"
 #include "stage_rule.h"
 
 namespace {
@@ -364,8 +365,8 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
                                                  int64_t n_rows, int32_t* __restrict__ blk_row,
                                                  int32_t* __restrict__ hub_rows, int32_t* __restrict__ hub_seg_ptr,
                                                  int32_t* __restrict__ seg_hub, int32_t* __restrict__ seg_begin,
-                                                 int32_t* __restrict__ seg_key, build_counters* __restrict__ ctr,
-                                                 int64_t max_blocks, int64_t max_hub, int64_t max_seg) {
+                                                 int32_t* __restrict__ seg_key, unsigned* __restrict__ hub_done,
+                                                 build_counters* __restrict__ ctr, int64_t max_blocks, int64_t max_hub, int64_t max_seg) {
   // (asked for here, looked at behind the sums below; written by pass 2)
   const int err = ctr->err;
   const int lane = threadIdx.x & (ISP_WAVE - 1);
@@ -407,6 +408,7 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
     if (hub && h < max_hub) {
       hub_rows[h] = (int32_t)i;
       hub_seg_ptr[h] = s0;
+      for (int k = 0; k < HF_SLICES; ++k) hub_done[(int64_t)h * HF_SLICES + k] = 0;
     }
     const int hx = (int)(pos >> 32 & 0xffff);  // the step's hub rows, shared out over the wavefronts
     if (hub) { s_ha[hx] = a; s_hb[hx] = b; s_hs[hx] = s0; }
@@ -702,7 +704,7 @@ static_assert(sizeof(build_counters) <= host_slot::SIZE, "the counters fit a slo
 // ---- workspace layout ------------------------------------------------------------------------------------
 struct ws_layout {
   size_t counters, cost, hubflag, nseg, mark, tile_cost, tile_hub, tile_seg, tile_mark, tile_stat, tile_err;
-  size_t blk_row, hub_rows, hub_seg_ptr, seg_hub, seg_begin, seg_key[2], seg_order[2], so_table, so_scanned, so_tmp;
+  size_t blk_row, hub_rows, hub_seg_ptr, hub_done, seg_hub, seg_begin, seg_key[2], seg_order[2], so_table, so_scanned, so_tmp;
   size_t inv_len, item_desc, partials, total;
   int64_t max_blocks, max_hub, max_seg;
 };
@@ -733,6 +735,7 @@ ws_layout make_layout(int64_t n_rows, int64_t nnz, const partition_params& pp, s
   L.blk_row = take((size_t)(max_blocks + 1) * 4);
   L.hub_rows = take((size_t)(max_hub + 1) * 4);
   L.hub_seg_ptr = take((size_t)(max_hub + 2) * 4);
+  L.hub_done = take((size_t)(max_hub + 1) * HF_SLICES * 4);
   L.seg_hub = take((size_t)(max_seg + 1) * 4);
   L.seg_begin = take((size_t)(max_seg + 1) * 4);
   for (int k = 0; k < 2; ++k) {
@@ -808,6 +811,7 @@ struct partition_out {
   int32_t *blk_row, *hub_rows, *hub_seg_ptr, *seg_hub, *seg_begin, *hubflag;
   const int32_t* seg_order;
   int4* item_desc;
+  unsigned* hub_done;
   float* partials;
   float* inv_len;
   build_counters h;
@@ -859,8 +863,8 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   ISP_LAUNCH_CHECK();
 #define ISP_GO(R)                                                                                                     \
   k_compact<R><<<T.n, BS_THREADS, 0, s>>>(indptr, indices, n_cols, pp, T, mark, hubflag, nseg, n_rows, blk_row, hub_rows, \
-                                          hub_seg_ptr, seg_hub, seg_begin, seg_key[0], ctr, L.max_blocks, L.max_hub,  \
-                                          L.max_seg)
+                                          hub_seg_ptr, seg_hub, seg_begin, seg_key[0],              \
+                                          (unsigned*)(base + L.hub_done), ctr, L.max_blocks, L.max_hub, L.max_seg)
   if (spread) ISP_GO(RPW_SMALL); else ISP_GO(RPW_LARGE);
 #undef ISP_GO
   ISP_LAUNCH_CHECK();
@@ -916,6 +920,7 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   }
   out->blk_row = blk_row; out->hub_rows = hub_rows; out->hub_seg_ptr = hub_seg_ptr; out->seg_hub = seg_hub;
   out->seg_begin = seg_begin; out->hubflag = hubflag; out->seg_order = seg_order; out->item_desc = item_desc;
+  out->hub_done = (unsigned*)(base + L.hub_done);
   out->partials = (float*)(base + L.partials);
   out->inv_len = (float*)(base + L.inv_len);
   return ISP_OK;
@@ -931,6 +936,7 @@ void fill_view(isp_view& v, int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   v.n_hub = po.h.n_hub; v.n_seg = po.h.n_seg;
   v.hub_t = pp.hub_t; v.seg_len = pp.seg_len;
   v.partials = po.partials;
+  v.hub_done = po.hub_done;
   v.inv_len = po.inv_len;
   v.n_real_rows = n_rows;
   v.piece_slot = nullptr;
@@ -984,6 +990,7 @@ isp_status build_packed(isp_csr* A, const partition_params& p1, int mid_t, char*
   // the pieces' sums go to the cut partition's partial rows and are added by its hub tables
   vp.hub_rows = cut.hub_rows; vp.hub_seg_ptr = cut.hub_seg_ptr; vp.n_hub = cut.h.n_hub;
   vp.partials = cut.partials;
+  vp.hub_done = nullptr;
   vp.inv_len = v.inv_len;
   vp.n_real_rows = n;
   vp.piece_slot = cut.seg_order;

@@ -22,6 +22,12 @@ __global__ void __launch_bounds__(ISP_WG) k_fused_fixup(isp_view A, int d, float
   hub_fixup<VEC, T, ACC>(A, d, 0, Y, ldy);
 }
 
+// The grouped kernels' (rows of at most one partial row): the order in which a launch that finishes its hub rows adds them.
+template <bool ACC>
+__global__ void __launch_bounds__(ISP_WG) k_fused_fixup_wg(isp_view A, int d, float* __restrict__ Y, int64_t ldy) {
+  hub_fixup_wg<4, 1, false, ACC>(A, d, 0, Y, ldy, 0);
+}
+
 template <class P, int LPG, int W, bool ADDR32, bool TAIL>
 __global__ void __launch_bounds__(ISP_WG) k_fused_grouped(isp_view A, const int64_t* __restrict__ indptr,
                                                           const int32_t* __restrict__ indices,
@@ -35,7 +41,8 @@ __global__ void __launch_bounds__(ISP_WG) k_fused_grouped(isp_view A, const int6
 // A32: every gather offset fits 32 bits.
 template <class P, int LPG, int W, bool A32>
 isp_status run_grouped(const isp_csr* A, const typename P::args& pa, int d, float* Y, int64_t ldy, hipStream_t s) {
-  const isp_view& v = A->v;
+  isp_view v = A->v;
+  if (!hf_pays(A, v, d)) v.hub_done = nullptr;
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
@@ -43,9 +50,8 @@ isp_status run_grouped(const isp_csr* A, const typename P::args& pa, int d, floa
     else k_fused_grouped<P, LPG, W, A32, false><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, pa, d, Y, ldy);
     ISP_LAUNCH_CHECK();
   }
-  if (v.n_hub > 0) {
-    const unsigned grid = (unsigned)((v.n_hub + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
-    k_fused_fixup<4, 1, P::ACCUMULATE><<<grid, ISP_WG, 0, s>>>(v, d, Y, ldy);
+  if (v.n_hub > 0 && !v.hub_done) {
+    k_fused_fixup_wg<P::ACCUMULATE><<<(unsigned)v.n_hub, ISP_WG, 0, s>>>(v, d, Y, ldy);
     ISP_LAUNCH_CHECK();
   }
   return ISP_OK;

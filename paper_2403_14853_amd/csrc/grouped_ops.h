@@ -10,6 +10,7 @@
 // after the first).
 #pragma once
 #include <type_traits>
+#include "hub_finish.h"
 #include "run_stream.h"
 
 namespace isp_dev {
@@ -61,7 +62,14 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
   const item_range it = locate_item(A, indptr, item);
   if (it.skip) return;
   auto& L = lds.w[w];
+  const bool finish = !P::PER_ENTRY && it.is_seg && A.hub_done;
+  hub_ref H{0, 0, 0};
+  if (finish) H.h = A.seg_hub[it.row];
   const rn_run R = rn_prepare<G>(it, indptr, indices, values, nullptr, L, lane);
+  if (finish) {
+    H.s0 = A.hub_seg_ptr[H.h];
+    H.s1 = A.hub_seg_ptr[H.h + 1];
+  }
 
   const int g = lane / LPG, q = lane % LPG;
   lane_cols<NV, TAIL> lc;  // this lane's columns: in range?  offset of the first (0 when out of range)
@@ -72,17 +80,14 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
     lc.off[v] = lc.on[v] ? (TAIL && col + 4 > d ? d - 4 : col) : 0;
     lc.dup[v] = TAIL && lc.on[v] ? col - lc.off[v] : 0;
   }
-  float* __restrict__ out = it.is_seg ? A.partials : Y;
-  const int64_t ldo = it.is_seg ? (int64_t)ISP_PARTIAL_TILE : ldy;
   float acc[W], head[W];  // head: the end of a row that began in an earlier run
 #pragma unroll
   for (int v = 0; v < W; ++v) acc[v] = head[v] = 0.f;
-  auto store_row = [&](int row, const float (&src)[W]) {  // this lane's columns to row `row` of the output
-    float* o = out + row * ldo;
+  auto store_to = [&](float* o, const float (&src)[W]) {  // this lane's columns of the output row at o
     float t[W];
 #pragma unroll
     for (int v = 0; v < W; ++v) t[v] = src[v];
-    if (P::ACCUMULATE && !it.is_seg) {  // (all of it is read before anything is written: a moved-back vector overlaps)
+    if (P::ACCUMULATE) {  // (all of it is read before anything is written: a moved-back vector overlaps)
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         float old[4];
@@ -99,6 +104,7 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
       if (lc.on[v]) store_vec<4>(o + lc.off[v], part);
     }
   };
+  auto store_row = [&](int row, const float (&src)[W]) { store_to(Y + row * ldy, src); };  // (of a row block)
   if (!P::PER_ENTRY && !P::ACCUMULATE)  // outputs of the empty rows
     for (int i = g; i < R.n_empty; i += G) store_row(L.dst[RN_EMPTY0 - i], acc);
 
@@ -227,7 +233,21 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
         float t[N];
 #pragma unroll
         for (int c = 0; c < N; ++c) t[c] = acc[c];
-        store_vec<N>(out + (int64_t)it.row * ldo + (idx0 >= 4 ? lc.off[NV - 1] + idx0 - 4 : lc.off[0] + idx0), t);
+        float* row = A.partials + (int64_t)it.row * ISP_PARTIAL_TILE;
+        const int c0 = idx0 >= 4 ? lc.off[NV - 1] + idx0 - 4 : lc.off[0] + idx0;
+        if (finish) hf_store<N>(row, (unsigned)c0 * 4u, t);
+        else store_vec<N>(row + c0, t);
+      }
+      if (finish && hf_last(A, H, 0, lane)) {
+        float sum[W];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          float t[4];
+          hf_sum<LPG, G == 1 ? 4 : 8>(A, H, (unsigned)lc.off[v] * 4u, lane, t);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) sum[4 * v + c] = t[c];
+        }
+        if (g == 0) store_to(Y + (int64_t)it.src_row * ldy, sum);
       }
       return;
     }

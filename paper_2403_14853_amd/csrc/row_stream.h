@@ -350,21 +350,21 @@ __device__ inline void hub_fixup(const isp_view& A, int d, int k0, float* __rest
   }
 }
 
-// The same combination with one workgroup per hub row, for SpMM: a row cut into more than 32 segments
-// (a vertex adjacent to a large share of the graph) is split four ways, each wavefront adds a contiguous
-// quarter of the partial rows in order and the quarters are added in order - a fixed summation tree, so
-// still deterministic.  Shorter rows are summed by the first wavefront alone, in segment order.
-// MEAN: the sum is divided by the row's length (hub rows are never empty).
-template <int VEC, int T, bool MEAN>
-__device__ inline void hub_fixup_wg(const isp_view& A, int d, int k0, float* __restrict__ Y, int64_t ldy) {
+// The same combination with one workgroup per hub row: a row of more than SPLIT_ABOVE segments is split four ways, each
+// wavefront adds a contiguous quarter of the partial rows in order and the quarters are added in order - a fixed summation
+// tree, so still deterministic.  Shorter rows are summed by the first wavefront alone, in segment order (the packed SpMM
+// layout, whose many rows of a few pieces would only pay for the barrier).
+// MEAN: the sum is divided by the row's length (hub rows are never empty).  ACC: it is added to the output row.
+template <int VEC, int T, bool MEAN, bool ACC = false>
+__device__ inline void hub_fixup_wg(const isp_view& A, int d, int k0, float* __restrict__ Y, int64_t ldy, int split_above) {
   __shared__ float part[ISP_WAVES_PER_WG][T][ISP_WAVE][VEC];
   const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x >> 6;
   const int h = blockIdx.x;
   const int s0 = A.hub_seg_ptr[h], s1 = A.hub_seg_ptr[h + 1];
-  const bool split = s1 - s0 > 32;  // uniform over the workgroup
+  const bool split = s1 - s0 > split_above;  // uniform over the workgroup
   if (!split && w > 0) return;
   const int q = split ? (s1 - s0 + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG : s1 - s0;
-  const int a = s0 + w * q, b = (a + q < s1) ? a + q : s1;
+  const int a = s0 + w * q < s1 ? s0 + w * q : s1, b = (a + q < s1) ? a + q : s1;
   float acc[T][VEC];
 #pragma unroll
   for (int tt = 0; tt < T; ++tt) {
@@ -418,7 +418,14 @@ __device__ inline void hub_fixup_wg(const isp_view& A, int d, int k0, float* __r
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[tt][v] *= inv;
     }
-    store_vec<VEC>(Y + (int64_t)row * ldy + k0 + rel, acc[tt]);
+    float* o = Y + (int64_t)row * ldy + k0 + rel;
+    if (ACC) {
+      float old[VEC];
+      load_vec<VEC>(o, old);
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) acc[tt][v] += old[v];
+    }
+    store_vec<VEC>(o, acc[tt]);
   }
 }
 

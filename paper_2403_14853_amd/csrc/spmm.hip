@@ -2,6 +2,7 @@
 // 3.4, 3.5).  The backward dX = A^T dY is this same code run on the cached transpose's handle
 // (Section 3.3).  Gather-bound: per nonzero one 4*d-byte row of X is fetched and d FMAs are done,
 // so the kernels are built around coalesced row gathers, not around matrix cores.
+#include "hub_finish.h"
 #include "run_stream.h"
 #include "stage_rule.h"
 
@@ -39,14 +40,17 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm(isp_view A, const int64_t* __re
 
 // One workgroup per hub row.
 template <int VEC, int T>
-__global__ void __launch_bounds__(ISP_WG) k_spmm_fixup(isp_view A, int d, int k0, float* __restrict__ Y, int64_t ldy) {
-  hub_fixup_wg<VEC, T, false>(A, d, k0, Y, ldy);
+__global__ void __launch_bounds__(ISP_WG) k_spmm_fixup(isp_view A, int d, int k0, float* __restrict__ Y, int64_t ldy,
+                                                       int split_above) {
+  hub_fixup_wg<VEC, T, false>(A, d, k0, Y, ldy, split_above);
 }
+// Pieces of the packed layout: rows of up to this many are added by one wavefront.
+constexpr int PACKED_SPLIT = 32;
 
 // Mean reduction: the fixed-order sum of a hub row's segments, divided by the row's length.
 __global__ void __launch_bounds__(ISP_WG) k_spmm_fixup_mean(isp_view A, int d, int k0, float* __restrict__ Y,
-                                                            int64_t ldy) {
-  hub_fixup_wg<4, 1, true>(A, d, k0, Y, ldy);
+                                                            int64_t ldy, int split_above) {
+  hub_fixup_wg<4, 1, true>(A, d, k0, Y, ldy, split_above);
 }
 
 template <int VEC, int T>
@@ -63,7 +67,7 @@ isp_status launch_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int
     ISP_LAUNCH_CHECK();
   }
   if (v.n_hub > 0) {
-    k_spmm_fixup<VEC, T><<<(unsigned)v.n_hub, ISP_WG, 0, s>>>(v, d, k0, Y, ldy);
+    k_spmm_fixup<VEC, T><<<(unsigned)v.n_hub, ISP_WG, 0, s>>>(v, d, k0, Y, ldy, 0);
     ISP_LAUNCH_CHECK();
   }
   return ISP_OK;
@@ -109,9 +113,16 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
   // each adds into a partial row, named by piece_slot.  A block never mixes real rows and pieces.
   const bool pieces = !it.is_seg && (int64_t)it.row >= A.n_real_rows;
   const bool to_partial = it.is_seg || pieces;
+  const bool finish = VEC == 4 && it.is_seg && A.hub_done;
+  hub_ref H{0, 0, 0};
+  if (finish) H.h = A.seg_hub[it.row];
   const rn_run R = rn_prepare<G>(it, indptr, indices, values,
                                  pieces ? A.piece_slot - A.n_real_rows : nullptr, L, lane);
 
+  if (finish) {
+    H.s0 = A.hub_seg_ptr[H.h];
+    H.s1 = A.hub_seg_ptr[H.h + 1];
+  }
   const int g = lane / LPG, q = lane % LPG;
   int col = k_base + (slice * LPG + q) * VEC;
   const bool lane_on = col < d;
@@ -173,7 +184,20 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
       float t[N];
 #pragma unroll
       for (int c = 0; c < N; ++c) t[c] = acc[c];
-      store_vec<N>(row_of(it.row) + idx0, t);
+      if (finish) hf_store<N>(A.partials + (int64_t)it.row * ISP_PARTIAL_TILE, (unsigned)(col - k_base + idx0) * 4u, t);
+      else store_vec<N>(row_of(it.row) + idx0, t);
+    }
+    if constexpr (VEC == 4) {
+      if (finish && hf_last(A, H, slice, lane)) {
+        float t[4];
+        hf_sum<LPG, CAP == GS_MAX_ENT ? 16 : 8>(A, H, (unsigned)(col - k_base) * 4u, lane, t);
+        if (MEAN) {
+          const float inv = A.inv_len[it.src_row];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) t[v] *= inv;
+        }
+        if (g == 0 && lane_on) store_vec<4>(Y + (int64_t)it.src_row * ldy + col, t);
+      }
     }
     return;
   }
@@ -214,13 +238,14 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
   const bool packed = A->has_packed && (!values_override || values_override_packed) &&
                       A->packed_block_cost + A->vp.hub_t <= GS_MAX_ENT &&
                       A->packed_block_cost / A->packed_row_cost <= GS_MAX_ROWS;
-  const isp_view& v = packed ? A->vp : A->v;
+  isp_view v = packed ? A->vp : A->v;
+  const int width = n_slices * LPG * VEC < d - k_base ? n_slices * LPG * VEC : d - k_base;
+  if (VEC < 4 || n_slices > HF_SLICES || !hf_pays(A, v, width)) v.hub_done = nullptr;  // (a fix-up launch adds the hub rows)
   // (one value per stored entry, in the order of the view's entries)
   const float* vals = values_override ? (packed ? values_override_packed : values_override) : v.values;
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG) * (unsigned)n_slices;
-    const int width = n_slices * LPG * VEC < d - k_base ? n_slices * LPG * VEC : d - k_base;
     const unsigned spare = packed && 2 * isp_stage::line_sum((uintptr_t)(X + k_base), ldx, width) > 7 * isp_stage::ALIGN
                                ? SPMM_FOUR_PER_CU : 0u;
     const bool a32 = v.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
@@ -247,11 +272,12 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
 #undef ISP_GO
     ISP_LAUNCH_CHECK();
   }
-  if (v.n_hub > 0) {
+  if (v.n_hub > 0 && !v.hub_done) {
     // the columns this launch covered: [k_base, min(d, k_base + n_slices * LPG * VEC))
     const int d_hi = (k_base + n_slices * LPG * VEC < d) ? k_base + n_slices * LPG * VEC : d;
-    if (mean_mode == 1) k_spmm_fixup_mean<<<(unsigned)v.n_hub, ISP_WG, 0, s>>>(v, d_hi, k_base, Y, ldy);  // VEC = 4 only
-    else k_spmm_fixup<VEC, 4 / VEC><<<(unsigned)v.n_hub, ISP_WG, 0, s>>>(v, d_hi, k_base, Y, ldy);
+    const int split = packed ? PACKED_SPLIT : 0;
+    if (mean_mode == 1) k_spmm_fixup_mean<<<(unsigned)v.n_hub, ISP_WG, 0, s>>>(v, d_hi, k_base, Y, ldy, split);  // VEC = 4 only
+    else k_spmm_fixup<VEC, 4 / VEC><<<(unsigned)v.n_hub, ISP_WG, 0, s>>>(v, d_hi, k_base, Y, ldy, split);
     ISP_LAUNCH_CHECK();
   }
   return ISP_OK;

@@ -58,6 +58,7 @@ extern "C" isp_status isp_spmm_static_scratch(const isp_csr_t* A, const float* X
   isp_csr view = *A;
   view.v.partials = ptr;
   view.vp.partials = ptr;
+  view.v.hub_done = view.vp.hub_done = nullptr;  // (the counters are the handle's: isp_spmm's calls on it may overlap this one)
   // A ragged operand is copied to a place in the handle's workspace that no other call writes.  Without one (little idle
   // room) it is gathered from where it is, by the same launches, so that the results stay isp_spmm's: 128 columns at a time,
   // the slower way to gather rows that start anywhere.  us without / with the copies / 256 at a time without (no hub segments):

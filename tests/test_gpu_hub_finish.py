@@ -1,0 +1,97 @@
+"""Hub rows that the launch of their segments puts together: numbers of segments around the quarters in which they are added, every
+lane shape, both column slices, more segments than the rule takes; several calls in a row (the counters start over by themselves),
+bit-identical through an alias, whose hub rows a fix-up launch adds, and within tolerance of the oracle."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2403_14853_amd as isp
+from gpu_util import assert_close, build, dev
+
+pytestmark = pytest.mark.gpu
+
+ENV = {"ISP_HUB_THRESHOLD": "16", "ISP_SEGMENT_LEN": "8", "ISP_BANDS": "1", "ISP_MID_THRESHOLD": "0"}
+
+
+def _graph(hub_lengths, n_rows, n_cols, seed, square=False):
+    rng = np.random.default_rng(seed)
+    deg = rng.integers(0, 5, n_rows)
+    deg[rng.permutation(n_rows)[:len(hub_lengths)]] = hub_lengths
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    rows = np.repeat(np.arange(n_rows), deg)
+    cols = rng.integers(0, n_cols, len(rows))
+    if square:  # most entries of the transpose in hub rows too
+        hot = rng.integers(0, 40, len(rows))
+        cols = np.where(rng.random(len(rows)) < 0.7, hot * (n_cols // 40), cols)
+    cols = cols[np.lexsort((cols, rows))].astype(np.int32)
+    values = rng.standard_normal(len(rows)).astype(np.float32)
+    saved = {k: os.environ.get(k) for k in ENV}
+    os.environ.update(ENV)
+    try:
+        A = build(indptr, cols, values, n_cols=n_cols)
+        isp.csr_transpose_cached(A)
+    finally:
+        for k, v in saved.items():
+            if v is None:
+                os.environ.pop(k)
+            else:
+                os.environ[k] = v
+    return indptr, cols, values, A, isp.csr_alias(A, max_d=320)
+
+
+FEW = list(range(17, 330, 8)) + [17, 20, 24, 25, 2_000, 2_001, 4_099]  # 3 to 513 segments
+MANY = [24] * 3_000
+
+
+@pytest.mark.parametrize("hubs, n_cols, widths", [
+    (FEW, 700, [3, 4, 16, 17, 32, 64, 65, 100, 128, 130, 200, 256, 301]),
+    (FEW, 82_000, [127, 128, 256]),   # 128 whole-line columns run as two slices
+    (MANY, 700, [8, 64, 100, 256]),
+])
+def test_spmm_and_mean(hubs, n_cols, widths):
+    indptr, cols, values, A, B = _graph(hubs, 4_000, n_cols, len(hubs) + n_cols)
+    info = A.info()
+    assert info["n_segments"] == sum((h + 7) // 8 for h in hubs) and (info["n_segments"] > 8_192) == (hubs is MANY)
+    length = np.maximum(np.diff(indptr), 1)[:, None]
+    for d in widths:
+        print("[case] %d segments, %d columns, d = %d" % (info["n_segments"], n_cols, d), flush=True)
+        for turn in range(3):
+            X = np.random.default_rng(10 * d + turn).standard_normal((n_cols, d)).astype(np.float32)
+            Xd = dev(X)
+            Y, Z = (torch.full((4_000, d), float("nan"), device="cuda") for _ in range(2))
+            isp.spmm(A, Xd, Y)
+            isp.spmm(B, Xd, Z)
+            assert torch.equal(Y, Z)
+            ref, mag = oracle.spmm(indptr, cols, values, X)
+            assert_close(Y, ref, mag, "spmm")
+            isp.spmm_reduce(A, Xd, Y, "mean")
+            isp.spmm_reduce(B, Xd, Z, "mean")
+            assert torch.equal(Y, Z)
+            assert_close(Y, ref / length, mag / length, "mean")
+    A.destroy()
+
+
+@pytest.mark.parametrize("hubs", [FEW, MANY])
+def test_fusedmm(hubs):
+    n = 4_000
+    indptr, cols, values, A, B = _graph(hubs, n, n, 5, square=True)
+    for d in (4, 16, 30, 64, 65, 128, 200, 256):
+        print("[case] fusedmm, %d hub rows, d = %d" % (len(hubs), d), flush=True)
+        for turn in range(2):
+            rng = np.random.default_rng(10 * d + turn)
+            X = (0.2 * rng.standard_normal((n, d))).astype(np.float32)
+            G = rng.standard_normal((n, d)).astype(np.float32)
+            Xd, Gd = dev(X), dev(G)
+            Y, Z = (torch.full((n, d), float("nan"), device="cuda") for _ in range(2))
+            isp.fusedmm(A, Xd, Y)
+            isp.fusedmm(B, Xd, Z)
+            assert torch.equal(Y, Z)
+            assert_close(Y, *oracle.fusedmm(indptr, cols, values, X), "fusedmm")
+            isp.fusedmm_backward(A, Xd, Gd, Y)
+            isp.fusedmm_backward(B, Xd, Gd, Z)
+            assert torch.equal(Y, Z)
+            assert_close(Y, *oracle.fusedmm_backward(indptr, cols, values, X, G), "fusedmm backward")
+    A.destroy()
