@@ -28,29 +28,31 @@ __global__ void __launch_bounds__(ISP_WG) k_fused_fixup_wg(isp_view A, int d, fl
   hub_fixup_wg<4, 1, false, ACC>(A, d, 0, Y, ldy, 0);
 }
 
-template <class P, int LPG, int W, bool ADDR32, bool TAIL>
+template <class P, int LPG, int W, bool ADDR32, bool TAIL, bool FINISH>
 __global__ void __launch_bounds__(ISP_WG) k_fused_grouped(isp_view A, const int64_t* __restrict__ indptr,
                                                           const int32_t* __restrict__ indices,
                                                           const float* __restrict__ values, typename P::args pa, int d,
                                                           float* __restrict__ Y, int64_t ldy) {
   __shared__ rn_lds lds;
-  fused_grouped_item<P, LPG, W, ADDR32, TAIL>(A, indptr, indices, values, pa, d, Y, ldy, lds);
+  fused_grouped_item<P, LPG, W, ADDR32, TAIL, FINISH>(A, indptr, indices, values, pa, d, Y, ldy, lds);
 }
 
 // LPG lanes with W floats each span the feature width: W * LPG >= d.
 // A32: every gather offset fits 32 bits.
 template <class P, int LPG, int W, bool A32>
 isp_status run_grouped(const isp_csr* A, const typename P::args& pa, int d, float* Y, int64_t ldy, hipStream_t s) {
-  isp_view v = A->v;
-  if (!hf_pays(A, v, d)) v.hub_done = nullptr;
+  const isp_view& v = A->v;
+  const bool finish = A32 && hf_pays(A, v);
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
-    if (d % 4) k_fused_grouped<P, LPG, W, A32, true><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, pa, d, Y, ldy);
-    else k_fused_grouped<P, LPG, W, A32, false><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, pa, d, Y, ldy);
+#define ISP_GO(TL, FN) k_fused_grouped<P, LPG, W, A32, TL, FN><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, pa, d, Y, ldy)
+    if (d % 4) { if (finish) ISP_GO(true, A32); else ISP_GO(true, false); }
+    else { if (finish) ISP_GO(false, A32); else ISP_GO(false, false); }
+#undef ISP_GO
     ISP_LAUNCH_CHECK();
   }
-  if (v.n_hub > 0 && !v.hub_done) {
+  if (v.n_hub > 0 && !finish) {
     k_fused_fixup_wg<P::ACCUMULATE><<<(unsigned)v.n_hub, ISP_WG, 0, s>>>(v, d, Y, ldy);
     ISP_LAUNCH_CHECK();
   }

@@ -42,7 +42,8 @@ struct policy_has_val2 : std::false_type {};
 template <class P>
 struct policy_has_val2<P, std::void_t<decltype(P::HAS_VAL2)>> : std::bool_constant<P::HAS_VAL2> {};
 
-template <class P, int LPG, int W, bool ADDR32, bool TAIL, class Lds>
+// FINISH: the launch puts hub rows together (hub_finish.h).
+template <class P, int LPG, int W, bool ADDR32, bool TAIL, bool FINISH = false, class Lds>
 __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __restrict__ indptr,
                                           const int32_t* __restrict__ indices, const float* __restrict__ values,
                                           const typename P::args& pa, int d, float* __restrict__ Y, int64_t ldy,
@@ -62,7 +63,7 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
   const item_range it = locate_item(A, indptr, item);
   if (it.skip) return;
   auto& L = lds.w[w];
-  const bool finish = !P::PER_ENTRY && it.is_seg && A.hub_done;
+  const bool finish = FINISH && it.is_seg;
   hub_ref H{0, 0, 0};
   if (finish) H.h = A.seg_hub[it.row];
   const rn_run R = rn_prepare<G>(it, indptr, indices, values, nullptr, L, lane);
@@ -238,7 +239,7 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
         if (finish) hf_store<N>(row, (unsigned)c0 * 4u, t);
         else store_vec<N>(row + c0, t);
       }
-      if (finish && hf_last(A, H, 0, lane)) {
+      if (FINISH && hf_last(A, H, 0, lane)) {
         float sum[W];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {

@@ -17,13 +17,14 @@ namespace isp_dev {
 
 constexpr int HF_SLICES = 2;     // counters per hub row: one per column slice of a launch
 
-// Whether the launch finishes its hub rows itself.  It does not where rows of more than 64 columns have very many segments,
-// two for every wavefront slot (which a fix-up's four wavefronts to a row add faster than the launch's last wavefronts).  us per SpMM
-// with the fix-up / without: 2 k rows, 20 k entries (52 segments): 16 columns 7.5 / 5.3, 128 9.1 / 6.6; 10 k, 300 k (2,523): 10.2 / 7.4
-// (32), 16.1 / 14.0 (128); 170 k, 1.7 M (6,583): 25.6 / 24.5, 68.4 / 67.9; 400 k, 4 M (5,987): 48.5 / 47.5, 171 / 170; 10 k, 1 M (13,911): 16.1 /
-// 15.2 (32), 20.8 / 20.0 (64), 31.0 / 31.7 (100), 44.4 / 46.0 (160); 40 k, 1.2 M (15,171): 27.5 / 26.0 (64), 61.1 / 62.4 (160).
-inline bool hf_pays(const isp_csr* A, const isp_view& v, int width) {
-  return v.n_seg <= 2 * A->wave_slots || width <= 64;
+// Whether a launch finishes its hub rows itself: not where it has more than two segments for every wavefront slot.  The fix-up's
+// wavefronts then have enough rows to fill the chip, and the launch spends longer in the chains (store, count, load) at the end
+// of its segments.  us with the fix-up / without, segments in brackets: SpMM, 16 and 128 columns: 2 k rows, 20 k entries (52) 7.5 / 5.3, 9.1 / 6.6;
+// 10 k, 300 k (2,523) 10.1 / 7.4, 16.1 / 14.0; 170 k, 1.7 M (6,583) 24.1 / 23.2, 68.4 / 67.9; 100 k, 4 M (8,192) 35.5 / 34.7, 112.1 /
+// 111.8; 10 k, 1 M (13,911) 16.1 / 15.1, 31.3 / 31.4; 20 k, 3 M (16,000) 26.0 / 26.1, 72.8 / 72.7; 60 k, 18 M (72,304) 114.8 / 122.4, 380 / 380;
+// FusedMM, 16 and 64 columns: 10 k, 300 k 12.3 / 9.3, 15.6 / 11.6; 20 k, 3 M 35.7 / 36.6, 56.5 / 56.5; 1 M, 17 M (39,440) 188 / 196, 375 / 373.
+inline bool hf_pays(const isp_csr* A, const isp_view& v) {
+  return v.hub_done && v.n_hub > 0 && v.n_seg <= 2 * A->wave_slots;
 }
 
 // A segment's row: its partial rows [s0, s1) and its counter.

@@ -37,7 +37,7 @@ struct isp_view {
   int32_t hub_t, seg_len;
   float* partials;         // n_seg * ISP_PARTIAL_TILE floats
   unsigned* hub_done;      // two counters per hub row, zero between launches (hub_finish.h); NULL: a fix-up launch adds
-                           // the segments (the packed layout's view, and handles with scratch of their own)
+                           // the segments (the packed layout's view, handles with scratch of their own)
   const float* inv_len;    // 1 / (stored entries of the row), 0 for an empty row; indexed by the rows of the
                            // handle's matrix (also in the view of a derived matrix)
   // Views of a derived matrix (packed SpMM layout) only: rows [n_real_rows, n_rows) are pieces of the handle's

@@ -80,6 +80,8 @@ isp_status launch_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int
 // ADDR32: every byte offset into X fits 32 bits and both factors of column * row-pitch fit 24 bits, so
 // the gather address is one full-rate 24-bit multiply-add on top of a scalar base pointer.
 // MEAN: finished rows are divided by their length (partial rows are not: their fix-up divides).
+// FINISH: hub rows are put together here (hub_finish.h).  A kernel of its own: launches that have none to finish ran 2 % longer
+// with that code in them (4 k rows, 37 k entries 4.41 -> 4.53 us).
 constexpr int SPMM_RING = 4;
 
 // On the packed layout, launches that gather more than three and a half lines of a row ask for LDS they do not use, so that a
@@ -94,7 +96,7 @@ constexpr int SPMM_RING = 4;
 //   2 (64 columns): 2326 / 2325;  1 (32): 1213 / 1248.
 constexpr unsigned SPMM_FOUR_PER_CU = 160 * 1024 / 4 - sizeof(rn_lds);
 
-template <int LPG, bool ADDR32, int VEC, bool MEAN, int CAP = GS_MAX_ENT>
+template <int LPG, bool ADDR32, int VEC, bool MEAN, bool FINISH, int CAP = GS_MAX_ENT>
 __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
     isp_view A, const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
     const float* __restrict__ values, const float* __restrict__ X, int64_t ldx, int d, int k_base, int n_slices,
@@ -113,7 +115,7 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
   // each adds into a partial row, named by piece_slot.  A block never mixes real rows and pieces.
   const bool pieces = !it.is_seg && (int64_t)it.row >= A.n_real_rows;
   const bool to_partial = it.is_seg || pieces;
-  const bool finish = VEC == 4 && it.is_seg && A.hub_done;
+  const bool finish = FINISH && it.is_seg;
   hub_ref H{0, 0, 0};
   if (finish) H.h = A.seg_hub[it.row];
   const rn_run R = rn_prepare<G>(it, indptr, indices, values,
@@ -187,8 +189,8 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
       if (finish) hf_store<N>(A.partials + (int64_t)it.row * ISP_PARTIAL_TILE, (unsigned)(col - k_base + idx0) * 4u, t);
       else store_vec<N>(row_of(it.row) + idx0, t);
     }
-    if constexpr (VEC == 4) {
-      if (finish && hf_last(A, H, slice, lane)) {
+    if constexpr (FINISH) {
+      if (hf_last(A, H, slice, lane)) {
         float t[4];
         hf_sum<LPG, CAP == GS_MAX_ENT ? 16 : 8>(A, H, (unsigned)(col - k_base) * 4u, lane, t);
         if (MEAN) {
@@ -238,9 +240,11 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
   const bool packed = A->has_packed && (!values_override || values_override_packed) &&
                       A->packed_block_cost + A->vp.hub_t <= GS_MAX_ENT &&
                       A->packed_block_cost / A->packed_row_cost <= GS_MAX_ROWS;
-  isp_view v = packed ? A->vp : A->v;
+  const isp_view& v = packed ? A->vp : A->v;
   const int width = n_slices * LPG * VEC < d - k_base ? n_slices * LPG * VEC : d - k_base;
-  if (VEC < 4 || n_slices > HF_SLICES || !hf_pays(A, v, width)) v.hub_done = nullptr;  // (a fix-up launch adds the hub rows)
+  const bool a32 = v.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
+                   ((uint64_t)v.n_cols * (uint64_t)ldx + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
+  const bool finish = VEC == 4 && a32 && n_slices <= HF_SLICES && hf_pays(A, v);  // (else a fix-up launch adds the hub rows)
   // (one value per stored entry, in the order of the view's entries)
   const float* vals = values_override ? (packed ? values_override_packed : values_override) : v.values;
   const int n_items = v.n_blocks + v.n_seg;
@@ -248,20 +252,21 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG) * (unsigned)n_slices;
     const unsigned spare = packed && 2 * isp_stage::line_sum((uintptr_t)(X + k_base), ldx, width) > 7 * isp_stage::ALIGN
                                ? SPMM_FOUR_PER_CU : 0u;
-    const bool a32 = v.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
-                     ((uint64_t)v.n_cols * (uint64_t)ldx + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
-#define ISP_GO(A32, MN)                                                                                        \
-  k_spmm_grouped<LPG, A32, VEC, MN><<<grid, ISP_WG, spare, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
+#define ISP_GO1(A32, MN, FN)                                                                                        \
+  k_spmm_grouped<LPG, A32, VEC, MN, FN><<<grid, ISP_WG, spare, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
                                                             n_slices, Y, ldy)
+#define ISP_GO(A32, MN) do { if (finish) ISP_GO1(A32, MN, A32 && VEC == 4); else ISP_GO1(A32, MN, false); } while (0)
     // (one group to a wavefront, 129 to 224 columns, has work for 14 per compute unit before seven at a time pay: 25 k columns,
     // 408 k entries, 208 columns (6.6 per unit) 31.4 us with five, 33.8 with seven; 17 k, 601 k: 176 (8.5) 34.7 / 36.7; 23 k, 1 M: 135 (17.2)
     // 51.2 / 46.8; 22 k, 862 k: 207 (14.8) 51.0 / 49.8)
     if (VEC == 4 && a32 && !packed && rn_small_tables(A, v, width, grid, LPG == ISP_WAVE ? 14 : 5)) {
-#define ISP_SMALL(MN)                                                                                              \
-  k_spmm_grouped<LPG, true, 4, MN, RN_SMALL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
+#define ISP_SMALL1(MN, FN)                                                                                              \
+  k_spmm_grouped<LPG, true, 4, MN, FN, RN_SMALL><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
                                                                      n_slices, Y, ldy)
+#define ISP_SMALL(MN) do { if (finish) ISP_SMALL1(MN, true); else ISP_SMALL1(MN, false); } while (0)
       if (mean_mode == 1) ISP_SMALL(true); else ISP_SMALL(false);
 #undef ISP_SMALL
+#undef ISP_SMALL1
     } else if constexpr (VEC < 4) {  // scalar lanes are only dispatched with 32-bit addressing and for the plain sum
       ISP_GO(true, false);
     } else if (mean_mode == 1) {
@@ -270,9 +275,10 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
       if (a32) ISP_GO(true, false); else ISP_GO(false, false);
     }
 #undef ISP_GO
+#undef ISP_GO1
     ISP_LAUNCH_CHECK();
   }
-  if (v.n_hub > 0 && !v.hub_done) {
+  if (v.n_hub > 0 && !finish) {
     // the columns this launch covered: [k_base, min(d, k_base + n_slices * LPG * VEC))
     const int d_hi = (k_base + n_slices * LPG * VEC < d) ? k_base + n_slices * LPG * VEC : d;
     const int split = packed ? PACKED_SPLIT : 0;
