@@ -30,6 +30,67 @@ __device__ inline float group_allreduce(float v) {
   return v;
 }
 
+// Four sums of LPG lanes at once: of a value per lane and step (p0 ... p3) each lane gets the group's total of step
+// group_step<LPG>(lane), and of the lanes with the same total group_step_owner<LPG> says one.  A stage halves the
+// values while there are several (a lane keeps one and hands the other to its partner), so four totals take 10 or 11 instructions
+// where four sums after one another take 12 (8 lanes) to 24 (64), and what is computed from a total is computed once,
+// not in every lane of the group.
+template <int LPG>
+__device__ __forceinline__ int group_step(int lane) {
+  if constexpr (LPG == 8) return (lane >> 2 & 1) | (lane & 2);
+  else if constexpr (LPG == 16) return (lane >> 3 & 1) | (lane >> 1 & 2);
+  else if constexpr (LPG == 32) return (lane >> 4 & 1) | (lane >> 2 & 2);
+  else return (lane >> 5 & 1) | (lane >> 3 & 2);
+}
+template <int LPG>
+__device__ __forceinline__ bool group_step_owner(int lane) { return (lane & (LPG / 4 - 1)) == 0; }
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_of(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+// lanes with `up` keep b and get their partner's b, the others a; CTRL moves a value to the partner
+template <int CTRL>
+__device__ __forceinline__ float pair_sum(float a, float b, bool up) { return (up ? b : a) + dpp_of<CTRL>(up ? a : b); }
+// (exchanges between rows of 16 and 32 lanes: one instruction hands b's even rows to a and a's odd rows to b)
+__device__ __forceinline__ float pair_sum_16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float pair_sum_32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_ROR8 = 0x128;  // (mirror: the other quad of 8 lanes)
+
+template <int LPG>
+__device__ __forceinline__ float group_sum_steps(float p0, float p1, float p2, float p3, int lane) {
+  float v;
+  if constexpr (LPG == 8) {
+    v = pair_sum<DPP_XOR2>(pair_sum<DPP_HALF_MIRROR>(p0, p1, lane & 4), pair_sum<DPP_HALF_MIRROR>(p2, p3, lane & 4), lane & 2);
+    return v + dpp_of<DPP_XOR1>(v);
+  } else if constexpr (LPG == 16) {
+    v = pair_sum<DPP_HALF_MIRROR>(pair_sum<DPP_ROR8>(p0, p1, lane & 8), pair_sum<DPP_ROR8>(p2, p3, lane & 8), lane & 4);
+  } else if constexpr (LPG == 32) {
+    v = pair_sum<DPP_ROR8>(pair_sum_16(p0, p1), pair_sum_16(p2, p3), lane & 8);
+    v += dpp_of<DPP_HALF_MIRROR>(v);
+  } else {
+    v = pair_sum_16(pair_sum_32(p0, p1), pair_sum_32(p2, p3));
+    v += dpp_of<DPP_ROR8>(v);
+    v += dpp_of<DPP_HALF_MIRROR>(v);
+  }
+  v += dpp_of<DPP_XOR1>(v);
+  return v + dpp_of<DPP_XOR2>(v);
+}
+// of four steps' values, step group_step(lane)'s
+template <int LPG>
+__device__ __forceinline__ float group_step_value(float p0, float p1, float p2, float p3, int lane) {
+  const int s = group_step<LPG>(lane);
+  const float lo = s & 1 ? p1 : p0, hi = s & 1 ? p3 : p2;
+  return s & 2 ? hi : lo;
+}
+
 // Sum W values per lane over the G = 64 / LPG groups (lanes with equal lane % LPG), leaving the sums spread over
 // the groups instead of complete in one: a stage that pairs lanes `O` apart splits the values in two halves,
 // each lane of a pair keeps one half and receives the partner's share of it, so the stages move W/2 + W/4 + ...

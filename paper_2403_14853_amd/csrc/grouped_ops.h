@@ -19,7 +19,8 @@ namespace isp_dev {
 // by the entry's matrix row); RING4 / RING8 steps in flight with one / two float4 per lane;
 // args { src[NSRC], lds_[NSRC], rowop[NROW], ldr[NROW], out_entry };
 // either edge<LPG>(args, a, src, rowop, acc, lane_on) accumulating into the row's result, or (PER_ENTRY)
-// entry<LPG>(a, src, rowop, lane_on) returning the value stored for the entry.
+// partial(src, rowop, lane_cols) returning the lane's share of a sum over the group, which times the entry's value is stored
+// for the entry.
 // A policy with HAS_VAL2 = true also gets a second value per stored entry, args::val2[p] (a parallel array in
 // the order of the matrix's entries; null = all ones), as an extra argument of edge().
 // ADDR32: every byte offset into the gathered operands fits 32 bits and both factors of column * row pitch
@@ -154,6 +155,15 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
 
   bool carried = R.mid;  // the next row to end began in an earlier run
   bool ended = false;    // a row has ended in this run
+  // PER_ENTRY: four steps' shares are summed over the group at a time.  A result is parked in its entry's LDS slot (the entry
+  // has been read) and written out in one coalesced sweep when the item is done.
+  float share[4] = {0.f, 0.f, 0.f, 0.f}, share_a[4] = {0.f, 0.f, 0.f, 0.f};
+  auto park = [&](int s0, int n) {  // steps [s0, s0 + n) of the run
+    const float val = group_step_value<LPG>(share_a[0], share_a[1], share_a[2], share_a[3], lane) *
+                      group_sum_steps<LPG>(share[0], share[1], share[2], share[3], lane);
+    const int k = group_step<LPG>(lane);
+    if (group_step_owner<LPG>(lane) && k < n) L.ent[R.start + s0 + k].y = __float_as_int(val);
+  };
   // SEG (a hub segment: one matrix row for the whole item): the row operand is loaded once and stays in
   // registers.  Row blocks issue a load with every step (load_first), FIRST_ONLY or not, which keeps their loop free
   // of row-change stalls.
@@ -167,7 +177,8 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
     }
     float x[RING][NSRC][W], r[RING][NR + 1][W], a2[RING];
     bool first = true;  // the step to take next is its row's first in this run
-    rn_stream<RING, !SEG && (!P::PER_ENTRY || FIRST_ONLY), !SEG, CHUNK>(
+    bool firsts[RING];  // PER_ENTRY, where nothing else happens at row ends: the same, kept since the step was requested
+    rn_stream<RING, !SEG && !P::PER_ENTRY, !SEG, CHUNK>(
         L, R,
         [&](int u, int c, int s, int row, bool in_first) {
 #pragma unroll
@@ -175,6 +186,7 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
           if constexpr (!SEG) {
 #pragma unroll
             for (int k = 0; k < NROW; ++k) load_first(pa.rowop[k], pa.ldr[k], row, in_first, r[u][k]);
+            firsts[u] = in_first;
           }
           if constexpr (policy_has_val2<P>::value) {
             // (a step past the run's end reads the run's first value: a valid position)
@@ -182,9 +194,9 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
             if (pa.val2) a2[u] = pa.val2[it.p + (s < R.cnt ? R.start + s : 0)];
           }
         },
-        [&](int u, float a, int s) {
+        [&](auto u, float a, int s) {
           if constexpr (!SEG) {
-            if (first || !FIRST_ONLY) {
+            if ((P::PER_ENTRY ? firsts[u] : first) || !FIRST_ONLY) {
 #pragma unroll
               for (int k = 0; k < NROW; ++k)
 #pragma unroll
@@ -193,10 +205,11 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
             first = false;
           }
           if constexpr (P::PER_ENTRY) {
-            // one output per stored entry, parked in the entry's LDS slot (its value has been read) and written
-            // out in one coalesced sweep when the item is done
-            const float val = P::template entry<LPG, W, TAIL>(a, x[u], rS, lc);
-            if (q == 0) L.ent[R.start + s].y = __float_as_int(val);
+            constexpr int k = decltype(u)::value % 4;
+            share[k] = P::template partial<W, TAIL>(x[u], rS, lc);
+            share_a[k] = a;
+            asm volatile("" : "+v"(share[k]));  // (else the shares are formed with their sum, and their operands held until then)
+            if constexpr (k == 3) park(s - 3, 4);
           } else if constexpr (policy_has_val2<P>::value) {
             P::template edge<LPG, W, TAIL>(pa, a, a2[u], x[u], rS, acc, lc);
           } else {
@@ -205,7 +218,6 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
         },
         [&](int, int row) {
           first = true;
-          if constexpr (P::PER_ENTRY) return;
 #pragma unroll
           for (int v = 0; v < W; ++v) head[v] = carried ? acc[v] : head[v];
           if (!carried) store_row(row, acc);
@@ -218,6 +230,8 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
   if (it.is_seg) run(std::true_type{}); else run(std::false_type{});
 
   if constexpr (P::PER_ENTRY) {
+    static_assert(RING % 4 == 0, "four steps at a time");
+    if (R.cnt & 3) park(R.cnt & ~3, R.cnt & 3);
     wave_lds_sync();
     const int n_ent = (int)(it.p_end - it.p);
     for (int i = lane; i < n_ent; i += ISP_WAVE) {

@@ -188,7 +188,7 @@ struct rn_cursor {
 };
 
 // Stream the runs.  load(u, col, s, row, first): request what ring slot u needs of entry s of the run, which lies in row `row`
-// (ROWS only: else 0);  add(u, a, s): take slot u into the running result, a the entry's value;  end_row(k, row): the
+// (ROWS only: else 0);  add(u, a, s): take slot u (a compile-time constant) into the running result, a the entry's value;  end_row(k, row): the
 // k-th non-empty row is complete in this lane's group, its output row is `row` (ENDS only; called by the lanes it
 // concerns only).  RING steps are in flight per lane.
 // A round of RING steps is consumed while the next one is requested, slot by slot, into the same registers; the
@@ -215,7 +215,7 @@ __device__ __forceinline__ void rn_stream(const Lds& L, const rn_run& R, Load&& 
       if (in_first) in.advance(L, R);
     }
   };
-  auto take = [&](int u, int s0) {
+  auto take = [&](auto u, int s0) {
     add(u, a[u], s0 + u);
     if constexpr (ENDS)
       if (out.end == s0 + u) {

@@ -98,9 +98,9 @@ struct sddmm_policy {
   static constexpr int NSRC = 1, NROW = 1, RING4 = 4, RING8 = 4;
   static constexpr bool PER_ENTRY = true, ACCUMULATE = false, ADD = ADD_;
   struct args { const float* src[1]; int64_t lds_[1]; const float* rowop[1]; int64_t ldr[1]; float* out_entry; };
-  template <int LPG, int W, bool TAIL>
-  __device__ static inline float entry(float a, const float (&x)[1][W], const float (&r)[1][W], const lane_cols<W / 4, TAIL>& lc) {
-    return a * group_allreduce<LPG>(dotw<W, TAIL>(r[0], x[0], lc));
+  template <int W, bool TAIL>
+  __device__ static inline float partial(const float (&x)[1][W], const float (&r)[1][W], const lane_cols<W / 4, TAIL>& lc) {
+    return dotw<W, TAIL>(r[0], x[0], lc);
   }
 };
 
