@@ -13,7 +13,7 @@
 // operand: Section 3.5).
 #include <limits.h>
 #include <new>
-#include "block_scan.h"
+#include "digit_scan.h"
 #include "host_slot.h"
 #include "hub_finish.h"
 #include "stage_rule.h"
@@ -463,57 +463,70 @@ __device__ __forceinline__ int4 segment_item(const item_tables& I, int s) {
   return make_int4(I.seg_begin[s], (int)p_end, s, hr);
 }
 
-// Up to SO_SMALL segments: schedule order in one launch, every segment counting those before it (by first column, then
+// Up to SO_RANK segments: schedule order in one launch, every segment counting those before it (by first column, then
 // number).  SO_SMALL^2 comparisons are 1.5 us of the chip's vector ALUs if all of it works on them, hence few segments per
-// workgroup (5,000 segments: 11.4 us at 64, which left most of the chip idle, 7.4 at 16); the radix sort below is five
-// launches per digit (a matrix of 1 M entries has about 5,000 segments: 100 us), a bitonic sort in one workgroup took 88 us.
-constexpr int SO_SMALL = 8192;
+// workgroup (5,000 segments: 11.4 us at 64, which left most of the chip idle, 7.4 at 16); a bitonic sort in one workgroup took 88 us.
+// The radix sort below is three launches per digit, which beyond SO_SMALL keys cost the host more than the ranking the
+// chip, up to twice as many.  us for a graph seen once (two partitions, two SpMMs), ranked / sorted / sorted in five launches per
+// digit: 4 M entries, 100 k rows (some 8,200 segments) 390 / 425 / 448; 8 M, 400 k (11,242) 807 / 874 / 915; 3 M, 20 k (16,013) 353 /
+// 373 / 403; 7 M, 60 k (20,754) 574 / 555; 15 M, 50 k (67,333), 32 columns - / 913 / 953.
+constexpr int SO_SMALL = 8192;  // keys in LDS at a time, and the most that is ranked before their number is known on the host
+constexpr int SO_RANK = 2 * SO_SMALL;
 constexpr int SO_SEGS = 16;     // segments per workgroup, one per lane of 16
 constexpr int SO_THREADS = 1024;
-// The same launch writes the work items: a segment's place is known with its rank, and workgroups beyond those of the segments
-// write the row blocks' (max_items bounds what the tables hold).  The counters are left in host_ctr.
+// The same launch writes the work items: a segment's place is known with its rank, and workgroups beyond the first seg_wgs,
+// those of the segments, write the row blocks' (max_items bounds what the tables hold).  The counters are left in host_ctr.
+// MANY: more keys than LDS takes.
+template <bool MANY>
 __global__ void __launch_bounds__(SO_THREADS) k_seg_rank(const int32_t* __restrict__ key,
                                                          const build_counters* __restrict__ ctr, int32_t* __restrict__ order,
                                                          item_tables I, int64_t max_items, build_counters* __restrict__ host_ctr,
-                                                         int4* __restrict__ desc) {
+                                                         int4* __restrict__ desc, int seg_wgs) {
   constexpr int PER = SO_SMALL / SO_THREADS, WAVES = SO_THREADS / ISP_WAVE, SHARES = SO_THREADS / SO_SEGS;
   __shared__ __align__(16) int keys[SO_SMALL];
   __shared__ int part[WAVES][SO_SEGS];
   if (host_ctr && blockIdx.x == 0 && threadIdx.x == 0) *host_ctr = *ctr;
   const int n = ctr->n_seg, n_blocks = ctr->n_blocks;
   // (a malformed matrix has no bounds to rely on; the rest the host sees to)
-  if (ctr->err || n > SO_SMALL || (int64_t)n_blocks + n > max_items) return;
-  if ((int)blockIdx.x >= SO_SMALL / SO_SEGS) {
-    const int b = ((int)blockIdx.x - SO_SMALL / SO_SEGS) * SO_THREADS + (int)threadIdx.x;
+  if (ctr->err || n > seg_wgs * SO_SEGS || (int64_t)n_blocks + n > max_items) return;
+  if ((int)blockIdx.x >= seg_wgs) {
+    const int b = ((int)blockIdx.x - seg_wgs) * SO_THREADS + (int)threadIdx.x;
     if (b < n_blocks) desc[b] = block_item(I, b);
     return;
   }
   if ((int)blockIdx.x * SO_SEGS >= n) return;
-  int kk[PER];  // (all of them on their way together)
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int j = u * SO_THREADS + threadIdx.x;
-    kk[u] = j < n ? key[j] : INT_MAX;
-  }
-#pragma unroll
-  for (int u = 0; u < PER; ++u) keys[u * SO_THREADS + threadIdx.x] = kk[u];
-  __syncthreads();
   const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x / ISP_WAVE;
   const int s = blockIdx.x * SO_SEGS + (threadIdx.x & (SO_SEGS - 1));
-  const int k = s < n ? keys[s] : 0;
+  const int k = s < n ? key[s] : 0;
+  int kk[PER];  // (all of them on their way together)
+  auto request = [&](int base) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int j = base + u * SO_THREADS + threadIdx.x;
+      kk[u] = j < n ? key[j] : INT_MAX;
+    }
+  };
+  request(0);
   // Share h of a segment's comparisons: every SHARES-th four keys.  Keys of lower-numbered segments count when equal,
   // others only when smaller (columns are below 2^31 - 1); the four around the segment itself are put right at the end.
   const int4* __restrict__ k4 = reinterpret_cast<const int4*>(keys);
-  const int n4 = (n + 3) / 4, own = s / 4;
   int rank = 0;
+  for (int base = 0; base < (MANY ? n : 1); base += SO_SMALL) {
+    if (MANY && base > 0) __syncthreads();  // (the keys before these have been compared)
+#pragma unroll
+    for (int u = 0; u < PER; ++u) keys[u * SO_THREADS + threadIdx.x] = kk[u];
+    __syncthreads();
+    if (MANY && base + SO_SMALL < n) request(base + SO_SMALL);
+    const int left = n - base < SO_SMALL ? n - base : SO_SMALL, n4 = (left + 3) / 4, own = s / 4 - base / 4;
 #pragma unroll 4
-  for (int j = threadIdx.x / SO_SEGS; j < n4; j += SHARES) {
-    const int4 kj = k4[j];
-    const int t = k + (j < own ? 1 : 0);
-    rank += (kj.x < t) + (kj.y < t) + (kj.z < t) + (kj.w < t);
+    for (int j = threadIdx.x / SO_SEGS; j < n4; j += SHARES) {
+      const int4 kj = k4[j];
+      const int t = k + (j < own ? 1 : 0);
+      rank += (kj.x < t) + (kj.y < t) + (kj.z < t) + (kj.w < t);
+    }
+    if (threadIdx.x < SO_SEGS && own >= 0 && own < n4)
+      for (int j = own * 4; j < s - base; ++j) rank += keys[j] == k;
   }
-  if (threadIdx.x < SO_SEGS)
-    for (int j = own * 4; j < s; ++j) rank += keys[j] == k;
 #pragma unroll
   for (int o = SO_SEGS; o < ISP_WAVE; o <<= 1) rank += __shfl_xor(rank, o);
   if (lane < SO_SEGS) part[w][lane] = rank;
@@ -530,6 +543,7 @@ __global__ void __launch_bounds__(SO_THREADS) k_seg_rank(const int32_t* __restri
 // ---- schedule order of the segments: stable radix sort (8-bit digits) by first column -----------------
 constexpr int SO_TILE = 256;
 constexpr int SO_RADIX = 256;
+static_assert(SO_TILE == BS_THREADS && SO_RADIX == BS_THREADS, "a digit per thread");
 
 __global__ void __launch_bounds__(SO_TILE) k_seg_hist(const int32_t* __restrict__ key, int n_seg, int shift, int n_tiles,
                                                       int32_t* __restrict__ table) {
@@ -546,8 +560,11 @@ __global__ void __launch_bounds__(SO_TILE) k_seg_hist(const int32_t* __restrict_
 __global__ void __launch_bounds__(SO_TILE) k_seg_scatter(const int32_t* __restrict__ key_in,
                                                          const int32_t* __restrict__ val_in, int n_seg, int shift,
                                                          int n_tiles, const int32_t* __restrict__ table_scanned,
+                                                         const int32_t* __restrict__ digit_total,
                                                          int32_t* __restrict__ key_out, int32_t* __restrict__ val_out) {
-  __shared__ int digits[SO_TILE];
+  __shared__ int digits[SO_TILE], start[SO_RADIX];  // start: elements with a smaller digit
+  int all;
+  start[threadIdx.x] = block_exclusive_scan<int>(digit_total[threadIdx.x], &all);
   const int s = blockIdx.x * SO_TILE + threadIdx.x;
   const int key = s < n_seg ? key_in[s] : 0;
   const int dg = s < n_seg ? (key >> shift) & (SO_RADIX - 1) : -1;
@@ -556,7 +573,7 @@ __global__ void __launch_bounds__(SO_TILE) k_seg_scatter(const int32_t* __restri
   if (dg < 0) return;
   int rank = 0;  // earlier elements of this tile with the same digit
   for (int t = 0; t < (int)threadIdx.x; ++t) rank += (digits[t] == dg);
-  const int dst = table_scanned[dg * n_tiles + blockIdx.x] + rank;
+  const int dst = start[dg] + table_scanned[dg * n_tiles + blockIdx.x] + rank;
   key_out[dst] = key;
   val_out[dst] = val_in ? val_in[s] : s;
 }
@@ -704,7 +721,7 @@ static_assert(sizeof(build_counters) <= host_slot::SIZE, "the counters fit a slo
 // ---- workspace layout ------------------------------------------------------------------------------------
 struct ws_layout {
   size_t counters, cost, hubflag, nseg, mark, tile_cost, tile_hub, tile_seg, tile_mark, tile_stat, tile_err;
-  size_t blk_row, hub_rows, hub_seg_ptr, hub_done, seg_hub, seg_begin, seg_key[2], seg_order[2], so_table, so_scanned, so_tmp;
+  size_t blk_row, hub_rows, hub_seg_ptr, hub_done, seg_hub, seg_begin, seg_key[2], seg_order[2], so_table, so_total;
   size_t inv_len, item_desc, partials, total;
   int64_t max_blocks, max_hub, max_seg;
 };
@@ -744,8 +761,7 @@ ws_layout make_layout(int64_t n_rows, int64_t nnz, const partition_params& pp, s
   }
   const int64_t so_tbl = (int64_t)SO_RADIX * ((max_seg + SO_TILE - 1) / SO_TILE + 1);
   L.so_table = take((size_t)(so_tbl + 1) * 4);
-  L.so_scanned = take((size_t)(so_tbl + 1) * 4);
-  L.so_tmp = take(isp_scan_tmp_bytes(so_tbl + 1));
+  L.so_total = take((size_t)SO_RADIX * 4);
   L.inv_len = take((size_t)(n_rows + 1) * 4);
   L.item_desc = take((size_t)(max_blocks + max_seg + 2) * 16);
   // (a derived matrix has no hub rows of its own, hence no partial rows)
@@ -880,7 +896,7 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   build_counters* host_ctr = small ? (build_counters*)slot.get() : nullptr;
   if (small) {
     const unsigned wgs = SO_SMALL / SO_SEGS + (unsigned)((L.max_blocks + SO_THREADS - 1) / SO_THREADS);
-    k_seg_rank<<<wgs, SO_THREADS, 0, s>>>(seg_key[0], ctr, seg_ord[0], items, max_items, host_ctr, item_desc);
+    k_seg_rank<false><<<wgs, SO_THREADS, 0, s>>>(seg_key[0], ctr, seg_ord[0], items, max_items, host_ctr, item_desc, SO_SMALL / SO_SEGS);
     ISP_LAUNCH_CHECK();
   }
   if (!host_ctr) ISP_HIP(hipMemcpyAsync(&h, ctr, sizeof(h), hipMemcpyDeviceToHost, s));
@@ -891,11 +907,17 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   if (h.n_blocks > L.max_blocks || h.n_hub > L.max_hub || h.n_seg > L.max_seg)
     return isp_fail(ISP_EINVAL, "internal: partition exceeds its bounds (%d/%lld blocks, %d/%lld hubs, %d/%lld segs)",
                     h.n_blocks, (long long)L.max_blocks, h.n_hub, (long long)L.max_hub, h.n_seg, (long long)L.max_seg);
-  if (!small || h.n_seg > SO_SMALL) {
+  if ((!small || h.n_seg > SO_SMALL) && h.n_seg <= SO_RANK) {
+    const int seg_wgs = (h.n_seg + SO_SEGS - 1) / SO_SEGS, wgs = seg_wgs + (h.n_blocks + SO_THREADS - 1) / SO_THREADS;
+    if (wgs > 0) {
+      k_seg_rank<true><<<(unsigned)wgs, SO_THREADS, 0, s>>>(seg_key[0], ctr, seg_ord[0], items, max_items, nullptr, item_desc, seg_wgs);
+      ISP_LAUNCH_CHECK();
+    }
+  } else if (!small || h.n_seg > SO_SMALL) {
     if (h.n_seg > 0) {  // schedule order: by first column, equal ones in order of position (stable)
       const int n_tiles = (h.n_seg + SO_TILE - 1) / SO_TILE;
       int32_t* table = (int32_t*)(base + L.so_table);
-      int32_t* scanned = (int32_t*)(base + L.so_scanned);
+      int32_t* total = (int32_t*)(base + L.so_total);
       int bits = 1;  // the keys are columns (< n_cols)
       while (bits < 31 && ((int64_t)1 << bits) < n_cols) ++bits;
       const int n_pass = (bits + 7) / 8;
@@ -904,9 +926,9 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
         const int32_t* vin = pass == 0 ? nullptr : seg_ord[pass & 1];
         k_seg_hist<<<n_tiles, SO_TILE, 0, s>>>(kin, h.n_seg, 8 * pass, n_tiles, table);
         ISP_LAUNCH_CHECK();
-        isp_status st;
-        if ((st = isp_scan_i32_to_i32(table, scanned, (int64_t)SO_RADIX * n_tiles, base + L.so_tmp, s)) != ISP_OK) return st;
-        k_seg_scatter<<<n_tiles, SO_TILE, 0, s>>>(kin, vin, h.n_seg, 8 * pass, n_tiles, scanned, seg_key[(pass + 1) & 1],
+        k_digit_scan<<<SO_RADIX, BS_THREADS, 0, s>>>(table, n_tiles, total);
+        ISP_LAUNCH_CHECK();
+        k_seg_scatter<<<n_tiles, SO_TILE, 0, s>>>(kin, vin, h.n_seg, 8 * pass, n_tiles, table, total, seg_key[(pass + 1) & 1],
                                                   seg_ord[(pass + 1) & 1]);
         ISP_LAUNCH_CHECK();
       }

@@ -136,7 +136,6 @@ isp_status isp_check_dense(const void* p, int64_t ld, int32_t d, int64_t rows, c
 // isp_scan_tmp_bytes(n) bytes.  in and out may not alias.
 size_t isp_scan_tmp_bytes(int64_t n);
 isp_status isp_scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, void* tmp, hipStream_t s);
-isp_status isp_scan_i32_to_i32(const int32_t* in, int32_t* out, int64_t n, void* tmp, hipStream_t s);
 
 // Partial rows of v's scratch that any operation writes: FusedMM wider than 256 columns has up to four to a segment.
 static inline int64_t isp_busy_rows(const isp_csr* A) {

@@ -88,6 +88,3 @@ isp_status isp_scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, void*
   return scan_impl<int32_t, int64_t>(in, out, n, tmp, s);
 }
 
-isp_status isp_scan_i32_to_i32(const int32_t* in, int32_t* out, int64_t n, void* tmp, hipStream_t s) {
-  return scan_impl<int32_t, int32_t>(in, out, n, tmp, s);
-}

@@ -8,7 +8,7 @@
 // (digit, tile) -> scatter with ranks taken in source order.  Integer work only, no atomics on
 // anything order-dependent.
 #include <new>
-#include "block_scan.h"
+#include "digit_scan.h"
 #include "host_slot.h"
 #include "stage_rule.h"
 
@@ -61,35 +61,6 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_hist(const int32_t* __rest
     if (base + k * RS_THREADS + threadIdx.x < n) atomicAdd(&hist[(key[k] >> shift) & (radix - 1)], 1);
   __syncthreads();
   for (int i = threadIdx.x; i < radix; i += RS_THREADS) table[(int64_t)i * n_tiles + blockIdx.x] = hist[i];
-}
-
-// One workgroup per digit: exclusive prefix of its counts over the tiles, in place, and the digit's total.  (The prefix
-// over the digits is a few hundred numbers, which every scatter workgroup adds up for itself: one launch instead of
-// the three of a device-wide scan.)
-__global__ void __launch_bounds__(RS_THREADS) k_digit_scan(int32_t* __restrict__ table, int n_tiles,
-                                                           int32_t* __restrict__ digit_total) {
-  int32_t* __restrict__ t = table + (int64_t)blockIdx.x * n_tiles;
-  int carry = 0;
-  constexpr int PER = 8;
-  for (int base = 0; base < n_tiles; base += RS_THREADS * PER) {
-    int v[PER], sum = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = base + (int)threadIdx.x * PER + k;
-      v[k] = i < n_tiles ? t[i] : 0;
-      sum += v[k];
-    }
-    int tot;
-    int run = carry + block_exclusive_scan<int>(sum, &tot);
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = base + (int)threadIdx.x * PER + k;
-      if (i < n_tiles) t[i] = run;
-      run += v[k];
-    }
-    carry += tot;
-  }
-  if (threadIdx.x == 0) digit_total[blockIdx.x] = carry;
 }
 
 // Stable scatter of one pass; the records travel as four parallel arrays (column key, source position,

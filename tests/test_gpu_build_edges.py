@@ -116,6 +116,12 @@ def test_many_segments(n_hub):
         os.environ.pop("ISP_HUB_THRESHOLD")
 
 
+@pytest.mark.parametrize("n_hub", [12345, 16384, 16385])
+def test_segments_beyond_one_table(n_hub):
+    """More keys than the ranking holds at a time, as many as it takes, and one more: the radix sort."""
+    test_many_segments(n_hub)
+
+
 @pytest.mark.parametrize("mid,with_values", [(0, True), (64, True), (64, False)])
 def test_large_symmetric(mid, with_values):
     print("threshold %d" % mid, flush=True)
