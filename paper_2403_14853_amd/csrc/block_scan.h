@@ -47,6 +47,7 @@ __device__ inline T block_exclusive_scan(T v, T* total) {
 template <typename T>
 __device__ inline T block_sum_of(const T* __restrict__ a, int n) {
   T s = 0;
+#pragma unroll 8
   for (int i = threadIdx.x; i < n; i += BS_THREADS) s += a[i];
   T tot;
   block_exclusive_scan<T>(s, &tot);

@@ -74,6 +74,11 @@ int isp_wave_slots() {
 
 namespace {
 
+__device__ __forceinline__ int64_t wave_uniform(int64_t v) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)v), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return (int64_t)((unsigned long long)hi << 32 | lo);
+}
+
 // Pieces of a hub row: its entries [a, b) cut where the columns cross band boundaries.  A row of degree
 // deg is cut into br = the largest power of two <= min(bands, deg / min_piece) coarse bands, each made of
 // bands / br fine bands of width ceil(n_cols / bands).  The whole wavefront calls this with the same row
@@ -82,7 +87,9 @@ namespace {
 // the scheduling benefit is lost, never correctness.
 __device__ inline void wave_hub_pieces(const int32_t* __restrict__ indices, int64_t a, int64_t b, int64_t n_cols,
                                        const partition_params& pp, int lane, int* samples, int64_t* first, int64_t* last) {
-  // (positions and columns fit 32 bits; relative to the row from here on)
+  // (the row is the wavefront's: kept in scalar registers; positions and columns fit 32 bits, relative to the row from here on)
+  a = wave_uniform(a);
+  b = wave_uniform(b);
   const int deg = (int)(b - a);
   const int32_t* __restrict__ row = indices + a;
   const int br = hub_bands(deg, pp);
@@ -99,10 +106,12 @@ __device__ inline void wave_hub_pieces(const int32_t* __restrict__ indices, int6
     const int gap = (int)(((unsigned)deg + CUT_COUNT * ISP_WAVE - 1u) / (CUT_COUNT * ISP_WAVE));
     const int ns = (int)((unsigned)(deg + gap - 1) / (unsigned)gap);
     int c[CUT_COUNT];
+    const unsigned lane_byte = (unsigned)lane * ((unsigned)gap * 4u);  // (a scalar base and one offset for all: gap is 2^21 at most)
 #pragma unroll
     for (int k = 0; k < CUT_COUNT; ++k) {
-      const int i = k * ISP_WAVE + lane;
-      c[k] = i < ns ? row[i * gap] : 0;
+      const char* from = reinterpret_cast<const char*>(row + (int64_t)k * ISP_WAVE * gap);
+      c[k] = 0;
+      if (k * ISP_WAVE + lane < ns) c[k] = *reinterpret_cast<const int32_t*>(from + lane_byte);
     }
     wave_lds_sync();  // (the row before this one has been searched)
 #pragma unroll
@@ -176,25 +185,40 @@ constexpr int RPW_SMALL = 16, RPW_LARGE = ISP_WAVE;
 // Pass 1.  Per row: degree, class, cost, segment count; indptr checks; column indices in [0, n_cols) (check).  Workgroups beyond the
 // tiles only check indices.
 template <int RPW>
-__global__ void __launch_bounds__(BS_THREADS) k_row_pass(const int64_t* __restrict__ indptr,
+__global__ void __launch_bounds__(BS_THREADS, 7) k_row_pass(const int64_t* __restrict__ indptr,
                                                   const int32_t* __restrict__ indices, int64_t n_rows, int64_t n_cols,
                                                   int64_t nnz, partition_params pp, bool check, row_tiles T,
                                                   int32_t* __restrict__ cost, int32_t* __restrict__ hubflag,
                                                   int32_t* __restrict__ nseg, float* __restrict__ inv_len) {
-  __shared__ unsigned long long s_stat[BS_THREADS / ISP_WAVE][STATS];
-  __shared__ unsigned long long s_cost[BS_THREADS / ISP_WAVE];
-  __shared__ int s_seg[BS_THREADS / ISP_WAVE], s_hub[BS_THREADS / ISP_WAVE], s_hubs[BS_THREADS / ISP_WAVE];
+  // The tile's numbers: STATS of them, then cost, segments, hub rows (a tile's cost: nnz + two units per row, below 2^32).  Added up
+  // in LDS: sums over the lanes held 14 values per lane and with them four workgroups to a compute unit instead of seven, too few for all
+  // tiles of 100 k rows at once (1 M entries: 14.5 us, now 11.2).
+  constexpr int COST = STATS, SEGS = STATS + 1, HUBS = STATS + 2;
+  __shared__ unsigned s_sum[STATS + 3];
+  __shared__ int s_hubs[BS_THREADS / ISP_WAVE];
   __shared__ int64_t s_ha[BS_THREADS], s_hb[BS_THREADS];  // the step's hub rows, [a, b), and their segments
   __shared__ int s_ns[BS_THREADS];
   __shared__ int s_samples[BS_THREADS / ISP_WAVE][CUT_COUNT * ISP_WAVE];
   __shared__ int s_err[BS_THREADS / ISP_WAVE];
   const int lane = threadIdx.x & (ISP_WAVE - 1), w = threadIdx.x / ISP_WAVE;
+  const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
+  constexpr int STEP = (BS_THREADS / ISP_WAVE) * RPW;  // rows at a time
+  const bool tile = (int)blockIdx.x < T.n;
+  auto row_of = [&](int64_t base) { return base + w * RPW + lane; };
+  auto in_tile = [&](int64_t i) { return tile && lane < RPW && i < r1; };
+  // (the first step's offsets are on their way while the indices are looked at)
+  const bool valid0 = in_tile(row_of(r0));
+  const int64_t a0 = valid0 ? indptr[row_of(r0)] : 0, b0 = valid0 ? indptr[row_of(r0) + 1] : 0;
   int my_err = 0;
   if (check) {
     bool bad = false;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += (int64_t)gridDim.x * blockDim.x) {
-      const int32_t c = indices[p];
-      bad |= (c < 0 || c >= n_cols);
+    const int64_t all = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += all * 4) {
+      int32_t c[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) c[u] = p + u * all < nnz ? indices[p + u * all] : 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) bad |= (c[u] < 0 || c[u] >= n_cols) && p + u * all < nnz;
     }
     my_err = bad ? 2 : 0;
   }
@@ -204,14 +228,16 @@ __global__ void __launch_bounds__(BS_THREADS) k_row_pass(const int64_t* __restri
     __syncthreads();
     if (threadIdx.x == 0) T.err[blockIdx.x] = s_err[0] | s_err[1] | s_err[2] | s_err[3];
   };
-  if ((int)blockIdx.x >= T.n) { report(); return; }
-  unsigned my_rows[5] = {0, 0, 0, 0, 0}, my_nnz[5] = {0, 0, 0, 0, 0}, my_max = 0, my_cost = 0;  // (a tile's cost: nnz + two units per row, below 2^32)
-  int my_seg = 0, my_hub = 0;
-  const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
-  for (int64_t base = r0; base < r1; base += (BS_THREADS / ISP_WAVE) * RPW) {  // (the workgroup stays together)
-    const int64_t i = base + w * RPW + lane;
-    const bool valid = lane < RPW && i < r1;
-    const int64_t a = valid ? indptr[i] : 0, b = valid ? indptr[i + 1] : 0;
+  if (!tile) { report(); return; }
+  if (threadIdx.x < STATS + 3) s_sum[threadIdx.x] = 0;  // (a barrier comes before the first is added to)
+  for (int64_t base = r0; base < r1; base += STEP) {  // (the workgroup stays together)
+    const int64_t i = row_of(base);
+    const bool valid = in_tile(i);
+    int64_t a = a0, b = b0;
+    if (base > r0) {
+      a = valid ? indptr[i] : 0;
+      b = valid ? indptr[i + 1] : 0;
+    }
     long long deg = b - a;
     if (valid && (deg < 0 || a < 0 || b > nnz || (i == 0 && a != 0) || (i == n_rows - 1 && b != nnz))) { my_err |= 1; deg = 0; }
     const bool hub = deg > pp.hub_t;
@@ -242,48 +268,23 @@ __global__ void __launch_bounds__(BS_THREADS) k_row_pass(const int64_t* __restri
     nseg[i] = ns;
     inv_len[i] = deg > 0 ? 1.f / (float)deg : 0.f;
     const int bin = degree_bin(deg, pp.hub_t);
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      my_rows[k] += (bin == k);
-      my_nnz[k] += (bin == k) ? (unsigned)deg : 0u;
+    atomicAdd(&s_sum[bin], 1u);
+    atomicAdd(&s_sum[5 + bin], (unsigned)deg);
+    atomicMax(&s_sum[10], (unsigned)deg);
+    if (hub) {
+      atomicAdd(&s_sum[SEGS], (unsigned)ns);
+      atomicAdd(&s_sum[HUBS], 1u);
+    } else {
+      atomicAdd(&s_sum[COST], (unsigned)c);
     }
-    my_max = (unsigned)deg > my_max ? (unsigned)deg : my_max;
-    my_seg += ns;
-    my_hub += hub;
-    my_cost += c;
   }
-  auto wave_sum = [](unsigned v) {
-#pragma unroll
-    for (int o = 1; o < ISP_WAVE; o <<= 1) v += __shfl_xor(v, o);
-    return v;
-  };
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const unsigned a = wave_sum(my_rows[k]), b = wave_sum(my_nnz[k]);
-    if (lane == 0) { s_stat[w][k] = a; s_stat[w][5 + k] = b; }
-  }
-#pragma unroll
-  for (int o = 1; o < ISP_WAVE; o <<= 1) {
-    const unsigned u = __shfl_xor(my_max, o);
-    my_max = u > my_max ? u : my_max;
-  }
-  const unsigned cost_sum = wave_sum(my_cost);
-  const int seg_sum = (int)wave_sum((unsigned)my_seg), hub_sum = (int)wave_sum((unsigned)my_hub);
-  if (lane == 0) { s_stat[w][10] = my_max; s_cost[w] = cost_sum; s_seg[w] = seg_sum; s_hub[w] = hub_sum; }
   report();  // (a barrier)
   if (threadIdx.x < STATS) {
-    const int k = threadIdx.x;
-    unsigned long long v = s_stat[0][k];
-#pragma unroll
-    for (int ww = 1; ww < BS_THREADS / ISP_WAVE; ++ww) {
-      const unsigned long long u = s_stat[ww][k];
-      v = k < 10 ? v + u : (u > v ? u : v);
-    }
-    T.stats[k * MAX_TILES + blockIdx.x] = v;
+    T.stats[threadIdx.x * MAX_TILES + blockIdx.x] = s_sum[threadIdx.x];
   } else if (threadIdx.x == ISP_WAVE) {
-    T.cost[blockIdx.x] = (int64_t)(s_cost[0] + s_cost[1] + s_cost[2] + s_cost[3]);
-    T.hub[blockIdx.x] = s_hub[0] + s_hub[1] + s_hub[2] + s_hub[3];
-    T.seg[blockIdx.x] = s_seg[0] + s_seg[1] + s_seg[2] + s_seg[3];
+    T.cost[blockIdx.x] = s_sum[COST];
+    T.hub[blockIdx.x] = (int)s_sum[HUBS];
+    T.seg[blockIdx.x] = (int)s_sum[SEGS];
   }
 }
 
@@ -295,61 +296,74 @@ __global__ void __launch_bounds__(BS_THREADS) k_mark_rows(const int32_t* __restr
                                                           int block_cost, int64_t force_row, row_tiles T, int n_err,
                                                           int32_t* __restrict__ mark, build_counters* __restrict__ ctr,
                                                           const int* __restrict__ flag, int* __restrict__ host_flag) {
-  // One workgroup more than tiles: what the counters tell the caller (pass 3 adds the counts), and a flag that earlier
-  // launches left on the device, if there is one, for the host.
-  if ((int)blockIdx.x == T.n) {
-    __shared__ unsigned long long part[BS_THREADS / ISP_WAVE][STATS];
-    const int lane = threadIdx.x & (ISP_WAVE - 1);
-    int err = 0;
+  // More workgroups than tiles: what the counters tell the caller (pass 3 adds the counts), one number each (one
+  // workgroup for all of them was what the launch waited for: 9.4 us on 1 M entries, now 6), and a flag that earlier launches left on the
+  // device, if there is one, for the host.
+  if ((int)blockIdx.x >= T.n) {
+    const int k = (int)blockIdx.x - T.n - 1;
+    if (k < 0) {
+      int err = 0;
 #pragma unroll 8
-    for (int i = threadIdx.x; i < n_err; i += BS_THREADS) err |= T.err[i];
-    const int err1 = __syncthreads_or(err & 1), err2 = __syncthreads_or(err & 2);
-    if (threadIdx.x == 0) {
-      ctr->err = (err1 ? 1 : 0) | (err2 ? 2 : 0);
-      if (host_flag) *host_flag = *flag;
+      for (int i = threadIdx.x; i < n_err; i += BS_THREADS) err |= T.err[i];
+      const int err1 = __syncthreads_or(err & 1), err2 = __syncthreads_or(err & 2);
+      if (threadIdx.x == 0) {
+        ctr->err = (err1 ? 1 : 0) | (err2 ? 2 : 0);
+        if (host_flag) *host_flag = *flag;
+      }
+      return;
     }
-    unsigned long long v[STATS] = {};
-#pragma unroll 2
+    __shared__ unsigned long long part[BS_THREADS / ISP_WAVE];
+    const bool add = k < 10;  // (the longest row is the largest of them)
+    unsigned long long v = 0;
+#pragma unroll 8
     for (int t = threadIdx.x; t < T.n; t += BS_THREADS) {
-#pragma unroll
-      for (int k = 0; k < STATS; ++k) {
-        const unsigned long long u = T.stats[k * MAX_TILES + t];
-        v[k] = k < 10 ? v[k] + u : (u > v[k] ? u : v[k]);
-      }
+      const unsigned long long u = T.stats[k * MAX_TILES + t];
+      v = add ? v + u : (u > v ? u : v);
     }
 #pragma unroll
-    for (int k = 0; k < STATS; ++k) {
-#pragma unroll
-      for (int o = 1; o < ISP_WAVE; o <<= 1) {
-        const unsigned long long u = __shfl_xor(v[k], o);
-        v[k] = k < 10 ? v[k] + u : (u > v[k] ? u : v[k]);
-      }
-      if (lane == 0) part[threadIdx.x / ISP_WAVE][k] = v[k];
+    for (int o = 1; o < ISP_WAVE; o <<= 1) {
+      const unsigned long long u = __shfl_xor(v, o);
+      v = add ? v + u : (u > v ? u : v);
     }
+    if ((threadIdx.x & (ISP_WAVE - 1)) == 0) part[threadIdx.x / ISP_WAVE] = v;
     __syncthreads();
-    if (threadIdx.x < STATS) {
-      const int k = threadIdx.x;
-      unsigned long long z = part[0][k];
-      for (int w = 1; w < BS_THREADS / ISP_WAVE; ++w) z = k < 10 ? z + part[w][k] : (part[w][k] > z ? part[w][k] : z);
-      if (k < 5) ctr->bin_rows[k] = z; else if (k < 10) ctr->bin_nnz[k - 5] = z; else ctr->max_degree = z;
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < BS_THREADS / ISP_WAVE; ++w) v = add ? v + part[w] : (part[w] > v ? part[w] : v);
+      if (k < 5) ctr->bin_rows[k] = v; else if (k < 10) ctr->bin_nnz[k - 5] = v; else ctr->max_degree = v;
     }
     return;
   }
-  int64_t cum0 = block_sum_of<int64_t>(T.cost, blockIdx.x);
   const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
+  struct row_info { int cost, before, begins; };  // its cost, the one of the row before it, whether it begins a block whatever they are
+  auto request = [&](int64_t i) {
+    row_info f{0, 0, 0};
+    if (i < r1) {
+      f.cost = cost[i];
+      f.begins = hubflag[i];
+      if (i > 0) {
+        f.before = cost[i - 1];
+        f.begins |= hubflag[i - 1];
+      }
+      f.begins |= i == 0 || i == force_row;
+    }
+    return f;
+  };
+  row_info f = request(r0 + threadIdx.x);  // (on its way beside the tiles' sums)
+  unsigned cum0 = (unsigned)(block_sum_of<int64_t>(T.cost, blockIdx.x) % block_cost);  // modulo block_cost
   int marks = 0;
   for (int64_t base = r0; base < r1; base += BS_THREADS) {
     const int64_t i = base + threadIdx.x;
     const bool valid = i < r1;
+    if (base > r0) f = request(i);
     int tot;
-    const int64_t cum = cum0 + block_exclusive_scan<int>(valid ? cost[i] : 0, &tot);
+    const unsigned cum = (cum0 + (unsigned)block_exclusive_scan<int>(f.cost, &tot)) % (unsigned)block_cost;
     if (valid) {
       // a multiple of block_cost lies in (cum - cost[i - 1], cum]: the remainder of cum is below the row before's cost
-      const int m = i == 0 || i == force_row || hubflag[i] || hubflag[i - 1] || cum % block_cost < cost[i - 1];
+      const int m = f.begins || (int)cum < f.before;
       mark[i] = m;
       marks += m;
     }
-    cum0 += tot;
+    cum0 = (cum0 + (unsigned)tot) % (unsigned)block_cost;
   }
   int tot;
   block_exclusive_scan<int>(marks, &tot);
@@ -358,7 +372,7 @@ __global__ void __launch_bounds__(BS_THREADS) k_mark_rows(const int32_t* __restr
 
 // Pass 3.  The tables: block starts, hub rows, their segments.
 template <int RPW>
-__global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
+__global__ void __launch_bounds__(BS_THREADS, 7) k_compact(const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
                                                  int64_t n_cols, partition_params pp, row_tiles T,
                                                  const int32_t* __restrict__ mark, const int32_t* __restrict__ hubflag,
                                                  const int32_t* __restrict__ nseg,
@@ -373,10 +387,20 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
   __shared__ int64_t s_ha[BS_THREADS], s_hb[BS_THREADS];
   __shared__ int s_hs[BS_THREADS];
   __shared__ int s_samples[BS_THREADS / ISP_WAVE][CUT_COUNT * ISP_WAVE];
+  const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
+  struct row_info { int mark, hub, nseg; int64_t a, b; };
+  auto request = [&](int64_t base) {
+    const int64_t i = base + (threadIdx.x / ISP_WAVE) * RPW + lane;
+    row_info f{0, 0, 0, 0, 0};
+    if (lane < RPW && i < r1) f = {mark[i], hubflag[i], nseg[i], indptr[i], indptr[i + 1]};
+    return f;
+  };
+  row_info f = request(r0);  // (on its way beside the tiles' sums)
   int mpos0, hpos0, seg0;
   {
     unsigned long long mh = 0;  // marks and hub rows of the earlier tiles, 32 bits each
     int sg = 0;
+#pragma unroll 4
     for (int t = threadIdx.x; t < (int)blockIdx.x; t += BS_THREADS) {
       mh += (unsigned long long)(unsigned)T.mark[t] << 32 | (unsigned)T.hub[t];
       sg += T.seg[t];
@@ -389,22 +413,21 @@ __global__ void __launch_bounds__(BS_THREADS) k_compact(const int64_t* __restric
   }
   // Rows of a malformed indptr may overlap: their segments together can wrap the 32-bit sums, whatever the tables' bounds.
   if (err & 1) return;  // (the host reports ISP_EBADCSR)
-  const int64_t r0 = (int64_t)blockIdx.x * T.rows, r1 = r0 + T.rows < n_rows ? r0 + T.rows : n_rows;
   for (int64_t base = r0; base < r1; base += (BS_THREADS / ISP_WAVE) * RPW) {
     const int64_t i = base + (threadIdx.x / ISP_WAVE) * RPW + lane;
-    const bool valid = lane < RPW && i < r1;  // (no early exit: the wavefront handles its hub rows together)
-    const int m = valid ? mark[i] : 0;
-    const bool hub = valid && hubflag[i];
+    if (base > r0) f = request(base);  // (no early exit: the wavefront handles its hub rows together)
+    const int m = f.mark;
+    const bool hub = f.hub;
     // one scan for the three positions (at most 256 marks and hub rows here)
     unsigned long long tot;
     const unsigned long long pos = block_exclusive_scan<unsigned long long>(
-        (unsigned long long)m << 48 | (unsigned long long)(hub ? 1 : 0) << 32 | (unsigned)(hub ? nseg[i] : 0), &tot);
+        (unsigned long long)m << 48 | (unsigned long long)(hub ? 1 : 0) << 32 | (unsigned)(hub ? f.nseg : 0), &tot);
     const int mpos = mpos0 + (int)(pos >> 48), h = hpos0 + (int)(pos >> 32 & 0xffff), s0 = seg0 + (int)(unsigned)pos;
     mpos0 += (int)(tot >> 48);
     hpos0 += (int)(tot >> 32 & 0xffff);
     seg0 += (int)(unsigned)tot;
     if (m && mpos < max_blocks) blk_row[mpos] = (int32_t)i;
-    const int64_t a = hub ? indptr[i] : 0, b = hub ? indptr[i + 1] : 0;
+    const int64_t a = hub ? f.a : 0, b = hub ? f.b : 0;
     if (hub && h < max_hub) {
       hub_rows[h] = (int32_t)i;
       hub_seg_ptr[h] = s0;
@@ -875,7 +898,7 @@ isp_status build_partition(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
   if (spread) ISP_GO(RPW_SMALL); else ISP_GO(RPW_LARGE);
 #undef ISP_GO
   ISP_LAUNCH_CHECK();
-  k_mark_rows<<<T.n + 1, BS_THREADS, 0, s>>>(cost, hubflag, n_rows, pp.block_cost, force_row, T, grid1, mark, ctr, flag, host_flag);
+  k_mark_rows<<<T.n + 1 + STATS, BS_THREADS, 0, s>>>(cost, hubflag, n_rows, pp.block_cost, force_row, T, grid1, mark, ctr, flag, host_flag);
   ISP_LAUNCH_CHECK();
 #define ISP_GO(R)                                                                                                     \
   k_compact<R><<<T.n, BS_THREADS, 0, s>>>(indptr, indices, n_cols, pp, T, mark, hubflag, nseg, n_rows, blk_row, hub_rows, \
