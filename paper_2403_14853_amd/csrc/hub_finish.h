@@ -23,9 +23,8 @@ constexpr int HF_SLICES = 2;     // counters per hub row: one per column slice o
 // 10 k, 300 k (2,523) 10.1 / 7.4, 16.1 / 14.0; 170 k, 1.7 M (6,583) 24.1 / 23.2, 68.4 / 67.9; 100 k, 4 M (8,192) 35.5 / 34.7, 112.1 /
 // 111.8; 10 k, 1 M (13,911) 16.1 / 15.1, 31.3 / 31.4; 20 k, 3 M (16,000) 26.0 / 26.1, 72.8 / 72.7; 60 k, 18 M (72,304) 114.8 / 122.4, 380 / 380;
 // FusedMM, 16 and 64 columns: 10 k, 300 k 12.3 / 9.3, 15.6 / 11.6; 20 k, 3 M 35.7 / 36.6, 56.5 / 56.5; 1 M, 17 M (39,440) 188 / 196, 375 / 373.
-inline bool hf_pays(const isp_csr* A, const isp_view& v) {
-  return v.hub_done && v.n_hub > 0 && v.n_seg <= 2 * A->wave_slots;
-}
+inline bool hf_few(const isp_csr* A, const isp_view& v) { return v.n_seg <= 2 * A->wave_slots; }
+inline bool hf_pays(const isp_csr* A, const isp_view& v) { return v.hub_done && v.n_hub > 0 && hf_few(A, v); }
 
 // A segment's row: its partial rows [s0, s1) and its counter.
 struct hub_ref {

@@ -11,6 +11,7 @@
 // Both backward forms are row passes over the cached transpose (whose perm gives p), so no
 // floating-point atomics are needed and results are deterministic.
 #include "row_stream.h"
+#include "hub_finish.h"
 #include "run_stream.h"
 
 namespace {
@@ -95,7 +96,8 @@ __device__ inline bool mm_better(float t, float best) { return MODE == R_MIN ? t
 
 constexpr int MINMAX_RING = 4;
 
-template <int LPG, int MODE>
+// FINISH: hub rows are put together here (hub_finish.h), with the results of the fix-up's fold in segment order, bit for bit.
+template <int LPG, int MODE, bool FINISH>
 __global__ void __launch_bounds__(ISP_WG) k_minmax_grouped(isp_view A, const int64_t* __restrict__ indptr,
                                                            const int32_t* __restrict__ indices,
                                                            const float* __restrict__ values,
@@ -111,7 +113,14 @@ __global__ void __launch_bounds__(ISP_WG) k_minmax_grouped(isp_view A, const int
   const item_range it = locate_item(A, indptr, item);
   if (it.skip) return;
   rn_wave_lds& L = lds.w[w];
+  const bool finish = FINISH && it.is_seg;
+  hub_ref H{0, 0, 0};
+  if (finish) H.h = A.seg_hub[it.row];
   const rn_run R = rn_prepare<G>(it, indptr, indices, values, nullptr, L, lane);
+  if (finish) {
+    H.s0 = A.hub_seg_ptr[H.h];
+    H.s1 = A.hub_seg_ptr[H.h + 1];
+  }
 
   const int g = lane / LPG, q = lane % LPG;
   // (lanes past d work on the last columns again and store what the columns' own lane stores)
@@ -186,7 +195,67 @@ __global__ void __launch_bounds__(ISP_WG) k_minmax_grouped(isp_view A, const int
         where[v] = take ? ow : where[v];
       }
     }
-    if (g == 0) store_row(it.row, best, where);
+    if constexpr (FINISH) {
+      float* row = A.partials + (int64_t)it.row * ISP_PARTIAL_TILE;
+      const unsigned byte = (unsigned)(col - k_base) * 4u;
+      if (g == 0) {
+        float wb[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) wb[v] = __int_as_float(where[v]);
+        hf_store<4>(row, byte, best);
+        hf_store<4>(row, byte + ARG_OFF * 4u, wb);
+      }
+      if (!hf_last(A, H, 0, lane)) return;
+      // Each group folds a contiguous part of the segments.  A NaN decides only as the row's first segment (nothing is better than it,
+      // and it is better than nothing): the later parts pass over theirs.
+      const int n = H.s1 - H.s0, part = (n + G - 1) / G, first = g * part, end = first + part < n ? first + part : n;
+      float* base = A.partials + (int64_t)H.s0 * ISP_PARTIAL_TILE;
+      constexpr int U = 8;  // partial rows in flight
+#pragma unroll
+      for (int v = 0; v < 4; ++v) where[v] = -1;
+      for (int i = 0; i < part; i += U) {
+        float t[U][4], wb[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int s = first + i + u < n ? first + i + u : n - 1;
+          const unsigned at = (unsigned)s * (unsigned)(ISP_PARTIAL_TILE * 4) + byte;
+          hf_load(base, at, t[u]);
+          hf_load(base, at + ARG_OFF * 4u, wb[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const bool start = where[v] < 0 && (g == 0 || t[u][v] == t[u][v]);
+            const bool take = first + i + u < end && i + u < part && (start || (where[v] >= 0 && mm_better<MODE>(t[u][v], best[v])));
+            best[v] = take ? t[u][v] : best[v];
+            where[v] = take ? __float_as_int(wb[u][v]) : where[v];
+          }
+      }
+#pragma unroll
+      for (int o = LPG; o < ISP_WAVE; o <<= 1) {  // neighbouring parts, the earlier one kept unless the later one is better
+        const bool later = (lane & o) != 0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float ob = __shfl_xor(best[v], o);
+          const int ow = __shfl_xor(where[v], o);
+          const float eb = later ? ob : best[v], lb = later ? best[v] : ob;
+          const int ew = later ? ow : where[v], lw = later ? where[v] : ow;
+          const bool take = lw >= 0 && (ew < 0 || mm_better<MODE>(lb, eb));
+          best[v] = take ? lb : eb;
+          where[v] = take ? lw : ew;
+        }
+      }
+      if (g == 0) {
+        float wb[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) wb[v] = __int_as_float(where[v]);
+        store_vec<4>(Y + (int64_t)it.src_row * ldy + col, best);
+        store_vec<4>(reinterpret_cast<float*>(arg) + (int64_t)it.src_row * d + col, wb);
+      }
+    } else if (g == 0) {
+      store_row(it.row, best, where);
+    }
     return;
   }
   if constexpr (G > 1) {  // rows cut by a run boundary (as in k_spmm_grouped)
@@ -415,7 +484,9 @@ __global__ void __launch_bounds__(ISP_WG) k_mark_lanes(isp_view A, const int64_t
   }
 }
 
-template <int LPG, bool HAS_VAL>
+// FINISH: hub rows are put together here (hub_finish.h; us of the whole backward with the fix-up / without: 2 k rows, 20 k entries:
+// 16 columns 13.7 / 11.0, 100 18.5 / 15.7; 10 k, 300 k: 16 18.1 / 15.7, 128 28.6 / 25.9; 100 k, 1 M: 32 35.4 / 32.9, 128 87.6 / 85.4).
+template <int LPG, bool HAS_VAL, bool FINISH>
 __global__ void __launch_bounds__(SELECT_WAVES * ISP_WAVE) k_select_grouped(isp_view At, const int64_t* __restrict__ indptr,
                                                            const int32_t* __restrict__ indices,
                                                            const float* __restrict__ values,
@@ -435,6 +506,9 @@ __global__ void __launch_bounds__(SELECT_WAVES * ISP_WAVE) k_select_grouped(isp_
   sel_wave_lds<HAS_VAL>& S = lds[w];
   rn_wave_lds& L = S.rn;
   const int n_all = (int)(it.p_end - it.p);
+  const bool finish = FINISH && it.is_seg;
+  hub_ref H{0, 0, 0};
+  if (finish) H.h = At.seg_hub[it.row];
   const rn_first_rows f = rn_request_rows(it, indptr, nullptr, lane);
   // stage the live entries: all the marks first, then what the live ones need
   constexpr int SB = GS_MAX_ENT / ISP_WAVE;
@@ -457,6 +531,10 @@ __global__ void __launch_bounds__(SELECT_WAVES * ISP_WAVE) k_select_grouped(isp_
       if (HAS_VAL) S.val[o] = values[p];
     }
     n_ent += __popcll(m);
+  }
+  if (finish) {
+    H.s0 = At.hub_seg_ptr[H.h];
+    H.s1 = At.hub_seg_ptr[H.h + 1];
   }
   if (lane == 0) { S.mask[SB] = 0; S.before[SB] = n_ent; }
   if (lane < RN_PAD) L.ent[n_ent + lane] = make_int2(0, 0);
@@ -514,7 +592,15 @@ __global__ void __launch_bounds__(SELECT_WAVES * ISP_WAVE) k_select_grouped(isp_
       float t[N];
 #pragma unroll
       for (int c = 0; c < N; ++c) t[c] = acc[c];
-      store_vec<N>(out + (int64_t)it.row * ldo + idx0, t);
+      if (finish) hf_store<N>(At.partials + (int64_t)it.row * ISP_PARTIAL_TILE, (unsigned)(col - k_base + idx0) * 4u, t);
+      else store_vec<N>(out + (int64_t)it.row * ldo + idx0, t);
+    }
+    if constexpr (FINISH) {
+      if (hf_last(At, H, 0, lane)) {
+        float t[4];
+        hf_sum<LPG, 8>(At, H, (unsigned)(col - k_base) * 4u, lane, t);
+        if (g == 0) store_vec<4>(dX + (int64_t)it.src_row * lddx + col, t);
+      }
     }
     return;
   }
@@ -562,6 +648,10 @@ __global__ void __launch_bounds__(ISP_WG) k_sum_fixup(isp_view A, int d, int k0,
   hub_fixup<VEC, 1, false>(A, d, k0, Y, ldy);
 }
 
+__global__ void __launch_bounds__(ISP_WG) k_sum_fixup_wg(isp_view A, int d, int k0, float* __restrict__ Y, int64_t ldy) {
+  hub_fixup_wg<4, 1, false>(A, d, k0, Y, ldy, 0);
+}
+
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
 unsigned item_grid(const isp_view& v) { return (unsigned)((v.n_blocks + v.n_seg + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG); }
@@ -587,13 +677,18 @@ template <int LPG, int MODE>
 isp_status minmax_grouped_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int k_base, float* Y,
                                int64_t ldy, int32_t* arg, hipStream_t s) {
   const isp_view& v = A->v;
+  // (twice the sum's bytes to add up, and what follows them in the launch: only up to a segment for every third wavefront slot.  us with the
+  // fix-up / without, segments in brackets: 2 k rows, 20 k entries (52): 16 columns 10.4 / 9.6, 100 13.7 / 11.0; 10 k, 100 k (484): 64 13.6 / 11.5; 50 k,
+  // 300 k (1,243): 32 16.9 / 13.9, 128 31.8 / 29.1; but 10 k, 300 k (2,526): 16 14.6 / 15.7, 128 21.2 / 26.8; 100 k, 1 M (6,467): 32 28.4 / 29.0)
+  const bool finish = hf_pays(A, v) && 3 * v.n_seg <= A->wave_slots;
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);
-    k_minmax_grouped<LPG, MODE><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, X, ldx, d, k_base, Y, ldy, arg);
+    if (finish) k_minmax_grouped<LPG, MODE, true><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, X, ldx, d, k_base, Y, ldy, arg);
+    else k_minmax_grouped<LPG, MODE, false><<<grid, ISP_WG, 0, s>>>(v, v.indptr, v.indices, v.values, X, ldx, d, k_base, Y, ldy, arg);
     ISP_LAUNCH_CHECK();
   }
-  if (v.n_hub > 0) {
+  if (v.n_hub > 0 && !finish) {
     k_reduce_fixup<2, MODE><<<hub_grid(v), ISP_WG, 0, s>>>(v, d, k_base, Y, ldy, arg);
     ISP_LAUNCH_CHECK();
   }
@@ -640,6 +735,7 @@ isp_status select_grouped_tile(const isp_csr* A, const int32_t* inv_perm, const 
                                int d, int k_base, float* dX, int64_t lddx, hipStream_t s) {
   const isp_csr* At = A->At;
   const isp_view &v = At->v, &va = A->v;
+  const bool finish = hf_pays(At, v);
   const int64_t words = (v.nnz + 3) / 4;
   k_zero_u32<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(At->sel_flags), words);
   ISP_LAUNCH_CHECK();
@@ -651,12 +747,19 @@ isp_status select_grouped_tile(const isp_csr* A, const int32_t* inv_perm, const 
   if (v.n_blocks + v.n_seg > 0) {
     const unsigned grid = (unsigned)((v.n_blocks + v.n_seg + SELECT_WAVES - 1) / SELECT_WAVES);
     constexpr int WG = SELECT_WAVES * ISP_WAVE;
-    if (v.values) k_select_grouped<LPG, true><<<grid, WG, 0, s>>>(v, v.indptr, v.indices, v.values, At->perm, At->sel_flags, dY, lddy, arg, d, k_base, dX, lddx);
-    else k_select_grouped<LPG, false><<<grid, WG, 0, s>>>(v, v.indptr, v.indices, v.values, At->perm, At->sel_flags, dY, lddy, arg, d, k_base, dX, lddx);
+#define ISP_GO(HV, FN)                                                                                                       \
+  k_select_grouped<LPG, HV, FN><<<grid, WG, 0, s>>>(v, v.indptr, v.indices, v.values, At->perm, At->sel_flags, dY, lddy, arg, d, \
+                                                    k_base, dX, lddx)
+    if (v.values) { if (finish) ISP_GO(true, true); else ISP_GO(true, false); }
+    else { if (finish) ISP_GO(false, true); else ISP_GO(false, false); }
+#undef ISP_GO
     ISP_LAUNCH_CHECK();
   }
-  if (v.n_hub > 0) {
-    k_sum_fixup<4><<<hub_grid(v), ISP_WG, 0, s>>>(v, d < k_base + 4 * LPG ? d : k_base + 4 * LPG, k_base, dX, lddx);
+  if (v.n_hub > 0 && !finish) {
+    const int d_hi = d < k_base + 4 * LPG ? d : k_base + 4 * LPG;
+    // (an alias of a handle whose launches finish their hub rows adds in their order)
+    if (hf_few(At, v)) k_sum_fixup_wg<<<(unsigned)v.n_hub, ISP_WG, 0, s>>>(v, d_hi, k_base, dX, lddx);
+    else k_sum_fixup<4><<<hub_grid(v), ISP_WG, 0, s>>>(v, d_hi, k_base, dX, lddx);
     ISP_LAUNCH_CHECK();
   }
   return ISP_OK;

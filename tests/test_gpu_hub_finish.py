@@ -95,3 +95,31 @@ def test_fusedmm(hubs):
             assert torch.equal(Y, Z)
             assert_close(Y, *oracle.fusedmm_backward(indptr, cols, values, X, G), "fusedmm backward")
     A.destroy()
+
+
+@pytest.mark.parametrize("hubs", [FEW, MANY])
+def test_min_and_max(hubs):
+    """Forward bit for bit (ties to the first entry), backward bit-identical through an alias and within tolerance."""
+    n = 4_000
+    indptr, cols, values, A, B = _graph(hubs, n, n, 9, square=True)
+    for d in (4, 30, 32, 64, 65, 100, 128, 131, 256):
+        for reduce in ("min", "max"):
+            print("[case] %s, %d hub rows, d = %d" % (reduce, len(hubs), d), flush=True)
+            for turn in range(2):
+                rng = np.random.default_rng(10 * d + turn)
+                X = rng.integers(-8, 9, (n, d)).astype(np.float32)  # (many ties)
+                G = rng.standard_normal((n, d)).astype(np.float32)
+                Xd, Gd = dev(X), dev(G)
+                Y, Z, dX, dZ = (torch.full((n, d), float("nan"), device="cuda") for _ in range(4))
+                arg, arg_b = (torch.full((n, d), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+                isp.spmm_reduce(A, Xd, Y, reduce, arg)
+                isp.spmm_reduce(B, Xd, Z, reduce, arg_b)
+                ref, ref_arg, _ = oracle.spmm_reduce(indptr, cols, values, X, reduce)
+                assert torch.equal(Y, Z) and torch.equal(arg, arg_b)
+                assert np.array_equal(Y.cpu().numpy(), ref) and np.array_equal(arg.cpu().numpy(), ref_arg)
+                isp.spmm_reduce_backward(A, Gd, dX, reduce, arg)
+                isp.spmm_reduce_backward(B, Gd, dZ, reduce, arg)
+                assert torch.equal(dX, dZ)
+                want, mag = oracle.spmm_reduce_backward(n, indptr, cols, values, G, reduce, ref_arg)
+                assert_close(dX, want, mag, "backward")
+    A.destroy()
