@@ -82,6 +82,8 @@ isp_status launch_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int
 // MEAN: finished rows are divided by their length (partial rows are not: their fix-up divides).
 // FINISH: hub rows are put together here (hub_finish.h).  A kernel of its own: launches that have none to finish ran 2 % longer
 // with that code in them (4 k rows, 37 k entries 4.41 -> 4.53 us).
+// STREAM: rows of Y that an item finishes are written past the caches (streams_output; kernels of their own as well: with the choice at
+// run time the small launch took 4.47 us).
 constexpr int SPMM_RING = 4;
 
 // On the packed layout, launches that gather more than three and a half lines of a row ask for LDS they do not use, so that a
@@ -96,7 +98,7 @@ constexpr int SPMM_RING = 4;
 //   2 (64 columns): 2326 / 2325;  1 (32): 1213 / 1248.
 constexpr unsigned SPMM_FOUR_PER_CU = 160 * 1024 / 4 - sizeof(rn_lds);
 
-template <int LPG, bool ADDR32, int VEC, bool MEAN, bool FINISH, int CAP = GS_MAX_ENT>
+template <int LPG, bool ADDR32, int VEC, bool MEAN, bool FINISH, int CAP = GS_MAX_ENT, bool STREAM = false>
 __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
     isp_view A, const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
     const float* __restrict__ values, const float* __restrict__ X, int64_t ldx, int d, int k_base, int n_slices,
@@ -137,12 +139,21 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
   float* __restrict__ out = to_partial ? A.partials + (col - k_base) : Y + col;
   const unsigned ldo = to_partial ? (unsigned)ISP_PARTIAL_TILE : (unsigned)ldy;  // (the launcher checks that it fits)
   auto row_of = [&](int dst) { return out + (uint64_t)(unsigned)dst * ldo; };
+  auto put = [&](int dst, const float (&o)[VEC]) {
+    if constexpr (STREAM && VEC == 4) {
+      if (!to_partial) {
+        store_vec4_nt(row_of(dst), o);
+        return;
+      }
+    }
+    store_vec<VEC>(row_of(dst), o);
+  };
 
   float acc[VEC], head[VEC], x[SPMM_RING][VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = head[v] = 0.f;
   if (!to_partial)  // the empty rows' outputs (also their mean); a piece is never empty
-    for (int i = g; i < R.n_empty; i += G) store_vec<VEC>(row_of(L.dst[RN_EMPTY0 - i]), acc);
+    for (int i = g; i < R.n_empty; i += G) put(L.dst[RN_EMPTY0 - i], acc);
 
   bool carried = R.mid;  // the next row to end began in an earlier run
   bool ended = false;    // a row has ended in this run
@@ -171,7 +182,7 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[v] *= inv;
           }
-          store_vec<VEC>(row_of(row), acc);
+          put(row, acc);
         }
         carried = false;
         ended = true;
@@ -226,7 +237,7 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
 #pragma unroll
         for (int v = 0; v < VEC; ++v) head[v] *= inv;
       }
-      store_vec<VEC>(row_of(L.dst[R.k]), head);
+      put(L.dst[R.k], head);
     }
   }
 }
@@ -245,6 +256,7 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
   const bool a32 = v.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
                    ((uint64_t)v.n_cols * (uint64_t)ldx + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
   const bool finish = VEC == 4 && a32 && n_slices <= HF_SLICES && hf_pays(A, v);  // (else a fix-up launch adds the hub rows)
+  const bool stream = streams_output(v.n_real_rows, d);
   // (one value per stored entry, in the order of the view's entries)
   const float* vals = values_override ? (packed ? values_override_packed : values_override) : v.values;
   const int n_items = v.n_blocks + v.n_seg;
@@ -252,9 +264,10 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG) * (unsigned)n_slices;
     const unsigned spare = packed && 2 * isp_stage::line_sum((uintptr_t)(X + k_base), ldx, width) > 7 * isp_stage::ALIGN
                                ? SPMM_FOUR_PER_CU : 0u;
-#define ISP_GO1(A32, MN, FN)                                                                                        \
-  k_spmm_grouped<LPG, A32, VEC, MN, FN><<<grid, ISP_WG, spare, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, k_base, \
-                                                            n_slices, Y, ldy)
+#define ISP_GO2(A32, MN, FN, ST)                                                                                    \
+  k_spmm_grouped<LPG, A32, VEC, MN, FN, GS_MAX_ENT, ST><<<grid, ISP_WG, spare, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, \
+                                                                                    k_base, n_slices, Y, ldy)
+#define ISP_GO1(A32, MN, FN) do { if (stream) ISP_GO2(A32, MN, FN, A32 && VEC == 4); else ISP_GO2(A32, MN, FN, false); } while (0)
 #define ISP_GO(A32, MN) do { if (finish) ISP_GO1(A32, MN, A32 && VEC == 4); else ISP_GO1(A32, MN, false); } while (0)
     // (one group to a wavefront, 129 to 224 columns, has work for 14 per compute unit before seven at a time pay: 25 k columns,
     // 408 k entries, 208 columns (6.6 per unit) 31.4 us with five, 33.8 with seven; 17 k, 601 k: 176 (8.5) 34.7 / 36.7; 23 k, 1 M: 135 (17.2)
@@ -276,6 +289,7 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
     }
 #undef ISP_GO
 #undef ISP_GO1
+#undef ISP_GO2
     ISP_LAUNCH_CHECK();
   }
   if (v.n_hub > 0 && !finish) {
