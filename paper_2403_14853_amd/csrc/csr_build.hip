@@ -192,9 +192,10 @@ __global__ void __launch_bounds__(BS_THREADS, 7) k_row_pass(const int64_t* __res
                                                   int32_t* __restrict__ nseg, float* __restrict__ inv_len) {
   // The tile's numbers: STATS of them, then cost, segments, hub rows (a tile's cost: nnz + two units per row, below 2^32).  Added up
   // in LDS: sums over the lanes held 14 values per lane and with them four workgroups to a compute unit instead of seven, too few for all
-  // tiles of 100 k rows at once (1 M entries: 14.5 us, now 11.2).
-  constexpr int COST = STATS, SEGS = STATS + 1, HUBS = STATS + 2;
-  __shared__ unsigned s_sum[STATS + 3];
+  // tiles of 100 k rows at once (1 M entries: 14.5 us, now 11.2).  Sixteen copies of each: rows of one class otherwise add to
+  // one address lane after lane (building 2.4 M uniform rows, 10 M entries: sums over the lanes 218 us, one copy 257, sixteen 171; 1 M rows, 4 M entries 93 / 85 / 70).
+  constexpr int COST = STATS, SEGS = STATS + 1, HUBS = STATS + 2, SUM_COPIES = 16;
+  __shared__ unsigned s_sum[STATS + 3][SUM_COPIES];
   __shared__ int s_hubs[BS_THREADS / ISP_WAVE];
   __shared__ int64_t s_ha[BS_THREADS], s_hb[BS_THREADS];  // the step's hub rows, [a, b), and their segments
   __shared__ int s_ns[BS_THREADS];
@@ -229,7 +230,9 @@ __global__ void __launch_bounds__(BS_THREADS, 7) k_row_pass(const int64_t* __res
     if (threadIdx.x == 0) T.err[blockIdx.x] = s_err[0] | s_err[1] | s_err[2] | s_err[3];
   };
   if (!tile) { report(); return; }
-  if (threadIdx.x < STATS + 3) s_sum[threadIdx.x] = 0;  // (a barrier comes before the first is added to)
+  static_assert((STATS + 3) * SUM_COPIES <= BS_THREADS, "a copy per thread");
+  const int own_sum = (int)threadIdx.x / SUM_COPIES, own_copy = (int)threadIdx.x % SUM_COPIES;
+  if (own_sum < STATS + 3) s_sum[own_sum][own_copy] = 0;  // (a barrier comes before the first is added to)
   for (int64_t base = r0; base < r1; base += STEP) {  // (the workgroup stays together)
     const int64_t i = row_of(base);
     const bool valid = in_tile(i);
@@ -268,24 +271,28 @@ __global__ void __launch_bounds__(BS_THREADS, 7) k_row_pass(const int64_t* __res
     nseg[i] = ns;
     inv_len[i] = deg > 0 ? 1.f / (float)deg : 0.f;
     const int bin = degree_bin(deg, pp.hub_t);
-    atomicAdd(&s_sum[bin], 1u);
-    atomicAdd(&s_sum[5 + bin], (unsigned)deg);
-    atomicMax(&s_sum[10], (unsigned)deg);
+    atomicAdd(&s_sum[bin][own_copy], 1u);
+    atomicAdd(&s_sum[5 + bin][own_copy], (unsigned)deg);
+    atomicMax(&s_sum[10][own_copy], (unsigned)deg);
     if (hub) {
-      atomicAdd(&s_sum[SEGS], (unsigned)ns);
-      atomicAdd(&s_sum[HUBS], 1u);
+      atomicAdd(&s_sum[SEGS][own_copy], (unsigned)ns);
+      atomicAdd(&s_sum[HUBS][own_copy], 1u);
     } else {
-      atomicAdd(&s_sum[COST], (unsigned)c);
+      atomicAdd(&s_sum[COST][own_copy], (unsigned)c);
     }
   }
   report();  // (a barrier)
-  if (threadIdx.x < STATS) {
-    T.stats[threadIdx.x * MAX_TILES + blockIdx.x] = s_sum[threadIdx.x];
-  } else if (threadIdx.x == ISP_WAVE) {
-    T.cost[blockIdx.x] = s_sum[COST];
-    T.hub[blockIdx.x] = (int)s_sum[HUBS];
-    T.seg[blockIdx.x] = (int)s_sum[SEGS];
+  unsigned v = own_sum < STATS + 3 ? s_sum[own_sum][own_copy] : 0u;
+#pragma unroll
+  for (int o = 1; o < SUM_COPIES; o <<= 1) {
+    const unsigned u = __shfl_xor(v, o);
+    v = own_sum != 10 ? v + u : (u > v ? u : v);
   }
+  if (own_copy != 0) return;
+  if (own_sum < STATS) T.stats[own_sum * MAX_TILES + blockIdx.x] = v;
+  else if (own_sum == COST) T.cost[blockIdx.x] = v;
+  else if (own_sum == SEGS) T.seg[blockIdx.x] = (int)v;
+  else if (own_sum == HUBS) T.hub[blockIdx.x] = (int)v;
 }
 
 // Pass 2.  Where blocks begin: block b at the first row whose cumulative short-row cost reaches b * block_cost, and at

@@ -250,3 +250,21 @@ def test_rewritten_values_of_more_blocks_than_a_grid_dimension_holds():
         _, _, t_values, perm = At.export()
         assert torch.equal(t_values, values[perm.long()])
     A.destroy()
+
+
+@pytest.mark.parametrize("n_rows", [500, 262_145, 1_100_000])
+@pytest.mark.parametrize("lengths", [[4], [0, 4, 5, 32, 33, 64, 65, 200]])
+def test_row_classes(n_rows, lengths):
+    """Rows and entries per degree class and the longest row, exactly: rows of one length, and of lengths around every class's edge, in
+    tiles of one step and of several."""
+    print("%d rows" % n_rows, flush=True)
+    rng = np.random.default_rng(n_rows)
+    deg = rng.choice(lengths, n_rows, p=None if len(lengths) == 1 else [.3, .3, .2, .1, .04, .03, .02, .01])
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    A = build(indptr, rng.integers(0, 1000, indptr[-1]).astype(np.int32), None, n_cols=1000)
+    info = A.info()
+    bins = np.digitize(deg, [1, 5, 33, info["hub_threshold"] + 1])
+    assert list(info["bin_rows"]) == [int((bins == k).sum()) for k in range(5)]
+    assert list(info["bin_nnz"]) == [int(deg[bins == k].sum()) for k in range(5)]
+    assert info["max_degree"] == deg.max() and info["n_hub_rows"] == int((bins == 4).sum())
+    A.destroy()
