@@ -15,7 +15,7 @@
 #include <new>
 #include "digit_scan.h"
 #include "host_slot.h"
-#include "hub_finish.h"
+#include "hub_rule.h"
 #include "stage_rule.h"
 
 namespace {
@@ -438,7 +438,7 @@ __global__ void __launch_bounds__(BS_THREADS, 7) k_compact(const int64_t* __rest
     if (hub && h < max_hub) {
       hub_rows[h] = (int32_t)i;
       hub_seg_ptr[h] = s0;
-      for (int k = 0; k < HF_SLICES; ++k) hub_done[(int64_t)h * HF_SLICES + k] = 0;
+      for (int k = 0; k < HF_SLICES; ++k) hub_done[(int64_t)h * HF_STRIDE + k] = 0;
     }
     const int hx = (int)(pos >> 32 & 0xffff);  // the step's hub rows, shared out over the wavefronts
     if (hub) { s_ha[hx] = a; s_hb[hx] = b; s_hs[hx] = s0; }
@@ -782,7 +782,7 @@ ws_layout make_layout(int64_t n_rows, int64_t nnz, const partition_params& pp, s
   L.blk_row = take((size_t)(max_blocks + 1) * 4);
   L.hub_rows = take((size_t)(max_hub + 1) * 4);
   L.hub_seg_ptr = take((size_t)(max_hub + 2) * 4);
-  L.hub_done = take((size_t)(max_hub + 1) * HF_SLICES * 4);
+  L.hub_done = take((size_t)(max_hub + 1) * HF_STRIDE * 4);
   L.seg_hub = take((size_t)(max_seg + 1) * 4);
   L.seg_begin = take((size_t)(max_seg + 1) * 4);
   for (int k = 0; k < 2; ++k) {

@@ -11,20 +11,10 @@
 // release and acquire of the whole L2 would write back and drop everything else in it.  The counter is an increment that
 // wraps to zero at the row's number of segments: nothing has to be cleared between launches.
 #pragma once
+#include "hub_rule.h"
 #include "row_stream.h"
 
 namespace isp_dev {
-
-constexpr int HF_SLICES = 2;     // counters per hub row: one per column slice of a launch
-
-// Whether a launch finishes its hub rows itself: not where it has more than two segments for every wavefront slot.  The fix-up's
-// wavefronts then have enough rows to fill the chip, and the launch spends longer in the chains (store, count, load) at the end
-// of its segments.  us with the fix-up / without, segments in brackets: SpMM, 16 and 128 columns: 2 k rows, 20 k entries (52) 7.5 / 5.3, 9.1 / 6.6;
-// 10 k, 300 k (2,523) 10.1 / 7.4, 16.1 / 14.0; 170 k, 1.7 M (6,583) 24.1 / 23.2, 68.4 / 67.9; 100 k, 4 M (8,192) 35.5 / 34.7, 112.1 /
-// 111.8; 10 k, 1 M (13,911) 16.1 / 15.1, 31.3 / 31.4; 20 k, 3 M (16,000) 26.0 / 26.1, 72.8 / 72.7; 60 k, 18 M (72,304) 114.8 / 122.4, 380 / 380;
-// FusedMM, 16 and 64 columns: 10 k, 300 k 12.3 / 9.3, 15.6 / 11.6; 20 k, 3 M 35.7 / 36.6, 56.5 / 56.5; 1 M, 17 M (39,440) 188 / 196, 375 / 373.
-inline bool hf_few(const isp_csr* A, const isp_view& v) { return v.n_seg <= 2 * A->wave_slots; }
-inline bool hf_pays(const isp_csr* A, const isp_view& v) { return v.hub_done && v.n_hub > 0 && hf_few(A, v); }
 
 // A segment's row: its partial rows [s0, s1) and its counter.
 struct hub_ref {
@@ -61,7 +51,7 @@ __device__ __forceinline__ bool hf_last(const isp_view& A, const hub_ref& H, int
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the partial row has arrived where every XCD reads it
   const unsigned n = (unsigned)(H.s1 - H.s0);
   unsigned before = 0;
-  if (lane == 0) before = atomicInc(A.hub_done + (int64_t)H.h * HF_SLICES + slice, n - 1u);
+  if (lane == 0) before = atomicInc(A.hub_done + (int64_t)H.h * HF_STRIDE + slice, n - 1u);
   const bool last = (unsigned)__builtin_amdgcn_readfirstlane((int)before) == n - 1u;
   asm volatile("" ::: "memory");
   return last;

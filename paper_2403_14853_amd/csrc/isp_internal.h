@@ -36,7 +36,7 @@ struct isp_view {
   int32_t n_hub, n_seg;
   int32_t hub_t, seg_len;
   float* partials;         // n_seg * ISP_PARTIAL_TILE floats
-  unsigned* hub_done;      // two counters per hub row, zero between launches (hub_finish.h); NULL: a fix-up launch adds
+  unsigned* hub_done;      // two counters per hub row, on a line of its own, zero between launches (hub_rule.h); NULL: a fix-up launch adds
                            // the segments (the packed layout's view, handles with scratch of their own)
   const float* inv_len;    // 1 / (stored entries of the row), 0 for an empty row; indexed by the rows of the
                            // handle's matrix (also in the view of a derived matrix)
