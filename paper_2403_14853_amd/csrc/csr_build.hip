@@ -1130,6 +1130,7 @@ isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
   A->vp = A->v;
   A->partial_rows = L.max_seg + 1;
   A->spmm_rows = po.h.n_seg;
+  A->longest_row_segs = po.h.n_hub > 0 ? (int32_t)row_segments((int64_t)po.h.max_degree, pp) : 0;
   A->has_packed = false; A->packed_values_rw = nullptr; A->packed_src_pos = nullptr;
   A->perm = nullptr; A->t_values_rw = nullptr; A->At = nullptr; A->is_transpose = false; A->mirror_aligned = false;
   A->mean_values = nullptr; A->mean_values_packed = nullptr; A->mean_values_valid = false; A->mean_values_used = false;

@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(ISP_WG) k_fused_grouped(isp_view A, const int6
 template <class P, int LPG, int W, bool A32>
 isp_status run_grouped(const isp_csr* A, const typename P::args& pa, int d, float* Y, int64_t ldy, hipStream_t s) {
   const isp_view& v = A->v;
-  const bool finish = A32 && hf_pays(A, v);
+  const bool finish = A32 && hf_pays(A, v, LPG);
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);

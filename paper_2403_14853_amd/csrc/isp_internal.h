@@ -75,6 +75,7 @@ struct isp_csr {
   int64_t spmm_rows;              // partial rows a SpMM launch on v or vp writes: n_seg, or the pieces where they are
                                   // more.  A built handle keeps scratch of its own for the pieces; whoever points v
                                   // and vp at one scratch gives it this many rows.
+  int32_t longest_row_segs;       // segments of v's longest row, as partition_sizes.h counts them
   bool has_packed;
   int packed_block_cost, packed_row_cost;  // of vp's partition (bounds of its blocks: see csr_build.hip)
   float* packed_values_rw;        // vp.values, writable, NULL without values

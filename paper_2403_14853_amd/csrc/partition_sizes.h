@@ -21,6 +21,12 @@ __host__ __device__ inline int hub_bands(int64_t deg, const partition_params& pp
   return br;
 }
 
+// Segments of a hub row of deg entries whose columns are spread evenly over its bands.
+inline int64_t row_segments(int64_t deg, const partition_params& pp) {
+  const int64_t br = hub_bands(deg, pp), len = (deg + br - 1) / br;
+  return br * ((len + pp.seg_len - 1) / pp.seg_len);
+}
+
 inline int64_t max_hub_rows(int64_t n_rows, int64_t nnz, const partition_params& pp) {
   const int64_t h = nnz / ((int64_t)pp.hub_t + 1);
   return h < n_rows ? h : n_rows;

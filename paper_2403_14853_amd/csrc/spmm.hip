@@ -255,7 +255,7 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
   const int width = n_slices * LPG * VEC < d - k_base ? n_slices * LPG * VEC : d - k_base;
   const bool a32 = v.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
                    ((uint64_t)v.n_cols * (uint64_t)ldx + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
-  const bool finish = VEC == 4 && a32 && n_slices <= HF_SLICES && hf_pays(A, v);  // (else a fix-up launch adds the hub rows)
+  const bool finish = VEC == 4 && a32 && n_slices <= HF_SLICES && hf_pays(A, v, LPG);  // (else a fix-up launch adds the hub rows)
   const bool stream = streams_output(v.n_real_rows, d);
   // (one value per stored entry, in the order of the view's entries)
   const float* vals = values_override ? (packed ? values_override_packed : values_override) : v.values;

@@ -42,13 +42,23 @@ def _graph(hub_lengths, n_rows, n_cols, seed, square=False):
     return indptr, cols, values, A, isp.csr_alias(A, max_d=320)
 
 
-FEW = list(range(17, 330, 8)) + [17, 20, 24, 25, 2_000, 2_001, 4_099]  # 3 to 513 segments
+FEW = list(range(17, 330, 8)) + [17, 20, 24, 25, 2_000, 2_001, 4_099]  # 3 to 513 segments: the longest row is too long
 MANY = [24] * 3_000
+# The longest row as long as the launches with 64, 32 and up to 16 lanes to a group finish, and a segment longer.
+SHORT = list(range(17, 330, 8)) + [17, 20, 24, 25, 504, 512]  # 3 to 64 segments: every launch
+WIDE, WIDER = SHORT + [1_024], SHORT + [1_025]                # 128 and 129
+LONG, LONGER = SHORT + [1_024, 4_096], SHORT + [1_024, 4_097]  # 512 and 513
 
 
 @pytest.mark.parametrize("hubs, n_cols, widths", [
     (FEW, 700, [3, 4, 16, 17, 32, 64, 65, 100, 128, 130, 200, 256, 301]),
     (FEW, 82_000, [127, 128, 256]),   # 128 whole-line columns run as two slices
+    (SHORT, 700, [3, 4, 16, 17, 32, 64, 65, 100, 128, 130, 200, 256, 301]),
+    (SHORT, 82_000, [127, 128, 200, 256]),
+    (WIDE, 700, [64, 65, 128, 130, 256]),
+    (WIDER, 700, [64, 65, 128, 130]),
+    (LONG, 700, [8, 30, 64, 100]),
+    (LONGER, 700, [8, 30, 64, 100]),
     (MANY, 700, [8, 64, 100, 256]),
 ])
 def test_spmm_and_mean(hubs, n_cols, widths):
@@ -74,7 +84,7 @@ def test_spmm_and_mean(hubs, n_cols, widths):
     A.destroy()
 
 
-@pytest.mark.parametrize("hubs", [FEW, MANY])
+@pytest.mark.parametrize("hubs", [FEW, MANY, SHORT, WIDE, LONG])
 def test_fusedmm(hubs):
     n = 4_000
     indptr, cols, values, A, B = _graph(hubs, n, n, 5, square=True)

@@ -36,3 +36,38 @@ int main() {
   return 0;
 }
 """)
+
+
+def test_long_rows_keep_the_fix_up(tmp_path):
+    """One wavefront adds the row that counts last, the fix-up's workgroup four times as fast: a matrix with a row of hundreds or
+    thousands of segments, few as they are together, is left to the fix-up, the sooner the fewer lane groups share the row."""
+    _run(tmp_path, r"""
+int main() {
+  unsigned done = 0;
+  int finished = 0, left = 0;
+  for (int64_t deg = 161; deg <= 600000; deg += deg / 7 + 1) {  // one such row among 20,000 of 8 entries
+    const int64_t nnz = 160000 + deg;
+    const partition_params p = get_params(20001, nnz, 4096);
+    isp_csr A{};
+    A.wave_slots = 4096;
+    A.longest_row_segs = (int32_t)row_segments(deg, p);
+    A.v.n_hub = 1;
+    A.v.n_seg = A.longest_row_segs;
+    if (A.v.n_seg > 8192) break;
+    // (the estimate against bounds of what the cuts leave: a band's part of the row, in segments)
+    if (A.v.n_seg < deg / p.seg_len || A.v.n_seg > deg / p.seg_len + 1 + p.bands) FAIL("%d segments of %lld\n", A.v.n_seg, (long long)deg);
+    for (int lpg : {4, 8, 16, 32, 64}) {
+      const int limit = lpg == 64 ? 64 : lpg == 32 ? 128 : 512;
+      if (hf_pays(&A, A.v, lpg)) FAIL("without counters\n");
+      A.v.hub_done = &done;
+      const bool pays = hf_pays(&A, A.v, lpg);
+      A.v.hub_done = nullptr;
+      if (pays != (A.v.n_seg <= limit)) FAIL("%d lanes, %d segments: %d\n", lpg, A.v.n_seg, (int)pays);
+      (pays ? finished : left) += 1;
+    }
+    if (!hf_few(&A, A.v)) FAIL("the order of the sums follows the segments of all rows\n");
+  }
+  printf("%d finished, %d left\n", finished, left);
+  return finished > 20 && left > 20 ? 0 : 1;
+}
+""")
