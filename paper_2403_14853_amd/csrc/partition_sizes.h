@@ -1,6 +1,7 @@
 // Sizes of the work partitions (csr_build.hip) as functions of the matrix's shape: host arithmetic only, so that the
 // bounds the workspaces are laid out by can be checked without a device.
 #pragma once
+#include <math.h>
 #include <stdlib.h>
 #include "isp_internal.h"
 
@@ -21,9 +22,12 @@ __host__ __device__ inline int hub_bands(int64_t deg, const partition_params& pp
   return br;
 }
 
-// Segments of a hub row of deg entries whose columns are spread evenly over its bands.
+// About how many segments a hub row of deg entries has: its columns spread over the bands, chance included (bands of 79 entries on average and
+// segments of 80: not a segment to a band but 1.4).
 inline int64_t row_segments(int64_t deg, const partition_params& pp) {
-  const int64_t br = hub_bands(deg, pp), len = (deg + br - 1) / br;
+  const int64_t br = hub_bands(deg, pp);
+  int64_t len = (deg + br - 1) / br;
+  if (br > 1) len += (int64_t)sqrt((double)len);
   return br * ((len + pp.seg_len - 1) / pp.seg_len);
 }
 

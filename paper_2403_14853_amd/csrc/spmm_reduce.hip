@@ -677,10 +677,7 @@ template <int LPG, int MODE>
 isp_status minmax_grouped_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int k_base, float* Y,
                                int64_t ldy, int32_t* arg, hipStream_t s) {
   const isp_view& v = A->v;
-  // (twice the sum's bytes to add up, and what follows them in the launch: only up to a segment for every third wavefront slot.  us with the
-  // fix-up / without, segments in brackets: 2 k rows, 20 k entries (52): 16 columns 10.4 / 9.6, 100 13.7 / 11.0; 10 k, 100 k (484): 64 13.6 / 11.5; 50 k,
-  // 300 k (1,243): 32 16.9 / 13.9, 128 31.8 / 29.1; but 10 k, 300 k (2,526): 16 14.6 / 15.7, 128 21.2 / 26.8; 100 k, 1 M (6,467): 32 28.4 / 29.0)
-  const bool finish = hf_pays(A, v, LPG) && 3 * v.n_seg <= A->wave_slots;
+  const bool finish = hf_minmax_pays(A, v, LPG);
   const int n_items = v.n_blocks + v.n_seg;
   if (n_items > 0) {
     const unsigned grid = (unsigned)((n_items + ISP_WAVES_PER_WG - 1) / ISP_WAVES_PER_WG);

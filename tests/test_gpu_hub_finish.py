@@ -45,7 +45,7 @@ def _graph(hub_lengths, n_rows, n_cols, seed, square=False):
 FEW = list(range(17, 330, 8)) + [17, 20, 24, 25, 2_000, 2_001, 4_099]  # 3 to 513 segments: the longest row is too long
 MANY = [24] * 3_000
 # The longest row as long as the launches with 64, 32 and up to 16 lanes to a group finish, and a segment longer.
-SHORT = list(range(17, 330, 8)) + [17, 20, 24, 25, 504, 512]  # 3 to 64 segments: every launch
+SHORT = list(range(17, 330, 8)) + [17, 20, 24, 25, 504, 512, 761, 768]  # 3 to 96 segments: every launch
 WIDE, WIDER = SHORT + [1_024], SHORT + [1_025]                # 128 and 129
 LONG, LONGER = SHORT + [1_024, 4_096], SHORT + [1_024, 4_097]  # 512 and 513
 
@@ -132,4 +132,78 @@ def test_min_and_max(hubs):
                 assert torch.equal(dX, dZ)
                 want, mag = oracle.spmm_reduce_backward(n, indptr, cols, values, G, reduce, ref_arg)
                 assert_close(dX, want, mag, "backward")
+    A.destroy()
+
+
+def _pairs(lengths, n, seed):
+    """Hub rows of these lengths, rows of 100 to 160 entries, which let the launch finish its hub rows, and rows of 0 to 5."""
+    rng = np.random.default_rng(seed)
+    deg = rng.integers(0, 6, n)
+    rows = rng.permutation(n)
+    deg[rows[:len(lengths)]] = lengths
+    deg[rows[len(lengths):len(lengths) + 60]] = rng.integers(100, 161, 60)
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    owner = np.repeat(np.arange(n), deg)
+    cols = rng.integers(0, n, len(owner))
+    cols = cols[np.lexsort((cols, owner))].astype(np.int32)
+    values = rng.integers(1, 4, len(owner)).astype(np.float32)
+    env = {"ISP_HUB_THRESHOLD": "160", "ISP_SEGMENT_LEN": "80", "ISP_BANDS": "1"}
+    saved = {k: os.environ.get(k) for k in env}
+    os.environ.update(env)
+    try:
+        dv = dev(values)
+        A = isp.csr_build(dev(indptr), dev(cols), dv, n_cols=n)
+    finally:
+        for k, v in saved.items():
+            if v is None:
+                os.environ.pop(k)
+            else:
+                os.environ[k] = v
+    return indptr, cols, values, dv, A, np.sort(rows[:len(lengths)])
+
+
+@pytest.mark.parametrize("d", [4, 30, 32, 33, 64, 65, 100, 128, 131])
+def test_min_and_max_in_the_launch_of_the_segments(d):
+    """The forward that finishes its hub rows, up to as many segments as it folds: bit for bit with the oracle (ties to the first entry),
+    and with the fix-up launch (an alias) also where products are NaN: a row's first entry, a later segment's first, a whole
+    segment, all segments of a lane group's part, everything but the row's end."""
+    lanes = 8 if d <= 32 else 16 if d <= 64 else 32
+    limit = 96 if lanes == 8 else 32  # segments of the longest row
+    n = 6_000
+    lengths = [80 * s - k for s in range(3, limit + 1, limit // 10) for k in (0, 79)] + [80 * limit] * 3
+    lengths = [h for h in lengths if h > 160]
+    indptr, cols, values, dv, A, hubs = _pairs(lengths, n, d)
+    info = A.info()
+    slots = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    assert info["n_segments"] == sum((h + 79) // 80 for h in lengths) and 3 * info["n_segments"] <= slots
+    assert 2 * info["bin_nnz"][3] >= info["segment_len"] * info["bin_rows"][3] > 0
+    rng = np.random.default_rng(d)
+    X = rng.integers(-8, 9, (n, d)).astype(np.float32)  # (many ties)
+    nan = values.copy()
+    for i, r in enumerate(hubs):
+        a, b = indptr[r], indptr[r + 1]
+        n_seg = -(-(b - a) // 80)
+        part = -(-n_seg // (64 // lanes))
+        first, last = [(0, 1), (80, 81), (0, 80), (80, 160), (80 * part, 160 * part), (0, b - a - 1)][i % 6]
+        nan[a + first:min(a + last, b)] = np.nan
+    Xd = dev(X)
+    for with_nan in (False, True):
+        if with_nan:
+            dv.copy_(dev(nan))
+            isp.csr_values_changed(A)
+        B = isp.csr_alias(A, max_d=d)
+        for reduce in ("min", "max"):
+            print("[case] %s, d = %d, %d segments, nan: %d" % (reduce, d, info["n_segments"], with_nan), flush=True)
+            for turn in range(2):  # (the counters start over by themselves)
+                Y, Z = (torch.full((n, d), 7.5, device="cuda") for _ in range(2))
+                arg, arg_b = (torch.full((n, d), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+                isp.spmm_reduce(A, Xd, Y, reduce, arg)
+                isp.spmm_reduce(B, Xd, Z, reduce, arg_b)
+                assert torch.equal(Y.view(torch.int32), Z.view(torch.int32)) and torch.equal(arg, arg_b)
+            if with_nan:
+                assert torch.isnan(Y[torch.from_numpy(hubs).cuda()]).any()
+            else:
+                ref, ref_arg, _ = oracle.spmm_reduce(indptr, cols, values, X, reduce)
+                assert np.array_equal(Y.cpu().numpy(), ref) and np.array_equal(arg.cpu().numpy(), ref_arg)
+        B.destroy()
     A.destroy()

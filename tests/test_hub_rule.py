@@ -54,10 +54,10 @@ int main() {
     A.v.n_hub = 1;
     A.v.n_seg = A.longest_row_segs;
     if (A.v.n_seg > 8192) break;
-    // (the estimate against bounds of what the cuts leave: a band's part of the row, in segments)
-    if (A.v.n_seg < deg / p.seg_len || A.v.n_seg > deg / p.seg_len + 1 + p.bands) FAIL("%d segments of %lld\n", A.v.n_seg, (long long)deg);
+    // (the estimate: full segments at least, at most three more to a band)
+    if (A.v.n_seg < deg / p.seg_len || A.v.n_seg > deg / p.seg_len + 3 * p.bands) FAIL("%d segments of %lld\n", A.v.n_seg, (long long)deg);
     for (int lpg : {4, 8, 16, 32, 64}) {
-      const int limit = lpg == 64 ? 64 : lpg == 32 ? 128 : 512;
+      const int limit = lpg == 64 ? 96 : lpg == 32 ? 128 : 512;
       if (hf_pays(&A, A.v, lpg)) FAIL("without counters\n");
       A.v.hub_done = &done;
       const bool pays = hf_pays(&A, A.v, lpg);
@@ -69,5 +69,37 @@ int main() {
   }
   printf("%d finished, %d left\n", finished, left);
   return finished > 20 && left > 20 ? 0 : 1;
+}
+""")
+
+
+def test_min_max_keeps_the_fix_up_where_nothing_hides_the_fold(tmp_path):
+    """Hub rows among rows too short for any row block to run as long as a segment, or of many segments."""
+    _run(tmp_path, r"""
+int main() {
+  unsigned done = 0;
+  isp_csr A{};
+  A.wave_slots = 4096;
+  A.v.hub_done = &done;
+  A.v.n_hub = 8;
+  A.v.n_seg = 64;
+  A.v.seg_len = 80;
+  A.longest_row_segs = 8;
+  if (hf_minmax_pays(&A, A.v, 16)) FAIL("no rows of 33 entries and more\n");
+  A.info.bin_rows[3] = 87;
+  A.info.bin_nnz[3] = 87 * 35;
+  if (hf_minmax_pays(&A, A.v, 16)) FAIL("rows of 35 entries\n");
+  A.info.bin_nnz[3] = 87 * 40;
+  for (int lpg : {8, 16, 32})
+    for (int n : {1, 8, 32, 33, 96, 97, 500}) {
+      A.longest_row_segs = n;
+      if (hf_minmax_pays(&A, A.v, lpg) != (n <= (lpg == 8 ? 96 : 32))) FAIL("%d lanes, %d segments\n", lpg, n);
+    }
+  A.longest_row_segs = 8;
+  A.v.n_seg = 1365;
+  if (!hf_minmax_pays(&A, A.v, 32)) FAIL("a segment for every third slot\n");
+  A.v.n_seg = 1366;
+  if (hf_minmax_pays(&A, A.v, 32)) FAIL("too many segments\n");
+  return 0;
 }
 """)
