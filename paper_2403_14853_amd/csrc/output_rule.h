@@ -1,0 +1,20 @@
+// Which outputs SpMM writes past the caches: host arithmetic only, so that the rule can be checked without a device.
+#pragma once
+#include <stdint.h>
+
+namespace isp_dev {
+
+// From 160 MB on.  The launch itself gains at any size from some 64 MB, as its output no longer pushes out of the Infinity Cache (256 MB) what it
+// still gathers; but whoever reads the output next then finds nothing of it there, and up to half the cache's size that costs as much or more.  us with
+// ordinary / these stores, R-MAT, 8 to 12 entries a row; the launch alone, with a dense product on its output, a training step of a two-layer GCN of that hidden width:
+//    32 columns:  66 MB 54.5 / 53.8, 135 / 142, 2455 / 2793;  130 MB 105 / 102, 218 / 214, 4223 / 4229;  160 MB 135 / 132, 262 / 259, 5231 / 5208
+//    64:          66 MB 57.1 / 56.4, 114 / 124, 1586 / 1750;  90 MB 80.5 / 79.7, 158 / 171, 2226 / 2387;  130 MB 114 / 112, 245 / 252, 2912 / 2935;
+//                160 MB 149 / 144, 317 / 313, 3654 / 3635;  300 MB 301 / 291, 473 / 470
+//   100:          90 MB 103 / 101, 224 / 232, 2109 / 2175;  160 MB 203 / 199, 401 / 397, 4099 / 4088
+//   128:          90 MB 80.6 / 80.5, 145 / 146, 1623 / 1690;  130 MB 115 / 113, 261 / 254, 2211 / 2173;  160 MB 150 / 144, 319 / 312, 2744 / 2705;  300 MB 321 / 296, 542 / 530
+// Rows narrower than a line (their parts are stored by several lane groups), alone and with the product: 8 columns 66 MB 114 / 112, 261 / 273; 160 MB 309 / 292, 677 / 677; 300 MB 611 / 573,
+// 1314 / 1291; 16 columns 160 MB 159 / 152, 407 / 409; 24 columns 154 / 149, 349 / 344.  Launches on the small LDS tables (run_stream.h), whose operand the L2s hold,
+// store as ever.
+inline bool streams_output(int64_t rows, int64_t d) { return rows * d >= (int64_t)40 << 20; }
+
+}  // namespace isp_dev

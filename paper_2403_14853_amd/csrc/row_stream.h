@@ -49,7 +49,7 @@ __device__ inline void store_vec(float* __restrict__ p, const float (&o)[VEC]) {
   *reinterpret_cast<V*>(p) = v;
 }
 
-// The same past the caches, for outputs that would only push out what the launch still gathers.
+// The same past the caches, for outputs that would only push out what the launch still gathers (output_rule.h).
 // (As an instruction of its own: next to an ordinary store in the other branch of a condition __builtin_nontemporal_store becomes one with
 // it, an ordinary one.  The two wait states are those between a store of 16 bytes and a write to its registers.)
 __device__ inline void store_vec4_nt(float* p, const float (&o)[4]) {
@@ -57,15 +57,6 @@ __device__ inline void store_vec4_nt(float* p, const float (&o)[4]) {
   const f4 v = {o[0], o[1], o[2], o[3]};
   asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
-
-// Whether an output is written past the caches: from 64 MB on, a quarter of the Infinity Cache, which then does not hold the operand, the
-// output and their gradients together, and they push out what the launch still gathers.  us with ordinary / these stores:
-// forward and backward in turn: 169 k rows, 2.4 M entries, 128 columns (87 MB) 181 / 169; 800 k, 8 M, 32 (102 MB) 208 / 186; 1 M uniform, 4 M, 128 (512 MB)
-// 767 / 733; 2.4 M, 60 M, 128 4890 / 4821; one SpMM again and again 600 k, 6 M, 128 (307 MB) 268 / 245; 300 k, 3 M, 128 (154 MB) 119 / 115; 600 k, 37 (89 MB)
-// 139 / 137.  Whoever reads the output next may find less of it in the caches: with an elementwise operation and a second SpMM on it 600 k, 128 826 / 799;
-// 300 k, 128 395 / 396; 169 k, 128 251 / 254; 600 k, 37 349 / 351; with smaller outputs that is all there is to it (all of them past the caches: 169 k, 47
-// columns, 32 MB, 52.7 / 52.7 and 129.6 / 131.9; 50 k, 500 k, 64, 13 MB, 14.8 / 14.9 and 42.2 / 43.6).
-inline bool streams_output(int64_t rows, int64_t d) { return rows * d >= (int64_t)16 << 20; }
 
 __device__ inline int bcast_i(int v, int src_lane) { return __builtin_amdgcn_readlane(v, src_lane); }
 __device__ inline float bcast_f(float v, int src_lane) {

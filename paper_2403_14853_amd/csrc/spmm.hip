@@ -3,6 +3,7 @@
 // (Section 3.3).  Gather-bound: per nonzero one 4*d-byte row of X is fetched and d FMAs are done,
 // so the kernels are built around coalesced row gathers, not around matrix cores.
 #include "hub_finish.h"
+#include "output_rule.h"
 #include "run_stream.h"
 #include "stage_rule.h"
 
@@ -82,7 +83,7 @@ isp_status launch_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int
 // MEAN: finished rows are divided by their length (partial rows are not: their fix-up divides).
 // FINISH: hub rows are put together here (hub_finish.h).  A kernel of its own: launches that have none to finish ran 2 % longer
 // with that code in them (4 k rows, 37 k entries 4.41 -> 4.53 us).
-// STREAM: rows of Y that an item finishes are written past the caches (streams_output; kernels of their own as well: with the choice at
+// STREAM: rows of Y that an item finishes are written past the caches (output_rule.h; never with the small LDS tables, whose operand the L2s hold; kernels of their own as well: with the choice at
 // run time the small launch took 4.47 us).
 constexpr int SPMM_RING = 4;
 
