@@ -31,8 +31,8 @@
  *   - A handle belongs to the HIP device that was current when it was built; using it with another device
  *     current yields ISP_EINVAL.
  *   - Calls that use the same handle (or a handle and its cached transpose) on different streams
- *     at the same time race on the handle's scratch (hub-row partial sums, SpMM's copy of a ragged dense operand);
- *     serialise them.
+ *     at the same time race on the handle's scratch (hub-row partial sums and the counters of their segments, SpMM's
+ *     copy of a ragged dense operand, the min / max backward's marks); serialise them.
  *   - Results are run-to-run bitwise deterministic: no floating-point atomics are used.
  *   - Environment variables (tuning and tests only; none is needed).  All are read when isp_csr_build runs and
  *     are kept in the handle; no compute call reads the environment.  (The partition sizes of a cached transpose

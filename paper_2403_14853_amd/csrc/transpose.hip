@@ -460,7 +460,7 @@ isp_status share_handle(const isp_csr* A, const int64_t* t_indptr, const int32_t
   At->v.indices = t_indices;
   At->v.values = t_values;
   At->v.partials = (float*)scratch;
-  At->v.hub_done = nullptr;  // (A's own: calls on A and A^T may overlap)
+  At->v.hub_done = nullptr;  // (this workspace has no counters of its own: hub rows are left to the fix-up launch)
   At->partial_rows = isp_shared_rows(A);
   const size_t row = ISP_PARTIAL_TILE * sizeof(float);
   char* rows_end = scratch + isp_align((size_t)At->partial_rows * row);
