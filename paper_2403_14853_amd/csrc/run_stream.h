@@ -40,7 +40,7 @@ using rn_lds = rn_lds_of<GS_MAX_ENT>;
 // must have more of; the launches' rules stand with them).  us with tables of 768 / RN_SMALL entries:
 //   SpMM: 20 k columns, 400 k entries, 64 columns 14.5 / 13.7; 10 k, 1 M: 16 16.3 / 14.7, 128 33.4 / 32.2; 50 k, 1.5 M: 32 27.1 /
 //   24.2, 64 35.3 / 32.6; beyond the L2s, 100 k, 1 M: 64 (26 MB) 29.4 / 30.0, 100 55.0 / 58.2;
-//   SDDMM: 10 k, 1 M: 16 13.0 / 11.7; 50 k, 1.5 M: 64 31.0 / 27.7; beyond, 100 k, 1 M: 64 27.3 / 28.2; 169 k, 2.4 M: 100 106 / 112.
+//   SDDMM: 10 k, 1 M: 16 12.8 / 11.7, 64 18.5 / 17.1; 50 k, 1.5 M: 32 21.0 / 18.7, 64 29.9 / 27.4; beyond, 100 k, 1 M: 64 21.5 / 22.3.
 constexpr int RN_SMALL = 448;
 constexpr int64_t RN_FIT_BYTES = 24 << 20;
 inline bool rn_small_tables(const isp_csr* A, const isp_view& v, int width, int64_t wgs, int per_cu) {

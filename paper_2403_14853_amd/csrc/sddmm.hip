@@ -132,9 +132,10 @@ isp_status launch_grouped(const isp_csr* A, const float* U, int64_t ldu, const f
 #define ISP_GO2(A32, AD, CAP) do { if (tail) ISP_GO(A32, AD, true, CAP); else ISP_GO(A32, AD, false, CAP); } while (0)
   if constexpr (LPG <= 16 && W == 4) {
     // Small tables only where the launch is long enough for the last workgroups to matter less: more than 12 per compute
-    // unit, beyond 32 columns 15.  us with five / seven at a time: 13 k columns, 674 k entries (12.1 per unit): 24 columns 10.2 / 9.4; 39 k,
-    // 993 k (12.3): 32 14.2 / 13.5, but 56 23.5 / 24.6; 111 k, 1.4 M (13.7): 40 31.0 / 33.1; 43 k, 1.2 M (21): 32 19.1 / 16.8; 42 k, 1.5 M (22): 48 29.8 /
-    // 26.5; 35 k, 870 k (10.5): 54 21.3 / 22.4; 51 k, 1 M (11.1): 8 12.9 / 13.4.  Never beyond 64 columns: 10 k, 1 M: 128 34.4 / 35.4.
+    // unit, beyond 32 columns 15.  us with five / seven at a time: 13 k columns, 674 k entries: 24 columns 9.6 / 9.1; 39 k,
+    // 993 k: 32 13.7 / 12.5, but 56 21.7 / 21.8; 111 k, 1.4 M: 40 29.1 / 30.1; 43 k, 1.2 M: 32 17.9 / 16.0; 42 k, 1.5 M: 48 29.2 /
+    // 26.7; 35 k, 870 k: 54 19.6 / 20.0; 51 k, 1 M: 8 12.4 / 12.1; 100 k, 1 M: 32 14.2 / 13.3, 64 21.5 / 22.3.  Never beyond 64 columns, where they made
+    // little difference either way (10 k, 1 M: 128 30.4 / 29.4).
     if (a32 && rn_small_tables(A, v, d_hi - k_lo, grid, d_hi - k_lo <= 32 ? 12 : 15)) {
       if (add) ISP_GO2(true, true, RN_SMALL); else ISP_GO2(true, false, RN_SMALL);
       ISP_LAUNCH_CHECK();
@@ -184,8 +185,9 @@ isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const
     //    half-rows of twice as many hot columns (the same effect, under the same conditions, as the column
     //    slices of SpMM);
     //  - otherwise rows wider than 128 floats go 128 columns at a time on the big graphs, and on others whose V is
-    //    beyond the L2s, where that cuts no cache line (256 columns, 2.4 M / 3 M entries: 259 -> 229 us / 366 -> 326;
-    //    at 200 columns it would be 222 -> 242), 256 on the rest.
+    //    beyond the L2s, where that cuts no cache line (us in one pass -> in windows, 2.4 M / 3 M entries: 256 columns 219 -> 189 / 307 -> 281, 192
+    //    161 -> 143 / 228 -> 203; at 200 columns it would be 187 -> 210 / 261 -> 299), 256 on the rest.  (On big graphs windows were the better way for
+    //    whole lines; for ragged rows they need not be: 248 columns, 1 M columns, 16.9 M entries 1877 in one pass, 2087 in windows.)
     const bool big = av.nnz >= ((int64_t)8 << 20);
     int wp = d;
     if (big && av.n_cols >= (1 << 19) && d > ISP_WAVE && d % ISP_WAVE == 0 && ldu % 32 == 0 && ldv % 32 == 0 &&
@@ -201,11 +203,11 @@ isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const
       const bool add = k_lo > 0;
       k_next = k_hi;
       // One float4 per lane up to 128 columns (two, which serve twice the entries per step, load the row operand with
-      // every step and hold twice the registers: 128 columns in one pass, us, one / two: 115 M entries 2648 / 2704, 16.9 M
-      // 717 / 737, 2.4 M 108 / 110), two above: with one, a wavefront has a single
-      // run and a reduction over all its lanes per entry.  That is only the better way for nearly full rows on graphs
+      // every step and hold twice the registers: 128 columns in one pass, us, one / two: 115 M entries 2558 / 2702, 2.4 M 93 / 98,
+      // 1.2 M 48.9 / 50.0), two above: with one, a wavefront has a single run.  That is only the better way for nearly full rows on graphs
       // with work for several times as many wavefronts as the chip holds (248 columns, us, one / two: 108 k entries
-      // 41 / 25, 589 k 61 / 45, 1.2 M 112 / 121, 3 M 380 / 391; 160 columns: 3 M 243 / 228).
+      // 21.8 / 16.8, 1.2 M 116 / 119, 2.4 M 236 / 249, 3 M 325 / 342; 160 columns: 108 k 21.3 / 15.0, 589 k 42.2 / 39.4, 1.2 M 83.8 / 74.1).  In between, one is the better
+      // way already at 589 k entries from 200 columns (45.1 / 47.8, 248 columns 51.7 / 57.5).
       if (w <= 32) st = launch_grouped<8, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
       else if (w <= 64) st = launch_grouped<16, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
       else if (w <= 128) st = launch_grouped<32, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
