@@ -4,9 +4,9 @@
 // into contiguous row blocks of about block_cost units, one unit per nonzero plus one per row
 // (a row's output write costs about as much as one gathered input row).  Hub rows
 // (degree > hub_t) never share a block; each is cut into segments of at most seg_len nonzeros whose
-// partial sums are combined later in a fixed order.  A hub row is cut first where its (sorted) columns
-// cross the boundaries of column bands, so that a segment gathers dense rows from one band only, and the
-// segments are scheduled in order of their first column: the whole chip then works on one band of the
+// partial sums are combined later in a fixed order.  On large matrices a hub row is cut first where its (sorted) columns
+// cross the boundaries of column bands, so that a segment gathers dense rows from one band only (which matrices:
+// partition_sizes.h), and the segments are scheduled in order of their first column: the whole chip then works on one band of the
 // dense operand at a time and the L2 caches hold that band's frequently used rows instead of a sample
 // of all of them.
 // Everything here is integer work and runs once per graph (balanced scheduling: paper Section 1(b); CSR
@@ -244,26 +244,32 @@ __global__ void __launch_bounds__(BS_THREADS, 7) k_row_pass(const int64_t* __res
     long long deg = b - a;
     if (valid && (deg < 0 || a < 0 || b > nnz || (i == 0 && a != 0) || (i == n_rows - 1 && b != nnz))) { my_err |= 1; deg = 0; }
     const bool hub = deg > pp.hub_t;
-    // the step's hub rows, shared out over the wavefronts
-    const unsigned long long hm = __ballot(hub);
-    if (lane == 0) s_hubs[w] = __popcll(hm);
-    __syncthreads();
-    int h0 = 0, n_hubs = 0;
+    int ns = 0;
+    if (pp.bands == 1) {  // (segments of one length: nothing to look for)
+      __syncthreads();    // (the sums are zero)
+      if (hub) ns = (int)((unsigned)(deg + pp.seg_len - 1) / (unsigned)pp.seg_len);
+    } else {
+      // the step's hub rows, shared out over the wavefronts
+      const unsigned long long hm = __ballot(hub);
+      if (lane == 0) s_hubs[w] = __popcll(hm);
+      __syncthreads();
+      int h0 = 0, n_hubs = 0;
 #pragma unroll
-    for (int ww = 0; ww < BS_THREADS / ISP_WAVE; ++ww) { h0 += ww < w ? s_hubs[ww] : 0; n_hubs += s_hubs[ww]; }
-    const int hx = h0 + __popcll(hm & ((1ull << lane) - 1ull));
-    if (hub) { s_ha[hx] = a; s_hb[hx] = b; }
-    __syncthreads();
-    for (int h = w; h < n_hubs; h += BS_THREADS / ISP_WAVE) {
-      int64_t first, last;
-      wave_hub_pieces(indices, s_ha[h], s_hb[h], n_cols, pp, lane, s_samples[w], &first, &last);
-      int cnt = (int)((unsigned)(last - first + pp.seg_len - 1) / (unsigned)pp.seg_len);
+      for (int ww = 0; ww < BS_THREADS / ISP_WAVE; ++ww) { h0 += ww < w ? s_hubs[ww] : 0; n_hubs += s_hubs[ww]; }
+      const int hx = h0 + __popcll(hm & ((1ull << lane) - 1ull));
+      if (hub) { s_ha[hx] = a; s_hb[hx] = b; }
+      __syncthreads();
+      for (int h = w; h < n_hubs; h += BS_THREADS / ISP_WAVE) {
+        int64_t first, last;
+        wave_hub_pieces(indices, s_ha[h], s_hb[h], n_cols, pp, lane, s_samples[w], &first, &last);
+        int cnt = (int)((unsigned)(last - first + pp.seg_len - 1) / (unsigned)pp.seg_len);
 #pragma unroll
-      for (int o = 1; o < ISP_WAVE; o <<= 1) cnt += __shfl_xor(cnt, o);
-      if (lane == 0) s_ns[h] = cnt;
+        for (int o = 1; o < ISP_WAVE; o <<= 1) cnt += __shfl_xor(cnt, o);
+        if (lane == 0) s_ns[h] = cnt;
+      }
+      __syncthreads();
+      if (hub) ns = s_ns[hx];
     }
-    __syncthreads();
-    const int ns = hub ? s_ns[hx] : 0;
     if (!valid) continue;
     const int32_t c = hub ? 0 : (int32_t)deg + pp.row_cost;
     cost[i] = c;
@@ -446,7 +452,19 @@ __global__ void __launch_bounds__(BS_THREADS, 7) k_compact(const int64_t* __rest
     const int n_hubs = (int)(tot >> 32 & 0xffff), hh0 = hpos0 - n_hubs;
     for (int hq = threadIdx.x / ISP_WAVE; hq < n_hubs; hq += BS_THREADS / ISP_WAVE) {
       const int hh = hh0 + hq, hs0 = s_hs[hq];
+      auto put = [&](int64_t s, int64_t q) {  // segment s begins at entry q
+        if (s >= max_seg) return;
+        seg_hub[s] = hh;
+        seg_begin[s] = (int32_t)q;
+        seg_key[s] = indices[q];
+      };
       int64_t first, last;
+      if (pp.bands == 1) {  // one piece: its segments side by side (by one lane, 100 k rows, 1 M entries, one graph seen once 240 us, 217 this way)
+        first = s_ha[hq];
+        last = s_hb[hq];
+        for (int64_t s = lane, q = first + (int64_t)lane * pp.seg_len; q < last; s += ISP_WAVE, q += (int64_t)ISP_WAVE * pp.seg_len) put(hs0 + s, q);
+        continue;
+      }
       wave_hub_pieces(indices, s_ha[hq], s_hb[hq], n_cols, pp, lane, s_samples[threadIdx.x / ISP_WAVE], &first, &last);
       // the row's segments, in order of position: piece by piece (lane by lane), each piece in runs of seg_len
       const int cnt = (int)((unsigned)(last - first + pp.seg_len - 1) / (unsigned)pp.seg_len);
@@ -457,12 +475,7 @@ __global__ void __launch_bounds__(BS_THREADS, 7) k_compact(const int64_t* __rest
         if (lane >= o) inc += t;
       }
       int64_t s = (int64_t)hs0 + inc - cnt;
-      for (int64_t q = first; q < last; q += pp.seg_len, ++s) {
-        if (s >= max_seg) continue;
-        seg_hub[s] = hh;
-        seg_begin[s] = (int32_t)q;
-        seg_key[s] = indices[q];
-      }
+      for (int64_t q = first; q < last; q += pp.seg_len, ++s) put(s, q);
     }
   }
   if ((int)blockIdx.x == T.n - 1 && threadIdx.x == 0) {  // the last tile's ends are the totals
@@ -1062,7 +1075,7 @@ isp_status build_packed(isp_csr* A, const partition_params& p1, int mid_t, char*
 }  // namespace
 
 size_t isp_partition_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int stage_min) {
-  const partition_params p1 = get_params(n_rows, nnz, isp_wave_slots());
+  const partition_params p1 = get_params(n_rows, nnz, isp_wave_slots(), n_cols);
   const ws_layout L = make_layout(n_rows, nnz, p1);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, p1);
   const size_t own = L.total + isp_stage::own_bytes(n_cols, nnz, L.total - L.partials, mid_t > 0, stage_min);
@@ -1102,7 +1115,7 @@ isp_status isp_refresh_packed_pair(isp_csr* A, hipStream_t s) {
 isp_status isp_build_handle(int64_t n_rows, int64_t n_cols, int64_t nnz, const int64_t* indptr,
                             const int32_t* indices, const float* values, void* ws, size_t ws_bytes, bool validate,
                             const isp_tuning& tune, hipStream_t s, isp_csr** out, const int* flag, int* host_flag) {
-  const partition_params pp = get_params(n_rows, nnz, isp_wave_slots());
+  const partition_params pp = get_params(n_rows, nnz, isp_wave_slots(), n_cols);
   const ws_layout L = make_layout(n_rows, nnz, pp);
   const int mid_t = mid_threshold(n_rows, n_cols, nnz, pp);
   packed_layout P{};

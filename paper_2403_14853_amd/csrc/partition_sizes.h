@@ -51,8 +51,8 @@ inline int env_int(const char* name, int dflt, int lo, int hi) {
   return (int)v;
 }
 
-// slots: wavefront slots of the device (4,096 on an MI355X: 256 compute units)
-inline partition_params get_params(int64_t n_rows, int64_t nnz, int64_t slots) {
+// slots: wavefront slots of the device (4,096 on an MI355X: 256 compute units); n_cols: where a cut by columns can pay (below)
+inline partition_params get_params(int64_t n_rows, int64_t nnz, int64_t slots, int64_t n_cols = INT64_MAX) {
   partition_params p;
   p.row_cost = 1;
   // Upper limits = what the grouped kernels' per-wave LDS tables hold (block_cost + hub_t <= 768
@@ -61,8 +61,8 @@ inline partition_params get_params(int64_t n_rows, int64_t nnz, int64_t slots) {
   // Small matrices get smaller row blocks, about as many as the chip has wavefront slots (compute units x 16):
   // a wavefront's work is a chain of dependent memory round trips, and a short chain on every slot
   // finishes sooner than a long one on a few (4,096 rows x 9 entries: 16 -> 7 us per SpMM).
-  int64_t auto_cost = (nnz + n_rows + slots - 1) / slots;
-  auto_cost = auto_cost < 16 ? 16 : (auto_cost > 256 ? 256 : auto_cost);
+  const int64_t share = (nnz + n_rows + slots - 1) / slots;  // cost units per slot
+  const int64_t auto_cost = share < 16 ? 16 : (share > 256 ? 256 : share);
   p.block_cost = env_int("ISP_BLOCK_COST", (int)auto_cost, 16, 256);
   // ... and shorter hub segments, for the same reason and because the segments are the heavy items that the
   // launch hands out last: a quarter of the per-slot share, between 80 and 512 entries, rows of more than two
@@ -76,13 +76,28 @@ inline partition_params get_params(int64_t n_rows, int64_t nnz, int64_t slots) {
   // benchmark graphs): segments of at most 320 and pieces from 128 entries are best or within 1 % of it for every
   // kernel on every one of them (233 k columns: SpMM 2.68 -> 2.59 ms, SDDMM 2.71 -> 2.60 ms; 2.4 M columns:
   // FusedMM 5.59 -> 5.41 ms; 1 M columns: FusedMM backward 1.36 -> 1.32 ms).
+  // Where the slots outnumber the items, the longest row of a block and the longest segment are the launch: 48 entries and
+  // 64 to a row up to 28 units per slot (115 k units), 64 and 96 up to 128 (520 k), 80 and 160 above.  With 80 and 160 / 48 and 64 / 64 and
+  // 96 (us; R-MAT): 2,859 rows, 34 k entries, 80 columns: SpMM 7.4 / 6.6 / 7.0, SDDMM 9.7 / 6.4 / 7.6, FusedMM 15.0 / 9.5 / 11.9, its backward
+  // 22.1 / 12.8 / 17.0; 4,092, 90 k, 200 columns: 11.9 / 10.5 / 10.1, 13.1 / 10.3 / 11.1, 32.2 / 17.4 / 26.1, 51.8 / 28.5 / 42.0; 7,881, 157 k, 133:
+  // 15.6 / 13.4 / 12.6, 19.5 / 14.6 / 15.2, 40.8 / 22.8 / 24.1; 30 k, 376 k, 24: 9.5 / 11.2 / 9.0, 8.1 / 8.0 / 7.8, 12.1 / 12.2 / 11.4; 19 k, 436 k, 24:
+  // 9.9 / 11.4 / 10.1.  Over 48 drawn matrices of 3 k to 500 k entries 64 and 96 save 4 % of a SpMM, 14 % of a SDDMM and 17 % of a
+  // FusedMM, and a graph seen once is built as fast; above, more segments cost the build more than they save (0.4 to 6 M entries: builds 20 % longer).
   const int seg_cap = 320;
-  int64_t auto_seg = (nnz + n_rows + slots - 1) / slots / 4;
-  auto_seg = auto_seg < 80 ? 80 : (auto_seg > seg_cap ? seg_cap : auto_seg);
-  const int auto_hub = 2 * auto_seg > 512 ? 512 : (int)(2 * auto_seg);
+  const int seg_min = share <= 28 ? 48 : share <= 128 ? 64 : 80;
+  const int64_t auto_seg = share / 4 < seg_min ? seg_min : (share / 4 > seg_cap ? seg_cap : share / 4);
+  const int auto_hub = seg_min < 80 ? 2 * seg_min - 32 : 2 * auto_seg > 512 ? 512 : (int)(2 * auto_seg);
   p.hub_t = env_int("ISP_HUB_THRESHOLD", auto_hub, 8, 512);
   p.seg_len = env_int("ISP_SEGMENT_LEN", (int)auto_seg, 8, 768);
-  int b = env_int("ISP_BANDS", 32, 1, MAX_BANDS);
+  // Rows are cut into equal segments instead of at column bands on matrices of up to 1.3 M units, and with fewer than 64 Ki columns
+  // up to 4 M: the segments' own order by first column is all the locality that they need, and bands leave about half as many again of
+  // them (a band of 45 entries, chance included, is a whole segment of 80 and the start of another).  us at 32, 64, 128 and 256 columns with 32 bands / without: 12 k columns,
+  // 1.5 M entries: SpMM 20.7 / 18.7, 27.5 / 26.3, 42.8 / 41.2, 79.8 / 79.4, FusedMM 25.8 / 22.8, 36.6 / 33.6, 59 / 55, 108 / 102, the build 82 / 57; 32 k, 4 M:
+  // SpMM 38.4 / 37.2, 58.5 / 57.4, 99.6 / 99.2, 199 / 197, the build 58 / 49; 100 k, 1 M: SpMM 17.3 / 15.9, 25.7 / 25.3, 45.1 / 42.9, 80.7 / 78.8, SDDMM
+  // 15.3 / 14.1, 22.6 / 22.4, 42.1 / 42.7, 87.4 / 88.2; but 50 k, 6 M: SpMM 56.0 / 53.5, 84.8 / 83.7, 147.5 / 150.3, 295 / 300, SDDMM at 256 302 / 317;
+  // 99 k, 3 M, 196 columns 206 / 215; 121 k, 4.5 M, 176 columns 239 / 251.
+  const int auto_bands = share <= 320 || (n_cols < (64 << 10) && share <= 1024) ? 1 : 32;
+  int b = env_int("ISP_BANDS", auto_bands, 1, MAX_BANDS);
   while (b & (b - 1)) b &= b - 1;  // round down to a power of two
   p.bands = b;
   // (the lower limit bounds the number of segments, hence the partial-sum rows the workspace must hold)
