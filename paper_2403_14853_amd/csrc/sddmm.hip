@@ -167,6 +167,12 @@ isp_status launch(const isp_csr* A, const float* U, int64_t ldu, const float* V,
   return ISP_OK;
 }
 
+// Below this size rows wider than 256 columns go 512 at a time (64 lanes, two float4): a pass there is the time of its chains, and two
+// passes stage every entry twice (us, 256 / 512 at a time: R-MAT, 1.5 k rows, 8 k entries, 344 columns 11.8 / 8.6; 4 k, 17 k, 432: 14.2 / 10.4; 20 k,
+// 79 k, 344: 21.7 / 18.0; 10 k, 204 k, 368: 33.5 / 29.8; 13 k, 445 k, 376: 54.8 / 51.0; uniform, 21 k, 420 k, 544: 124 / 125; but 111 k, 801 k, 584: 235 / 247;
+// 11 k, 1.1 M, 272: 130 / 156; 58 k, 1.9 M, 336: 191 / 197).
+constexpr int64_t SDDMM_WIDE_NNZ = 3 << 18;
+
 constexpr int64_t SLICE_FLOATS = 16 << 20;  // V of 64 MB, twice the L2s
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
@@ -194,7 +200,7 @@ isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const
         !A->tune.sddmm_one_pass)
       wp = ISP_WAVE;
     else if (d > 2 * ISP_WAVE && (big || (ldu % 32 == 0 && ldv % 32 == 0 && av.n_cols * ldv >= SLICE_FLOATS))) wp = 2 * ISP_WAVE;
-    else if (d > ISP_PARTIAL_TILE) wp = ISP_PARTIAL_TILE;
+    else if (d > ISP_PARTIAL_TILE) wp = av.nnz < SDDMM_WIDE_NNZ ? 2 * ISP_PARTIAL_TILE : ISP_PARTIAL_TILE;
     isp_status st = ISP_OK;
     for (int k_lo = 0, k_next; k_lo < d && st == ISP_OK; k_lo = k_next) {
       int k_hi = k_lo + wp < d ? k_lo + wp : d;
@@ -207,10 +213,14 @@ isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const
       // 1.2 M 48.9 / 50.0), two above: with one, a wavefront has a single run.  That is only the better way for nearly full rows on graphs
       // with work for several times as many wavefronts as the chip holds (248 columns, us, one / two: 108 k entries
       // 21.8 / 16.8, 1.2 M 116 / 119, 2.4 M 236 / 249, 3 M 325 / 342; 160 columns: 108 k 21.3 / 15.0, 589 k 42.2 / 39.4, 1.2 M 83.8 / 74.1).  In between, one is the better
-      // way already at 589 k entries from 200 columns (45.1 / 47.8, 248 columns 51.7 / 57.5).
+      // way already at 589 k entries from 200 columns (45.1 / 47.8, 248 columns 51.7 / 57.5).  On small matrices, where a wavefront's run is what the
+      // launch takes, two are the better way from 65 columns up (R-MAT, 2.4 k rows, 46 k entries, 104 columns 6.9 / 5.6; 2.8 k, 64 k, 122: 6.8 / 5.6; 7 k, 186 k,
+      // 88: 10.2 / 9.2; 13 k, 247 k, 70: 13.0 / 11.3; uniform, 4.9 k, 67 k, 96: 6.5 / 5.9; but 31 k, 374 k, 120: 28.0 / 29.7).
       if (w <= 32) st = launch_grouped<8, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
       else if (w <= 64) st = launch_grouped<16, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      else if (w <= 128 && av.nnz < (1 << 18)) st = launch_grouped<16, 8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
       else if (w <= 128) st = launch_grouped<32, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      else if (w > ISP_PARTIAL_TILE) st = launch_grouped<64, 8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
       else if (w <= 192 || av.nnz < (1 << 20)) st = launch_grouped<32, 8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
       else st = launch_grouped<64, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
     }
