@@ -17,4 +17,10 @@ namespace isp_dev {
 // store as ever.
 inline bool streams_output(int64_t rows, int64_t d) { return rows * d >= (int64_t)40 << 20; }
 
+// The packed layout's partial rows, `pieces` of them and `width` columns in this launch: from 96 MB on, of which the fix-up would find less in
+// the caches than they cost the gathers.  us with ordinary / these stores: 233 k columns, 115 M entries, some 370 k pieces, 128 columns (190 MB) 2438 / 2413,
+// 602 in five launches 11960 / 11865; 2.4 M, 124 M: 4586 / 4567; 800 k, 40 M, 247 k pieces: 50 columns (49 MB) 763 / 760, 100 (99 MB) 1431 / 1402, 128 1377 /
+// 1366; 120 k, 40 M, 305 k: 32 (39 MB) 281 / 285, 64 (78 MB) 469 / 470, 100 (122 MB) 838 / 835; 100 k, 16 M, 112 k: 32 122 / 124, 64 (29 MB) 202 / 204, 128 (57 MB) 374 / 376.
+inline bool streams_pieces(int64_t pieces, int64_t width) { return pieces * width >= (int64_t)24 << 20; }
+
 }  // namespace isp_dev

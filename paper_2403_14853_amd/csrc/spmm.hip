@@ -83,9 +83,10 @@ isp_status launch_tile(const isp_csr* A, const float* X, int64_t ldx, int d, int
 // MEAN: finished rows are divided by their length (partial rows are not: their fix-up divides).
 // FINISH: hub rows are put together here (hub_finish.h).  A kernel of its own: launches that have none to finish ran 2 % longer
 // with that code in them (4 k rows, 37 k entries 4.41 -> 4.53 us).
-// STREAM: rows of Y that an item finishes are written past the caches (output_rule.h; never with the small LDS tables, whose operand the L2s hold; kernels of their own as well: with the choice at
-// run time the small launch took 4.47 us).
+// STREAM: what is written past the caches: STREAM_ROWS: rows of Y that an item finishes (output_rule.h; never with the small LDS tables, whose operand the L2s
+// hold), STREAM_PIECES: the packed layout's partial rows.  Kernels of their own as well: with the choice at run time the small launch took 4.47 us.
 constexpr int SPMM_RING = 4;
+constexpr int STREAM_ROWS = 1, STREAM_PIECES = 2;
 
 // On the packed layout, launches that gather more than three and a half lines of a row ask for LDS they do not use, so that a
 // compute unit holds four workgroups instead of five: the rows of X that the whole chip has in flight and in use at a time then
@@ -99,7 +100,7 @@ constexpr int SPMM_RING = 4;
 //   2 (64 columns): 2326 / 2325;  1 (32): 1213 / 1248.
 constexpr unsigned SPMM_FOUR_PER_CU = 160 * 1024 / 4 - sizeof(rn_lds);
 
-template <int LPG, bool ADDR32, int VEC, bool MEAN, bool FINISH, int CAP = GS_MAX_ENT, bool STREAM = false>
+template <int LPG, bool ADDR32, int VEC, bool MEAN, bool FINISH, int CAP = GS_MAX_ENT, int STREAM = 0>
 __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
     isp_view A, const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
     const float* __restrict__ values, const float* __restrict__ X, int64_t ldx, int d, int k_base, int n_slices,
@@ -141,8 +142,8 @@ __global__ void __launch_bounds__(ISP_WG) k_spmm_grouped(
   const unsigned ldo = to_partial ? (unsigned)ISP_PARTIAL_TILE : (unsigned)ldy;  // (the launcher checks that it fits)
   auto row_of = [&](int dst) { return out + (uint64_t)(unsigned)dst * ldo; };
   auto put = [&](int dst, const float (&o)[VEC]) {
-    if constexpr (STREAM && VEC == 4) {
-      if (!to_partial) {
+    if constexpr (VEC == 4 && STREAM != 0) {
+      if (STREAM == (STREAM_ROWS | STREAM_PIECES) || to_partial == (STREAM == STREAM_PIECES)) {
         store_vec4_nt(row_of(dst), o);
         return;
       }
@@ -257,7 +258,7 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
   const bool a32 = v.n_cols < (1 << 24) && ldx * 4 < (1 << 24) &&
                    ((uint64_t)v.n_cols * (uint64_t)ldx + (uint64_t)d) * 4u < ((uint64_t)1 << 32);
   const bool finish = VEC == 4 && a32 && n_slices <= HF_SLICES && hf_pays(A, v, LPG);  // (else a fix-up launch adds the hub rows)
-  const bool stream = streams_output(v.n_real_rows, d);
+  const bool stream = streams_output(v.n_real_rows, d), stream_pieces = packed && streams_pieces(A->info.spmm_pieces, width);
   // (one value per stored entry, in the order of the view's entries)
   const float* vals = values_override ? (packed ? values_override_packed : values_override) : v.values;
   const int n_items = v.n_blocks + v.n_seg;
@@ -268,8 +269,13 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
 #define ISP_GO2(A32, MN, FN, ST)                                                                                    \
   k_spmm_grouped<LPG, A32, VEC, MN, FN, GS_MAX_ENT, ST><<<grid, ISP_WG, spare, s>>>(v, v.indptr, v.indices, vals, X, ldx, d, \
                                                                                     k_base, n_slices, Y, ldy)
-#define ISP_GO1(A32, MN, FN) do { if (stream) ISP_GO2(A32, MN, FN, A32 && VEC == 4); else ISP_GO2(A32, MN, FN, false); } while (0)
-#define ISP_GO(A32, MN) do { if (finish) ISP_GO1(A32, MN, A32 && VEC == 4); else ISP_GO1(A32, MN, false); } while (0)
+#define ISP_GO1(A32, MN, FN) do { if (stream) ISP_GO2(A32, MN, FN, A32 && VEC == 4 ? STREAM_ROWS : 0); else ISP_GO2(A32, MN, FN, 0); } while (0)
+#define ISP_GO_PACKED(A32, MN)                                                                                         \
+  do {                                                                                                              \
+    if (stream) ISP_GO2(A32, MN, false, A32 && VEC == 4 ? STREAM_ROWS | STREAM_PIECES : 0);                            \
+    else ISP_GO2(A32, MN, false, A32 && VEC == 4 ? STREAM_PIECES : 0);                                                 \
+  } while (0)
+#define ISP_GO(A32, MN) do { if (stream_pieces) ISP_GO_PACKED(A32, MN); else if (finish) ISP_GO1(A32, MN, A32 && VEC == 4); else ISP_GO1(A32, MN, false); } while (0)
     // (one group to a wavefront, 129 to 224 columns, has work for 14 per compute unit before seven at a time pay: 25 k columns,
     // 408 k entries, 208 columns (6.6 per unit) 31.4 us with five, 33.8 with seven; 17 k, 601 k: 176 (8.5) 34.7 / 36.7; 23 k, 1 M: 135 (17.2)
     // 51.2 / 46.8; 22 k, 862 k: 207 (14.8) 51.0 / 49.8)
@@ -291,6 +297,7 @@ isp_status launch_grouped(const isp_csr* A, const float* X, int64_t ldx, int d, 
 #undef ISP_GO
 #undef ISP_GO1
 #undef ISP_GO2
+#undef ISP_GO_PACKED
     ISP_LAUNCH_CHECK();
   }
   if (v.n_hub > 0 && !finish) {
