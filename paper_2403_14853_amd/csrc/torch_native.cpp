@@ -28,6 +28,12 @@ PyObject* g_transpose = nullptr;  // binding.csr_transpose_cached
 struct Cell {
   std::atomic<isp_csr_t*> h{nullptr};
   int64_t n_rows = 0, n_cols = 0, nnz = 0;
+  void* home = nullptr;            // the stream that was current when the handle was made: its workspace's own
+  std::atomic<bool> away{false};   // calls have run on another one
+  isp_csr_t* on(void* stream) {    // the handle for a call on `stream`
+    if (stream != home) away.store(true, std::memory_order_relaxed);
+    return h;
+  }
 };
 using CellPtr = std::shared_ptr<Cell>;
 
@@ -125,7 +131,22 @@ PyObject* py_cell(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   c->n_cols = PyLong_AsLongLong(a[2]);
   c->nnz = PyLong_AsLongLong(a[3]);
   if (PyErr_Occurred()) return nullptr;
+  if (c->h.load()) c->home = c10::hip::getCurrentHIPStream().stream();
   return wrap(std::move(c), CELL);
+}
+// (cell, stream): a call on that stream is about to use the handle
+PyObject* py_cell_on(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
+  ISP_ARGS(2)
+  Cell* c = cell_of(a[0]);
+  if (!c) return nullptr;
+  c->on(stream_of(a[1]));
+  Py_RETURN_NONE;
+}
+PyObject* py_cell_away(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
+  ISP_ARGS(1)
+  Cell* c = cell_of(a[0]);
+  if (!c) return nullptr;
+  return PyBool_FromLong(c->away.load());
 }
 PyObject* py_cell_clear(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   ISP_ARGS(1)
@@ -144,7 +165,7 @@ PyObject* py_spmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   if (!c || !dense_of(a[1], X) || !dense_of(a[2], Y)) return nullptr;
   if (X.rows != c->n_cols || Y.rows != c->n_rows || Y.d != X.d) return fail("X has A's columns as rows, Y its rows, both the same width");
   void* s = stream_of(a[3]);
-  return call([&] { return FN(c->h, X.p, X.ld, (int32_t)X.d, Y.p, Y.ld, s); });
+  return call([&] { return FN(c->on(s), X.p, X.ld, (int32_t)X.d, Y.p, Y.ld, s); });
 }
 
 // (cell, U, V, out, flags, stream)
@@ -159,7 +180,7 @@ PyObject* py_sddmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   const unsigned flags = (unsigned)PyLong_AsUnsignedLong(a[4]);
   void* s = stream_of(a[5]);
   float* o = static_cast<float*>(out.data_ptr());
-  return call([&] { return isp_sddmm(c->h, U.p, U.ld, V.p, V.ld, (int32_t)U.d, flags, o, s); });
+  return call([&] { return isp_sddmm(c->on(s), U.p, U.ld, V.p, V.ld, (int32_t)U.d, flags, o, s); });
 }
 
 // (cell, X, Y, op, stream)
@@ -172,7 +193,7 @@ PyObject* py_fusedmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   const int op = (int)PyLong_AsLong(a[3]);
   void* s = stream_of(a[4]);
   if (PyErr_Occurred()) return nullptr;
-  return call([&] { return isp_fusedmm(c->h, X.p, X.ld, (int32_t)X.d, op, Y.p, Y.ld, s); });
+  return call([&] { return isp_fusedmm(c->on(s), X.p, X.ld, (int32_t)X.d, op, Y.p, Y.ld, s); });
 }
 
 // (cell, X, dY, dX, op, stream)
@@ -185,7 +206,7 @@ PyObject* py_fusedmm_backward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   const int op = (int)PyLong_AsLong(a[4]);
   void* s = stream_of(a[5]);
   if (PyErr_Occurred()) return nullptr;
-  return call([&] { return isp_fusedmm_backward(c->h, X.p, X.ld, G.p, G.ld, (int32_t)X.d, op, O.p, O.ld, s); });
+  return call([&] { return isp_fusedmm_backward(c->on(s), X.p, X.ld, G.p, G.ld, (int32_t)X.d, op, O.p, O.ld, s); });
 }
 
 // The arg array of min / max (None: absent).
@@ -214,7 +235,7 @@ PyObject* py_spmm_reduce(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   const int red = (int)PyLong_AsLong(a[3]);
   void* s = stream_of(a[5]);
   if (PyErr_Occurred()) return nullptr;
-  return call([&] { return isp_spmm_reduce(c->h, X.p, X.ld, (int32_t)X.d, red, Y.p, Y.ld, arg, s); });
+  return call([&] { return isp_spmm_reduce(c->on(s), X.p, X.ld, (int32_t)X.d, red, Y.p, Y.ld, arg, s); });
 }
 
 // (cell, dY, dX, reduce, arg, stream)
@@ -229,7 +250,7 @@ PyObject* py_spmm_reduce_backward(PyObject*, PyObject* const* a, Py_ssize_t narg
   const int red = (int)PyLong_AsLong(a[3]);
   void* s = stream_of(a[5]);
   if (PyErr_Occurred()) return nullptr;
-  return call([&] { return isp_spmm_reduce_backward(c->h, G.p, G.ld, (int32_t)G.d, red, arg, O.p, O.ld, s); });
+  return call([&] { return isp_spmm_reduce_backward(c->on(s), G.p, G.ld, (int32_t)G.d, red, arg, O.p, O.ld, s); });
 }
 
 // ---- autograd -------------------------------------------------------------------------------------------------
@@ -267,7 +288,7 @@ void sync_values(Graph& g) {
   if (!g.values.defined()) return;
   const uint32_t v = g.values._version();
   if (v == g.version) return;
-  check(isp_csr_values_changed(g.A->h, current_stream()));
+  check(isp_csr_values_changed(g.A->on(current_stream()), current_stream()));
   g.version = v;
 }
 
@@ -288,7 +309,8 @@ isp_csr_t* transpose(Graph& g) {
       throw python_error(std::move(e));
     }
   }
-  return g.At->h;
+  g.A->on(current_stream());  // (its entries' tables and its scratch are used with the transpose's)
+  return g.At->on(current_stream());
 }
 
 Tensor new_like(const Tensor& t, int64_t rows, int64_t d) { return at::empty({rows, d}, t.options().requires_grad(false)); }
@@ -314,7 +336,7 @@ struct SpmmBackward : torch::autograd::Node {
       const Tensor x = X.unpack();
       const Dense V = dense(x);
       out[0] = at::empty({graph->A->nnz}, dY.options());
-      check(isp_sddmm(graph->A->h, G.p, G.ld, V.p, V.ld, (int32_t)G.d, 0, static_cast<float*>(out[0].data_ptr()), current_stream()));
+      check(isp_sddmm(graph->A->on(current_stream()), G.p, G.ld, V.p, V.ld, (int32_t)G.d, 0, static_cast<float*>(out[0].data_ptr()), current_stream()));
     }
     return out;
   }
@@ -334,7 +356,7 @@ struct ReduceBackward : torch::autograd::Node {
     const Dense G = dense(dY);
     out[0] = new_like(dY, graph->A->n_cols, G.d);
     const Dense O = dense(out[0]);
-    check(isp_spmm_reduce_backward(graph->A->h, G.p, G.ld, (int32_t)G.d, reduce,
+    check(isp_spmm_reduce_backward(graph->A->on(current_stream()), G.p, G.ld, (int32_t)G.d, reduce,
                                    arg.defined() ? static_cast<const int32_t*>(arg.data_ptr()) : nullptr, O.p, O.ld, current_stream()));
     return out;
   }
@@ -354,7 +376,7 @@ struct FusedBackward : torch::autograd::Node {
     const Dense V = dense(x), G = dense(dY);
     out[0] = new_like(x, V.rows, V.d);
     const Dense O = dense(out[0]);
-    check(isp_fusedmm_backward(graph->A->h, V.p, V.ld, G.p, G.ld, (int32_t)V.d, ISP_OP_SIGMOID, O.p, O.ld, current_stream()));
+    check(isp_fusedmm_backward(graph->A->on(current_stream()), V.p, V.ld, G.p, G.ld, (int32_t)V.d, ISP_OP_SIGMOID, O.p, O.ld, current_stream()));
     return out;
   }
 };
@@ -419,7 +441,7 @@ PyObject* py_ag_spmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
       Y = new_like(xc, g->A->n_rows, X.d);
       const Dense O = dense(Y);
       sync_values(*g);
-      check(isp_spmm(g->A->h, X.p, X.ld, (int32_t)X.d, O.p, O.ld, current_stream()));
+      check(isp_spmm(g->A->on(current_stream()), X.p, X.ld, (int32_t)X.d, O.p, O.ld, current_stream()));
     }
     if (torch::autograd::compute_requires_grad(values, x)) {
       auto node = std::shared_ptr<SpmmBackward>(new SpmmBackward(), torch::autograd::deleteNode);
@@ -456,7 +478,7 @@ PyObject* py_ag_reduce(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
       if (reduce != ISP_REDUCE_MEAN) arg = at::empty({g->A->n_rows, X.d}, Y.options().dtype(at::kInt));
       const Dense O = dense(Y);
       sync_values(*g);
-      check(isp_spmm_reduce(g->A->h, X.p, X.ld, (int32_t)X.d, reduce, O.p, O.ld,
+      check(isp_spmm_reduce(g->A->on(current_stream()), X.p, X.ld, (int32_t)X.d, reduce, O.p, O.ld,
                             arg.defined() ? static_cast<int32_t*>(arg.data_ptr()) : nullptr, current_stream()));
     }
     if (torch::autograd::compute_requires_grad(x)) {
@@ -492,7 +514,7 @@ PyObject* py_ag_fused(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
       Y = new_like(xc, X.rows, X.d);
       const Dense O = dense(Y);
       sync_values(*g);
-      check(isp_fusedmm(g->A->h, X.p, X.ld, (int32_t)X.d, ISP_OP_SIGMOID, O.p, O.ld, current_stream()));
+      check(isp_fusedmm(g->A->on(current_stream()), X.p, X.ld, (int32_t)X.d, ISP_OP_SIGMOID, O.p, O.ld, current_stream()));
     }
     if (torch::autograd::compute_requires_grad(x)) {
       auto node = std::shared_ptr<FusedBackward>(new FusedBackward(), torch::autograd::deleteNode);
@@ -532,6 +554,8 @@ PyMethodDef methods[] = {
     ISP_DEF("init", py_init),
     ISP_DEF("cell", py_cell),
     ISP_DEF("cell_clear", py_cell_clear),
+    ISP_DEF("cell_on", py_cell_on),
+    ISP_DEF("cell_away", py_cell_away),
     ISP_DEF("spmm", py_spmm<isp_spmm>),
     ISP_DEF("spmm_static_scratch", py_spmm<isp_spmm_static_scratch>),
     ISP_DEF("sddmm", py_sddmm),
