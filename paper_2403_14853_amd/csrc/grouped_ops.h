@@ -21,6 +21,11 @@ namespace isp_dev {
 // either edge<LPG>(args, a, src, rowop, acc, lane_on) accumulating into the row's result, or (PER_ENTRY)
 // partial(src, rowop, lane_cols) returning the lane's share of a sum over the group, which times the entry's value is stored
 // for the entry.
+// A policy with PAIR_LPG has three steps in place of edge(): dots(x, r, lane_cols, p), the lane's shares of NDOT dot products (0:
+// none are needed); scalars(t, s), what the edge function makes of their totals, NSCAL numbers; apply(a, s, x, acc).  Groups of PAIR_LPG
+// lanes and more work on two entries at a time where the ring holds four: the totals share their reduction over the lanes and one evaluation
+// of the edge function, whose exponential and reciprocal take as long as eight other instructions (from which width on that pays: with
+// the policies).
 // A policy with HAS_VAL2 = true also gets a second value per stored entry, args::val2[p] (a parallel array in
 // the order of the matrix's entries; null = all ones), as an extra argument of edge().
 // ADDR32: every byte offset into the gathered operands fits 32 bits and both factors of column * row pitch
@@ -42,6 +47,16 @@ template <class P, class = void>
 struct policy_has_val2 : std::false_type {};
 template <class P>
 struct policy_has_val2<P, std::void_t<decltype(P::HAS_VAL2)>> : std::bool_constant<P::HAS_VAL2> {};
+
+template <class P, class = void>
+struct policy_in_steps : std::false_type {};
+template <class P>
+struct policy_in_steps<P, std::void_t<decltype(P::PAIR_LPG)>> : std::true_type {};
+template <class P, int LPG, int RING>
+constexpr bool policy_pairs() {
+  if constexpr (policy_in_steps<P>::value) return P::NDOT > 0 && LPG >= P::PAIR_LPG && RING >= 4;
+  else return false;
+}
 
 // FINISH: the launch puts hub rows together (hub_finish.h).
 template <class P, int LPG, int W, bool ADDR32, bool TAIL, bool FINISH = false, class Lds>
@@ -178,7 +193,35 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
     float x[RING][NSRC][W], r[RING][NR + 1][W], a2[RING];
     bool first = true;  // the step to take next is its row's first in this run
     bool firsts[RING];  // PER_ENTRY, where nothing else happens at row ends: the same, kept since the step was requested
-    rn_stream<RING, !SEG && !P::PER_ENTRY, !SEG, CHUNK>(
+    // two steps at a time, where that leaves another two in flight
+    constexpr bool PAIRS = policy_pairs<P, LPG, RING>();
+    float sc[2][2];  // (of the pair's steps, NSCAL each)
+    auto pair = [&](auto u0) {
+      if constexpr (PAIRS) {
+        constexpr int U = decltype(u0)::value, ND = P::NDOT, NS = P::NSCAL;
+        float p[2][ND], t[ND], o[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          if constexpr (!SEG) {
+            if (firsts[U + k] || !FIRST_ONLY) {
+#pragma unroll
+              for (int j = 0; j < NROW; ++j)
+#pragma unroll
+                for (int v = 0; v < W; ++v) rS[j][v] = r[U + k][j < NR ? j : 0][v];
+            }
+          }
+          P::template dots<W, TAIL>(x[U + k], rS, lc, p[k]);
+#pragma unroll
+          for (int j = 0; j < ND; ++j) asm volatile("" : "+v"(p[k][j]));  // (formed before the next step's row operand takes the registers)
+        }
+#pragma unroll
+        for (int j = 0; j < ND; ++j) t[j] = group_pair_sum<LPG>(p[0][j], p[1][j], lane);
+        P::scalars(t, o);
+#pragma unroll
+        for (int j = 0; j < NS; ++j) group_pair_split<LPG>(o[j], lane, sc[0][j], sc[1][j]);
+      }
+    };
+    rn_stream<RING, !SEG && !P::PER_ENTRY, !SEG, CHUNK, PAIRS>(
         L, R,
         [&](int u, int c, int s, int row, bool in_first) {
 #pragma unroll
@@ -195,7 +238,7 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
           }
         },
         [&](auto u, float a, int s) {
-          if constexpr (!SEG) {
+          if constexpr (!SEG && !PAIRS) {
             if ((P::PER_ENTRY ? firsts[u] : first) || !FIRST_ONLY) {
 #pragma unroll
               for (int k = 0; k < NROW; ++k)
@@ -210,6 +253,18 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
             share_a[k] = a;
             asm volatile("" : "+v"(share[k]));  // (else the shares are formed with their sum, and their operands held until then)
             if constexpr (k == 3) park(s - 3, 4);
+          } else if constexpr (PAIRS) {
+            P::template apply<W>(a, sc[decltype(u)::value % 2], x[u], acc);
+          } else if constexpr (policy_in_steps<P>::value) {
+            constexpr int ND = P::NDOT;
+            float t[2] = {}, o[2];  // (all of them, where no dot product is needed: scalars() reads them)
+            if constexpr (ND > 0) {
+              P::template dots<W, TAIL>(x[u], rS, lc, t);
+#pragma unroll
+              for (int j = 0; j < ND; ++j) t[j] = group_allreduce<LPG>(t[j]);
+            }
+            P::scalars(t, o);
+            P::template apply<W>(a, o, x[u], acc);
           } else if constexpr (policy_has_val2<P>::value) {
             P::template edge<LPG, W, TAIL>(pa, a, a2[u], x[u], rS, acc, lc);
           } else {
@@ -225,7 +280,8 @@ __device__ inline void fused_grouped_item(const isp_view& A, const int64_t* __re
           ended = true;
 #pragma unroll
           for (int v = 0; v < W; ++v) acc[v] = 0.f;
-        });
+        },
+        pair);
   };
   if (it.is_seg) run(std::true_type{}); else run(std::false_type{});
 

@@ -194,8 +194,15 @@ struct rn_cursor {
 // A round of RING steps is consumed while the next one is requested, slot by slot, into the same registers; the
 // entries are read from LDS CHUNK steps before they are needed.  A row's end is the step number at which it
 // ends, kept per lane: one comparison a step.
-template <int RING, bool ENDS, bool ROWS, int CHUNK = RN_CHUNK, class Lds, class Load, class Add, class End>
-__device__ __forceinline__ void rn_stream(const Lds& L, const rn_run& R, Load&& load, Add&& add, End&& end_row) {
+// PAIRS: slots are taken and requested again two at a time; pair(u) comes before add(u) and add(u + 1), of which the second is
+// left out (and what slot u + 1 holds means nothing) where a run ends with slot u.
+struct rn_no_pairs {
+  template <class U>
+  __device__ __forceinline__ void operator()(U) const {}
+};
+template <int RING, bool ENDS, bool ROWS, int CHUNK = RN_CHUNK, bool PAIRS = false, class Lds, class Load, class Add, class End,
+          class Pair = rn_no_pairs>
+__device__ __forceinline__ void rn_stream(const Lds& L, const rn_run& R, Load&& load, Add&& add, End&& end_row, Pair&& pair = Pair()) {
   static_assert(RING % (2 * CHUNK) == 0 && 2 * CHUNK <= RN_PAD, "fetches alternate between two buffers");
   const int2* __restrict__ ep = L.ent + R.start;
   constexpr int C = CHUNK;
@@ -223,6 +230,12 @@ __device__ __forceinline__ void rn_stream(const Lds& L, const rn_run& R, Load&& 
         out.advance(L, R);
       }
   };
+  auto take_pair = [&](auto u, int s0, bool both) {  // slots u, u + 1
+    pair(u);
+    take(u, s0);
+    if (both) take(std::integral_constant<int, decltype(u)::value + 1>{}, s0);
+  };
+  static_assert(!PAIRS || (RING % 2 == 0 && CHUNK == 2), "a pair's entries are read together");
   // Requests behind a condition make the compiler wait for everything in flight, so the steady state has none.  The
   // steps left over after the last whole round do ask whether there is a step.
   const int rounds = R.steps / RING, rest = R.steps - rounds * RING;  // wave-uniform
@@ -237,14 +250,21 @@ __device__ __forceinline__ void rn_stream(const Lds& L, const rn_run& R, Load&& 
     for (int r = 1; r < rounds; ++r, s0 += RING) {
       rn_for<RING>([&](auto u) {
         if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], s0 + RING + u + C);
-        take(u, s0);
-        request(u, e[(u / C) & 1][u % C], s0 + RING + u);
+        if constexpr (!PAIRS) {
+          take(u, s0);
+          request(u, e[(u / C) & 1][u % C], s0 + RING + u);
+        } else if constexpr (u % 2 == 0) {
+          take_pair(u, s0, true);
+          request(u, e[(u / C) & 1][0], s0 + RING + u);
+          request(u + 1, e[(u / C) & 1][1], s0 + RING + u + 1);
+        }
       });
     }
     if (rest > 0) {
       rn_for<RING>([&](auto u) {
         if constexpr (u % C == 0) fetch(e[(u / C + 1) & 1], s0 + RING + u + C);
-        take(u, s0);
+        if constexpr (!PAIRS) take(u, s0);
+        else if constexpr (u % 2 == 0) take_pair(u, s0, true);
         if (u < rest) request(u, e[(u / C) & 1][u % C], s0 + RING + u);
       });
       s0 += RING;
@@ -257,7 +277,11 @@ __device__ __forceinline__ void rn_stream(const Lds& L, const rn_run& R, Load&& 
   }
   const int left = R.cnt - s0;  // of this lane's run
   rn_for<RING>([&](auto u) {
-    if (u < left) take(u, s0);
+    if constexpr (!PAIRS) {
+      if (u < left) take(u, s0);
+    } else if constexpr (u % 2 == 0) {
+      if (u < left) take_pair(u, s0, u + 1 < left);
+    }
   });
 }
 
