@@ -59,6 +59,13 @@ isp_status run_grouped(const isp_csr* A, const typename P::args& pa, int d, floa
   return ISP_OK;
 }
 
+// Up to 16 columns four lanes hold a row, and a step serves 16 entries instead of 8, half of whose lanes were idle; below this size, where a
+// launch is the time of its chains, the longer start of 16 runs counts.  us with 8 / 4 lanes, forward and backward (R-MAT, directed, 8 columns): 3 k
+// rows, 30 k entries 5.3 / 5.5, 12.0 / 12.0; 10 k, 100 k: 6.3 / 6.1, 15.0 / 13.3; 20 k, 300 k: 10.1 / 9.0, 24.7 / 21.2; 100 k, 1 M: 17.9 / 14.7,
+// 49.5 / 41.3; 60 k, 2.8 M: 35.2 / 28.0, 96.6 / 77.5 (16 columns 36.0 / 29.8, 99.1 / 81.0; symmetric 65.4 / 47.3); 200 k, 8 M: 91.7 / 73.5, 250 / 199; 230 k,
+// 60 M: 521 / 413, 1489 / 1140; uniform, 500 k, 8 M, which waits for its gathers: 117.2 / 116.6, 385 / 386.
+constexpr int64_t FUSED_NARROW_NNZ = 64 << 10;
+
 // One or two float4 per lane.  Two halve the lanes per dot product, so a step covers twice the entries with one
 // lane-reduction stage and one evaluation of the edge function less per entry, but hold twice the registers and load
 // the row operand with every step.  With as few entries as the chip's wavefronts finish in a few rounds the length of their runs counts,
@@ -85,6 +92,7 @@ isp_status run_grouped_d(const isp_csr* A, const typename P::args& pa, int d, fl
     if (d <= 128) return run_grouped<P, 16, 8, false>(A, pa, d, Y, ldy, s);
     return run_grouped<P, 32, 8, false>(A, pa, d, Y, ldy, s);
   }
+  if (d <= 16 && A->info.nnz >= FUSED_NARROW_NNZ) return run_grouped<P, 4, 4, true>(A, pa, d, Y, ldy, s);
   if (d <= 32) return run_grouped<P, 8, 4, true>(A, pa, d, Y, ldy, s);
   if (!two_vectors(A, d)) {
     if (d <= 64) return run_grouped<P, 16, 4, true>(A, pa, d, Y, ldy, s);

@@ -20,8 +20,8 @@ __device__ inline float group_allreduce(float v) {
   // quad_perm [1,0,3,2] and [2,3,0,1]: xor 1, xor 2
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));
-  // row_half_mirror (reverse within 8 lanes): pairs the two quads of an 8-lane half
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));
+  if constexpr (LPG >= 8)  // row_half_mirror (reverse within 8 lanes): pairs the two quads of an 8-lane half
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));
   if constexpr (LPG >= 16)  // row_mirror (reverse within 16 lanes)
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, true));
   if constexpr (LPG >= 32)  // swap halves of 32 lanes: swizzle bit mode, xor mask 0x10
@@ -32,12 +32,13 @@ __device__ inline float group_allreduce(float v) {
 
 // Four sums of LPG lanes at once: of a value per lane and step (p0 ... p3) each lane gets the group's total of step
 // group_step<LPG>(lane), and of the lanes with the same total group_step_owner<LPG> says one.  A stage halves the
-// values while there are several (a lane keeps one and hands the other to its partner), so four totals take 10 or 11 instructions
-// where four sums after one another take 12 (8 lanes) to 24 (64), and what is computed from a total is computed once,
+// values while there are several (a lane keeps one and hands the other to its partner), so four totals take 9 to 11 instructions
+// where four sums after one another take 8 (4 lanes) to 24 (64), and what is computed from a total is computed once,
 // not in every lane of the group.
 template <int LPG>
 __device__ __forceinline__ int group_step(int lane) {
-  if constexpr (LPG == 8) return (lane >> 2 & 1) | (lane & 2);
+  if constexpr (LPG == 4) return (lane >> 1 & 1) | (lane << 1 & 2);
+  else if constexpr (LPG == 8) return (lane >> 2 & 1) | (lane & 2);
   else if constexpr (LPG == 16) return (lane >> 3 & 1) | (lane >> 1 & 2);
   else if constexpr (LPG == 32) return (lane >> 4 & 1) | (lane >> 2 & 2);
   else return (lane >> 5 & 1) | (lane >> 3 & 2);
@@ -67,7 +68,9 @@ constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_ROR
 template <int LPG>
 __device__ __forceinline__ float group_sum_steps(float p0, float p1, float p2, float p3, int lane) {
   float v;
-  if constexpr (LPG == 8) {
+  if constexpr (LPG == 4) {
+    return pair_sum<DPP_XOR1>(pair_sum<DPP_XOR2>(p0, p1, lane & 2), pair_sum<DPP_XOR2>(p2, p3, lane & 2), lane & 1);
+  } else if constexpr (LPG == 8) {
     v = pair_sum<DPP_XOR2>(pair_sum<DPP_HALF_MIRROR>(p0, p1, lane & 4), pair_sum<DPP_HALF_MIRROR>(p2, p3, lane & 4), lane & 2);
     return v + dpp_of<DPP_XOR1>(v);
   } else if constexpr (LPG == 16) {

@@ -1,0 +1,50 @@
+"""SDDMM and FusedMM up to 16 columns, where four lanes hold a row: widths around it, rows of every remainder of its 16 runs, hub rows, and sizes
+on both sides of the one from which FusedMM takes it."""
+import numpy as np
+import pytest
+import torch
+
+import graphgen
+import oracle
+import paper_2403_14853_amd as isp
+from gpu_util import assert_close, build, dev
+
+pytestmark = pytest.mark.gpu
+
+
+def graph(n, nnz, seed):
+    """Rows of 0 ... 33 entries, every length among them, and three hub rows; exactly nnz entries."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, 34, n)
+    lens[:34] = np.arange(34)
+    lens[34:37] = [900, 331, 177]
+    k = n - 1
+    while lens.sum() != nnz:  # (the last rows make up the difference)
+        step = int(np.clip(nnz - lens.sum(), -lens[k], 60 - lens[k]))
+        lens[k] += step
+        k -= 1
+    indptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    indices = np.concatenate([np.sort(rng.choice(n, m, replace=False)) for m in lens]).astype(np.int32)
+    return indptr, indices, graphgen.uniform(nnz, seed)
+
+
+@pytest.mark.parametrize("d", [4, 5, 7, 8, 12, 13, 16, 17])
+@pytest.mark.parametrize("nnz", [(64 << 10) - 1, 64 << 10])
+def test_narrow_rows(d, nnz):
+    n = 4000
+    indptr, indices, values = graph(n, nnz, d)
+    rng = np.random.default_rng(d)
+    X = (0.5 * rng.standard_normal((n, d))).astype(np.float32)
+    G = rng.standard_normal((n, d)).astype(np.float32)
+    A = build(indptr, indices, values)
+    isp.csr_transpose_cached(A)
+    out = torch.empty(nnz, device="cuda")
+    for scale in (False, True):
+        isp.sddmm(A, dev(G), dev(X), out, scale_by_a=scale)
+        assert_close(out, *oracle.sddmm(indptr, indices, values if scale else None, G, X, scale_by_a=scale), "sddmm")
+    Y = torch.empty(n, d, device="cuda")
+    for op in ("sigmoid", "dot", "one"):
+        isp.fusedmm(A, dev(X), Y, op=op)
+        assert_close(Y, *oracle.fusedmm(indptr, indices, values, X, op=op), "forward " + op)
+        isp.fusedmm_backward(A, dev(X), dev(G), Y, op=op)
+        assert_close(Y, *oracle.fusedmm_backward(indptr, indices, values, X, G, op=op), "backward " + op)
