@@ -712,7 +712,11 @@ isp_status fwd_all(const isp_csr* A, const float* X, int64_t ldx, int d, float* 
       for (int k0 = 0; k0 < d && st == ISP_OK; k0 += 2 * ISP_WAVE) {
         const int k_base = d - k0 < 4 ? d - 4 : k0;  // (no launch narrower than a float4 lane)
         const int w = d - k_base < 2 * ISP_WAVE ? d - k_base : 2 * ISP_WAVE;
-        if (w <= 32) st = minmax_grouped_tile<8, MODE>(A, X, ldx, d, k_base, Y, ldy, arg, s);
+        // Four lanes to a row of up to 16 columns from 512 Ki entries (us with 8 / 4, max, 8 columns, R-MAT: 3 k rows, 30 k entries 10.1 / 10.5; 10 k, 100 k: 11.2 /
+        // 11.7; 20 k, 300 k: 15.4 / 15.0; 60 k, 600 k: 18.7 / 17.6; 100 k, 1 M: 25.2 / 23.1; 60 k, 2.8 M: 41.9 / 38.3; 200 k, 8 M: 103 / 92; 230 k, 60 M: 623 / 545;
+        // uniform, 100 k, 1 M 15.8 / 12.6, 500 k, 8 M: 117.7 / 114.2).
+        if (w <= 16 && av.nnz >= (512 << 10)) st = minmax_grouped_tile<4, MODE>(A, X, ldx, d, k_base, Y, ldy, arg, s);
+        else if (w <= 32) st = minmax_grouped_tile<8, MODE>(A, X, ldx, d, k_base, Y, ldy, arg, s);
         else if (w <= 64) st = minmax_grouped_tile<16, MODE>(A, X, ldx, d, k_base, Y, ldy, arg, s);
         else st = minmax_grouped_tile<32, MODE>(A, X, ldx, d, k_base, Y, ldy, arg, s);
       }

@@ -1,5 +1,5 @@
-"""SDDMM and FusedMM up to 16 columns, where four lanes hold a row: widths around it, rows of every remainder of its 16 runs, hub rows, and sizes
-on both sides of the one from which FusedMM takes it."""
+"""SDDMM, FusedMM and min / max up to 16 columns, where four lanes hold a row: widths around it, rows of every remainder of its 16 runs, hub rows, and sizes
+on both sides of those from which FusedMM and min / max take it."""
 import numpy as np
 import pytest
 import torch
@@ -48,3 +48,24 @@ def test_narrow_rows(d, nnz):
         assert_close(Y, *oracle.fusedmm(indptr, indices, values, X, op=op), "forward " + op)
         isp.fusedmm_backward(A, dev(X), dev(G), Y, op=op)
         assert_close(Y, *oracle.fusedmm_backward(indptr, indices, values, X, G, op=op), "backward " + op)
+
+
+@pytest.mark.parametrize("d", [4, 6, 11, 16])
+@pytest.mark.parametrize("nnz", [(512 << 10) - 1, 512 << 10])
+@pytest.mark.parametrize("integers", [False, True])
+def test_narrow_min_max(d, nnz, integers):
+    n = 32_000
+    indptr, indices, values = graph(n, nnz, d)
+    rng = np.random.default_rng(d)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    if integers:  # many equal products: the first entry wins
+        values = rng.integers(-1, 2, nnz).astype(np.float32)
+        X = rng.integers(-2, 3, (n, d)).astype(np.float32)
+    A = build(indptr, indices, values)
+    for reduce in ("min", "max"):
+        Y = torch.full((n, d), float("nan"), device="cuda")
+        arg = torch.full((n, d), -7, dtype=torch.int32, device="cuda")
+        isp.spmm_reduce(A, dev(X), Y, reduce, arg)
+        ref, ref_arg, _ = oracle.spmm_reduce(indptr, indices, values, X, reduce)
+        assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
+        assert np.array_equal(arg.cpu().numpy(), ref_arg)
