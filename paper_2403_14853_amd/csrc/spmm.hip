@@ -360,7 +360,9 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
   //    start anywhere and are not copied (below): there every launch pays for the lines that its edges cut (602 columns:
   //    667 -> 620 on 2.4 M entries, 4931 -> 4584 on 16.9 M);
   //  - in a launch of up to 128 columns the smallest group that covers them wins (groups of 4 lanes, which share an
-  //    instruction between 16 entries, only from 1 M entries up: they take longer to set an item up);
+  //    instruction between 16 entries, only from 768 Ki entries up: they take longer to set an item up; us with 8 / 4 lanes, 8 and 16 columns,
+  //    R-MAT: 10 k rows, 100 k entries 6.2 / 6.2, 6.1 / 6.1; 60 k, 600 k: 10.4 / 10.5, 10.3 / 10.7; 200 k, 800 k: 13.9 / 11.8, 14.6 / 13.1; 5 k, 800 k:
+  //    12.5 / 10.8, 12.0 / 10.7; 100 k, 990 k: 14.5 / 13.0, 15.2 / 14.7; uniform, 30 k, 120 k 4.9 / 5.2, 5.1 / 5.2, 50 k, 900 k 8.8 / 8.2, 9.5 / 8.8);
   //  - 128 whole-line columns run as two 64-column slices, dealt to alternating XCDs, where the dense operand is far
   //    larger than an L2 (each L2 then keeps half-rows of twice as many hot columns): from 80 k columns up (60 k: 47 ->
   //    50), but with the packed layout, whose bands already fit, only from 512 k (233 k columns: 2509 -> 2665; 2.4 M:
@@ -393,7 +395,7 @@ isp_status isp_spmm_grouped_launch(const isp_csr* A, const float* X, int64_t ldx
     const int k_base = isp_stage::tile_start(k0, d);
     w = isp_stage::tile_width(k_base, d, tile, av.n_cols);
     int lpg = 32;
-    if (w <= 16 && av.nnz >= 1000000) lpg = 4;
+    if (w <= 16 && av.nnz >= (768 << 10)) lpg = 4;
     else if (w <= 32) lpg = 8;
     else if (w <= 64 || (w == 128 && slices)) lpg = 16;
     else if (w > 128 && w <= 224) lpg = 64;

@@ -1,5 +1,5 @@
-"""SDDMM, FusedMM and min / max up to 16 columns, where four lanes hold a row: widths around it, rows of every remainder of its 16 runs, hub rows, and sizes
-on both sides of those from which FusedMM and min / max take it."""
+"""SpMM, SDDMM, FusedMM and min / max up to 16 columns, where four lanes hold a row: widths around it, rows of every remainder of its 16 runs, hub rows, and sizes
+on both sides of those from which SpMM, FusedMM and min / max take it."""
 import numpy as np
 import pytest
 import torch
@@ -69,3 +69,15 @@ def test_narrow_min_max(d, nnz, integers):
         ref, ref_arg, _ = oracle.spmm_reduce(indptr, indices, values, X, reduce)
         assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
         assert np.array_equal(arg.cpu().numpy(), ref_arg)
+
+
+@pytest.mark.parametrize("d", [4, 9, 16])
+@pytest.mark.parametrize("nnz", [(768 << 10) - 1, 768 << 10])
+def test_narrow_spmm(d, nnz):
+    n = 48_000
+    indptr, indices, values = graph(n, nnz, d)
+    X = graphgen.normal((n, d), d)
+    A = build(indptr, indices, values)
+    Y = torch.empty(n, d, device="cuda")
+    isp.spmm(A, dev(X), Y)
+    assert_close(Y, *oracle.spmm(indptr, indices, values, X))
