@@ -114,7 +114,12 @@ def _stream(stream=None):
 
 
 def _raw(stream):
-    return None if stream is None else stream.cuda_stream
+    """A stream as the native module takes it: None for the current one, its address, negative if torch did not make it (the id
+    of such a stream is its address)."""
+    if stream is None:
+        return None
+    raw = stream.cuda_stream
+    return -raw if getattr(stream, "stream_id", None) == raw else raw
 
 
 def _dptr(t):
@@ -130,26 +135,33 @@ class _Shared:
     """What the CSR objects of a matrix and of its cached transpose have in common: the library handle and the tensors that it
     borrows.  The last of the two objects to go gives both back at once.  (Had they kept each other alive, the garbage collector would
     have had to find them: a program that makes a handle per mini-batch allocated fresh workspaces all the while, 16 M entries, 89 k
-    rows, 32 columns 3085 us per graph seen once instead of 1590, with 54 GB reserved instead of 5.)"""
+    rows, 32 columns 3085 us per graph seen once instead of 1590, with 54 GB reserved instead of 5.)
 
-    def __init__(self, handle, keep):
+    Each tensor's memory belongs to the stream that it was allocated on, which may be neither the one that the handle was made on nor those that
+    calls ran on; so the allocator is told of all streams in use before a tensor is let go (Tensor.record_stream)."""
+
+    def __init__(self, handle, keep, source=None):
         self.handle, self.keep, self.cells = handle, keep, []
-        self.aliased = False
+        self.source = source  # (of an alias: the cell of the CSR object whose arrays its calls read)
 
     def close(self):
-        if self.handle is not None:
+        if self.handle is None:
+            return
+        try:
+            _nat.cells_release(self.cells, self.keep, self.source)
+            if len(self.cells) > 1 and any(map(_nat.cell_foreign, self.cells)):
+                # A stream of somebody else's may have been destroyed, so it cannot be asked whether calls on it still run.  As ever: without a
+                # transpose the caller sees to it, with one the collector frees the tensors.
+                parked = [self.keep]
+                parked.append(parked)
+        finally:
             load_library().isp_csr_destroy(self.handle)
-        for cell in self.cells:
-            _nat.cell_clear(cell)
-        self.handle = self.keep = None
+            for cell in self.cells:
+                _nat.cell_clear(cell)
+            self.handle = self.keep = self.source = None
 
     def __del__(self):
         try:
-            if len(self.cells) > 1 and (self.aliased or any(map(_nat.cell_away, self.cells))):
-                # The allocator knows the workspaces' own stream only, and calls on others may still run: with a transpose,
-                # the collector has always been the one to free them.
-                parked = [self.keep]
-                parked.append(parked)
             self.close()
         except Exception:
             pass
@@ -158,13 +170,13 @@ class _Shared:
 class CSR:
     """A library handle plus the tensors it borrows.  Create with :func:`csr_build`."""
 
-    def __init__(self, handle, n_rows, n_cols, nnz, keep, owner=None):
+    def __init__(self, handle, n_rows, n_cols, nnz, keep, owner=None, source=None):
         self._h = handle
         self._cell = _native().cell(handle.value or 0, n_rows, n_cols, nnz)  # the handle as the native module sees it
         self.n_rows, self.n_cols, self.nnz = n_rows, n_cols, nnz
         self._keep = keep          # tensors the C side points into
         self._is_transpose = owner is not None  # (the source CSR's cached transpose)
-        self._shared = owner._shared if owner is not None else _Shared(handle, keep)
+        self._shared = owner._shared if owner is not None else _Shared(handle, keep, source)
         self._shared.cells.append(self._cell)
         self._At = None
 
@@ -254,7 +266,9 @@ def _own_workspace(workspace, nbytes, device):
 
 def csr_build(indptr, indices, values=None, n_cols=None, *, trusted=False, stream=None, workspace=None) -> CSR:
     """isp_csr_build on torch CUDA tensors (indptr int64, indices int32, values fp32 or None).
-    workspace: optional uint8 CUDA tensor of at least csr_build_workspace() bytes (kept alive by the handle)."""
+    workspace: optional uint8 CUDA tensor of at least csr_build_workspace() bytes (kept alive by the handle).
+    The tensors may have been made on another stream than the handle's calls run on, provided that one has waited for it: until they are let
+    go the handle keeps them, and then it tells the allocator which streams still use them (torch's own streams; on others the caller waits)."""
     import torch
     lib = load_library()
     assert indptr.is_cuda and indptr.dtype == torch.int64 and indptr.is_contiguous()
@@ -270,7 +284,7 @@ def csr_build(indptr, indices, values=None, n_cols=None, *, trusted=False, strea
     _check(lib.isp_csr_build(n_rows, n_cols, nnz, _dptr(indptr), _dptr(indices), _dptr(values), _dptr(ws),
                              ws.numel(), ISP_TRUSTED if trusted else 0, _stream(stream), ctypes.byref(h)))
     A = CSR(h, n_rows, n_cols, nnz, [indptr, indices, values, ws])
-    _nat.cell_on(A._cell, _raw(stream))
+    _nat.cell_ran(A._cell, _raw(stream))
     return A
 
 
@@ -288,9 +302,8 @@ def csr_transpose_cached(A: CSR, *, stream=None, workspace=None):
     _check(lib.isp_csr_transpose_cached(A._h, _dptr(ws), ws.numel(), _stream(stream), ctypes.byref(At_h),
                                         ctypes.byref(was)))
     A._keep.append(ws)
-    _nat.cell_on(A._cell, _raw(stream))
+    _nat.cell_ran(A._cell, _raw(stream))
     A._At = CSR(At_h, A.n_cols, A.n_rows, A.nnz, [ws], owner=A)
-    _nat.cell_on(A._At._cell, _raw(stream))
     return A._At, bool(was.value)
 
 
@@ -308,8 +321,7 @@ def csr_alias(A: CSR, max_d: int = 256, *, workspace=None) -> CSR:
     ws = _own_workspace(workspace, csr_alias_workspace(A, max_d), A._keep[0].device)
     h = ctypes.c_void_p()
     _check(lib.isp_csr_alias(A._h, int(max_d), _dptr(ws), ws.numel(), ctypes.byref(h)))
-    B = CSR(h, A.n_rows, A.n_cols, A.nnz, [A._keep[0], ws, A])
-    A._shared.aliased = True  # (its calls read A's arrays on whatever stream they run)
+    B = CSR(h, A.n_rows, A.n_cols, A.nnz, [A._keep[0], ws, A], source=A._cell)
     if A._At is not None:  # the alias's own copy of the cached transpose (a cache hit: no device work)
         At_h = ctypes.c_void_p()
         _check(lib.isp_csr_transpose_cached(h, None, 0, None, ctypes.byref(At_h), None))
@@ -320,8 +332,8 @@ def csr_alias(A: CSR, max_d: int = 256, *, workspace=None) -> CSR:
 def csr_values_changed(A: CSR, *, stream=None):
     """isp_csr_values_changed: the caller has rewritten A's values tensor in place; the cached transpose's
     values are gathered again, everything else stays cached."""
-    _nat.cell_on(A._cell, _raw(stream))
     _check(load_library().isp_csr_values_changed(A._h, _stream(stream)))
+    _nat.cell_ran(A._cell, _raw(stream))
 
 
 def spmm(A: CSR, X, Y, *, stream=None):

@@ -11,9 +11,13 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/utils/pybind.h>
 #include <ATen/ATen.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
+#include <hip/hip_runtime_api.h>
 #include <atomic>
 #include <memory>
+#include <mutex>
+#include <vector>
 #include "isp.h"
 
 namespace {
@@ -24,16 +28,47 @@ using torch::autograd::variable_list;
 PyObject* g_check = nullptr;      // binding._check: raises IspError for a status
 PyObject* g_transpose = nullptr;  // binding.csr_transpose_cached
 
+// The stream of a call.  own: one of torch's, which live as long as the process; a stream that somebody else made may be gone when
+// a handle is dropped.
+struct Where {
+  void* s;
+  bool own;
+};
+
 // A handle as the Python object CSR owns it; destroy() on that object clears h for everybody who shares the cell.
 struct Cell {
   std::atomic<isp_csr_t*> h{nullptr};
   int64_t n_rows = 0, n_cols = 0, nnz = 0;
-  void* home = nullptr;            // the stream that was current when the handle was made: its workspace's own
-  std::atomic<bool> away{false};   // calls have run on another one
-  isp_csr_t* on(void* stream) {    // the handle for a call on `stream`
-    if (stream != home) away.store(true, std::memory_order_relaxed);
-    return h;
+
+  // The streams that calls on the handle have been put on.
+  struct Use {
+    void* s;
+    int device;
+  };
+  void ran_on(Where w) {
+    if (!w.own) {
+      foreign.store(true, std::memory_order_relaxed);
+      return;
+    }
+    if (w.s == last.load(std::memory_order_relaxed)) return;
+    std::lock_guard<std::mutex> lock(m);
+    last.store(w.s, std::memory_order_relaxed);
+    for (const Use& u : uses)
+      if (u.s == w.s) return;
+    hipDevice_t device = 0;
+    if (w.s ? hipStreamGetDevice((hipStream_t)w.s, &device) != hipSuccess : hipGetDevice(&device) != hipSuccess) {
+      foreign.store(true, std::memory_order_relaxed);
+      return;
+    }
+    uses.push_back({w.s, device});
   }
+  std::atomic<bool> foreign{false};  // a call ran on a stream that is not one of torch's
+  std::mutex m;
+  std::vector<Use> uses;
+
+ private:
+  static inline char none;  // (the default stream is a null pointer)
+  std::atomic<void*> last{&none};
 };
 using CellPtr = std::shared_ptr<Cell>;
 
@@ -105,19 +140,26 @@ bool dense_of(PyObject* o, Dense& out) {
   return !bad;
 }
 
-void* stream_of(PyObject* o) {  // None: the current stream of the current device
-  if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
-  return PyLong_AsVoidPtr(o);
+Where here() {  // the current stream of the current device
+  const auto s = c10::hip::getCurrentHIPStream();
+  void* const p = s.stream();
+  return {p, !p || s.id() != reinterpret_cast<intptr_t>(p)};  // (the id of a stream that torch has not made is its address)
+}
+Where stream_of(PyObject* o) {  // None: the current one; else its address, negative if it is not one of torch's
+  if (o == Py_None) return here();
+  const long long p = PyLong_AsLongLong(o);
+  return {reinterpret_cast<void*>(p < 0 ? -p : p), p >= 0};
 }
 
 #define ISP_ARGS(n)                                                                            \
   if (nargs != (n)) { PyErr_SetString(PyExc_TypeError, "wrong number of arguments"); return nullptr; }
 
 template <class F>
-PyObject* call(F&& f) {  // the library call with the interpreter released, its status as a Python int
+PyObject* call(Cell* c, Where w, F&& f) {  // the library call on c's handle with the interpreter released, its status as a Python int
   isp_status st;
   Py_BEGIN_ALLOW_THREADS
-  st = f();
+  st = f(c->h.load(), w.s);
+  if (st == ISP_OK || st == ISP_EHIP) c->ran_on(w);  // (else nothing has been launched)
   Py_END_ALLOW_THREADS
   return PyLong_FromLong(st);
 }
@@ -131,22 +173,55 @@ PyObject* py_cell(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   c->n_cols = PyLong_AsLongLong(a[2]);
   c->nnz = PyLong_AsLongLong(a[3]);
   if (PyErr_Occurred()) return nullptr;
-  if (c->h.load()) c->home = c10::hip::getCurrentHIPStream().stream();
   return wrap(std::move(c), CELL);
 }
-// (cell, stream): a call on that stream is about to use the handle
-PyObject* py_cell_on(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
+// (cell, stream): a call through ctypes on that stream has used the handle
+PyObject* py_cell_ran(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   ISP_ARGS(2)
   Cell* c = cell_of(a[0]);
   if (!c) return nullptr;
-  c->on(stream_of(a[1]));
+  const Where w = stream_of(a[1]);
+  if (PyErr_Occurred()) return nullptr;
+  c->ran_on(w);
   Py_RETURN_NONE;
 }
-PyObject* py_cell_away(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
+// (cell) -> has a call run on a stream that is not one of torch's?
+PyObject* py_cell_foreign(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   ISP_ARGS(1)
   Cell* c = cell_of(a[0]);
   if (!c) return nullptr;
-  return PyBool_FromLong(c->away.load());
+  return PyBool_FromLong(c->foreign.load());
+}
+// (cells, list, cell or None): before the list's tensors are let go.  The allocator hears of every stream that calls on the cells' handles
+// ran on, and reuses the memory once those are through; the other cell (an alias's source, whose arrays the calls read) takes the
+// streams over.
+PyObject* py_cells_release(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
+  ISP_ARGS(3)
+  Cell* heir = nullptr;
+  if (a[2] != Py_None && !(heir = cell_of(a[2]))) return nullptr;
+  if (!PyList_Check(a[0]) || !PyList_Check(a[1])) return fail("lists of cells and of what they borrow");
+  std::vector<Cell::Use> uses;
+  for (Py_ssize_t i = 0; i < PyList_GET_SIZE(a[0]); ++i) {
+    Cell* c = cell_of(PyList_GET_ITEM(a[0], i));
+    if (!c) return nullptr;
+    std::lock_guard<std::mutex> lock(c->m);
+    uses.insert(uses.end(), c->uses.begin(), c->uses.end());
+    if (heir && c->foreign.load()) heir->foreign.store(true);
+  }
+  for (size_t u = 0; u < uses.size(); ++u) {
+    bool again = false;
+    for (size_t v = 0; v < u; ++v) again |= uses[v].s == uses[u].s;
+    if (again) continue;
+    if (heir) heir->ran_on({uses[u].s, true});
+    const auto dev = static_cast<c10::DeviceIndex>(uses[u].device);
+    const auto s = uses[u].s ? c10::hip::getStreamFromExternal((hipStream_t)uses[u].s, dev) : c10::hip::getDefaultHIPStream(dev);
+    for (Py_ssize_t i = 0; i < PyList_GET_SIZE(a[1]); ++i) {
+      PyObject* o = PyList_GET_ITEM(a[1], i);
+      // (Tensor.record_stream without the dispatcher: a mode that is active where a handle happens to go has no part in this)
+      if (THPVariable_Check(o)) c10::hip::HIPCachingAllocator::recordStream(THPVariable_Unpack(o).storage().data_ptr(), s);
+    }
+  }
+  Py_RETURN_NONE;
 }
 PyObject* py_cell_clear(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   ISP_ARGS(1)
@@ -164,8 +239,9 @@ PyObject* py_spmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   Dense X, Y;
   if (!c || !dense_of(a[1], X) || !dense_of(a[2], Y)) return nullptr;
   if (X.rows != c->n_cols || Y.rows != c->n_rows || Y.d != X.d) return fail("X has A's columns as rows, Y its rows, both the same width");
-  void* s = stream_of(a[3]);
-  return call([&] { return FN(c->on(s), X.p, X.ld, (int32_t)X.d, Y.p, Y.ld, s); });
+  const Where w = stream_of(a[3]);
+  if (PyErr_Occurred()) return nullptr;
+  return call(c, w, [&](isp_csr_t* h, void* s) { return FN(h, X.p, X.ld, (int32_t)X.d, Y.p, Y.ld, s); });
 }
 
 // (cell, U, V, out, flags, stream)
@@ -178,9 +254,10 @@ PyObject* py_sddmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   const Tensor& out = THPVariable_Unpack(a[3]);
   if (U.rows != c->n_rows || V.rows != c->n_cols || V.d != U.d || out.numel() != c->nnz) return fail("U has A's rows, V its columns as rows, out one value per entry");
   const unsigned flags = (unsigned)PyLong_AsUnsignedLong(a[4]);
-  void* s = stream_of(a[5]);
+  const Where w = stream_of(a[5]);
+  if (PyErr_Occurred()) return nullptr;
   float* o = static_cast<float*>(out.data_ptr());
-  return call([&] { return isp_sddmm(c->on(s), U.p, U.ld, V.p, V.ld, (int32_t)U.d, flags, o, s); });
+  return call(c, w, [&](isp_csr_t* h, void* s) { return isp_sddmm(h, U.p, U.ld, V.p, V.ld, (int32_t)U.d, flags, o, s); });
 }
 
 // (cell, X, Y, op, stream)
@@ -191,9 +268,9 @@ PyObject* py_fusedmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   if (!c || !dense_of(a[1], X) || !dense_of(a[2], Y)) return nullptr;
   if (X.rows != c->n_rows || Y.rows != X.rows || Y.d != X.d) return fail("X and Y have A's rows and one width");
   const int op = (int)PyLong_AsLong(a[3]);
-  void* s = stream_of(a[4]);
+  const Where w = stream_of(a[4]);
   if (PyErr_Occurred()) return nullptr;
-  return call([&] { return isp_fusedmm(c->on(s), X.p, X.ld, (int32_t)X.d, op, Y.p, Y.ld, s); });
+  return call(c, w, [&](isp_csr_t* h, void* s) { return isp_fusedmm(h, X.p, X.ld, (int32_t)X.d, op, Y.p, Y.ld, s); });
 }
 
 // (cell, X, dY, dX, op, stream)
@@ -204,9 +281,9 @@ PyObject* py_fusedmm_backward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   if (!c || !dense_of(a[1], X) || !dense_of(a[2], G) || !dense_of(a[3], O)) return nullptr;
   if (G.rows != X.rows || G.d != X.d || O.rows != X.rows || O.d != X.d) return fail("X, dY and dX have one shape");
   const int op = (int)PyLong_AsLong(a[4]);
-  void* s = stream_of(a[5]);
+  const Where w = stream_of(a[5]);
   if (PyErr_Occurred()) return nullptr;
-  return call([&] { return isp_fusedmm_backward(c->on(s), X.p, X.ld, G.p, G.ld, (int32_t)X.d, op, O.p, O.ld, s); });
+  return call(c, w, [&](isp_csr_t* h, void* s) { return isp_fusedmm_backward(h, X.p, X.ld, G.p, G.ld, (int32_t)X.d, op, O.p, O.ld, s); });
 }
 
 // The arg array of min / max (None: absent).
@@ -233,9 +310,9 @@ PyObject* py_spmm_reduce(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   if (X.rows != c->n_cols || Y.rows != c->n_rows || Y.d != X.d) return fail("X has A's columns as rows, Y its rows, both the same width");
   if (!arg_of(a[4], c, X.d, true, &arg)) return nullptr;
   const int red = (int)PyLong_AsLong(a[3]);
-  void* s = stream_of(a[5]);
+  const Where w = stream_of(a[5]);
   if (PyErr_Occurred()) return nullptr;
-  return call([&] { return isp_spmm_reduce(c->on(s), X.p, X.ld, (int32_t)X.d, red, Y.p, Y.ld, arg, s); });
+  return call(c, w, [&](isp_csr_t* h, void* s) { return isp_spmm_reduce(h, X.p, X.ld, (int32_t)X.d, red, Y.p, Y.ld, arg, s); });
 }
 
 // (cell, dY, dX, reduce, arg, stream)
@@ -248,9 +325,9 @@ PyObject* py_spmm_reduce_backward(PyObject*, PyObject* const* a, Py_ssize_t narg
   if (G.rows != c->n_rows || O.rows != c->n_cols || O.d != G.d) return fail("dY has A's rows, dX its columns as rows, both the same width");
   if (!arg_of(a[4], c, G.d, false, &arg)) return nullptr;
   const int red = (int)PyLong_AsLong(a[3]);
-  void* s = stream_of(a[5]);
+  const Where w = stream_of(a[5]);
   if (PyErr_Occurred()) return nullptr;
-  return call([&] { return isp_spmm_reduce_backward(c->on(s), G.p, G.ld, (int32_t)G.d, red, arg, O.p, O.ld, s); });
+  return call(c, w, [&](isp_csr_t* h, void* s) { return isp_spmm_reduce_backward(h, G.p, G.ld, (int32_t)G.d, red, arg, O.p, O.ld, s); });
 }
 
 // ---- autograd -------------------------------------------------------------------------------------------------
@@ -281,18 +358,25 @@ Dense dense(const Tensor& t) {
   if (const char* bad = dense_of(t, o)) assertion(bad);
   return o;
 }
-void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+// A library call on a cell's handle and the current stream.
+template <class F>
+void run(Cell& c, F&& f) {
+  const Where w = here();
+  const isp_status st = f(c.h.load(), w.s);
+  if (st == ISP_OK || st == ISP_EHIP) c.ran_on(w);
+  check(st);
+}
 
 // Everything the handle keeps of the values follows an in-place change of the tensor.
 void sync_values(Graph& g) {
   if (!g.values.defined()) return;
   const uint32_t v = g.values._version();
   if (v == g.version) return;
-  check(isp_csr_values_changed(g.A->on(current_stream()), current_stream()));
+  run(*g.A, [](isp_csr_t* h, void* s) { return isp_csr_values_changed(h, s); });
   g.version = v;
 }
 
-isp_csr_t* transpose(Graph& g) {
+Cell& transpose(Graph& g) {
   sync_values(g);
   if (!g.At || !g.At->h.load()) {
     pybind11::gil_scoped_acquire gil;
@@ -309,8 +393,7 @@ isp_csr_t* transpose(Graph& g) {
       throw python_error(std::move(e));
     }
   }
-  g.A->on(current_stream());  // (its entries' tables and its scratch are used with the transpose's)
-  return g.At->on(current_stream());
+  return *g.At;
 }
 
 Tensor new_like(const Tensor& t, int64_t rows, int64_t d) { return at::empty({rows, d}, t.options().requires_grad(false)); }
@@ -330,13 +413,13 @@ struct SpmmBackward : torch::autograd::Node {
     if (task_should_compute_output(1)) {
       out[1] = new_like(dY, graph->A->n_cols, G.d);
       const Dense O = dense(out[1]);
-      check(isp_spmm(transpose(*graph), G.p, G.ld, (int32_t)G.d, O.p, O.ld, current_stream()));
+      run(transpose(*graph), [&](isp_csr_t* h, void* s) { return isp_spmm(h, G.p, G.ld, (int32_t)G.d, O.p, O.ld, s); });
     }
     if (need_dA && task_should_compute_output(0)) {
       const Tensor x = X.unpack();
       const Dense V = dense(x);
       out[0] = at::empty({graph->A->nnz}, dY.options());
-      check(isp_sddmm(graph->A->on(current_stream()), G.p, G.ld, V.p, V.ld, (int32_t)G.d, 0, static_cast<float*>(out[0].data_ptr()), current_stream()));
+      run(*graph->A, [&](isp_csr_t* h, void* s) { return isp_sddmm(h, G.p, G.ld, V.p, V.ld, (int32_t)G.d, 0, static_cast<float*>(out[0].data_ptr()), s); });
     }
     return out;
   }
@@ -356,8 +439,9 @@ struct ReduceBackward : torch::autograd::Node {
     const Dense G = dense(dY);
     out[0] = new_like(dY, graph->A->n_cols, G.d);
     const Dense O = dense(out[0]);
-    check(isp_spmm_reduce_backward(graph->A->on(current_stream()), G.p, G.ld, (int32_t)G.d, reduce,
-                                   arg.defined() ? static_cast<const int32_t*>(arg.data_ptr()) : nullptr, O.p, O.ld, current_stream()));
+    run(*graph->A, [&](isp_csr_t* h, void* s) {
+      return isp_spmm_reduce_backward(h, G.p, G.ld, (int32_t)G.d, reduce, arg.defined() ? static_cast<const int32_t*>(arg.data_ptr()) : nullptr, O.p, O.ld, s);
+    });
     return out;
   }
 };
@@ -376,7 +460,7 @@ struct FusedBackward : torch::autograd::Node {
     const Dense V = dense(x), G = dense(dY);
     out[0] = new_like(x, V.rows, V.d);
     const Dense O = dense(out[0]);
-    check(isp_fusedmm_backward(graph->A->on(current_stream()), V.p, V.ld, G.p, G.ld, (int32_t)V.d, ISP_OP_SIGMOID, O.p, O.ld, current_stream()));
+    run(*graph->A, [&](isp_csr_t* h, void* s) { return isp_fusedmm_backward(h, V.p, V.ld, G.p, G.ld, (int32_t)V.d, ISP_OP_SIGMOID, O.p, O.ld, s); });
     return out;
   }
 };
@@ -441,7 +525,7 @@ PyObject* py_ag_spmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
       Y = new_like(xc, g->A->n_rows, X.d);
       const Dense O = dense(Y);
       sync_values(*g);
-      check(isp_spmm(g->A->on(current_stream()), X.p, X.ld, (int32_t)X.d, O.p, O.ld, current_stream()));
+      run(*g->A, [&](isp_csr_t* h, void* s) { return isp_spmm(h, X.p, X.ld, (int32_t)X.d, O.p, O.ld, s); });
     }
     if (torch::autograd::compute_requires_grad(values, x)) {
       auto node = std::shared_ptr<SpmmBackward>(new SpmmBackward(), torch::autograd::deleteNode);
@@ -478,8 +562,9 @@ PyObject* py_ag_reduce(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
       if (reduce != ISP_REDUCE_MEAN) arg = at::empty({g->A->n_rows, X.d}, Y.options().dtype(at::kInt));
       const Dense O = dense(Y);
       sync_values(*g);
-      check(isp_spmm_reduce(g->A->on(current_stream()), X.p, X.ld, (int32_t)X.d, reduce, O.p, O.ld,
-                            arg.defined() ? static_cast<int32_t*>(arg.data_ptr()) : nullptr, current_stream()));
+      run(*g->A, [&](isp_csr_t* h, void* s) {
+        return isp_spmm_reduce(h, X.p, X.ld, (int32_t)X.d, reduce, O.p, O.ld, arg.defined() ? static_cast<int32_t*>(arg.data_ptr()) : nullptr, s);
+      });
     }
     if (torch::autograd::compute_requires_grad(x)) {
       auto node = std::shared_ptr<ReduceBackward>(new ReduceBackward(), torch::autograd::deleteNode);
@@ -514,7 +599,7 @@ PyObject* py_ag_fused(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
       Y = new_like(xc, X.rows, X.d);
       const Dense O = dense(Y);
       sync_values(*g);
-      check(isp_fusedmm(g->A->on(current_stream()), X.p, X.ld, (int32_t)X.d, ISP_OP_SIGMOID, O.p, O.ld, current_stream()));
+      run(*g->A, [&](isp_csr_t* h, void* s) { return isp_fusedmm(h, X.p, X.ld, (int32_t)X.d, ISP_OP_SIGMOID, O.p, O.ld, s); });
     }
     if (torch::autograd::compute_requires_grad(x)) {
       auto node = std::shared_ptr<FusedBackward>(new FusedBackward(), torch::autograd::deleteNode);
@@ -554,8 +639,9 @@ PyMethodDef methods[] = {
     ISP_DEF("init", py_init),
     ISP_DEF("cell", py_cell),
     ISP_DEF("cell_clear", py_cell_clear),
-    ISP_DEF("cell_on", py_cell_on),
-    ISP_DEF("cell_away", py_cell_away),
+    ISP_DEF("cell_ran", py_cell_ran),
+    ISP_DEF("cell_foreign", py_cell_foreign),
+    ISP_DEF("cells_release", py_cells_release),
     ISP_DEF("spmm", py_spmm<isp_spmm>),
     ISP_DEF("spmm_static_scratch", py_spmm<isp_spmm_static_scratch>),
     ISP_DEF("sddmm", py_sddmm),

@@ -1,5 +1,5 @@
-"""When a handle's workspaces are given back: at once, whichever of the matrix and its transpose goes last, without the garbage
-collector; but not while calls on another stream than the workspaces' own may still run."""
+"""When a handle's memory is given back: at once, whichever of the matrix and its transpose goes last, without the garbage
+collector; and nobody gets it while calls on another stream than the memory's own may still run."""
 import gc
 
 import numpy as np
@@ -9,6 +9,7 @@ import torch
 import graphgen
 import oracle
 import paper_2403_14853_amd as isp
+from paper_2403_14853_amd import autograd as isp_autograd
 from gpu_util import assert_close
 
 pytestmark = pytest.mark.gpu
@@ -75,28 +76,165 @@ def test_destroyed_matrices_take_their_transpose_along(graph):
     assert allocated() == before
 
 
-@pytest.mark.parametrize("how", ["current", "argument", "alias"])
-def test_other_streams_leave_it_to_the_collector(graph, how):
+class Busy:
+    """Keeps a stream at work for some tenths of a second."""
+
+    def __init__(self, stream):
+        with torch.cuda.stream(stream):
+            self.keep = torch.zeros(1 << 30, device="cuda")
+            for _ in range(300):
+                self.keep.mul_(2)
+        self.stream = stream
+
+    def still(self):
+        return not self.stream.query()
+
+
+def in_use():
+    """Bytes that the allocator cannot hand out, blocks among them that other streams still use."""
+    torch.cuda.synchronize()
+    torch.empty(1, device="cuda")  # (it looks at what has finished when it is asked)
+    return torch.cuda.memory_stats()["active_bytes.all.current"]
+
+
+def ranges(tensors):
+    return [(t.data_ptr(), t.numel() * t.element_size()) for t in tensors if torch.is_tensor(t)]
+
+
+def given_again(blocks, stream):
+    """Which of the blocks the allocator hands out to requests of their sizes on that stream (nothing is written to them)."""
+    with torch.cuda.stream(stream):
+        got = [torch.empty(n, dtype=torch.uint8, device="cuda") for _, n in sorted(blocks, key=lambda b: -b[1])]
+    return [(p, n) for p, n in blocks if any(p < t.data_ptr() + t.numel() and t.data_ptr() < p + n for t in got)]
+
+
+@pytest.mark.parametrize("transpose", [False, True])
+@pytest.mark.parametrize("end", ["dropped", "destroyed"])
+def test_borrowed_tensors_of_another_stream(graph, transpose, end):
+    """As a loader hands them over: copied on a stream of its own, which the computing stream has waited for."""
+    indptr, indices, values, _ = graph
+    X = torch.from_numpy(graphgen.normal((N, D), 5)).cuda()
+    Y = torch.empty_like(X)
+    main, copies = torch.cuda.current_stream(), torch.cuda.Stream()
+    before = in_use()
+    with torch.cuda.stream(copies):
+        dev = [torch.from_numpy(a).cuda() for a in (indptr, indices, values)]
+    main.wait_stream(copies)
+    copies.synchronize()
+    A = isp.csr_build(*dev)
+    if transpose:
+        isp.csr_transpose_cached(A)
+    blocks = ranges(dev)
+    busy = Busy(main)
+    isp.spmm(A, X, Y)
+    if end == "destroyed":
+        A.destroy()
+    del A, dev
+    again = given_again(blocks, copies)
+    assert busy.still() and not again
+    torch.cuda.synchronize()
+    assert_close(Y, *oracle.spmm(indptr, indices, values, X.cpu().numpy()))
+    del busy
+    assert in_use() == before
+
+
+@pytest.mark.parametrize("transpose", [False, True])
+@pytest.mark.parametrize("how", ["current", "argument", "transpose", "autograd", "alias", "alias last"])
+def test_calls_on_another_stream(graph, how, transpose):
+    if how == "transpose" and not transpose:
+        pytest.skip("needs one")
+    X = torch.from_numpy(graphgen.normal((N, D), 5)).cuda()
+    Y = torch.empty_like(X)
+    main, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    before = in_use()
+    if how == "autograd":
+        G = isp_autograd.SparseGraph(*graph[3])
+        A = G.handle
+    else:
+        A = isp.csr_build(*graph[3])
+    if transpose:
+        isp.csr_transpose_cached(A)
+    blocks = ranges(A._keep[3:])  # the workspaces
+    side.wait_stream(main)
+    busy = Busy(side)
+    if how == "current":
+        with torch.cuda.stream(side):
+            isp.spmm(A, X, Y)
+    elif how == "argument":
+        isp.spmm(A, X, Y, stream=side)
+    elif how == "transpose":
+        isp.spmm(isp.csr_transpose_cached(A)[0], X, Y, stream=side)
+    elif how == "autograd":
+        with torch.cuda.stream(side):
+            out = isp_autograd.spmm(G, X)
+        del G
+    elif how == "alias":
+        B = isp.csr_alias(A)
+        isp.spmm(B, X, Y, stream=side)
+        blocks += ranges([B._keep[1]])
+        del B
+    else:  # (the alias is what lets go of its matrix)
+        B = isp.csr_alias(A)
+        isp.spmm(B, X, Y, stream=side)
+        del A
+        A = B
+        del B
+    del A
+    again = given_again(blocks, main)
+    assert busy.still() and not again
+    torch.cuda.synchronize()
+    if how == "autograd":
+        Y.copy_(out)
+        del out
+    if how != "transpose":
+        assert_close(Y, *oracle.spmm(*graph[:3], X.cpu().numpy()))
+    del busy
+    assert in_use() == before
+
+
+@pytest.mark.parametrize("how", ["current", "argument"])
+def test_streams_that_torch_did_not_make_leave_it_to_the_collector(graph, how):
     X = torch.zeros(N, D, device="cuda")
     Y = torch.empty_like(X)
     before = allocated()
     A = isp.csr_build(*graph[3])
     isp.csr_transpose_cached(A)
-    side = torch.cuda.Stream()
-    side.wait_stream(torch.cuda.current_stream())
+    made = torch.cuda.Stream()
+    foreign = torch.cuda.ExternalStream(made.cuda_stream)
+    foreign.wait_stream(torch.cuda.current_stream())
     if how == "current":
-        with torch.cuda.stream(side):
+        with torch.cuda.stream(foreign):
             isp.spmm(A, X, Y)
-    elif how == "argument":
-        isp.spmm(isp.csr_transpose_cached(A)[0], X, Y, stream=side)
     else:
-        B = isp.csr_alias(A)
-        isp.spmm(B, X, Y, stream=side)
-        del B
-    torch.cuda.current_stream().wait_stream(side)
+        isp.spmm(A, X, Y, stream=foreign)
+    torch.cuda.current_stream().wait_stream(foreign)
     held = allocated()
     del A
     assert held >= allocated() > before
     gc.collect()
-    gc.collect()  # (an alias lets go of its matrix in the first)
     assert allocated() == before
+
+
+def test_handles_used_first_and_dropped_during_a_capture(graph):
+    indptr, indices, values, dev = graph
+    X = torch.from_numpy(graphgen.normal((N, D), 5)).cuda()
+    Y = torch.empty_like(X)
+    A, B = isp.csr_build(*dev), isp.csr_build(*dev)
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    other.wait_stream(torch.cuda.current_stream())
+    isp.spmm(B, X, torch.empty_like(X), stream=other)
+    torch.cuda.synchronize()
+    isp.spmm(A, X, Y)
+    g = torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=side):
+        isp.spmm(A, X, Y, stream=side)
+        del B
+    ref = oracle.spmm(indptr, indices, values, X.cpu().numpy())
+    for _ in range(3):
+        Y.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert_close(Y, *ref)
+        torch.cuda.synchronize()
