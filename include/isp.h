@@ -113,7 +113,7 @@ isp_status isp_csr_build_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, 
 /*
  * Wrap the caller's CSR arrays in a handle and prepare the work partition: rows are classed by
  * degree; short rows are grouped into contiguous row blocks of about equal (nnz + rows); hub rows
- * (degree > hub threshold) are cut into segments of bounded length, at column-band boundaries first,
+ * (degree > hub threshold) are cut into segments of bounded length, in large matrices at column-band boundaries first,
  * which are scheduled in column order (Section 1(b): balanced scheduling; Section 3.5: CSR operand).
  * For large matrices with many columns (8 Mi .. 256 Mi entries, >= 64 Ki columns) the tuned SpMM also gets a packed
  * layout of its own: rows longer than 256 entries are cut into column-band pieces of 64 entries or more, and

@@ -31,19 +31,23 @@ def _graph(n, n_cols, nnz, hub, seg):
     return indptr, cols, rng.standard_normal(nnz).astype(np.float32)
 
 
-@pytest.mark.parametrize("share, more, n, n_cols, hub, seg", [
-    (28, 0, 2_000, 2_000, 64, 48), (28, 1, 2_000, 2_000, 96, 64),
-    (64, 0, 6_000, 6_000, 96, 64), (64, 1, 6_000, 6_000, 160, 80),
-    (320, 0, 70_000, 70_000, 160, 80), (320, 1, 70_000, 70_000, 160, 80), (320, 1, 30_000, 65_535, 160, 80),
-    (1024, 0, 65_535, 65_535, 512, 256), (1024, 1, 65_535, 65_535, 512, 256),
+@pytest.mark.parametrize("share, more, n, n_cols, hub, seg, banded", [
+    (28, 0, 2_000, 2_000, 64, 48, False), (28, 1, 2_000, 2_000, 96, 64, False),
+    (64, 0, 6_000, 6_000, 96, 64, False), (64, 1, 6_000, 6_000, 160, 80, False),
+    (320, 0, 70_000, 70_000, 160, 80, False), (320, 1, 70_000, 70_000, 160, 80, True), (320, 1, 30_000, 65_535, 160, 80, False),
+    (512, 0, 65_535, 65_535, 256, 128, False), (512, 1, 65_535, 65_535, 256, 128, True),
+    (1024, 0, 32_768, 32_768, 512, 256, False), (1024, 1, 32_768, 32_768, 512, 256, True), (1024, 0, 20_000, 32_769, 512, 256, True),
 ])
-def test_both_sides_of_a_size(share, more, n, n_cols, hub, seg):
+def test_both_sides_of_a_size(share, more, n, n_cols, hub, seg, banded):
     nnz = share * SLOTS + more - n
     print("[case] %d + %d units, %d rows" % (share, more, n), flush=True)
     indptr, cols, values = _graph(n, n_cols, nnz, hub, seg)
     A = build(indptr, cols, values, n_cols=n_cols)
     info = A.info()
     assert (info["hub_threshold"], info["segment_len"]) == (hub, seg)
+    deg = np.diff(indptr)
+    equal = int((-(-deg[deg > hub] // seg)).sum())  # (a row that is cut at bands has segments that end there as well)
+    assert info["n_segments"] > equal if banded else info["n_segments"] == equal
     rng = np.random.default_rng(1)
     for d in (20, 136):
         X = (0.1 * rng.standard_normal((n_cols, d))).astype(np.float32)
