@@ -52,7 +52,7 @@ inline int env_int(const char* name, int dflt, int lo, int hi) {
 }
 
 // slots: wavefront slots of the device (4,096 on an MI355X: 256 compute units); n_cols: where a cut by columns can pay (below)
-inline partition_params get_params(int64_t n_rows, int64_t nnz, int64_t slots, int64_t n_cols = INT64_MAX) {
+inline partition_params get_params(int64_t n_rows, int64_t nnz, int64_t slots, int64_t n_cols) {
   partition_params p;
   p.row_cost = 1;
   // Upper limits = what the grouped kernels' per-wave LDS tables hold (block_cost + hub_t <= 768

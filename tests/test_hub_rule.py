@@ -47,7 +47,7 @@ int main() {
   int finished = 0, left = 0;
   for (int64_t deg = 161; deg <= 600000; deg += deg / 7 + 1) {  // one such row among 20,000 of 8 entries
     const int64_t nnz = 160000 + deg;
-    const partition_params p = get_params(20001, nnz, 4096);
+    const partition_params p = get_params(20001, nnz, 4096, 20001);
     isp_csr A{};
     A.wave_slots = 4096;
     A.longest_row_segs = (int32_t)row_segments(deg, p);

@@ -16,7 +16,7 @@ int main() {
     for (int64_t deg = 200; deg <= 3000; ++deg) {
       const int64_t nnz = n * deg;
       if (nnz < (8 << 20) || nnz > (256 << 20)) continue;  // (where the layout is chosen)
-      const partition_params p1 = get_params(n, nnz, 4096), pc = cut_params(p1, 256);
+      const partition_params p1 = get_params(n, nnz, 4096, n), pc = cut_params(p1, 256);
       // columns spread evenly over the bands: every band holds a piece, as many segments as its length needs
       auto cut = [&](const partition_params& p) -> int64_t {
         if (deg <= p.hub_t) return 0;

@@ -64,3 +64,26 @@ int main() {
   return 0;
 }
 """)
+
+
+def test_bounds_hold_the_segments(tmp_path):
+    """What the workspace is laid out for, against rows that are all of one length: as many segments as such rows can have, with equal segments and with bands,
+    whose pieces may all end in a short one."""
+    run(tmp_path, r"""
+int main() {
+  long equal = 0, banded = 0;
+  for (int64_t share : {1, 8, 28, 29, 64, 65, 200, 320, 321, 400, 512, 700, 1024, 1025, 1400, 5000})
+    for (int64_t n_cols : {100, 3000, 32768, 65535, 65536, 2000000})
+      for (int64_t per : {65, 97, 128, 129, 161, 320, 321, 513, 1000, 5000, 70000}) {
+        const int64_t units = share * SLOTS, n = units / (per + 1), nnz = n * per;
+        if (n == 0) continue;
+        const partition_params p = get_params(n, nnz, SLOTS, n_cols);
+        if (per <= p.hub_t) continue;
+        const int64_t rows = max_hub_rows(n, nnz, p), most = max_segments(n, nnz, p);
+        const int64_t each = p.bands == 1 ? (per + p.seg_len - 1) / p.seg_len : per / p.seg_len + hub_bands(per, p);
+        if (rows < n || most < n * each) FAIL("%lld rows of %lld, %lld columns, %d bands: %lld segments, laid out for %lld\n", (long long)n, (long long)per, (long long)n_cols, p.bands, (long long)(n * each), (long long)most);
+        (p.bands == 1 ? equal : banded) += share > 320 && n_cols < 65536;
+      }
+  return equal > 0 && banded > 0 ? 0 : 1;  // (both where the number of columns decides)
+}
+""")

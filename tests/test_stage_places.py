@@ -50,7 +50,7 @@ int main() {
     for (int64_t per = 4; per <= 4000; per += per / 4 + 1) {
       const int64_t nnz = n * per;
       if (nnz < (8 << 20) || nnz > (256 << 20)) continue;
-      const partition_params p1 = get_params(n, nnz, 4096);
+      const partition_params p1 = get_params(n, nnz, 4096, n);
       const size_t rows = (size_t)(max_segments(n, nnz, p1) + 1) * 1024, own = isp_stage::own_bytes(n, nnz, rows, true);
       if (rows + own < isp_stage::wanted(n, nnz)) FAIL("no place: %lld x %lld\n", (long long)n, (long long)per);
     }
