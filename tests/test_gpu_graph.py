@@ -108,7 +108,8 @@ def test_graph_with_the_packed_layout_the_static_scratch_and_the_one_pass_backwa
     """The packed SpMM layout (forced onto a small graph), the entry point whose scratch is the library's static
     array, and the one-pass FusedMM backward of a symmetric pattern, captured and replayed."""
     import os
-    keys = dict(ISP_HUB_THRESHOLD="24", ISP_SEGMENT_LEN="16", ISP_BLOCK_COST="32", ISP_MID_THRESHOLD="10", ISP_MIN_PIECE="4")
+    keys = dict(ISP_HUB_THRESHOLD="24", ISP_SEGMENT_LEN="16", ISP_BLOCK_COST="32", ISP_MID_THRESHOLD="10", ISP_MIN_PIECE="4",
+                ISP_BANDS="32")
     os.environ.update(keys)
     try:
         w = graphgen.make_config(1, shrink=16)

@@ -86,7 +86,8 @@ def test_forced_packed_layout_small_graph(d, mid, seg, min_piece, bands):
 
 
 def test_values_rewritten_in_place_reach_the_packed_copy():
-    _env(ISP_HUB_THRESHOLD=24, ISP_SEGMENT_LEN=16, ISP_BLOCK_COST=32, ISP_MID_THRESHOLD=10, ISP_MIN_PIECE=4)
+    _env(ISP_HUB_THRESHOLD=24, ISP_SEGMENT_LEN=16, ISP_BLOCK_COST=32, ISP_MID_THRESHOLD=10, ISP_MIN_PIECE=4,
+         ISP_BANDS=32)  # (matrices of this size have no bands by themselves)
     w = graphgen.make_config(1, shrink=64)
     d = 64
     X = np.random.default_rng(0).standard_normal((w.n, d)).astype(np.float32)
@@ -108,7 +109,8 @@ def test_values_rewritten_in_place_reach_the_packed_copy():
 
 
 def test_unsorted_duplicated_rectangular_and_no_values():
-    _env(ISP_HUB_THRESHOLD=24, ISP_SEGMENT_LEN=16, ISP_BLOCK_COST=32, ISP_MID_THRESHOLD=8, ISP_MIN_PIECE=4)
+    _env(ISP_HUB_THRESHOLD=24, ISP_SEGMENT_LEN=16, ISP_BLOCK_COST=32, ISP_MID_THRESHOLD=8, ISP_MIN_PIECE=4,
+         ISP_BANDS=32)
     for seed, (nr, nc, nz) in enumerate([(300, 200, 6000), (50, 4000, 3000), (2000, 37, 9000), (1, 500, 400)]):
         indptr, indices, values = graphgen.random_csr(nr, nc, nz, seed, sorted_cols=bool(seed % 2), allow_dup=True)
         for vals in (values, None):

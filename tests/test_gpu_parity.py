@@ -21,19 +21,19 @@ def _announce(request):
     torch.cuda.synchronize()
 
 
-def _partition_env(hub=None, seg=None, block=None):
-    for k, v in (("ISP_HUB_THRESHOLD", hub), ("ISP_SEGMENT_LEN", seg), ("ISP_BLOCK_COST", block)):
+def _partition_env(hub=None, seg=None, block=None, bands=None):
+    for k, v in (("ISP_HUB_THRESHOLD", hub), ("ISP_SEGMENT_LEN", seg), ("ISP_BLOCK_COST", block), ("ISP_BANDS", bands)):
         if v is None:
             os.environ.pop(k, None)
         else:
             os.environ[k] = str(v)
 
 
-@pytest.fixture
-def small_partition():
+@pytest.fixture(params=[1, 32], ids=["equal", "bands"])
+def small_partition(request):
     """Small hub threshold / segment / block sizes so that tiny graphs span many work items,
-    hub segments and ragged tails."""
-    _partition_env(hub=24, seg=16, block=32)
+    hub segments and ragged tails; hub rows in equal segments or cut at column bands."""
+    _partition_env(hub=24, seg=16, block=32, bands=request.param)
     yield
     _partition_env()
 

@@ -14,11 +14,11 @@ from gpu_util import assert_close, build, dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture
-def small_partition():
-    os.environ.update(ISP_HUB_THRESHOLD="24", ISP_SEGMENT_LEN="16", ISP_BLOCK_COST="32")
+@pytest.fixture(params=["1", "32"], ids=["equal", "bands"])
+def small_partition(request):
+    os.environ.update(ISP_HUB_THRESHOLD="24", ISP_SEGMENT_LEN="16", ISP_BLOCK_COST="32", ISP_BANDS=request.param)
     yield
-    for k in ("ISP_HUB_THRESHOLD", "ISP_SEGMENT_LEN", "ISP_BLOCK_COST"):
+    for k in ("ISP_HUB_THRESHOLD", "ISP_SEGMENT_LEN", "ISP_BLOCK_COST", "ISP_BANDS"):
         os.environ.pop(k, None)
 
 
