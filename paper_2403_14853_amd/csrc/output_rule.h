@@ -17,10 +17,12 @@ namespace isp_dev {
 // store as ever.
 inline bool streams_output(int64_t rows, int64_t d) { return rows * d >= (int64_t)40 << 20; }
 
-// The packed layout's partial rows, `pieces` of them and `width` columns in this launch: from 96 MB on, of which the fix-up would find less in
-// the caches than they cost the gathers.  us with ordinary / these stores: 233 k columns, 115 M entries, some 370 k pieces, 128 columns (190 MB) 2438 / 2413,
-// 602 in five launches 11960 / 11865; 2.4 M, 124 M: 4586 / 4567; 800 k, 40 M, 247 k pieces: 50 columns (49 MB) 763 / 760, 100 (99 MB) 1431 / 1402, 128 1377 /
-// 1366; 120 k, 40 M, 305 k: 32 (39 MB) 281 / 285, 64 (78 MB) 469 / 470, 100 (122 MB) 838 / 835; 100 k, 16 M, 112 k: 32 122 / 124, 64 (29 MB) 202 / 204, 128 (57 MB) 374 / 376.
-inline bool streams_pieces(int64_t pieces, int64_t width) { return pieces * width >= (int64_t)24 << 20; }
+// The packed layout's partial rows, `pieces` of them and `width` columns in this launch: from 88 MB on, of which the fix-up would find less in
+// the caches than they cost the gathers.  us with ordinary / these stores, MB in brackets: 233 k columns, 115 M entries, 863 k pieces: 48 columns (166) 1203 / 1197, 64 (221) 1217 / 1210,
+// 68 (235) 1917 / 1907; 800 k, 40 M, 247 k pieces: 88 (87) 1191 / 1181, 92 (91) 1168 / 1159, 96 (95) 1046 / 1040, 100 (99) 1394 / 1389, with values 1419 / 1415, 128 (127) 1318 / 1307;
+// 120 k, 40 M, 305 k: 64 (78) 427.0 / 426.1, 76 (93) 689.6 / 688.6, 100 (122) 806 / 802; 1.2 M, 60 M, 366 k: 64 (94) 1026 / 1018, 72 (106) 1605 / 1595; 400 k, 30 M, 194 k: 120 (93) 1016 /
+// 1014.  Below, matrices of many columns still gain (800 k: 80 (79) 1007 / 996) and of few lose (100 k, 16 M, 112 k: 150 (67) 501.8 / 503.4, 192 (86) 555.3 / 558.5, where 256 (114)
+// loses too, 728.7 / 731.2).
+inline bool streams_pieces(int64_t pieces, int64_t width) { return pieces * width >= 22000000; }
 
 }  // namespace isp_dev

@@ -12,7 +12,7 @@ from gpu_util import assert_close, build, dev
 
 pytestmark = pytest.mark.gpu
 
-FLOATS = 24 << 20  # 96 MB of partial rows
+FLOATS = 22_000_000  # 88 MB of partial rows
 ENV = {"ISP_HUB_THRESHOLD": "24", "ISP_SEGMENT_LEN": "16", "ISP_BLOCK_COST": "32", "ISP_MID_THRESHOLD": "8", "ISP_MIN_PIECE": "4", "ISP_BANDS": "32"}
 
 
