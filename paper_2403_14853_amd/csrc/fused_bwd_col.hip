@@ -8,6 +8,7 @@ struct g_args21 { const float* src[2]; int64_t lds_[2]; const float* rowop[1]; i
 
 template <int OP>
 struct g_bwd_col {  // over A^T: gathered x_i and g_i, row operand x_j:  dX_j += a s g_i + dz x_i
+  static constexpr fused_pass PASS = fused_pass::two_pass;
   static constexpr int NSRC = 2, NROW = 1, RING4 = 4, RING8 = 2;
   static constexpr bool PER_ENTRY = false, ACCUMULATE = true;
   // (two entries at a time: figures with the row pass's policy; the one-pass backward of symmetric patterns, with three dot products and twice the

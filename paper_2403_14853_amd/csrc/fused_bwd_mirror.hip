@@ -13,6 +13,7 @@ struct g_args22 { const float* src[2]; int64_t lds_[2]; const float* rowop[2]; i
 
 template <int OP>
 struct g_bwd_mirror {  // gathered x_j and g_j, row operands x_i and g_i
+  static constexpr fused_pass PASS = fused_pass::one_pass;
   static constexpr int NSRC = 2, NROW = 2, RING4 = 4, RING8 = 2;
   static constexpr bool PER_ENTRY = false, ACCUMULATE = false, HAS_VAL2 = true;
   using args = g_args22;

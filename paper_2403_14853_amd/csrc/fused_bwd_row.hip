@@ -7,6 +7,7 @@ struct g_args12 { const float* src[1]; int64_t lds_[1]; const float* rowop[2]; i
 
 template <int OP>
 struct g_bwd_row {  // gathered x_j, row operands x_i and g_i:  dX_i += dz x_j
+  static constexpr fused_pass PASS = fused_pass::two_pass;
   static constexpr int NSRC = 1, NROW = 2, RING4 = 4, RING8 = 2;
   static constexpr bool PER_ENTRY = false, ACCUMULATE = false;
   // Two entries at a time, us of the whole backward of a directed graph (both passes) one / two: R-MAT, 60 k rows, 1.5 M entries: 64 columns 105.6 / 102,

@@ -7,6 +7,7 @@ struct g_args1 { const float* src[1]; int64_t lds_[1]; const float* rowop[1]; in
 
 template <int OP>
 struct g_fwd {  // gathered x_j, row operand x_i
+  static constexpr fused_pass PASS = fused_pass::forward;
   static constexpr int NSRC = 1, NROW = 1, RING4 = 4, RING8 = 4;
   static constexpr bool PER_ENTRY = false, ACCUMULATE = false;
   // Two entries at a time, us one / two: R-MAT, 60 k rows, 1.5 M entries: 128 columns 63.4 / 60.0, 256 127 / 111; 200 k, 4 M: 164.6 / 162.2, 390 / 388; not with

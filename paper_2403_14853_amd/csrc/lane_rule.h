@@ -1,0 +1,50 @@
+// How many lanes hold a row, and with how many vectors each, in the kernels whose choice follows from sizes alone: host arithmetic, so that the
+// rules can be checked without a device.
+#pragma once
+#include <stdint.h>
+
+namespace isp_dev {
+
+// The passes of FusedMM: forward; the row and column passes that a directed graph's backward takes; the one of a symmetric pattern's.
+enum class fused_pass { forward, two_pass, one_pass };
+
+// Four lanes hold a row of up to 16 columns, and a step serves 16 entries instead of 8, half of whose lanes were idle.  On few entries a launch is the time
+// of its chains.  With hub rows (n_hub of them) that is a segment's, which 16 runs finish in half the steps; without, the longer start of 16 runs.
+
+// SDDMM (w columns in this launch): everywhere with hub rows, else from 64 Ki entries.  us with 8 / 4 lanes, 8 columns: R-MAT: 800 rows, 8 k entries 4.1 / 3.8; 4 k, 36 k: 4.2 / 4.0; 12 k, 100 k:
+// 4.6 / 4.3; 40 k, 300 k: 7.1 / 5.7; 100 k, 1 M: 13.0 / 10.5; 60 k, 2.8 M: 27.8 / 22.6, 16 columns 28.1 / 24.1; 200 k, 8 M: 75.9 / 63.8; 230 k, 60 M: 469 / 398; uniform: 4 k, 36 k:
+// 4.15 / 4.24; 9 k, 60 k: 4.37 / 4.48; 3 k, 64 k: 4.35 / 4.32; 12 k, 100 k: 4.7 / 4.6; 8 k, 180 k: 5.5 / 4.9; 500 k, 8 M: 118.4 / 119.6.
+inline bool sddmm_four_lanes(int64_t w, int64_t nnz, int64_t n_hub) { return w <= 16 && (n_hub > 0 || nnz >= 64 << 10); }
+
+// FusedMM: from 64 Ki entries with hub rows, else from 120 Ki (forward) and 96 Ki (backward).  us with 8 / 4 lanes, 8 columns, forward and backward: R-MAT, directed: 4 k, 36 k: 5.4 / 5.6,
+// 12.2 / 12.1; 9 k, 60 k: 6.0 / 6.0, 13.6 / 13.1; 6 k, 80 k: 6.0 / 5.8, 14.0 / 12.8; 12 k, 100 k: 6.3 / 6.3, 14.9 / 13.5; 3.8 k, 120 k: 6.2 / 5.8, 14.9 / 12.9; 8 k, 180 k: 7.0 / 6.4,
+// 17.1 / 14.9; 40 k, 300 k: 9.7 / 8.2, 24.8 / 20.2; 100 k, 1 M: 17.9 / 14.7, 49.5 / 41.3; 60 k, 2.8 M: 35.2 / 28.0, 96.6 / 77.5 (16 columns 36.0 / 29.8, 99.1 / 81.0;
+// symmetric 65.4 / 47.3); 200 k, 8 M: 91.7 / 73.5, 250 / 199; 230 k, 60 M: 521 / 413, 1489 / 1140; uniform: 4 k, 36 k: 5.0 / 5.5, 10.9 / 11.7; 6 k, 80 k: 5.5 / 6.2, 12.5 / 13.1; 12 k, 100 k:
+// 5.7 / 5.9, 13.2 / 12.5; 3.8 k, 120 k: 6.2 / 6.6, 14.3 / 14.1; 20 k, 130 k: 6.0 / 5.7, 14.2 / 12.8; 30 k, 200 k: 6.7 / 6.0, 16.6 / 14.1; 500 k, 8 M, which waits for its gathers: 117.2 /
+// 116.6, 385 / 386.
+inline bool fused_four_lanes(fused_pass pass, int64_t d, int64_t nnz, int64_t n_hub) {
+  return d <= 16 && nnz >= (n_hub > 0 ? 64 << 10 : pass == fused_pass::forward ? 120 << 10 : 96 << 10);
+}
+
+// The min / max backward (w columns in this launch, hub rows of the transpose): below 32 Mi entries with hub rows, else from 256 Ki.  us with 8 / 4 lanes, 8 and 16 columns: R-MAT: 4 k, 36 k: 11.0 / 10.7,
+// 11.0 / 10.9; 3.8 k, 120 k: 11.6 / 11.5, 12.1 / 11.8; 8 k, 180 k: 12.7 / 12.2, 12.4 / 12.2; 60 k, 500 k: 19.4 / 18.7, 20.9 / 20.5; 400 k, 4 M: 66.9 / 64.4, 76.7 / 75.4; 1 M, 17 M: 264 / 253,
+// 292 / 281; but 230 k, 60 M: 534 / 539, 581 / 584; uniform: 4 k, 36 k: 10.7 / 11.2, 10.4 / 11.4; 8 k, 180 k: 11.8 / 12.5, 11.8 / 12.5; 12 k, 300 k: 12.4 / 12.6, 12.8 / 12.8; 30 k, 400 k:
+// 13.6 / 13.3, 16.3 / 15.9.
+inline bool select_four_lanes(int64_t w, int64_t nnz, int64_t n_hub) { return w <= 16 && nnz < (32 << 20) && (n_hub > 0 || nnz >= (256 << 10)); }
+
+// FusedMM beyond 32 columns: one or two float4 per lane.  Two halve the lanes per dot product, so a step covers twice the entries with one
+// lane-reduction stage and one evaluation of the edge function less per entry, but hold twice the registers and load
+// the row operand with every step.  With as few entries as the chip's wavefronts finish in a few rounds the length of their runs counts,
+// and two it is: beyond 128 columns below 1 Mi entries, beyond 64 below 3/4 Mi (us, one / two, forward and backward: R-MAT, 1.2 k rows, 13 k entries, 227
+// columns 17.0 / 10.9, 46.7 / 29.4; 12 k, 482 k, 144: 42.0 / 33.6, 77 / 62; 11 k, 899 k, 203: 78 / 58, 149 / 126; 3.8 k, 120 k, 96: 11.7 / 9.7, 18.2 /
+// 15.5; uniform, 6 k, 196 k, 176: 22.4 / 19.3, 42.0 / 36.5; 7 k, 406 k, 72: 23.3 / 19.6, 51.6 / 36.6; but 133 k, 1.04 M, 200: 118 / 113, 233 / 254;
+// 68 k, 1.07 M, 123: 54.3 / 61.4, 176 / 196; 27 k, 560 k, 60: 19.2 / 21.1, 53.6 / 55.2).  Larger ones have one everywhere (128 columns, us, one / two: forward on 2.4 M entries
+// 113 / 116, on 16.9 M 823 / 858, backward 240 / 266, 2830 / 2936) except where rows average 200 entries and nearly
+// all work lies in hub segments (115 M entries: 3077 / 2764, backward 7697 / 6860).
+// live_rows: rows with entries.
+inline bool fused_two_vectors(int64_t d, int64_t live_rows, int64_t nnz) {
+  if (live_rows > 0 && nnz >= 200 * live_rows) return true;
+  return d > 128 ? nnz < (1 << 20) : d > 64 && nnz < (3 << 18);
+}
+
+}  // namespace isp_dev

@@ -6,6 +6,7 @@
 // lanes spread over the feature dimension, and reduces each product across the wave.  Results
 // of up to 64 consecutive entries are collected one per lane and stored coalesced.
 #include "grouped_ops.h"
+#include "lane_rule.h"
 
 namespace {
 using namespace isp_dev;
@@ -216,9 +217,7 @@ isp_status isp_sddmm_launch(const isp_csr* A, const float* U, int64_t ldu, const
       // way already at 589 k entries from 200 columns (45.1 / 47.8, 248 columns 51.7 / 57.5).  On small matrices, where a wavefront's run is what the
       // launch takes, two are the better way from 65 columns up (R-MAT, 2.4 k rows, 46 k entries, 104 columns 6.9 / 5.6; 2.8 k, 64 k, 122: 6.8 / 5.6; 7 k, 186 k,
       // 88: 10.2 / 9.2; 13 k, 247 k, 70: 13.0 / 11.3; uniform, 4.9 k, 67 k, 96: 6.5 / 5.9; but 31 k, 374 k, 120: 28.0 / 29.7).
-      // Up to 16 columns four lanes hold a row (us with 8 / 4, 8 columns, R-MAT: 3 k rows, 30 k entries 4.1 / 4.0; 20 k, 300 k: 6.7 / 5.7; 100 k, 1 M: 13.0 / 10.5;
-      // 60 k, 2.8 M: 27.8 / 22.6, 16 columns 28.1 / 24.1; 200 k, 8 M: 75.9 / 63.8; 230 k, 60 M: 469 / 398; uniform, 500 k, 8 M: 118.4 / 119.6).
-      if (w <= 16) st = launch_grouped<4, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
+      if (sddmm_four_lanes(w, av.nnz, av.n_hub)) st = launch_grouped<4, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
       else if (w <= 32) st = launch_grouped<8, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
       else if (w <= 64) st = launch_grouped<16, 4>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);
       else if (w <= 128 && av.nnz < (1 << 18)) st = launch_grouped<16, 8>(A, U, ldu, V, ldv, k_lo, k_hi, add, scale, out, s);

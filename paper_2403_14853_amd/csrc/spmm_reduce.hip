@@ -12,6 +12,7 @@
 // floating-point atomics are needed and results are deterministic.
 #include "row_stream.h"
 #include "hub_finish.h"
+#include "lane_rule.h"
 #include "run_stream.h"
 
 namespace {
@@ -840,9 +841,7 @@ isp_status isp_spmm_reduce_bwd_launch(isp_csr* A, const float* dY, int64_t lddy,
     for (int k0 = 0; k0 < d && st == ISP_OK; k0 += ISP_PARTIAL_TILE) {
       const int k_base = d - k0 < 4 ? d - 4 : k0;  // (no launch narrower than a float4 lane)
       const int w = d - k_base < ISP_PARTIAL_TILE ? d - k_base : ISP_PARTIAL_TILE;
-      // (four lanes to a row of up to 16 columns, us with 8 / 4, 8 and 16 columns, R-MAT: 10 k rows, 100 k entries 14.5 / 14.3, 14.3 / 14.3; 60 k, 600 k: 21.3 / 20.1, 22.6 / 21.4;
-      // 400 k, 4 M: 66.9 / 64.4, 76.7 / 75.4; 1 M, 17 M: 264 / 253, 292 / 281; uniform, 30 k, 300 k 16.8 / 15.9, 19.1 / 18.5; but 230 k, 60 M: 534 / 539, 581 / 584)
-      if (w <= 16 && A->v.nnz < (32 << 20)) st = select_grouped_tile<4>(A, inv_perm, dY, lddy, arg, d, k_base, dX, lddx, s);
+      if (select_four_lanes(w, A->v.nnz, A->At->v.n_hub)) st = select_grouped_tile<4>(A, inv_perm, dY, lddy, arg, d, k_base, dX, lddx, s);
       else if (w <= 32) st = select_grouped_tile<8>(A, inv_perm, dY, lddy, arg, d, k_base, dX, lddx, s);
       else if (w <= 64) st = select_grouped_tile<16>(A, inv_perm, dY, lddy, arg, d, k_base, dX, lddx, s);
       else if (w <= 128) st = select_grouped_tile<32>(A, inv_perm, dY, lddy, arg, d, k_base, dX, lddx, s);

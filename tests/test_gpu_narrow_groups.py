@@ -1,5 +1,5 @@
 """SpMM, SDDMM, FusedMM and min / max up to 16 columns, where four lanes hold a row: widths around it, rows of every remainder of its 16 runs, hub rows, and sizes
-on both sides of those from which SpMM, FusedMM and min / max take it."""
+on both sides of those from which SpMM, FusedMM, min / max and their backward take it (the rules on the CPU: test_lane_rule.py)."""
 import numpy as np
 import pytest
 import torch
@@ -12,12 +12,13 @@ from gpu_util import assert_close, build, dev
 pytestmark = pytest.mark.gpu
 
 
-def graph(n, nnz, seed):
+def graph(n, nnz, seed, hubs=True):
     """Rows of 0 ... 33 entries, every length among them, and three hub rows; exactly nnz entries."""
     rng = np.random.default_rng(seed)
     lens = rng.integers(0, 34, n)
     lens[:34] = np.arange(34)
-    lens[34:37] = [900, 331, 177]
+    if hubs:
+        lens[34:37] = [900, 331, 177]
     k = n - 1
     while lens.sum() != nnz:  # (the last rows make up the difference)
         step = int(np.clip(nnz - lens.sum(), -lens[k], 60 - lens[k]))
@@ -29,15 +30,17 @@ def graph(n, nnz, seed):
 
 
 @pytest.mark.parametrize("d", [4, 5, 7, 8, 12, 13, 16, 17])
-@pytest.mark.parametrize("nnz", [(64 << 10) - 1, 64 << 10])
-def test_narrow_rows(d, nnz):
-    n = 4000
-    indptr, indices, values = graph(n, nnz, d)
+@pytest.mark.parametrize("nnz, hubs", [((64 << 10) - 1, True), (64 << 10, True), ((64 << 10) - 1, False), (64 << 10, False),
+                                       ((96 << 10) - 1, False), (96 << 10, False), ((120 << 10) - 1, False), (120 << 10, False)])
+def test_narrow_rows(d, nnz, hubs):
+    n = nnz // 16
+    indptr, indices, values = graph(n, nnz, d, hubs)
     rng = np.random.default_rng(d)
     X = (0.5 * rng.standard_normal((n, d))).astype(np.float32)
     G = rng.standard_normal((n, d)).astype(np.float32)
     A = build(indptr, indices, values)
     isp.csr_transpose_cached(A)
+    assert (A.info()["n_hub_rows"] > 0) == hubs
     out = torch.empty(nnz, device="cuda")
     for scale in (False, True):
         isp.sddmm(A, dev(G), dev(X), out, scale_by_a=scale)
@@ -81,3 +84,27 @@ def test_narrow_spmm(d, nnz):
     Y = torch.empty(n, d, device="cuda")
     isp.spmm(A, dev(X), Y)
     assert_close(Y, *oracle.spmm(indptr, indices, values, X))
+
+
+@pytest.mark.parametrize("d", [4, 11, 16, 17])
+@pytest.mark.parametrize("nnz, hubs", [((256 << 10) - 1, True), ((256 << 10) - 1, False), (256 << 10, False)])
+def test_narrow_max_backward(d, nnz, hubs):
+    n = 16_000
+    indptr, indices, values = graph(n, nnz, d, hubs)
+    if hubs:  # (of the transpose, whose rows the backward takes)
+        rows = np.repeat(np.arange(n), np.diff(indptr))
+        indices[:: 50] = 7
+        indices = indices[np.lexsort((indices, rows))]
+    rng = np.random.default_rng(d)
+    X = rng.integers(-2, 3, (n, d)).astype(np.float32)
+    G = rng.standard_normal((n, d)).astype(np.float32)
+    A = build(indptr, indices, values)
+    assert (isp.csr_transpose_cached(A)[0].info()["n_hub_rows"] > 0) == hubs
+    for reduce in ("min", "max"):
+        Y, dX = (torch.full((n, d), float("nan"), device="cuda") for _ in range(2))
+        arg = torch.full((n, d), -7, dtype=torch.int32, device="cuda")
+        isp.spmm_reduce(A, dev(X), Y, reduce, arg)
+        ref, ref_arg, _ = oracle.spmm_reduce(indptr, indices, values, X, reduce)
+        assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref) and np.array_equal(arg.cpu().numpy(), ref_arg)
+        isp.spmm_reduce_backward(A, dev(G), dX, reduce, arg)
+        assert_close(dX, *oracle.spmm_reduce_backward(n, indptr, indices, values, G, reduce, ref_arg), "backward " + reduce)
