@@ -61,9 +61,10 @@ isp_status run_grouped(const isp_csr* A, const typename P::args& pa, int d, floa
 }
 
 // P's shape on A (lane_rule.h); ISP_FUSED_W=4 / 8 forces one or two vectors (d > 32).
-inline bool two_vectors(const isp_csr* A, int d) {
+template <class P>
+bool two_vectors(const isp_csr* A, int d) {
   if (A->tune.fused_w) return A->tune.fused_w == 8;
-  return fused_two_vectors(d, A->info.n_rows - A->info.bin_rows[0], A->info.nnz);
+  return fused_two_vectors(P::PASS, d, A->info.n_rows, A->info.n_rows - A->info.bin_rows[0], A->info.nnz);
 }
 template <class P>
 isp_status run_grouped_d(const isp_csr* A, const typename P::args& pa, int d, float* Y, int64_t ldy, hipStream_t s) {
@@ -77,7 +78,7 @@ isp_status run_grouped_d(const isp_csr* A, const typename P::args& pa, int d, fl
   }
   if (fused_four_lanes(P::PASS, d, A->info.nnz, A->v.n_hub)) return run_grouped<P, 4, 4, true>(A, pa, d, Y, ldy, s);
   if (d <= 32) return run_grouped<P, 8, 4, true>(A, pa, d, Y, ldy, s);
-  if (!two_vectors(A, d)) {
+  if (!two_vectors<P>(A, d)) {
     if (d <= 64) return run_grouped<P, 16, 4, true>(A, pa, d, Y, ldy, s);
     if (d <= 128) return run_grouped<P, 32, 4, true>(A, pa, d, Y, ldy, s);
     return run_grouped<P, 64, 4, true>(A, pa, d, Y, ldy, s);

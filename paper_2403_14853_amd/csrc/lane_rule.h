@@ -34,16 +34,25 @@ inline bool select_four_lanes(int64_t w, int64_t nnz, int64_t n_hub) { return w 
 
 // FusedMM beyond 32 columns: one or two float4 per lane.  Two halve the lanes per dot product, so a step covers twice the entries with one
 // lane-reduction stage and one evaluation of the edge function less per entry, but hold twice the registers and load
-// the row operand with every step.  With as few entries as the chip's wavefronts finish in a few rounds the length of their runs counts,
-// and two it is: beyond 128 columns below 1 Mi entries, beyond 64 below 3/4 Mi (us, one / two, forward and backward: R-MAT, 1.2 k rows, 13 k entries, 227
-// columns 17.0 / 10.9, 46.7 / 29.4; 12 k, 482 k, 144: 42.0 / 33.6, 77 / 62; 11 k, 899 k, 203: 78 / 58, 149 / 126; 3.8 k, 120 k, 96: 11.7 / 9.7, 18.2 /
-// 15.5; uniform, 6 k, 196 k, 176: 22.4 / 19.3, 42.0 / 36.5; 7 k, 406 k, 72: 23.3 / 19.6, 51.6 / 36.6; but 133 k, 1.04 M, 200: 118 / 113, 233 / 254;
-// 68 k, 1.07 M, 123: 54.3 / 61.4, 176 / 196; 27 k, 560 k, 60: 19.2 / 21.1, 53.6 / 55.2).  Larger ones have one everywhere (128 columns, us, one / two: forward on 2.4 M entries
+// the row operand with every step.  Large matrices have one everywhere (128 columns, us, one / two: forward on 2.4 M entries
 // 113 / 116, on 16.9 M 823 / 858, backward 240 / 266, 2830 / 2936) except where rows average 200 entries and nearly
-// all work lies in hub segments (115 M entries: 3077 / 2764, backward 7697 / 6860).
+// all work lies in hub segments (115 M entries: 3077 / 2764, backward 7697 / 6860).  With as few entries as the chip's wavefronts finish in a few rounds
+// the length of their runs counts, and two it is: beyond 128 columns below 1 Mi entries, beyond 64 below 3/4 Mi - in a directed graph's
+// backward, whose passes take two entries at a time with one vector and have too short a ring for it with two, only with operands that the caches
+// hold (6 MB; from 129 to 160 columns, where two vectors gain most, 48 MB).
+// us, one (in pairs where the pass has them) / two:
+//   forward: uniform, 7 k rows, 406 k entries: 72 columns 19.7 / 18.0, 144 34.8 / 25.1, 256 35.9 / 30.8; 30 k, 600 k: 26.9 / 26.4, 53.3 / 49.5, 85.9 / 88.4; 50 k, 1 M: 144 102 / 110; R-MAT, 15 k,
+//   600 k: 29.9 / 25.5, 53.4 / 43.9, 54.2 / 49.4; 80 k, 800 k: 36.9 / 36.1, 67.4 / 58.2, 90.5 / 83.5 (100 39.5 / 42.7); 68 k, 1.3 M: 128 60.0 / 59.8, 256 113.6 / 117.9;
+//   two passes: uniform, 7 k, 406 k: 72 (2 MB) 58.1 / 52.7, 128 (3.6) 58.9 / 57.7, 200 (5.6) 120.6 / 120.6, 256 (7.2) 133 / 143; 30 k, 600 k: 72 (8.6) 92.0 / 97.0, 128 (15) 128 / 139, 256 265 / 284;
+//   R-MAT, 3.8 k, 120 k: 128 27.0 / 26.5, 144 44.1 / 41.2; 12 k, 482 k: 72 (3.5) 60.8 / 60.6, 128 (6.1) 61.7 / 63.4, 200 (9.6) 105 / 109; 15 k, 600 k: 144 (8.6) 144 / 131, 256 (15) 156 / 159; 60 k,
+//   600 k: 72 (17) 79.4 / 85.4, 128 92.6 / 101.3, 144 (35) 147 / 144, 256 215 / 233; 80 k, 800 k: 100 (32) 124 / 137, 144 (46) 202 / 195, 256 281 / 300; 150 k, 750 k: 144 (86) 213 / 222; uniform, 60 k,
+//   600 k: 144 (35) 186 / 195;
+//   one pass: R-MAT, 12 k, 482 k: 72 45.0 / 34.6, 128 45.4 / 36.7, 256 77.6 / 71.1; 60 k, 800 k: 144 136 / 122, 256 190 / 195; 100 k, 500 k: 128 75.2 / 69.0, 256 162 / 151; 133 k, 1.04 M: 144
+//   178 / 159, 256 265 / 278; but 60 k, 800 k: 128 78.7 / 84.1, 200 k, 1 M: 128 131 / 151.
 // live_rows: rows with entries.
-inline bool fused_two_vectors(int64_t d, int64_t live_rows, int64_t nnz) {
+inline bool fused_two_vectors(fused_pass pass, int64_t d, int64_t n_rows, int64_t live_rows, int64_t nnz) {
   if (live_rows > 0 && nnz >= 200 * live_rows) return true;
+  if (pass == fused_pass::two_pass && n_rows * d > (d > 128 && d <= 160 ? 12 << 20 : 3 << 19)) return false;
   return d > 128 ? nnz < (1 << 20) : d > 64 && nnz < (3 << 18);
 }
 

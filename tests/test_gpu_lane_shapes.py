@@ -30,6 +30,7 @@ def _graph(n, nnz, seed):
     (6_000, (1 << 18) - 1, False, [65, 97, 128]), (6_000, 1 << 18, False, [65, 97, 128]),
     (9_000, (3 << 18) - 1, True, [65, 128, 257, 300, 517]), (9_000, 3 << 18, True, [65, 128, 257, 300, 517]),
     (12_000, (1 << 20) - 1, True, [129, 250]), (12_000, 1 << 20, True, [129, 250]),
+    (12_288, 300_000, True, [128, 129]),  # (a directed graph's backward: one vector again beyond 6 MB)
 ])
 def test_against_the_oracle(n, nnz, fused, widths):
     indptr, cols, values = _graph(n, nnz, n + nnz)

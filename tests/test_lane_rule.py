@@ -46,3 +46,23 @@ int main() {
   return 0;
 }
 """)
+
+
+def test_two_vectors(tmp_path):
+    """(The two passes of a directed graph's backward, which one vector runs in pairs of entries, took up to 13 % longer with two beyond the L2s.)"""
+    run(tmp_path, r"""
+int main() {
+  for (fused_pass p : {fused_pass::forward, fused_pass::one_pass, fused_pass::two_pass}) {
+    CHECK(!fused_two_vectors(p, 64, 1000, 900, 20000) && fused_two_vectors(p, 65, 1000, 900, 20000) && fused_two_vectors(p, 256, 1000, 900, 20000));
+    CHECK(fused_two_vectors(p, 128, 6000, 5000, 3 * Mi / 4 - 1) && !fused_two_vectors(p, 128, 6000, 5000, 3 * Mi / 4));
+    CHECK(fused_two_vectors(p, 129, 6000, 5500, Mi - 1) && !fused_two_vectors(p, 129, 6000, 5500, Mi));
+    CHECK(fused_two_vectors(p, 40, 233000, 233000, 115000000));  // (rows of 200 entries and more)
+    CHECK(fused_two_vectors(p, 128, 12288, 12000, 300000) && fused_two_vectors(p, 128, 12289, 12000, 300000) == (p != fused_pass::two_pass));
+  }
+  CHECK(fused_two_vectors(fused_pass::two_pass, 144, 87381, 80000, 800000) && !fused_two_vectors(fused_pass::two_pass, 144, 87382, 80000, 800000));  // (12 Mi floats)
+  CHECK(fused_two_vectors(fused_pass::two_pass, 160, 50000, 40000, 800000) && !fused_two_vectors(fused_pass::two_pass, 161, 50000, 40000, 800000));
+  CHECK(!fused_two_vectors(fused_pass::two_pass, 100, 60000, 33000, 600000) && !fused_two_vectors(fused_pass::two_pass, 256, 80000, 45000, 800000));  // (90.8 -> 101, 281 -> 300 us with two)
+  CHECK(!fused_two_vectors(fused_pass::two_pass, 128, 30000, 30000, 600000));  // (uniform: 128 -> 139)
+  return 0;
+}
+""")
