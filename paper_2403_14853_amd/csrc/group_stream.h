@@ -94,33 +94,31 @@ __device__ __forceinline__ float group_step_value(float p0, float p1, float p2, 
   return s & 2 ? hi : lo;
 }
 
-// Two sums of LPG lanes at once: of a value per lane and step (p0, p1) half of the group's lanes get the total of the first, the
+// Two sums of LPG lanes at once, 16 lanes and more: of a value per lane and step (p0, p1) half of the group's lanes get the total of the first, the
 // others of the second, so that what is computed from a total is computed once for both; group_pair_split then hands both results
-// to all lanes.  A pair takes 6 instructions where two sums take 8 (8 and 16 lanes), 10 and 8 where it took 10 (32) and 12 (64) with
-// an exchange through LDS in each.
+// to all lanes.  A pair of sums takes 6 instructions with 16 or 32 lanes and 9 with 64, where two sums take 8, 12 and 16, the latter with exchanges through LDS; every result handed back takes 3 more with 16 lanes and 2 with 32 or 64.  So 16 lanes gain by the shared evaluation of the
+// edge function alone (two dot products and one or two results: 15 or 18 instead of 16, less one evaluation), more lanes by both.
 template <int LPG>
 __device__ __forceinline__ float group_pair_sum(float p0, float p1, int lane) {
+  static_assert(LPG >= 16, "no policy pairs entries with fewer lanes");
   float v;
-  if constexpr (LPG == 8) {
-    v = pair_sum<DPP_HALF_MIRROR>(p0, p1, lane & 4);
-  } else {
-    if constexpr (LPG == 16) v = pair_sum<DPP_ROR8>(p0, p1, lane & 8);
-    else if constexpr (LPG == 32) v = pair_sum_16(p0, p1);
-    else {
-      v = pair_sum_32(p0, p1);
-      v = pair_sum_16(v, v);
-    }
-    if constexpr (LPG > 16) v += dpp_of<DPP_ROR8>(v);
-    v += dpp_of<DPP_HALF_MIRROR>(v);
+  if constexpr (LPG == 16) v = pair_sum<DPP_ROR8>(p0, p1, lane & 8);
+  else if constexpr (LPG == 32) v = pair_sum_16(p0, p1);
+  else {
+    v = pair_sum_32(p0, p1);
+    v = pair_sum_16(v, v);
   }
+  if constexpr (LPG > 16) v += dpp_of<DPP_ROR8>(v);
+  v += dpp_of<DPP_HALF_MIRROR>(v);
   v += dpp_of<DPP_XOR1>(v);
   return v + dpp_of<DPP_XOR2>(v);
 }
 template <int LPG>
 __device__ __forceinline__ void group_pair_split(float v, int lane, float& v0, float& v1) {
-  if constexpr (LPG <= 16) {
-    const bool up = lane & (LPG / 2);
-    const float other = dpp_of<LPG == 8 ? DPP_HALF_MIRROR : DPP_ROR8>(v);
+  static_assert(LPG >= 16, "no policy pairs entries with fewer lanes");
+  if constexpr (LPG == 16) {
+    const bool up = lane & 8;
+    const float other = dpp_of<DPP_ROR8>(v);
     v0 = up ? other : v;
     v1 = up ? v : other;
   } else if constexpr (LPG == 32) {
