@@ -96,7 +96,8 @@ __device__ __forceinline__ float group_step_value(float p0, float p1, float p2, 
 
 // Two sums of LPG lanes at once, 16 lanes and more: of a value per lane and step (p0, p1) half of the group's lanes get the total of the first, the
 // others of the second, so that what is computed from a total is computed once for both; group_pair_split then hands both results
-// to all lanes.  A pair of sums takes 6 instructions with 16 or 32 lanes and 9 with 64, where two sums take 8, 12 and 16, the latter with exchanges through LDS; every result handed back takes 3 more with 16 lanes and 2 with 32 or 64.  So 16 lanes gain by the shared evaluation of the
+// to all lanes.  A pair of sums takes 6 instructions with 16 or 32 lanes and 9 with 64, where two sums take 8, 12 and 16, the latter with exchanges
+// through LDS; every result handed back takes 3 more with 16 lanes and 2 with 32 or 64.  So 16 lanes gain by the shared evaluation of the
 // edge function alone (two dot products and one or two results: 15 or 18 instead of 16, less one evaluation), more lanes by both.
 template <int LPG>
 __device__ __forceinline__ float group_pair_sum(float p0, float p1, int lane) {

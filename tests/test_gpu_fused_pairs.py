@@ -1,5 +1,7 @@
-"""FusedMM two entries at a time: runs that end with the first of a pair, rows that change between the two, hub segments of odd
+"""FusedMM two entries at a time (16, 32 and 64 lanes to a row with one vector per lane; the forward also 32 with two) and one at a time: runs that end with the first of a pair, rows that change between the two, hub segments of odd
 length, and entries that a pair reads beyond its run."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -22,10 +24,18 @@ def directed(lens, seed, avoid=()):
     return indptr, np.concatenate(rows).astype(np.int32)
 
 
-# (8, 16, 32 and 64 lanes to a row, one and two vectors per lane, widths that are no multiple of 4)
+@pytest.fixture(params=["4", "8"], ids=["one vector", "two vectors"])
+def vectors(request):
+    """(Small graphs have two by themselves beyond 64 columns.)"""
+    os.environ["ISP_FUSED_W"] = request.param
+    yield
+    os.environ.pop("ISP_FUSED_W")
+
+
+# (one vector: 8, 16, 32 and 64 lanes to a row; two: 8, 16 and 32; widths that are no multiple of 4)
 @pytest.mark.parametrize("d", [32, 47, 64, 65, 128, 131, 256])
 @pytest.mark.parametrize("op", ["sigmoid", "dot", "one"])
-def test_rows_of_every_remainder(d, op):
+def test_rows_of_every_remainder(vectors, d, op):
     rng = np.random.default_rng(d)
     lens = np.concatenate([np.arange(17).repeat(5), rng.integers(0, 12, N - 85 - 3), [701, 130, 97]])
     rng.shuffle(lens)
@@ -44,7 +54,7 @@ def test_rows_of_every_remainder(d, op):
 
 @pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("bad", [np.inf, np.nan])
-def test_values_of_rows_that_no_entry_names_stay_out(d, bad):
+def test_values_of_rows_that_no_entry_names_stay_out(vectors, d, bad):
     rng = np.random.default_rng(d)
     lens = rng.integers(0, 10, N)
     poisoned = np.array([0, 1, 5, 450, N - 1])  # (what lies behind an item's entries reads as column 0)

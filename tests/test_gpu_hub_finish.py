@@ -162,18 +162,20 @@ def _pairs(lengths, n, seed):
     return indptr, cols, values, dv, A, np.sort(rows[:len(lengths)])
 
 
-@pytest.mark.parametrize("d", [4, 30, 32, 33, 64, 65, 100, 128, 131])
-def test_min_and_max_in_the_launch_of_the_segments(d):
+@pytest.mark.parametrize("d, n", [(4, 6_000), (16, 6_000), (30, 6_000), (32, 6_000), (33, 6_000), (64, 6_000), (65, 6_000), (100, 6_000), (128, 6_000), (131, 6_000),
+                                  (4, 190_000), (11, 190_000), (16, 190_000)])
+def test_min_and_max_in_the_launch_of_the_segments(d, n):
     """The forward that finishes its hub rows, up to as many segments as it folds: bit for bit with the oracle (ties to the first entry),
     and with the fix-up launch (an alias) also where products are NaN: a row's first entry, a later segment's first, a whole
     segment, all segments of a lane group's part, everything but the row's end."""
-    lanes = 8 if d <= 32 else 16 if d <= 64 else 32
-    limit = 96 if lanes == 8 else 32  # segments of the longest row
-    n = 6_000
+    many = n > 6_000  # (entries enough for four lanes to a row)
+    lanes = 4 if many else 8 if d <= 32 else 16 if d <= 64 else 32
+    limit = 96 if lanes <= 8 else 32  # segments of the longest row
     lengths = [80 * s - k for s in range(3, limit + 1, limit // 10) for k in (0, 79)] + [80 * limit] * 3
     lengths = [h for h in lengths if h > 160]
     indptr, cols, values, dv, A, hubs = _pairs(lengths, n, d)
     info = A.info()
+    assert (info["nnz"] >= 512 << 10) == many
     slots = 16 * torch.cuda.get_device_properties(0).multi_processor_count
     assert info["n_segments"] == sum((h + 79) // 80 for h in lengths) and 3 * info["n_segments"] <= slots
     assert 2 * info["bin_nnz"][3] >= info["segment_len"] * info["bin_rows"][3] > 0

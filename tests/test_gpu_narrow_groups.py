@@ -108,3 +108,29 @@ def test_narrow_max_backward(d, nnz, hubs):
         assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref) and np.array_equal(arg.cpu().numpy(), ref_arg)
         isp.spmm_reduce_backward(A, dev(G), dX, reduce, arg)
         assert_close(dX, *oracle.spmm_reduce_backward(n, indptr, indices, values, G, reduce, ref_arg), "backward " + reduce)
+
+
+@pytest.mark.parametrize("d", [4, 7, 16])
+@pytest.mark.parametrize("hubs", [False, True])
+def test_narrow_one_pass_backward(d, hubs):
+    """Symmetric patterns, whose FusedMM backward is one pass; the values are not symmetric."""
+    n = 6_000
+    rng = np.random.default_rng(d)
+    u, v = rng.integers(0, n, (2, 50_000))
+    if hubs:
+        u[:4_000] = rng.integers(0, 5, 4_000) * 1_000
+    keys = np.unique(np.concatenate([u * n + v, v * n + u]))
+    assert len(keys) >= 96 << 10
+    rows, indices = keys // n, (keys % n).astype(np.int32)
+    indptr = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int64)
+    values = graphgen.uniform(len(keys), d)
+    X = (0.5 * rng.standard_normal((n, d))).astype(np.float32)
+    G = rng.standard_normal((n, d)).astype(np.float32)
+    A = build(indptr, indices, values)
+    isp.csr_transpose_cached(A)
+    info = A.info()
+    assert info["symmetric_pattern"] == 1 and (info["n_hub_rows"] > 0) == hubs
+    Y = torch.full((n, d), float("nan"), device="cuda")
+    for op in ("sigmoid", "dot", "one"):
+        isp.fusedmm_backward(A, dev(X), dev(G), Y, op=op)
+        assert_close(Y, *oracle.fusedmm_backward(indptr, indices, values, X, G, op=op), "backward " + op)
