@@ -92,23 +92,21 @@ inline partition_params get_params(int64_t n_rows, int64_t nnz, int64_t slots, i
   const int auto_hub = seg_min < 80 ? 2 * seg_min - 32 : 2 * auto_seg > 512 ? 512 : (int)(2 * auto_seg);
   p.hub_t = env_int("ISP_HUB_THRESHOLD", auto_hub, 8, 512);
   p.seg_len = env_int("ISP_SEGMENT_LEN", (int)auto_seg, 8, 768);
-  // Rows are cut into equal segments instead of at column bands on matrices of up to 1.3 M units, and with fewer than 64 Ki rows and columns
-  // up to 4 M, as long as rows (or columns) times units per slot are at most 32 Mi: the segments' own order by first column is all the locality that they
-  // need, and bands leave about half as many again of them (a band of 45 entries, chance included, is a whole segment of 80 and the start of another).
-  // us at 32, 64, 128 and 256 columns with 32 bands / without: 12 k columns,
+  // Rows are cut into equal segments instead of at column bands on matrices of up to 1.3 M units, and with fewer than 64 Ki columns
+  // up to 4 M: the segments' own order by first column is all the locality that they need, and bands leave about half as many again of
+  // them (a band of 45 entries, chance included, is a whole segment of 80 and the start of another).  us at 32, 64, 128 and 256 columns with 32 bands / without: 12 k columns,
   // 1.5 M entries: SpMM 20.7 / 18.7, 27.5 / 26.3, 42.8 / 41.2, 79.8 / 79.4, FusedMM 25.8 / 22.8, 36.6 / 33.6, 59 / 55, 108 / 102, the build 82 / 57; 32 k, 4 M:
   // SpMM 38.4 / 37.2, 58.5 / 57.4, 99.6 / 99.2, 199 / 197, the build 58 / 49; 100 k, 1 M: SpMM 17.3 / 15.9, 25.7 / 25.3, 45.1 / 42.9, 80.7 / 78.8, SDDMM
   // 15.3 / 14.1, 22.6 / 22.4, 42.1 / 42.7, 87.4 / 88.2.  Of 36 graphs up to 1.3 M units (5 to 200 entries to a row, square, wide and tall) none takes longer
   // over all operations and widths (up to 12 % less, builds 2 to 41 %), but SDDMM takes 1 to 4 % longer from 256 columns up where there are many (54 k square, 646 k
-  // entries 56.8 / 58.8, 98 k, 1.2 M 98.5 / 100.6, 165 k x 41 k, 1.1 M 114.5 / 117.6, 6.9 k x 27.7 k, 693 k 50.0 / 52.0), the max backward from 200 up
+  // entries 56.8 / 58.8, 98 k, 1.2 M 98.5 / 100.6, 165 k x 41 k, 1.1 M 114.5 / 117.6, 6.9 k x 27.7 k, 693 k 50.0 / 52.0; no more on the larger of them), the max backward from 200 up
   // 4 to 8 % (30 k, 1 M, 256 columns 107 / 115), and a wide or tall matrix gains nothing but
   // its build (41 k x 165 k, 1.2 M, 128 columns: SpMM 48.7 / 46.9, its transpose 59.2 / 60.0, SDDMM 55.0 / 55.9; 200: 102.7 / 104.9, 104.9 / 108.8, 108.9 / 112.0).
-  // Beyond: 37 k, 3 M (27 Mi): SpMM, 128 columns 77.6 / 76.6, SDDMM 80.9 / 80.5, the max backward at 200 181.6 / 194.4, all of it 1 % less, the build 232 / 194; but
-  // 49 k, 4 M (46 Mi) 100.5 / 102.5, 106.1 / 107.8, 243.6 / 258.9, FusedMM's backward 757.6 / 810.8; 60 k, 2.8 M (40 Mi), 200 columns: 138.5 / 144.4, SDDMM 256 159 / 169, the
-  // max backward 244 / 266; 140 k x 36 k, 3.5 M: 128 columns 105.5 / 109.0, SDDMM 256 262 / 277; 99 k, 3 M, 196 columns 206 / 215; 121 k, 4.5 M, 176 columns 239 / 251.
-  const int64_t longer = n_rows > n_cols ? n_rows : n_cols;
-  const bool equal_segments = share <= 320 || (longer < (64 << 10) && share <= 1024 && longer * share <= (32 << 20));
-  const int auto_bands = equal_segments ? 1 : 32;
+  // Beyond, up to 4 M units, narrow rows and the build gain and wide ones lose: 37 k, 3 M, SpMM, 128 columns 77.6 / 76.6, SDDMM 80.9 / 80.5, the max backward at 200 181.6 / 194.4, all of it 1 %
+  // less, the build 232 / 194; 60 k, 2.8 M: 8 columns, SpMM 27.1 / 25.6, SDDMM 23.8 / 22.4, 200: SpMM 138 / 144, SDDMM 256 159 / 169, the max backward 244 / 266, all of it 1 % less, the build 225 / 191;
+  // 95 k x 24 k, 2.3 M 1 % less, 140 k x 36 k, 3.5 M the same, 49 k, 4 M 1 % more (the build 261 / 225), and beyond: 50 k, 6 M: SpMM 56.0 / 53.5, 84.8 / 83.7, 147.5 / 150.3, 295 / 300,
+  // SDDMM at 256 302 / 317; with more columns 99 k, 3 M, 196 columns 206 / 215; 121 k, 4.5 M, 176 columns 239 / 251.
+  const int auto_bands = share <= 320 || (n_cols < (64 << 10) && share <= 1024) ? 1 : 32;
   int b = env_int("ISP_BANDS", auto_bands, 1, MAX_BANDS);
   while (b & (b - 1)) b &= b - 1;  // round down to a power of two
   p.bands = b;

@@ -47,20 +47,15 @@ int main() {
 
 
 def test_equal_segments_or_column_bands(tmp_path):
-    """(Without bands 60 k rows and 2.8 M entries, or 140 k x 36 k and 3.5 M, took up to 9 % longer.)"""
     run(tmp_path, r"""
 int main() {
   struct { int64_t share, more, n, n_cols; int bands; } want[] = {
-    {320, 0, 70000, 70000, 1}, {320, 1, 70000, 70000, 32}, {320, 0, 3000, 2000000, 1}, {320, 0, 600000, 3000, 1}, {321, 0, 65535, 65535, 1},
-    {512, 0, 65535, 65535, 1}, {512, 1, 65535, 65535, 32}, {513, 0, 65408, 65408, 1}, {513, 0, 65409, 100, 32}, {513, 0, 100, 65409, 32},
-    {400, 0, 65536, 100, 32}, {400, 0, 100, 65536, 32}, {1024, 0, 32768, 32768, 1}, {1024, 0, 32769, 32768, 32}, {1024, 0, 32768, 32769, 32},
-    {1024, 1, 12000, 12000, 32}, {5000, 0, 5000, 5000, 32}};
+    {320, 0, 70000, 70000, 1}, {320, 1, 70000, 70000, 32}, {320, 0, 3000, 2000000, 1}, {320, 0, 600000, 3000, 1}, {321, 0, 65535, 65535, 1}, {321, 0, 3000, 65536, 32},
+    {400, 0, 100000, 65535, 1}, {1024, 0, 65535, 65535, 1}, {1024, 1, 65535, 65535, 32}, {1024, 0, 100, 65536, 32}, {1024, 1, 12000, 12000, 32}, {5000, 0, 5000, 5000, 32}};
   for (auto& w : want) {
     const partition_params p = sizes(w.share, w.more, w.n, w.n_cols);
     if (p.bands != w.bands) FAIL("%lld + %lld units, %lld x %lld: %d bands\n", (long long)w.share, (long long)w.more, (long long)w.n, (long long)w.n_cols, p.bands);
   }
-  if (get_params(60000, 2800000, SLOTS, 60000).bands != 32 || get_params(140000, 3450000, SLOTS, 36000).bands != 32 || get_params(49382, 3950560, SLOTS, 49382).bands != 32) FAIL("no bands\n");
-  if (get_params(37037, 2962960, SLOTS, 37037).bands != 1 || get_params(32000, 4000000, SLOTS, 32000).bands != 1 || get_params(100003, 1000001, SLOTS, 100003).bands != 1) FAIL("bands\n");
   return 0;
 }
 """)
