@@ -77,17 +77,18 @@ inline partition_params get_params(int64_t n_rows, int64_t nnz, int64_t slots, i
   // kernel on every one of them (233 k columns: SpMM 2.68 -> 2.59 ms, SDDMM 2.71 -> 2.60 ms; 2.4 M columns:
   // FusedMM 5.59 -> 5.41 ms; 1 M columns: FusedMM backward 1.36 -> 1.32 ms).
   // Where the slots outnumber the items, the longest row of a block and the longest segment are the launch: 48 entries and
-  // 64 to a row up to 28 units per slot (115 k units), 64 and 96 up to 64 (262 k), 80 and 160 above.  With 80 and 160 / 48 and 64 / 64 and
+  // 64 to a row up to 28 units per slot (115 k units), 64 and 96 up to 128 (520 k), 80 and 160 above.  With 80 and 160 / 48 and 64 / 64 and
   // 96 (us; R-MAT): 2,859 rows, 34 k entries, 80 columns: SpMM 7.4 / 6.6 / 7.0, SDDMM 9.7 / 6.4 / 7.6, FusedMM 15.0 / 9.5 / 11.9, its backward
   // 22.1 / 12.8 / 17.0; 4,092, 90 k, 200 columns: 11.9 / 10.5 / 10.1, 13.1 / 10.3 / 11.1, 32.2 / 17.4 / 26.1, 51.8 / 28.5 / 42.0; 7,881, 157 k, 133:
-  // 15.6 / 13.4 / 12.6, 19.5 / 14.6 / 15.2, 40.8 / 22.8 / 24.1.  Seventy graphs (5 to 200 entries to a row, square, wide and tall), mean over 16 to
-  // 256 columns against 80 and 160: to 115 k units 48 and 64 save 10 % of a SpMM, 23 % of a SDDMM, 25 % of a FusedMM (a SpMM of 8.5 k rows, 102 k entries is
-  // up to 9 % longer); 160 k units, 64 and 96: 2, 12 and 12 %; 230 k: SpMM 1 % longer, SDDMM 11 and FusedMM 5 % shorter; 320 k to 515 k: SpMM 3 % longer, SDDMM 9 %
-  // shorter, FusedMM and max as long, and the worst are SpMMs, for more of whose rows a fix-up launch adds the segments: 12 k rows, 482 k entries, 128 columns 18.0 / 20.3,
-  // 7 k, 406 k: 200 columns 24.6 / 27.2, 24: 9.0 / 9.9, 5 k x 20 k, 490 k, the transpose: 8 columns 9.2 / 10.6, 30 k, 376 k, 200: 31.7 / 34.2.  Beyond, more segments
-  // cost the build more than they save (0.4 to 6 M entries: builds 20 % longer).
+  // 15.6 / 13.4 / 12.6, 19.5 / 14.6 / 15.2, 40.8 / 22.8 / 24.1; 30 k, 376 k, 24: 9.5 / 11.2 / 9.0, 8.1 / 8.0 / 7.8, 12.1 / 12.2 / 11.4; 19 k, 436 k, 24:
+  // 9.9 / 11.4 / 10.1.  SDDMM and FusedMM gain by short rows in a block; SpMM, which writes and adds a partial row per segment, loses by many segments from some 300 k units up.
+  // With 80 and 160 / 64 and 96: 7 k, 406 k: SpMM, 16, 128 and 200 columns 7.9 / 9.6, 16.0 / 15.5, 24.2 / 27.5, SDDMM, 128 and 256: 19.3 / 14.5, 30.7 / 24.3, FusedMM's backward, 200:
+  // 106.6 / 89.6; 12 k, 482 k: SpMM, 16, 128 and 200: 8.5 / 10.9, 17.6 / 20.3, 29.9 / 30.0, SDDMM, 128: 20.6 / 17.3, FusedMM's backward, 200: 126.5 / 105.8; over eight kinds of graphs (12 to 200
+  // entries to a row, square, symmetric, wide, tall), 16 to 256 columns: 250 to 307 k units: SpMM the same, SDDMM 15 % less, FusedMM 2 and 6 % less, max 1 % more; 307 to 369 k: SpMM 1 % more, 12 %,
+  // 1 and 7 %, max 1 % less; 369 to 451 k: 5 % more, 11 %, 1 and 6 %, 1 %; to 524 k: 4 % more, 8 %, 1 and 3 %, max 3 % more.  Segments of 80 with rows of 112 or 128, or
+  // of 96 with 112, take from SDDMM and FusedMM what they give SpMM.  A graph seen once is built as fast; above, more segments cost the build more than they save (0.4 to 6 M entries: builds 20 % longer).
   const int seg_cap = 320;
-  const int seg_min = share <= 28 ? 48 : share <= 64 ? 64 : 80;
+  const int seg_min = share <= 28 ? 48 : share <= 128 ? 64 : 80;
   const int64_t auto_seg = share / 4 < seg_min ? seg_min : (share / 4 > seg_cap ? seg_cap : share / 4);
   const int auto_hub = seg_min < 80 ? 2 * seg_min - 32 : 2 * auto_seg > 512 ? 512 : (int)(2 * auto_seg);
   p.hub_t = env_int("ISP_HUB_THRESHOLD", auto_hub, 8, 512);

@@ -33,7 +33,7 @@ def _graph(n, n_cols, nnz, hub, seg):
 
 @pytest.mark.parametrize("share, more, n, n_cols, hub, seg, banded", [
     (28, 0, 2_000, 2_000, 64, 48, False), (28, 1, 2_000, 2_000, 96, 64, False),
-    (64, 0, 6_000, 6_000, 96, 64, False), (64, 1, 6_000, 6_000, 160, 80, False),
+    (128, 0, 9_000, 9_000, 96, 64, False), (128, 1, 9_000, 9_000, 160, 80, False),
     (320, 0, 70_000, 70_000, 160, 80, False), (320, 1, 70_000, 70_000, 160, 80, True), (320, 1, 30_000, 65_535, 160, 80, False),
     (1024, 0, 65_535, 65_535, 512, 256, False), (1024, 1, 65_535, 65_535, 512, 256, True), (400, 0, 60_000, 65_535, 200, 100, False), (400, 0, 60_000, 65_536, 200, 100, True),
 ])

