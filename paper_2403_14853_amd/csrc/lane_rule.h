@@ -39,7 +39,7 @@ inline bool select_four_lanes(int64_t w, int64_t nnz, int64_t n_hub) { return w 
 // all work lies in hub segments (115 M entries: 3077 / 2764, backward 7697 / 6860).  With as few entries as the chip's wavefronts finish in a few rounds
 // the length of their runs counts, and two it is: beyond 128 columns below 1 Mi entries, beyond 64 below 3/4 Mi - in a directed graph's
 // backward, whose passes take two entries at a time with one vector and have too short a ring for it with two, only with operands that the caches
-// hold (6 MB; from 129 to 160 columns, where two vectors gain most, 48 MB).
+// hold (6 MB; from 129 to 160 columns, where two vectors gain most, 48 MB); in a symmetric pattern's from 512 Ki entries on only with operands of 20 MB, beyond 160 columns 32 MB.
 // us, one (in pairs where the pass has them) / two:
 //   forward: uniform, 7 k rows, 406 k entries: 72 columns 19.7 / 18.0, 144 34.8 / 25.1, 256 35.9 / 30.8; 30 k, 600 k: 26.9 / 26.4, 53.3 / 49.5, 85.9 / 88.4; 50 k, 1 M: 144 102 / 110; R-MAT, 15 k,
 //   600 k: 29.9 / 25.5, 53.4 / 43.9, 54.2 / 49.4; 80 k, 800 k: 36.9 / 36.1, 67.4 / 58.2, 90.5 / 83.5 (100 39.5 / 42.7); 68 k, 1.3 M: 128 60.0 / 59.8, 256 113.6 / 117.9;
@@ -47,12 +47,15 @@ inline bool select_four_lanes(int64_t w, int64_t nnz, int64_t n_hub) { return w 
 //   R-MAT, 3.8 k, 120 k: 128 27.0 / 26.5, 144 44.1 / 41.2; 12 k, 482 k: 72 (3.5) 60.8 / 60.6, 128 (6.1) 61.7 / 63.4, 200 (9.6) 105 / 109; 15 k, 600 k: 144 (8.6) 144 / 131, 256 (15) 156 / 159; 60 k,
 //   600 k: 72 (17) 79.4 / 85.4, 128 92.6 / 101.3, 144 (35) 147 / 144, 256 215 / 233; 80 k, 800 k: 100 (32) 124 / 137, 144 (46) 202 / 195, 256 281 / 300; 150 k, 750 k: 144 (86) 213 / 222; uniform, 60 k,
 //   600 k: 144 (35) 186 / 195;
-//   one pass: R-MAT, 12 k, 482 k: 72 45.0 / 34.6, 128 45.4 / 36.7, 256 77.6 / 71.1; 60 k, 800 k: 144 136 / 122, 256 190 / 195; 100 k, 500 k: 128 75.2 / 69.0, 256 162 / 151; 133 k, 1.04 M: 144
-//   178 / 159, 256 265 / 278; but 60 k, 800 k: 128 78.7 / 84.1, 200 k, 1 M: 128 131 / 151.
+//   one pass: R-MAT, 12 k, 482 k: 72 45.0 / 34.6, 128 45.4 / 36.7, 256 77.6 / 71.1; 15 k, 600 k: 128 (7.7 MB) 60.8 / 52.0, 200 (12) 115 / 99, 256 (15) 117 / 108; 30 k, 600 k, uniform: 128 (15) 83.5 / 82.8, 256 (31)
+//   177 / 169; 60 k, 800 k: 144 136 / 122; 100 k, 500 k: 128 (51) 75.2 / 69.0, 256 (102) 162 / 151; but 60 k, 600 k: 72 (17) 57.5 / 50.7, 100 (24) 58.9 / 64.2, 128 60.9 / 66.0, 200 (48) 125 / 131; 133 k, 1.04 M: 144
+//   178 / 159, 256 265 / 278; 200 k, 1 M: 200 255 / 273.  (Beyond these numbers of entries two would still gain on small operands: 20 k, 900 k: 72 82.4 / 59.5, 128 83.0 / 63.0.)
 // live_rows: rows with entries.
 inline bool fused_two_vectors(fused_pass pass, int64_t d, int64_t n_rows, int64_t live_rows, int64_t nnz) {
   if (live_rows > 0 && nnz >= 200 * live_rows) return true;
-  if (pass == fused_pass::two_pass && n_rows * d > (d > 128 && d <= 160 ? 12 << 20 : 3 << 19)) return false;
+  const bool wide = d > 160, between = d > 128 && !wide;
+  if (pass == fused_pass::two_pass && n_rows * d > (between ? 12 << 20 : 3 << 19)) return false;
+  if (pass == fused_pass::one_pass && !between && nnz >= (512 << 10) && n_rows * d > (wide ? 8 << 20 : 5 << 20)) return false;
   return d > 128 ? nnz < (1 << 20) : d > 64 && nnz < (3 << 18);
 }
 

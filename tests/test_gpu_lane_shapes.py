@@ -53,3 +53,26 @@ def test_against_the_oracle(n, nnz, fused, widths):
             isp.fusedmm_backward(A, dev(X), dev(G), Y)
             assert_close(Y, *oracle.fusedmm_backward(indptr, cols, values, X, G), "fusedmm backward")
     A.destroy()
+
+
+def test_one_pass_backward_on_both_sides_of_an_operand_s_size():
+    """A symmetric pattern of more than 512 Ki entries, whose backward has one vector again beyond 20 MB, from 161 columns up 32 MB."""
+    n = 41_000
+    rng = np.random.default_rng(3)
+    u, v = (n * rng.random((2, 300_000)) ** np.array([[2.0], [1.0]])).astype(np.int64)
+    keys = np.unique(np.concatenate([u * n + v, v * n + u]))
+    indptr = np.concatenate([[0], np.cumsum(np.bincount(keys // n, minlength=n))]).astype(np.int64)
+    indices = (keys % n).astype(np.int32)
+    values = rng.standard_normal(len(keys)).astype(np.float32)
+    A = build(indptr, indices, values)
+    isp.csr_transpose_cached(A)
+    info = A.info()
+    assert info["symmetric_pattern"] == 1 and 512 << 10 <= info["nnz"] < 3 << 18
+    for d in (127, 128, 204, 205):
+        assert (n * d <= (5 << 20 if d <= 128 else 8 << 20)) == (d in (127, 204))
+        X = (0.1 * rng.standard_normal((n, d))).astype(np.float32)
+        G = rng.standard_normal((n, d)).astype(np.float32)
+        Y = torch.full((n, d), float("nan"), device="cuda")
+        isp.fusedmm_backward(A, dev(X), dev(G), Y)
+        assert_close(Y, *oracle.fusedmm_backward(indptr, indices, values, X, G), "d = %d" % d)
+    A.destroy()

@@ -59,6 +59,14 @@ int main() {
     CHECK(fused_two_vectors(p, 40, 233000, 233000, 115000000));  // (rows of 200 entries and more)
     CHECK(fused_two_vectors(p, 128, 12288, 12000, 300000) && fused_two_vectors(p, 128, 12289, 12000, 300000) == (p != fused_pass::two_pass));
   }
+  for (int64_t nnz : {512 * Ki - 1, 512 * Ki}) {
+    const bool few = nnz < 512 * Ki;
+    CHECK(fused_two_vectors(fused_pass::one_pass, 128, 40960, 40000, nnz) && fused_two_vectors(fused_pass::one_pass, 128, 40961, 40000, nnz) == few);  // (5 Mi floats)
+    CHECK(fused_two_vectors(fused_pass::one_pass, 256, 32768, 30000, nnz) && fused_two_vectors(fused_pass::one_pass, 256, 32769, 30000, nnz) == few);  // (8 Mi)
+    CHECK(fused_two_vectors(fused_pass::one_pass, 160, 90000, 80000, nnz) && fused_two_vectors(fused_pass::one_pass, 161, 90000, 80000, nnz) == few);
+    CHECK(fused_two_vectors(fused_pass::forward, 256, 90000, 80000, nnz));
+  }
+  CHECK(!fused_two_vectors(fused_pass::one_pass, 100, 60000, 60000, 600000));  // (58.9 -> 64.2 us with two)
   CHECK(fused_two_vectors(fused_pass::two_pass, 144, 87381, 80000, 800000) && !fused_two_vectors(fused_pass::two_pass, 144, 87382, 80000, 800000));  // (12 Mi floats)
   CHECK(fused_two_vectors(fused_pass::two_pass, 160, 50000, 40000, 800000) && !fused_two_vectors(fused_pass::two_pass, 161, 50000, 40000, 800000));
   CHECK(!fused_two_vectors(fused_pass::two_pass, 100, 60000, 33000, 600000) && !fused_two_vectors(fused_pass::two_pass, 256, 80000, 45000, 800000));  // (90.8 -> 101, 281 -> 300 us with two)
