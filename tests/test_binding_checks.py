@@ -51,6 +51,15 @@ def test_tensors_without_storage_raise(nat, cell):
                 torch.func.vmap(call)(X)
 
 
+def test_release_looks_at_its_arguments(nat, cell):
+    nat.cells_release([cell], [torch.zeros(3), None, object()], None)  # (no call has run on a stream)
+    nat.cells_release([cell, cell], [], cell)
+    for bad in (lambda: nat.cells_release(cell, [], None), lambda: nat.cells_release([cell], (), None), lambda: nat.cells_release([1], [], None),
+                lambda: nat.cells_release([cell], [], 1), lambda: nat.cells_release([cell], []), lambda: nat.cell_ran(cell, "x"), lambda: nat.cell_foreign(None)):
+        with pytest.raises((AssertionError, TypeError, ValueError)):
+            bad()
+
+
 def test_forward_mode_is_refused(nat, cell):
     import torch.autograd.forward_ad as fw
     graph = nat.graph(cell, object(), None)
